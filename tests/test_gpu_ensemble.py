@@ -57,3 +57,22 @@ def test_limits_are_refused():
     ok = torch.zeros((2, 1, 4), dtype=torch.int32, device="cuda")
     with pytest.raises(kge.KgeError):
         kge.ensemble(ok, 0.0)
+
+
+@pytest.mark.parametrize("M,K,K_out,pool,p", [
+    (32, 256, 256, 8192, -1.0),      # 8,192 entries, most of them distinct: the table fills up; more than 256 candidates
+    (32, 256, 32, 8192, 1.0),        # ... the last K_out of the 64-bin bound
+    (33, 65, 33, 140, 1.0),          # lists of one piece and one rank, the first K_out of the 256-bin bound
+    (5, 256, 100, 256, -0.5),        # every model lists the same entities
+    (1, 1, 2, 1, -1.0)])
+def test_table_and_selection_edges(orc, M, K, K_out, pool, p):
+    g = np.random.default_rng(M * 1000 + K)
+    lists = np.stack([[g.permutation(pool)[:K] + 1_000_000 * q for q in range(3)] for _ in range(M)]).astype(np.int32)
+    if pool >= 8192:                                                   # lists that share next to nothing
+        lists = g.permutation(3 * M * K).reshape(M, 3, K).astype(np.int32)
+    if K > 64:                                                         # repeats inside a list: in one piece of 64 ranks, across pieces, many
+        lists[0, 0, 40] = lists[0, 0, 3]
+        lists[M // 2, 1, K - 1] = lists[M // 2, 1, 0]
+        lists[M - 1, 2, 5:] = lists[M - 1, 2, 4]
+        lists[M - 1, 0, 7:60:3] = -1
+    _check(orc, lists, p, K_out)
