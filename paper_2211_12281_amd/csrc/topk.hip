@@ -1,7 +1,8 @@
 // Link prediction (arXiv 2211.12281, Section 3.2 "Inference"): every query is scored against a range of
 // entity rows and the K best are kept.
 //
-//   1. prep      build the queries (Table 2), their norms and rounding residuals, squared norms of the candidates
+//   1. prep      build the queries (Table 2), their norms and rounding residuals (and, for distance scorers with many query
+//                tiles, the squared norms of the candidates; otherwise the scan makes those from its tiles)
 //   2. scan      MFMA scoring of [256 queries] x [candidate tiles]; an accumulator entry that beats the
 //                query's current threshold is appended to the query's candidate buffer (rare after warm-up);
 //                the table is walked in growing chunks, thresholds are refreshed between chunks
@@ -18,7 +19,7 @@
 namespace {
 
 constexpr int TK_ST = 32;               // candidate rows per tile
-constexpr int TK_HALF = 64;             // entries of one private append area
+constexpr int TK_HALF = 64;             // entries of one private append area (TopkPlan::half: fewer where there are 512 splits)
 
 struct TopkArgs {
     const void *Qmat;                   // [Qp][dp] queries (table element type)
@@ -29,13 +30,15 @@ struct TopkArgs {
     int32_t valid_bytes;                // d * sizeof(element)
     int64_t ncand;
     int64_t cand_lo;                    // entity id of candidate 0
-    const float *tn;                    // [ncand rounded up to a tile] MINUS the squared norms of the candidates
+    const float *tn;                    // [ncand rounded up to a tile] MINUS the squared norms of the candidates, or nullptr:
+                                        // the scan makes them itself (kernels with FN)
+    uint32_t *tmax;                     // largest squared norm of a candidate (kernels with FN)
     const float *thr;                   // [Qp] current threshold (local value units)
     const float *vt;                    // [Qp] value of the held-out tail (local units), +inf when absent
     const int32_t *true_t;              // [Q] entity ids, or nullptr
-    uint2 *seg;                         // [Qp][nseg][2][TK_HALF] {value bits, candidate index}: private append
+    uint2 *seg;                         // [Qp][nseg][2][half] {value bits, candidate index}: private append
     int32_t *segcnt;                    // [Qp][nseg][2]           areas of each (query, split, lane half)
-    int32_t nseg;
+    int32_t nseg, half;
     uint32_t *rankcnt;                  // [Qp] candidates whose value beats the held-out tail's
     int32_t nq;                         // number of real queries (rows past it are padding)
     int64_t tile_lo, tile_hi;
@@ -70,7 +73,12 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // consecutive rows at one chunk index then fall into 16 different bank groups (an XOR with row mod 8 reaches half the
 // LDS's rate: half of the LDS's active cycles were bank conflicts).  The MFMAs of tile t+1 are issued before the epilogue of tile t, so the
 // matrix pipe works while the vector ALU filters.
-template <bool BF16, int RB, int KIND, int OB, bool TH = false>
+//
+// FN: the squared norms of the candidates (distance scorers: part of the value; all: their maximum, which the safety check
+// needs) come from the tiles in the LDS instead of a pass of their own over the table.  Every workgroup of a distance scan
+// makes the norms of every tile (a wave those of eight rows), which pays while few query tiles share a candidate tile;
+// the bilinear scan needs only the maximum and gives each candidate tile to one of the query tiles.
+template <bool BF16, int RB, int KIND, int OB, bool TH = false, bool FN = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void topk_scan_kernel(const TopkArgs a) {
     static_assert(!TH || (OB == 2 && KIND == KGE_KIND_DIST), "TransH: one block of queries, one of normals");
@@ -79,7 +87,8 @@ void topk_scan_kernel(const TopkArgs a) {
     constexpr int TILE_BYTES = TK_ST * RB;
     constexpr int NINST = TILE_BYTES / 1024;            // wave-wide 1 KB copies per tile
     constexpr int IPW = NINST / 4;                      // ... per wave
-    constexpr int LPW = IPW + 1;                        // plus the norms
+    constexpr bool SIDE = KIND == KGE_KIND_DIST && !FN; // the norms stream beside the tiles
+    constexpr int LPW = IPW + (SIDE ? 1 : 0);
     constexpr int NSTAGE = RB == 512 ? 4 : 3;
     constexpr int SIDE_SLOTS = NSTAGE + 1;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -161,7 +170,7 @@ void topk_scan_kernel(const TopkArgs a) {
                 async_copy16(gp, lbase + jj * 1024);
             }
         }
-        async_copy4(a.tn + tile * TK_ST + lr, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
+        if constexpr (SIDE) async_copy4(a.tn + tile * TK_ST + lr, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
     };
     // ---- A-fragment addresses: chunk (2 ks + g) of row lr sits at position chunk ^ tk_swz(lr) ----------
     int frag_off[8];
@@ -177,7 +186,7 @@ void topk_scan_kernel(const TopkArgs a) {
         uint4 av[AH > 0 ? AH + 1 : KS];
 #pragma unroll
         for (int ks = 0; ks < (AH > 0 ? AH : KS); ++ks) av[ks] = *(const uint4 *)(base + frag_off[ks & 7] + 256 * (ks >> 3));
-        if constexpr (KIND == KGE_KIND_DIST) {
+        if constexpr (SIDE) {
             // TransE: the accumulators start at -|t|^2 of their candidate row and the queries are stored
             // doubled, so the contraction itself yields 2 q.t - |t|^2
             const char *tside = side_base + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256;
@@ -210,12 +219,50 @@ void topk_scan_kernel(const TopkArgs a) {
         }
     };
 
+    // ---- norms of a tile from its LDS stage: eight lanes per row, 16 bytes per lane and 128-byte piece of the row (an odd row
+    // starts one piece later, so that the two rows of sixteen lanes fall into different halves of the banks) ----
+    float *nrm = (float *)side_base;                    // [2][32] minus the squared norms (even and odd slots)
+    float nmax = 0.f;
+    auto norm_tile = [&](int slot) {
+        const int row = wave * 8 + (lane >> 3);
+        const char *base = lds + (slot % NSTAGE) * TILE_BYTES + row * RB + (lane & 7) * 16;
+        constexpr int NP = RB / 128;
+        float sq = 0.f;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const kge_u32x4 v = *(const kge_u32x4 *)(base + ((i + row) % NP) * 128);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if constexpr (BF16) {
+                    const float x0 = __uint_as_float(v[k] << 16), x1 = __uint_as_float(v[k] & 0xffff0000u);
+                    sq = fmaf(x0, x0, sq); sq = fmaf(x1, x1, sq);
+                } else { const float x0 = __uint_as_float(v[k]); sq = fmaf(x0, x0, sq); }
+            }
+        }
+        sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0xB1, 0xf, 0xf, true));    // lane ^ 1
+        sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0x4E, 0xf, 0xf, true));    // lane ^ 2
+        sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0x141, 0xf, 0xf, true));   // 7 - lane: the other four
+        if constexpr (KIND == KGE_KIND_DIST) if ((lane & 7) == 0) nrm[(slot & 1) * 32 + row] = -sq;
+        nmax = fmaxf(nmax, sq);
+    };
+    int turn = FN && KIND == KGE_KIND_MULT ? (int)(t0 % a.own_tiles) : 0;    // bilinear: the query tile whose turn a candidate tile is
+    auto norms_of = [&](int slot) {
+        if constexpr (FN) {
+            if constexpr (KIND == KGE_KIND_DIST) norm_tile(slot);
+            else {
+                if (turn == own_tile) norm_tile(slot);
+                turn = turn + 1 == a.own_tiles ? 0 : turn + 1;
+            }
+        }
+    };
+
 #pragma unroll
     for (int s2 = 0; s2 < NSTAGE - 1; ++s2) issue(t0 + s2, s2);
     wait_vmcnt<(NSTAGE - 2) * LPW>();
     __syncthreads();
     issue(t0 + NSTAGE - 1, NSTAGE - 1);
     kge_f32x16 acc[OB];
+    norms_of(0);
     mma_tile(0, acc);
 
     for (int64_t tile = t0; tile < t1; ++tile) {
@@ -225,10 +272,20 @@ void topk_scan_kernel(const TopkArgs a) {
         wait_vmcnt<(NSTAGE - 2) * LPW>();
         __syncthreads();
         issue(tile + NSTAGE, slot + NSTAGE);
+        if constexpr (FN) { if (tile + 1 < t1) norms_of(slot + 1); }
         mma_tile(slot + 1, accn);                       // (the last iteration recomputes a stale stage: unused)
         // ---- epilogue of tile `tile`: cheap wave-level test first, the append path only on a hit ----
         const bool tile_full = tile * TK_ST + TK_ST <= a.ncand;
         float vv[NQ][16];                               // the values are the accumulators themselves
+        if constexpr (FN && KIND == KGE_KIND_DIST) {    // (this tile's norms were written before the barrier above)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const kge_f32x4 tn4 = *(const kge_f32x4 *)(nrm + (slot & 1) * 32 + 8 * j + 4 * g);
+#pragma unroll
+                for (int ob = 0; ob < NQ; ++ob)
+                    for (int u = 0; u < 4; ++u) acc[ob][4 * j + u] += tn4[u];
+            }
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             if constexpr (TH) { const float x = acc[1][i] - cq; vv[0][i] = fmaf(x, x, acc[0][i]); }
@@ -264,9 +321,9 @@ void topk_scan_kernel(const TopkArgs a) {
                     if (vv[ob][i] > thr[ob]) {
                         const int64_t cand = tile * TK_ST + 8 * (i >> 2) + 4 * g + (i & 3);
                         // (the area's address is formed here, on the rarely taken path, instead of living in registers)
-                        if (myc[ob] < TK_HALF)
-                            a.seg[(((size_t)qid[ob] * a.nseg + split) * 2 + g) * TK_HALF + myc[ob]] = make_uint2(__float_as_uint(vv[ob][i]), (uint32_t)cand);
-                        ++myc[ob];                      // counts past TK_HALF mark the overflow for the compaction
+                        if (myc[ob] < a.half)
+                            a.seg[(((size_t)qid[ob] * a.nseg + split) * 2 + g) * a.half + myc[ob]] = make_uint2(__float_as_uint(vv[ob][i]), (uint32_t)cand);
+                        ++myc[ob];                      // counts past the area mark the overflow for the compaction
                     }
                 }
             }
@@ -280,6 +337,10 @@ void topk_scan_kernel(const TopkArgs a) {
     if (a.true_t) {
 #pragma unroll
         for (int ob = 0; ob < NQ; ++ob) if (above[ob] && qid[ob] < a.nq) atomicAdd(a.rankcnt + qid[ob], above[ob]);
+    }
+    if constexpr (FN) {
+        nmax = kge_wave_max(nmax);
+        if (lane == 0 && nmax > 0.f) atomicMax(a.tmax, __float_as_uint(nmax));   // (positive: bit order = value order)
     }
 }
 
@@ -295,19 +356,6 @@ __device__ __forceinline__ uint2 unpack_value(uint64_t w) {
     const uint32_t ord = (uint32_t)(w >> 32);
     const uint32_t vbits = ord ^ ((ord >> 31) ? 0x80000000u : 0xFFFFFFFFu);
     return make_uint2(vbits, 0xFFFFFFFFu - (uint32_t)w);
-}
-
-__device__ void bitonic_desc_u64(uint64_t *s, int P) {
-    for (int k = 2; k <= P; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = threadIdx.x; t < P / 2; t += blockDim.x) {
-                const int i = 2 * t - (t & (j - 1)), p = i + j;          // pair (i, i + j)
-                const bool desc = (i & k) == 0;
-                const uint64_t x = s[i], y = s[p];
-                if ((x < y) == desc) { s[i] = y; s[p] = x; }
-            }
-            __syncthreads();
-        }
 }
 
 struct KeyIdx { double key; int idx; };
@@ -327,84 +375,169 @@ __device__ void bitonic_asc_pair(double *key, int *idx, int P) {
         }
 }
 
-// per query: merge the kept list with the fresh append areas, keep the KP best, refresh the threshold.
-// Two launches per chunk.  After the first chunk a query's list is a few KP long, and a workgroup whose LDS holds
-// TK_SORTCAP_SMALL entries leaves room for eight on a compute unit instead of two (the reads of a query's scattered
-// entries and the sort's chain of barriers are all latency: what a compute unit needs is more workgroups): the first launch (cap = TK_SORTCAP_SMALL, redo written) takes the queries whose lists
-// fit and marks the others, the second (cap = TK_SORTCAP, redo read) takes the marked ones.
-constexpr int TK_SORTCAP = 8192;        // entries one workgroup can sort in LDS
-constexpr int TK_SORTCAP_SMALL = 2048;
-__global__ void topk_compact_kernel(uint2 *keep, int32_t *keepcnt, const uint2 *seg, const int32_t *segcnt, int nseg,
-                                    int nsplit, int KP, float *thr, int32_t *flag, int Q, int cap, int32_t *redo, int second) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-    uint64_t *s = (uint64_t *)lds;
-    __shared__ int total, over;
-    const int q = blockIdx.x;
+// Per query: merge the kept list with the fresh append areas, keep the KP best (in no particular order), refresh the threshold.
+// The KP-th key is found by refining a range: a histogram of the keys in it over at most 1,024 bins, the bin that holds the
+// KP-th, again with that bin - two or three rounds as a rule, seven at most, since the keys (value, index) differ - where a
+// sort of the list takes 55 to 91 steps with a barrier each.  All of it is latency, so a compute unit wants many workgroups:
+// the list lives in the LDS up to TK_LISTCAP entries (32 KB; what the first chunk can append to a query, and more than a later
+// one appends as a rule); the appends of a longer one are read again from the areas in every round.
+constexpr int TK_LISTCAP = 4096;
+constexpr int TK_MAXAREAS = 1024;       // 2 nseg at most
+constexpr int TK_BINS = 1024;
+__global__ __launch_bounds__(256) void topk_compact_kernel(uint2 *keep, int32_t *keepcnt, const uint2 *seg, const int32_t *segcnt,
+                                                           int nseg, int half, int nsplit, int KP, float *thr, int32_t *flag, int Q) {
+    __shared__ uint64_t s[TK_LISTCAP];
+    __shared__ int hist[TK_BINS];
+    __shared__ int abase[TK_MAXAREAS + 1];                  // start of every area's entries behind the kept list
+    __shared__ int wsum[4], total_s, over, found, out_n;
+    __shared__ uint64_t wlo[4], whi[4], next_lo, next_hi;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (q >= Q) return;
-    if (second && !redo[q]) return;
     const int kept = keepcnt[q];
-    __shared__ int abase[512 + 1];                          // start of every area's entries in the sort buffer
-    const int nareas = nsplit * 2;                          // <= 2 * nseg <= 512
-    if (threadIdx.x == 0) over = 0;
+    const int nareas = nsplit * 2;                          // <= 2 * nseg <= TK_MAXAREAS
+    if (tid == 0) { over = 0; out_n = 0; }
     __syncthreads();
-    // counts (clamped to the area size), then their exclusive prefix sums behind the kept list: thread t takes the areas
-    // 2 t and 2 t + 1 (256 threads, at most 512 areas), a shuffle scan inside every wave, the waves' sums through the LDS
+    // counts (clamped to the area size), then their exclusive prefix sums behind the kept list: thread t takes four areas
+    // in a row, a shuffle scan inside every wave, the waves' sums through the LDS
     {
-        __shared__ int wsum[4];
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a0 = 2 * threadIdx.x;
-        int c[2];
+        const int a0 = 4 * tid;
+        int c[4], incl = 0;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < 4; ++j) {
             c[j] = a0 + j < nareas ? segcnt[(size_t)q * nseg * 2 + a0 + j] : 0;
-            if (c[j] > TK_HALF) { over = 1; c[j] = TK_HALF; }
+            if (c[j] > half) { over = 1; c[j] = half; }
+            incl += c[j];
         }
-        int incl = c[0] + c[1];
+        const int own = incl;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
         if (lane == 63) wsum[wave] = incl;
         __syncthreads();
-        int start = kept + incl - (c[0] + c[1]);
+        int start = kept + incl - own;
         for (int w = 0; w < wave; ++w) start += wsum[w];
-        if (a0 <= nareas) abase[a0] = start;
-        if (a0 + 1 <= nareas) abase[a0 + 1] = start + c[0];
-        if (a0 + 2 == nareas) abase[a0 + 2] = start + c[0] + c[1];
-        __syncthreads();
-        if (threadIdx.x == 0) total = abase[nareas];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (a0 + j <= nareas) abase[a0 + j] = start;
+            start += c[j];
+        }
+        if (tid == 255) { if (nareas == TK_MAXAREAS) abase[nareas] = start; total_s = start; }
     }
     __syncthreads();
-    if (!second) {                                          // (the same for every thread)
-        const bool fits = total <= cap;
-        if (threadIdx.x == 0) redo[q] = fits ? 0 : 1;
-        if (!fits) return;
+    if (over && tid == 0) flag[q] = 1;                      // entries were dropped: exhaustive re-rank later
+    const int total = total_s;
+    const bool in_lds = total <= TK_LISTCAP;                // (the same for every thread)
+    // entry i >= kept: its area by bisection (four searches, then four loads in flight per thread)
+    auto load4 = [&](int i0, uint64_t (&k)[4]) {
+        int lo[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) lo[u] = 0;
+        for (int step = 512; step > 0; step >>= 1) {
+            if (step >= nareas) continue;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (lo[u] + step < nareas && abase[lo[u] + step] <= i0 + u * 256) lo[u] += step;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * 256;
+            uint2 e = make_uint2(0u, 0u);
+            if (i < total) e = seg[((size_t)q * nseg * 2 + lo[u]) * half + (i - abase[lo[u]])];
+            k[u] = pack_value(e.x, e.y);
+        }
+    };
+    for (int i = tid; i < kept; i += 256) { const uint2 e = keep[(size_t)q * KP + i]; s[i] = pack_value(e.x, e.y); }
+    if (in_lds)
+        for (int i0 = kept + tid; i0 < total; i0 += 1024) {
+            uint64_t k[4];
+            load4(i0, k);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) if (i0 + u * 256 < total) s[i0 + u * 256] = k[u];
+        }
+    __syncthreads();
+    auto walk = [&](auto &&f) {                             // f(key) for every entry of the list
+        const int n = in_lds ? total : kept;
+        for (int i = tid; i < n; i += 256) f(s[i]);
+        if (!in_lds)
+            for (int i0 = kept + tid; i0 < total; i0 += 1024) {
+                uint64_t k[4];
+                load4(i0, k);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) if (i0 + u * 256 < total) f(k[u]);
+            }
+    };
+    uint64_t cut = 0;                                       // keys >= cut stay
+    if (total > KP) {
+        uint64_t mn = ~0ull, mx = 0ull;
+        walk([&](uint64_t k) { mn = k < mn ? k : mn; mx = k > mx ? k : mx; });
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint64_t x = __shfl_xor((unsigned long long)mn, o), y = __shfl_xor((unsigned long long)mx, o);
+            mn = x < mn ? x : mn; mx = y > mx ? y : mx;
+        }
+        if (lane == 0) { wlo[wave] = mn; whi[wave] = mx; }
+        __syncthreads();
+        uint64_t lo = wlo[0], hi = whi[0];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) { lo = wlo[w] < lo ? wlo[w] : lo; hi = whi[w] > hi ? whi[w] : hi; }
+        int need = KP;                                      // taken from the top of [lo, hi]
+        for (;;) {
+            const uint64_t width = hi - lo;
+            const int bits = width ? 64 - __clzll((long long)width) : 0, shift = bits > 10 ? bits - 10 : 0;
+#pragma unroll
+            for (int j = 0; j < TK_BINS / 256; ++j) hist[j * 256 + tid] = 0;
+            __syncthreads();
+            walk([&](uint64_t k) { if (k >= lo && k <= hi) atomicAdd(&hist[(int)((k - lo) >> shift)], 1); });
+            __syncthreads();
+            // thread t holds four bins from the top; its first bin counts behind those of the threads before it
+            const int b0 = TK_BINS - 1 - 4 * tid;
+            int c[4], incl = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { c[j] = hist[b0 - j]; incl += c[j]; }
+            const int own = incl;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
+            if (lane == 63) wsum[wave] = incl;
+            __syncthreads();
+            int before = incl - own;
+            for (int w = 0; w < wave; ++w) before += wsum[w];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (before < need && before + c[j] >= need) {      // (exactly one bin of all)
+                    next_lo = lo + ((uint64_t)(b0 - j) << shift);
+                    next_hi = next_lo + ((1ull << shift) - 1);
+                    found = need - before;                         // taken from this bin
+                    if (c[j] == need - before || shift == 0) found = 0;    // all of it
+                }
+                before += c[j];
+            }
+            __syncthreads();
+            lo = next_lo; hi = next_hi < hi ? next_hi : hi;
+            need = found;
+            if (need == 0) break;
+        }
+        cut = lo;
     }
-    for (int i = threadIdx.x; i < kept; i += blockDim.x) { const uint2 e = keep[(size_t)q * KP + i]; s[i] = pack_value(e.x, e.y); }
-    // every thread copies whole areas (an area holds one or two entries as a rule, 64 at most): the loads of different
-    // threads are independent, so the memory latency is paid once or twice per thread, not once per area of the query
-    // (the order does not matter: the sort below is total)
-    for (int a2 = threadIdx.x; a2 < nareas; a2 += blockDim.x) {
-        const int base = abase[a2], c = abase[a2 + 1] - base;
-        if (c > 0) {
-            if (base + c <= cap) {
-                const uint2 *src = seg + ((size_t)q * nseg * 2 + a2) * TK_HALF;
-                for (int li = 0; li < c; ++li) { const uint2 e = src[li]; s[base + li] = pack_value(e.x, e.y); }
-            } else over = 1;
+    // (the walk reads the kept list from the LDS, so its global copy may be rewritten)
+    uint64_t mn = ~0ull;
+    walk([&](uint64_t k) {
+        if (k >= cut) {
+            keep[(size_t)q * KP + atomicAdd(&out_n, 1)] = unpack_value(k);
+            mn = k < mn ? k : mn;
+        }
+    });
+    if (total >= KP) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) { const uint64_t x = __shfl_xor((unsigned long long)mn, o); mn = x < mn ? x : mn; }
+        __syncthreads();
+        if (lane == 0) wlo[wave] = mn;
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+            for (int w = 1; w < 4; ++w) mn = wlo[w] < mn ? wlo[w] : mn;
+            thr[q] = __uint_as_float(unpack_value(mn).x);
         }
     }
-    __syncthreads();
-    if (over) { if (threadIdx.x == 0) flag[q] = 1; }         // entries were dropped: exhaustive re-rank later
-    int n = total < cap ? total : cap;
-    if (over && total > cap) n = kept;                       // partially filled: keep the old list
-    int P = 2;
-    while (P < n) P <<= 1;
-    for (int i = n + threadIdx.x; i < P; i += blockDim.x) s[i] = 0;   // padding sorts last
-    __syncthreads();
-    bitonic_desc_u64(s, P);
-    const int keepn = n < KP ? n : KP;
-    for (int i = threadIdx.x; i < keepn; i += blockDim.x) keep[(size_t)q * KP + i] = unpack_value(s[i]);
-    if (threadIdx.x == 0) {
-        keepcnt[q] = keepn;
-        if (n >= KP) thr[q] = __uint_as_float(unpack_value(s[KP - 1]).x);
-    }
+    if (tid == 0) keepcnt[q] = total < KP ? total : KP;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -520,12 +653,17 @@ __global__ __launch_bounds__(256) void topk_rescore_kernel(KgeModelDev m, const 
         }
         constexpr int RPI = 64 / DW;                    // rows per wave-wide load
         const int sub = lane / DW, dw = lane % DW;
-        for (int rr = 0; rr < 64; rr += RPI) {
-            const int64_t c = __shfl(cand, rr + sub);
-            uint32_t v = 0u;
-            if (live(dw * E))
-                v = *(const uint32_t *)((const char *)m.ent + (c * m.ent_ld + column(dw * E)) * (BF16 ? 2 : 4));
-            mine[(rr + sub) * (DW + 1) + dw] = v;
+        // (sixteen loads in flight: one after the other, each waits out the memory's latency)
+        for (int r0 = 0; r0 < 64; r0 += 16 * RPI) {
+            uint32_t v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int64_t c = __shfl(cand, r0 + u * RPI + sub);
+                v[u] = 0u;
+                if (live(dw * E)) v[u] = *(const uint32_t *)((const char *)m.ent + (c * m.ent_ld + column(dw * E)) * (BF16 ? 2 : 4));
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) mine[(r0 + u * RPI + sub) * (DW + 1) + dw] = v[u];
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -689,11 +827,17 @@ __global__ void topk_exact_kernel(KgeModelDev m, const int32_t *h, const int32_t
 // ---------------------------------------------------------------------------------------------
 // preparation
 // ---------------------------------------------------------------------------------------------
+// (the launch of the queries also clears the running maximum of the norms and writes the zero bytes of padding columns)
+__device__ __forceinline__ void topk_clear(uint32_t *tmax, uint32_t *zeros) {
+    if (blockIdx.x == 0 && threadIdx.x < 64) { zeros[threadIdx.x] = 0u; if (threadIdx.x == 0) *tmax = 0u; }
+}
+
 // one wave per query: Q row in the table type, value of the held-out tail, rounding-bound coefficients
 template <bool BF16>
 __global__ void topk_prep_kernel(KgeModelDev m, const int32_t *h, const int32_t *r, const int32_t *true_t, int Q,
                                  int Qp, int dp, void *Qm, float *vt, QInfo *qinfo, float *thr, int32_t *cnt,
-                                 int32_t *flag, uint32_t *rankcnt) {
+                                 int32_t *flag, uint32_t *rankcnt, uint32_t *tmax, uint32_t *zeros) {
+    topk_clear(tmax, zeros);
     const int lane = threadIdx.x & 63;
     const int q = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (q >= Qp) return;
@@ -750,7 +894,8 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 template <bool BF16>
 __global__ void topk_prep_th_kernel(KgeModelDev m, const int32_t *h, const int32_t *r, const int32_t *true_t, int Q,
                                     int Qp, int dp, void *Qm, void *Wm, float *cq, double *qx, float *vt, QInfo *qinfo,
-                                    float *thr, int32_t *cnt, int32_t *flag, uint32_t *rankcnt) {
+                                    float *thr, int32_t *cnt, int32_t *flag, uint32_t *rankcnt, uint32_t *tmax, uint32_t *zeros) {
+    topk_clear(tmax, zeros);
     const int lane = threadIdx.x & 63;
     const int q = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (q >= Qp) return;
@@ -870,10 +1015,8 @@ __global__ void topk_fill_empty_kernel(int32_t *out_idx, float *out_score, int64
     if (out_rank && i < Q) out_rank[i] = 1;
 }
 
-__global__ void topk_zero_kernel(uint32_t *p, uint32_t *z) { if (threadIdx.x == 0) *p = 0u; if (threadIdx.x < 64) z[threadIdx.x] = 0u; }
-
 struct TopkPlan {
-    bool bf16, th; int es, rb, dp, ob, own, dim; int Qp; int KP, KPP, nseg; int64_t npad;
+    bool bf16, th, fn; int es, rb, dp, ob, own, dim; int Qp; int KP, KPP, nseg, half; int64_t npad;
 };
 
 TopkPlan make_plan(const kge_model_t &m, int64_t Q, int64_t ncand, int K) {
@@ -881,17 +1024,33 @@ TopkPlan make_plan(const kge_model_t &m, int64_t Q, int64_t ncand, int K) {
     p.bf16 = m.dtype == KGE_BF16; p.es = p.bf16 ? 2 : 4;
     p.rb = m.dim * p.es <= 512 ? 512 : 1024; p.dp = p.rb / p.es;
     p.th = m.scorer == KGE_TRANSH; p.dim = m.dim;
-    p.ob = p.rb == 512 ? 2 : 1; p.own = p.th ? 128 : 128 * p.ob;          // TransH: the second row block holds the normals
+    // Two blocks of 32 queries per wave where the registers allow it (TransH: the second block holds the normals), so that an
+    // LDS fragment feeds two MFMAs.  Up to 512 queries one block: the scan is then bound by the table's bytes and by a round's
+    // latency, tiles of 128 queries pad less, and the registers have room for the norms (TransE, d 256, 2M candidates, one block
+    // against two: 730 / 893 us for 256 queries, 1,059 / 1,218 for 512, 1,850 / 1,781 for 1,024).
+    p.ob = p.rb == 512 && (p.th || Q > 512) ? 2 : 1; p.own = p.th ? 128 : 128 * p.ob;
     p.Qp = (int)kge_round_up(Q, p.own);
     p.KP = (int)kge_round_up(2 * K + 56, 64);
     p.KPP = 1; while (p.KPP < p.KP) p.KPP <<= 1;
-    { int w = 1024 / (p.Qp / p.own); p.nseg = w < 32 ? 32 : (w > 256 ? 256 : w); }
+    // splits of the candidates, each with its append areas: 512 (two workgroups per compute unit: the copies of one run beside
+    // the epilogue of the other) for one or two query tiles, about four turns of the 256 compute units above.  512 splits take
+    // areas of 30 entries instead of 64 unless there is one tile of one block: a workspace is never larger than with 256 splits
+    // of 256 queries, and an area holds as many entries per candidate it covers.
+    const int tiles = p.Qp / p.own;
+    { int w = 1024 / tiles; p.nseg = w < 32 ? 32 : tiles <= 2 ? 512 : (w > 256 ? 256 : w); }
+    p.half = tiles > 2 || (tiles == 1 && p.ob == 1 && p.rb == 512) ? TK_HALF : 30;
+    // Norms inside the scan (FN) or in a pass of their own.  Bilinear: always inside (one query tile's turn per candidate tile:
+    // 9.66 against 10.0 ms for 8,192 queries over 2M rows, 0.64 against 0.92 for 256).  Distance: every query tile makes them
+    // again, so inside while there are few - up to 24 for TransH (1M rows, 8 / 16 tiles: 1.41 / 2.57 inside, 1.62 / 2.72 ms
+    // outside), up to 4 for rows over 512 bytes (4 / 8 / 16 tiles: 1.55 / 2.62 / 4.94 against 1.87 / 2.52 / 4.43); with two
+    // blocks of queries per wave never (the kernel spills 40 registers: 892 against 943 us for one tile, 1,477 against 1,244 for two).
+    p.fn = (m.scorer == KGE_DISTMULT || m.scorer == KGE_COMPLEX) || (p.th ? tiles <= 24 : p.rb == 1024 ? tiles <= 4 : p.ob == 1);
     p.npad = kge_round_up(ncand > 0 ? ncand : 1, TK_ST);
     return p;
 }
 
 struct TopkWs {
-    void *Qm; float *vt, *thr, *tn; QInfo *qinfo; int32_t *cnt, *flag, *redo; uint32_t *rankcnt, *tmax; uint2 *keep, *seg; int32_t *segcnt; double *keyd; uint32_t *zeros;
+    void *Qm; float *vt, *thr, *tn; QInfo *qinfo; int32_t *cnt, *flag; uint32_t *rankcnt, *tmax; uint2 *keep, *seg; int32_t *segcnt; double *keyd; uint32_t *zeros;
     void *Wm; float *cq; double *qx;                    // TransH only
 };
 
@@ -902,11 +1061,10 @@ size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w) {
     w.vt = (float *)take((size_t)p.Qp * 4); w.thr = (float *)take((size_t)p.Qp * 4);
     w.qinfo = (QInfo *)take((size_t)p.Qp * sizeof(QInfo));
     w.cnt = (int32_t *)take((size_t)p.Qp * 4); w.flag = (int32_t *)take((size_t)p.Qp * 4);
-    w.redo = (int32_t *)take((size_t)p.Qp * 4);
     w.rankcnt = (uint32_t *)take((size_t)p.Qp * 4); w.tmax = (uint32_t *)take(256); w.zeros = (uint32_t *)take(256);
-    w.tn = (float *)take((size_t)p.npad * 4);
+    w.tn = p.fn ? nullptr : (float *)take((size_t)p.npad * 4);
     w.keep = (uint2 *)take((size_t)p.Qp * p.KP * 8);
-    w.seg = (uint2 *)take((size_t)p.Qp * p.nseg * 2 * TK_HALF * 8);
+    w.seg = (uint2 *)take((size_t)p.Qp * p.nseg * 2 * p.half * 8);
     w.segcnt = (int32_t *)take((size_t)p.Qp * p.nseg * 2 * 4);
     w.keyd = (double *)take((size_t)p.Qp * p.KP * 8);
     w.Wm = nullptr; w.cq = nullptr; w.qx = nullptr;
@@ -917,14 +1075,29 @@ size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w) {
     return off + 256;
 }
 
-template <bool BF16, int RB, int KIND, int OB, bool TH = false>
+template <bool BF16, int RB, int KIND, int OB, bool TH, bool FN>
 int launch_scan(const TopkArgs &a, int own_tiles, int nsplit, hipStream_t st) {
     constexpr int NSTAGE = RB == 512 ? 4 : 3;
     constexpr int LDS = NSTAGE * TK_ST * RB + (NSTAGE + 1) * 4 * 256;
     static KgeLdsLimit lds_limit;
-    if (lds_limit.set((const void *)topk_scan_kernel<BF16, RB, KIND, OB, TH>, LDS) != KGE_OK) return KGE_E_HIP;
-    hipLaunchKernelGGL((topk_scan_kernel<BF16, RB, KIND, OB, TH>), dim3(own_tiles * ((nsplit + 7) / 8 * 8)), dim3(256), LDS, st, a);
+    if (lds_limit.set((const void *)topk_scan_kernel<BF16, RB, KIND, OB, TH, FN>, LDS) != KGE_OK) return KGE_E_HIP;
+    hipLaunchKernelGGL((topk_scan_kernel<BF16, RB, KIND, OB, TH, FN>), dim3(own_tiles * ((nsplit + 7) / 8 * 8)), dim3(256), LDS, st, a);
     return kge_launch_status();
+}
+
+template <bool BF16>
+int scan(const TopkPlan &p, int kind, const TopkArgs &a, int own_tiles, int nsplit, hipStream_t st) {
+    if (p.th) return p.fn ? launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, true>(a, own_tiles, nsplit, st)
+                          : launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, false>(a, own_tiles, nsplit, st);
+    if (kind == KGE_KIND_MULT) {
+        if (p.rb == 1024) return launch_scan<BF16, 1024, KGE_KIND_MULT, 1, false, true>(a, own_tiles, nsplit, st);
+        return p.ob == 1 ? launch_scan<BF16, 512, KGE_KIND_MULT, 1, false, true>(a, own_tiles, nsplit, st)
+                         : launch_scan<BF16, 512, KGE_KIND_MULT, 2, false, true>(a, own_tiles, nsplit, st);
+    }
+    if (p.rb == 1024) return p.fn ? launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, true>(a, own_tiles, nsplit, st)
+                                  : launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, false>(a, own_tiles, nsplit, st);
+    if (p.ob == 1) return launch_scan<BF16, 512, KGE_KIND_DIST, 1, false, true>(a, own_tiles, nsplit, st);
+    return launch_scan<BF16, 512, KGE_KIND_DIST, 2, false, false>(a, own_tiles, nsplit, st);
 }
 
 }  // namespace
@@ -959,24 +1132,23 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     if (stride * TK_ST >= (1ll << 32)) return KGE_E_UNSUPPORTED;     // the scan advances its sources by a 32-bit step per tile
     const int kind = (model.scorer == KGE_DISTMULT || model.scorer == KGE_COMPLEX) ? KGE_KIND_MULT : KGE_KIND_DIST;
 
-    hipLaunchKernelGGL(topk_zero_kernel, dim3(1), dim3(64), 0, st, w.tmax, w.zeros);
     if (p.th) {
-        if (p.bf16) hipLaunchKernelGGL(topk_prep_th_kernel<true>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.Wm, w.cq, w.qx, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt);
-        else hipLaunchKernelGGL(topk_prep_th_kernel<false>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.Wm, w.cq, w.qx, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt);
+        if (p.bf16) hipLaunchKernelGGL(topk_prep_th_kernel<true>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.Wm, w.cq, w.qx, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt, w.tmax, w.zeros);
+        else hipLaunchKernelGGL(topk_prep_th_kernel<false>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.Wm, w.cq, w.qx, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt, w.tmax, w.zeros);
     }
     if (p.bf16) {
-        if (!p.th) hipLaunchKernelGGL(topk_prep_kernel<true>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt);
-        hipLaunchKernelGGL(topk_tnorm_kernel<true>, dim3((unsigned)(p.npad / 4 < 8192 ? (p.npad + 3) / 4 : 8192)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
+        if (!p.th) hipLaunchKernelGGL(topk_prep_kernel<true>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt, w.tmax, w.zeros);
+        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel<true>, dim3((unsigned)(p.npad / 4 < 8192 ? (p.npad + 3) / 4 : 8192)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
     } else {
-        if (!p.th) hipLaunchKernelGGL(topk_prep_kernel<false>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt);
-        hipLaunchKernelGGL(topk_tnorm_kernel<false>, dim3((unsigned)(p.npad / 4 < 8192 ? (p.npad + 3) / 4 : 8192)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
+        if (!p.th) hipLaunchKernelGGL(topk_prep_kernel<false>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt, w.tmax, w.zeros);
+        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel<false>, dim3((unsigned)(p.npad / 4 < 8192 ? (p.npad + 3) / 4 : 8192)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
     }
     if (hipGetLastError() != hipSuccess) return KGE_E_HIP;
 
     TopkArgs base{};
     base.Qmat = w.Qm; base.Wmat = w.Wm; base.cq = w.cq; base.ent = cand0; base.ent_stride = stride; base.valid_bytes = model.dim * p.es;
-    base.ncand = ncand; base.cand_lo = lo; base.tn = w.tn; base.thr = w.thr; base.vt = w.vt; base.true_t = true_t;
-    base.seg = w.seg; base.segcnt = w.segcnt; base.nseg = p.nseg; base.rankcnt = w.rankcnt; base.nq = (int)Q; base.zeros = w.zeros;
+    base.ncand = ncand; base.cand_lo = lo; base.tn = w.tn; base.tmax = w.tmax; base.thr = w.thr; base.vt = w.vt; base.true_t = true_t;
+    base.seg = w.seg; base.segcnt = w.segcnt; base.nseg = p.nseg; base.half = p.half; base.rankcnt = w.rankcnt; base.nq = (int)Q; base.zeros = w.zeros;
     const int own_tiles = p.Qp / p.own;
     const int64_t total_tiles = p.npad / TK_ST;
     // Growing chunks: thresholds are refreshed between chunks.  The first chunk appends everything (64
@@ -984,9 +1156,6 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     // been seen, so a query with a well-mixed candidate order appends about 3 KP entries per chunk,
     // spread over nsplit x 2 private areas of TK_HALF entries.
     int64_t seen = 0;
-    const int compact_lds = TK_SORTCAP * 8;
-    static KgeLdsLimit compact_limit;
-    if (compact_limit.set((const void *)topk_compact_kernel, compact_lds) != KGE_OK) return KGE_E_HIP;
     while (seen < total_tiles) {
         int64_t tiles = seen == 0 ? (p.nseg * (TK_HALF / TK_ST) < 128 ? p.nseg * (TK_HALF / TK_ST) : 128) : 3 * seen;
         if (tiles > total_tiles - seen) tiles = total_tiles - seen;
@@ -999,20 +1168,13 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
         int rc;
         {
             KgeProfScope prof(KGE_PROF_TOPK_SCAN, st);
-            if (p.th) rc = p.bf16 ? launch_scan<true, 512, KGE_KIND_DIST, 2, true>(c, own_tiles, nsplit, st)
-                                  : launch_scan<false, 512, KGE_KIND_DIST, 2, true>(c, own_tiles, nsplit, st);
-            else if (p.bf16 && p.rb == 512) rc = kind == KGE_KIND_MULT ? launch_scan<true, 512, KGE_KIND_MULT, 2>(c, own_tiles, nsplit, st) : launch_scan<true, 512, KGE_KIND_DIST, 2>(c, own_tiles, nsplit, st);
-            else if (p.bf16) rc = kind == KGE_KIND_MULT ? launch_scan<true, 1024, KGE_KIND_MULT, 1>(c, own_tiles, nsplit, st) : launch_scan<true, 1024, KGE_KIND_DIST, 1>(c, own_tiles, nsplit, st);
-            else if (p.rb == 512) rc = kind == KGE_KIND_MULT ? launch_scan<false, 512, KGE_KIND_MULT, 2>(c, own_tiles, nsplit, st) : launch_scan<false, 512, KGE_KIND_DIST, 2>(c, own_tiles, nsplit, st);
-            else rc = kind == KGE_KIND_MULT ? launch_scan<false, 1024, KGE_KIND_MULT, 1>(c, own_tiles, nsplit, st) : launch_scan<false, 1024, KGE_KIND_DIST, 1>(c, own_tiles, nsplit, st);
+            rc = p.bf16 ? scan<true>(p, kind, c, own_tiles, nsplit, st) : scan<false>(p, kind, c, own_tiles, nsplit, st);
         }
         if (rc != KGE_OK) return rc;
         seen += tiles;
         const int areas_of = (nsplit + 7) / 8 * 8 < p.nseg ? (nsplit + 7) / 8 * 8 : p.nseg;
-        hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)Q), dim3(256), TK_SORTCAP_SMALL * 8, st, w.keep, w.cnt, w.seg, w.segcnt,
-                           p.nseg, areas_of, p.KP, w.thr, w.flag, (int)Q, TK_SORTCAP_SMALL, w.redo, 0);
-        hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)Q), dim3(256), compact_lds, st, w.keep, w.cnt, w.seg, w.segcnt,
-                           p.nseg, areas_of, p.KP, w.thr, w.flag, (int)Q, TK_SORTCAP, w.redo, 1);
+        hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)Q), dim3(256), 0, st, w.keep, w.cnt, w.seg, w.segcnt, p.nseg, p.half, areas_of,
+                           p.KP, w.thr, w.flag, (int)Q);
     }
     const int64_t nres = Q * p.KP;
     const int final_lds = p.KPP * 12;

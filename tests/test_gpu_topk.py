@@ -71,6 +71,31 @@ def test_many_candidates_several_chunks(orc, scorer, bf16, dim):
     _check(orc, scorer, G, bf16, 0, 60000, 100, true_t)
 
 
+@pytest.mark.parametrize("scorer,bf16,dim,Q", [
+    ("transe", True, 256, 128), ("transe", True, 208, 129), ("rotate", False, 128, 512), ("transe", True, 256, 513),
+    ("distmult", True, 256, 512), ("complex", False, 64, 513),        # one / two blocks of queries per wave
+    ("transe", True, 512, 512), ("rotate", False, 256, 513),          # rows over 512 bytes: norms inside / outside the scan
+    ("distmult", True, 400, 130),
+    ("transh", True, 64, 3072), ("transh", False, 32, 3073)])         # ... TransH
+def test_query_counts_around_the_scan_variants(orc, scorer, bf16, dim, Q):
+    n = 2000 if Q > 1000 else 5003                                     # (two chunks and a ragged last tile)
+    G = make_case(scorer, n, 7, dim, Q, 0, bf16)
+    _check(orc, scorer, G, bf16, 1, n, 20, ks.uniform_ids(ks.rng(4, ks.TAG_HELDOUT), 0, n, Q))
+
+
+def test_long_lists_of_appends(orc):
+    """Scores that rise with the id: every candidate of a chunk beats the threshold, so a query's list outgrows the LDS while
+    no append area overflows; with K = 256 and repeated rows, whose values tie at the cut."""
+    G = make_case("distmult", 16384, 3, 32, 5, 0, False)
+    G["rel"][:] = np.abs(G["rel"]) + 0.01
+    G["ent"] = np.abs(G["ent"]) * np.linspace(0.1, 3.0, 16384).astype(np.float32)[:, None]
+    G["ent"] = G["ent"][np.argsort(G["ent"].astype(np.float64).sum(1))].astype(np.float32)
+    G["ent"][9000:9400] = G["ent"][9000]
+    G["ent"][15000:16384] = G["ent"][15000]
+    _check(orc, "distmult", G, False, 0, 16384, 256, np.array([15500, 3, 9100, 16383, 0], dtype=np.int32))
+    _check(orc, "distmult", G, False, 0, 9300, 200, None)
+
+
 def test_ties_sub_ranges_and_padding(orc):
     G = make_case("distmult", 3000, 5, 32, 10, 0, False)
     for dst, src in [(1500, 3), (77, 3), (2999, 120), (10, 120), (5, 6)]:
