@@ -141,8 +141,8 @@ int kge_score(const kge_model_t *model, const int32_t *h, const int32_t *r, cons
               size_t ws_bytes, void *hip_stream);
 
 /*
- * Forward + backward of one micro-batch (losses of Section 3.1; the shared negative block is
- * never written to memory):
+ * Forward + backward of one micro-batch (losses of Section 3.1; the fp32 scores of the shared negative
+ * block are written to the workspace for small blocks only, up to a few million pairs):
  *   loss_out      float[1]           loss_scale * sum_b L_b + reg_l3 * Omega_S
  *   g_ent         float[(2B+N) * d]  gradient rows, one per gathered entity slot, in the order
  *                                    heads (B), positive tails (B), shared negatives (N);
@@ -487,10 +487,12 @@ int kge_calibrate_copy(const void *src, void *dst, size_t bytes, double *gbs_out
  *                             whose scores outgrow the fixed reference exponent of the default kernel)
  *   KGE_DEBUG_GRADT_RECOMPUTE the pass over the negatives recomputes the scores also where the forward pass has kept its
  *                             weights for it (sampled softmax, bilinear scorers, bf16 rows of 512 bytes)
+ *   KGE_DEBUG_BLOCK_PASSES    the passes of kge_loss_bwd on the block kernels also for small blocks, whose scores the library
+ *                             writes to the workspace (each of the four knobs above that names a pass selects this as well)
  * Returns KGE_E_INVALID_ARG for an unknown knob or a value other than 0 / 1.
  */
 enum { KGE_DEBUG_FWD_ONE_ROLE = 0, KGE_DEBUG_GRADT_ONE_ROLE = 1, KGE_DEBUG_SCORE_F32_MFMA = 2, KGE_DEBUG_TWO_ROLE = 3,
-       KGE_DEBUG_GRADT_RECOMPUTE = 4 };
+       KGE_DEBUG_GRADT_RECOMPUTE = 4, KGE_DEBUG_BLOCK_PASSES = 5 };
 int kge_debug_select(int knob, int value);
 
 /* Static description of a status code. */

@@ -411,7 +411,8 @@ def ensemble(lists, p: float, K_out: int = 10):
     return out_idx, out_score
 
 
-DEBUG_KNOBS = {"fwd_one_role": 0, "gradt_one_role": 1, "score_f32_mfma": 2, "two_role": 3, "gradt_recompute": 4}
+DEBUG_KNOBS = {"fwd_one_role": 0, "gradt_one_role": 1, "score_f32_mfma": 2, "two_role": 3, "gradt_recompute": 4,
+               "block_passes": 5}
 
 
 def debug_select(knob: str, value: bool):

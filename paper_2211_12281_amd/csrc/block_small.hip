@@ -1,0 +1,403 @@
+// Both passes of kge_loss_bwd for small blocks (2-norm and bilinear scorers, all but TransH): the score block is written to memory.
+//
+// A micro-batch of a few hundred triples and negatives (Table 3 trains with B 256-640, N 256-1,536) leaves the chip idle: the
+// block kernels own 128 rows per workgroup, so the streamed operand is cut into one or two tiles per workgroup, and what a pass
+// takes is not its contractions but the fixed part of a workgroup, the split partials it writes (128 rows x d fp32 each, 20-30 MB
+// for any batch) and the reads of dozens of partials per row in the chain rule.  While B x N fp32 scores stay in the L2 the job
+// is better cut differently:
+//   scores      S[b, n], one 32 x 32 tile per wave, operands straight from memory (both are contiguous along d)
+//   rows        one workgroup per query: loss, gradient of the positive score and the coefficients C[b, n] = dL/dS[b, n] (distance
+//               scorers: over the distance) from its row of S; once per pair - made from S and a row constant by every workgroup of
+//               the gradients, the exponentials bound that launch (26 us instead of 19 for the RotatE case below)
+//   gradients   one launch for both operands: dQ = C T and dT = C^t Q; a workgroup makes 32 rows x 64 or 128 columns, its eight waves
+//               share out the contraction index and add up through the LDS, so that there are no partials in memory
+// (kge_loss_bwd, block kernels / here: RotatE fp32, B 448, N 1,088, d 256: 108 / 55 us; ComplEx bf16, B 640, N 1,536, d 400: 110 / 43 us;
+// the launches of the first: gather 7.6, scores 13.5, rows 5.2, gradients 19, chain rule 10 us.)
+// What bounds each launch is its latency: start-up, two or three dependent loads and the matrix instructions of one wave.
+// Arithmetic as in the block kernels: bf16 operands with fp32 accumulation, or three bf16 pieces per fp32 value.
+#include "block_kernel.hpp"
+#include "prep_kernels.h"
+#include "row_finish.hpp"
+
+namespace {
+
+constexpr int SMALL_AHEAD = 2;         // matrix steps of the gradients in flight (3 and 4: the same time, 1-4 % slower on long contractions)
+
+struct SmallArgs {
+    const void *Q, *T;                 // [Bp][dp] queries, [Np][dp] negatives (rows past B, N and columns past d are zero)
+    const KgeRowInfo *rowinfo;         // [Bp]
+    const float *tn;                   // [Np] squared norms of the negatives
+    float *S; int64_t ldS;             // [Bp][ldS] scores (written for b < B, n < N only)
+    const void *C;                     // [Bp][ldS] coefficients in the table type (zero behind the block up to a multiple of 32)
+    int32_t B, N, Bp, Np, dp, dim;
+    float *accq, *acct;                // [q_splits][Bp][dp], [t_splits][Np][dp] gradient rows (columns < dim rounded up to a tile)
+    float4 *sumt;                      // [t_splits][Np] {sum of the coefficients of the column, 0, 0, 0}: distance scorers
+    int32_t q_blocks, d_tiles;         // gradient launch: workgroups of the queries' part, column tiles
+    int32_t q_splits, t_splits, q_steps, t_steps;   // ... splits of the contraction index, matrix steps of sixteen per split
+};
+
+// eight consecutive values of a row as one operand of a 16-deep matrix step: a bf16 fragment or three bf16 pieces
+template <bool BF16> struct Frag;
+template <> struct Frag<true> { uint4 v; };
+template <> struct Frag<false> { KgeP3 v; };
+template <bool BF16> __device__ __forceinline__ kge_f32x16 small_mma(kge_f32x16 acc, const Frag<BF16> &a, const Frag<BF16> &b) {
+    if constexpr (BF16) return kge_mma16<true>(acc, a.v, b.v);
+    else return kge_mma3(acc, a.v, b.v);
+}
+
+// ---- scores: workgroup = 64 queries x 64 negatives, wave = 32 x 32 ----
+template <bool BF16, int KIND>
+__global__ __launch_bounds__(256) void small_score_kernel(const SmallArgs a) {
+    constexpr int ES = BF16 ? 2 : 4, U = BF16 ? 16 : 8;         // matrix steps (16 columns) requested together
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, g = lane >> 5;
+    const int b0 = blockIdx.y * 64 + (wave >> 1) * 32, n0 = blockIdx.x * 64 + (wave & 1) * 32;
+    if (b0 >= a.B || n0 >= a.N) return;
+    const char *pq = (const char *)a.Q + ((size_t)(b0 + lr) * a.dp + 8 * g) * ES;
+    const char *pt = (const char *)a.T + ((size_t)(n0 + lr) * a.dp + 8 * g) * ES;
+    kge_f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    const int steps = (a.dim + 15) / 16;                        // (rounded up to U: dp is a multiple of 256 (bf16) or 128 columns, zero past d)
+    for (int s = 0; s < steps; s += U) {
+        uint4 q[U][ES / 2], t[U][ES / 2];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < ES / 2; ++e) {
+                q[u][e] = *(const uint4 *)(pq + (s + u) * 16 * ES + e * 16);
+                t[u][e] = *(const uint4 *)(pt + (s + u) * 16 * ES + e * 16);
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            Frag<BF16> fq, ft;
+            if constexpr (BF16) { fq.v = q[u][0]; ft.v = t[u][0]; }
+            else { fq.v = kge_split3(q[u][0], q[u][1]); ft.v = kge_split3(t[u][0], t[u][1]); }
+            acc = small_mma<BF16>(acc, fq, ft);
+        }
+    }
+    // lane = negative n0 + lr; register i = query b0 + 8 (i / 4) + 4 g + i % 4
+    const int n = n0 + lr;
+    float sv[16];
+    if constexpr (KIND == KGE_KIND_MULT) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sv[i] = acc[i];
+    } else {
+        // |q|^2 + |t|^2 - 2 q.t; entries where it cancels (below 1e-3 of the norms) by direct differences
+        const float tn = a.tn[n];
+        float d2[16], thr[16];
+        bool cancel = false;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float qn = a.rowinfo[b0 + 8 * (i >> 2) + 4 * g + (i & 3)].qn;
+            d2[i] = fmaf(-2.f, acc[i], qn + tn);
+            thr[i] = 1e-3f * (qn + tn);
+            cancel = cancel || d2[i] < thr[i];
+        }
+        if (__any(cancel)) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (d2[i] < thr[i])
+                    d2[i] = kge_direct_d2<BF16, false>((const char *)a.Q + (size_t)(b0 + 8 * (i >> 2) + 4 * g + (i & 3)) * a.dp * ES,
+                                                       (const char *)a.T + (size_t)n * a.dp * ES, nullptr, a.dp);
+                asm volatile("" ::: "memory");                  // keeps the branch from being turned into selects
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float dd = fmaxf(d2[i], 0.f);
+            sv[i] = dd > 0.f ? -dd * __builtin_amdgcn_rsqf(dd) : 0.f;
+        }
+    }
+    if (n < a.N) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int b = b0 + 8 * (i >> 2) + 4 * g + (i & 3);
+            if (b < a.B) a.S[(size_t)b * a.ldS + n] = sv[i];
+        }
+    }
+}
+
+// ---- gradients: workgroup = 32 own rows x CT columns, eight waves share the split's part of the contraction index ----
+// A lane's columns are CT / 32 neighbours (one load per streamed row), column h of every lane is block h of the matrix product.
+template <bool BF16, int KIND, bool OWN_Q, int CT>
+__device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile, int d_tile, int split, float *lds) {
+    constexpr int NB = CT / 32;                                 // columns per lane, column blocks
+    constexpr int ES = BF16 ? 2 : 4, XW = NB * ES / 4;          // 32-bit words of a lane's columns
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, g = lane >> 5;
+    const int o = own_tile * 32 + lr;                           // own row of the lane's coefficients
+    const int str_n = OWN_Q ? a.N : a.B;
+    const int dcol = d_tile * CT + NB * lr;
+    const char *X = (const char *)(OWN_Q ? a.T : a.Q) + (size_t)dcol * ES;
+    const size_t xrow = (size_t)a.dp * ES, crow = (size_t)a.ldS * ES;
+    const char *Cp = (const char *)a.C + (OWN_Q ? (size_t)o * crow : (size_t)o * ES);
+    kge_f32x16 acc[NB];
+#pragma unroll
+    for (int h = 0; h < NB; ++h) for (int i = 0; i < 16; ++i) acc[h][i] = 0.f;
+    float csum = 0.f;
+    const int steps = (str_n + 15) / 16, per_split = OWN_Q ? a.q_steps : a.t_steps;
+    const int s0 = split * per_split, s1 = min(steps, s0 + per_split), per = (s1 - s0 + 7) / 8;
+    const int s_lo = s0 + wave * per, s_hi = min(s1, s_lo + per);
+    // raw operands of a step: the lane's eight streamed rows (rows and columns behind the block: zero coefficients, zero rows)
+    struct Raw { uint32_t c[OWN_Q ? 2 * ES : 8], x[8][XW]; };
+    auto load = [&](int s, Raw &r) {
+        const int k0 = s * 16 + 8 * g;
+        if constexpr (OWN_Q) {                                  // (rows of C start 16-byte aligned)
+#pragma unroll
+            for (int e = 0; e < ES / 2; ++e) {
+                const uint4 v = *(const uint4 *)(Cp + (size_t)k0 * ES + e * 16);
+                r.c[4 * e] = v.x; r.c[4 * e + 1] = v.y; r.c[4 * e + 2] = v.z; r.c[4 * e + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if constexpr (BF16) r.c[j] = *(const uint16_t *)(Cp + (size_t)(k0 + j) * crow);
+                else r.c[j] = *(const uint32_t *)(Cp + (size_t)(k0 + j) * crow);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const char *p = X + (size_t)(k0 + j) * xrow;
+            if constexpr (XW == 1) r.x[j][0] = *(const uint32_t *)p;
+            else if constexpr (XW == 2) { const uint2 v = *(const uint2 *)p; r.x[j][0] = v.x; r.x[j][1] = v.y; }
+            else { const uint4 v = *(const uint4 *)p; r.x[j][0] = v.x; r.x[j][1] = v.y; r.x[j][2] = v.z; r.x[j][3] = v.w; }
+        }
+    };
+    auto step = [&](const Raw &r) {
+        Frag<BF16> fc;
+        if constexpr (BF16) {
+            if constexpr (OWN_Q) fc.v = make_uint4(r.c[0], r.c[1], r.c[2], r.c[3]);
+            else fc.v = make_uint4(r.c[0] | (r.c[1] << 16), r.c[2] | (r.c[3] << 16), r.c[4] | (r.c[5] << 16), r.c[6] | (r.c[7] << 16));
+        } else fc.v = kge_split3(make_uint4(r.c[0], r.c[1], r.c[2], r.c[3]), make_uint4(r.c[4], r.c[5], r.c[6], r.c[7]));
+        if constexpr (!OWN_Q && KIND == KGE_KIND_DIST) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) csum += __uint_as_float(BF16 ? r.c[j] << 16 : r.c[j]);
+        }
+#pragma unroll
+        for (int h = 0; h < NB; ++h) {
+            Frag<BF16> f;
+            if constexpr (BF16) {                               // column h of the eight streamed rows, two rows per word
+                uint32_t w[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t x0 = r.x[2 * j][h >> 1], x1 = r.x[2 * j + 1][h >> 1];
+                    w[j] = h & 1 ? (x0 >> 16) | (x1 & 0xffff0000u) : (x0 & 0xffffu) | (x1 << 16);
+                }
+                f.v = make_uint4(w[0], w[1], w[2], w[3]);
+            } else
+                f.v = kge_split3(make_uint4(r.x[0][h], r.x[1][h], r.x[2][h], r.x[3][h]), make_uint4(r.x[4][h], r.x[5][h], r.x[6][h], r.x[7][h]));
+            acc[h] = small_mma<BF16>(acc[h], fc, f);
+        }
+    };
+    if (s_lo < s_hi) {                                          // (the next AH - 1 steps are requested before this one is used)
+        constexpr int AH = SMALL_AHEAD;
+        Raw r[AH];
+#pragma unroll
+        for (int u = 0; u < AH - 1; ++u) load(min(s_lo + u, s_hi - 1), r[u]);
+        for (int s = s_lo; s < s_hi; s += AH) {
+#pragma unroll
+            for (int u = 0; u < AH; ++u) {
+                if (s + u < s_hi) {
+                    load(min(s + u + AH - 1, s_hi - 1), r[(u + AH - 1) % AH]);
+                    step(r[u]);
+                }
+            }
+        }
+    }
+    // Register i of acc[h]: own row 8 (i / 4) + 4 g + i % 4, column NB lr + h.  The upper four waves hand theirs to the lower four,
+    // those add up in wave order.
+    float *mine = lds + (wave & 3) * 32 * CT;
+    auto at = [&](int i) { return mine + (8 * (i >> 2) + 4 * g + (i & 3)) * CT + NB * lr; };
+    float *csums = lds + 4 * 32 * CT;
+    if constexpr (!OWN_Q && KIND == KGE_KIND_DIST) {
+        csum += __shfl_xor(csum, 32);
+        if (g == 0) csums[wave * 32 + lr] = csum;
+    }
+    if (wave >= 4) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int h = 0; h < NB; h += 2) *(float2 *)(at(i) + h) = make_float2(acc[h][i], acc[h + 1][i]);
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int h = 0; h < NB; h += 2) {
+                const float2 v = *(const float2 *)(at(i) + h);
+                *(float2 *)(at(i) + h) = make_float2(acc[h][i] + v.x, acc[h + 1][i] + v.y);
+            }
+    }
+    __syncthreads();
+    float *out = (OWN_Q ? a.accq : a.acct) + (size_t)split * (OWN_Q ? a.Bp : a.Np) * a.dp;
+#pragma unroll
+    for (int e = 0; e < CT / 64; ++e) {
+        const int i = (e * 512 + threadIdx.x) * 4;
+        kge_f32x4 v = *(const kge_f32x4 *)(lds + i);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += *(const kge_f32x4 *)(lds + w * 32 * CT + i);
+        *(kge_f32x4 *)(out + (size_t)(own_tile * 32 + i / CT) * a.dp + d_tile * CT + i % CT) = v;
+    }
+    if constexpr (!OWN_Q && KIND == KGE_KIND_DIST)
+        if (d_tile == 0 && threadIdx.x < 32) {
+            float t = csums[threadIdx.x];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) t += csums[w * 32 + threadIdx.x];
+            a.sumt[(size_t)split * a.Np + own_tile * 32 + threadIdx.x] = make_float4(t, 0.f, 0.f, 0.f);
+        }
+}
+
+template <bool BF16, int KIND, int CT>
+__global__ __launch_bounds__(512) void small_grad_kernel(const SmallArgs a) {
+    __shared__ __attribute__((aligned(16))) float lds[4 * 32 * CT + 8 * 32];
+    // (workgroups go to the eight dies in turn: the column tiles and splits of an own tile, which read the same rows of C or X, stay together)
+    int blk = blockIdx.x;
+    const bool q = blk < a.q_blocks;
+    if (!q) blk -= a.q_blocks;
+    const int splits = q ? a.q_splits : a.t_splits, inner = a.d_tiles * splits;
+    const int kk = blk >> 3, own = (kk / inner) * 8 + (blk & 7), d_tile = kk % inner % a.d_tiles, split = kk % inner / a.d_tiles;
+    if (own * 32 >= (q ? a.B : a.N)) return;
+    if (q) small_grad_body<BF16, KIND, true, CT>(a, own, d_tile, split, lds);
+    else small_grad_body<BF16, KIND, false, CT>(a, own, d_tile, split, lds);
+}
+
+// ---- rows: loss statistics of a row of S and their finish, one workgroup per query (rows past B get what kge_rowfinish_kernel gives
+// them); with C the row's coefficients in the table type (C of fp32 tables may be S itself: a thread overwrites what it has read) ----
+struct SmallRowsArgs {
+    const float *S; int64_t ldS; int B, N, Bp; int loss; float gamma, adv_temp, c_corr, scale; const float *pos; KgeRowInfo *rowinfo;
+    float *lossb, *gpos; void *C; int bf16, dist; float4 *sumq; int q_splits;
+};
+__global__ __launch_bounds__(256) void small_rows_kernel(const SmallRowsArgs a) {
+    __shared__ float red[4][4], Kb;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N, loss = a.loss;
+    const int npad = (N + 31) / 32 * 32;
+    auto put = [&](int n, float c) {
+        if (a.bf16) ((__bf16 *)a.C)[(size_t)b * a.ldS + n] = (__bf16)c;
+        else ((float *)a.C)[(size_t)b * a.ldS + n] = c;
+    };
+    if (b >= a.B) {
+        if (tid == 0) { a.lossb[b] = 0.f; a.gpos[b] = 0.f; a.rowinfo[b].K = -INFINITY; }
+        if (a.C && b < (a.B + 31) / 32 * 32) for (int n = tid; n < npad; n += 256) put(n, 0.f);
+        return;
+    }
+    const float xscale = (loss == KGE_LOGSIGMOID ? a.adv_temp : 1.f) * KGE_LOG2E;
+    const float *row = a.S + (size_t)b * a.ldS;
+    constexpr int R = 8;                                        // scores that a thread keeps (2,048 negatives)
+    float v[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) { const int n = tid + 256 * j; v[j] = n < N ? row[n] : -INFINITY; }
+    const float fp = a.pos[b];
+    float m = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < R; ++j) m = fmaxf(m, tid + 256 * j < N ? v[j] * xscale : -INFINITY);
+    for (int n = tid + 256 * R; n < N; n += 256) m = fmaxf(m, row[n] * xscale);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (lane == 0) red[0][wave] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+    const float m_neg = m > -INFINITY ? -m : 0.f;               // (a row of nothing but -inf: every weight 0)
+    float l = 0.f, ac = 0.f;
+    auto add = [&](float s) {
+        const float e = kge_exp2(fmaf(s, xscale, m_neg));
+        l += e;
+        if (loss == KGE_LOGSIGMOID) {
+            const float y = a.gamma + s, t = kge_exp2(-fabsf(y) * KGE_LOG2E);
+            if (e > 0.f) ac = fmaf(e, fmaxf(y, 0.f) + KGE_LN2 * kge_log2(1.f + t), ac);
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < R; ++j) if (tid + 256 * j < N) add(v[j]);
+    for (int n = tid + 256 * R; n < N; n += 256) add(row[n]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { l += __shfl_xor(l, o); ac += __shfl_xor(ac, o); }
+    if (lane == 0) { red[1][wave] = l; red[2][wave] = ac; }
+    __syncthreads();
+    if (tid == 0) {
+        l = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+        ac = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
+        const KgeRowFinish o = kge_rowfinish_merged(m, l, ac, N, loss, a.gamma, a.c_corr, a.scale, fp);
+        a.lossb[b] = o.L; a.gpos[b] = o.gp; a.rowinfo[b].K = o.K;
+        Kb = o.K;
+    }
+    if (!a.C) return;
+    __syncthreads();
+    const float K = Kb;
+    float csum = 0.f;
+    auto coef = [&](int n, float s) {
+        float w = kge_exp2(fmaf(s, xscale, K));
+        if (loss == KGE_LOGSIGMOID) {
+            const float y = a.gamma + s;
+            const float t = kge_exp2(-fabsf(y) * KGE_LOG2E), rcp = __builtin_amdgcn_rcpf(1.f + t);
+            w *= y >= 0.f ? rcp : t * rcp;
+        }
+        if (a.dist) w = s < 0.f ? w * __builtin_amdgcn_rcpf(-s) : 0.f;
+        put(n, w);
+        csum += a.bf16 ? (float)(__bf16)w : w;                  // (of what the contractions see)
+    };
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int n = tid + 256 * j;
+        if (n < N) coef(n, v[j]); else if (n < npad) put(n, 0.f);
+    }
+    for (int n = tid + 256 * R; n < npad; n += 256) { if (n < N) coef(n, row[n]); else put(n, 0.f); }
+    if (a.dist) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) csum += __shfl_xor(csum, o);
+        if (lane == 0) red[3][wave] = csum;
+        __syncthreads();
+        for (int s = tid; s < a.q_splits; s += 256)             // (the whole sum with the first split's partial rows)
+            a.sumq[(size_t)s * a.Bp + b] = make_float4(s == 0 ? (red[3][0] + red[3][1]) + (red[3][2] + red[3][3]) : 0.f, 0.f, 0.f, 0.f);
+    }
+}
+
+}  // namespace
+
+int kge_run_small_rows(const float *S, int64_t ldS, int B, int N, int Bp, int loss, float gamma, float adv_temp, float c_corr, float scale,
+                       const float *pos, KgeRowInfo *rowinfo, float *lossb, float *gpos, hipStream_t st, void *C, bool bf16, int kind,
+                       float4 *sumq, int q_splits) {
+    if (Bp == 0) return KGE_OK;
+    const SmallRowsArgs a{S, ldS, B, N, Bp, loss, gamma, adv_temp, c_corr, scale, pos, rowinfo, lossb, gpos, C, bf16 ? 1 : 0,
+                          kind == KGE_KIND_DIST ? 1 : 0, sumq, q_splits};
+    hipLaunchKernelGGL(small_rows_kernel, dim3(Bp), dim3(256), 0, st, a);
+    return kge_launch_status();
+}
+
+int kge_run_small_score(bool bf16, int kind, const void *Q, const void *T, const KgeRowInfo *rowinfo, const float *tn, int B, int N, int Bp,
+                        int Np, int dp, int dim, float *S, int64_t ldS, hipStream_t st) {
+    if (dp % 128 || Bp % 64 || Np % 64 || B < 1 || N < 1 || Bp / 64 > 65535) return KGE_E_INVALID_ARG;
+    KgeProfScope prof(KGE_PROF_BLOCK_FWD, st);
+    SmallArgs a{};
+    a.Q = Q; a.T = T; a.rowinfo = rowinfo; a.tn = tn; a.S = S; a.ldS = ldS; a.B = B; a.N = N; a.Bp = Bp; a.Np = Np; a.dp = dp; a.dim = dim;
+    const dim3 grid((N + 63) / 64, (B + 63) / 64);
+#define SMALL_SCORE(BF, KD) hipLaunchKernelGGL((small_score_kernel<BF, KD>), grid, dim3(256), 0, st, a)
+    if (bf16) { if (kind == KGE_KIND_DIST) SMALL_SCORE(true, KGE_KIND_DIST); else SMALL_SCORE(true, KGE_KIND_MULT); }
+    else      { if (kind == KGE_KIND_DIST) SMALL_SCORE(false, KGE_KIND_DIST); else SMALL_SCORE(false, KGE_KIND_MULT); }
+#undef SMALL_SCORE
+    return kge_launch_status();
+}
+
+// splits of the gradients' contraction index (str streamed rows): a wave of a workgroup's eight takes sixteen matrix steps at most
+int kge_small_splits(int str) { return (str + 2047) / 2048; }
+
+int kge_run_small_grad(bool bf16, int kind, const void *Q, const void *T, const void *C, int64_t ldS, int B, int N, int Bp, int Np, int dp,
+                       int dim, int q_splits, int t_splits, float *accq, float *acct, float4 *sumt, hipStream_t st) {
+    if (dp % 128 || Bp % 32 || Np % 32 || ldS % 8 || B < 1 || N < 1 || q_splits != kge_small_splits(N) || t_splits != kge_small_splits(B))
+        return KGE_E_INVALID_ARG;
+    KgeProfScope prof(KGE_PROF_BLOCK_GRADT, st);
+    SmallArgs a{};
+    a.Q = Q; a.T = T; a.C = C; a.ldS = ldS; a.B = B; a.N = N; a.Bp = Bp; a.Np = Np; a.dp = dp; a.dim = dim;
+    a.accq = accq; a.acct = acct; a.sumt = sumt;
+    const int ct = dim > 64 ? 128 : 64;
+    a.d_tiles = (dim + ct - 1) / ct;
+    a.q_splits = q_splits; a.t_splits = t_splits;
+    a.q_steps = ((N + 15) / 16 + q_splits - 1) / q_splits; a.t_steps = ((B + 15) / 16 + t_splits - 1) / t_splits;
+    a.q_blocks = (B + 255) / 256 * 8 * a.d_tiles * q_splits;
+    const dim3 grid(a.q_blocks + (N + 255) / 256 * 8 * a.d_tiles * t_splits);
+#define SMALL_GRAD(BF, KD) do { if (ct == 128) hipLaunchKernelGGL((small_grad_kernel<BF, KD, 128>), grid, dim3(512), 0, st, a); \
+                                else hipLaunchKernelGGL((small_grad_kernel<BF, KD, 64>), grid, dim3(512), 0, st, a); } while (0)
+    if (bf16) { if (kind == KGE_KIND_DIST) SMALL_GRAD(true, KGE_KIND_DIST); else SMALL_GRAD(true, KGE_KIND_MULT); }
+    else      { if (kind == KGE_KIND_DIST) SMALL_GRAD(false, KGE_KIND_DIST); else SMALL_GRAD(false, KGE_KIND_MULT); }
+#undef SMALL_GRAD
+    return kge_launch_status();
+}

@@ -50,6 +50,7 @@ struct Geometry {
                                         // 1-norm, and in training calls TransH rows over 512 bytes (2-norm; the matrix-core
                                         // kernels have no registers for two operands of that width)
     int pn;                             // ... the norm they compute
+    bool small;                         // training call: both passes with the scores in memory (block_small.hip)
     int es, rb, dp, kind;
     int B, N, Bp, Np;
     int own_tiles_b, own_tiles_n, own_tiles_s;   // own tiles of the FWD pass (queries), the GRADT and the SCORE pass (negatives)
@@ -76,6 +77,23 @@ int validate_model(const kge_model_t *m) {
     if (!m->ent || !m->rel || m->ent_ld < m->dim || m->rel_ld < k) return KGE_E_INVALID_ARG;
     if (m->scorer == KGE_TRANSH && (!m->relw || m->relw_ld < m->dim)) return KGE_E_INVALID_ARG;
     return KGE_OK;
+}
+
+// Whether both passes of a training call run with the scores in memory (block_small.hip), by the padded size of the block.
+// Measured on both sides of the lines (whole kge_loss_bwd, block kernels / in memory, us):
+//   bf16 rows of 512 bytes (their block kernels are the best there are)  1,024 x 2,048: TransE 72 / 49, ComplEx 55 / 49;
+//     4,096 x 1,024: 76 / 74, 59 / 73;  1,024 x 4,096: 80 / 68, 74 / 64 (a long row of S is cheap, many rows are not);
+//     2,048 x 4,096: 82 / 104, 70 / 99
+//   other rows  RotatE fp32 d 256: 512 x 1,024 102 / 50, 2,048 x 4,096 232 / 174;  ComplEx bf16 d 400: 89 / 41, 168 / 158;
+//     DistMult fp32 d 128: 68 / 39, 114 / 107;  512 x 16,384 (RotatE d 128 / ComplEx d 400): 158 / 164, 199 / 233
+// The scores of the largest block that qualifies take less memory than the split partials of the block kernels.
+bool small_applies(const Geometry &g) {
+    if (g.B == 0 || g.N == 0 || g.l1 || g.transh) return false;
+    for (int k : {KGE_KNOB_FWD_ONE_ROLE, KGE_KNOB_GRADT_ONE_ROLE, KGE_KNOB_TWO_ROLE, KGE_KNOB_GRADT_RECOMPUTE, KGE_KNOB_BLOCK_PASSES})
+        if (kge_knob(k)) return false;
+    const int64_t pairs = (int64_t)g.Bp * g.Np;
+    if (g.bf16 && g.rb == 512) return pairs <= (g.Np >= 2 * (int64_t)g.Bp ? 1 << 22 : 1 << 21);
+    return pairs <= (g.Np <= 16 * (int64_t)g.Bp ? 7 << 20 : 1 << 22);
 }
 
 Geometry make_geometry(const kge_model_t &m, int64_t B, int64_t N, bool train = false) {
@@ -115,6 +133,8 @@ Geometry make_geometry(const kge_model_t &m, int64_t B, int64_t N, bool train = 
     split(g.own_tiles_s, g.str_tiles_b, g.nsplit_s, g.tps_s, kge_block_occ(g.bf16, g.rb, g.transh, KGE_MODE_SCORE), 1);
     g.dsplit_q = (g.bf16 && (g.rb == 1024 || g.transh)) ? 2 : 1;
     g.dsplit_t = (g.bf16 && g.rb == 1024) ? 2 : 1;
+    g.small = train && small_applies(g);
+    if (g.small) { g.nsplit_q = kge_small_splits(g.N); g.nsplit_t = kge_small_splits(g.B); }
     if (g.l1) {
         g.nsplit_q = kge_l1_nsplit(g.Bp, g.Np, g.dp, g.transh);
         g.nsplit_t = kge_l1_nsplit(g.Np, g.Bp, g.dp, g.transh);
@@ -146,6 +166,7 @@ struct Buffers {
     float4 *stat_part; float *accq, *accq2; float4 *sumq; float *acct; float4 *sumt;
     float *regv;                       // L3 norms of the gathered slots: [Bp heads][Bp tails][Np negatives]
     float *S, *Q32;                    // 1-norm scorers: the score block [Bp][Np], the queries unrounded [Bp][dp]
+    void *C;                           // small blocks: the coefficients of the pairs in the table type (fp32: in place of S)
     float *W32, *A, *P;                // ... TransH: the unit normals unrounded, w^ . t and sign(x) . w^ per pair [Bp][Np]
     void *Qp2, *Tp2;                   // score-only calls on fp32 tables: two fp16 planes of the scaled Q (TransH: and of W) and T
     float *t_inv;                      // ... 1 / scale of the rows of T
@@ -171,10 +192,14 @@ size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
         b.Qp2 = c.take<char>((g.transh ? 4 : 2) * rowsB * 2); b.Tp2 = c.take<char>(2 * rowsN * 2); b.t_inv = c.take<float>(g.Np);
     }
     b.Q2 = nullptr; b.Qt = b.Wt = b.Tt = nullptr; b.lossb = b.gpos = nullptr; b.stat_part = nullptr;
-    b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.nbias = nullptr;
+    b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.C = nullptr; b.nbias = nullptr;
     if (bwd) {
         b.Q2 = g.transh && !g.l1 ? c.take<char>(rowsB * es) : nullptr;
-        if (!g.l1) {
+        if (g.small) {
+            b.S = c.take<float>((size_t)g.Bp * g.Np);
+            b.C = g.bf16 ? (void *)c.take<char>((size_t)g.Bp * g.Np * 2) : (void *)b.S;
+        }
+        else if (!g.l1) {
             b.Qt = c.take<char>(rowsB * es);
             b.Wt = g.transh ? c.take<char>(rowsB * es) : nullptr;
             b.Tt = c.take<char>(rowsN * es);
@@ -184,7 +209,7 @@ size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
         }
         b.lossb = c.take<float>(g.Bp);
         b.gpos = c.take<float>(g.Bp);
-        b.stat_part = c.take<float4>((size_t)g.nsplit_q * g.Bp);
+        b.stat_part = g.small ? nullptr : c.take<float4>((size_t)g.nsplit_q * g.Bp);
         b.accq = c.take<float>((size_t)g.nsplit_q * rowsB);
         b.accq2 = g.transh ? c.take<float>((size_t)g.nsplit_q * rowsB) : nullptr;
         b.sumq = c.take<float4>((size_t)g.nsplit_q * g.Bp);
@@ -193,7 +218,7 @@ size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
         b.regv = c.take<float>((size_t)2 * g.Bp + g.Np);
         b.nbias = c.take<float>(g.Np);
         b.pstore = b.Qs = nullptr;
-        if (g.B > 0 && g.N > 0 && !g.l1 && kge_gradp_applies(g.bf16, g.rb, g.transh, g.dsplit_q, g.kind)) {
+        if (g.B > 0 && g.N > 0 && !g.l1 && !g.small && kge_gradp_applies(g.bf16, g.rb, g.transh, g.dsplit_q, g.kind)) {
             b.pstore = c.take<char>((size_t)g.own_tiles_b * g.nsplit_q * (g.tps_q / 2) * 16384);
             b.Qs = c.take<char>((size_t)g.nsplit_q * rowsB * es);
         }
@@ -434,7 +459,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     const bool keep_weights = have_block && !g.l1 && cfg->loss == KGE_SAMPLED_SOFTMAX && b.pstore != nullptr;
 
     // (the kernels that need no transposed copy of the negatives get queries and negatives from ONE launch)
-    const bool plain_gather = have_block && (g.l1 || kge_fwd_pp_applies(g.bf16, g.rb, g.transh, g.dsplit_q));
+    const bool plain_gather = have_block && (g.l1 || g.small || kge_fwd_pp_applies(g.bf16, g.rb, g.transh, g.dsplit_q));
     // (negatives that the call draws itself: in that launch; where the rows are gathered otherwise, in a launch of their own)
     if (gen && N > 0 && !plain_gather) {
         rc = kge_run_negatives(((uint64_t)gen->seed_hi << 32) | gen->seed_lo, gen->step, gen->step_counter, gen->tag, gen->lo,
@@ -449,12 +474,14 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     else rc = kge_run_qbuild(md, h, r, t, g.B, g.Bp, g.dp, b.Q, b.W, b.Q2, b.Q32, b.W32, b.rowinfo, b.pos, nullptr, st);
     if (rc != KGE_OK) return rc;
     KgeBlockArgs a{};
-    if (have_block && g.l1) {
+    if (g.small) {
+        rc = kge_run_small_score(g.bf16, g.kind, b.Q, b.T, b.rowinfo, b.tn, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, b.S, g.Np, st);
+        if (rc != KGE_OK) return rc;
+    } else if (have_block && g.l1) {
         // 1-norm: the score block goes to memory, one row pass gives the loss statistics
         rc = g.transh ? kge_run_l1h_score(g.bf16, b.Q32, b.W32, b.T, g.B, g.N, g.Bp, g.Np, g.dp, b.S, b.A, b.P, g.Np, st, g.pn)
                       : kge_run_l1_score(g.bf16, b.Q32, b.T, g.B, g.N, g.Bp, g.Np, g.dp, b.S, g.Np, st);
         if (rc != KGE_OK) return rc;
-        if ((rc = kge_run_l1_rowstat(b.S, g.Np, g.B, g.N, g.Bp, cfg->loss, cfg->gamma, cfg->adv_temp, b.stat_part, st)) != KGE_OK) return rc;
     } else if (have_block) {
         // (the two-role row-owner kernel transposes its tiles in the LDS and needs no transposed copy of the negatives)
         if (!plain_gather && (rc = kge_run_tgather_t(md, neg, g.N, g.Np, g.dp, b.T, b.Tt, b.tn, st)) != KGE_OK) return rc;
@@ -474,7 +501,10 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     // (the plans of the sparse update that the caller asked for: their sorts need the ids alone and share the launch of the
     // rows' finish where there is one of that kind; otherwise they follow at the end)
     bool planned = false;
-    if (keep_weights && plans) {
+    if (have_block && (g.small || g.l1))                    // one row pass gives the loss statistics and their finish
+        rc = kge_run_small_rows(b.S, g.Np, g.B, g.N, g.Bp, cfg->loss, cfg->gamma, cfg->adv_temp, c_corr, scale, b.pos, b.rowinfo, b.lossb,
+                                b.gpos, st, g.small ? b.C : nullptr, g.bf16, g.kind, b.sumq, g.nsplit_q);
+    else if (keep_weights && plans) {
         const KgeRowFinishQArgs rf{b.stat_part, g.nsplit_q, g.Bp, g.B, g.N, cfg->loss, cfg->gamma, c_corr, scale, b.pos, b.rowinfo,
                                    b.lossb, b.gpos, (const uint16_t *)b.Q, (uint16_t *)b.Qs};
         rc = kge_run_sparse_adam_plan_tables(plans, n_plans, st, &rf);
@@ -483,10 +513,14 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
         rc = kge_run_rowfinish_qscale(b.stat_part, g.nsplit_q, g.Bp, g.B, g.N, cfg->loss, cfg->gamma, c_corr, scale, b.pos, b.rowinfo,
                                       b.lossb, b.gpos, b.Q, b.Qs, st);
     else
-        rc = kge_run_rowfinish(b.stat_part, have_block ? (g.l1 ? 1 : g.nsplit_q) : 0, g.Bp, g.B, have_block ? g.N : 0, cfg->loss,
+        rc = kge_run_rowfinish(b.stat_part, have_block ? g.nsplit_q : 0, g.Bp, g.B, have_block ? g.N : 0, cfg->loss,
                                cfg->gamma, c_corr, scale, b.pos, b.rowinfo, b.lossb, b.gpos, have_block ? nullptr : loss_out, st);
     if (rc != KGE_OK) return rc;
-    if (have_block && g.l1 && g.transh) {
+    if (g.small) {
+        rc = kge_run_small_grad(g.bf16, g.kind, b.Q, b.T, b.C, g.Np, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, g.nsplit_q, g.nsplit_t, b.accq,
+                                b.acct, b.sumt, st);
+        if (rc != KGE_OK) return rc;
+    } else if (have_block && g.l1 && g.transh) {
         if ((rc = kge_run_l1h_grad(g.bf16, true, b.Q32, b.W32, b.T, b.S, b.A, b.P, g.Np, b.rowinfo, g.B, g.N, g.Bp, g.Np, g.dp,
                                    cfg->loss, cfg->gamma, cfg->adv_temp, g.nsplit_q, b.accq, b.accq2, st, g.pn)) != KGE_OK) return rc;
         if ((rc = kge_run_l1h_grad(g.bf16, false, b.Q32, b.W32, b.T, b.S, b.A, b.P, g.Np, b.rowinfo, g.B, g.N, g.Np, g.Bp, g.dp,
@@ -513,7 +547,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
                                    g_ent, g_rel, g_relw, g_ent_idx, g_rel_idx, cfg->reg_l3, b.regv,
                                    b.acct, b.sumt, g.nsplit_t, g.Np, g.N, model->dim, g.kind == KGE_KIND_DIST && !g.l1, b.T, neg,
                                    g_ent + (size_t)2 * B * model->dim, g_ent_idx + 2 * B, b.regv + (size_t)2 * g.Bp,
-                                   b.lossb, scale, loss_out, st, keep_weights);
+                                   b.lossb, scale, loss_out, st, keep_weights, g.small);
         if (rc != KGE_OK) return rc;
     } else {
         if ((rc = kge_run_chain(md, h, r, t, g.B, g.Bp, g.dp, b.accq, b.accq2, b.sumq, b.stat_part, b.rowinfo, 0, b.gpos,

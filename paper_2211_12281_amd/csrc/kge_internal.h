@@ -35,7 +35,7 @@ struct KgeLdsLimit {
 
 // Kernel choices that only tests and benchmarks override (kge_debug_select); 0 = the library's own choice.
 enum { KGE_KNOB_FWD_ONE_ROLE = 0, KGE_KNOB_GRADT_ONE_ROLE = 1, KGE_KNOB_SCORE_F32_MFMA = 2, KGE_KNOB_TWO_ROLE = 3,
-       KGE_KNOB_GRADT_RECOMPUTE = 4, KGE_KNOBS = 5 };
+       KGE_KNOB_GRADT_RECOMPUTE = 4, KGE_KNOB_BLOCK_PASSES = 5, KGE_KNOBS = 6 };
 int kge_knob(int knob);
 
 static inline int64_t kge_round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }

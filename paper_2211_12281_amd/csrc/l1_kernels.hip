@@ -83,42 +83,9 @@ __global__ __launch_bounds__(256) void l1_score_kernel(const float *Q, const voi
     }
 }
 
-__device__ __forceinline__ float l1_wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
 __device__ __forceinline__ float l1_sigmoid(float y) {
     const float t = __builtin_amdgcn_exp2f(-fabsf(y) * L1_LOG2E), rcp = 1.f / (1.f + t);
     return y >= 0.f ? rcp : t * rcp;
-}
-
-// Row statistics of the loss (Section 3.1 "Loss Functions"), one wave per query: with x = a s (log-sigmoid
-// loss, a the self-adversarial temperature) or x = s (sampled softmax), both times log2(e):
-// {m = max_n x_n, sum_n 2^(x_n - m), sum_n 2^(x_n - m) softplus(gamma + s_n), 0}
-__global__ __launch_bounds__(256) void l1_rowstat_kernel(const float *S, int64_t ldS, int B, int N, int Bp, int loss, float gamma,
-                                                         float adv_temp, float4 *stat) {
-    const int lane = threadIdx.x & 63;
-    const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (b >= Bp) return;
-    if (b >= B) { if (lane == 0) stat[b] = make_float4(-INFINITY, 0.f, 0.f, 0.f); return; }
-    const float xscale = (loss == KGE_LOGSIGMOID ? adv_temp : 1.f) * L1_LOG2E;
-    const float *row = S + (int64_t)b * ldS;
-    float m = -INFINITY;
-    for (int n = lane; n < N; n += 64) m = fmaxf(m, row[n] * xscale);
-    m = l1_wave_max(m);
-    float l = 0.f, ac = 0.f;
-    for (int n = lane; n < N; n += 64) {
-        const float s = row[n], e = __builtin_amdgcn_exp2f(fmaf(s, xscale, -m));
-        l += e;
-        if (loss == KGE_LOGSIGMOID) {
-            const float y = gamma + s;
-            const float t = __builtin_amdgcn_exp2f(-fabsf(y) * L1_LOG2E);
-            ac = fmaf(e, fmaxf(y, 0.f) + L1_LN2 * __builtin_amdgcn_logf(1.f + t), ac);
-        }
-    }
-    l = kge_wave_sum(l); ac = kge_wave_sum(ac);
-    if (lane == 0) stat[b] = make_float4(m, l, ac, 0.f);
 }
 
 // out[split][o, j] = -sum_s w(o, s) sign(own_oj - str_sj) over the split's rows of the streamed operand: with
@@ -410,13 +377,6 @@ int kge_run_l1_score(bool bf16, const float *Q, const void *T, int B, int N, int
     const dim3 grid(Np / L1_TILE, Bp / L1_TILE);
     if (bf16) hipLaunchKernelGGL(l1_score_kernel<true>, grid, dim3(256), 0, st, Q, T, B, N, dp, S, ldS);
     else      hipLaunchKernelGGL(l1_score_kernel<false>, grid, dim3(256), 0, st, Q, T, B, N, dp, S, ldS);
-    return kge_launch_status();
-}
-
-int kge_run_l1_rowstat(const float *S, int64_t ldS, int B, int N, int Bp, int loss, float gamma, float adv_temp,
-                       float4 *stat, hipStream_t st) {
-    if (Bp == 0) return KGE_OK;
-    hipLaunchKernelGGL(l1_rowstat_kernel, dim3((Bp + 3) / 4), dim3(256), 0, st, S, ldS, B, N, Bp, loss, gamma, adv_temp, stat);
     return kge_launch_status();
 }
 

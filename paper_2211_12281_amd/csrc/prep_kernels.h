@@ -60,15 +60,14 @@ int kge_run_chain_tfinish(const KgeModelDev &m, const int32_t *h, const int32_t 
                           float *g_relw, int32_t *g_ent_idx, int32_t *g_rel_idx, float reg, float *regv,
                           const float *accT_part, const float4 *sumT_part, int nsplit_t, int Np, int N, int d, int dist_kind,
                           const void *T, const int32_t *neg, float *g_neg, int32_t *g_neg_idx, float *regn,
-                          const float *lossb, float scale, float *loss_out, hipStream_t st, bool part_bf16 = false);   // also loss_out = scale * sum of lossb
+                          const float *lossb, float scale, float *loss_out, hipStream_t st, bool part_bf16 = false,     // also loss_out = scale * sum of lossb
+                          bool finished = false);                 // finished: the coefficients in the queries' partials are (stat_part is not read)
 // loss_out += reg * (sum of regv over the 2B + N gathered slots), laid out [Bp heads][Bp tails][N negatives]
 int kge_run_reg_add(const float *regv, int B, int Bp, int N, float reg, float *loss_out, hipStream_t st);
 
-// 1-norm distance scorers (l1_kernels.hip): score block, row statistics of the loss, gradient rows
+// 1-norm distance scorers (l1_kernels.hip): score block, gradient rows
 int kge_run_l1_score(bool bf16, const float *Q, const void *T, int B, int N, int Bp, int Np, int dp, float *S, int64_t ldS,
                      hipStream_t st);
-int kge_run_l1_rowstat(const float *S, int64_t ldS, int B, int N, int Bp, int loss, float gamma, float adv_temp,
-                       float4 *stat, hipStream_t st);
 int kge_l1_nsplit(int own_pad, int str_pad, int dp, bool transh);
 int kge_run_l1_grad(bool bf16, bool own_is_query, const void *own, const void *str, const float *S, int64_t ldS,
                     const KgeRowInfo *rowinfo, int B, int N, int own_pad, int str_pad, int dp, int loss, float gamma,
@@ -81,3 +80,14 @@ int kge_run_l1h_grad(bool bf16, bool own_is_query, const float *Q, const float *
                      const float *P, int64_t ldS, const KgeRowInfo *rowinfo, int B, int N, int own_pad, int str_pad, int dp,
                      int loss, float gamma, float adv_temp, int nsplit, float *acc_part, float *acc_part2, hipStream_t st,
                      int pn = 1);
+
+// block_small.hip: both passes for small blocks with the scores in memory (no TransH, no 1-norm); partials with finished
+// coefficients.  kge_run_small_rows also serves the 1-norm's score blocks (without C).
+int kge_small_splits(int str);
+int kge_run_small_score(bool bf16, int kind, const void *Q, const void *T, const KgeRowInfo *rowinfo, const float *tn, int B, int N, int Bp,
+                        int Np, int dp, int dim, float *S, int64_t ldS, hipStream_t st);
+int kge_run_small_rows(const float *S, int64_t ldS, int B, int N, int Bp, int loss, float gamma, float adv_temp, float c_corr, float scale,
+                       const float *pos, KgeRowInfo *rowinfo, float *lossb, float *gpos, hipStream_t st, void *C = nullptr,
+                       bool bf16 = false, int kind = 0, float4 *sumq = nullptr, int q_splits = 0);
+int kge_run_small_grad(bool bf16, int kind, const void *Q, const void *T, const void *C, int64_t ldS, int B, int N, int Bp, int Np, int dp,
+                       int dim, int q_splits, int t_splits, float *accq, float *acct, float4 *sumt, hipStream_t st);

@@ -203,9 +203,11 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
     const int gl = kge_tgather_group_lanes(dp, ES), rpl = 64 / gl, rpw = KGE_TG_INFLIGHT * rpl;
     const int nbase = (blk * (blockDim.x >> 6) + (threadIdx.x >> 6)) * rpw;
     if (nbase >= Np) return;
-    if (m.dim == dp && lpr <= 64 && (m.ent_ld * ES) % 16 == 0 && ((uintptr_t)m.ent & 15) == 0) {
-        // unpadded, 16-byte aligned rows: ONE load per lane and row, four rows (groups of rows) requested together
-        const int grp = lane / gl, lg = lane % gl;
+    if (lpr <= 64 && (m.dim * ES) % 16 == 0 && (m.ent_ld * ES) % 16 == 0 && ((uintptr_t)m.ent & 15) == 0) {
+        // 16-byte aligned rows: ONE load per lane and row, four rows (groups of rows) requested together; the lanes past the row
+        // fill the padding columns with zeros (one row after the other, 64 columns at a time, the launch took 15.7 us for rows of
+        // 800 bytes and 11.5 for rows of 128, now 8.7 and 5.4)
+        const int grp = lane / gl, lg = lane % gl, lrow = m.dim * ES / 16;
         uint4 v[KGE_TG_INFLIGHT];
         int64_t off[KGE_TG_INFLIGHT];
         // ids drawn here: lane l draws the id of row nbase + l % rpw (one Philox block per lane instead of one per row and
@@ -227,7 +229,7 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
 #pragma unroll
         for (int u = 0; u < KGE_TG_INFLIGHT; ++u) {
             v[u] = make_uint4(0u, 0u, 0u, 0u);
-            if (off[u] >= 0 && lg < lpr) v[u] = *(const uint4 *)((const char *)m.ent + off[u] * ES + lg * 16);
+            if (off[u] >= 0 && lg < lrow) v[u] = *(const uint4 *)((const char *)m.ent + off[u] * ES + lg * 16);
         }
 #pragma unroll
         for (int u = 0; u < KGE_TG_INFLIGHT; ++u) {
@@ -414,6 +416,7 @@ struct KgeChainArgs {
     KgeModelDev m; const int32_t *h, *r, *t; int B, Bp, dp; const float *acc_part, *acc_part2; const float4 *sum_part, *stat_part;
     const KgeRowInfo *rowinfo; int nsplit; const float *gpos; float *g_ent, *g_rel, *g_relw; int32_t *g_ent_idx, *g_rel_idx;
     float reg; float *regv;
+    int32_t fin;                       // the partials carry finished coefficients (block_small.hip): summed as they are
 };
 struct KgeTfinishArgs {
     const float *accT_part; const float4 *sumT_part; int nsplit, Np, N, dp, d, dist_kind; const void *T; const int32_t *neg;
@@ -446,7 +449,7 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
     const float K2 = rowinfo[b].K;
     // (the vector-pipe kernels apply the finished coefficients themselves: their partials are summed as they are)
     auto kappa = [&](int s) {
-        if (m.vec) return 1.f;
+        if (m.vec || a.fin) return 1.f;
         const float ms = stat_part[(size_t)s * Bp + b].x;
         return ms > -INFINITY ? exp2f(ms + K2) : 0.f;
     };
@@ -830,7 +833,7 @@ int kge_run_chain(const KgeModelDev &m, const int32_t *h, const int32_t *r, cons
     if (B == 0) return KGE_OK;
     const int grid = (B + 3) / 4;
     const KgeChainArgs a{m, h, r, t, B, Bp, dp, acc_part, acc_part2, sum_part, stat_part, rowinfo, nsplit, gpos,
-                         g_ent, g_rel, g_relw, g_ent_idx, g_rel_idx, reg, regv};
+                         g_ent, g_rel, g_relw, g_ent_idx, g_rel_idx, reg, regv, 0};
 #define KGE_CHAIN(BF, SC) hipLaunchKernelGGL((kge_chain_kernel<BF, SC>), dim3(grid), dim3(256), 0, st, a)
     if (m.bf16) { KGE_SC_SWITCH(true, KGE_CHAIN) } else { KGE_SC_SWITCH(false, KGE_CHAIN) }
 #undef KGE_CHAIN
@@ -855,11 +858,11 @@ int kge_run_chain_tfinish(const KgeModelDev &m, const int32_t *h, const int32_t 
                           float *g_relw, int32_t *g_ent_idx, int32_t *g_rel_idx, float reg, float *regv,
                           const float *accT_part, const float4 *sumT_part, int nsplit_t, int Np, int N, int d, int dist_kind,
                           const void *T, const int32_t *neg, float *g_neg, int32_t *g_neg_idx, float *regn,
-                          const float *lossb, float scale, float *loss_out, hipStream_t st, bool part_bf16) {
+                          const float *lossb, float scale, float *loss_out, hipStream_t st, bool part_bf16, bool finished) {
     if (B == 0 || N == 0) return KGE_E_INVALID_ARG;
     const int cb = (B + 3) / 4, tb = (N + 3) / 4;
     const KgeChainArgs a{m, h, r, t, B, Bp, dp, acc_part, acc_part2, sum_part, stat_part, rowinfo, nsplit, gpos,
-                         g_ent, g_rel, g_relw, g_ent_idx, g_rel_idx, reg, regv};
+                         g_ent, g_rel, g_relw, g_ent_idx, g_rel_idx, reg, regv, finished ? 1 : 0};
     const KgeTfinishArgs f{accT_part, sumT_part, nsplit_t, Np, N, dp, d, dist_kind, T, neg, g_neg, g_neg_idx, m.ent, m.ent_ld, reg, regn};
     if (part_bf16) {
         // (written by the bilinear kernels on bf16 rows of 512 bytes only)

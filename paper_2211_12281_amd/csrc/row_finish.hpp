@@ -2,6 +2,7 @@
 // sorts of the step's row ids (sparse_adam.hip).
 #pragma once
 #include "kge_internal.h"
+#include <math.h>
 
 // ---------------------------------------------------------------------------------------------
 // per-row finish of the loss (Section 3.1): combines the split statistics with the positive score
@@ -9,25 +10,11 @@
 __device__ __forceinline__ float kge_softplus_f(float y) { return fmaxf(y, 0.f) + log1pf(expf(-fabsf(y))); }
 
 struct KgeRowFinish { float L, gp, K; };
-__device__ __forceinline__ KgeRowFinish kge_rowfinish_row(const float4 *stat_part, int nsplit, int Bp, int b, int N, int loss,
-                                                          float gamma, float c_corr, float scale, float fp) {
+// from the statistics of the whole row: m the maximum of x log2(e) (x = a s or s), l the sum of exp(x - max), ac the sum of
+// exp(x - max) softplus(gamma + s)
+__device__ __forceinline__ KgeRowFinish kge_rowfinish_merged(float m, float l, float ac, int N, int loss, float gamma, float c_corr,
+                                                             float scale, float fp) {
     const float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
-    // merge the splits: m is the running maximum of x * log2(e) (x = a*s or s), l the sum of
-    // exp(x - max), ac the sum of exp(x - max) * softplus(gamma + s)
-    float m = -INFINITY, l = 0.f, ac = 0.f;
-    for (int s0 = 0; s0 < nsplit; s0 += 8) {                // fixed order; eight loads in flight
-        float4 pv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) pv[u] = stat_part[(size_t)(s0 + u < nsplit ? s0 + u : nsplit - 1) * Bp + b];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float4 p = pv[u];
-            if (s0 + u >= nsplit || p.x == -INFINITY) continue;
-            const float mn = fmaxf(m, p.x);
-            const float r0 = exp2f(m - mn), r1 = exp2f(p.x - mn);
-            l = l * r0 + p.y * r1; ac = ac * r0 + p.z * r1; m = mn;
-        }
-    }
     KgeRowFinish o;
     if (loss == KGE_LOGSIGMOID) {
         o.L = kge_softplus_f(-(gamma + fp));
@@ -46,6 +33,27 @@ __device__ __forceinline__ KgeRowFinish kge_rowfinish_row(const float4 *stat_par
     }
     return o;
 }
+__device__ __forceinline__ KgeRowFinish kge_rowfinish_row(const float4 *stat_part, int nsplit, int Bp, int b, int N, int loss,
+                                                          float gamma, float c_corr, float scale, float fp) {
+    // merge the splits: m is the running maximum of x * log2(e) (x = a*s or s), l the sum of
+    // exp(x - max), ac the sum of exp(x - max) * softplus(gamma + s)
+    float m = -INFINITY, l = 0.f, ac = 0.f;
+    for (int s0 = 0; s0 < nsplit; s0 += 8) {                // fixed order; eight loads in flight
+        float4 pv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) pv[u] = stat_part[(size_t)(s0 + u < nsplit ? s0 + u : nsplit - 1) * Bp + b];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float4 p = pv[u];
+            if (s0 + u >= nsplit || p.x == -INFINITY) continue;
+            const float mn = fmaxf(m, p.x);
+            const float r0 = exp2f(m - mn), r1 = exp2f(p.x - mn);
+            l = l * r0 + p.y * r1; ac = ac * r0 + p.z * r1; m = mn;
+        }
+    }
+    return kge_rowfinish_merged(m, l, ac, N, loss, gamma, c_corr, scale, fp);
+}
+
 
 // The same finish, one wave per row, which also leaves the bf16 query row (256 elements) scaled for every forward split s:
 // qs[s][b] = bf16(exp2(ref_s[b] + K[b]) q[b]), ref_s the reference exponent that split s weighted the row's scores

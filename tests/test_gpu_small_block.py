@@ -1,0 +1,79 @@
+"""Training calls on small blocks (scores in the workspace) against the oracle at the sizes where their tiles, splits and paddings
+end; and the block kernels, which larger blocks use, on the cases of test_gpu_loss_bwd.py that are too small to reach them."""
+import pytest
+
+import test_gpu_loss_bwd as base
+from helpers import RTOL_BF16, RTOL_F32, dev_idx, gpu_model, make_case, norm_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,B,N", [
+    ("transe", 256, True, 33, 65), ("rotate", 256, False, 31, 2049),   # one row over a tile; two splits of the queries' pass
+    ("complex", 400, True, 2100, 40), ("distmult", 64, False, 2049, 33),   # ... of the pass over the negatives
+    ("transe", 72, False, 16, 16), ("complex", 16, True, 15, 17),      # one matrix step and its neighbours; narrow rows
+    ("rotate", 144, True, 64, 4200), ("distmult", 248, False, 260, 255),
+    ("transe", 512, True, 7, 1)])
+@pytest.mark.parametrize("loss", ["logsigmoid", "sampled_softmax"])
+def test_small_blocks_match_oracle(orc, scorer, dim, bf16, B, N, loss):
+    amp = 0.3 if scorer in ("distmult", "complex") else 0.1
+    G = make_case(scorer, 3000, 9, dim, B, N, bf16, amp=amp, zipf=True)
+    kw = dict(n_ent_for_c=3000) if loss == "sampled_softmax" else dict(gamma=1.0, adv_temp=0.7)
+    base._compare(orc, scorer, loss, G, bf16, 3000, kw=dict(kw, reg_l3=1e-3 if B % 2 else 0.0))
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", [
+    ("transe", 256, True, "logsigmoid", 1024, 2048), ("transe", 256, True, "logsigmoid", 1024, 2049),
+    ("complex", 256, True, "sampled_softmax", 900, 4600), ("rotate", 128, False, "logsigmoid", 2600, 2700),
+    ("complex", 400, True, "sampled_softmax", 300, 12000)])
+def test_both_sides_of_the_rule_agree(scorer, dim, bf16, loss, B, N):
+    """Blocks at the line between the two routes, each route against the other (block_passes takes the block kernels for all)."""
+    import paper_2211_12281_amd as kge
+    G = make_case(scorer, 9000, 9, dim, B, N, bf16, amp=0.3 if scorer == "complex" else 0.1, zipf=True)
+    model = gpu_model(scorer, G, bf16)
+    args = (dev_idx(G["h"]), dev_idx(G["r"]), dev_idx(G["t"]), dev_idx(G["neg"]))
+    kw = dict(n_ent_for_c=9000) if loss == "sampled_softmax" else dict(gamma=2.0, adv_temp=0.8)
+    got = {k: v.clone() for k, v in kge.loss_bwd(model, loss, *args, **kw).items() if v is not None}
+    kge.debug_select("block_passes", True)
+    try:
+        want = kge.loss_bwd(model, loss, *args, **kw)
+    finally:
+        kge.debug_select("block_passes", False)
+    tol = RTOL_BF16 if bf16 else RTOL_F32
+    assert abs(got["loss"].item() - want["loss"].item()) <= 1e-4 * abs(want["loss"].item())
+    for sl in (slice(0, B), slice(B, 2 * B), slice(2 * B, 2 * B + N)):
+        assert norm_err(got["g_ent"][sl].cpu().numpy(), want["g_ent"][sl].cpu().numpy()) <= tol
+    assert norm_err(got["g_rel"].cpu().numpy(), want["g_rel"].cpu().numpy()) <= tol
+
+
+@pytest.fixture
+def block_passes():
+    import paper_2211_12281_amd as kge
+    kge.debug_select("block_passes", True)
+    yield
+    kge.debug_select("block_passes", False)
+
+
+@pytest.mark.parametrize("scorer", base.SCORERS)
+@pytest.mark.parametrize("loss", ["logsigmoid", "sampled_softmax"])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_block_kernels_match_oracle(orc, block_passes, scorer, loss, bf16):
+    base.test_loss_and_gradients_match_oracle(orc, scorer, loss, bf16)
+
+
+@pytest.mark.parametrize("scorer,dim,bf16", [("complex", 256, True), ("transe", 256, False), ("distmult", 128, False), ("rotate", 256, True),
+                                             ("distmult", 32, False), ("complex", 512, True)])
+def test_block_kernels_other_row_sizes(orc, block_passes, scorer, dim, bf16):
+    base.test_other_row_sizes(orc, scorer, dim, bf16)
+
+
+@pytest.mark.parametrize("scorer", ["transe", "complex"])
+def test_block_kernels_edge_shapes(orc, block_passes, scorer):
+    base.test_edge_shapes(orc, scorer)
+
+
+@pytest.mark.parametrize("scorer", ["distmult", "complex"])
+def test_block_kernels_scores_that_outgrow_the_first_tile(orc, block_passes, scorer):
+    for name in dir(base):
+        if "outgrow" in name and name.startswith("test_"):
+            getattr(base, name)(orc, scorer)
