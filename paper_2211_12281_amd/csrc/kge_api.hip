@@ -412,7 +412,7 @@ int kge_score(const kge_model_t *model, const int32_t *h, const int32_t *r, cons
     if (rc != KGE_OK || !block) return rc;
     if (g.l1 && g.transh)
         return kge_run_l1h_score(g.bf16, b.Q32, b.W32, b.T, g.B, g.N, g.Bp, g.Np, g.dp, neg_out, nullptr, nullptr, g.N, st);
-    if (g.l1) return kge_run_l1_score(g.bf16, b.Q32, b.T, g.B, g.N, g.Bp, g.Np, g.dp, neg_out, g.N, st);
+    if (g.l1) return kge_run_l1_score(g.bf16, b.Q32, b.T, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, neg_out, g.N, st);
     if (score_h2_applies(g)) {
         return kge_launch_score_h2(g.kind, g.dp, b.Qp2, b.Tp2, b.t_inv, (const float *)b.Q, (const float *)b.T,
                                  g.transh ? (const float *)b.W : nullptr, b.rowinfo, b.tn, g.B, g.N,
@@ -480,7 +480,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     } else if (have_block && g.l1) {
         // 1-norm: the score block goes to memory, one row pass gives the loss statistics
         rc = g.transh ? kge_run_l1h_score(g.bf16, b.Q32, b.W32, b.T, g.B, g.N, g.Bp, g.Np, g.dp, b.S, b.A, b.P, g.Np, st, g.pn)
-                      : kge_run_l1_score(g.bf16, b.Q32, b.T, g.B, g.N, g.Bp, g.Np, g.dp, b.S, g.Np, st);
+                      : kge_run_l1_score(g.bf16, b.Q32, b.T, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, b.S, g.Np, st);
         if (rc != KGE_OK) return rc;
     } else if (have_block) {
         // (the two-role row-owner kernel transposes its tiles in the LDS and needs no transposed copy of the negatives)
@@ -503,7 +503,8 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     bool planned = false;
     if (have_block && (g.small || g.l1))                    // one row pass gives the loss statistics and their finish
         rc = kge_run_small_rows(b.S, g.Np, g.B, g.N, g.Bp, cfg->loss, cfg->gamma, cfg->adv_temp, c_corr, scale, b.pos, b.rowinfo, b.lossb,
-                                b.gpos, st, g.small ? b.C : nullptr, g.bf16, g.kind, b.sumq, g.nsplit_q);
+                                b.gpos, st, g.small ? b.C : g.transh ? nullptr : b.S, g.small && g.bf16, g.small ? g.kind : KGE_KIND_MULT,
+                                b.sumq, g.nsplit_q);
     else if (keep_weights && plans) {
         const KgeRowFinishQArgs rf{b.stat_part, g.nsplit_q, g.Bp, g.B, g.N, cfg->loss, cfg->gamma, c_corr, scale, b.pos, b.rowinfo,
                                    b.lossb, b.gpos, (const uint16_t *)b.Q, (uint16_t *)b.Qs};
@@ -526,11 +527,9 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
         if ((rc = kge_run_l1h_grad(g.bf16, false, b.Q32, b.W32, b.T, b.S, b.A, b.P, g.Np, b.rowinfo, g.B, g.N, g.Np, g.Bp, g.dp,
                                    cfg->loss, cfg->gamma, cfg->adv_temp, g.nsplit_t, b.acct, nullptr, st, g.pn)) != KGE_OK) return rc;
     } else if (have_block && g.l1) {
-        // gradient rows of the queries and of the shared negatives from S and the finished row constants
-        if ((rc = kge_run_l1_grad(g.bf16, true, b.Q32, b.T, b.S, g.Np, b.rowinfo, g.B, g.N, g.Bp, g.Np, g.dp, cfg->loss, cfg->gamma,
-                                  cfg->adv_temp, g.nsplit_q, b.accq, st)) != KGE_OK) return rc;
-        if ((rc = kge_run_l1_grad(g.bf16, false, b.T, b.Q32, b.S, g.Np, b.rowinfo, g.B, g.N, g.Np, g.Bp, g.dp, cfg->loss, cfg->gamma,
-                                  cfg->adv_temp, g.nsplit_t, b.acct, st)) != KGE_OK) return rc;
+        // gradient rows of the queries and of the shared negatives from the pairs' weights, which the row pass left in S
+        if ((rc = kge_run_l1_grad(g.bf16, true, b.Q32, b.T, b.S, g.Np, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, g.nsplit_q, b.accq, st)) != KGE_OK) return rc;
+        if ((rc = kge_run_l1_grad(g.bf16, false, b.T, b.Q32, b.S, g.Np, g.B, g.N, g.Np, g.Bp, g.dp, model->dim, g.nsplit_t, b.acct, st)) != KGE_OK) return rc;
     } else if (have_block) {
         // pass 2 (column owner): gradient of the shared negatives from the finished row constants
         KgeBlockArgs c = a;

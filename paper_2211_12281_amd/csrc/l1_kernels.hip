@@ -9,7 +9,8 @@
 // The queries are read from an unrounded fp32 copy also when the tables are bf16 (a sign flips when rounding moves a
 // difference across zero; the table rows themselves are exact).  All three block kernels stage 64 x 64 fp32 tiles in the LDS (row pitch 68 floats: the 16 lanes that read 16
 // different rows at one column offset hit 16 different 16-byte bank groups) and keep a 4 x 4 register tile per
-// thread; they are bound by the vector pipe.
+// thread; they are bound by the vector pipe in large blocks and by the latency of a chunk (loads, barrier) in small ones, so the loads of
+// the next chunk are issued before the present one is used (gradient passes 44 -> 24 us each at 512 x 1,280 x 384).
 #include "row_ops.hpp"
 
 namespace {
@@ -21,51 +22,77 @@ constexpr float L1_BIG = 0x1p100f;     // scale of the operands of the sign comp
 
 typedef float l1_f32x4 __attribute__((ext_vector_type(4)));
 
-// rows [r0, r0 + 64) x columns [c0, c0 + 64) of a row-major [rows][ld] array of the table type -> fp32 LDS tile
-// (times scale, a power of two)
-template <bool BF16>
-__device__ __forceinline__ void l1_stage(const void *src, int64_t ld, int r0, int c0, float *tile, float scale = 1.f) {
+// rows [r0, r0 + 64) x columns [c0, c0 + 64) of a row-major [rows][ld] array of the table type -> fp32 LDS tile, in two halves:
+// the loads of the next tile are issued before this one is used
+template <int R> struct L1TileR { uint32_t w[R / 16][4]; };      // R rows
+using L1Tile = L1TileR<L1_TILE>;
+template <bool BF16, int R>
+__device__ __forceinline__ void l1_fetch(const void *src, int64_t ld, int r0, int c0, L1TileR<R> &t) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < R / 16; ++k) {
         const int e = threadIdx.x + 256 * k, row = e >> 4, cq = e & 15;
         const int64_t off = (int64_t)(r0 + row) * ld + c0 + 4 * cq;
-        l1_f32x4 v;
         if constexpr (BF16) {
             const uint2 raw = *(const uint2 *)((const __bf16 *)src + off);
-            v = l1_f32x4{__uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u),
-                         __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xffff0000u)};
+            t.w[k][0] = raw.x; t.w[k][1] = raw.y;
         } else {
-            v = *(const l1_f32x4 *)((const float *)src + off);
+            const uint4 raw = *(const uint4 *)((const float *)src + off);
+            t.w[k][0] = raw.x; t.w[k][1] = raw.y; t.w[k][2] = raw.z; t.w[k][3] = raw.w;
         }
-        *(l1_f32x4 *)(tile + row * L1_PITCH + 4 * cq) = v * scale;
     }
 }
-
-// S[b, n] = -sum_j |q_bj - t_nj|; workgroup = 64 queries x 64 negatives, thread = queries 4 ty + i, negatives tx + 16 k
-template <bool BF16>
-__global__ __launch_bounds__(256) void l1_score_kernel(const float *Q, const void *T, int B, int N, int dp, float *S, int64_t ldS) {
-    __shared__ __attribute__((aligned(16))) float qs[L1_TILE * L1_PITCH], ts[L1_TILE * L1_PITCH];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int n0 = blockIdx.x * L1_TILE, b0 = blockIdx.y * L1_TILE;
-    float acc[4][4];
+template <bool BF16, int R>
+__device__ __forceinline__ void l1_put(const L1TileR<R> &t, float *tile) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int k = 0; k < R / 16; ++k) {
+        const int e = threadIdx.x + 256 * k, row = e >> 4, cq = e & 15;
+        l1_f32x4 v;
+        if constexpr (BF16)
+            v = l1_f32x4{__uint_as_float(t.w[k][0] << 16), __uint_as_float(t.w[k][0] & 0xffff0000u),
+                         __uint_as_float(t.w[k][1] << 16), __uint_as_float(t.w[k][1] & 0xffff0000u)};
+        else v = l1_f32x4{__uint_as_float(t.w[k][0]), __uint_as_float(t.w[k][1]), __uint_as_float(t.w[k][2]), __uint_as_float(t.w[k][3])};
+        *(l1_f32x4 *)(tile + row * L1_PITCH + 4 * cq) = v;
+    }
+}
+template <bool BF16>
+__device__ __forceinline__ void l1_stage(const void *src, int64_t ld, int r0, int c0, float *tile) {
+    L1Tile t;
+    l1_fetch<BF16>(src, ld, r0, c0, t);
+    l1_put<BF16>(t, tile);
+}
+
+// S[b, n] = -sum_j |q_bj - t_nj|; workgroup = 16 QR queries x 64 negatives, thread = queries QR ty + i, negatives tx + 16 k
+template <bool BF16, int QR>
+__global__ __launch_bounds__(256) void l1_score_kernel(const float *Q, const void *T, int B, int N, int dp, int cols, float *S, int64_t ldS) {
+    __shared__ __attribute__((aligned(16))) float qs[16 * QR * L1_PITCH], ts[L1_TILE * L1_PITCH];
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const int n0 = blockIdx.x * L1_TILE, b0 = blockIdx.y * 16 * QR;
+    float acc[QR][4];
+#pragma unroll
+    for (int i = 0; i < QR; ++i)
         for (int k = 0; k < 4; ++k) acc[i][k] = 0.f;
-    for (int j0 = 0; j0 < dp; j0 += L1_TILE) {
+    L1TileR<16 * QR> tq;
+    L1Tile tt;
+    l1_fetch<false>(Q, dp, b0, 0, tq);
+    l1_fetch<BF16>(T, dp, n0, 0, tt);
+    for (int j0 = 0; j0 < cols; j0 += L1_TILE) {
         __syncthreads();
-        l1_stage<false>(Q, dp, b0, j0, qs);
-        l1_stage<BF16>(T, dp, n0, j0, ts);
+        l1_put<false>(tq, qs);
+        l1_put<BF16>(tt, ts);
         __syncthreads();
+        if (j0 + L1_TILE < cols) {
+            l1_fetch<false>(Q, dp, b0, j0 + L1_TILE, tq);
+            l1_fetch<BF16>(T, dp, n0, j0 + L1_TILE, tt);
+        }
 #pragma unroll 4
         for (int jq = 0; jq < 16; ++jq) {
-            l1_f32x4 q4[4], t4[4];
+            l1_f32x4 q4[QR], t4[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                q4[i] = *(const l1_f32x4 *)(qs + (4 * ty + i) * L1_PITCH + 4 * jq);
-                t4[i] = *(const l1_f32x4 *)(ts + (tx + 16 * i) * L1_PITCH + 4 * jq);
-            }
+            for (int i = 0; i < QR; ++i) q4[i] = *(const l1_f32x4 *)(qs + (QR * ty + i) * L1_PITCH + 4 * jq);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i) t4[i] = *(const l1_f32x4 *)(ts + (tx + 16 * i) * L1_PITCH + 4 * jq);
+#pragma unroll
+            for (int i = 0; i < QR; ++i)
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -73,8 +100,8 @@ __global__ __launch_bounds__(256) void l1_score_kernel(const float *Q, const voi
         }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int b = b0 + 4 * ty + i;
+    for (int i = 0; i < QR; ++i) {
+        const int b = b0 + QR * ty + i;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int n = n0 + tx + 16 * k;
@@ -96,62 +123,77 @@ __device__ __forceinline__ float l1_sigmoid(float y) {
 // are fp32, the negatives of the table type.  Both operands are scaled by 2^100 when they are loaded (exact), so that
 // sign(own - str) = median(-1, (own - str) 2^100, 1) is one subtraction and one median: a non-zero difference of
 // two floats whose magnitudes exceed 2^-76 is at least 2^-100, its scaled value at least 1; a zero difference
-// stays zero (sub-gradient 0).  Three vector operations per (own row, streamed row, dimension).  Per chunk of 32
-// streamed rows the weights w = 2^(x log2e + K_b) (times sigma(gamma + s) for the log-sigmoid loss) are computed
-// once from S and the finished row constants into the LDS.
+// stays zero (sub-gradient 0).  Three vector operations per (own row, streamed row, dimension).  The weights w come from the
+// row pass, which leaves them in place of the scores.
 constexpr int L1_GO = 128, L1_GD = 64, L1_GS = 32;   // own rows, dimensions, streamed rows per chunk of a gradient workgroup
 constexpr int L1_WP = 132;                            // floats per LDS row of the weights (16 lanes x 16 bytes stay conflict-free)
 
 template <bool BF16, bool OWN_Q>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void l1_grad_kernel(
-        const void *own, const void *str, const float *S, int64_t ldS, const KgeRowInfo *rowinfo, int B, int N, int own_pad,
-        int dp, int chunks, int cps, int loss, float gamma, float adv_temp, float *acc_part) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void l1_grad_kernel(
+        const void *own, const void *str, const float *W, int64_t ldW, int B, int N, int own_pad, int dp, int chunks, int cps, float *acc_part) {
     __shared__ __attribute__((aligned(16))) float ss[L1_GS * L1_PITCH], ws[L1_GS * L1_WP];
     constexpr bool SBF = BF16 && OWN_Q, OBF = BF16 && !OWN_Q;   // table type of the streamed / own operand
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     const int o0 = blockIdx.x * L1_GO, j0 = blockIdx.y * L1_GD, split = blockIdx.z;
-    const float xscale = (loss == KGE_LOGSIGMOID ? adv_temp : 1.f) * L1_LOG2E;
     float ov[8][4], acc[8][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 8; ++i) {
+        const int64_t off = (int64_t)(o0 + 4 * ty + (i & 3) + 64 * (i >> 2)) * dp + j0 + 4 * tx;
+        l1_f32x4 v;
+        if constexpr (OBF) {
+            const uint2 r = *(const uint2 *)((const __bf16 *)own + off);
+            v = l1_f32x4{__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u), __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u)};
+        } else v = *(const l1_f32x4 *)((const float *)own + off);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int o = o0 + 4 * ty + (i & 3) + 64 * (i >> 2);
-            ov[i][c] = El<OBF>::ld(own, (int64_t)o * dp + j0 + 4 * tx + c) * L1_BIG;
-            acc[i][c] = 0.f;
-        }
+        for (int c = 0; c < 4; ++c) { ov[i][c] = v[c] * L1_BIG; acc[i][c] = 0.f; }
+    }
     const int c_lo = split * cps, c_hi = min(chunks, (split + 1) * cps);
-    for (int ch = c_lo; ch < c_hi; ++ch) {
+    // a chunk's rows and weights are requested before the chunk in front of it is used
+    uint32_t raw[2][4];
+    float wv[16];
+    auto fetch = [&](int ch) {
         const int s0 = ch * L1_GS;
-        __syncthreads();                                    // everyone is done with the previous chunk
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int e = threadIdx.x + 256 * k, row = e >> 4, cq = e & 15;
             const int64_t off = (int64_t)(s0 + row) * dp + j0 + 4 * cq;
-            l1_f32x4 v;
             if constexpr (SBF) {
-                const uint2 raw = *(const uint2 *)((const __bf16 *)str + off);
-                v = l1_f32x4{__uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xffff0000u),
-                             __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xffff0000u)};
+                const uint2 v = *(const uint2 *)((const __bf16 *)str + off);
+                raw[k][0] = v.x; raw[k][1] = v.y;
             } else {
-                v = *(const l1_f32x4 *)((const float *)str + off);
+                const uint4 v = *(const uint4 *)((const float *)str + off);
+                raw[k][0] = v.x; raw[k][1] = v.y; raw[k][2] = v.z; raw[k][3] = v.w;
             }
-            *(l1_f32x4 *)(ss + row * L1_PITCH + 4 * cq) = v * L1_BIG;
         }
-#pragma unroll 4
+#pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int e = threadIdx.x + 256 * k;
-            // consecutive threads take consecutive negatives: the reads of S are coalesced either way
+            // consecutive threads take consecutive negatives: the reads of W are coalesced either way
             const int ol = OWN_Q ? e >> 5 : e & 127, sl = OWN_Q ? e & 31 : e >> 7;
             const int b = OWN_Q ? o0 + ol : s0 + sl, n = OWN_Q ? s0 + sl : o0 + ol;
-            float w = 0.f;
-            if (b < B && n < N) {
-                const float sc = S[(int64_t)b * ldS + n];
-                w = __builtin_amdgcn_exp2f(fmaf(sc, xscale, rowinfo[b].K));
-                if (loss == KGE_LOGSIGMOID) w *= l1_sigmoid(gamma + sc);
-            }
-            ws[sl * L1_WP + ol] = w;
+            wv[k] = b < B && n < N ? W[(int64_t)b * ldW + n] : 0.f;
         }
+    };
+    if (c_lo < c_hi) fetch(c_lo);
+    for (int ch = c_lo; ch < c_hi; ++ch) {
+        __syncthreads();                                    // everyone is done with the previous chunk
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int e = threadIdx.x + 256 * k, row = e >> 4, cq = e & 15;
+            l1_f32x4 v;
+            if constexpr (SBF)
+                v = l1_f32x4{__uint_as_float(raw[k][0] << 16), __uint_as_float(raw[k][0] & 0xffff0000u),
+                             __uint_as_float(raw[k][1] << 16), __uint_as_float(raw[k][1] & 0xffff0000u)};
+            else v = l1_f32x4{__uint_as_float(raw[k][0]), __uint_as_float(raw[k][1]), __uint_as_float(raw[k][2]), __uint_as_float(raw[k][3])};
+            *(l1_f32x4 *)(ss + row * L1_PITCH + 4 * cq) = v * L1_BIG;
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            const int ol = OWN_Q ? e >> 5 : e & 127, sl = OWN_Q ? e & 31 : e >> 7;
+            ws[sl * L1_WP + ol] = wv[k];
+        }
+        if (ch + 1 < c_hi) fetch(ch + 1);
         __syncthreads();
 #pragma unroll 4
         for (int sl = 0; sl < L1_GS; ++sl) {
@@ -368,15 +410,22 @@ __global__ __launch_bounds__(256) void l1h_grad_kernel(const float *Q, const flo
 
 }  // namespace
 
-int kge_run_l1_score(bool bf16, const float *Q, const void *T, int B, int N, int Bp, int Np, int dp, float *S, int64_t ldS,
+int kge_run_l1_score(bool bf16, const float *Q, const void *T, int B, int N, int Bp, int Np, int dp, int dim, float *S, int64_t ldS,
                      hipStream_t st) {
     if (Bp % L1_TILE || Np % L1_TILE || dp % L1_TILE) return KGE_E_INVALID_ARG;
     if (Bp == 0 || Np == 0) return KGE_OK;
     if (Bp / L1_TILE > 65535) return KGE_E_UNSUPPORTED;   // grid limit of the second dimension
     KgeProfScope prof(KGE_PROF_BLOCK_SCORE, st);
-    const dim3 grid(Np / L1_TILE, Bp / L1_TILE);
-    if (bf16) hipLaunchKernelGGL(l1_score_kernel<true>, grid, dim3(256), 0, st, Q, T, B, N, dp, S, ldS);
-    else      hipLaunchKernelGGL(l1_score_kernel<false>, grid, dim3(256), 0, st, Q, T, B, N, dp, S, ldS);
+    // (rows past B and N and columns past the dimension are padding: no workgroup takes a tile of them alone)
+    const int cols = (dim + L1_TILE - 1) / L1_TILE * L1_TILE, nt = (N + L1_TILE - 1) / L1_TILE;
+    // 64 x 64 tiles feed eight operations from every LDS read; 32 queries per tile where the others would not fill the chip twice
+    // (512 x 1,280 x 384: 22 us against 31)
+    const bool half = (int64_t)nt * ((B + 63) / 64) < 512;
+    const dim3 grid(nt, half ? (B + 31) / 32 : (B + 63) / 64);
+#define L1_SCORE(BF, QR) hipLaunchKernelGGL((l1_score_kernel<BF, QR>), grid, dim3(256), 0, st, Q, T, B, N, dp, cols, S, ldS)
+    if (bf16) { if (half) L1_SCORE(true, 2); else L1_SCORE(true, 4); }
+    else      { if (half) L1_SCORE(false, 2); else L1_SCORE(false, 4); }
+#undef L1_SCORE
     return kge_launch_status();
 }
 
@@ -390,16 +439,16 @@ int kge_l1_nsplit(int own_pad, int str_pad, int dp, bool transh) {
     return (chunks + cps - 1) / cps;
 }
 
-int kge_run_l1_grad(bool bf16, bool own_is_query, const void *own, const void *str, const float *S, int64_t ldS,
-                    const KgeRowInfo *rowinfo, int B, int N, int own_pad, int str_pad, int dp, int loss, float gamma,
-                    float adv_temp, int nsplit, float *acc_part, hipStream_t st) {
+int kge_run_l1_grad(bool bf16, bool own_is_query, const void *own, const void *str, const float *W, int64_t ldW, int B, int N, int own_pad,
+                    int str_pad, int dp, int dim, int nsplit, float *acc_part, hipStream_t st) {
     if (own_pad % L1_GO || str_pad % L1_GS || dp % L1_GD) return KGE_E_INVALID_ARG;
     if (nsplit <= 0 || nsplit != kge_l1_nsplit(own_pad, str_pad, dp, false)) return KGE_E_INVALID_ARG;
     KgeProfScope prof(own_is_query ? KGE_PROF_BLOCK_FWD : KGE_PROF_BLOCK_GRADT, st);
-    const int chunks = str_pad / L1_GS, cps = (chunks + nsplit - 1) / nsplit;
-    const dim3 grid(own_pad / L1_GO, dp / L1_GD, nsplit);
-#define L1_GRAD(BF, OQ) hipLaunchKernelGGL((l1_grad_kernel<BF, OQ>), grid, dim3(256), 0, st, own, str, S, ldS, rowinfo, B, N, \
-                                           own_pad, dp, chunks, cps, loss, gamma, adv_temp, acc_part)
+    // (the split count is that of the padded block, its work that of the rows and columns there are; a split past them writes zeros)
+    const int own_n = own_is_query ? B : N, str_n = own_is_query ? N : B;
+    const int chunks = (str_n + L1_GS - 1) / L1_GS, cps = (chunks + nsplit - 1) / nsplit;
+    const dim3 grid((own_n + L1_GO - 1) / L1_GO, (dim + L1_GD - 1) / L1_GD, nsplit);
+#define L1_GRAD(BF, OQ) hipLaunchKernelGGL((l1_grad_kernel<BF, OQ>), grid, dim3(256), 0, st, own, str, W, ldW, B, N, own_pad, dp, chunks, cps, acc_part)
     if (bf16) { if (own_is_query) L1_GRAD(true, true); else L1_GRAD(true, false); }
     else      { if (own_is_query) L1_GRAD(false, true); else L1_GRAD(false, false); }
 #undef L1_GRAD

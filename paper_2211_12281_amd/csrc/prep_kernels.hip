@@ -425,7 +425,8 @@ struct KgeTfinishArgs {
 
 // PB: the partials of the queries' gradient rows are bf16 in the paired-column words that the forward pass of
 // block_sym.hip writes (word lane + 64 kk of a row: columns lane + 128 kk and lane + 64 + 128 kk; rows of 256 columns)
-template <bool BF16, int SC, bool PB = false>
+// W4: the four waves of a workgroup share the splits of ONE row (each sums a quarter, in split order, the quarters in wave order)
+template <bool BF16, int SC, bool PB = false, bool W4 = false>
 __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
     const KgeModelDev &m = a.m;
     const int32_t *h = a.h, *r = a.r, *t = a.t;
@@ -436,8 +437,8 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
     float *g_ent = a.g_ent, *g_rel = a.g_rel, *g_relw = a.g_relw, *regv = a.regv;
     int32_t *g_ent_idx = a.g_ent_idx, *g_rel_idx = a.g_rel_idx;
     const float reg = a.reg;
-    const int lane = threadIdx.x & 63;
-    const int b = blk * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int b = W4 ? blk : blk * (blockDim.x >> 6) + wave;
     if (b >= B) return;
     const int d = m.dim, c = d >> 1;
     KgeRowCtx<BF16> cx;
@@ -466,19 +467,20 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
         tv[k] = j < d ? tj : 0.f;
         wt += cx.w[k] * tv[k];
     }
-    for (int s0 = 0; s0 < nsplit; s0 += 4) {
+    const int per = W4 ? (nsplit + 3) / 4 : nsplit, s_lo = W4 ? min(nsplit, wave * per) : 0, s_hi = W4 ? min(nsplit, s_lo + per) : nsplit;
+    for (int s0 = s_lo; s0 < s_hi; s0 += 4) {
         float kap[4], v1[4][KGE_MAXJ], v2[4][KGE_MAXJ];
         float4 p[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int s = s0 + u < nsplit ? s0 + u : nsplit - 1;      // past the end: the last split again, weight 0
-            kap[u] = s0 + u < nsplit ? kappa(s) : 0.f;
+            const int s = s0 + u < s_hi ? s0 + u : s_hi - 1;          // past the end: the last split again, weight 0
+            kap[u] = s0 + u < s_hi ? kappa(s) : 0.f;
             p[u] = m.vec ? make_float4(0.f, 0.f, 0.f, 0.f) : sum_part[(size_t)s * Bp + b];
 #pragma unroll
             for (int k = 0; k < KGE_MAXJ; ++k) {
                 v1[u][k] = v2[u][k] = 0.f;
                 if constexpr (PB) continue;
-                if (64 * k >= dp) continue;                // wave-uniform: the partial rows are dp columns long
+                if (64 * k >= d) continue;                 // wave-uniform: columns past the row (not every kernel writes them)
                 v1[u][k] = acc_part[((size_t)s * Bp + b) * dp + lane + 64 * k];
                 if (SC == KGE_TRANSH) v2[u][k] = acc_part2[((size_t)s * Bp + b) * dp + lane + 64 * k];
             }
@@ -495,6 +497,25 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
             s1 += kap[u] * p[u].x; s2 += kap[u] * p[u].y; s3 += kap[u] * p[u].z;
 #pragma unroll
             for (int k = 0; k < KGE_MAXJ; ++k) { a1[k] += kap[u] * v1[u][k]; a2[k] += kap[u] * v2[u][k]; }
+        }
+    }
+    if constexpr (W4) {
+        constexpr int NV = (SC == KGE_TRANSH ? 2 : 1) * KGE_MAXJ + 3;
+        __shared__ float quarter[3][NV * 64];
+        if (wave > 0) {
+            float *q = quarter[wave - 1] + lane;
+#pragma unroll
+            for (int k = 0; k < KGE_MAXJ; ++k) { q[64 * k] = a1[k]; if (SC == KGE_TRANSH) q[64 * (KGE_MAXJ + k)] = a2[k]; }
+            q[64 * (NV - 3)] = s1; q[64 * (NV - 2)] = s2; q[64 * (NV - 1)] = s3;
+        }
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int w = 0; w < 3; ++w) {
+            const float *q = quarter[w] + lane;
+#pragma unroll
+            for (int k = 0; k < KGE_MAXJ; ++k) { a1[k] += q[64 * k]; if (SC == KGE_TRANSH) a2[k] += q[64 * (KGE_MAXJ + k)]; }
+            s1 += q[64 * (NV - 3)]; s2 += q[64 * (NV - 2)]; s3 += q[64 * (NV - 1)];
         }
     }
     const bool mult = SC == KGE_DISTMULT || SC == KGE_COMPLEX;
@@ -628,6 +649,7 @@ __device__ __forceinline__ void kge_tfinish_body(int blk, const KgeTfinishArgs &
     if (n >= N) return;
     float cs = 0.f;
     if (dist_kind)
+#pragma unroll 4
         for (int s = 0; s < nsplit; ++s) cs += sumT_part[(size_t)s * Np + n].x;
     // A lane takes FOUR consecutive columns per step (d is a multiple of 4: a group lies inside the row or past its end),
     // so that a partial row is one 16-byte load per lane.  The row itself is read once (from the gathered copy when
@@ -660,22 +682,22 @@ __device__ __forceinline__ void kge_tfinish_body(int blk, const KgeTfinishArgs &
         const int j = 4 * (lane + 64 * k);
         if (j >= d) continue;
         float v[4] = {0.f, 0.f, 0.f, 0.f};
-        // two splits are requested together, then added in split order
-        for (int s0 = 0; s0 < nsplit; s0 += 2) {
-            const bool two = s0 + 1 < nsplit;
-            float4 p0, p1 = make_float4(0.f, 0.f, 0.f, 0.f);
-            if constexpr (PB) {
-                const uint16_t *pb = (const uint16_t *)accT_part;
-                const uint2 w0 = *(const uint2 *)(pb + ((size_t)s0 * Np + n) * dp + j);
-                const uint2 w1 = two ? *(const uint2 *)(pb + ((size_t)(s0 + 1) * Np + n) * dp + j) : make_uint2(0u, 0u);
-                p0 = make_float4(__uint_as_float(w0.x << 16), __uint_as_float(w0.x & 0xFFFF0000u), __uint_as_float(w0.y << 16), __uint_as_float(w0.y & 0xFFFF0000u));
-                p1 = make_float4(__uint_as_float(w1.x << 16), __uint_as_float(w1.x & 0xFFFF0000u), __uint_as_float(w1.y << 16), __uint_as_float(w1.y & 0xFFFF0000u));
-            } else {
-                p0 = *(const float4 *)(accT_part + ((size_t)s0 * Np + n) * dp + j);
-                if (two) p1 = *(const float4 *)(accT_part + ((size_t)(s0 + 1) * Np + n) * dp + j);
+        // four splits are requested together, then added in split order
+        for (int s0 = 0; s0 < nsplit; s0 += 4) {
+            float4 p[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (s0 + u >= nsplit) break;                    // (the same for every lane)
+                if constexpr (PB) {
+                    const uint2 w = *(const uint2 *)((const uint16_t *)accT_part + ((size_t)(s0 + u) * Np + n) * dp + j);
+                    p[u] = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xFFFF0000u));
+                } else p[u] = *(const float4 *)(accT_part + ((size_t)(s0 + u) * Np + n) * dp + j);
             }
-            v[0] += p0.x; v[1] += p0.y; v[2] += p0.z; v[3] += p0.w;
-            if (two) { v[0] += p1.x; v[1] += p1.y; v[2] += p1.z; v[3] += p1.w; }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (s0 + u >= nsplit) break;
+                v[0] += p[u].x; v[1] += p[u].y; v[2] += p[u].z; v[3] += p[u].w;
+            }
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -694,13 +716,13 @@ template <bool BF16, int SC>
 __global__ __launch_bounds__(256) void kge_chain_kernel(KgeChainArgs a) { kge_chain_body<BF16, SC>(blockIdx.x, a); }
 // both finishing kernels in ONE launch (the first chain_blocks workgroups run the chain rule of the queries): they
 // read different partials and write different gradient rows
-template <bool BF16, int SC, bool PB = false>
+template <bool BF16, int SC, bool PB = false, bool W4 = false>
 __global__ __launch_bounds__(256) void kge_chain_tfinish_kernel(int chain_blocks, KgeChainArgs c, KgeTfinishArgs t, const float *lossb, float scale,
                                          float *loss_out) {
     // (workgroup 0: the loss of the batch from the rows' losses, the reduction that would otherwise be a launch
     // of its own between the two passes)
     if (blockIdx.x == 0) kge_loss_reduce_body(lossb, c.B, scale, loss_out);
-    else if ((int)blockIdx.x <= chain_blocks) kge_chain_body<BF16, SC, PB>(blockIdx.x - 1, c);
+    else if ((int)blockIdx.x <= chain_blocks) kge_chain_body<BF16, SC, PB, W4>(blockIdx.x - 1, c);
     else kge_tfinish_body<BF16, PB>(blockIdx.x - 1 - chain_blocks, t);
 }
 
@@ -860,7 +882,11 @@ int kge_run_chain_tfinish(const KgeModelDev &m, const int32_t *h, const int32_t 
                           const void *T, const int32_t *neg, float *g_neg, int32_t *g_neg_idx, float *regn,
                           const float *lossb, float scale, float *loss_out, hipStream_t st, bool part_bf16, bool finished) {
     if (B == 0 || N == 0) return KGE_E_INVALID_ARG;
-    const int cb = (B + 3) / 4, tb = (N + 3) / 4;
+    // More than eight splits and a wave waits for several groups of partials one after the other: up to 1,024 rows the four waves of a
+    // workgroup share them (TransH fp32 512 x 1,024 x 128, 64 splits: whole call 96 -> 85 us; 2,048 x 4,096, 16 splits: 216 without,
+    // 236 with - there the rows alone fill the chip).
+    const bool w4 = nsplit > 8 && B <= 1024 && !part_bf16;
+    const int cb = w4 ? B : (B + 3) / 4, tb = (N + 3) / 4;
     const KgeChainArgs a{m, h, r, t, B, Bp, dp, acc_part, acc_part2, sum_part, stat_part, rowinfo, nsplit, gpos,
                          g_ent, g_rel, g_relw, g_ent_idx, g_rel_idx, reg, regv, finished ? 1 : 0};
     const KgeTfinishArgs f{accT_part, sumT_part, nsplit_t, Np, N, dp, d, dist_kind, T, neg, g_neg, g_neg_idx, m.ent, m.ent_ld, reg, regn};
@@ -873,7 +899,8 @@ int kge_run_chain_tfinish(const KgeModelDev &m, const int32_t *h, const int32_t 
             hipLaunchKernelGGL((kge_chain_tfinish_kernel<true, KGE_COMPLEX, true>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out);
         return kge_launch_status();
     }
-#define KGE_CT(BF, SC) hipLaunchKernelGGL((kge_chain_tfinish_kernel<BF, SC>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out)
+#define KGE_CT(BF, SC) do { if (w4) hipLaunchKernelGGL((kge_chain_tfinish_kernel<BF, SC, false, true>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out); \
+                            else hipLaunchKernelGGL((kge_chain_tfinish_kernel<BF, SC>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out); } while (0)
     if (m.bf16) { KGE_SC_SWITCH(true, KGE_CT) } else { KGE_SC_SWITCH(false, KGE_CT) }
 #undef KGE_CT
     return kge_launch_status();

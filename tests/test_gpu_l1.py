@@ -113,6 +113,16 @@ def test_other_row_sizes_and_shapes(orc, dim, bf16):
         _compare(orc, "transe", "logsigmoid", G, bf16, 3000, dict(gamma=0.35 * dim, adv_temp=0.2, loss_scale=0.37))
 
 
+@pytest.mark.parametrize("dim,bf16,B,N", [
+    (72, False, 1440, 1473), (64, True, 1408, 1472),     # score tiles of 64 queries (the sizes above take tiles of 32) and the last of the others
+    (136, False, 257, 1300),                             # columns past the row in its last tile; rows past the block in its last tiles
+    (32, True, 1024, 40), (32, True, 1025, 40)])         # four waves per row in the chain rule, and one
+def test_tiles_and_their_edges(orc, dim, bf16, B, N):
+    G = _grid_case("transe", 3000, 9, dim, B, N, False)
+    _compare(orc, "transe", "sampled_softmax", G, bf16, 3000, dict(n_ent_for_c=3000))
+    _compare(orc, "transe", "logsigmoid", G, bf16, 3000, dict(gamma=0.35 * dim, adv_temp=0.2, loss_scale=0.37))
+
+
 def test_regulariser_and_repeatability(orc):
     import paper_2211_12281_amd as kge
     G = _grid_case("transe", 2000, 5, 64, 96, 200, True)
