@@ -4,11 +4,15 @@
 // "Regularisation").  The projection of the 2B + N gathered slots is the second dense contraction of
 // the paper's cost model, (B + N) |e_F| d (Section 4.1), and so is its backward pass to M_H, M_T.
 //
-// Both contractions run through ONE matrix-core kernel, C[M, N] = A[M, K] . B[N, K]^t with both operands
-// contiguous along K (so that an MFMA fragment is one 16-byte load per lane and no LDS staging is needed):
-//   forward    P[slot, d]  = F[idx[slot], :] . M[d, :]^t          (A rows gathered through the index array)
-//   backward   G[d, f]     = dP^t[d, slots] . F^t[f, slots]^t     (transposed copies written by the row kernels;
-//                                                                   split over the slots, partials summed in order)
+//   forward    P[slot, d]  = F[idx[slot], :] . M[d, :]^t     both operands contiguous along the contraction (enc_gemm_nt_kernel);
+//                                                            the feature rows are gathered by the copies into the LDS
+//   backward   G[d, f]     = sum over slots of dP[slot, d] F[idx[slot], f]     both operands contiguous ACROSS it
+//                                                            (enc_gemm_tn_kernel): rows are copied into the LDS as they lie - the
+//                                                            feature rows again straight from the table - and read transposed;
+//                                                            split over the slots, partials summed in order
+// (The backward contraction used to run on transposed copies of both operands: writing them took 39 us of gather, 9 us of zeroing their
+// padding and the detour of the row kernel through the LDS, against 22 us for the contraction itself; 24,576 slots,
+// 768 x 256, bf16: encode + encode_bwd 182 -> 94 us.)
 #include "kge_internal.h"
 #include "row_ops.hpp"
 
@@ -34,17 +38,16 @@ __device__ __forceinline__ enc_f32x16 enc_mma16(enc_f32x16 acc, enc_u32x4 a, enc
     }
 }
 
-// One contraction C[split][M, N] (fp32) = A[M, K] . B[N, K]^t, K counted in k-steps of 32 bytes of a row (16 bf16
-// or 8 fp32).  Rows at or beyond m_valid / n_valid read as zero.  A's row r is table row idx0[r] for r < n_idx0,
-// idx1[r - n_idx0] beyond (gather == 0: row r itself): the gather of the feature rows is part of the load.
+// One contraction C[M, N] (fp32) = A[M, K] . B[N, K]^t, K counted in k-steps of 32 bytes of a row (16 bf16 or 8 fp32).
+// A's row r is table row idx0[r] for r < n_idx0, idx1[r - n_idx0] beyond: the gather of the feature rows is part of the load.
 struct EncGemm {
-    const char *A; int64_t lda_b; const int32_t *idx0, *idx1; int n_idx0; int gather; int m_valid;
+    const char *A; int64_t lda_b; const int32_t *idx0, *idx1; int n_idx0, m_valid;
     const char *B; int64_t ldb_b; int n_valid;
-    float *C; int64_t ldc, split_stride;
-    int ksteps, kps, nsplit, tiles_m, tiles_n;
+    float *C; int64_t ldc;
+    int ksteps, tiles_m, tiles_n;
 };
 // A launch runs two contractions (heads against M_H, tails and negatives against M_T) so that the chip is filled
-// once; work items enumerate (contraction, split, row tile, column tile), column tile fastest.
+// once; work items enumerate (contraction, row tile, column tile), column tile fastest.
 struct EncGemmPair { EncGemm g[2]; int wgs0, total; };
 
 constexpr int ENC_NSTAGE = 4;                                // chunks resident in the LDS ring
@@ -88,11 +91,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bool second = w >= pr.wgs0;
     const EncGemm &q = pr.g[second ? 1 : 0];
     w -= second ? pr.wgs0 : 0;
-    const int tn = w % q.tiles_n; w /= q.tiles_n;
-    const int tm = w % q.tiles_m, split = w / q.tiles_m;
-    const int m0 = tm * ENC_TILE, n0 = tn * ENC_TILE;
-    const int k_lo = split * q.kps, k_hi = min(q.ksteps, k_lo + q.kps);
-    const int nfull = (k_hi - k_lo) >> 1, rem = (k_hi - k_lo) & 1;
+    const int m0 = w / q.tiles_n * ENC_TILE, n0 = w % q.tiles_n * ENC_TILE;
+    const int nfull = q.ksteps >> 1, rem = q.ksteps & 1;
     // staging: copy j (j < 2) of wave v fills rows 32 v + 16 j .. + 15 of a tile; this lane's row and piece
     const int srow = lane >> 2, piece = (lane & 3) ^ ((srow >> 1) & 3);
     const char *ga[2], *gb[2];
@@ -100,9 +100,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int j = 0; j < 2; ++j) {
         const int ra = m0 + 32 * wave + 16 * j + srow, rb = n0 + 32 * wave + 16 * j + srow;
         int64_t src = 0;
-        if (ra < q.m_valid) src = q.gather ? (ra < q.n_idx0 ? (int64_t)q.idx0[ra] : (int64_t)q.idx1[ra - q.n_idx0]) : (int64_t)ra;
-        ga[j] = q.A + src * q.lda_b + piece * 16 + (int64_t)k_lo * 32;
-        gb[j] = q.B + (int64_t)(rb < q.n_valid ? rb : 0) * q.ldb_b + piece * 16 + (int64_t)k_lo * 32;
+        if (ra < q.m_valid) src = ra < q.n_idx0 ? (int64_t)q.idx0[ra] : (int64_t)q.idx1[ra - q.n_idx0];
+        ga[j] = q.A + src * q.lda_b + piece * 16;
+        gb[j] = q.B + (int64_t)(rb < q.n_valid ? rb : 0) * q.ldb_b + piece * 16;
     }
     // the row indices must have arrived before the loop: a compiler-inserted wait inside it would drain the ring
 #pragma unroll
@@ -166,7 +166,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         compute(0);
     }
     // accumulator layout: lane holds column lr of the B side; register e holds A-side row 8 (e/4) + 4 g + e%4
-    float *Cs = q.C + (int64_t)split * q.split_stride;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -175,7 +174,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int row = m0 + wm + 32 * i + 8 * (e >> 2) + 4 * g + (e & 3);
-                if (row < q.m_valid && col < q.n_valid) Cs[(int64_t)row * q.ldc + col] = acc[i][j][e];
+                if (row < q.m_valid && col < q.n_valid) q.C[(int64_t)row * q.ldc + col] = acc[i][j][e];
             }
         }
 }
@@ -186,56 +185,99 @@ __device__ __forceinline__ void enc_philox_round(uint32_t (&c)[4], uint32_t k0, 
     const uint32_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
     c[0] = n0; c[1] = lo1; c[2] = n2; c[3] = lo0;
 }
-// dropout factor of element (slot, column): counter (slot, column / 4, step, tag), word column % 4; kept when
-// the word is >= thr = floor(p 2^32), then scaled by 1 / (1 - p)
-__device__ __forceinline__ float enc_dropout(uint32_t seed_lo, uint32_t seed_hi, uint32_t step, uint32_t tag, uint32_t slot,
-                                             int col, uint32_t thr, float scale) {
-    if (thr == 0u) return 1.f;
+// dropout factors of elements (slot, column .. column + 3), column a multiple of four: counter (slot, column / 4, step, tag), word
+// column % 4; kept when the word is >= thr = floor(p 2^32), then scaled by 1 / (1 - p).  (One generator block for four columns: with a
+// block per element the row kernels were bound by its integer multiplications, 23 and 40 us where these take 13 and 20.)
+__device__ __forceinline__ void enc_dropout4(uint32_t seed_lo, uint32_t seed_hi, uint32_t step, uint32_t tag, uint32_t slot, int col,
+                                             uint32_t thr, float scale, float (&f)[4]) {
+    if (thr == 0u) { f[0] = f[1] = f[2] = f[3] = 1.f; return; }
     uint32_t c[4] = { slot, (uint32_t)(col >> 2), step, tag };
     uint32_t k0 = seed_lo, k1 = seed_hi;
 #pragma unroll
     for (int r = 0; r < 10; ++r) { enc_philox_round(c, k0, k1); k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
-    return c[col & 3] >= thr ? scale : 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f[u] = c[u] >= thr ? scale : 0.f;
 }
 
 struct EncRowArgs {
     const void *ent_s; int64_t ent_ld; const int32_t *h, *t, *neg; int B, N, d;
     uint32_t seed_lo, seed_hi, step, tag, thr; float scale, reg_t, reg_s, reg_f;
+    int wide;                                              // every row of every operand starts where four elements load and store at once
 };
+// four consecutive elements of a row
+template <bool BF16> __device__ __forceinline__ void enc_ld4(const void *p, int64_t i, bool wide, float (&v)[4]) {
+    if (wide) {
+        if constexpr (BF16) {
+            const uint2 r = *(const uint2 *)((const __bf16 *)p + i);
+            v[0] = __uint_as_float(r.x << 16); v[1] = __uint_as_float(r.x & 0xffff0000u);
+            v[2] = __uint_as_float(r.y << 16); v[3] = __uint_as_float(r.y & 0xffff0000u);
+        } else { const enc_f32x4 r = *(const enc_f32x4 *)((const float *)p + i); v[0] = r[0]; v[1] = r[1]; v[2] = r[2]; v[3] = r[3]; }
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = El<BF16>::ld(p, i + u);
+    }
+}
+template <bool BF16> __device__ __forceinline__ void enc_st4(void *p, int64_t i, bool wide, const float (&v)[4]) {
+    if (wide) {
+        if constexpr (BF16) {
+            typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf4;
+            const bf4 r = { (__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3] };
+            *(uint2 *)((__bf16 *)p + i) = __builtin_bit_cast(uint2, r);
+        } else *(enc_f32x4 *)((float *)p + i) = enc_f32x4{v[0], v[1], v[2], v[3]};
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) El<BF16>::st(p, i + u, v[u]);
+    }
+}
 __device__ __forceinline__ int enc_slot_entity(const EncRowArgs &a, int i) {
     return i < a.B ? a.h[i] : (i < 2 * a.B ? a.t[i - a.B] : a.neg[i - 2 * a.B]);
 }
 __device__ __forceinline__ float enc_l3(float c3) { return cbrtf(kge_wave_sum(c3)); }
 
-// forward rows: e = s + D o P, the three norms of the slot; one wave per slot, lane holds columns lane + 64 k
+// forward rows: e = s + D o P, the three norms of the slot; one wave per slot, a lane holds columns 4 lane + 256 k .. + 3; regv: one
+// sum per workgroup of four slots
+constexpr int ENC_G4 = 2;                                  // groups of four columns per lane (d <= 512)
 template <bool BF16>
-__global__ void enc_finish_kernel(EncRowArgs a, const float *P, void *e_out, float *regv) {
-    const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (i >= 2 * a.B + a.N) return;
-    const int64_t soff = (int64_t)enc_slot_entity(a, i) * a.ent_ld;
-    float ct = 0.f, cs = 0.f, cf = 0.f;
-    for (int j = lane; j < a.d; j += 64) {
-        const float p = P[(int64_t)i * a.d + j], s = El<BF16>::ld(a.ent_s, soff + j);
-        const float e = s + enc_dropout(a.seed_lo, a.seed_hi, a.step, a.tag, (uint32_t)i, j, a.thr, a.scale) * p;
-        El<BF16>::st(e_out, (int64_t)i * a.d + j, e);
-        ct += fabsf(e) * e * e; cs += fabsf(s) * s * s; cf += fabsf(p) * p * p;
+__global__ __launch_bounds__(256) void enc_finish_kernel(EncRowArgs a, const float *P, void *e_out, double *regv) {
+    __shared__ float part[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = blockIdx.x * 4 + wave;
+    const bool reg = a.reg_t > 0.f || a.reg_s > 0.f || a.reg_f > 0.f, wide = a.wide != 0;
+    float v = 0.f;
+    if (i < 2 * a.B + a.N) {
+        const int64_t soff = (int64_t)enc_slot_entity(a, i) * a.ent_ld, off = (int64_t)i * a.d;
+        float ct = 0.f, cs = 0.f, cf = 0.f;
+#pragma unroll
+        for (int k = 0; k < ENC_G4; ++k) {
+            const int j = 4 * lane + 256 * k;
+            if (j >= a.d) continue;
+            float p[4], s[4], D[4], e[4];
+            enc_ld4<false>(P, off + j, wide, p);
+            enc_ld4<BF16>(a.ent_s, soff + j, wide, s);
+            enc_dropout4(a.seed_lo, a.seed_hi, a.step, a.tag, (uint32_t)i, j, a.thr, a.scale, D);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                e[u] = s[u] + D[u] * p[u];
+                ct += fabsf(e[u]) * e[u] * e[u]; cs += fabsf(s[u]) * s[u] * s[u]; cf += fabsf(p[u]) * p[u] * p[u];
+            }
+            enc_st4<BF16>(e_out, off + j, wide, e);
+        }
+        if (reg) v = a.reg_t * enc_l3(ct) + a.reg_s * enc_l3(cs) + a.reg_f * enc_l3(cf);
     }
-    const bool reg = a.reg_t > 0.f || a.reg_s > 0.f || a.reg_f > 0.f;
-    if (reg) {
-        const float v = a.reg_t * enc_l3(ct) + a.reg_s * enc_l3(cs) + a.reg_f * enc_l3(cf);
-        if (lane == 0) regv[i] = v;
-    }
+    if (!reg) return;
+    if (lane == 0) part[wave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) regv[blockIdx.x] = ((double)part[0] + (double)part[1]) + ((double)part[2] + (double)part[3]);
 }
 
-// reg_out = sum of regv in a fixed order (one workgroup)
-__global__ void enc_reg_reduce_kernel(const float *regv, int n, int on, float *reg_out) {
+// reg_out = sum of the workgroups' sums in a fixed order (one workgroup)
+__global__ void enc_reg_reduce_kernel(const double *regv, int n, int on, float *reg_out) {
     __shared__ double sh[1024];
     double p[4] = {0, 0, 0, 0};
     if (on)
         for (int i0 = threadIdx.x; i0 < n; i0 += 4 * 1024)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { const int i = i0 + u * 1024; p[u] += i < n ? (double)regv[i] : 0.0; }
+            for (int u = 0; u < 4; ++u) { const int i = i0 + u * 1024; p[u] += i < n ? regv[i] : 0.0; }
     sh[threadIdx.x] = (p[0] + p[1]) + (p[2] + p[3]);
     __syncthreads();
     for (int o = 512; o > 0; o >>= 1) {
@@ -245,183 +287,242 @@ __global__ void enc_reg_reduce_kernel(const float *regv, int n, int on, float *r
     if (threadIdx.x == 0) *reg_out = (float)sh[0];
 }
 
-// Transposed buffers of the backward pass: columns [0, Bh) hold the head slots (Bh = B padded to a tile), columns
-// [Bh, Bh + B + N) the tail and negative slots - the two groups contract against different projection matrices.
-// The row kernels below work on groups of 32 slots that never straddle the two sections: workgroup w takes head
-// slots 32 w .. if w < ceil(B / 32), else tail-section slots 32 (w - ceil(B / 32)) ..
-struct EncGroup { int slot0, count, col0; };      // first slot, valid slots (<= 32), first column
-__device__ __forceinline__ EncGroup enc_group(int w, int B, int N, int Bh) {
-    const int hg = (B + 31) / 32;
-    EncGroup gr;
-    if (w < hg) { gr.slot0 = 32 * w; gr.count = min(32, B - gr.slot0); gr.col0 = gr.slot0; }
-    else { const int o = 32 * (w - hg); gr.slot0 = B + o; gr.count = min(32, B + N - o); gr.col0 = Bh + o; }
-    return gr;
+// backward rows, one wave per slot: de' = de + reg_t grad||e||, g_es = de' + reg_s grad||s||, dP = D o de' + reg_f grad||P||; dP in the
+// table type, row by row (16 bytes per lane's group; the rows start 16-byte aligned).  Workgroup 0 also writes the zero bytes that the
+// contraction reads where there is no element.
+template <bool BF16>
+__global__ __launch_bounds__(256) void enc_bwd_rows_kernel(EncRowArgs a, const float *P, const float *de, float *g_es, void *dP, uint32_t *zeros) {
+    const int lane = threadIdx.x & 63;
+    if (blockIdx.x == 0 && threadIdx.x < 64) zeros[threadIdx.x] = 0u;
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= 2 * a.B + a.N) return;
+    const bool wide = a.wide != 0;
+    const int64_t soff = (int64_t)enc_slot_entity(a, i) * a.ent_ld, off = (int64_t)i * a.d;
+    float pv[ENC_G4][4], sv[ENC_G4][4], ev[ENC_G4][4], dv[ENC_G4][4], Df[ENC_G4][4];
+    float ct = 0.f, cs = 0.f, cf = 0.f;
+#pragma unroll
+    for (int k = 0; k < ENC_G4; ++k) {
+        const int j = 4 * lane + 256 * k;
+        if (j >= a.d) continue;
+        enc_ld4<false>(P, off + j, wide, pv[k]);
+        enc_ld4<BF16>(a.ent_s, soff + j, wide, sv[k]);
+        enc_ld4<false>(de, off + j, wide, dv[k]);
+        enc_dropout4(a.seed_lo, a.seed_hi, a.step, a.tag, (uint32_t)i, j, a.thr, a.scale, Df[k]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float e = sv[k][u] + Df[k][u] * pv[k][u];
+            ev[k][u] = e;
+            ct += fabsf(e) * e * e; cs += fabsf(sv[k][u]) * sv[k][u] * sv[k][u]; cf += fabsf(pv[k][u]) * pv[k][u] * pv[k][u];
+        }
+    }
+    float ft = 0.f, fs = 0.f, ff = 0.f;
+    if (a.reg_t > 0.f) { const float nrm = enc_l3(ct); ft = nrm > 0.f ? a.reg_t / (nrm * nrm) : 0.f; }
+    if (a.reg_s > 0.f) { const float nrm = enc_l3(cs); fs = nrm > 0.f ? a.reg_s / (nrm * nrm) : 0.f; }
+    if (a.reg_f > 0.f) { const float nrm = enc_l3(cf); ff = nrm > 0.f ? a.reg_f / (nrm * nrm) : 0.f; }
+#pragma unroll
+    for (int k = 0; k < ENC_G4; ++k) {
+        const int j = 4 * lane + 256 * k;
+        if (j >= a.d) continue;
+        float gs[4], dp[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float dep = dv[k][u] + ft * fabsf(ev[k][u]) * ev[k][u];
+            gs[u] = dep + fs * fabsf(sv[k][u]) * sv[k][u];
+            dp[u] = Df[k][u] * dep + ff * fabsf(pv[k][u]) * pv[k][u];
+        }
+        enc_st4<false>(g_es, off + j, wide, gs);
+        enc_st4<BF16>(dP, off + j, true, dp);
+    }
 }
 
-// 32 x len tile (fp32 in the LDS, row stride len + 1) -> rows of the transposed buffer, 8 columns per store
+// One section (heads against M_H, or tails and negatives against M_T) of the backward contraction, C[split][d, fd] (fp32) =
+// sum over the split's slots of A[slot, d] F[id(slot), fd]; slot s of the section is entity ids0[s] (s < n0) or ids1[s - n0].
+struct EncTn { const char *A; const int32_t *ids0, *ids1; int n0, slots; float *C; };
+struct EncTnPair { EncTn g[2]; const char *feat; int64_t ldf_b; int d, fd, sps, tiles_m, tiles_n, wgs0, total; const void *zeros; };
+
+// Workgroup = 128 x 128 outputs, wave = 64 x 64; both operands come into the LDS as rows of 128 columns, in chunks of 8 KB per operand
+// (32 slots bf16, 16 fp32) through the same ring as above.  bf16: a fragment holds eight slots of one column, which the LDS transpose
+// read (ds_read_b64_tr_b16) makes of four 8-byte pieces of four rows; the 16-byte pieces of a row are XOR-swizzled by 4 (row % 4) so that
+// the four rows of a read lie in different quarters of the banks.  fp32: a lane reads single values (one slot, consecutive columns
+// across the lanes), pieces swizzled by 8 (row % 2).  The ids of the split's slots are fetched into the LDS first: a load in the loop
+// would wait for the copies in flight.  Columns past d or fd and slots past the section read zero bytes.
+constexpr int ENC_MAX_SPS = 1024;                            // slots per split at most
+constexpr int ENC_TN_WGS = 512;                              // (encode + encode_bwd, 24,576 slots x 768 x 256: bf16 84 us with 512 as with 384, fp32 237 / 259; 256: 86 / 285)
 template <bool BF16>
-__device__ __forceinline__ void enc_write_transposed(const float *tile, int ldt, int len, void *dst, int64_t ncols,
-                                                      const EncGroup &gr) {
-    // element (j, 8 q .. 8 q + 7): one 16-byte (bf16) or two 16-byte (fp32) stores; columns past the group's count
-    // are padding or belong to nobody (they stay zero / are written as zero)
-    for (int idx = threadIdx.x; idx < len * 4; idx += 256) {
-        const int j = idx >> 2, q = idx & 3;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void enc_gemm_tn_kernel(const EncTnPair pr) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int ES = BF16 ? 2 : 4, RBY = 128 * ES, CH = ENC_HALF_BYTES / RBY, LPR = RBY / 16, RPI = 64 / LPR;   // row bytes, slots per chunk, lanes per row, rows per copy
+    static_assert(CH == 8 * RPI, "eight copies per operand and chunk");
+    int32_t *ids = (int32_t *)(lds + ENC_LDS_BYTES);         // [ENC_MAX_SPS]
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, g = lane >> 5;
+    const int per = (pr.total + 7) >> 3;
+    int w = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+    if (w >= pr.total || ((int)blockIdx.x >> 3) >= per) return;
+    const bool second = w >= pr.wgs0;
+    const EncTn &q = pr.g[second ? 1 : 0];
+    w -= second ? pr.wgs0 : 0;
+    const int tn = w % pr.tiles_n; w /= pr.tiles_n;
+    const int tm = w % pr.tiles_m, split = w / pr.tiles_m;
+    const int m0 = tm * ENC_TILE, n0 = tn * ENC_TILE;
+    const int s_lo = split * pr.sps, s_hi = min(q.slots, s_lo + pr.sps), nch = (s_hi - s_lo + CH - 1) / CH;
+    for (int i = tid; i < nch * CH; i += 256) {
+        const int sl = s_lo + i;
+        ids[i] = sl < s_hi ? (sl < q.n0 ? q.ids0[sl] : q.ids1[sl - q.n0]) : -1;
+    }
+    __syncthreads();
+    // copy j (j < 2) of wave v fills rows (2 v + j) RPI .. of a chunk; this lane's row of a copy and its piece of the row
+    const int srow = lane / LPR;
+    int piece[2];
+    bool in_a[2], in_b[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int row = (2 * wave + j) * RPI + srow;
+        piece[j] = (lane % LPR) ^ (BF16 ? (row & 3) << 2 : (row & 1) << 3);
+        in_a[j] = m0 + piece[j] * (16 / ES) < pr.d;          // (d and fd are multiples of a piece)
+        in_b[j] = n0 + piece[j] * (16 / ES) < pr.fd;
+    }
+    const char *fa = pr.feat + (int64_t)n0 * ES, *aa = q.A + (int64_t)m0 * ES;
+    auto issue = [&](int c) {                                // chunk min(c, nch - 1) -> stage c % ENC_NSTAGE
+        const int cc = min(c, nch - 1);
+        const uint32_t sb = lds0 + (uint32_t)(c & (ENC_NSTAGE - 1)) * ENC_STAGE_BYTES + (uint32_t)wave * 2048;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int row = cc * CH + (2 * wave + j) * RPI + srow, id = ids[row];
+            const void *pa = id >= 0 && in_a[j] ? (const void *)(aa + (int64_t)(s_lo + row) * pr.d * ES + piece[j] * 16) : pr.zeros;
+            const void *pb = id >= 0 && in_b[j] ? (const void *)(fa + (int64_t)id * pr.ldf_b + piece[j] * 16) : pr.zeros;
+            enc_async_copy16(pa, __builtin_amdgcn_readfirstlane(sb + j * 1024));
+            enc_async_copy16(pb, __builtin_amdgcn_readfirstlane(sb + ENC_HALF_BYTES + j * 1024));
+        }
+    };
+    enc_f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 2; ++j)
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64;
+    auto compute = [&](int stage) {
+        const char *sa = lds + stage * ENC_STAGE_BYTES, *sb = sa + ENC_HALF_BYTES;
+        if constexpr (BF16) {
+            typedef short i16x4 __attribute__((ext_vector_type(4)));
+            const int i16 = lane & 15, q16 = (lane >> 4) & 1;
+            // source lane i16 of a group of sixteen points at row 16 ks + 8 g + 4 hh + i16 / 4, columns .. + 16 q16 + 4 (i16 % 4) .. + 3 and
+            // receives column .. + lane % 32 of the rows 16 ks + 8 g + 4 hh .. + 3
+            auto frag = [&](const char *s, int c0, int ks) {
+                const int pc = (c0 / 8 + 2 * q16 + ((i16 & 3) >> 1)) ^ ((i16 >> 2) << 2);
+                const char *p = s + (16 * ks + 8 * g + (i16 >> 2)) * RBY + pc * 16 + (i16 & 1) * 8;
+                const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3))) *)p));
+                const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3))) *)(p + 4 * RBY)));
+                return enc_u32x4{lo.x, lo.y, hi.x, hi.y};
+            };
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                enc_u32x4 xa[2], xb[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) { xa[i] = frag(sa, wm + 32 * i, ks); xb[i] = frag(sb, wn + 32 * i, ks); }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = enc_mma16<true>(acc[i][j], xa[i], xb[j]);
+            }
+        } else {
+            auto val = [&](const char *s, int c0, int kk) {  // slot 2 kk + g, column c0 + lane % 32
+                return *(const float *)(s + (2 * kk + g) * RBY + ((((c0 + lr) >> 2) ^ (g << 3)) * 16) + (lr & 3) * 4);
+            };
+#pragma unroll
+            for (int kk = 0; kk < CH / 2; ++kk) {
+                float xa[2], xb[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) { xa[i] = val(sa, wm + 32 * i, kk); xb[i] = val(sb, wn + 32 * i, kk); }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i], xb[j], acc[i][j], 0, 0, 0);
+            }
+        }
+    };
+    for (int c = 0; c < ENC_NSTAGE - 1; ++c) issue(c);
+    for (int c = 0; c < nch; ++c) {
+        enc_wait_vmcnt<(ENC_NSTAGE - 2) * ENC_LPW>();
+        __syncthreads();                                     // chunk c is complete; everyone is done with chunk c - 1
+        issue(c + ENC_NSTAGE - 1);                           // ... whose stage is refilled (past the end: a harmless repeat)
+        compute(c & (ENC_NSTAGE - 1));
+    }
+    enc_wait_vmcnt<0>();                                     // no copy may be in flight when the LDS is released
+    float *Cs = q.C + (int64_t)split * pr.d * pr.fd;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int col = n0 + wn + 32 * j + lr;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int row = m0 + wm + 32 * i + 8 * (e >> 2) + 4 * g + (e & 3);
+                if (row < pr.d && col < pr.fd) Cs[(int64_t)row * pr.fd + col] = acc[i][j][e];
+            }
+        }
+}
+
+// out[e] = sum over the splits, in split order; both projections in one launch
+__global__ void enc_split_reduce_kernel(const float *part, int nsplit_h, int nsplit_t, int64_t count, float *g_mh, float *g_mt) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 2 * count) return;
+    const bool tail = i >= count;
+    i -= tail ? count : 0;
+    const float *p = part + (tail ? (int64_t)nsplit_h * count : 0) + i;
+    const int n = tail ? nsplit_t : nsplit_h;
+    float s = 0.f;
+    int k = 0;
+    for (; k + 8 <= n; k += 8) {                             // eight loads in flight
         float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = (8 * q + u < gr.count) ? tile[(8 * q + u) * ldt + j] : 0.f;
-        if (8 * q >= gr.count) continue;
-        char *p = (char *)dst + ((int64_t)j * ncols + gr.col0 + 8 * q) * (BF16 ? 2 : 4);
-        if constexpr (BF16) {
-            typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf2;
-            enc_u32x4 o;
+        for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(k + u) * count];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { bf2 t = { (__bf16)v[2 * u], (__bf16)v[2 * u + 1] }; o[u] = __builtin_bit_cast(uint32_t, t); }
-            *(enc_u32x4 *)p = o;
-        } else {
-            *(enc_f32x4 *)p = enc_f32x4{v[0], v[1], v[2], v[3]};
-            *(enc_f32x4 *)(p + 16) = enc_f32x4{v[4], v[5], v[6], v[7]};
-        }
+        for (int u = 0; u < 8; ++u) s += v[u];
     }
+    for (; k < n; ++k) s += p[(int64_t)k * count];
+    (tail ? g_mt : g_mh)[i] = s;
 }
 
-// backward rows (a workgroup takes a group of 32 slots, a wave 8 of them in turn): de' = de + reg_t grad||e||,
-// g_es = de' + reg_s grad||s||, dP = D o de' + reg_f grad||P||; dP leaves through the LDS as dP^t[d][columns]
-template <bool BF16>
-__global__ __launch_bounds__(256) void enc_bwd_rows_kernel(EncRowArgs a, const float *P, const float *de, float *g_es,
-                                                           void *dPt, int Bh, int64_t ncols) {
-    extern __shared__ float tile[];                        // [32][d + 1]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const EncGroup gr = enc_group(blockIdx.x, a.B, a.N, Bh);
-    const int ldt = a.d + 1;
-    for (int r = wave; r < gr.count; r += 4) {
-        const int i = gr.slot0 + r;
-        const int64_t soff = (int64_t)enc_slot_entity(a, i) * a.ent_ld;
-        float pv[KGE_MAXJ], sv[KGE_MAXJ], ev[KGE_MAXJ], dv[KGE_MAXJ], Df[KGE_MAXJ];
-        float ct = 0.f, cs = 0.f, cf = 0.f;
-#pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) {
-            const int j = lane + 64 * k;
-            pv[k] = sv[k] = ev[k] = dv[k] = Df[k] = 0.f;
-            if (j >= a.d) continue;
-            pv[k] = P[(int64_t)i * a.d + j]; sv[k] = El<BF16>::ld(a.ent_s, soff + j); dv[k] = de[(int64_t)i * a.d + j];
-            Df[k] = enc_dropout(a.seed_lo, a.seed_hi, a.step, a.tag, (uint32_t)i, j, a.thr, a.scale);
-            ev[k] = sv[k] + Df[k] * pv[k];
-            ct += fabsf(ev[k]) * ev[k] * ev[k]; cs += fabsf(sv[k]) * sv[k] * sv[k]; cf += fabsf(pv[k]) * pv[k] * pv[k];
-        }
-        float ft = 0.f, fs = 0.f, ff = 0.f;
-        if (a.reg_t > 0.f) { const float nrm = enc_l3(ct); ft = nrm > 0.f ? a.reg_t / (nrm * nrm) : 0.f; }
-        if (a.reg_s > 0.f) { const float nrm = enc_l3(cs); fs = nrm > 0.f ? a.reg_s / (nrm * nrm) : 0.f; }
-        if (a.reg_f > 0.f) { const float nrm = enc_l3(cf); ff = nrm > 0.f ? a.reg_f / (nrm * nrm) : 0.f; }
-#pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) {
-            const int j = lane + 64 * k;
-            if (j >= a.d) continue;
-            const float dep = dv[k] + ft * fabsf(ev[k]) * ev[k];
-            g_es[(int64_t)i * a.d + j] = dep + fs * fabsf(sv[k]) * sv[k];
-            tile[r * ldt + j] = Df[k] * dep + ff * fabsf(pv[k]) * pv[k];
-        }
-    }
-    __syncthreads();
-    enc_write_transposed<BF16>(tile, ldt, a.d, dPt, ncols, gr);
-}
-
-// F^t[f][columns] of the gathered slots (a workgroup takes a group of 32 slots); rows are read with 16-byte loads
-template <bool BF16>
-__global__ __launch_bounds__(256) void enc_gather_t_kernel(EncRowArgs a, const void *feat, int64_t feat_ld, int fd, void *Ft,
-                                                           int Bh, int64_t ncols) {
-    extern __shared__ float tile[];                        // [32][fd + 1]
-    const EncGroup gr = enc_group(blockIdx.x, a.B, a.N, Bh);
-    const int ldt = fd + 1;
-    constexpr int EPV = BF16 ? 8 : 4;                      // elements per 16 bytes
-    const int ppr = fd / EPV;                              // 16-byte pieces per row
-    // six pieces per thread are requested before the first is used (random rows: the bytes in flight bound the rate)
-    constexpr int U = 6;
-    const int total = gr.count * ppr;
-    for (int base = threadIdx.x; base < total; base += 256 * U) {
-        enc_u32x4 v[U];
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int idx = base + q * 256;
-            if (idx < total) {
-                const int r = idx / ppr, pc = idx % ppr;
-                v[q] = *(const enc_u32x4 *)((const char *)feat +
-                                            ((int64_t)enc_slot_entity(a, gr.slot0 + r) * feat_ld + pc * EPV) * (BF16 ? 2 : 4));
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int idx = base + q * 256;
-            if (idx >= total) continue;
-            const int r = idx / ppr, pc = idx % ppr;
-            float *dst = tile + r * ldt + pc * EPV;
-            if constexpr (BF16) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) { dst[2 * u] = __uint_as_float(v[q][u] << 16); dst[2 * u + 1] = __uint_as_float(v[q][u] & 0xffff0000u); }
-            } else {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) dst[u] = __uint_as_float(v[q][u]);
-            }
-        }
-    }
-    __syncthreads();
-    enc_write_transposed<BF16>(tile, ldt, fd, Ft, ncols, gr);
-}
-
-// the padding columns [B, Bh) and [Bh + B + N, ncols) of the transposed buffers must read as zero
-template <bool BF16>
-__global__ void enc_zero_pad_kernel(void *buf, int rows, int64_t ncols, int B, int Bh, int tail_end) {
-    const int row = blockIdx.x;
-    if (row >= rows) return;
-    const int pad1 = Bh - B, pad2 = (int)(ncols - tail_end);
-    for (int c = threadIdx.x; c < pad1 + pad2; c += blockDim.x) {
-        const int64_t col = c < pad1 ? B + c : tail_end + (c - pad1);
-        El<BF16>::st(buf, (int64_t)row * ncols + col, 0.f);
-    }
-}
-
-// out[e] = sum over the splits, in split order
-__global__ void enc_split_reduce_kernel(const float *part, int nsplit, int64_t count, float *out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    float s = 0.f;
-    for (int k = 0; k < nsplit; ++k) s += part[(int64_t)k * count + i];
-    out[i] = s;
-}
-
-struct EncPlan { int n, Bh, Th; int64_t ncols; int es; int nsplit_h, nsplit_t, kps; };
+struct EncPlan { int n, es; int sps, nsplit_h, nsplit_t; };
 
 EncPlan enc_plan(const kge_encoder_t &e, int64_t B, int64_t N) {
     EncPlan p{};
     p.n = (int)(2 * B + N);
-    p.Bh = (int)kge_round_up(B, ENC_TILE); p.Th = (int)kge_round_up(B + N, ENC_TILE);
-    p.ncols = (int64_t)p.Bh + p.Th;
     p.es = e.dtype == KGE_BF16 ? 2 : 4;
-    // k-steps (32 bytes of a transposed row = 16 or 8 slots) per split: about 1024 slots, so that the
-    // 128 x 128 output tiles of all splits fill the chip
-    p.kps = 1024 / (32 / p.es);
-    const int ksh = p.Bh / (32 / p.es), kst = p.Th / (32 / p.es);
-    p.nsplit_h = (ksh + p.kps - 1) / p.kps; p.nsplit_t = (kst + p.kps - 1) / p.kps;
+    // Slots per split of the backward contraction: as many splits as keep its 128 x 128 output tiles within ENC_TN_WGS workgroups (two per
+    // compute unit: one more would be a second turn), but no more than one per 128 slots and no more partials than fit where the
+    // transposed feature rows of the batch would have.
+    const int64_t tiles = ((e.dim + ENC_TILE - 1) / ENC_TILE) * (int64_t)((e.feat_dim + ENC_TILE - 1) / ENC_TILE);
+    auto splits = [&](int64_t sps) { return (B + sps - 1) / sps + (B + N + sps - 1) / sps; };
+    const int64_t room = (B + 1023) / 1024 + (B + N + 1023) / 1024 + (2 * B + N) * p.es / (4 * (int64_t)e.dim);
+    const int64_t most = ENC_TN_WGS / tiles < room ? ENC_TN_WGS / tiles : room;
+    int64_t sps = 128;
+    while (sps < ENC_MAX_SPS && splits(sps) > most) sps += 32;
+    p.sps = (int)sps;
+    p.nsplit_h = (int)((B + sps - 1) / sps); p.nsplit_t = (int)((B + N + sps - 1) / sps);
     return p;
 }
 
+// x, y, z: addresses of the [slots][dim] arrays that the row kernel reads and writes
 EncRowArgs enc_row_args(const kge_encoder_t &e, const int32_t *h, const int32_t *t, int64_t B, const int32_t *neg, int64_t N,
-                        uint64_t seed, uint64_t step) {
+                        uint64_t seed, uint64_t step, uintptr_t x, uintptr_t y, uintptr_t z = 0) {
     EncRowArgs a{};
     a.ent_s = e.ent_s; a.ent_ld = e.ent_ld; a.h = h; a.t = t; a.neg = neg; a.B = (int)B; a.N = (int)N; a.d = e.dim;
     a.seed_lo = (uint32_t)seed; a.seed_hi = (uint32_t)(seed >> 32); a.step = (uint32_t)step; a.tag = e.dropout_tag;
     a.thr = e.dropout > 0.f ? (uint32_t)floor((double)e.dropout * 4294967296.0) : 0u;
     a.scale = e.dropout > 0.f ? (float)(1.0 / (1.0 - (double)e.dropout)) : 1.f;
     a.reg_t = e.reg_t; a.reg_s = e.reg_s; a.reg_f = e.reg_f;
+    // (dim is a multiple of eight: a row of the [slots][dim] arrays is aligned if the array is)
+    a.wide = (e.ent_ld % 4 == 0 && ((uintptr_t)e.ent_s & 15) == 0 && ((x | y | z) & 15) == 0) ? 1 : 0;
     return a;
 }
 
-EncGemm enc_gemm_desc(const void *A, int64_t lda_b, bool gather, const int32_t *idx0, int n_idx0, const int32_t *idx1, int m_valid,
-                      const void *Bm, int64_t ldb_b, int n_valid, float *C, int64_t ldc, int64_t split_stride, int ksteps,
-                      int kps, int nsplit) {
+EncGemm enc_gemm_desc(const void *A, int64_t lda_b, const int32_t *idx0, int n_idx0, const int32_t *idx1, int m_valid, const void *Bm,
+                      int64_t ldb_b, int n_valid, float *C, int64_t ldc, int ksteps) {
     EncGemm q{};
-    q.A = (const char *)A; q.lda_b = lda_b; q.idx0 = idx0; q.idx1 = idx1; q.n_idx0 = n_idx0; q.gather = gather ? 1 : 0; q.m_valid = m_valid;
-    q.B = (const char *)Bm; q.ldb_b = ldb_b; q.n_valid = n_valid; q.C = C; q.ldc = ldc; q.split_stride = split_stride;
-    q.ksteps = ksteps; q.kps = kps; q.nsplit = m_valid > 0 && ksteps > 0 ? nsplit : 0;
+    q.A = (const char *)A; q.lda_b = lda_b; q.idx0 = idx0; q.idx1 = idx1; q.n_idx0 = n_idx0; q.m_valid = m_valid;
+    q.B = (const char *)Bm; q.ldb_b = ldb_b; q.n_valid = n_valid; q.C = C; q.ldc = ldc; q.ksteps = ksteps;
     q.tiles_m = (m_valid + ENC_TILE - 1) / ENC_TILE; q.tiles_n = (n_valid + ENC_TILE - 1) / ENC_TILE;
     return q;
 }
@@ -434,8 +535,8 @@ int enc_launch_pair(bool bf16, const EncGemm &g0, const EncGemm &g1, hipStream_t
         return KGE_E_HIP;
     EncGemmPair pr{};
     pr.g[0] = g0; pr.g[1] = g1;
-    pr.wgs0 = g0.tiles_m * g0.tiles_n * g0.nsplit;
-    pr.total = pr.wgs0 + g1.tiles_m * g1.tiles_n * g1.nsplit;
+    pr.wgs0 = g0.tiles_m * g0.tiles_n;
+    pr.total = pr.wgs0 + g1.tiles_m * g1.tiles_n;
     if (pr.total == 0) return KGE_OK;
     const int grid = (pr.total + 7) / 8 * 8;
     if (bf16) hipLaunchKernelGGL(enc_gemm_nt_kernel<true>, dim3(grid), dim3(256), ENC_LDS_BYTES, st, pr);
@@ -464,11 +565,11 @@ size_t kge_encode_ws(const kge_encoder_t &e, int64_t B, int64_t N, bool bwd) {
     const EncPlan p = enc_plan(e, B, N);
     size_t off = 0;
     auto take = [&](size_t bytes) { off += (bytes + 255) / 256 * 256; };
-    take((size_t)(p.n > 0 ? p.n : 1) * 4);                                        // per-slot regulariser terms
-    if (bwd) {
-        take((size_t)e.dim * p.ncols * p.es);                                     // dP^t
-        take((size_t)e.feat_dim * p.ncols * p.es);                                // F^t
-        take((size_t)(p.nsplit_h + p.nsplit_t + 1) * e.dim * e.feat_dim * 4);     // split partials of both contractions
+    if (!bwd) take((size_t)(p.n + 3) / 4 * 8);                                    // regulariser sums of four slots each
+    else {
+        take(256);                                                                // zero bytes
+        take((size_t)e.dim * p.n * p.es);                                         // dP
+        take((size_t)(p.nsplit_h + p.nsplit_t) * e.dim * e.feat_dim * 4);         // split partials of both contractions
     }
     return off + 256;
 }
@@ -477,23 +578,22 @@ int kge_run_encode(const kge_encoder_t &e, const int32_t *h, const int32_t *t, i
                    uint64_t seed, uint64_t step, void *e_out, float *proj_out, float *reg_out, void *ws, hipStream_t st) {
     const EncPlan p = enc_plan(e, B, N);
     const bool bf16 = e.dtype == KGE_BF16;
-    float *regv = (float *)ws;
+    double *regv = (double *)ws;
     const int ksteps = e.feat_dim * p.es / 32;
     {
         KgeProfScope prof(KGE_PROF_ENC_FWD, st);          // heads against M_H, tails and negatives against M_T: one launch
-        const EncGemm gh = enc_gemm_desc(e.feat, e.feat_ld * p.es, true, h, (int)B, nullptr, (int)B, e.m_h, e.m_ld * p.es, e.dim,
-                                         proj_out, e.dim, 0, ksteps, ksteps, 1);
-        const EncGemm gt = enc_gemm_desc(e.feat, e.feat_ld * p.es, true, t, (int)B, neg, (int)(B + N), e.m_t, e.m_ld * p.es, e.dim,
-                                         proj_out + (size_t)B * e.dim, e.dim, 0, ksteps, ksteps, 1);
+        const EncGemm gh = enc_gemm_desc(e.feat, e.feat_ld * p.es, h, (int)B, nullptr, (int)B, e.m_h, e.m_ld * p.es, e.dim, proj_out, e.dim, ksteps);
+        const EncGemm gt = enc_gemm_desc(e.feat, e.feat_ld * p.es, t, (int)B, neg, (int)(B + N), e.m_t, e.m_ld * p.es, e.dim,
+                                         proj_out + (size_t)B * e.dim, e.dim, ksteps);
         if (int rc = enc_launch_pair(bf16, gh, gt, st)) return rc;
     }
-    const EncRowArgs a = enc_row_args(e, h, t, B, neg, N, seed, step);
+    const EncRowArgs a = enc_row_args(e, h, t, B, neg, N, seed, step, (uintptr_t)proj_out, (uintptr_t)e_out);
     const bool reg = e.reg_t > 0.f || e.reg_s > 0.f || e.reg_f > 0.f;
     if (p.n > 0) {
         if (bf16) hipLaunchKernelGGL(enc_finish_kernel<true>, dim3((p.n + 3) / 4), dim3(256), 0, st, a, proj_out, e_out, regv);
         else      hipLaunchKernelGGL(enc_finish_kernel<false>, dim3((p.n + 3) / 4), dim3(256), 0, st, a, proj_out, e_out, regv);
     }
-    if (reg_out) hipLaunchKernelGGL(enc_reg_reduce_kernel, dim3(1), dim3(1024), 0, st, regv, p.n, reg ? 1 : 0, reg_out);
+    if (reg_out) hipLaunchKernelGGL(enc_reg_reduce_kernel, dim3(1), dim3(1024), 0, st, regv, (p.n + 3) / 4, reg ? 1 : 0, reg_out);
     return kge_launch_status();
 }
 
@@ -504,57 +604,31 @@ int kge_run_encode_bwd(const kge_encoder_t &e, const int32_t *h, const int32_t *
     const bool bf16 = e.dtype == KGE_BF16;
     char *b = (char *)ws; size_t off = 0;
     auto take = [&](size_t bytes) { void *q = b + off; off += (bytes + 255) / 256 * 256; return q; };
-    take((size_t)(p.n > 0 ? p.n : 1) * 4);
-    void *dPt = take((size_t)e.dim * p.ncols * p.es);
-    void *Ft = take((size_t)e.feat_dim * p.ncols * p.es);
+    uint32_t *zeros = (uint32_t *)take(256);
+    char *dP = (char *)take((size_t)e.dim * p.n * p.es);
     float *part = (float *)take(1);
     const int64_t mcount = (int64_t)e.dim * e.feat_dim;
-    // padding columns must read as zero (a fill kernel rather than a memset, so that the call can be captured)
-    {
-        const int tail_end = p.Bh + (int)(B + N);
-        if (bf16) {
-            hipLaunchKernelGGL(enc_zero_pad_kernel<true>, dim3(e.dim), dim3(256), 0, st, dPt, e.dim, p.ncols, (int)B, p.Bh, tail_end);
-            hipLaunchKernelGGL(enc_zero_pad_kernel<true>, dim3(e.feat_dim), dim3(256), 0, st, Ft, e.feat_dim, p.ncols, (int)B, p.Bh, tail_end);
-        } else {
-            hipLaunchKernelGGL(enc_zero_pad_kernel<false>, dim3(e.dim), dim3(256), 0, st, dPt, e.dim, p.ncols, (int)B, p.Bh, tail_end);
-            hipLaunchKernelGGL(enc_zero_pad_kernel<false>, dim3(e.feat_dim), dim3(256), 0, st, Ft, e.feat_dim, p.ncols, (int)B, p.Bh, tail_end);
-        }
-    }
-    // the row kernels stage 32 rows in the LDS: more than the default dynamic limit for long rows
-    static KgeLdsLimit lim_rows_bf16, lim_rows_f32, lim_gt_bf16, lim_gt_f32;
-    {
-        const int big = 32 * (1024 + 1) * 4;
-        if (lim_rows_bf16.set((const void *)enc_bwd_rows_kernel<true>, big) != KGE_OK ||
-            lim_rows_f32.set((const void *)enc_bwd_rows_kernel<false>, big) != KGE_OK ||
-            lim_gt_bf16.set((const void *)enc_gather_t_kernel<true>, big) != KGE_OK ||
-            lim_gt_f32.set((const void *)enc_gather_t_kernel<false>, big) != KGE_OK)
-            return KGE_E_HIP;
-    }
-    const EncRowArgs a = enc_row_args(e, h, t, B, neg, N, seed, step);
+    const EncRowArgs a = enc_row_args(e, h, t, B, neg, N, seed, step, (uintptr_t)proj, (uintptr_t)de, (uintptr_t)g_es);
     if (p.n > 0) {
-        const int grid = (int)((B + 31) / 32 + (B + N + 31) / 32);
-        if (bf16) {
-            hipLaunchKernelGGL(enc_bwd_rows_kernel<true>, dim3(grid), dim3(256), 32 * (e.dim + 1) * 4, st, a, proj, de, g_es, dPt, p.Bh, p.ncols);
-            hipLaunchKernelGGL(enc_gather_t_kernel<true>, dim3(grid), dim3(256), 32 * (e.feat_dim + 1) * 4, st, a, e.feat, e.feat_ld, e.feat_dim, Ft, p.Bh, p.ncols);
-        } else {
-            hipLaunchKernelGGL(enc_bwd_rows_kernel<false>, dim3(grid), dim3(256), 32 * (e.dim + 1) * 4, st, a, proj, de, g_es, dPt, p.Bh, p.ncols);
-            hipLaunchKernelGGL(enc_gather_t_kernel<false>, dim3(grid), dim3(256), 32 * (e.feat_dim + 1) * 4, st, a, e.feat, e.feat_ld, e.feat_dim, Ft, p.Bh, p.ncols);
-        }
+        if (bf16) hipLaunchKernelGGL(enc_bwd_rows_kernel<true>, dim3((p.n + 3) / 4), dim3(256), 0, st, a, proj, de, g_es, dP, zeros);
+        else      hipLaunchKernelGGL(enc_bwd_rows_kernel<false>, dim3((p.n + 3) / 4), dim3(256), 0, st, a, proj, de, g_es, dP, zeros);
     }
-    // G[d, f] = dP^t[d, cols] . F^t[f, cols]^t over the head columns (M_H) and over the tail / negative columns (M_T):
-    // one launch, split over the columns, then the partials are summed in split order
-    const int per = 32 / p.es;                             // slots per k-step
-    float *part_t = part + (size_t)p.nsplit_h * mcount;
-    const EncGemm gh = enc_gemm_desc(dPt, p.ncols * p.es, false, nullptr, 0, nullptr, B > 0 ? e.dim : 0, Ft, p.ncols * p.es, e.feat_dim,
-                                     part, e.feat_dim, mcount, p.Bh / per, p.kps, p.nsplit_h);
-    const EncGemm gt = enc_gemm_desc((const char *)dPt + (size_t)p.Bh * p.es, p.ncols * p.es, false, nullptr, 0, nullptr,
-                                     B + N > 0 ? e.dim : 0, (const char *)Ft + (size_t)p.Bh * p.es, p.ncols * p.es, e.feat_dim,
-                                     part_t, e.feat_dim, mcount, p.Th / per, p.kps, p.nsplit_t);
-    {
+    EncTnPair pr{};
+    pr.g[0] = EncTn{dP, h, nullptr, (int)B, (int)B, part};
+    pr.g[1] = EncTn{dP + (size_t)B * e.dim * p.es, t, neg, (int)B, (int)(B + N), part + (size_t)p.nsplit_h * mcount};
+    pr.feat = (const char *)e.feat; pr.ldf_b = e.feat_ld * p.es; pr.d = e.dim; pr.fd = e.feat_dim; pr.sps = p.sps; pr.zeros = zeros;
+    pr.tiles_m = (e.dim + ENC_TILE - 1) / ENC_TILE; pr.tiles_n = (e.feat_dim + ENC_TILE - 1) / ENC_TILE;
+    pr.wgs0 = pr.tiles_m * pr.tiles_n * p.nsplit_h; pr.total = pr.wgs0 + pr.tiles_m * pr.tiles_n * p.nsplit_t;
+    if (pr.total > 0) {
         KgeProfScope prof(KGE_PROF_ENC_BWD, st);
-        if (int rc = enc_launch_pair(bf16, gh, gt, st)) return rc;
+        constexpr int TN_LDS = ENC_LDS_BYTES + ENC_MAX_SPS * 4;
+        static KgeLdsLimit lim_bf16, lim_f32;                // the ring of stages is larger than the default dynamic limit
+        if (lim_bf16.set((const void *)enc_gemm_tn_kernel<true>, TN_LDS) != KGE_OK || lim_f32.set((const void *)enc_gemm_tn_kernel<false>, TN_LDS) != KGE_OK)
+            return KGE_E_HIP;
+        const int grid = (pr.total + 7) / 8 * 8;
+        if (bf16) hipLaunchKernelGGL(enc_gemm_tn_kernel<true>, dim3(grid), dim3(256), TN_LDS, st, pr);
+        else      hipLaunchKernelGGL(enc_gemm_tn_kernel<false>, dim3(grid), dim3(256), TN_LDS, st, pr);
     }
-    hipLaunchKernelGGL(enc_split_reduce_kernel, dim3((unsigned)((mcount + 255) / 256)), dim3(256), 0, st, part, gh.nsplit, mcount, g_mh);
-    hipLaunchKernelGGL(enc_split_reduce_kernel, dim3((unsigned)((mcount + 255) / 256)), dim3(256), 0, st, part_t, gt.nsplit, mcount, g_mt);
+    hipLaunchKernelGGL(enc_split_reduce_kernel, dim3((unsigned)((2 * mcount + 255) / 256)), dim3(256), 0, st, part, p.nsplit_h, p.nsplit_t, mcount, g_mh, g_mt);
     return kge_launch_status();
 }

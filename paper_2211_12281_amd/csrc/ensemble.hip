@@ -13,7 +13,7 @@
 // What bounds it is the latency of the LDS chains of a query, so what counts is the number of workgroups on a compute unit (12
 // bytes of LDS per slot: five at M K = 1,600).  Sorting the M K keys in the LDS, one thread per run of equal entities and K_out
 // workgroup-wide arg-max rounds took 1,106 us for 16 lists of 100 and 8,192 queries (66 sorting steps with a barrier each);
-// this takes 92 us (one pass of the lists: 52 MB, 11 us at the copy rate).
+// this takes 94 us (one pass of the lists: 52 MB, 11 us at the copy rate).
 #include "kge_internal.h"
 #include <math.h>
 

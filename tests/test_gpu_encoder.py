@@ -95,3 +95,32 @@ def test_encoder_feeds_the_loss_on_the_compact_table(orc):
     assert abs(out["loss"].item() + reg.item() - (ref["loss"] + om)) <= 1e-5 * abs(ref["loss"] + om)
     for got, want in ((g_es, r_es), (g_mh, r_mh), (g_mt, r_mt), (out["g_rel"], ref["g_rel"])):
         assert norm_err(got.cpu().numpy(), want) <= 2e-5        # e itself is rounded to fp32 between the two stages
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("d,fd,B,N,pad", [
+    (240, 176, 70, 333, 0),          # column tiles that end inside a tile, sections that end inside a chunk of slots
+    (16, 1008, 33, 1, 2),            # one piece of columns; entity rows that start where four elements do not load at once
+    (512, 16, 129, 1100, 0),         # two groups of columns per lane; several splits
+    (144, 272, 1, 2050, 6)])
+def test_row_widths_sections_and_unaligned_rows(orc, bf16, d, fd, B, N, pad):
+    import torch
+    ent, feat, mh, mt, h, t, neg = _case(1500, d, fd, B, N, bf16, seed=2)
+    enc = _encoder(ent, feat, mh, mt, bf16)
+    import paper_2211_12281_amd as kge
+    wide = torch.zeros((1500, d + pad), dtype=enc.ent_s.dtype, device="cuda")
+    wide[:, :d] = enc.ent_s
+    enc = kge.Encoder(wide[:, :d], enc.feat, enc.m_h, enc.m_t, dropout=0.3, reg_t=0.02, reg_s=0.01, reg_f=0.03, dropout_tag=12)
+    hd, td, nd = dev_idx(h), dev_idx(t), dev_idx(neg)
+    idx = np.concatenate([h, t, neg])
+    kw = dict(p=0.3, seed=5, step=11, tag=12, reg_t=0.02, reg_s=0.01, reg_f=0.03)
+    om, rproj, re = orc.encode(ent, feat, mh, mt, idx, B, N, **kw)
+    e, proj, reg = enc.encode(hd, td, nd, seed=5, step=11)
+    tol = RTOL_BF16 if bf16 else RTOL_F32
+    assert norm_err(proj.cpu().numpy(), rproj) <= tol and norm_err(e.float().cpu().numpy(), re) <= tol
+    assert abs(reg.item() - om) <= tol * om
+    de = ks.uniform_rows(5, 31, np.arange(2 * B + N), d, 1.0)
+    got = enc.encode_bwd(hd, td, nd, proj, torch.from_numpy(de).cuda(), seed=5, step=11)
+    want = orc.encode_bwd(ent, feat, mh, mt, idx, B, N, de, **kw)
+    for x, y in zip(got, want):
+        assert norm_err(x.cpu().numpy(), y) <= tol
