@@ -132,16 +132,43 @@ __device__ __forceinline__ float kge_log2(float x) { return __builtin_amdgcn_log
 // Squared distance of one (query, tail) pair by direct differences; the fallback for block entries
 // whose norm-expansion form cancels.  TransH: u = q - t + (w.t) w.
 template <bool BF16, bool TRANSH>
-__device__ __noinline__ float kge_direct_d2(const void *qv, const void *tv, const void *wv, int dp) {
+__device__ __forceinline__ float kge_direct_d2_inline(const void *qv, const void *tv, const void *wv, int dp) {
     using E = typename KgeElem<BF16>::type;
     const E *q = (const E *)qv, *t = (const E *)tv, *w = (const E *)wv;
     float A = 0.f;
     if constexpr (TRANSH)
+#pragma unroll 1
         for (int j = 0; j < dp; ++j) A += kge_elem_to_float(w[j]) * kge_elem_to_float(t[j]);
     float acc = 0.f;
+#pragma unroll 1
     for (int j = 0; j < dp; ++j) {
         float x = kge_elem_to_float(q[j]) - kge_elem_to_float(t[j]);
         if constexpr (TRANSH) x += A * kge_elem_to_float(w[j]);
+        acc += x * x;
+    }
+    return acc;
+}
+template <bool BF16, bool TRANSH>
+__device__ __noinline__ float kge_direct_d2(const void *qv, const void *tv, const void *wv, int dp) {
+    return kge_direct_d2_inline<BF16, TRANSH>(qv, tv, wv, dp);
+}
+
+// the same for operands that are bf16 planes of rows of dp elements (their three pieces add up to the fp32 value), plane strides in bytes
+template <bool TRANSH>
+__device__ __forceinline__ float kge_direct_d2_planes(const char *qv, int64_t qplane, const char *tv, int64_t tplane, const char *wv, int64_t wplane, int dp) {
+    auto val = [](const char *r, int64_t plane, int j) {
+        const __bf16 *x = (const __bf16 *)r;
+        return ((float)x[j] + (float)x[j + plane / 2]) + (float)x[j + plane];
+    };
+    float A = 0.f;
+    if constexpr (TRANSH)
+#pragma unroll 1
+        for (int j = 0; j < dp; ++j) A += val(wv, wplane, j) * val(tv, tplane, j);
+    float acc = 0.f;
+#pragma unroll 1
+    for (int j = 0; j < dp; ++j) {
+        float x = val(qv, qplane, j) - val(tv, tplane, j);
+        if constexpr (TRANSH) x += A * val(wv, wplane, j);
         acc += x * x;
     }
     return acc;
@@ -158,11 +185,15 @@ struct KgeBlockCfg {
     static constexpr int ST = KGE_STREAM_TILE;
     static constexpr int NB = DP / 32;                     // 32-column output blocks of phase 2
     static constexpr int NBH = NB / DSPLIT;                // ... handled by one z-slice
-    static constexpr int X_BYTES = ST * RB;                // [ST rows][RB bytes], chunk c of row r at c ^ (r & 7)
+    // PL: the operands come as bf16 planes; a tile is three planes of [ST rows][2 DP bytes], chunk c of row r at c ^ kge_pl_swz(r), and the
+    // transposed fragments of phase 2 are LDS transpose reads of it (ds_read_b64_tr_b16)
+    static constexpr bool PL = kge_block_planes(BF16, RB, MODE);
+    static constexpr int PLANE = ST * DP * 2;
+    static constexpr int X_BYTES = PL ? 3 * PLANE : ST * RB;    // else [ST rows][RB bytes], chunk c of row r at c ^ (r & 7)
     static constexpr int XT_ROWB = ST * ES;                // one transposed row: ST stream entries (64 or 128 bytes)
     static constexpr int XT_BYTES = DP * XT_ROWB;
     static constexpr bool HAS_X2 = TRANSH && !OWN_ROW;     // second streamed operand (normals)
-    static constexpr bool HAS_XT = MODE != KGE_MODE_SCORE;
+    static constexpr bool HAS_XT = MODE != KGE_MODE_SCORE && !PL;
     static constexpr int NX = HAS_X2 ? 2 : 1;
     static constexpr int STAGE_BYTES = X_BYTES * NX + (HAS_XT ? XT_BYTES * NX : 0);
     static constexpr int SIDE_SLOT = OWN_ROW ? 4 * 256 : 4 * 1024;   // per-wave copies of the tile's side info
@@ -173,13 +204,17 @@ struct KgeBlockCfg {
     // of 1,024 bytes: pass over the negatives 550 -> 461 us, pass over the queries 589 -> 727 us with 170-320 bytes of
     // scratch).  The score block of this kernel stays on the fp32 instructions: kge_score on fp32 tables runs
     // block_f32h2_score.hip, and this one is what that is compared with.
-    static constexpr bool X3 = !BF16 && ((MODE == KGE_MODE_FWD && RB <= 512) || MODE == KGE_MODE_GRADT);
+    static constexpr bool X3 = PL || (!BF16 && MODE == KGE_MODE_GRADT);
     static constexpr int OCC = kge_block_occ(BF16, RB, TRANSH, MODE);
-    static constexpr int LDS_MAX = 160 * 1024 / OCC;
+    // TransH queries as planes: q and w^ together would take 192 registers, and the compiler then reloads a third of them from scratch in
+    // every tile, so the wave's 32 rows of w^ stay in the LDS, laid out like a tile (8,192 x 4,096 x 128: 289 -> 208 us)
+    static constexpr bool WL = PL && TRANSH && OWN_ROW;
+    static constexpr int WL_BYTES = WL ? 4 * X_BYTES : 0;
+    static constexpr int LDS_MAX = 160 * 1024 / OCC - WL_BYTES;
     static constexpr int NSTAGE_RAW = (LDS_MAX - SIDE_SLOT) / (STAGE_BYTES + SIDE_SLOT);   // n stages + (n+1) side slots fit
     static constexpr int NSTAGE = NSTAGE_RAW > 4 ? 4 : NSTAGE_RAW;
     static constexpr int SIDE_SLOTS = NSTAGE + 1;
-    static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES + SIDE_SLOTS * SIDE_SLOT;
+    static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES + SIDE_SLOTS * SIDE_SLOT + WL_BYTES;
     static constexpr int X_IPW = X_BYTES / 1024 / 4;       // 1 KB wave-wide copies per wave and tile
     static constexpr int XT_IPW = XT_BYTES / 1024 / 4;
     static constexpr int LPW = X_IPW * NX + (HAS_XT ? XT_IPW * NX : 0) + 1;
@@ -189,6 +224,11 @@ struct KgeBlockCfg {
     static_assert(OW == 1 || !TRANSH, "two own fragments per wave leave no registers for the TransH operands");
     static_assert(KS % 8 == 0, "phase 1 works in groups of four fragments, split in two halves");
 };
+
+// Position of the 16-byte chunks of a plane row of 256 bytes: sixteen consecutive rows at one chunk index (phase 1) fall into sixteen
+// different bank groups, and so do four consecutive rows at four neighbouring chunks (the transpose reads of phase 2).
+__device__ __forceinline__ constexpr int kge_pl_swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
+typedef short kge_i16x4 __attribute__((ext_vector_type(4)));
 
 template <bool BF16, int RB, int MODE, bool TRANSH, int KIND, int LOSS, int DSPLIT>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256),
@@ -220,19 +260,32 @@ void kge_block_kernel(const KgeBlockArgs a) {
     if (split >= a.nsplit) return;
 
     // ---- own operand fragments: 16 bytes per lane per 32-byte k-step --------------------------
-    uint4 own[OW][C::KS];
-    uint4 ownw[(TRANSH && OWN_ROW) ? C::KS : 1];
+    constexpr bool PL = C::PL;
+    const int64_t own_plane = (int64_t)a.own_pad * C::DP * 2, str_plane = (int64_t)a.str_tiles * C::ST * C::DP * 2;   // PL: bytes per plane
+    uint4 own[OW][PL ? 1 : C::KS];
+    uint4 ownw[(TRANSH && OWN_ROW && !PL) ? C::KS : 1];
+    // the own operand as bf16 pieces, sixteen contraction indices per entry
+    constexpr bool X3 = C::X3, WL = C::WL;
+    KgeP3 ownp[X3 ? OW : 1][X3 ? C::KS / 2 : 1], ownwp[(X3 && TRANSH && OWN_ROW && !PL) ? C::KS / 2 : 1];
     float o_qn[OW], o_c[OW], o_wn[OW], o_tn[OW];          // own-side scalars
 #pragma unroll
     for (int h = 0; h < OW; ++h) {
         const int oidx = oidx0 + 32 * h;
-        const char *p = (const char *)a.own + (size_t)oidx * RB + g * 16;
+        if constexpr (PL) {
+            const char *p = (const char *)a.own + (size_t)oidx * (C::DP * 2) + g * 16;
 #pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) own[h][ks] = *(const uint4 *)(p + ks * 32);
-        if constexpr (TRANSH && OWN_ROW) {
-            const char *pw = (const char *)a.own2 + (size_t)oidx * RB + g * 16;
+            for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
-            for (int ks = 0; ks < C::KS; ++ks) ownw[ks] = *(const uint4 *)(pw + ks * 32);
+                for (int k2 = 0; k2 < C::KS / 2; ++k2) ownp[h][k2].p[pl] = *(const uint4 *)(p + pl * own_plane + k2 * 32);
+        } else {
+            const char *p = (const char *)a.own + (size_t)oidx * RB + g * 16;
+#pragma unroll
+            for (int ks = 0; ks < C::KS; ++ks) own[h][ks] = *(const uint4 *)(p + ks * 32);
+            if constexpr (TRANSH && OWN_ROW) {
+                const char *pw = (const char *)a.own2 + (size_t)oidx * RB + g * 16;
+#pragma unroll
+                for (int ks = 0; ks < C::KS; ++ks) ownw[ks] = *(const uint4 *)(pw + ks * 32);
+            }
         }
         o_qn[h] = 0.f; o_c[h] = 0.f; o_wn[h] = 1.f; o_tn[h] = 0.f;
         if constexpr (OWN_ROW) {
@@ -263,9 +316,12 @@ void kge_block_kernel(const KgeBlockArgs a) {
     // ---- asynchronous staging of one stream tile --------------------------------------------------
     // X tile: instruction jj of this wave covers LDS bytes [(wave*X_IPW + jj) KB, +1 KB) of the tile; the
     // lane's 16 bytes are position (byte % RB)/16 of row byte/RB and must hold source chunk pos ^ (row & 7).
-    int x_off[C::X_IPW];                                   // source byte offset inside the tile
+    // (PL: copy c = wave X_IPW + jj fills rows 4 (c % 8) .. + 3 of plane c / 8; the lane's offset differs by (c % 4) in the swizzle only)
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int pl_off = (lane >> 4) * (C::DP * 2) + (((lane & 15) ^ ((lane >> 4) << 2)) * 16);
+    int x_off[PL ? 1 : C::X_IPW];                          // source byte offset inside the tile
 #pragma unroll
-    for (int jj = 0; jj < C::X_IPW; ++jj) {
+    for (int jj = 0; jj < (PL ? 0 : C::X_IPW); ++jj) {
         const int byte = (wave * C::X_IPW + jj) * 1024 + lane * 16;
         const int r = byte / RB, pos = (byte % RB) / 16;
         x_off[jj] = r * RB + ((pos ^ (r & 7)) * 16);
@@ -284,18 +340,42 @@ void kge_block_kernel(const KgeBlockArgs a) {
             xt_off[jj] = (int64_t)row * a.strT_ld * C::ES + c * 16;
         }
     }
+    const char *own_w = lds + C::NSTAGE * C::STAGE_BYTES + C::SIDE_SLOTS * C::SIDE_SLOT + wave * (WL ? C::X_BYTES : 0);
+    if constexpr (WL) {                                    // (the wave's own copies: the wait for its first tile covers them)
+        const uint32_t wl0 = lds0 + C::NSTAGE * C::STAGE_BYTES + C::SIDE_SLOTS * C::SIDE_SLOT + wave_u * C::X_BYTES;
+        const int64_t woff = (int64_t)(own_base + wave_u * 32) * (C::DP * 2);
+#pragma unroll
+        for (int c = 0; c < C::X_BYTES / 1024; ++c) {
+            const char *src = (const char *)a.own2 + (c >> 3) * own_plane + woff + (c & 7) * 1024;
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(wl0 + c * 1024)),
+                         "v"(pl_off ^ ((c & 3) << 4)), "s"(src) : "memory");
+        }
+    }
     auto issue = [&](int tile, int slot) {
         tile = tile < t1 ? tile : t1 - 1;                  // past the end: a harmless repeat keeps vmcnt uniform
         const uint32_t sbase = lds0 + (slot % C::NSTAGE) * C::STAGE_BYTES;
-        const char *src = (const char *)a.str + (size_t)tile * C::ST * RB;
+        if constexpr (PL) {
+            const int64_t toff = (int64_t)__builtin_amdgcn_readfirstlane(tile) * (C::ST * C::DP * 2);
 #pragma unroll
-        for (int jj = 0; jj < C::X_IPW; ++jj)
-            kge_async_copy16(src + x_off[jj], __builtin_amdgcn_readfirstlane(sbase + (wave * C::X_IPW + jj) * 1024));
-        if constexpr (C::HAS_X2) {
-            const char *src2 = (const char *)a.str2 + (size_t)tile * C::ST * RB;
+            for (int op = 0; op < C::NX; ++op)
+#pragma unroll
+                for (int jj = 0; jj < C::X_IPW; ++jj) {
+                    const int c = wave_u * C::X_IPW + jj;
+                    const char *src = (const char *)(op ? a.str2 : a.str) + (c >> 3) * str_plane + toff + (c & 7) * 1024;
+                    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(sbase + op * C::X_BYTES + c * 1024)),
+                                 "v"(pl_off ^ ((c & 3) << 4)), "s"(src) : "memory");
+                }
+        } else {
+            const char *src = (const char *)a.str + (size_t)tile * C::ST * RB;
 #pragma unroll
             for (int jj = 0; jj < C::X_IPW; ++jj)
-                kge_async_copy16(src2 + x_off[jj], __builtin_amdgcn_readfirstlane(sbase + C::X_BYTES + (wave * C::X_IPW + jj) * 1024));
+                kge_async_copy16(src + x_off[jj], __builtin_amdgcn_readfirstlane(sbase + (wave * C::X_IPW + jj) * 1024));
+            if constexpr (C::HAS_X2) {
+                const char *src2 = (const char *)a.str2 + (size_t)tile * C::ST * RB;
+#pragma unroll
+                for (int jj = 0; jj < C::X_IPW; ++jj)
+                    kge_async_copy16(src2 + x_off[jj], __builtin_amdgcn_readfirstlane(sbase + C::X_BYTES + (wave * C::X_IPW + jj) * 1024));
+            }
         }
         if constexpr (C::HAS_XT) {
             const char *srct = (const char *)a.strT + (size_t)tile * C::ST * C::ES;
@@ -318,6 +398,22 @@ void kge_block_kernel(const KgeBlockArgs a) {
     int frag_off[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) frag_off[b] = lr * RB + 16 * (((2 * b) ^ (lr & 6)) | (g ^ (lr & 1)));
+    // PL: chunk (2 k2 + g) of row lr of a plane; and the transpose reads: source lane i of a group of sixteen points at row
+    // 16 j2 + 8 hh + 4 g + i / 4, columns 32 blk + 16 q16 + 4 (i % 4) .. + 3, and lane l receives column 32 blk + l % 32 of the rows
+    // 16 j2 + 8 hh + 4 g .. + 3 - the streamed rows of its coefficients 8 j2 + 4 hh .. + 3
+    int pl_frag[PL ? 8 : 1], pl_tr[2][PL ? C::NB : 1];
+    if constexpr (PL) {
+        const int i16 = lane & 15, q16 = (lane >> 4) & 1;
+#pragma unroll
+        for (int k2 = 0; k2 < 8; ++k2) pl_frag[k2] = lr * (C::DP * 2) + ((2 * k2 + g) ^ kge_pl_swz(lr)) * 16;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int b = 0; b < C::NB; ++b) {
+                const int row = 8 * hh + 4 * g + (i16 >> 2);
+                pl_tr[hh][b] = row * (C::DP * 2) + ((4 * b + 2 * q16 + ((i16 & 3) >> 1)) ^ kge_pl_swz(row)) * 16 + (i16 & 1) * 8;
+            }
+    }
 
 #pragma unroll
     for (int s2 = 0; s2 < C::NSTAGE - 1; ++s2) issue(t0 + s2, s2);
@@ -326,19 +422,27 @@ void kge_block_kernel(const KgeBlockArgs a) {
     // operation in flight) would also drain the asynchronous copies of the coming tiles on every iteration.
 #pragma unroll
     for (int h = 0; h < OW; ++h) {
+        if constexpr (PL) {
 #pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks) {
-            asm volatile("" : "+v"(own[h][ks].x), "+v"(own[h][ks].y), "+v"(own[h][ks].z), "+v"(own[h][ks].w));
-            if constexpr (TRANSH && OWN_ROW)
-                asm volatile("" : "+v"(ownw[ks].x), "+v"(ownw[ks].y), "+v"(ownw[ks].z), "+v"(ownw[ks].w));
+            for (int k2 = 0; k2 < C::KS / 2; ++k2)
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    uint4 &v = ownp[h][k2].p[pl];
+                    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+                }
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < C::KS; ++ks) {
+                asm volatile("" : "+v"(own[h][ks].x), "+v"(own[h][ks].y), "+v"(own[h][ks].z), "+v"(own[h][ks].w));
+                if constexpr (TRANSH && OWN_ROW)
+                    asm volatile("" : "+v"(ownw[ks].x), "+v"(ownw[ks].y), "+v"(ownw[ks].z), "+v"(ownw[ks].w));
+            }
         }
         asm volatile("" : "+v"(o_qn[h]), "+v"(o_c[h]), "+v"(o_wn[h]), "+v"(o_tn[h]));
     }
 
-    // the own operand as bf16 pieces, two k-steps per entry (the fp32 fragments are not used again)
-    constexpr bool X3 = C::X3;
-    KgeP3 ownp[X3 ? OW : 1][X3 ? C::KS / 2 : 1], ownwp[(X3 && TRANSH && OWN_ROW) ? C::KS / 2 : 1];
-    if constexpr (X3) {
+    // (fp32 rows over 512 bytes: split here; the fp32 fragments are not used again)
+    if constexpr (X3 && !PL) {
 #pragma unroll
         for (int h = 0; h < OW; ++h)
 #pragma unroll
@@ -371,10 +475,24 @@ void kge_block_kernel(const KgeBlockArgs a) {
     // ---- phase 1: acc[h][stream, own] = X_tile . own^t; a fragment read from the LDS feeds all own fragments
     constexpr bool HASW = TRANSH && !OWN_ROW;
     constexpr int G1 = HASW ? 2 : 4, NG1 = C::KS / G1;      // fragments per group, groups
-    uint4 av[C::KS], aw[HASW ? C::KS : 1];
+    uint4 av[PL ? 1 : C::KS], aw[HASW && !PL ? C::KS : 1];
+    KgeP3 xp[PL ? C::KS / 2 : 1], xwp[HASW && PL ? C::KS / 2 : 1], owp[WL ? C::KS / 2 : 1];
     auto ld1 = [&](const char *stage, int grp) {
+        if constexpr (PL) {
 #pragma unroll
-        for (int k = 0; k < G1; ++k) {
+            for (int k = 0; k < G1 / 2; ++k) {
+                const int k2 = grp * (G1 / 2) + k;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    xp[k2].p[pl] = *(const uint4 *)(stage + pl_frag[k2] + pl * C::PLANE);
+                    if constexpr (WL) owp[k2].p[pl] = *(const uint4 *)(own_w + pl_frag[k2] + pl * C::PLANE);
+                    if constexpr (HASW) xwp[k2].p[pl] = *(const uint4 *)(stage + C::X_BYTES + pl_frag[k2] + pl * C::PLANE);
+                }
+            }
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < (PL ? 0 : G1); ++k) {
             const int ks = grp * G1 + k;
             av[ks] = *(const uint4 *)(stage + frag_off[ks & 3] + 128 * (ks >> 2));
             if constexpr (HASW) aw[ks] = *(const uint4 *)(stage + C::X_BYTES + frag_off[ks & 3] + 128 * (ks >> 2));
@@ -394,6 +512,13 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 for (int h = 0; h < OW; ++h) acc[h] = kge_mma16<BF16>(acc[h], av[ks], own[h][ks]);
                 if constexpr (TRANSH && OWN_ROW) accw = kge_mma16<BF16>(accw, av[ks], ownw[ks]);
                 if constexpr (HASW) accw = kge_mma16<BF16>(accw, aw[ks], own[0][ks]);
+            } else if constexpr (PL) {
+                if ((k & 1) == 0) {
+#pragma unroll
+                    for (int h = 0; h < OW; ++h) acc[h] = kge_mma3(acc[h], xp[ks >> 1], ownp[h][ks >> 1]);
+                    if constexpr (WL) accw = kge_mma3(accw, xp[ks >> 1], owp[ks >> 1]);
+                    if constexpr (HASW) accw = kge_mma3(accw, xwp[ks >> 1], ownp[0][ks >> 1]);
+                }
             } else if ((k & 1) == 0) {                      // bf16 pieces: two k-steps at a time (G1 is even)
                 const KgeP3 x = kge_split3(av[ks], av[ks + 1]);
 #pragma unroll
@@ -407,11 +532,31 @@ void kge_block_kernel(const KgeBlockArgs a) {
     constexpr int G2 = BF16 ? (HASW ? 1 : 2) : 1;          // blocks per group
     constexpr int NG2 = PHASE2 ? C::NBH / G2 : 0;
     constexpr int F2 = BF16 ? 2 : 4;                       // 16-byte fragments per block
-    uint4 av2[PHASE2 ? C::NBH : 1][F2], aw2[(PHASE2 && HASW) ? C::NBH : 1][F2];
+    uint4 av2[PHASE2 && !PL ? C::NBH : 1][F2], aw2[(PHASE2 && HASW && !PL) ? C::NBH : 1][F2];
+    KgeP3 tp[PL ? C::NBH : 1][2], twp[PL && HASW ? C::NBH : 1][2];
     auto ld2 = [&](const char *stage, int grp) {
+        if constexpr (PL) {
+            auto frag = [&](const char *s, int blk, int j2, KgeP3 &x) {
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    const char *q = s + pl * C::PLANE + j2 * (16 * C::DP * 2);
+                    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((kge_i16x4 __attribute__((address_space(3))) *)(q + pl_tr[0][dblk0 + blk])));
+                    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((kge_i16x4 __attribute__((address_space(3))) *)(q + pl_tr[1][dblk0 + blk])));
+                    x.p[pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                }
+            };
+#pragma unroll
+            for (int bb = 0; bb < G2; ++bb)
+#pragma unroll
+                for (int j2 = 0; j2 < 2; ++j2) {
+                    frag(stage, grp * G2 + bb, j2, tp[grp * G2 + bb][j2]);
+                    if constexpr (HASW) frag(stage + C::X_BYTES, grp * G2 + bb, j2, twp[grp * G2 + bb][j2]);
+                }
+            return;
+        }
         const char *xt = stage + C::X_BYTES * C::NX;
 #pragma unroll
-        for (int bb = 0; bb < G2; ++bb) {
+        for (int bb = 0; bb < (PL ? 0 : G2); ++bb) {
             const int blk = grp * G2 + bb;
             const int row = (dblk0 + blk) * 32 + lr;
 #pragma unroll
@@ -458,6 +603,13 @@ void kge_block_kernel(const KgeBlockArgs a) {
                             acc2[0][blk] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[r], coefs2[4 * j + r], acc2[0][blk], 0, 0, 0);
                     }
                 }
+            } else if constexpr (PL) {
+#pragma unroll
+                for (int j2 = 0; j2 < 2; ++j2) {
+                    acc2[0][blk] = kge_mma3(acc2[0][blk], tp[blk][j2], coefp[j2]);
+                    if constexpr (TRANSH && OWN_ROW) acc2b[blk] = kge_mma3(acc2b[blk], tp[blk][j2], coefp2[j2]);
+                    if constexpr (HASW) acc2[0][blk] = kge_mma3(acc2[0][blk], twp[blk][j2], coefp2[j2]);
+                }
             } else {
 #pragma unroll
                 for (int j2 = 0; j2 < 2; ++j2) {            // stream entries 16 j2 .. + 15: fragments 2 j2 and 2 j2 + 1
@@ -497,17 +649,37 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 cancel = cancel || d2[i] < thr[i];
             }
             if (__any(cancel)) {
+                auto again = [&](int i) {
+                    const int sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
+                    const int b = OWN_ROW ? oidx : sidx, n = OWN_ROW ? sidx : oidx;
+                    constexpr int ROWB = PL ? C::DP * 2 : RB;
+                    const char *qb = (const char *)(OWN_ROW ? a.own : a.str) + (size_t)b * ROWB;
+                    const char *tb = (const char *)(OWN_ROW ? a.str : a.own) + (size_t)n * ROWB;
+                    const char *wb = TRANSH ? (const char *)(OWN_ROW ? a.own2 : a.str2) + (size_t)b * ROWB : nullptr;
+                    const int64_t qp = OWN_ROW ? own_plane : str_plane, tp = OWN_ROW ? str_plane : own_plane;
+                    if constexpr (PL) return kge_direct_d2_planes<TRANSH>(qb, qp, tb, tp, wb, qp, C::DP);
+                    else if constexpr (BF16) return kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
+                    else return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
+                };
+                if constexpr (BF16) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    if (d2[i] < thr[i]) {
-                        const int sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
-                        const int b = OWN_ROW ? oidx : sidx, n = OWN_ROW ? sidx : oidx;
-                        const char *qb = (const char *)(OWN_ROW ? a.own : a.str) + (size_t)b * RB;
-                        const char *tb = (const char *)(OWN_ROW ? a.str : a.own) + (size_t)n * RB;
-                        const char *wb = TRANSH ? (const char *)(OWN_ROW ? a.own2 : a.str2) + (size_t)b * RB : nullptr;
-                        d2[i] = kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
+                    for (int i = 0; i < 16; ++i) {
+                        if (d2[i] < thr[i]) d2[i] = again(i);
+                        asm volatile("" ::: "memory");      // keeps the branch from being turned into selects
                     }
-                    asm volatile("" ::: "memory");          // keeps the branch from being turned into selects
+                } else {
+                    // fp32: a loop over the lane's entries, in line - a call costs its caller-saved registers all through the kernel, where
+                    // the bf16 pieces leave none (bf16 tables have them, and lose 0.5-1.5 % by this form)
+                    uint32_t todo = 0;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) todo |= d2[i] < thr[i] ? 1u << i : 0u;
+                    while (todo) {
+                        const int i = __builtin_ctz(todo);
+                        todo &= todo - 1;
+                        const float v = again(i);
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) d2[k] = k == i ? v : d2[k];
+                    }
                 }
             }
 #pragma unroll
@@ -587,7 +759,9 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 const float c1 = KIND == KGE_KIND_DIST ? u * dv[i] : u;
                 coef[i] = c1;
                 if constexpr (KIND == KGE_KIND_DIST) sum1[h] += c1;
-                if constexpr (TRANSH) coef2[i] = c1 * Av[i];
+                // (planes: the streamed rows are q and w^ themselves, not q - c w^ and w^)
+                if constexpr (TRANSH && PL) coef2[i] = c1 * (Av[i] - *(const float *)(side + sl * 16 + 4));
+                else if constexpr (TRANSH) coef2[i] = c1 * Av[i];
             }
         }
         if constexpr (PHASE2) {

@@ -50,6 +50,7 @@ struct Geometry {
                                         // 1-norm, and in training calls TransH rows over 512 bytes (2-norm; the matrix-core
                                         // kernels have no registers for two operands of that width)
     int pn;                             // ... the norm they compute
+    bool planes;                        // training call on the fp32 block kernels that read bf16 planes (kge_block_planes)
     bool small;                         // training call: both passes with the scores in memory (block_small.hip)
     int es, rb, dp, kind;
     int B, N, Bp, Np;
@@ -135,6 +136,7 @@ Geometry make_geometry(const kge_model_t &m, int64_t B, int64_t N, bool train = 
     g.dsplit_t = (g.bf16 && g.rb == 1024) ? 2 : 1;
     g.small = train && small_applies(g);
     if (g.small) { g.nsplit_q = kge_small_splits(g.N); g.nsplit_t = kge_small_splits(g.B); }
+    g.planes = train && !g.l1 && !g.small && g.B > 0 && g.N > 0 && kge_block_planes(g.bf16, g.rb, KGE_MODE_FWD);
     if (g.l1) {
         g.nsplit_q = kge_l1_nsplit(g.Bp, g.Np, g.dp, g.transh);
         g.nsplit_t = kge_l1_nsplit(g.Np, g.Bp, g.dp, g.transh);
@@ -162,6 +164,7 @@ struct Carver {
 
 struct Buffers {
     void *Q, *W, *Q2, *T, *Qt, *Wt, *Tt;
+    void *Q3, *W3, *T3;                // three bf16 pieces of Q, of TransH's unit normals and of T, [3][rows][dp] (Geometry::planes)
     KgeRowInfo *rowinfo; float *tn, *pos, *lossb, *gpos;
     float4 *stat_part; float *accq, *accq2; float4 *sumq; float *acct; float4 *sumt;
     float *regv;                       // L3 norms of the gathered slots: [Bp heads][Bp tails][Np negatives]
@@ -178,9 +181,12 @@ struct Buffers {
 size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
     Carver c(ws);
     const size_t es = g.es, rowsB = (size_t)g.Bp * g.dp, rowsN = (size_t)g.Np * g.dp;
-    b.Q = c.take<char>(rowsB * es);
-    b.W = g.transh ? c.take<char>(rowsB * es) : nullptr;
-    b.T = c.take<char>(rowsN * es);
+    b.Q = g.planes ? nullptr : c.take<char>(rowsB * es);
+    b.W = g.transh && !g.planes ? c.take<char>(rowsB * es) : nullptr;
+    b.T = g.planes ? nullptr : c.take<char>(rowsN * es);
+    b.Q3 = g.planes ? c.take<char>(rowsB * 6) : nullptr;
+    b.W3 = g.transh && g.planes ? c.take<char>(rowsB * 6) : nullptr;
+    b.T3 = g.planes ? c.take<char>(rowsN * 6) : nullptr;
     b.rowinfo = c.take<KgeRowInfo>(g.Bp);
     b.tn = c.take<float>(g.Np);
     b.pos = c.take<float>(g.Bp);
@@ -194,11 +200,12 @@ size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
     b.Q2 = nullptr; b.Qt = b.Wt = b.Tt = nullptr; b.lossb = b.gpos = nullptr; b.stat_part = nullptr;
     b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.C = nullptr; b.nbias = nullptr;
     if (bwd) {
-        b.Q2 = g.transh && !g.l1 ? c.take<char>(rowsB * es) : nullptr;
+        b.Q2 = g.transh && !g.l1 && !g.planes ? c.take<char>(rowsB * es) : nullptr;
         if (g.small) {
             b.S = c.take<float>((size_t)g.Bp * g.Np);
             b.C = g.bf16 ? (void *)c.take<char>((size_t)g.Bp * g.Np * 2) : (void *)b.S;
         }
+        else if (g.planes) {}
         else if (!g.l1) {
             b.Qt = c.take<char>(rowsB * es);
             b.Wt = g.transh ? c.take<char>(rowsB * es) : nullptr;
@@ -459,7 +466,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     const bool keep_weights = have_block && !g.l1 && cfg->loss == KGE_SAMPLED_SOFTMAX && b.pstore != nullptr;
 
     // (the kernels that need no transposed copy of the negatives get queries and negatives from ONE launch)
-    const bool plain_gather = have_block && (g.l1 || g.small || kge_fwd_pp_applies(g.bf16, g.rb, g.transh, g.dsplit_q));
+    const bool plain_gather = have_block && (g.l1 || g.small || g.planes || kge_fwd_pp_applies(g.bf16, g.rb, g.transh, g.dsplit_q));
     // (negatives that the call draws itself: in that launch; where the rows are gathered otherwise, in a launch of their own)
     if (gen && N > 0 && !plain_gather) {
         rc = kge_run_negatives(((uint64_t)gen->seed_hi << 32) | gen->seed_lo, gen->step, gen->step_counter, gen->tag, gen->lo,
@@ -469,7 +476,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     if (plain_gather) {
         KgeProfScope prof(KGE_PROF_GATHER, st);
         rc = kge_run_qbuild_tgather(md, h, r, t, g.B, g.Bp, g.dp, b.Q, b.W, b.Q2, b.Q32, b.W32, b.rowinfo, b.pos,
-                                    neg, g.N, g.Np, b.T, b.tn, st, nullptr, nullptr, nullptr, nullptr, b.nbias, gen);
+                                    neg, g.N, g.Np, b.T, b.tn, st, nullptr, nullptr, nullptr, nullptr, b.nbias, gen, b.Q3, b.W3, b.T3);
     }
     else rc = kge_run_qbuild(md, h, r, t, g.B, g.Bp, g.dp, b.Q, b.W, b.Q2, b.Q32, b.W32, b.rowinfo, b.pos, nullptr, st);
     if (rc != KGE_OK) return rc;
@@ -486,11 +493,11 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
         // (the two-role row-owner kernel transposes its tiles in the LDS and needs no transposed copy of the negatives)
         if (!plain_gather && (rc = kge_run_tgather_t(md, neg, g.N, g.Np, g.dp, b.T, b.Tt, b.tn, st)) != KGE_OK) return rc;
         // (nor does the two-role kernel of the pass over the negatives need transposed queries)
-        if (!kge_gradt_pp_applies(g.bf16, g.rb, g.transh, g.dsplit_t) &&
+        if (!g.planes && !kge_gradt_pp_applies(g.bf16, g.rb, g.transh, g.dsplit_t) &&
             (rc = kge_run_transpose(g.transh ? b.Q2 : b.Q, b.Qt, g.Bp, g.dp, g.bf16, st)) != KGE_OK) return rc;
-        if (g.transh && (rc = kge_run_transpose(b.W, b.Wt, g.Bp, g.dp, g.bf16, st)) != KGE_OK) return rc;
+        if (g.transh && !g.planes && (rc = kge_run_transpose(b.W, b.Wt, g.Bp, g.dp, g.bf16, st)) != KGE_OK) return rc;
         // pass 1 (row owner): loss statistics of every row and the unnormalised gradient of the queries
-        a.own = b.Q; a.own2 = b.W; a.str = b.T; a.strT = b.Tt; a.strT_ld = g.Np; a.rowinfo = b.rowinfo; a.tn = b.tn;
+        a.own = g.planes ? b.Q3 : b.Q; a.own2 = g.planes ? b.W3 : b.W; a.str = g.planes ? b.T3 : b.T; a.strT = b.Tt; a.strT_ld = g.Np; a.rowinfo = b.rowinfo; a.tn = b.tn;
         a.B = g.B; a.N = g.N; a.dp = g.dp; a.str_tiles = g.str_tiles_n; a.tiles_per_split = g.tps_q;
         a.kind = g.kind; a.loss = cfg->loss; a.gamma = cfg->gamma; a.adv_temp = cfg->adv_temp; a.c_corr = c_corr;
         a.stat_part = b.stat_part; a.acc_part = b.accq; a.acc_part2 = b.accq2; a.sum_part = b.sumq; a.own_pad = g.Bp;
@@ -533,7 +540,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     } else if (have_block) {
         // pass 2 (column owner): gradient of the shared negatives from the finished row constants
         KgeBlockArgs c = a;
-        c.own = b.T; c.own2 = nullptr; c.str = b.Q; c.str2 = b.W; c.strT = b.Qt; c.strT2 = b.Wt; c.strT_ld = g.Bp;
+        c.own = a.str; c.own2 = nullptr; c.str = a.own; c.str2 = a.own2; c.strT = b.Qt; c.strT2 = b.Wt; c.strT_ld = g.Bp;
         c.str_tiles = g.str_tiles_b; c.tiles_per_split = g.tps_t;
         c.acc_part = b.acct; c.acc_part2 = nullptr; c.sum_part = b.sumt; c.stat_part = nullptr; c.own_pad = g.Np;
         if (keep_weights) c.str2 = b.Qs; else c.pstore = nullptr;    // (str2: the scaled queries; the recomputing kernel behind streams the plain ones)

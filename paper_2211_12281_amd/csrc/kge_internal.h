@@ -67,6 +67,13 @@ constexpr int kge_block_occ(bool bf16, int rb, bool transh, int mode) {
     return (mode == KGE_MODE_SCORE && !transh && KGE_STREAM_TILE * rb <= 32 * 1024) ? 2 : 1;
 }
 
+// fp32 training passes on rows of up to 512 bytes read their operands as three bf16 planes [3][rows][dp] (x = x0 + x1 + x2, see
+// kge_split3), which the gather writes instead of the fp32 rows and their transposed copies.  With fp32 operands every wave split every
+// streamed value twice, once for each phase, on the vector pipe that the loss weights need (TransH 8,192 x 4,096 x 128: 329 + 262 us for the
+// two passes, 15 for the transposes and gathers saved; now 208 + 199.  TransE: whole call 326 -> 238 us; DistMult 4,096 x 4,096 x 96:
+// 166 -> 123).  Rows of 1,024 bytes stay: their planes leave no registers in the pass over the queries.
+constexpr bool kge_block_planes(bool bf16, int rb, int mode) { return !bf16 && rb == 512 && mode != KGE_MODE_SCORE; }
+
 // Per-row side information of the queries: squared norm of q, c = w.q (TransH), the per-row
 // constant K of the gradient coefficient exp2(x * log2e + K) (log2 domain), squared norm of the
 // (rounded) TransH normal.
@@ -75,6 +82,7 @@ struct __attribute__((aligned(16))) KgeRowInfo { float qn, c, K, wn; };
 // Arguments of one block-kernel launch.  "own" is the operand a workgroup keeps in registers
 // (queries when OWN_ROW, negatives otherwise); "str" is the operand streamed through LDS.
 struct KgeBlockArgs {
+    // (kge_block_planes: own, own2, str, str2 are bf16 planes [3][own_pad or 32 str_tiles][dp] and there are no transposed copies)
     const void *own, *own2;        // [own_pad][dp]; own2: TransH normals when OWN_ROW
     const void *str, *str2;        // [str_pad][dp]; str2: TransH normals when !OWN_ROW
     const void *strT, *strT2;      // [dp][strT_ld] transposed stream operand(s), GRAD only

@@ -32,7 +32,9 @@ int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t
                            const int32_t *neg, int N, int Np, void *T, float *tn, hipStream_t st, float *pos_out = nullptr,
                            void *q_planes = nullptr, void *t_planes = nullptr, float *t_inv_scale = nullptr,
                            float *bias = nullptr,             // bias [Np]: 0 for the N negatives, -inf behind them
-                           const KgeNegGen *gen = nullptr);   // gen->out set: neg is ignored, the ids are drawn and written there
+                           const KgeNegGen *gen = nullptr,    // gen->out set: neg is ignored, the ids are drawn and written there
+                           // fp32 tables: the rows of Q, of TransH's unit normals and of T as three bf16 pieces [3][rows][dp]; Q and T may be null
+                           void *q3 = nullptr, void *w3 = nullptr, void *t3 = nullptr);
 // gather of the negatives and their transposed copy Tt [dp][Np] in one launch
 int kge_run_tgather_t(const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T, void *Tt, float *tn,
                       hipStream_t st);

@@ -70,9 +70,11 @@ struct KgeQbuildArgs {
     float *pos_ws, *pos_out;
     _Float16 *planes;                  // optional: the two fp16 pieces of the scaled q, [2][Bp][dp], with W two more for the
                                        // unit normal (scaled by KGE_PLANE_UNIT_SCALE); then rowinfo.K = 1 / scale of the row
+    uint16_t *q3, *w3;                 // optional: the three bf16 pieces of q and of the unit normal, [3][Bp][dp] each (Q may be null then)
 };
 struct KgeTgatherArgs {
     const int32_t *neg; int N, Np; void *T; float *tn; _Float16 *planes; float *inv_scale; float *bias;
+    uint16_t *t3;                      // optional: the three bf16 pieces of the rows, [3][Np][dp] (T may be null then)
     KgeNegGen gen;                     // gen.out set: the ids are drawn here (and written to gen.out) instead of read from neg
 };
 
@@ -93,6 +95,16 @@ __device__ __forceinline__ void kge_store_planes(_Float16 *planes, int64_t n, in
     planes[i] = x1; planes[n + i] = (_Float16)(xs - (float)x1);
 }
 
+// x as three bf16 pieces (round to nearest at each step), piece p of element i at planes[p n + i]
+__device__ __forceinline__ void kge_store_pieces(uint16_t *planes, int64_t n, int64_t i, float x) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const __bf16 b = (__bf16)x;
+        planes[p * n + i] = __builtin_bit_cast(uint16_t, b);
+        x -= (float)b;
+    }
+}
+
 template <bool BF16, int SC>
 __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a) {
     const KgeModelDev &m = a.m;
@@ -105,7 +117,9 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
     if (b >= Bp) return;
     if (b >= B) {
         for (int j = lane; j < dp; j += 64) {
-            El<BF16>::st(Q, (int64_t)b * dp + j, 0.f);
+            if (Q) El<BF16>::st(Q, (int64_t)b * dp + j, 0.f);
+            if (!BF16 && a.q3) kge_store_pieces(a.q3, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
+            if (!BF16 && a.w3) kge_store_pieces(a.w3, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
             if (W) El<BF16>::st(W, (int64_t)b * dp + j, 0.f);
             if (Q2) El<BF16>::st(Q2, (int64_t)b * dp + j, 0.f);
             if (Q32) Q32[(int64_t)b * dp + j] = 0.f;
@@ -138,7 +152,9 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
         qn += qr * qr; cq += wr * qr; wn += wr * wr;          // norms of what the matrix cores will see
         wt += cx.w[k] * tv[k];
         if (j < dp) {
-            El<BF16>::st(Q, (int64_t)b * dp + j, cx.q[k]);
+            if (Q) El<BF16>::st(Q, (int64_t)b * dp + j, cx.q[k]);
+            if (!BF16 && a.q3) kge_store_pieces(a.q3, (int64_t)Bp * dp, (int64_t)b * dp + j, cx.q[k]);
+            if (!BF16 && a.w3) kge_store_pieces(a.w3, (int64_t)Bp * dp, (int64_t)b * dp + j, cx.w[k]);
             if (W) El<BF16>::st(W, (int64_t)b * dp + j, cx.w[k]);
             if (Q32) Q32[(int64_t)b * dp + j] = cx.q[k];      // unrounded copies for the 1-norm kernels
             if (W32) W32[(int64_t)b * dp + j] = cx.w[k];
@@ -193,7 +209,7 @@ __host__ __device__ inline int kge_tgather_rows_per_wave(int dp, int es) { retur
 template <bool BF16>
 __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T,
                                                  float *tn, _Float16 *planes = nullptr, float *inv_scale = nullptr,
-                                                 const KgeNegGen *gen = nullptr) {
+                                                 const KgeNegGen *gen = nullptr, uint16_t *t3 = nullptr) {
     const int lane = threadIdx.x & 63;
     const bool draw = gen && gen->out;
     uint32_t step = 0;
@@ -235,7 +251,7 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
         for (int u = 0; u < KGE_TG_INFLIGHT; ++u) {
             const int n = nbase + u * rpl + grp;
             const bool live = n < Np && lg < lpr;
-            if (live) *(uint4 *)((char *)T + ((int64_t)n * dp) * ES + lg * 16) = v[u];
+            if (live && T) *(uint4 *)((char *)T + ((int64_t)n * dp) * ES + lg * 16) = v[u];
             const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
             float s = 0.f, amax = 0.f;
 #pragma unroll
@@ -251,6 +267,19 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
                 if (o < gl) { s += __shfl_xor(s, o); amax = fmaxf(amax, __shfl_xor(amax, o)); }
             if (lg == 0 && n < Np) tn[n] = s;
             if constexpr (!BF16) {
+                if (t3 && live) {                       // the lane's four elements: one 8-byte store per plane
+                    float x[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) x[k] = __uint_as_float(w[k]);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) {
+                        typedef __bf16 b4 __attribute__((ext_vector_type(4)));
+                        b4 o;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) { o[k] = (__bf16)x[k]; x[k] -= (float)o[k]; }
+                        *(b4 *)(t3 + ((int64_t)p * Np + n) * dp + lg * 4) = o;
+                    }
+                }
                 if (planes) {
                     float inv;
                     const float sc = kge_plane_scale(amax, inv);
@@ -283,7 +312,8 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
         float s = 0.f, amax = 0.f;
         for (int j = lane; j < dp; j += 64) {
             float v = (n < N && j < m.dim) ? El<BF16>::ld(m.ent, off + j) : 0.f;
-            El<BF16>::st(T, (int64_t)n * dp + j, v);
+            if (T) El<BF16>::st(T, (int64_t)n * dp + j, v);
+            if (!BF16 && t3) kge_store_pieces(t3, (int64_t)Np * dp, (int64_t)n * dp + j, v);
             s += v * v; amax = fmaxf(amax, fabsf(v));
         }
         s = kge_wave_sum(s);
@@ -313,7 +343,7 @@ __global__ void kge_qbuild_tgather_kernel(int q_blocks, KgeQbuildArgs a, KgeTgat
     if (g.bias)                                                         // 0 for the negatives, -inf for the padding rows behind them
         for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < g.Np; n += gridDim.x * blockDim.x) g.bias[n] = n < g.N ? 0.f : -INFINITY;
     if ((int)blockIdx.x < q_blocks) kge_qbuild_body<BF16, SC>(blockIdx.x, a);
-    else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen);
+    else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen, g.t3);
 }
 
 // gather of the shared negatives AND their transposed copy in one launch: a workgroup takes 32 negatives, every
@@ -772,7 +802,7 @@ int kge_run_qbuild(const KgeModelDev &m, const int32_t *h, const int32_t *r, con
                    float *pos_out, hipStream_t st, void *planes) {
     const int grid = (Bp + 3) / 4;
     if (grid == 0) return KGE_OK;
-    const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)planes};
+    const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)planes, nullptr, nullptr};
 #define KGE_QBUILD(BF, SC) hipLaunchKernelGGL((kge_qbuild_kernel<BF, SC>), dim3(grid), dim3(256), 0, st, a)
     if (m.bf16) { KGE_SC_SWITCH(true, KGE_QBUILD) } else { KGE_SC_SWITCH(false, KGE_QBUILD) }
 #undef KGE_QBUILD
@@ -783,12 +813,13 @@ int kge_run_qbuild(const KgeModelDev &m, const int32_t *h, const int32_t *r, con
 int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t *r, const int32_t *t, int B, int Bp,
                            int dp, void *Q, void *W, void *Q2, float *Q32, float *W32, KgeRowInfo *rowinfo, float *pos_ws,
                            const int32_t *neg, int N, int Np, void *T, float *tn, hipStream_t st, float *pos_out,
-                           void *q_planes, void *t_planes, float *t_inv_scale, float *bias, const KgeNegGen *gen) {
+                           void *q_planes, void *t_planes, float *t_inv_scale, float *bias, const KgeNegGen *gen, void *q3, void *w3, void *t3) {
     const int rows_wg = 4 * kge_tgather_rows_per_wave(dp, m.bf16 ? 2 : 4);
     const int qb = (Bp + 3) / 4, tb = (Np + rows_wg - 1) / rows_wg;
     if (qb == 0 || tb == 0 || ((q_planes || t_planes) && m.bf16) || (t_planes && !t_inv_scale)) return KGE_E_INVALID_ARG;
-    const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)q_planes};
-    const KgeTgatherArgs g{neg, N, Np, T, tn, (_Float16 *)t_planes, t_inv_scale, bias, gen ? *gen : KgeNegGen{}};
+    const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)q_planes,
+                          (uint16_t *)q3, (uint16_t *)w3};
+    const KgeTgatherArgs g{neg, N, Np, T, tn, (_Float16 *)t_planes, t_inv_scale, bias, (uint16_t *)t3, gen ? *gen : KgeNegGen{}};
 #define KGE_QT(BF, SC) hipLaunchKernelGGL((kge_qbuild_tgather_kernel<BF, SC>), dim3(qb + tb), dim3(256), 0, st, qb, a, g)
     if (m.bf16) { KGE_SC_SWITCH(true, KGE_QT) } else { KGE_SC_SWITCH(false, KGE_QT) }
 #undef KGE_QT

@@ -77,3 +77,18 @@ def test_block_kernels_scores_that_outgrow_the_first_tile(orc, block_passes, sco
     for name in dir(base):
         if "outgrow" in name and name.startswith("test_"):
             getattr(base, name)(orc, scorer)
+
+
+@pytest.mark.parametrize("scorer,dim,B,N", [("transh", 128, 129, 257), ("transh", 8, 31, 33), ("transe", 40, 1, 4000), ("rotate", 128, 300, 1),
+                                            ("complex", 64, 130, 95), ("distmult", 120, 127, 161)])
+@pytest.mark.parametrize("loss", ["logsigmoid", "sampled_softmax"])
+def test_block_kernels_on_planes(orc, block_passes, scorer, dim, B, N, loss):
+    """fp32 rows of up to 512 bytes, which the block kernels read as bf16 pieces: padding columns, a row more or less than a tile; the
+    heads among the negatives and short relations, so that distances of the norm expansion cancel and are taken again from the rows."""
+    G = make_case(scorer, 3000, 9, dim, B, N, False, amp=0.3 if scorer in ("distmult", "complex") else 0.1, zipf=True)
+    if scorer in ("transe", "transh"):
+        G["rel"] *= 0.03
+        n = min(B, N // 2)
+        G["neg"][:n] = G["h"][:n]
+    kw = dict(n_ent_for_c=3000) if loss == "sampled_softmax" else dict(gamma=1.0, adv_temp=0.7)
+    base._compare(orc, scorer, loss, G, False, 3000, kw=kw)
