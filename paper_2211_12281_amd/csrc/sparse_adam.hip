@@ -399,9 +399,10 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
     if (n == 0) return;                                    // (uniform: every thread holds the same totals)
     // the list starts where `passes` exchanges of buffers end in (ka, pa); in LDS the last step writes (ka, pa) itself
     const bool in_lds = n <= SMALL_CAP;
-    // the list is collected in LDS, or, when it is longer than SMALL_CAP, in the second pair of output buffers
-    uint32_t *lk = in_lds ? (passes == 0 ? ka + base : s_key[0]) : kb + base;
-    uint32_t *lp = in_lds ? (passes == 0 ? pa + base : s_pos[0]) : pb + base;
+    // the list is collected in LDS, or, when it is longer than SMALL_CAP, in the second pair of output buffers; where the
+    // workgroup's bits are the whole id (passes == 0) it is the result, of whatever length
+    uint32_t *lk = passes == 0 ? ka + base : in_lds ? s_key[0] : kb + base;
+    uint32_t *lp = passes == 0 ? pa + base : in_lds ? s_pos[0] : pb + base;
 #pragma unroll
     for (int r = 0; r < SMALL_ROUNDS; ++r) {
         if (r < rounds) {

@@ -115,6 +115,25 @@ def test_long_runs_of_equal_ids(orc, runs):
     assert norm_err(gm[touched], rm[touched]) <= RTOL_F32 and norm_err(gv[touched], rv[touched]) <= RTOL_F32
 
 
+@pytest.mark.parametrize("n_rows,runs", [(200, [(17, 6000), (5, 3000), (199, 3100)]), (32, [(31, 4000), (3, 9)]), (11, [(4, 9000), (0, 4)]),
+                                         (64, [(63, 3073), (1, 2048)])])
+def test_long_runs_in_tables_whose_ids_fit_the_selecting_bits(orc, n_rows, runs):
+    """Runs longer than a list in LDS where no bits of the id are left to order by: the collected list is the result, and belongs
+    into the buffers that the update reads."""
+    import paper_2211_12281_amd as kge
+    theta, m, v = _state(n_rows, 64, 3, True)
+    idx = np.concatenate([np.full(n, row, np.int32) for row, n in runs])
+    grads = (np.random.default_rng(5).normal(size=(idx.size, 64)) * 1e-2).astype(F)
+    dth, dm, dv = [torch.from_numpy(a.copy()).cuda() for a in (theta, m, v)]
+    kge.sparse_adam(dth, None, dm, dv, torch.from_numpy(idx).cuda(), torch.from_numpy(grads).cuda(), 1e-3, step=2)
+    rth, rm, rv, touched = orc.sparse_adam(theta, m, v, idx, grads, float(F(1e-3)), float(F(0.9)), float(F(0.999)),
+                                           float(F(1e-8)), 2)
+    gth, gm, gv = dth.cpu().numpy(), dm.cpu().numpy(), dv.cpu().numpy()
+    assert touched.sum() == len(runs) and np.array_equal(gth[~touched], theta[~touched])
+    assert update_err_ok(gth[touched], theta[touched], rth[touched])
+    assert norm_err(gm[touched], rm[touched]) <= RTOL_F32 and norm_err(gv[touched], rv[touched]) <= RTOL_F32
+
+
 @pytest.mark.parametrize("n_rows", [4096, 65536, 1 << 21])
 def test_one_list_of_several_long_runs(orc, n_rows):
     """Ids that all fall into ONE list of the one-launch sort (the same low byte), longer than the list kept in LDS, with
