@@ -214,15 +214,21 @@ __device__ __forceinline__ void adam_apply(uint32_t key, int col, float4 g, int6
 // ---------------------------------------------------------------------------------------------
 // Up to SMALL_MAX row ids in ONE launch (the ids of a training step: 2B + N of them).  Only the grouping of equal ids and
 // the position order inside a group matter to the update, so the order is (id & 255, id >> 8, position): workgroup w owns
-// the ids whose low byte is w (low five bits, 32 workgroups, for a table of at most SMALL_FEW ids).  Two workgroups share
+// the ids whose low byte is w (low five or six bits, 32 or 64 workgroups, for a table of at most SMALL_FEW or SMALL_MID ids: lists of
+// 64 to 128 ids on average, so that an even spread never reaches the long-list path; with 32 workgroups for 8,192 ids half of the lists
+// did: 17.5 us against 8.0).  Two workgroups share
 // a compute unit (66 KB of LDS, 64 registers), so that the 256 + 32 workgroups of a step's entity and relation table run
 // in one turn (with the LDS of a whole compute unit each, the 32 past the 256th waited for a second turn: 18-20 us
 // instead of 14-18).  It reads ALL ids (a few tens of KB, from L2), counts those of lower workgroups (its place in the
 // output) and collects its own in position order; then it orders its list by the remaining bits, stable: a list
-// of up to 256 entries by counting, for every entry, the entries that come before it (one entry per thread); a longer
+// of up to 256 entries by counting, for every entry, the entries that come before it (four threads per entry); a longer
 // one (one id repeated thousands of times) after its dominant id has been split off, or, if what remains is still longer,
 // by counting passes of four bits; the list lies in LDS, or in the second pair of output buffers when it is longer than
 // SMALL_CAP.  No workgroup waits for another; several tables go into one launch (workgroup ranges).
+// What bounds it is instruction issue of sixteen waves on a compute unit, not the reading: 20,480 ids cost 5.4 us to read and count, 5
+// to collect before the elements without own ids were passed over by a scalar mask, 5 more where a hot id made a list long (every wave
+// counted all 64 candidates; now each counts four).  Alone 15.6 -> 11.8 us (Zipf ids), 2,048 ids 9.7 -> 7.0, with two tables of 8,192
+// relation ids 21.0 -> 14.2.
 // ---------------------------------------------------------------------------------------------
 constexpr int SMALL_MAX = 32768;
 constexpr int SMALL_CAP = 3072;                             // longest list that is ordered in LDS
@@ -232,14 +238,14 @@ constexpr int SMALL_DIRECT = 256;                           // longest list that
 constexpr int SMALL_PT = 256;                               // threads that take part in a counting pass (a rare path: its
                                                             // counters are kept small so that two workgroups share a compute unit)
 constexpr int SMALL_TABLES = 4;
-constexpr int SMALL_FEW = 8192;                            // a table of at most this many ids is cut into 32 parts, not 256
+constexpr int SMALL_FEW = 2048, SMALL_MID = 8192;          // a table of at most so many ids is cut into 32, 64 parts, not 256
 __host__ __device__ constexpr int small_cnt_at(int f) { return f + (f >> 4); }     // one pad word per 16: strided reads spread over banks
 
 struct SmallSort { const int32_t *idx; int M, bits, lb; uint32_t *ka, *kb, *pa, *pb; };   // bits: of the largest id; lb: of the id that select the workgroup
 // the low bits that select a table's workgroup (a function of the table alone: the order of the sorted ids, and with it
 // the association order of the sums, must not depend on what else is in the launch)
 static void small_parts(const int *ms, int n, int *lb) {
-    for (int k = 0; k < n; ++k) lb[k] = ms[k] <= SMALL_FEW ? 5 : 8;
+    for (int k = 0; k < n; ++k) lb[k] = ms[k] <= SMALL_FEW ? 5 : ms[k] <= SMALL_MID ? 6 : 8;
 }
 struct SmallSorts { SmallSort t[SMALL_TABLES]; };
 
@@ -323,6 +329,21 @@ __device__ __forceinline__ bool small_pass_trivial(const uint32_t *sk, const uin
     return true;
 }
 
+// The place of entry e (its id: key) in a list of n <= SMALL_DIRECT: the entries with a smaller id, and those with the same id that
+// come before it.  The four threads of an entry (tid / 4) count sixteen entries a step between them and add up; all return the sum.
+__device__ __forceinline__ int small_rank(const uint32_t *list, uint32_t key, int e, int n) {
+    int rank = 0;
+    const int sub = 4 * (threadIdx.x & 3);
+    for (int j0 = 0; j0 < n; j0 += 16) {
+        const int j = j0 + sub;
+        const uint4 k4 = *(const uint4 *)&list[j];         // (j < SMALL_DIRECT: inside the list's array, entries from n on are not counted)
+        rank += (j < n && (k4.x < key || (k4.x == key && j < e))) + (j + 1 < n && (k4.y < key || (k4.y == key && j + 1 < e))) +
+                (j + 2 < n && (k4.z < key || (k4.z == key && j + 2 < e))) + (j + 3 < n && (k4.w < key || (k4.w == key && j + 3 < e)));
+    }
+    rank += __shfl_xor(rank, 1);
+    return rank + __shfl_xor(rank, 2);
+}
+
 __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int wg) {
     __shared__ uint32_t s_cnt[16 * SMALL_PT + SMALL_PT];
     __shared__ uint32_t s_rc[SMALL_ROUNDS * (SMALL_NT / 64)];   // own ids of every (round, wave), then their offsets
@@ -371,6 +392,8 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
     }
     const uint64_t below = (1ull << lane) - 1ull;
     uint32_t lower = 0;                                    // ids of lower workgroups seen by this thread
+    uint32_t any = 0;                                      // bit 4 r + j: the wave holds own ids in element j of round r (uniform)
+    static_assert(4 * SMALL_ROUNDS <= 32, "a bit per element");
 #pragma unroll
     for (int r = 0; r < SMALL_ROUNDS; ++r) {
         if (r < rounds) {
@@ -381,7 +404,9 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
             for (int j = 0; j < 4; ++j) {
                 const bool in = i + j < M;
                 lower += in && (int)(e[j] & lmask) < w;
-                own += (uint32_t)__builtin_popcountll(__ballot(in && (int)(e[j] & lmask) == w));
+                const uint64_t o = __ballot(in && (int)(e[j] & lmask) == w);
+                own += (uint32_t)__builtin_popcountll(o);
+                any |= (o != 0 ? 1u : 0u) << (4 * r + j);
             }
             if (lane == 0) s_rc[r * (SMALL_NT / 64) + wave] = own;
         }
@@ -408,14 +433,18 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
         if (r < rounds) {
             const int i = 4 * (r * SMALL_NT + tid);
             const uint32_t e[4] = { id[r].x, id[r].y, id[r].z, id[r].w };
+            // (a group of 256 ids holds one of the workgroup's on average: most of the elements, and a third of the groups, none)
+            if ((any >> (4 * r) & 15u) == 0) continue;
+            uint32_t at = s_rc[r * (SMALL_NT / 64) + wave];    // plus the own ids of lower lanes in this round
             bool mine[4];
-            int before = 0;                                // own ids of lower lanes in this round
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
+                mine[j] = false;
+                if ((any >> (4 * r + j) & 1u) == 0) continue;
                 mine[j] = i + j < M && (int)(e[j] & lmask) == w;
-                before += __builtin_popcountll(__ballot(mine[j]) & below);
+                const uint64_t o = __ballot(mine[j]);
+                at = __builtin_amdgcn_mbcnt_hi((uint32_t)(o >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)o, at));
             }
-            int at = (int)s_rc[r * (SMALL_NT / 64) + wave] + before;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (mine[j]) { lk[at] = e[j]; lp[at] = (uint32_t)(i + j); ++at; }
@@ -425,33 +454,35 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
     if (passes == 0) return;
     if (n <= SMALL_DIRECT) {
         // the place of entry e: the entries with a smaller id, and those with the same id that come before it
-        if (tid < n) {
-            const uint32_t key = s_key[0][tid];
-            int rank = 0;
-            const int n4 = n & ~3;
-            for (int j = 0; j < n4; j += 4) {
-                const uint4 k4 = *(const uint4 *)&s_key[0][j];              // (the same address in every lane: a broadcast)
-                rank += (k4.x < key || (k4.x == key && j < tid)) + (k4.y < key || (k4.y == key && j + 1 < tid)) +
-                        (k4.z < key || (k4.z == key && j + 2 < tid)) + (k4.w < key || (k4.w == key && j + 3 < tid));
-            }
-            for (int j = n4; j < n; ++j) { const uint32_t kj = s_key[0][j]; rank += kj < key || (kj == key && j < tid); }
-            ka[base + rank] = key; pa[base + rank] = s_pos[0][tid];
+        const int e = tid >> 2;
+        if (e < n) {
+            const uint32_t key = s_key[0][e];
+            const int rank = small_rank(s_key[0], key, e, n);
+            if ((tid & 3) == 0) { ka[base + rank] = key; pa[base + rank] = s_pos[0][e]; }
         }
     } else {
         // A long list is usually ONE id repeated (Zipf's hottest rows): the entries with that id keep their order as one
         // group, and only the others are ordered - by counting predecessors among themselves - and placed before or
         // behind the group.  (Which id is taken only decides how fast this is.)
-        // the most frequent id among the list's first 64 entries (ties: the earliest), found by every wave for itself
+        // the most frequent id among the list's first 64 entries (ties: the earliest): wave v counts the entries 4 v .. 4 v + 3
+        constexpr int NW = SMALL_NT / 64;
+        static_assert(4 * NW == 64, "sixteen waves share the candidates");
         const uint32_t mine = lk[lane];
-        int votes = 0;
-        for (int j = 0; j < 64; ++j) votes += mine == (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
-        int best = (votes << 6) | (63 - lane);
+        int best = 0;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) { const int other = __shfl_xor(best, o); best = other > best ? other : best; }
-        const uint32_t hot = (uint32_t)__builtin_amdgcn_readlane((int)mine, 63 - (best & 63));
+        for (int u = 0; u < 4; ++u) {
+            const int j = 4 * wave + u;
+            const int votes = __builtin_popcountll(__ballot(mine == (uint32_t)__builtin_amdgcn_readlane((int)mine, j)));
+            const int v = (votes << 6) | (63 - j);
+            best = v > best ? v : best;
+        }
+        if (lane == 0) s_wave[wave] = (uint32_t)best;
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < NW; ++v) { const int x = (int)s_wave[v]; best = x > best ? x : best; }
+        const uint32_t hot = (uint32_t)__builtin_amdgcn_readlane((int)mine, __builtin_amdgcn_readfirstlane(63 - (best & 63)));
         // wave v takes the contiguous piece [v cw, (v + 1) cw) of the list, 64 consecutive entries per step (coalesced: the
         // list may lie in global memory), twice: to count, then to place; ranks inside a step come from ballots
-        constexpr int NW = SMALL_NT / 64;
         const int cw = ((n + NW - 1) / NW + 63) & ~63, wlo = wave * cw < n ? wave * cw : n, whi = wlo + cw < n ? wlo + cw : n;
         int cold = 0, less = 0;                            // of the wave (the same in every lane)
         for (int e0 = wlo; e0 < whi; e0 += 512) {
@@ -460,6 +491,7 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
             for (int u = 0; u < 8; ++u) { const int e = e0 + 64 * u + lane; k[u] = e < whi ? lk[e] : hot; }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
+                if (e0 + 64 * u >= whi) break;
                 cold += __builtin_popcountll(__ballot(k[u] != hot));
                 less += __builtin_popcountll(__ballot(k[u] < hot));
             }
@@ -484,6 +516,7 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
+                    if (e0 + 64 * u >= whi) break;
                     const int e = e0 + 64 * u + lane;
                     const bool is_cold = k[u] != hot;
                     const uint64_t mc = __ballot(is_cold);
@@ -497,18 +530,11 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
             }
             __syncthreads();
             const int nc = n_cold, n_hot = n - nc;
-            if (tid < nc) {
-                const uint32_t key = s_key[1][tid];
-                int rank = 0;
-                const int nc4 = nc & ~3;
-                for (int j = 0; j < nc4; j += 4) {
-                    const uint4 k4 = *(const uint4 *)&s_key[1][j];          // (the same address in every lane: a broadcast)
-                    rank += (k4.x < key || (k4.x == key && j < tid)) + (k4.y < key || (k4.y == key && j + 1 < tid)) +
-                            (k4.z < key || (k4.z == key && j + 2 < tid)) + (k4.w < key || (k4.w == key && j + 3 < tid));
-                }
-                for (int j = nc4; j < nc; ++j) { const uint32_t kj = s_key[1][j]; rank += kj < key || (kj == key && j < tid); }
-                const int to = base + rank + (key > hot ? n_hot : 0);
-                ka[to] = key; pa[to] = s_pos[1][tid];
+            const int e = tid >> 2;
+            if (e < nc) {
+                const uint32_t key = s_key[1][e];
+                const int to = base + small_rank(s_key[1], key, e, nc) + (key > hot ? n_hot : 0);
+                if ((tid & 3) == 0) { ka[to] = key; pa[to] = s_pos[1][e]; }
             }
             return;
         }

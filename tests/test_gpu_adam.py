@@ -115,6 +115,24 @@ def test_long_runs_of_equal_ids(orc, runs):
     assert norm_err(gm[touched], rm[touched]) <= RTOL_F32 and norm_err(gv[touched], rv[touched]) <= RTOL_F32
 
 
+@pytest.mark.parametrize("n_rows,M", [(3000, 2048), (3000, 2049), (64, 8192), (65, 8192), (40000, 8193), (33, 2048), (256, 32768)])
+@pytest.mark.parametrize("own", [1, 255, 256, 257, 1023])
+def test_lists_at_the_edges_of_the_one_launch_sort(orc, n_rows, M, own):
+    """Tables on both sides of the lines between 32, 64 and 256 workgroups, with one workgroup's list at the lengths where a list is
+    ordered otherwise; the counts of every row against numpy's, through the update with unit gradients."""
+    import paper_2211_12281_amd as kge
+    g = np.random.default_rng(M + own)
+    idx = g.integers(0, n_rows, M).astype(np.int32)
+    idx = np.where(idx % 32 == 0, idx + 1 if n_rows % 32 != 1 else (idx + 1) % n_rows, idx).clip(0, n_rows - 1).astype(np.int32)
+    at = g.choice(M, own, replace=False)
+    idx[at] = 32 * g.integers(0, (n_rows + 31) // 32, own).clip(0, (n_rows - 1) // 32)      # ids with five zero low bits
+    theta = np.zeros((n_rows, 4), F)
+    dth, dm, dv = [torch.from_numpy(theta.copy()).cuda() for _ in range(3)]
+    kge.sparse_adam(dth, None, dm, dv, torch.from_numpy(idx).cuda(), torch.ones(M, 4).cuda(), 1e-3, step=1)
+    want = np.bincount(idx, minlength=n_rows).astype(F) * F(1 - F(0.9))                     # m = (1 - beta1) sum of the gradients
+    assert norm_err(dm.cpu().numpy(), np.repeat(want[:, None], 4, 1)) <= RTOL_F32
+
+
 @pytest.mark.parametrize("n_rows,runs", [(200, [(17, 6000), (5, 3000), (199, 3100)]), (32, [(31, 4000), (3, 9)]), (11, [(4, 9000), (0, 4)]),
                                          (64, [(63, 3073), (1, 2048)])])
 def test_long_runs_in_tables_whose_ids_fit_the_selecting_bits(orc, n_rows, runs):
