@@ -105,7 +105,8 @@ __device__ __forceinline__ void kge_store_pieces(uint16_t *planes, int64_t n, in
     }
 }
 
-template <bool BF16, int SC>
+// NJ: columns per lane (dp <= 64 NJ)
+template <bool BF16, int SC, int NJ = KGE_MAXJ>
 __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a) {
     const KgeModelDev &m = a.m;
     const int32_t *h = a.h, *r = a.r, *t = a.t;
@@ -130,21 +131,21 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
         if (lane == 0) { rowinfo[b] = KgeRowInfo{0.f, 0.f, a.planes ? 1.f : 0.f, 0.f}; if (pos_ws) pos_ws[b] = 0.f; }
         return;
     }
-    KgeRowCtx<BF16> cx;
-    kge_build_query<BF16, SC>(m, h[b], r[b], lane, cx);
+    KgeRowCtx<BF16, NJ> cx;
+    kge_build_query<BF16, SC, NJ>(m, h[b], r[b], lane, cx);
     const int d = m.dim;
     const int64_t toff = (int64_t)t[b] * m.ent_ld;
     float qn = 0.f, cq = 0.f, wn = 0.f, s_pos = 0.f, wt = 0.f;
-    float tv[KGE_MAXJ];
+    float tv[NJ];
     float q_scale = 1.f, q_inv = 0.f;
     if (a.planes) {
         float amax = 0.f;
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) amax = fmaxf(amax, fabsf(cx.q[k]));
+        for (int k = 0; k < NJ; ++k) amax = fmaxf(amax, fabsf(cx.q[k]));
         q_scale = kge_plane_scale(kge_wave_max(amax), q_inv);
     }
 #pragma unroll
-    for (int k = 0; k < KGE_MAXJ; ++k) {
+    for (int k = 0; k < NJ; ++k) {
         const int j = lane + 64 * k;
         const float tj = El<BF16>::ld(m.ent, toff + (j < d ? j : 0));
         tv[k] = j < d ? tj : 0.f;
@@ -167,14 +168,14 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
     if (SC == KGE_TRANSH) { cq = kge_wave_sum(cq); wn = kge_wave_sum(wn); wt = kge_wave_sum(wt); }
     if (Q2) {   // TransH: q - c * w_hat, the operand of the negatives' gradient contraction
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) {
+        for (int k = 0; k < NJ; ++k) {
             const int j = lane + 64 * k;
             if (j < dp) El<BF16>::st(Q2, (int64_t)b * dp + j, El<BF16>::rnd(cx.q[k]) - cq * El<BF16>::rnd(cx.w[k]));
         }
     }
     // positive score by the direct formula (Table 2), fp32
 #pragma unroll
-    for (int k = 0; k < KGE_MAXJ; ++k) {
+    for (int k = 0; k < NJ; ++k) {
         if (SC == KGE_DISTMULT || SC == KGE_COMPLEX) s_pos += cx.q[k] * tv[k];
         else {
             float x = cx.q[k] - tv[k];
@@ -338,11 +339,11 @@ template <bool BF16, int SC>
 __global__ void kge_qbuild_kernel(KgeQbuildArgs a) { kge_qbuild_body<BF16, SC>(blockIdx.x, a); }
 // query build and gather of the negatives in ONE launch (the first q_blocks workgroups build queries): the two are
 // independent, and a launch of their own each would cost the second one's start-up on the critical path
-template <bool BF16, int SC>
+template <bool BF16, int SC, int NJ>
 __global__ void kge_qbuild_tgather_kernel(int q_blocks, KgeQbuildArgs a, KgeTgatherArgs g) {
     if (g.bias)                                                         // 0 for the negatives, -inf for the padding rows behind them
         for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < g.Np; n += gridDim.x * blockDim.x) g.bias[n] = n < g.N ? 0.f : -INFINITY;
-    if ((int)blockIdx.x < q_blocks) kge_qbuild_body<BF16, SC>(blockIdx.x, a);
+    if ((int)blockIdx.x < q_blocks) kge_qbuild_body<BF16, SC, NJ>(blockIdx.x, a);
     else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen, g.t3);
 }
 
@@ -456,7 +457,8 @@ struct KgeTfinishArgs {
 // PB: the partials of the queries' gradient rows are bf16 in the paired-column words that the forward pass of
 // block_sym.hip writes (word lane + 64 kk of a row: columns lane + 128 kk and lane + 64 + 128 kk; rows of 256 columns)
 // W4: the four waves of a workgroup share the splits of ONE row (each sums a quarter, in split order, the quarters in wave order)
-template <bool BF16, int SC, bool PB = false, bool W4 = false>
+// NJ: columns per lane (dim <= 64 NJ): registers decide how many rows are in flight
+template <bool BF16, int SC, bool PB = false, bool W4 = false, int NJ = KGE_MAXJ>
 __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
     const KgeModelDev &m = a.m;
     const int32_t *h = a.h, *r = a.r, *t = a.t;
@@ -471,8 +473,8 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
     const int b = W4 ? blk : blk * (blockDim.x >> 6) + wave;
     if (b >= B) return;
     const int d = m.dim, c = d >> 1;
-    KgeRowCtx<BF16> cx;
-    kge_build_query<BF16, SC>(m, h[b], r[b], lane, cx);
+    KgeRowCtx<BF16, NJ> cx;
+    kge_build_query<BF16, SC, NJ>(m, h[b], r[b], lane, cx);
     const int64_t toff = (int64_t)t[b] * m.ent_ld;
     const float gp = gpos[b];
     // the row pass leaves, per split, sums of UNNORMALISED weights relative to that split's running
@@ -487,10 +489,10 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
     // The partials of four splits are requested together (the wave would otherwise wait for one row of one split
     // at a time) and then added in split order: the sums do not depend on the grouping.
     float s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    float a1[KGE_MAXJ], a2[KGE_MAXJ], tv[KGE_MAXJ], dq[KGE_MAXJ], dtp[KGE_MAXJ];
+    float a1[NJ], a2[NJ], tv[NJ], dq[NJ], dtp[NJ];
     float wt = 0.f;
 #pragma unroll
-    for (int k = 0; k < KGE_MAXJ; ++k) {
+    for (int k = 0; k < NJ; ++k) {
         const int j = lane + 64 * k;
         a1[k] = a2[k] = 0.f;
         const float tj = El<BF16>::ld(m.ent, toff + (j < d ? j : 0));
@@ -499,7 +501,7 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
     }
     const int per = W4 ? (nsplit + 3) / 4 : nsplit, s_lo = W4 ? min(nsplit, wave * per) : 0, s_hi = W4 ? min(nsplit, s_lo + per) : nsplit;
     for (int s0 = s_lo; s0 < s_hi; s0 += 4) {
-        float kap[4], v1[4][KGE_MAXJ], v2[4][KGE_MAXJ];
+        float kap[4], v1[4][NJ], v2[4][NJ];
         float4 p[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -507,7 +509,7 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
             kap[u] = s0 + u < s_hi ? kappa(s) : 0.f;
             p[u] = m.vec ? make_float4(0.f, 0.f, 0.f, 0.f) : sum_part[(size_t)s * Bp + b];
 #pragma unroll
-            for (int k = 0; k < KGE_MAXJ; ++k) {
+            for (int k = 0; k < NJ; ++k) {
                 v1[u][k] = v2[u][k] = 0.f;
                 if constexpr (PB) continue;
                 if (64 * k >= d) continue;                 // wave-uniform: columns past the row (not every kernel writes them)
@@ -526,16 +528,16 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
         for (int u = 0; u < 4; ++u) {
             s1 += kap[u] * p[u].x; s2 += kap[u] * p[u].y; s3 += kap[u] * p[u].z;
 #pragma unroll
-            for (int k = 0; k < KGE_MAXJ; ++k) { a1[k] += kap[u] * v1[u][k]; a2[k] += kap[u] * v2[u][k]; }
+            for (int k = 0; k < NJ; ++k) { a1[k] += kap[u] * v1[u][k]; a2[k] += kap[u] * v2[u][k]; }
         }
     }
     if constexpr (W4) {
-        constexpr int NV = (SC == KGE_TRANSH ? 2 : 1) * KGE_MAXJ + 3;
+        constexpr int NV = (SC == KGE_TRANSH ? 2 : 1) * NJ + 3;
         __shared__ float quarter[3][NV * 64];
         if (wave > 0) {
             float *q = quarter[wave - 1] + lane;
 #pragma unroll
-            for (int k = 0; k < KGE_MAXJ; ++k) { q[64 * k] = a1[k]; if (SC == KGE_TRANSH) q[64 * (KGE_MAXJ + k)] = a2[k]; }
+            for (int k = 0; k < NJ; ++k) { q[64 * k] = a1[k]; if (SC == KGE_TRANSH) q[64 * (NJ + k)] = a2[k]; }
             q[64 * (NV - 3)] = s1; q[64 * (NV - 2)] = s2; q[64 * (NV - 1)] = s3;
         }
         __syncthreads();
@@ -544,20 +546,20 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
         for (int w = 0; w < 3; ++w) {
             const float *q = quarter[w] + lane;
 #pragma unroll
-            for (int k = 0; k < KGE_MAXJ; ++k) { a1[k] += q[64 * k]; if (SC == KGE_TRANSH) a2[k] += q[64 * (KGE_MAXJ + k)]; }
+            for (int k = 0; k < NJ; ++k) { a1[k] += q[64 * k]; if (SC == KGE_TRANSH) a2[k] += q[64 * (NJ + k)]; }
             s1 += q[64 * (NV - 3)]; s2 += q[64 * (NV - 2)]; s3 += q[64 * (NV - 1)];
         }
     }
     const bool mult = SC == KGE_DISTMULT || SC == KGE_COMPLEX;
-    float dwh[KGE_MAXJ];
+    float dwh[NJ];
     if (mult) {
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) { dq[k] = a1[k] + gp * tv[k]; dtp[k] = gp * cx.q[k]; }
+        for (int k = 0; k < NJ; ++k) { dq[k] = a1[k] + gp * tv[k]; dtp[k] = gp * cx.q[k]; }
     } else {
         if (SC == KGE_TRANSH) wt = kge_wave_sum(wt);
-        float u[KGE_MAXJ], d2 = 0.f;
+        float u[NJ], d2 = 0.f;
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) {
+        for (int k = 0; k < NJ; ++k) {
             u[k] = cx.q[k] - tv[k] + (SC == KGE_TRANSH ? wt * cx.w[k] : 0.f);
             d2 += u[k] * u[k];
         }
@@ -569,11 +571,11 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
         float aw = 0.f, cq = 0.f;
         if (SC == KGE_TRANSH) {
 #pragma unroll
-            for (int k = 0; k < KGE_MAXJ; ++k) { aw += pos_term(k) * cx.w[k]; cq += cx.w[k] * cx.q[k]; }
+            for (int k = 0; k < NJ; ++k) { aw += pos_term(k) * cx.w[k]; cq += cx.w[k] * cx.q[k]; }
             aw = kge_wave_sum(aw); cq = kge_wave_sum(cq);
         }
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) {
+        for (int k = 0; k < NJ; ++k) {
             const float apu = pos_term(k);
             dq[k] = a1[k] - s1 * cx.q[k] + apu;
             dtp[k] = -apu;
@@ -590,29 +592,29 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
     float wdq = 0.f;
     if (SC == KGE_TRANSH) {
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) wdq += cx.w[k] * dq[k];
+        for (int k = 0; k < NJ; ++k) wdq += cx.w[k] * dq[k];
         wdq = kge_wave_sum(wdq);
         float wdw = 0.f;
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) { dwh[k] += -cx.wh * dq[k] - wdq * cx.h[k]; wdw += cx.w[k] * dwh[k]; }
+        for (int k = 0; k < NJ; ++k) { dwh[k] += -cx.wh * dq[k] - wdq * cx.h[k]; wdw += cx.w[k] * dwh[k]; }
         wdw = kge_wave_sum(wdw);
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) dwh[k] = (dwh[k] - cx.w[k] * wdw) / cx.wnorm;
+        for (int k = 0; k < NJ; ++k) dwh[k] = (dwh[k] - cx.w[k] * wdw) / cx.wnorm;
     }
     float *gh = g_ent + (int64_t)b * d, *gt = g_ent + (int64_t)(B + b) * d;
     const int k_rel = m.rel_dim;
     float *gr = g_rel + (int64_t)b * k_rel;
     // complex scorers need the partner component of dq, held by another lane: exchange through LDS
     if (SC == KGE_COMPLEX || SC == KGE_ROTATE) {
-        __shared__ float xch[4][KGE_MAXJ * 64];
+        __shared__ float xch[4][NJ * 64];
         float *tmp = xch[threadIdx.x >> 6];
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) tmp[lane + 64 * k] = dq[k];
+        for (int k = 0; k < NJ; ++k) tmp[lane + 64 * k] = dq[k];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) {
+        for (int k = 0; k < NJ; ++k) {
             const int j = lane + 64 * k;
             if (j >= d) continue;
             const bool re = j < c;
@@ -636,7 +638,7 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
         }
     }
 #pragma unroll
-    for (int k = 0; k < KGE_MAXJ; ++k) {
+    for (int k = 0; k < NJ; ++k) {
         const int j = lane + 64 * k;
         if (j >= d) continue;
         gt[j] = dtp[k];
@@ -650,11 +652,11 @@ __device__ __forceinline__ void kge_chain_body(int blk, const KgeChainArgs &a) {
         // reg * sign(x_j) x_j^2 / ||x||_3^2 the gradient of the slot (every lane re-reads what it wrote above)
         float ch = 0.f, ct = 0.f;
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) { ch += fabsf(cx.h[k]) * cx.h[k] * cx.h[k]; ct += fabsf(tv[k]) * tv[k] * tv[k]; }
+        for (int k = 0; k < NJ; ++k) { ch += fabsf(cx.h[k]) * cx.h[k] * cx.h[k]; ct += fabsf(tv[k]) * tv[k] * tv[k]; }
         const float nh = cbrtf(kge_wave_sum(ch)), nt = cbrtf(kge_wave_sum(ct));
         const float fh = nh > 0.f ? reg / (nh * nh) : 0.f, ft = nt > 0.f ? reg / (nt * nt) : 0.f;
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) {
+        for (int k = 0; k < NJ; ++k) {
             const int j = lane + 64 * k;
             if (j >= d) continue;
             gh[j] += fh * fabsf(cx.h[k]) * cx.h[k];
@@ -746,13 +748,13 @@ template <bool BF16, int SC>
 __global__ __launch_bounds__(256) void kge_chain_kernel(KgeChainArgs a) { kge_chain_body<BF16, SC>(blockIdx.x, a); }
 // both finishing kernels in ONE launch (the first chain_blocks workgroups run the chain rule of the queries): they
 // read different partials and write different gradient rows
-template <bool BF16, int SC, bool PB = false, bool W4 = false>
+template <bool BF16, int SC, bool PB = false, bool W4 = false, int NJ = KGE_MAXJ>
 __global__ __launch_bounds__(256) void kge_chain_tfinish_kernel(int chain_blocks, KgeChainArgs c, KgeTfinishArgs t, const float *lossb, float scale,
                                          float *loss_out) {
     // (workgroup 0: the loss of the batch from the rows' losses, the reduction that would otherwise be a launch
     // of its own between the two passes)
     if (blockIdx.x == 0) kge_loss_reduce_body(lossb, c.B, scale, loss_out);
-    else if ((int)blockIdx.x <= chain_blocks) kge_chain_body<BF16, SC, PB, W4>(blockIdx.x - 1, c);
+    else if ((int)blockIdx.x <= chain_blocks) kge_chain_body<BF16, SC, PB, W4, NJ>(blockIdx.x - 1, c);
     else kge_tfinish_body<BF16, PB>(blockIdx.x - 1 - chain_blocks, t);
 }
 
@@ -820,9 +822,12 @@ int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t
     const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)q_planes,
                           (uint16_t *)q3, (uint16_t *)w3};
     const KgeTgatherArgs g{neg, N, Np, T, tn, (_Float16 *)t_planes, t_inv_scale, bias, (uint16_t *)t3, gen ? *gen : KgeNegGen{}};
-#define KGE_QT(BF, SC) hipLaunchKernelGGL((kge_qbuild_tgather_kernel<BF, SC>), dim3(qb + tb), dim3(256), 0, st, qb, a, g)
+    // (kernels for the columns of a padded row: the query is built without branches, lanes past the row read its first column again)
+#define KGE_QT_NJ(BF, SC, NJ) hipLaunchKernelGGL((kge_qbuild_tgather_kernel<BF, SC, NJ>), dim3(qb + tb), dim3(256), 0, st, qb, a, g)
+#define KGE_QT(BF, SC) do { if (dp <= 128) KGE_QT_NJ(BF, SC, 2); else if (dp <= 256) KGE_QT_NJ(BF, SC, 4); else KGE_QT_NJ(BF, SC, KGE_MAXJ); } while (0)
     if (m.bf16) { KGE_SC_SWITCH(true, KGE_QT) } else { KGE_SC_SWITCH(false, KGE_QT) }
 #undef KGE_QT
+#undef KGE_QT_NJ
     return kge_launch_status();
 }
 
@@ -925,15 +930,21 @@ int kge_run_chain_tfinish(const KgeModelDev &m, const int32_t *h, const int32_t 
         // (written by the bilinear kernels on bf16 rows of 512 bytes only)
         if (!m.bf16 || dp != 256 || m.vec || (m.scorer != KGE_DISTMULT && m.scorer != KGE_COMPLEX)) return KGE_E_INVALID_ARG;
         if (m.scorer == KGE_DISTMULT)
-            hipLaunchKernelGGL((kge_chain_tfinish_kernel<true, KGE_DISTMULT, true>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out);
+            hipLaunchKernelGGL((kge_chain_tfinish_kernel<true, KGE_DISTMULT, true, false, 4>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out);
         else
-            hipLaunchKernelGGL((kge_chain_tfinish_kernel<true, KGE_COMPLEX, true>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out);
+            hipLaunchKernelGGL((kge_chain_tfinish_kernel<true, KGE_COMPLEX, true, false, 4>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out);
         return kge_launch_status();
     }
-#define KGE_CT(BF, SC) do { if (w4) hipLaunchKernelGGL((kge_chain_tfinish_kernel<BF, SC, false, true>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out); \
-                            else hipLaunchKernelGGL((kge_chain_tfinish_kernel<BF, SC>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out); } while (0)
+    // Kernels for the columns that a row has: with arrays for 512 columns the TransH rule took 171 registers, two waves per SIMD, and with
+    // it the gradient rows of the negatives in the same launch (TransH fp32 1,024 x 1,024 x 128, whole call: 79 -> 63 us; 8,192 x 4,096
+    // step 468 -> 452; RotatE fp32 4,096 x 4,096 x 256 385 -> 372; ComplEx bf16 4,096 x 16,384 step 198 -> 196).
+#define KGE_CT_LAUNCH(BF, SC, W4, NJ) hipLaunchKernelGGL((kge_chain_tfinish_kernel<BF, SC, false, W4, NJ>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out)
+#define KGE_CT_NJ(BF, SC, W4) do { if (m.dim <= 128) KGE_CT_LAUNCH(BF, SC, W4, 2); else if (m.dim <= 256) KGE_CT_LAUNCH(BF, SC, W4, 4); else KGE_CT_LAUNCH(BF, SC, W4, KGE_MAXJ); } while (0)
+#define KGE_CT(BF, SC) do { if (w4) KGE_CT_NJ(BF, SC, true); else KGE_CT_NJ(BF, SC, false); } while (0)
     if (m.bf16) { KGE_SC_SWITCH(true, KGE_CT) } else { KGE_SC_SWITCH(false, KGE_CT) }
 #undef KGE_CT
+#undef KGE_CT_NJ
+#undef KGE_CT_LAUNCH
     return kge_launch_status();
 }
 #undef KGE_SC_SWITCH

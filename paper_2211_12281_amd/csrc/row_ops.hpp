@@ -34,9 +34,9 @@ constexpr int KGE_MAXJ = 8;   // dim <= 512 -> at most 8 columns per lane
 
 // The query of triple b (fp32, unrounded), spread over a wave: lane holds columns lane + 64*k.
 // Returns through references what the callers need besides q.
-template <bool BF16>
+template <bool BF16, int NJ = KGE_MAXJ>     // NJ: columns per lane, dim <= 64 NJ
 struct KgeRowCtx {
-    float h[KGE_MAXJ], r[KGE_MAXJ], w[KGE_MAXJ], q[KGE_MAXJ];
+    float h[NJ], r[NJ], w[NJ], q[NJ];
     float wh;      // w_hat . h     (TransH)
     float wnorm;   // ||w|| clamped (TransH)
 };
@@ -44,16 +44,16 @@ struct KgeRowCtx {
 // Builds q for one triple.  For complex scorers lane column j < d/2 pairs with j + d/2, which is a
 // different lane/slot in general, so partner values are fetched from memory again (L1/L2 hits).
 // SC >= 0 fixes the scorer at compile time (straight-line code: the loads of a row are issued together).
-template <bool BF16, int SC = -1>
+template <bool BF16, int SC = -1, int NJ = KGE_MAXJ>
 __device__ __forceinline__ void kge_build_query(const KgeModelDev &m, int hi, int ri, int lane,
-                                                KgeRowCtx<BF16> &cx) {
+                                                KgeRowCtx<BF16, NJ> &cx) {
     const int d = m.dim, c = d >> 1;
     const int64_t hoff = (int64_t)hi * m.ent_ld, roff = (int64_t)ri * m.rel_ld, woff = (int64_t)ri * m.relw_ld;
     float wn2 = 0.f, whp = 0.f;
     // Branch-free: lanes past the row read column 0 instead and are zeroed afterwards, so that all loads of the row
     // are issued together rather than one branch (and one wait) at a time.
 #pragma unroll
-    for (int k = 0; k < KGE_MAXJ; ++k) {
+    for (int k = 0; k < NJ; ++k) {
         const int j = lane + 64 * k;
         const bool ok = j < d;
         const int js = ok ? j : 0;
@@ -91,7 +91,7 @@ __device__ __forceinline__ void kge_build_query(const KgeModelDev &m, int hi, in
         const float nrm = fmaxf(sqrtf(wn2), 1e-12f), inv = 1.f / nrm;
         cx.wnorm = nrm; cx.wh = whp * inv;
 #pragma unroll
-        for (int k = 0; k < KGE_MAXJ; ++k) {
+        for (int k = 0; k < NJ; ++k) {
             cx.w[k] *= inv;                                           // unit normal
             cx.q[k] = (lane + 64 * k < d) ? cx.h[k] - cx.wh * cx.w[k] + cx.r[k] : 0.f;
         }

@@ -92,3 +92,13 @@ def test_block_kernels_on_planes(orc, block_passes, scorer, dim, B, N, loss):
         G["neg"][:n] = G["h"][:n]
     kw = dict(n_ent_for_c=3000) if loss == "sampled_softmax" else dict(gamma=1.0, adv_temp=0.7)
     base._compare(orc, scorer, loss, G, False, 3000, kw=kw)
+
+
+@pytest.mark.parametrize("scorer,bf16", [("transh", False), ("rotate", True), ("complex", False), ("transe", True), ("distmult", False)])
+@pytest.mark.parametrize("dim", [64, 128, 144, 256, 272])
+@pytest.mark.parametrize("N", [50, 2100])
+def test_columns_per_lane_of_the_row_kernels(orc, scorer, bf16, dim, N):
+    """Widths on both sides of the lines between the row kernels for 128, 256 and 512 columns, with few and with many splits."""
+    dim = dim if bf16 or dim <= 256 else 240               # (fp32 rows end at 256 columns)
+    G = make_case(scorer, 3000, 9, dim, 37, N, bf16, amp=0.3 if scorer in ("distmult", "complex") else 0.1, zipf=True)
+    base._compare(orc, scorer, "logsigmoid", G, bf16, 3000, kw=dict(gamma=1.0, adv_temp=0.7, reg_l3=1e-3))
