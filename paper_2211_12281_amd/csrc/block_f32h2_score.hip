@@ -40,6 +40,12 @@ struct ScoreH2Args {
     int B, N, Bp, Np, own_tiles, nsplit, tiles_per_split, str_tiles, xcd_per;
     float *S_out;                                      // [B][N]
 };
+// NT: scores that outgrow the L2 caches are written past them, which leaves the streamed operand its place there (67 MB, whole call:
+// DistMult 2,048 x 8,192 x 256 47.0 -> 44.7 us, TransE 50.2 -> 47.9); a template, because the compiler folds the two stores of a branch into one
+template <bool NT> __device__ __forceinline__ void h2_store(const ScoreH2Args &a, size_t i, float v) {
+    if constexpr (NT) __builtin_nontemporal_store(v, a.S_out + i);
+    else a.S_out[i] = v;
+}
 
 // workgroups that stream the same queries share a die (workgroup ids go round the 8 dies: with 8 or more splits a die
 // takes the splits congruent to it; with fewer, a split takes 8 / splits dies and the own tiles are dealt over them)
@@ -54,7 +60,7 @@ __device__ __forceinline__ bool h2_place(const ScoreH2Args &a, int &own_tile, in
     return t0 < t1;
 }
 
-template <int DP, int KIND>
+template <int DP, int KIND, bool NT>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void score_h2_kernel(const ScoreH2Args a) {
     constexpr int RB = DP * 2, KS = DP / 16;           // bytes of a plane row, k-steps of 16
@@ -178,7 +184,7 @@ void score_h2_kernel(const ScoreH2Args a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int b = t * H2_ST + 8 * (i >> 2) + 4 * g + (i & 3);
-                if (b < a.B) a.S_out[(size_t)b * a.N + oidx] = sv[i];
+                if (b < a.B) h2_store<NT>(a, (size_t)b * a.N + oidx, sv[i]);
             }
         }
     }
@@ -189,7 +195,7 @@ void score_h2_kernel(const ScoreH2Args a) {
 // - 2 q'.t + A (2 w.q' - A (2 - |w|^2)), A = w.t): the stream carries the two planes of q' AND of w (the unit normals
 // all with the scale KGE_PLANE_UNIT_SCALE), a stage of the ring holds a 256-byte piece of the rows (128 dimensions of
 // four planes of 32 queries, 32 KB) and a tile takes DP / 128 stages; the accumulators live across a tile's stages.
-template <int DP>
+template <int DP, bool NT>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, 1)))
 void score_h2_transh_kernel(const ScoreH2Args a) {
     constexpr int RB = DP * 2, HB = 256, NH = RB / HB, KH = 8;        // bytes of a plane row, of a piece; pieces; k-steps per piece
@@ -313,7 +319,7 @@ void score_h2_transh_kernel(const ScoreH2Args a) {
             for (int i = 0; i < 16; ++i) {
                 const int b = t * H2_ST + 8 * (i >> 2) + 4 * g + (i & 3);
                 const float dd = fmaxf(d2[i], 0.f);
-                if (b < a.B) a.S_out[(size_t)b * a.N + oidx] = dd > 0.f ? -dd * __builtin_amdgcn_rsqf(dd) : 0.f;   // -sqrt(d2)
+                if (b < a.B) h2_store<NT>(a, (size_t)b * a.N + oidx, dd > 0.f ? -dd * __builtin_amdgcn_rsqf(dd) : 0.f);   // -sqrt(d2)
             }
         }
     }
@@ -336,20 +342,20 @@ int launch_h2(K kern, int lds_bytes, KgeLdsLimit &lds_limit, const ScoreH2Args &
     return kge_launch_status();
 }
 
-template <int DP>
+template <int DP, bool NT>
 int launch_transh(const ScoreH2Args &a, hipStream_t st) {
     constexpr int LDS = H2_NSTAGE * (4 * H2_ST * 256) + H2_NSTAGE * 4 * 1024;
     static_assert(LDS <= 160 * 1024, "LDS budget");
     static KgeLdsLimit lds_limit;
-    return launch_h2(score_h2_transh_kernel<DP>, LDS, lds_limit, a, st);
+    return launch_h2(score_h2_transh_kernel<DP, NT>, LDS, lds_limit, a, st);
 }
 
-template <int DP, int KIND>
+template <int DP, int KIND, bool NT>
 int launch_one(const ScoreH2Args &a, hipStream_t st) {
     constexpr int LDS = H2_NSTAGE_ONE * (2 * H2_ST * DP * 2) + H2_NSTAGE_ONE * 4 * 1024;
     static_assert(2 * LDS <= 160 * 1024, "LDS budget of two workgroups");
     static KgeLdsLimit lds_limit;
-    return launch_h2(score_h2_kernel<DP, KIND>, LDS, lds_limit, a, st);
+    return launch_h2(score_h2_kernel<DP, KIND, NT>, LDS, lds_limit, a, st);
 }
 
 }  // namespace
@@ -371,7 +377,12 @@ int kge_launch_score_h2(int kind, int dp, const void *Qp, const void *Tp, const 
     a.tiles_per_split = (a.str_tiles + want - 1) / want;
     a.nsplit = (a.str_tiles + a.tiles_per_split - 1) / a.tiles_per_split;
     KgeProfScope prof(KGE_PROF_BLOCK_SCORE, st);
-    if (W32) return dp == 256 ? launch_transh<256>(a, st) : launch_transh<128>(a, st);
-    if (dp == 256) return kind == KGE_KIND_MULT ? launch_one<256, KGE_KIND_MULT>(a, st) : launch_one<256, KGE_KIND_DIST>(a, st);
-    return kind == KGE_KIND_MULT ? launch_one<128, KGE_KIND_MULT>(a, st) : launch_one<128, KGE_KIND_DIST>(a, st);
+    // (eight L2 caches of 4 MB: below, the caller may find the scores there; and whole 128-byte lines per store: of broken ones the caches
+    // merge the halves - RotatE 8,192 x 8,191 x 112: 100 us through them, 118 past them)
+    const bool nt = (int64_t)B * N * 4 > 32ll << 20 && N % 32 == 0 && ((uintptr_t)S_out & 127) == 0;
+#define H2_NT(F, ...) (nt ? F<__VA_ARGS__, true>(a, st) : F<__VA_ARGS__, false>(a, st))
+    if (W32) return dp == 256 ? H2_NT(launch_transh, 256) : H2_NT(launch_transh, 128);
+    if (dp == 256) return kind == KGE_KIND_MULT ? H2_NT(launch_one, 256, KGE_KIND_MULT) : H2_NT(launch_one, 256, KGE_KIND_DIST);
+    return kind == KGE_KIND_MULT ? H2_NT(launch_one, 128, KGE_KIND_MULT) : H2_NT(launch_one, 128, KGE_KIND_DIST);
+#undef H2_NT
 }

@@ -158,3 +158,20 @@ def test_tables_with_a_row_stride_larger_than_the_dimension(orc, scorer, bf16, d
     else:
         assert np.all(same)
     assert np.max(np.abs(sc.cpu().numpy() - rsc)) <= RTOL_F32 * np.max(np.abs(rsc))
+
+
+@pytest.mark.parametrize("scorer,dim", [("distmult", 64), ("transe", 128), ("transh", 64), ("complex", 256)])
+@pytest.mark.parametrize("N", [8191, 8192, 8224])
+def test_blocks_larger_than_the_caches_equal_their_parts(scorer, dim, N):
+    """fp32 blocks of more than 32 MB, whose stores go past the caches where rows are whole lines: the bits of the calls for a part of
+    the queries."""
+    import torch
+    import paper_2211_12281_amd as kge
+    B = 1030
+    G = make_case(scorer, 5000, 7, dim, B, N, False)
+    model = gpu_model(scorer, G, False)
+    h, r, t, neg = (dev_idx(G[k]) for k in ("h", "r", "t", "neg"))
+    pos, got = kge.score(model, h, r, t, neg)
+    for lo, hi in ((0, 33), (500, 601), (1000, B)):
+        p, s = kge.score(model, h[lo:hi].contiguous(), r[lo:hi].contiguous(), t[lo:hi].contiguous(), neg)
+        assert torch.equal(s, got[lo:hi]) and torch.equal(p, pos[lo:hi])
