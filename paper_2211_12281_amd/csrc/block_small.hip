@@ -11,10 +11,13 @@
 //               the gradients, the exponentials bound that launch (26 us instead of 19 for the RotatE case below)
 //   gradients   one launch for both operands: dQ = C T and dT = C^t Q; a workgroup makes 32 rows x 64 or 128 columns, its eight waves
 //               share out the contraction index and add up through the LDS, so that there are no partials in memory
-// (kge_loss_bwd, block kernels / here: RotatE fp32, B 448, N 1,088, d 256: 108 / 55 us; ComplEx bf16, B 640, N 1,536, d 400: 110 / 43 us;
+// (kge_loss_bwd, block kernels / here: RotatE fp32, B 448, N 1,088, d 256: 108 / 53 us; ComplEx bf16, B 640, N 1,536, d 400: 112 / 46 us;
 // the launches of the first: gather 7.6, scores 13.5, rows 5.2, gradients 19, chain rule 10 us.)
 // What bounds each launch is its latency: start-up, two or three dependent loads and the matrix instructions of one wave.
-// Arithmetic as in the block kernels: bf16 operands with fp32 accumulation, or three bf16 pieces per fp32 value.
+// Arithmetic: bf16 operands with fp32 accumulation, or three bf16 pieces per fp32 value.  On bf16 tables the coefficients are
+// finished when they are made, where the block kernels round the weight relative to a row reference (the dominating pairs are 1 and
+// round to themselves) and apply the normaliser in fp32; so dQ takes every coefficient as TWO bf16 pieces, 17 significand bits, and its
+// error stays below theirs.  dT takes the first piece alone, as their pass over the negatives does.
 #include "block_kernel.hpp"
 #include "prep_kernels.h"
 #include "row_finish.hpp"
@@ -28,7 +31,8 @@ struct SmallArgs {
     const KgeRowInfo *rowinfo;         // [Bp]
     const float *tn;                   // [Np] squared norms of the negatives
     float *S; int64_t ldS;             // [Bp][ldS] scores (written for b < B, n < N only)
-    const void *C;                     // [Bp][ldS] coefficients in the table type (zero behind the block up to a multiple of 32)
+    const uint32_t *C;                 // [Bp][ldS] coefficients (zero behind the block up to a multiple of 32): fp32, or two bf16 pieces
+                                       // (low half + high half) on bf16 tables
     int32_t B, N, Bp, Np, dp, dim;
     float *accq, *acct;                // [q_splits][Bp][dp], [t_splits][Np][dp] gradient rows (columns < dim rounded up to a tile)
     float4 *sumt;                      // [t_splits][Np] {sum of the coefficients of the column, 0, 0, 0}: distance scorers
@@ -128,8 +132,8 @@ __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile
     const int str_n = OWN_Q ? a.N : a.B;
     const int dcol = d_tile * CT + NB * lr;
     const char *X = (const char *)(OWN_Q ? a.T : a.Q) + (size_t)dcol * ES;
-    const size_t xrow = (size_t)a.dp * ES, crow = (size_t)a.ldS * ES;
-    const char *Cp = (const char *)a.C + (OWN_Q ? (size_t)o * crow : (size_t)o * ES);
+    const size_t xrow = (size_t)a.dp * ES;
+    const uint32_t *Cp = a.C + (OWN_Q ? (size_t)o * a.ldS : (size_t)o);
     kge_f32x16 acc[NB];
 #pragma unroll
     for (int h = 0; h < NB; ++h) for (int i = 0; i < 16; ++i) acc[h][i] = 0.f;
@@ -138,21 +142,18 @@ __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile
     const int s0 = split * per_split, s1 = min(steps, s0 + per_split), per = (s1 - s0 + 7) / 8;
     const int s_lo = s0 + wave * per, s_hi = min(s1, s_lo + per);
     // raw operands of a step: the lane's eight streamed rows (rows and columns behind the block: zero coefficients, zero rows)
-    struct Raw { uint32_t c[OWN_Q ? 2 * ES : 8], x[8][XW]; };
+    struct Raw { uint32_t c[8], x[8][XW]; };
     auto load = [&](int s, Raw &r) {
         const int k0 = s * 16 + 8 * g;
         if constexpr (OWN_Q) {                                  // (rows of C start 16-byte aligned)
 #pragma unroll
-            for (int e = 0; e < ES / 2; ++e) {
-                const uint4 v = *(const uint4 *)(Cp + (size_t)k0 * ES + e * 16);
+            for (int e = 0; e < 2; ++e) {
+                const uint4 v = *(const uint4 *)(Cp + k0 + 4 * e);
                 r.c[4 * e] = v.x; r.c[4 * e + 1] = v.y; r.c[4 * e + 2] = v.z; r.c[4 * e + 3] = v.w;
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if constexpr (BF16) r.c[j] = *(const uint16_t *)(Cp + (size_t)(k0 + j) * crow);
-                else r.c[j] = *(const uint32_t *)(Cp + (size_t)(k0 + j) * crow);
-            }
+            for (int j = 0; j < 8; ++j) r.c[j] = Cp[(size_t)(k0 + j) * a.ldS];
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -163,10 +164,12 @@ __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile
         }
     };
     auto step = [&](const Raw &r) {
-        Frag<BF16> fc;
+        Frag<BF16> fc, fc2;                                     // fc2: the second pieces (dQ on bf16 tables)
         if constexpr (BF16) {
-            if constexpr (OWN_Q) fc.v = make_uint4(r.c[0], r.c[1], r.c[2], r.c[3]);
-            else fc.v = make_uint4(r.c[0] | (r.c[1] << 16), r.c[2] | (r.c[3] << 16), r.c[4] | (r.c[5] << 16), r.c[6] | (r.c[7] << 16));
+            auto first = [&](int j) { return (r.c[j] & 0xffffu) | (r.c[j + 1] << 16); };
+            auto second = [&](int j) { return (r.c[j] >> 16) | (r.c[j + 1] & 0xffff0000u); };
+            fc.v = make_uint4(first(0), first(2), first(4), first(6));
+            if constexpr (OWN_Q) fc2.v = make_uint4(second(0), second(2), second(4), second(6));
         } else fc.v = kge_split3(make_uint4(r.c[0], r.c[1], r.c[2], r.c[3]), make_uint4(r.c[4], r.c[5], r.c[6], r.c[7]));
         if constexpr (!OWN_Q && KIND == KGE_KIND_DIST) {
 #pragma unroll
@@ -185,6 +188,7 @@ __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile
                 f.v = make_uint4(w[0], w[1], w[2], w[3]);
             } else
                 f.v = kge_split3(make_uint4(r.x[0][h], r.x[1][h], r.x[2][h], r.x[3][h]), make_uint4(r.x[4][h], r.x[5][h], r.x[6][h], r.x[7][h]));
+            if constexpr (BF16 && OWN_Q) acc[h] = small_mma<BF16>(acc[h], fc2, f);
             acc[h] = small_mma<BF16>(acc[h], fc, f);
         }
     };
@@ -262,18 +266,24 @@ __global__ __launch_bounds__(512) void small_grad_kernel(const SmallArgs a) {
 }
 
 // ---- rows: loss statistics of a row of S and their finish, one workgroup per query (rows past B get what kge_rowfinish_kernel gives
-// them); with C the row's coefficients in the table type (C of fp32 tables may be S itself: a thread overwrites what it has read) ----
+// them); with C the row's coefficients, fp32 or two bf16 pieces (C may be S itself: a thread overwrites what it has read) ----
 struct SmallRowsArgs {
     const float *S; int64_t ldS; int B, N, Bp; int loss; float gamma, adv_temp, c_corr, scale; const float *pos; KgeRowInfo *rowinfo;
-    float *lossb, *gpos; void *C; int bf16, dist; float4 *sumq; int q_splits;
+    float *lossb, *gpos; uint32_t *C; int bf16, dist; float4 *sumq; int q_splits;
 };
 __global__ __launch_bounds__(256) void small_rows_kernel(const SmallRowsArgs a) {
     __shared__ float red[4][4], Kb;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N, loss = a.loss;
     const int npad = (N + 31) / 32 * 32;
-    auto put = [&](int n, float c) {
-        if (a.bf16) ((__bf16 *)a.C)[(size_t)b * a.ldS + n] = (__bf16)c;
-        else ((float *)a.C)[(size_t)b * a.ldS + n] = c;
+    auto put = [&](int n, float c) -> float {                   // returns what the contraction over the negatives sees of it
+        uint32_t w = __float_as_uint(c);
+        if (a.bf16) {
+            const __bf16 x0 = (__bf16)c, x1 = (__bf16)(c - (float)x0);
+            w = (uint32_t)__builtin_bit_cast(uint16_t, x0) | (uint32_t)__builtin_bit_cast(uint16_t, x1) << 16;
+            c = (float)x0 + (float)x1;
+        }
+        a.C[(size_t)b * a.ldS + n] = w;
+        return c;
     };
     if (b >= a.B) {
         if (tid == 0) { a.lossb[b] = 0.f; a.gpos[b] = 0.f; a.rowinfo[b].K = -INFINITY; }
@@ -332,8 +342,7 @@ __global__ __launch_bounds__(256) void small_rows_kernel(const SmallRowsArgs a) 
             w *= y >= 0.f ? rcp : t * rcp;
         }
         if (a.dist) w = s < 0.f ? w * __builtin_amdgcn_rcpf(-s) : 0.f;
-        put(n, w);
-        csum += a.bf16 ? (float)(__bf16)w : w;                  // (of what the contractions see)
+        csum += put(n, w);
     };
 #pragma unroll
     for (int j = 0; j < R; ++j) {
@@ -357,7 +366,7 @@ int kge_run_small_rows(const float *S, int64_t ldS, int B, int N, int Bp, int lo
                        const float *pos, KgeRowInfo *rowinfo, float *lossb, float *gpos, hipStream_t st, void *C, bool bf16, int kind,
                        float4 *sumq, int q_splits) {
     if (Bp == 0) return KGE_OK;
-    const SmallRowsArgs a{S, ldS, B, N, Bp, loss, gamma, adv_temp, c_corr, scale, pos, rowinfo, lossb, gpos, C, bf16 ? 1 : 0,
+    const SmallRowsArgs a{S, ldS, B, N, Bp, loss, gamma, adv_temp, c_corr, scale, pos, rowinfo, lossb, gpos, (uint32_t *)C, bf16 ? 1 : 0,
                           kind == KGE_KIND_DIST ? 1 : 0, sumq, q_splits};
     hipLaunchKernelGGL(small_rows_kernel, dim3(Bp), dim3(256), 0, st, a);
     return kge_launch_status();
@@ -386,7 +395,7 @@ int kge_run_small_grad(bool bf16, int kind, const void *Q, const void *T, const 
         return KGE_E_INVALID_ARG;
     KgeProfScope prof(KGE_PROF_BLOCK_GRADT, st);
     SmallArgs a{};
-    a.Q = Q; a.T = T; a.C = C; a.ldS = ldS; a.B = B; a.N = N; a.Bp = Bp; a.Np = Np; a.dp = dp; a.dim = dim;
+    a.Q = Q; a.T = T; a.C = (const uint32_t *)C; a.ldS = ldS; a.B = B; a.N = N; a.Bp = Bp; a.Np = Np; a.dp = dp; a.dim = dim;
     a.accq = accq; a.acct = acct; a.sumt = sumt;
     const int ct = dim > 64 ? 128 : 64;
     a.d_tiles = (dim + ct - 1) / ct;

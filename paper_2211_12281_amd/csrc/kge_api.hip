@@ -168,8 +168,8 @@ struct Buffers {
     KgeRowInfo *rowinfo; float *tn, *pos, *lossb, *gpos;
     float4 *stat_part; float *accq, *accq2; float4 *sumq; float *acct; float4 *sumt;
     float *regv;                       // L3 norms of the gathered slots: [Bp heads][Bp tails][Np negatives]
-    float *S, *Q32;                    // 1-norm scorers: the score block [Bp][Np], the queries unrounded [Bp][dp]
-    void *C;                           // small blocks: the coefficients of the pairs in the table type (fp32: in place of S)
+    float *S, *Q32;                    // small blocks and 1-norm scorers: the score block [Bp][Np], later the pairs' coefficients in
+                                       // its place; the queries unrounded [Bp][dp]
     float *W32, *A, *P;                // ... TransH: the unit normals unrounded, w^ . t and sign(x) . w^ per pair [Bp][Np]
     void *Qp2, *Tp2;                   // score-only calls on fp32 tables: two fp16 planes of the scaled Q (TransH: and of W) and T
     float *t_inv;                      // ... 1 / scale of the rows of T
@@ -198,13 +198,10 @@ size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
         b.Qp2 = c.take<char>((g.transh ? 4 : 2) * rowsB * 2); b.Tp2 = c.take<char>(2 * rowsN * 2); b.t_inv = c.take<float>(g.Np);
     }
     b.Q2 = nullptr; b.Qt = b.Wt = b.Tt = nullptr; b.lossb = b.gpos = nullptr; b.stat_part = nullptr;
-    b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.C = nullptr; b.nbias = nullptr;
+    b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.nbias = nullptr;
     if (bwd) {
         b.Q2 = g.transh && !g.l1 && !g.planes ? c.take<char>(rowsB * es) : nullptr;
-        if (g.small) {
-            b.S = c.take<float>((size_t)g.Bp * g.Np);
-            b.C = g.bf16 ? (void *)c.take<char>((size_t)g.Bp * g.Np * 2) : (void *)b.S;
-        }
+        if (g.small) b.S = c.take<float>((size_t)g.Bp * g.Np);
         else if (g.planes) {}
         else if (!g.l1) {
             b.Qt = c.take<char>(rowsB * es);
@@ -510,7 +507,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     bool planned = false;
     if (have_block && (g.small || g.l1))                    // one row pass gives the loss statistics and their finish
         rc = kge_run_small_rows(b.S, g.Np, g.B, g.N, g.Bp, cfg->loss, cfg->gamma, cfg->adv_temp, c_corr, scale, b.pos, b.rowinfo, b.lossb,
-                                b.gpos, st, g.small ? b.C : g.transh ? nullptr : b.S, g.small && g.bf16, g.small ? g.kind : KGE_KIND_MULT,
+                                b.gpos, st, g.transh ? nullptr : b.S, g.small && g.bf16, g.small ? g.kind : KGE_KIND_MULT,
                                 b.sumq, g.nsplit_q);
     else if (keep_weights && plans) {
         const KgeRowFinishQArgs rf{b.stat_part, g.nsplit_q, g.Bp, g.B, g.N, cfg->loss, cfg->gamma, c_corr, scale, b.pos, b.rowinfo,
@@ -525,7 +522,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
                                cfg->gamma, c_corr, scale, b.pos, b.rowinfo, b.lossb, b.gpos, have_block ? nullptr : loss_out, st);
     if (rc != KGE_OK) return rc;
     if (g.small) {
-        rc = kge_run_small_grad(g.bf16, g.kind, b.Q, b.T, b.C, g.Np, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, g.nsplit_q, g.nsplit_t, b.accq,
+        rc = kge_run_small_grad(g.bf16, g.kind, b.Q, b.T, b.S, g.Np, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, g.nsplit_q, g.nsplit_t, b.accq,
                                 b.acct, b.sumt, st);
         if (rc != KGE_OK) return rc;
     } else if (have_block && g.l1 && g.transh) {

@@ -84,7 +84,8 @@ int kge_run_l1h_grad(bool bf16, bool own_is_query, const float *Q, const float *
                      int pn = 1);
 
 // block_small.hip: both passes for small blocks with the scores in memory (no TransH, no 1-norm); partials with finished
-// coefficients.  kge_run_small_rows also serves the 1-norm's score blocks (without C).
+// coefficients, which take the place of the scores (C = S): fp32, or two bf16 pieces in a word on bf16 tables.
+// kge_run_small_rows also serves the 1-norm's score blocks (TransH: without C).
 int kge_small_splits(int str);
 int kge_run_small_score(bool bf16, int kind, const void *Q, const void *T, const KgeRowInfo *rowinfo, const float *tn, int B, int N, int Bp,
                         int Np, int dp, int dim, float *S, int64_t ldS, hipStream_t st);

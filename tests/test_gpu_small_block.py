@@ -1,5 +1,6 @@
 """Training calls on small blocks (scores in the workspace) against the oracle at the sizes where their tiles, splits and paddings
 end; and the block kernels, which larger blocks use, on the cases of test_gpu_loss_bwd.py that are too small to reach them."""
+import numpy as np
 import pytest
 
 import test_gpu_loss_bwd as base
@@ -44,6 +45,33 @@ def test_both_sides_of_the_rule_agree(scorer, dim, bf16, loss, B, N):
     for sl in (slice(0, B), slice(B, 2 * B), slice(2 * B, 2 * B + N)):
         assert norm_err(got["g_ent"][sl].cpu().numpy(), want["g_ent"][sl].cpu().numpy()) <= tol
     assert norm_err(got["g_rel"].cpu().numpy(), want["g_rel"].cpu().numpy()) <= tol
+
+
+@pytest.mark.parametrize("scorer,dim,B,N,amp", [("distmult", 256, 300, 900, 0.5), ("distmult", 400, 130, 2500, 0.9), ("transe", 256, 200, 1024, 0.1)])
+def test_query_gradients_hold_more_than_one_bf16_of_a_coefficient(orc, scorer, dim, B, N, amp):
+    """bf16 tables, with relations that leave the heads as they are (no rounding of the query): the heads' gradient rows are then
+    sum_n c_n t_n (distances: c_n / distance (t_n - q)) with exact operands, and c_n in two bf16 pieces is within 2^-17 of itself -
+    peaked scores, whose dominating coefficient one bf16 would move by up to 2^-9."""
+    import paper_2211_12281_amd as kge
+    G = make_case(scorer, 3000, 5, dim, B, N, True, amp=amp)
+    G["rel"][:] = 1.0 if scorer == "distmult" else 0.0
+    loss, kw = ("sampled_softmax", dict(n_ent_for_c=3000)) if scorer == "distmult" else ("logsigmoid", dict(gamma=1.0, adv_temp=4.0))
+    out = kge.loss_bwd(gpu_model(scorer, G, True), loss, *(dev_idx(G[k]) for k in ("h", "r", "t", "neg")), loss_scale=1.0, **kw)
+    ref = orc.loss_bwd(scorer, loss, G["ent"], G["rel"], None, G["h"], G["r"], G["t"], G["neg"], loss_scale=1.0, **kw)
+    pos, S = orc.score_batch(scorer, G["ent"], G["rel"], None, G["h"], G["r"], G["t"], G["neg"])
+    T, q = G["ent"][G["neg"]].astype(np.float64), G["ent"][G["h"]].astype(np.float64)
+    if loss == "sampled_softmax":
+        z = np.concatenate([pos[:, None], S + np.log(2999 / N)], axis=1)
+        z = np.exp(z - z.max(axis=1, keepdims=True))
+        c, spread = z[:, 1:] / z.sum(axis=1, keepdims=True), np.abs(T)
+        terms = c @ spread
+    else:
+        w = np.exp(4.0 * (S - S.max(axis=1, keepdims=True)))
+        c = w / w.sum(axis=1, keepdims=True) / (1.0 + np.exp(-(1.0 + S))) / np.maximum(-S, 1e-30)
+        terms = np.stack([c[b] @ np.abs(T - q[b]) for b in range(B)])
+    want = ref["g_ent"][:B]
+    excess = np.abs(out["g_ent"][:B].cpu().numpy().astype(np.float64) - want) - (2.0 ** -17 * terms + RTOL_F32 * np.abs(want).max())
+    assert excess.max() <= 0, float(excess.max() / np.abs(want).max())
 
 
 @pytest.fixture
