@@ -3,7 +3,7 @@
 //
 //   1. prep      build the queries (Table 2), their norms and rounding residuals (and, for distance scorers with many query
 //                tiles, the squared norms of the candidates; otherwise the scan makes those from its tiles)
-//   2. scan      MFMA scoring of [256 queries] x [candidate tiles]; an accumulator entry that beats the
+//   2. scan      MFMA scoring of [128 or 256 queries] x [candidate tiles]; an accumulator entry that beats the
 //                query's current threshold is appended to the query's candidate buffer (rare after warm-up);
 //                the table is walked in growing chunks, thresholds are refreshed between chunks
 //   3. compact   per query: keep the KP best buffered entries (KP > K), new threshold = the KP-th value
@@ -19,7 +19,7 @@
 namespace {
 
 constexpr int TK_ST = 32;               // candidate rows per tile
-constexpr int TK_HALF = 64;             // entries of one private append area (TopkPlan::half: fewer where there are 512 splits)
+constexpr int TK_HALF = 64;             // entries of one private append area
 
 struct TopkArgs {
     const void *Qmat;                   // [Qp][dp] queries (table element type)
@@ -36,9 +36,9 @@ struct TopkArgs {
     const float *thr;                   // [Qp] current threshold (local value units)
     const float *vt;                    // [Qp] value of the held-out tail (local units), +inf when absent
     const int32_t *true_t;              // [Q] entity ids, or nullptr
-    uint2 *seg;                         // [Qp][nseg][2][half] {value bits, candidate index}: private append
+    uint2 *seg;                         // [Qp][nseg][2][TK_HALF] {value bits, candidate index}: private append
     int32_t *segcnt;                    // [Qp][nseg][2]           areas of each (query, split, lane half)
-    int32_t nseg, half;
+    int32_t nseg;
     uint32_t *rankcnt;                  // [Qp] candidates whose value beats the held-out tail's
     int32_t nq;                         // number of real queries (rows past it are padding)
     int64_t tile_lo, tile_hi;
@@ -321,8 +321,8 @@ void topk_scan_kernel(const TopkArgs a) {
                     if (vv[ob][i] > thr[ob]) {
                         const int64_t cand = tile * TK_ST + 8 * (i >> 2) + 4 * g + (i & 3);
                         // (the area's address is formed here, on the rarely taken path, instead of living in registers)
-                        if (myc[ob] < a.half)
-                            a.seg[(((size_t)qid[ob] * a.nseg + split) * 2 + g) * a.half + myc[ob]] = make_uint2(__float_as_uint(vv[ob][i]), (uint32_t)cand);
+                        if (myc[ob] < TK_HALF)
+                            a.seg[(((size_t)qid[ob] * a.nseg + split) * 2 + g) * TK_HALF + myc[ob]] = make_uint2(__float_as_uint(vv[ob][i]), (uint32_t)cand);
                         ++myc[ob];                      // counts past the area mark the overflow for the compaction
                     }
                 }
@@ -385,7 +385,7 @@ constexpr int TK_LISTCAP = 4096;
 constexpr int TK_MAXAREAS = 1024;       // 2 nseg at most
 constexpr int TK_BINS = 1024;
 __global__ __launch_bounds__(256) void topk_compact_kernel(uint2 *keep, int32_t *keepcnt, const uint2 *seg, const int32_t *segcnt,
-                                                           int nseg, int half, int nsplit, int KP, float *thr, int32_t *flag, int Q) {
+                                                           int nseg, int nsplit, int KP, float *thr, int32_t *flag, int Q) {
     __shared__ uint64_t s[TK_LISTCAP];
     __shared__ int hist[TK_BINS];
     __shared__ int abase[TK_MAXAREAS + 1];                  // start of every area's entries behind the kept list
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(uint2 *keep, int32_t 
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             c[j] = a0 + j < nareas ? segcnt[(size_t)q * nseg * 2 + a0 + j] : 0;
-            if (c[j] > half) { over = 1; c[j] = half; }
+            if (c[j] > TK_HALF) { over = 1; c[j] = TK_HALF; }
             incl += c[j];
         }
         const int own = incl;
@@ -441,7 +441,7 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(uint2 *keep, int32_t 
         for (int u = 0; u < 4; ++u) {
             const int i = i0 + u * 256;
             uint2 e = make_uint2(0u, 0u);
-            if (i < total) e = seg[((size_t)q * nseg * 2 + lo[u]) * half + (i - abase[lo[u]])];
+            if (i < total) e = seg[((size_t)q * nseg * 2 + lo[u]) * TK_HALF + (i - abase[lo[u]])];
             k[u] = pack_value(e.x, e.y);
         }
     };
@@ -1016,7 +1016,7 @@ __global__ void topk_fill_empty_kernel(int32_t *out_idx, float *out_score, int64
 }
 
 struct TopkPlan {
-    bool bf16, th, fn; int es, rb, dp, ob, own, dim; int Qp; int KP, KPP, nseg, half; int64_t npad;
+    bool bf16, th, fn; int es, rb, dp, ob, own, dim; int Qp; int KP, KPP, nseg; int64_t npad;
 };
 
 TopkPlan make_plan(const kge_model_t &m, int64_t Q, int64_t ncand, int K) {
@@ -1032,13 +1032,12 @@ TopkPlan make_plan(const kge_model_t &m, int64_t Q, int64_t ncand, int K) {
     p.Qp = (int)kge_round_up(Q, p.own);
     p.KP = (int)kge_round_up(2 * K + 56, 64);
     p.KPP = 1; while (p.KPP < p.KP) p.KPP <<= 1;
-    // splits of the candidates, each with its append areas: 512 (two workgroups per compute unit: the copies of one run beside
-    // the epilogue of the other) for one or two query tiles, about four turns of the 256 compute units above.  512 splits take
-    // areas of 30 entries instead of 64 unless there is one tile of one block: a workspace is never larger than with 256 splits
-    // of 256 queries, and an area holds as many entries per candidate it covers.
+    // Splits of the candidates, each with its append areas.  Two workgroups per compute unit, so that the copies of one run beside the
+    // epilogue of the other: 512 splits for one query tile on rows of 512 bytes (TransH, 128 queries, 5M candidates: 979 us, 256 splits
+    // 1,253), 256 for two (TransE, 256 queries, 1M: 456; 512 splits 525) and on wider rows, whose ring of stages leaves one workgroup
+    // the LDS of a compute unit (d 512, 128 queries, 1M: 550 / 595); about four turns of the 256 compute units above.
     const int tiles = p.Qp / p.own;
-    { int w = 1024 / tiles; p.nseg = w < 32 ? 32 : tiles <= 2 ? 512 : (w > 256 ? 256 : w); }
-    p.half = tiles > 2 || (tiles == 1 && p.ob == 1 && p.rb == 512) ? TK_HALF : 30;
+    { int w = 1024 / tiles; p.nseg = w < 32 ? 32 : tiles == 1 && p.rb == 512 ? 512 : (w > 256 ? 256 : w); }
     // Norms inside the scan (FN) or in a pass of their own.  Bilinear: always inside (one query tile's turn per candidate tile:
     // 9.66 against 10.0 ms for 8,192 queries over 2M rows, 0.64 against 0.92 for 256).  Distance: every query tile makes them
     // again, so inside while there are few - up to 24 for TransH (1M rows, 8 / 16 tiles: 1.41 / 2.57 inside, 1.62 / 2.72 ms
@@ -1064,7 +1063,7 @@ size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w) {
     w.rankcnt = (uint32_t *)take((size_t)p.Qp * 4); w.tmax = (uint32_t *)take(256); w.zeros = (uint32_t *)take(256);
     w.tn = p.fn ? nullptr : (float *)take((size_t)p.npad * 4);
     w.keep = (uint2 *)take((size_t)p.Qp * p.KP * 8);
-    w.seg = (uint2 *)take((size_t)p.Qp * p.nseg * 2 * p.half * 8);
+    w.seg = (uint2 *)take((size_t)p.Qp * p.nseg * 2 * TK_HALF * 8);
     w.segcnt = (int32_t *)take((size_t)p.Qp * p.nseg * 2 * 4);
     w.keyd = (double *)take((size_t)p.Qp * p.KP * 8);
     w.Wm = nullptr; w.cq = nullptr; w.qx = nullptr;
@@ -1148,16 +1147,19 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     TopkArgs base{};
     base.Qmat = w.Qm; base.Wmat = w.Wm; base.cq = w.cq; base.ent = cand0; base.ent_stride = stride; base.valid_bytes = model.dim * p.es;
     base.ncand = ncand; base.cand_lo = lo; base.tn = w.tn; base.tmax = w.tmax; base.thr = w.thr; base.vt = w.vt; base.true_t = true_t;
-    base.seg = w.seg; base.segcnt = w.segcnt; base.nseg = p.nseg; base.half = p.half; base.rankcnt = w.rankcnt; base.nq = (int)Q; base.zeros = w.zeros;
+    base.seg = w.seg; base.segcnt = w.segcnt; base.nseg = p.nseg; base.rankcnt = w.rankcnt; base.nq = (int)Q; base.zeros = w.zeros;
     const int own_tiles = p.Qp / p.own;
     const int64_t total_tiles = p.npad / TK_ST;
-    // Growing chunks: thresholds are refreshed between chunks.  The first chunk appends everything (64
-    // candidates per split and lane half fill a private area exactly); afterwards a chunk is 3x what has
-    // been seen, so a query with a well-mixed candidate order appends about 3 KP entries per chunk,
-    // spread over nsplit x 2 private areas of TK_HALF entries.
+    // Growing chunks: thresholds are refreshed between chunks.  The first chunk appends everything: it holds at most 128
+    // tiles and two per split, so that an area (one lane half: TK_ST / 2 candidates of a tile) takes 32 entries and a query
+    // 4,096; afterwards a chunk is 3x what has been seen, so a query with a well-mixed candidate order appends about 3 KP
+    // entries per chunk, spread over nsplit x 2 private areas.  Neighbouring rows that all beat the threshold fill the areas
+    // of their split: up to 128 in a row fit.
+    constexpr int FIRST_TILES = 2;
+    static_assert(FIRST_TILES * TK_ST / 2 <= TK_HALF, "the first chunk overflows no area");
     int64_t seen = 0;
     while (seen < total_tiles) {
-        int64_t tiles = seen == 0 ? (p.nseg * (TK_HALF / TK_ST) < 128 ? p.nseg * (TK_HALF / TK_ST) : 128) : 3 * seen;
+        int64_t tiles = seen == 0 ? (p.nseg * FIRST_TILES < 128 ? p.nseg * FIRST_TILES : 128) : 3 * seen;
         if (tiles > total_tiles - seen) tiles = total_tiles - seen;
         TopkArgs c = base;
         c.tile_lo = seen; c.tile_hi = seen + tiles; c.own_tiles = own_tiles;
@@ -1173,8 +1175,8 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
         if (rc != KGE_OK) return rc;
         seen += tiles;
         const int areas_of = (nsplit + 7) / 8 * 8 < p.nseg ? (nsplit + 7) / 8 * 8 : p.nseg;
-        hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)Q), dim3(256), 0, st, w.keep, w.cnt, w.seg, w.segcnt, p.nseg, p.half, areas_of,
-                           p.KP, w.thr, w.flag, (int)Q);
+        hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)Q), dim3(256), 0, st, w.keep, w.cnt, w.seg, w.segcnt, p.nseg, areas_of, p.KP,
+                           w.thr, w.flag, (int)Q);
     }
     const int64_t nres = Q * p.KP;
     const int final_lds = p.KPP * 12;

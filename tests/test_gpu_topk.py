@@ -96,6 +96,49 @@ def test_long_lists_of_appends(orc):
     _check(orc, "distmult", G, False, 0, 9300, 200, None)
 
 
+@pytest.mark.parametrize("scorer,dim,bf16,Q", [("distmult", 64, True, 200), ("transh", 64, True, 100), ("complex", 400, True, 60),
+                                               ("transe", 128, False, 128)])
+def test_neighbouring_winners_fit_an_append_area(scorer, dim, bf16, Q):
+    """Tables whose ids are sorted by type: 100 neighbouring rows beat every query's threshold.  They fit the append areas of their
+    split (50 per lane half of 64 entries), so the call takes the time of the same rows in another order and not that of the exhaustive
+    scan, which is some tens of times longer; and the same list either way."""
+    import torch
+    import paper_2211_12281_amd as kge
+    n, hot = 400_000, 100
+    g = torch.Generator(device="cuda").manual_seed(3)
+    table = torch.rand((n, dim), generator=g, device="cuda") * 0.1 + 0.01
+    at = 300_013                                           # (the chunks of the scan end at 4,096 x 4^k rows)
+    table[at:at + hot] = 0.25 + 0.01 * torch.rand((hot, dim), generator=g, device="cuda")
+    r = torch.zeros((3, dim), device="cuda")
+    if scorer in ("distmult", "complex"):
+        r[:, :dim // 2 if scorer == "complex" else dim] = 1.0
+    else:
+        r += 0.2                                           # the queries lie near the hot rows
+    relw = torch.randn((3, dim), generator=g, device="cuda") if scorer == "transh" else None
+    dt = torch.bfloat16 if bf16 else torch.float32
+    h = torch.randint(0, at, (Q,), generator=g, device="cuda", dtype=torch.int32)
+    rr = torch.randint(0, 3, (Q,), generator=g, device="cuda", dtype=torch.int32)
+    perm = torch.randperm(n, generator=g, device="cuda")
+    back = torch.empty_like(perm)
+    back[perm] = torch.arange(n, device="cuda")            # row i of the table is row back[i] of the shuffled one
+    res, times = [], []
+    for t, heads in ((table, h), (table[perm], back[h.long()].to(torch.int32))):
+        model = kge.Model(scorer, t.to(dt).contiguous(), r.to(dt), relw.to(dt) if relw is not None else None)
+        best = 1e9
+        for _ in range(4):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            idx, sc, _ = kge.topk(model, heads, rr, 0, n, 100)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+        res.append(((idx if t is table else perm[idx.long()].to(torch.int32)).cpu().numpy(), sc.cpu().numpy()))
+    assert np.array_equal(res[0][1], res[1][1])            # (ties are ordered by the table's own ids: compared as sets)
+    assert np.mean([set(a) == set(b) for a, b in zip(res[0][0], res[1][0])]) > 0.9
+    assert times[0] < 3 * times[1], times
+
+
 def test_ties_sub_ranges_and_padding(orc):
     G = make_case("distmult", 3000, 5, 32, 10, 0, False)
     for dst, src in [(1500, 3), (77, 3), (2999, 120), (10, 120), (5, 6)]:
