@@ -16,7 +16,8 @@ int kge_run_sparse_adam_plan_tables(const kge_adam_plan_t *pl, int n, hipStream_
 int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, int64_t Q, int64_t lo, int64_t hi,
                  int K, int32_t *out_idx, float *out_score, const int32_t *true_t, int64_t *out_rank, void *ws,
                  size_t ws_bytes, hipStream_t st);
-size_t kge_topk_ws(const kge_model_t &model, int64_t Q, int64_t ncand, int K);
+// (the ws functions: the bytes of the call itself, or with most set the largest of any call that is no larger in any argument)
+size_t kge_topk_ws(const kge_model_t &model, int64_t Q, int64_t ncand, int K, bool most);
 int kge_launch_score_h2(int kind, int dp, const void *Qp, const void *Tp, const float *t_inv, const float *Q32, const float *T32,
                         const float *W32, const KgeRowInfo *rowinfo, const float *tn, int B, int N, int Bp, int Np, float *S_out,
                         hipStream_t st);
@@ -286,7 +287,7 @@ size_t kge_workspace_bytes(int op, const kge_model_t *model, int64_t B, int64_t 
     case KGE_OP_SPARSE_ADAM: return N <= 4096 ? kge_sparse_adam_ws(B, (int)N) : 0;
     case KGE_OP_TOPK:
         if (validate_model(model) != KGE_OK || K < 1 || K > 256) return 0;
-        return kge_topk_ws(*model, B, N, (int)K);
+        return kge_topk_ws(*model, B, N, (int)K, true);
     case KGE_OP_PARTITION: return (N >= 1 && N <= 64) ? kge_partition_ws(B, (int)N) : 0;
     case KGE_OP_SAMPLER_BUILD: return (N >= 1 && N <= 64) ? kge_sampler_ws(B) : 0;
     default: return 0;
@@ -749,7 +750,7 @@ int kge_topk(const kge_model_t *model, const int32_t *h, const int32_t *r, int64
     if (!h || !r || !out_idx || !out_score) return KGE_E_INVALID_ARG;
     if (!ws) return KGE_E_WORKSPACE_TOO_SMALL;
     ws = align_ws(ws, ws_bytes);
-    if (kge_topk_ws(*model, Q, cand_hi - cand_lo, K) - 256 > ws_bytes) return KGE_E_WORKSPACE_TOO_SMALL;
+    if (kge_topk_ws(*model, Q, cand_hi - cand_lo, K, false) - 256 > ws_bytes) return KGE_E_WORKSPACE_TOO_SMALL;
     return kge_run_topk(*model, h, r, Q, cand_lo, cand_hi, K, out_idx, out_score, true_t, out_rank, ws, ws_bytes,
                         (hipStream_t)hip_stream);
 }

@@ -1036,7 +1036,7 @@ TopkPlan make_plan(const kge_model_t &m, int64_t Q, int64_t ncand, int K) {
     // epilogue of the other: 512 splits for one query tile on rows of 512 bytes (TransH, 128 queries, 5M candidates: 979 us, 256 splits
     // 1,253), 256 for two (TransE, 256 queries, 1M: 456; 512 splits 525) and on wider rows, whose ring of stages leaves one workgroup
     // the LDS of a compute unit (d 512, 128 queries, 1M: 550 / 595); about four turns of the 256 compute units above.
-    const int tiles = p.Qp / p.own;
+    const int tiles = p.Qp > 0 ? p.Qp / p.own : 1;
     { int w = 1024 / tiles; p.nseg = w < 32 ? 32 : tiles == 1 && p.rb == 512 ? 512 : (w > 256 ? 256 : w); }
     // Norms inside the scan (FN) or in a pass of their own.  Bilinear: always inside (one query tile's turn per candidate tile:
     // 9.66 against 10.0 ms for 8,192 queries over 2M rows, 0.64 against 0.92 for 256).  Distance: every query tile makes them
@@ -1053,7 +1053,8 @@ struct TopkWs {
     void *Wm; float *cq; double *qx;                    // TransH only
 };
 
-size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w) {
+// most: sizes that no smaller call exceeds (fewer queries can take more areas in all: 1,024 / tiles is rounded down)
+size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w, bool most = false) {
     char *b = (char *)ws; size_t off = 0;
     auto take = [&](size_t bytes) { void *q = b ? b + off : nullptr; off += (bytes + 255) / 256 * 256; return q; };
     w.Qm = take((size_t)p.Qp * p.rb);
@@ -1063,8 +1064,10 @@ size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w) {
     w.rankcnt = (uint32_t *)take((size_t)p.Qp * 4); w.tmax = (uint32_t *)take(256); w.zeros = (uint32_t *)take(256);
     w.tn = p.fn ? nullptr : (float *)take((size_t)p.npad * 4);
     w.keep = (uint2 *)take((size_t)p.Qp * p.KP * 8);
-    w.seg = (uint2 *)take((size_t)p.Qp * p.nseg * 2 * TK_HALF * 8);
-    w.segcnt = (int32_t *)take((size_t)p.Qp * p.nseg * 2 * 4);
+    size_t areas = (size_t)p.Qp * p.nseg * 2;
+    if (most && p.Qp / p.own > 4 && areas < (size_t)p.own * 1024 * 2) areas = (size_t)p.own * 1024 * 2;
+    w.seg = (uint2 *)take(areas * TK_HALF * 8);
+    w.segcnt = (int32_t *)take(areas * 4);
     w.keyd = (double *)take((size_t)p.Qp * p.KP * 8);
     w.Wm = nullptr; w.cq = nullptr; w.qx = nullptr;
     if (p.th) {
@@ -1101,11 +1104,11 @@ int scan(const TopkPlan &p, int kind, const TopkArgs &a, int own_tiles, int nspl
 
 }  // namespace
 
-size_t kge_topk_ws(const kge_model_t &model, int64_t Q, int64_t ncand, int K) {
+size_t kge_topk_ws(const kge_model_t &model, int64_t Q, int64_t ncand, int K, bool most) {
     if (Q < 0 || ncand < 0 || K < 1 || K > 256) return 0;
     TopkPlan p = make_plan(model, Q, ncand, K);
     TopkWs w;
-    return topk_carve(p, nullptr, w);
+    return topk_carve(p, nullptr, w, most);
 }
 
 int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, int64_t Q, int64_t lo, int64_t hi,

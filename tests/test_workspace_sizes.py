@@ -1,0 +1,43 @@
+"""Workspace sizes never fall as a call grows: one workspace sized for the largest batch serves every smaller one (host only)."""
+import ctypes as C
+import random
+
+import pytest
+
+import paper_2211_12281_amd.binding as b
+
+
+def _model(rng, scorer):
+    m = b.KgeModelT()
+    m.scorer, m.p_norm, m.dtype = scorer, rng.choice([1, 2, 2]), rng.randrange(2)
+    unit, most = (16, 512) if m.dtype == 1 else (8, 256)
+    m.dim = unit * rng.choice([rng.randint(1, most // unit), most // unit, most // unit // 2])
+    m.rel_dim = m.dim // 2 if scorer == b.SCORERS["rotate"] else m.dim
+    m.n_ent = m.n_rel = 10 ** 7
+    m.ent = m.rel = m.relw = 4096
+    m.ent_ld = m.rel_ld = m.relw_ld = m.dim
+    return m
+
+
+def _pair(rng, bits):
+    """A size and one that is no larger: near it, or anything below."""
+    big = int(2 ** rng.uniform(0, bits)) - (rng.random() < 0.1)
+    return big, rng.choice([big, rng.randint(0, big), max(0, big - rng.randint(0, 600))])
+
+
+def _check(pairs):
+    worse = [(c, small, large) for c, small, large in pairs if not 0 < small <= large]
+    assert not worse, (len(worse), worse[:3])
+
+
+@pytest.mark.parametrize("scorer", sorted(b.SCORERS))
+def test_topk(scorer):
+    lib, rng = b.load(), random.Random(scorer)
+    def run():
+        for _ in range(4000):
+            m = _model(rng, b.SCORERS[scorer])
+            (Q, q), (n, m_) = _pair(rng, 14), _pair(rng, 24)
+            K = rng.randint(1, 256)
+            k = rng.choice([K, rng.randint(1, K)])
+            yield (m.dtype, m.dim, (q, m_, k), (Q, n, K)), lib.kge_workspace_bytes(3, C.byref(m), q, m_, k), lib.kge_workspace_bytes(3, C.byref(m), Q, n, K)
+    _check(run())
