@@ -438,7 +438,9 @@ size_t kge_encode_workspace_bytes(int op, const kge_encoder_t *enc, int64_t B, i
  *   KGE_OP_PARTITION               B = n triples, N = D; model may be NULL
  *   KGE_OP_SAMPLER_BUILD           B = n triples, N = D; model may be NULL
  *   KGE_OP_ENCODE, KGE_OP_ENCODE_BWD  see kge_encode_workspace_bytes (these two take a kge_encoder_t)
- * Returns 0 for an invalid request.
+ * Returns 0 for an invalid request.  The size for KGE_OP_SCORE, KGE_OP_LOSS_BWD and KGE_OP_TOPK never falls as B, N or K
+ * grows: a workspace sized for the largest call of a loop serves its smaller ones (a ragged last batch) too.  A call itself needs
+ * what it uses, which may be less.
  */
 size_t kge_workspace_bytes(int op, const kge_model_t *model, int64_t B, int64_t N, int64_t K);
 

@@ -61,6 +61,9 @@ struct Geometry {
     int nsplit_t, tps_t;                // GRADT launches: splits over the queries
     int nsplit_s, tps_s;                // SCORE launches: splits over the queries
     int dsplit_q, dsplit_t;
+    // what the buffers of a training call are sized by: rows of split partials of the two passes (padded rows times splits), pairs
+    // of the score block, records of kept weights; at_most() raises them to bounds
+    size_t part_q, part_t, pairs, records;
 };
 
 constexpr int TARGET_WGS = 256;         // one workgroup per compute unit
@@ -89,13 +92,19 @@ int validate_model(const kge_model_t *m) {
 //   other rows  RotatE fp32 d 256: 512 x 1,024 102 / 50, 2,048 x 4,096 232 / 174;  ComplEx bf16 d 400: 89 / 41, 168 / 158;
 //     DistMult fp32 d 128: 68 / 39, 114 / 107;  512 x 16,384 (RotatE d 128 / ComplEx d 400): 158 / 164, 199 / 233
 // The scores of the largest block that qualifies take less memory than the split partials of the block kernels.
-bool small_applies(const Geometry &g) {
-    if (g.B == 0 || g.N == 0 || g.l1 || g.transh) return false;
+struct SmallLimits { int64_t always, most; };           // pairs up to which every block is small, above which none is
+SmallLimits small_limits(const Geometry &g) {
+    if (g.l1 || g.transh) return {0, 0};
     for (int k : {KGE_KNOB_FWD_ONE_ROLE, KGE_KNOB_GRADT_ONE_ROLE, KGE_KNOB_TWO_ROLE, KGE_KNOB_GRADT_RECOMPUTE, KGE_KNOB_BLOCK_PASSES})
-        if (kge_knob(k)) return false;
-    const int64_t pairs = (int64_t)g.Bp * g.Np;
-    if (g.bf16 && g.rb == 512) return pairs <= (g.Np >= 2 * (int64_t)g.Bp ? 1 << 22 : 1 << 21);
-    return pairs <= (g.Np <= 16 * (int64_t)g.Bp ? 7 << 20 : 1 << 22);
+        if (kge_knob(k)) return {0, 0};
+    if (g.bf16 && g.rb == 512) return {1 << 21, 1 << 22};
+    return {1 << 22, 7 << 20};
+}
+bool small_applies(const Geometry &g) {
+    if (g.B == 0 || g.N == 0) return false;
+    const SmallLimits lim = small_limits(g);
+    const bool wide = g.bf16 && g.rb == 512 ? g.Np >= 2 * (int64_t)g.Bp : g.Np <= 16 * (int64_t)g.Bp;
+    return (int64_t)g.Bp * g.Np <= (wide ? lim.most : lim.always);
 }
 
 Geometry make_geometry(const kge_model_t &m, int64_t B, int64_t N, bool train = false) {
@@ -142,6 +151,9 @@ Geometry make_geometry(const kge_model_t &m, int64_t B, int64_t N, bool train = 
         g.nsplit_q = kge_l1_nsplit(g.Bp, g.Np, g.dp, g.transh);
         g.nsplit_t = kge_l1_nsplit(g.Np, g.Bp, g.dp, g.transh);
     }
+    g.part_q = (size_t)g.nsplit_q * g.Bp; g.part_t = (size_t)g.nsplit_t * g.Np;
+    g.pairs = (size_t)g.Bp * g.Np;
+    g.records = (size_t)g.own_tiles_b * g.nsplit_q * (g.tps_q / 2);
     return g;
 }
 
@@ -202,33 +214,71 @@ size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
     b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.nbias = nullptr;
     if (bwd) {
         b.Q2 = g.transh && !g.l1 && !g.planes ? c.take<char>(rowsB * es) : nullptr;
-        if (g.small) b.S = c.take<float>((size_t)g.Bp * g.Np);
+        if (g.small) b.S = c.take<float>(g.pairs);
         else if (g.planes) {}
         else if (!g.l1) {
             b.Qt = c.take<char>(rowsB * es);
             b.Wt = g.transh ? c.take<char>(rowsB * es) : nullptr;
             b.Tt = c.take<char>(rowsN * es);
         } else {
-            b.S = c.take<float>((size_t)g.Bp * g.Np);
-            if (g.transh) { b.A = c.take<float>((size_t)g.Bp * g.Np); b.P = c.take<float>((size_t)g.Bp * g.Np); }
+            b.S = c.take<float>(g.pairs);
+            if (g.transh) { b.A = c.take<float>(g.pairs); b.P = c.take<float>(g.pairs); }
         }
         b.lossb = c.take<float>(g.Bp);
         b.gpos = c.take<float>(g.Bp);
-        b.stat_part = g.small ? nullptr : c.take<float4>((size_t)g.nsplit_q * g.Bp);
-        b.accq = c.take<float>((size_t)g.nsplit_q * rowsB);
-        b.accq2 = g.transh ? c.take<float>((size_t)g.nsplit_q * rowsB) : nullptr;
-        b.sumq = c.take<float4>((size_t)g.nsplit_q * g.Bp);
-        b.acct = c.take<float>((size_t)g.nsplit_t * rowsN);
-        b.sumt = c.take<float4>((size_t)g.nsplit_t * g.Np);
+        b.stat_part = g.small ? nullptr : c.take<float4>(g.part_q);
+        b.accq = c.take<float>(g.part_q * g.dp);
+        b.accq2 = g.transh ? c.take<float>(g.part_q * g.dp) : nullptr;
+        b.sumq = c.take<float4>(g.part_q);
+        b.acct = c.take<float>(g.part_t * g.dp);
+        b.sumt = c.take<float4>(g.part_t);
         b.regv = c.take<float>((size_t)2 * g.Bp + g.Np);
         b.nbias = c.take<float>(g.Np);
         b.pstore = b.Qs = nullptr;
         if (g.B > 0 && g.N > 0 && !g.l1 && !g.small && kge_gradp_applies(g.bf16, g.rb, g.transh, g.dsplit_q, g.kind)) {
-            b.pstore = c.take<char>((size_t)g.own_tiles_b * g.nsplit_q * (g.tps_q / 2) * 16384);
-            b.Qs = c.take<char>((size_t)g.nsplit_q * rowsB * es);
+            b.pstore = c.take<char>(g.records * 16384);
+            b.Qs = c.take<char>(g.part_q * g.dp * es);
         }
     }
     return c.off + 256;
+}
+
+// The bytes of a training call of the size of g, or of any that is no larger in B and N, whichever route that takes: what a caller
+// sizes a workspace for its largest batch by.  A call needs what it carves itself; the split counts, and with them the partials, go up
+// and down as a side of the block grows, and so do the routes.
+size_t most_ws(const Geometry &g) {
+    Buffers b;
+    size_t most = carve(g, true, nullptr, b);
+    if (g.B == 0 || g.N == 0) return most;
+    const SmallLimits lim = small_limits(g);
+    auto least = [](size_t x, size_t y) { return x < y ? x : y; };
+    auto take = [&](const Geometry &x) { const size_t bytes = carve(x, true, nullptr, b); most = bytes > most ? bytes : most; };
+    if (lim.most > 0) {
+        // splits of up to 2,048 streamed rows: ceil(Np / 2,048) Bp rows of partials with Bp Np <= lim.most
+        Geometry x = g;
+        x.small = true; x.planes = false;
+        x.pairs = least(g.pairs, (size_t)lim.most);
+        x.part_q = least((size_t)kge_small_splits(g.Np) * g.Bp, x.pairs / 2048 + g.Bp);
+        x.part_t = least((size_t)kge_small_splits(g.Bp) * g.Np, x.pairs / 2048 + g.Np);
+        take(x);
+    }
+    if ((int64_t)g.pairs > lim.always) {
+        // own tiles x splits: a split each of `target` workgroups at most, rounded up, and no split without a streamed tile
+        auto part = [&](int own_tiles, int rows, int str_tiles, int target) {
+            return (size_t)(rows / own_tiles) * least((size_t)own_tiles * str_tiles, (size_t)own_tiles + target - 1);
+        };
+        Geometry x = g;
+        x.small = false; x.planes = !g.l1 && kge_block_planes(g.bf16, g.rb, KGE_MODE_FWD);
+        if (g.l1) {
+            x.part_q = kge_l1_most_part(g.Bp, g.Np, g.dp, g.transh); x.part_t = kge_l1_most_part(g.Np, g.Bp, g.dp, g.transh);
+        } else {
+            x.part_q = part(g.own_tiles_b, g.Bp, g.str_tiles_n, TARGET_WGS * kge_block_occ(g.bf16, g.rb, g.transh, KGE_MODE_FWD));
+            x.part_t = part(g.own_tiles_n, g.Np, g.str_tiles_b, TARGET_WGS * kge_block_occ(g.bf16, g.rb, g.transh, KGE_MODE_GRADT));
+            x.records = (size_t)g.own_tiles_b * ((g.str_tiles_n + g.tps_q) / 2);
+        }
+        take(x);
+    }
+    return most;
 }
 
 KgeModelDev dev_model(const kge_model_t &m) {
@@ -280,9 +330,9 @@ size_t kge_workspace_bytes(int op, const kge_model_t *model, int64_t B, int64_t 
     case KGE_OP_SCORE:
     case KGE_OP_LOSS_BWD: {
         if (validate_model(model) != KGE_OK || B >= (1ll << 30) || N >= (1ll << 30)) return 0;
-        Geometry g = make_geometry(*model, B, N, op == KGE_OP_LOSS_BWD);
+        const Geometry g = make_geometry(*model, B, N, op == KGE_OP_LOSS_BWD);
         Buffers b;
-        return carve(g, op == KGE_OP_LOSS_BWD, nullptr, b);
+        return op == KGE_OP_LOSS_BWD ? most_ws(g) : carve(g, false, nullptr, b);
     }
     case KGE_OP_SPARSE_ADAM: return N <= 4096 ? kge_sparse_adam_ws(B, (int)N) : 0;
     case KGE_OP_TOPK:

@@ -439,6 +439,11 @@ int kge_l1_nsplit(int own_pad, int str_pad, int dp, bool transh) {
     return (chunks + cps - 1) / cps;
 }
 
+size_t kge_l1_most_part(int own_pad, int str_pad, int dp, bool transh) {
+    const size_t go = transh ? L1H_GO : L1_GO, own = own_pad / go, split = own + 1023 / (dp / L1_GD), whole = own * (str_pad / L1_GS);
+    return go * (split < whole ? split : whole);
+}
+
 int kge_run_l1_grad(bool bf16, bool own_is_query, const void *own, const void *str, const float *W, int64_t ldW, int B, int N, int own_pad,
                     int str_pad, int dp, int dim, int nsplit, float *acc_part, hipStream_t st) {
     if (own_pad % L1_GO || str_pad % L1_GS || dp % L1_GD) return KGE_E_INVALID_ARG;

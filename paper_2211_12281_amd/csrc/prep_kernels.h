@@ -71,6 +71,7 @@ int kge_run_reg_add(const float *regv, int B, int Bp, int N, float reg, float *l
 int kge_run_l1_score(bool bf16, const float *Q, const void *T, int B, int N, int Bp, int Np, int dp, int dim, float *S, int64_t ldS,
                      hipStream_t st);
 int kge_l1_nsplit(int own_pad, int str_pad, int dp, bool transh);
+size_t kge_l1_most_part(int own_pad, int str_pad, int dp, bool transh);   // rows of partials (own_pad nsplit) of any block that is no larger
 // W: the finished weights dL/dS of the pairs (kge_run_small_rows); columns past dim rounded up to 64 are not written
 int kge_run_l1_grad(bool bf16, bool own_is_query, const void *own, const void *str, const float *W, int64_t ldW, int B, int N, int own_pad,
                     int str_pad, int dp, int dim, int nsplit, float *acc_part, hipStream_t st);

@@ -41,3 +41,20 @@ def test_topk(scorer):
             k = rng.choice([K, rng.randint(1, K)])
             yield (m.dtype, m.dim, (q, m_, k), (Q, n, K)), lib.kge_workspace_bytes(3, C.byref(m), q, m_, k), lib.kge_workspace_bytes(3, C.byref(m), Q, n, K)
     _check(run())
+
+
+@pytest.mark.parametrize("op", [0, 1])                     # kge_score, kge_loss_bwd
+@pytest.mark.parametrize("scorer", sorted(b.SCORERS))
+def test_score_and_loss(scorer, op):
+    """Among the pairs: sizes around the lines between the routes of kge_loss_bwd, whose workspaces differ most."""
+    lib, rng = b.load(), random.Random(scorer + str(op))
+    def run():
+        for _ in range(12000):
+            m = _model(rng, b.SCORERS[scorer])
+            (B, B_), (N, N_) = _pair(rng, 14), _pair(rng, 15)
+            if rng.random() < 0.3:                          # (a million to eight million pairs)
+                B = int(2 ** rng.uniform(7, 13)); N = int(2 ** rng.uniform(20, 23) / B)
+                B_, N_ = max(0, B - rng.randint(0, B // 2)), max(0, N - rng.choice([0, rng.randint(0, N // 2)]))
+            yield ((scorer, m.dtype, m.dim, m.p_norm, B_, N_, B, N), lib.kge_workspace_bytes(op, C.byref(m), B_, N_, 0),
+                   lib.kge_workspace_bytes(op, C.byref(m), B, N, 0))
+    _check(run())
