@@ -427,7 +427,7 @@ int kge_encode_bwd(const kge_encoder_t *enc, const int32_t *h, const int32_t *t,
                    const int32_t *neg, int64_t N, uint64_t seed, uint64_t step, const float *proj,
                    const float *de, float *g_es, float *g_mh, float *g_mt, void *ws, size_t ws_bytes,
                    void *hip_stream);
-/* Workspace of the two calls above (op = KGE_OP_ENCODE or KGE_OP_ENCODE_BWD); 0 for invalid arguments. */
+/* Workspace of the two calls above (op = KGE_OP_ENCODE or KGE_OP_ENCODE_BWD); never less for a larger B or N; 0 for invalid arguments. */
 size_t kge_encode_workspace_bytes(int op, const kge_encoder_t *enc, int64_t B, int64_t N);
 
 /*

@@ -347,7 +347,7 @@ struct EncTnPair { EncTn g[2]; const char *feat; int64_t ldf_b; int d, fd, sps, 
 // across the lanes), pieces swizzled by 8 (row % 2).  The ids of the split's slots are fetched into the LDS first: a load in the loop
 // would wait for the copies in flight.  Columns past d or fd and slots past the section read zero bytes.
 constexpr int ENC_MAX_SPS = 1024;                            // slots per split at most
-constexpr int ENC_TN_WGS = 512;                              // (encode + encode_bwd, 24,576 slots x 768 x 256: bf16 84 us with 512 as with 384, fp32 237 / 259; 256: 86 / 285)
+constexpr int ENC_TN_WGS = 512;                              // (both calls, 24,576 slots x 768 x 256, the same slots again and again - new ones take 94: bf16 82 us, 384 workgroups 83, 256 86; fp32 242 / 265 / 292)
 template <bool BF16>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void enc_gemm_tn_kernel(const EncTnPair pr) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -484,7 +484,7 @@ __global__ void enc_split_reduce_kernel(const float *part, int nsplit_h, int nsp
     (tail ? g_mt : g_mh)[i] = s;
 }
 
-struct EncPlan { int n, es; int sps, nsplit_h, nsplit_t; };
+struct EncPlan { int n, es; int sps, nsplit_h, nsplit_t; int64_t most_splits; };   // most_splits: of any call that is no larger
 
 EncPlan enc_plan(const kge_encoder_t &e, int64_t B, int64_t N) {
     EncPlan p{};
@@ -501,6 +501,9 @@ EncPlan enc_plan(const kge_encoder_t &e, int64_t B, int64_t N) {
     while (sps < ENC_MAX_SPS && splits(sps) > most) sps += 32;
     p.sps = (int)sps;
     p.nsplit_h = (int)((B + sps - 1) / sps); p.nsplit_t = (int)((B + N + sps - 1) / sps);
+    // (sps jumps by 32, so the splits of a larger batch can be fewer; all of these bounds grow with the batch)
+    const int64_t bound = most > splits(ENC_MAX_SPS) ? most : splits(ENC_MAX_SPS);
+    p.most_splits = bound < splits(128) ? bound : splits(128);
     return p;
 }
 
@@ -561,7 +564,7 @@ int kge_validate_encoder(const kge_encoder_t *e) {
     return KGE_OK;
 }
 
-size_t kge_encode_ws(const kge_encoder_t &e, int64_t B, int64_t N, bool bwd) {
+size_t kge_encode_ws(const kge_encoder_t &e, int64_t B, int64_t N, bool bwd, bool most) {
     const EncPlan p = enc_plan(e, B, N);
     size_t off = 0;
     auto take = [&](size_t bytes) { off += (bytes + 255) / 256 * 256; };
@@ -569,7 +572,7 @@ size_t kge_encode_ws(const kge_encoder_t &e, int64_t B, int64_t N, bool bwd) {
     else {
         take(256);                                                                // zero bytes
         take((size_t)e.dim * p.n * p.es);                                         // dP
-        take((size_t)(p.nsplit_h + p.nsplit_t) * e.dim * e.feat_dim * 4);         // split partials of both contractions
+        take((size_t)(most ? p.most_splits : p.nsplit_h + p.nsplit_t) * e.dim * e.feat_dim * 4);         // split partials of both contractions
     }
     return off + 256;
 }

@@ -26,7 +26,7 @@ int kge_run_partition(const int32_t *h, const int32_t *t, int64_t n, int64_t par
 size_t kge_partition_ws(int64_t n, int D);
 size_t kge_sampler_ws(int64_t n);
 int kge_validate_encoder(const kge_encoder_t *e);
-size_t kge_encode_ws(const kge_encoder_t &e, int64_t B, int64_t N, bool bwd);
+size_t kge_encode_ws(const kge_encoder_t &e, int64_t B, int64_t N, bool bwd, bool most);
 int kge_run_encode(const kge_encoder_t &e, const int32_t *h, const int32_t *t, int64_t B, const int32_t *neg, int64_t N,
                    uint64_t seed, uint64_t step, void *e_out, float *proj_out, float *reg_out, void *ws, hipStream_t st);
 int kge_run_encode_bwd(const kge_encoder_t &e, const int32_t *h, const int32_t *t, int64_t B, const int32_t *neg, int64_t N,
@@ -368,7 +368,7 @@ int kge_step_counter_add(uint64_t *step_counter, uint64_t inc, void *hip_stream)
 size_t kge_encode_workspace_bytes(int op, const kge_encoder_t *enc, int64_t B, int64_t N) {
     if ((op != KGE_OP_ENCODE && op != KGE_OP_ENCODE_BWD) || kge_validate_encoder(enc) != KGE_OK) return 0;
     if (B < 0 || N < 0 || 2 * B + N >= (1ll << 30)) return 0;
-    return kge_encode_ws(*enc, B, N, op == KGE_OP_ENCODE_BWD);
+    return kge_encode_ws(*enc, B, N, op == KGE_OP_ENCODE_BWD, true);
 }
 
 int kge_encode(const kge_encoder_t *enc, const int32_t *h, const int32_t *t, int64_t B, const int32_t *neg, int64_t N,
@@ -382,7 +382,7 @@ int kge_encode(const kge_encoder_t *enc, const int32_t *h, const int32_t *t, int
     if (2 * B + N > 0 && (!e_out || !proj_out)) return KGE_E_INVALID_ARG;
     if (!ws) return KGE_E_WORKSPACE_TOO_SMALL;
     ws = align_ws(ws, ws_bytes);
-    if (kge_encode_ws(*enc, B, N, false) - 256 > ws_bytes) return KGE_E_WORKSPACE_TOO_SMALL;
+    if (kge_encode_ws(*enc, B, N, false, false) - 256 > ws_bytes) return KGE_E_WORKSPACE_TOO_SMALL;
     return kge_run_encode(*enc, h, t, B, neg, N, seed, step, e_out, proj_out, reg_out, ws, (hipStream_t)hip_stream);
 }
 
@@ -398,7 +398,7 @@ int kge_encode_bwd(const kge_encoder_t *enc, const int32_t *h, const int32_t *t,
     if (!g_mh || !g_mt) return KGE_E_INVALID_ARG;
     if (!ws) return KGE_E_WORKSPACE_TOO_SMALL;
     ws = align_ws(ws, ws_bytes);
-    if (kge_encode_ws(*enc, B, N, true) - 256 > ws_bytes) return KGE_E_WORKSPACE_TOO_SMALL;
+    if (kge_encode_ws(*enc, B, N, true, false) - 256 > ws_bytes) return KGE_E_WORKSPACE_TOO_SMALL;
     return kge_run_encode_bwd(*enc, h, t, B, neg, N, seed, step, proj, de, g_es, g_mh, g_mt, ws, (hipStream_t)hip_stream);
 }
 

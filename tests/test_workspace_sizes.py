@@ -58,3 +58,20 @@ def test_score_and_loss(scorer, op):
             yield ((scorer, m.dtype, m.dim, m.p_norm, B_, N_, B, N), lib.kge_workspace_bytes(op, C.byref(m), B_, N_, 0),
                    lib.kge_workspace_bytes(op, C.byref(m), B, N, 0))
     _check(run())
+
+
+@pytest.mark.parametrize("op", [6, 7])                     # kge_encode, kge_encode_bwd
+def test_encoder(op):
+    lib, rng = b.load(), random.Random(op)
+    def run():
+        for _ in range(20000):
+            e = b.KgeEncoderT()
+            e.dtype = rng.randrange(2)
+            unit = 16 if e.dtype == 1 else 8
+            e.dim, e.feat_dim = unit * rng.randint(1, 512 // unit), unit * rng.choice([rng.randint(1, 1024 // unit), 768 // unit])
+            e.n_ent, e.ent_ld, e.feat_ld, e.m_ld = 10 ** 6, e.dim, e.feat_dim, e.feat_dim
+            e.ent_s = e.feat = e.m_h = e.m_t = 4096
+            (B, B_), (N, N_) = _pair(rng, 14), _pair(rng, 15)
+            yield ((e.dtype, e.dim, e.feat_dim, B_, N_, B, N), lib.kge_encode_workspace_bytes(op, C.byref(e), B_, N_),
+                   lib.kge_encode_workspace_bytes(op, C.byref(e), B, N))
+    _check(run())
