@@ -221,6 +221,7 @@ struct KgeBlockCfg {
     static_assert(NSTAGE >= 2, "two stages must fit");
     static_assert(X_BYTES % 4096 == 0 && XT_BYTES % 4096 == 0, "tile copies must divide over four waves");
     static_assert((NSTAGE - 2) * LPW < 64, "vmcnt range");
+    static_assert(!TRANSH || BF16 || PL || MODE == KGE_MODE_SCORE, "TransH trains on bf16 rows, on planes, or on the vector pipe");
     static_assert(OW == 1 || !TRANSH, "two own fragments per wave leave no registers for the TransH operands");
     static_assert(KS % 8 == 0, "phase 1 works in groups of four fragments, split in two halves");
 };
@@ -266,7 +267,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
     uint4 ownw[(TRANSH && OWN_ROW && !PL) ? C::KS : 1];
     // the own operand as bf16 pieces, sixteen contraction indices per entry
     constexpr bool X3 = C::X3, WL = C::WL;
-    KgeP3 ownp[X3 ? OW : 1][X3 ? C::KS / 2 : 1], ownwp[(X3 && TRANSH && OWN_ROW && !PL) ? C::KS / 2 : 1];
+    KgeP3 ownp[X3 ? OW : 1][X3 ? C::KS / 2 : 1];
     float o_qn[OW], o_c[OW], o_wn[OW], o_tn[OW];          // own-side scalars
 #pragma unroll
     for (int h = 0; h < OW; ++h) {
@@ -447,10 +448,6 @@ void kge_block_kernel(const KgeBlockArgs a) {
         for (int h = 0; h < OW; ++h)
 #pragma unroll
             for (int k2 = 0; k2 < C::KS / 2; ++k2) ownp[h][k2] = kge_split3(own[h][2 * k2], own[h][2 * k2 + 1]);
-        if constexpr (TRANSH && OWN_ROW) {
-#pragma unroll
-            for (int k2 = 0; k2 < C::KS / 2; ++k2) ownwp[k2] = kge_split3(ownw[2 * k2], ownw[2 * k2 + 1]);
-        }
     }
 
     // ---- state of the tile in work (set by the loops below, used by the pieces) -------------------
@@ -469,7 +466,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
     };
     kge_f32x16 acc[OW], accw;                              // phase-1 accumulators: [stream, own]
     uint4 bf[OW][2], bf2[2];                               // bf16 B-operands of phase 2
-    float coefs[(BF16 || X3) ? 1 : 16], coefs2[(BF16 || X3) ? 1 : 16];   // fp32 B-operands of phase 2 (OW == 1) ...
+    float coefs[(BF16 || X3) ? 1 : 16];                    // fp32 B-operands of phase 2 (OW == 1) ...
     KgeP3 coefp[2], coefp2[2];                             // ... or their bf16 pieces
 
     // ---- phase 1: acc[h][stream, own] = X_tile . own^t; a fragment read from the LDS feeds all own fragments
@@ -523,8 +520,6 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 const KgeP3 x = kge_split3(av[ks], av[ks + 1]);
 #pragma unroll
                 for (int h = 0; h < OW; ++h) acc[h] = kge_mma3(acc[h], x, ownp[h][ks >> 1]);
-                if constexpr (TRANSH && OWN_ROW) accw = kge_mma3(accw, x, ownwp[ks >> 1]);
-                if constexpr (HASW) accw = kge_mma3(accw, kge_split3(aw[ks], aw[ks + 1]), ownp[0][ks >> 1]);
             }
         }
     };
@@ -592,16 +587,8 @@ void kge_block_kernel(const KgeBlockArgs a) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const kge_f32x4 fa = __builtin_bit_cast(kge_f32x4, av2[blk][j]);
-                    kge_f32x4 fw;
-                    if constexpr (HASW) fw = __builtin_bit_cast(kge_f32x4, aw2[blk][j]);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        acc2[0][blk] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[r], coefs[4 * j + r], acc2[0][blk], 0, 0, 0);
-                        if constexpr (TRANSH && OWN_ROW)
-                            acc2b[blk] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[r], coefs2[4 * j + r], acc2b[blk], 0, 0, 0);
-                        if constexpr (HASW)
-                            acc2[0][blk] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[r], coefs2[4 * j + r], acc2[0][blk], 0, 0, 0);
-                    }
+                    for (int r = 0; r < 4; ++r) acc2[0][blk] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[r], coefs[4 * j + r], acc2[0][blk], 0, 0, 0);
                 }
             } else if constexpr (PL) {
 #pragma unroll
@@ -615,9 +602,6 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 for (int j2 = 0; j2 < 2; ++j2) {            // stream entries 16 j2 .. + 15: fragments 2 j2 and 2 j2 + 1
                     const KgeP3 x = kge_split3(av2[blk][2 * j2], av2[blk][2 * j2 + 1]);
                     acc2[0][blk] = kge_mma3(acc2[0][blk], x, coefp[j2]);
-                    if constexpr (TRANSH && OWN_ROW) acc2b[blk] = kge_mma3(acc2b[blk], x, coefp2[j2]);
-                    if constexpr (HASW)
-                        acc2[0][blk] = kge_mma3(acc2[0][blk], kge_split3(aw2[blk][2 * j2], aw2[blk][2 * j2 + 1]), coefp2[j2]);
                 }
             }
         }
@@ -780,7 +764,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 }
             } else if constexpr (!X3) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) { coefs[i] = coef[i]; if constexpr (TRANSH) coefs2[i] = coef2[i]; }
+                for (int i = 0; i < 16; ++i) coefs[i] = coef[i];
             } else {
                 auto four = [](const float *c) { return make_uint4(__float_as_uint(c[0]), __float_as_uint(c[1]), __float_as_uint(c[2]), __float_as_uint(c[3])); };
 #pragma unroll

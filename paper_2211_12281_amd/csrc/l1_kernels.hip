@@ -17,7 +17,7 @@ namespace {
 
 constexpr int L1_TILE = 64;            // rows and columns of a staged tile
 constexpr int L1_PITCH = 68;           // floats per LDS row
-constexpr float L1_LOG2E = 1.4426950408889634f, L1_LN2 = 0.6931471805599453f;
+constexpr float L1_LOG2E = 1.4426950408889634f;
 constexpr float L1_BIG = 0x1p100f;     // scale of the operands of the sign computation
 
 typedef float l1_f32x4 __attribute__((ext_vector_type(4)));
