@@ -159,7 +159,9 @@ int kge_score(const kge_model_t *model, const int32_t *h, const int32_t *r, cons
  * accumulation.  fp32 tables -> every operand value as three bf16 pieces x0 + x1 + x2 (round to nearest at each step:
  * 24 significand bits, the exponent range of fp32, nothing scaled) and the six piece products of total order <= 2 on
  * the bf16 matrix cores with fp32 accumulation (what is dropped is below 2^-26 |a| |b| per product); the pass over the
- * queries with rows of 1,024 bytes uses the fp32 matrix instructions.
+ * queries with rows of 1,024 bytes uses the fp32 matrix instructions, unless the scores are in memory.  Where they are, the
+ * coefficients dL/dS of bf16 tables enter the queries' gradients as two bf16 pieces and the negatives' as one; elsewhere
+ * the queries' are one piece of the weight relative to a reference of its row, times the row's factor in fp32.
  */
 int kge_loss_bwd(const kge_model_t *model, const kge_loss_cfg_t *cfg, const int32_t *h,
                  const int32_t *r, const int32_t *t, int64_t B, const int32_t *neg, int64_t N,
@@ -241,8 +243,8 @@ int kge_sparse_adam_plan_tables(const kge_adam_plan_t *plans, int32_t n_tables, 
 /*
  * kge_loss_bwd_sampled and kge_sparse_adam_plan_tables in one call (Section 4, "Training": one step = sample, gather, score,
  * update).  The sorts of a step's row ids need the ids alone, so the call puts them where they cost least: with the sampled
- * softmax on bilinear bf16 rows of 512 bytes they share the launch that finishes the rows' losses between the two block
- * passes (one launch less per step, and the finish passes under the sorts); in every other configuration they follow the
+ * softmax on bilinear bf16 rows of 512 bytes, in blocks whose scores are not in memory, they share the launch that finishes the
+ * rows' losses between the two block passes (one launch less per step, and the finish passes under the sorts); otherwise they follow the
  * call's other work.  Results - losses, gradients, ids, and every plan in its workspace - equal those of the two calls, bit
  * for bit.  plans[k].idx must be complete when the call starts, or be neg_out, or an array that ends in neg_out (e.g. one
  * buffer [h | t | neg_out]); g_ent_idx and g_rel_idx, which the call writes last, are rejected (KGE_E_INVALID_ARG).

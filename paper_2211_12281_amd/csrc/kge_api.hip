@@ -86,11 +86,12 @@ int validate_model(const kge_model_t *m) {
 
 // Whether both passes of a training call run with the scores in memory (block_small.hip), by the padded size of the block.
 // Measured on both sides of the lines (whole kge_loss_bwd, block kernels / in memory, us):
-//   bf16 rows of 512 bytes (their block kernels are the best there are)  1,024 x 2,048: TransE 72 / 49, ComplEx 55 / 49;
-//     4,096 x 1,024: 76 / 74, 59 / 73;  1,024 x 4,096: 80 / 68, 74 / 64 (a long row of S is cheap, many rows are not);
-//     2,048 x 4,096: 82 / 104, 70 / 99
-//   other rows  RotatE fp32 d 256: 512 x 1,024 102 / 50, 2,048 x 4,096 232 / 174;  ComplEx bf16 d 400: 89 / 41, 168 / 158;
-//     DistMult fp32 d 128: 68 / 39, 114 / 107;  512 x 16,384 (RotatE d 128 / ComplEx d 400): 158 / 164, 199 / 233
+//   bf16 rows of 512 bytes (their block kernels are the best there are)  2,048 x 1,024: TransE 58 / 52, ComplEx softmax 50 / 51;
+//     4,096 x 1,024: 63 / 76, 57 / 73;  1,024 x 4,096: 68 / 70, 73 / 67 (a long row of S is cheap, many rows are not);
+//     2,048 x 4,096: 81 / 107, 68 / 103
+//   other rows  RotatE fp32 d 256: 512 x 1,024 88 / 48, 2,048 x 3,584 268 / 155, 2,048 x 4,096 225 / 171;  ComplEx bf16 d 400: 75 / 43,
+//     201 / 153, 168 / 166;  DistMult fp32 d 128 (its block kernels read planes): 48 / 38, 99 / 94, 85 / 102, 512 x 8,192 74 / 86;
+//     512 x 16,384: RotatE d 128 105 / 158, ComplEx d 400 176 / 237
 // The scores of the largest block that qualifies take less memory than the split partials of the block kernels.
 struct SmallLimits { int64_t always, most; };           // pairs up to which every block is small, above which none is
 SmallLimits small_limits(const Geometry &g) {

@@ -7,9 +7,9 @@
 //   gradients   dq[b, j] = -sum_n w(b, n) sign(q_bj - t_nj),   dt[n, j] = +sum_b w(b, n) sign(q_bj - t_nj)
 // with w(b, n) = dL/dS[b, n] from S and the finished row constants; sign(0) = 0 (sub-gradient at the kink).
 // The queries are read from an unrounded fp32 copy also when the tables are bf16 (a sign flips when rounding moves a
-// difference across zero; the table rows themselves are exact).  All three block kernels stage 64 x 64 fp32 tiles in the LDS (row pitch 68 floats: the 16 lanes that read 16
-// different rows at one column offset hit 16 different 16-byte bank groups) and keep a 4 x 4 register tile per
-// thread; they are bound by the vector pipe in large blocks and by the latency of a chunk (loads, barrier) in small ones, so the loads of
+// difference across zero; the table rows themselves are exact).  The block kernels stage fp32 tiles in the LDS (row pitch 68 floats: the
+// 16 lanes that read 16 different rows at one column offset hit 16 different 16-byte bank groups): the scores 64 x 64 or 32 x 64 with a
+// 4 x 4 or 2 x 4 register tile per thread, the gradients 32 streamed rows x 64 columns against an 8 x 4 register tile; they are bound by the vector pipe in large blocks and by the latency of a chunk (loads, barrier) in small ones, so the loads of
 // the next chunk are issued before the present one is used (gradient passes 44 -> 24 us each at 512 x 1,280 x 384).
 #include "row_ops.hpp"
 
@@ -118,8 +118,8 @@ __device__ __forceinline__ float l1_sigmoid(float y) {
 // out[split][o, j] = -sum_s w(o, s) sign(own_oj - str_sj) over the split's rows of the streamed operand: with
 // own = queries this is dq (s runs over the negatives), with own = negatives it is dt (s runs over the queries;
 // the sign flips twice).  Workgroup = 128 own rows x 64 dimensions; thread = own rows 4 ty + i + 64 i',
-// dimensions 4 tx + c (an 8 x 4 register tile: three 16-byte LDS reads feed 32 sign terms; about 120 registers,
-// four waves per SIMD).  The queries
+// dimensions 4 tx + c (an 8 x 4 register tile: three 16-byte LDS reads feed 32 sign terms; 156 to 162 registers
+// with the next chunk in flight, three waves per SIMD).  The queries
 // are fp32, the negatives of the table type.  Both operands are scaled by 2^100 when they are loaded (exact), so that
 // sign(own - str) = median(-1, (own - str) 2^100, 1) is one subtraction and one median: a non-zero difference of
 // two floats whose magnitudes exceed 2^-76 is at least 2^-100, its scaled value at least 1; a zero difference

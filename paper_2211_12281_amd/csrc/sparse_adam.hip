@@ -213,12 +213,12 @@ __device__ __forceinline__ void adam_apply(uint32_t key, int col, float4 g, int6
 
 // ---------------------------------------------------------------------------------------------
 // Up to SMALL_MAX row ids in ONE launch (the ids of a training step: 2B + N of them).  Only the grouping of equal ids and
-// the position order inside a group matter to the update, so the order is (id & 255, id >> 8, position): workgroup w owns
+// the position order inside a group matter to the update, so the order is (low bits of the id, its other bits, position): workgroup w owns
 // the ids whose low byte is w (low five or six bits, 32 or 64 workgroups, for a table of at most SMALL_FEW or SMALL_MID ids: lists of
 // 64 to 128 ids on average, so that an even spread never reaches the long-list path; with 32 workgroups for 8,192 ids half of the lists
 // did: 17.5 us against 8.0).  Two workgroups share
-// a compute unit (66 KB of LDS, 64 registers), so that the 256 + 32 workgroups of a step's entity and relation table run
-// in one turn (with the LDS of a whole compute unit each, the 32 past the 256th waited for a second turn: 18-20 us
+// a compute unit (66 KB of LDS, 64 registers), so that the workgroups of a step's entity and relation table, 256 and 32
+// or 64, run in one turn (with the LDS of a whole compute unit each, those past the 256th waited for a second turn: 18-20 us
 // instead of 14-18).  It reads ALL ids (a few tens of KB, from L2), counts those of lower workgroups (its place in the
 // output) and collects its own in position order; then it orders its list by the remaining bits, stable: a list
 // of up to 256 entries by counting, for every entry, the entries that come before it (four threads per entry); a longer
@@ -351,7 +351,7 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
     __shared__ uint32_t s_pos[2][SMALL_CAP];
     __shared__ uint32_t s_wave[SMALL_NT / 64];
     // workgroups 0 .. nb0 - 1 take the first table, the next nb1 the second, ...: a table of up to SMALL_FEW ids is cut into
-    // 32 parts (by the low five bits), a longer one into 256
+    // 32 parts (by the low five bits), one of up to SMALL_MID into 64, a longer one into 256
     int first = 0, ti = SMALL_TABLES - 1;
     bool found = false;
 #pragma unroll
