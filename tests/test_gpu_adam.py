@@ -115,22 +115,32 @@ def test_long_runs_of_equal_ids(orc, runs):
     assert norm_err(gm[touched], rm[touched]) <= RTOL_F32 and norm_err(gv[touched], rv[touched]) <= RTOL_F32
 
 
-@pytest.mark.parametrize("n_rows,M", [(3000, 2048), (3000, 2049), (64, 8192), (65, 8192), (40000, 8193), (33, 2048), (256, 32768)])
-@pytest.mark.parametrize("own", [1, 255, 256, 257, 1023])
-def test_lists_at_the_edges_of_the_one_launch_sort(orc, n_rows, M, own):
-    """Tables on both sides of the lines between 32, 64 and 256 workgroups, with one workgroup's list at the lengths where a list is
-    ordered otherwise; the counts of every row against numpy's, through the update with unit gradients."""
+@pytest.mark.parametrize("bits,M", [(5, 2048), (6, 2049), (6, 8192), (8, 8193), (8, 32768)])
+@pytest.mark.parametrize("n_rows", [3000, 1 << 18])
+@pytest.mark.parametrize("own,hot", [(1, 0), (255, 0), (256, 0), (257, 0), (257, 1), (257, 2), (1023, 0), (1023, 766), (1023, 767), (1023, 1023)])
+def test_lists_at_the_edges_of_the_one_launch_sort(orc, bits, M, n_rows, own, hot):
+    """Tables on both sides of the lines between 32, 64 and 256 workgroups (the low bits that select one), with ONE workgroup's list at
+    the lengths where a list is ordered otherwise (256 entries), and long lists whose most frequent id leaves 256 others, one more, all or
+    none; with more bits of the id left to order by, and a gradient of its own for every position, so that a position that goes with
+    another id shows."""
     import paper_2211_12281_amd as kge
-    g = np.random.default_rng(M + own)
+    g = np.random.default_rng(1000 * bits + own + hot)
+    part = 1 << bits
     idx = g.integers(0, n_rows, M).astype(np.int32)
-    idx = np.where(idx % 32 == 0, idx + 1 if n_rows % 32 != 1 else (idx + 1) % n_rows, idx).clip(0, n_rows - 1).astype(np.int32)
-    at = g.choice(M, own, replace=False)
-    idx[at] = 32 * g.integers(0, (n_rows + 31) // 32, own).clip(0, (n_rows - 1) // 32)      # ids with five zero low bits
-    theta = np.zeros((n_rows, 4), F)
-    dth, dm, dv = [torch.from_numpy(theta.copy()).cuda() for _ in range(3)]
-    kge.sparse_adam(dth, None, dm, dv, torch.from_numpy(idx).cuda(), torch.ones(M, 4).cuda(), 1e-3, step=1)
-    want = np.bincount(idx, minlength=n_rows).astype(F) * F(1 - F(0.9))                     # m = (1 - beta1) sum of the gradients
-    assert norm_err(dm.cpu().numpy(), np.repeat(want[:, None], 4, 1)) <= RTOL_F32
+    idx[idx % part == 5] -= 1                              # nobody else in the list of the ids that end in 5
+    members = 5 + part * g.integers(1, n_rows // part, own)
+    members[g.permutation(own)[:hot]] = 5 + part * (n_rows // part // 2)
+    idx[g.choice(M, own, replace=False)] = members
+    assert np.count_nonzero(idx % part == 5) == own and n_rows > part
+    theta, m, v = _state(n_rows, 8, 3, True)
+    grads = (g.normal(size=(M, 8)) * 1e-2).astype(F)
+    dth, dm, dv = [torch.from_numpy(a.copy()).cuda() for a in (theta, m, v)]
+    kge.sparse_adam(dth, None, dm, dv, torch.from_numpy(idx).cuda(), torch.from_numpy(grads).cuda(), 1e-3, step=2)
+    rth, rm, rv, touched = orc.sparse_adam(theta, m, v, idx, grads, float(F(1e-3)), float(F(0.9)), float(F(0.999)), float(F(1e-8)), 2)
+    gth, gm, gv = dth.cpu().numpy(), dm.cpu().numpy(), dv.cpu().numpy()
+    assert np.array_equal(gth[~touched], theta[~touched])
+    assert update_err_ok(gth[touched], theta[touched], rth[touched])
+    assert norm_err(gm[touched], rm[touched]) <= RTOL_F32 and norm_err(gv[touched], rv[touched]) <= RTOL_F32
 
 
 @pytest.mark.parametrize("n_rows,runs", [(200, [(17, 6000), (5, 3000), (199, 3100)]), (32, [(31, 4000), (3, 9)]), (11, [(4, 9000), (0, 4)]),

@@ -27,10 +27,13 @@ def _model(kge, scorer, T, bf16):
 
 
 @pytest.mark.parametrize("fused", [False, True])     # the negatives from a call of their own / drawn inside kge_loss_bwd_sampled
-@pytest.mark.parametrize("scorer,d,bf16,loss", [("complex", 256, True, "sampled_softmax"), ("distmult", 64, False, "logsigmoid")])
-def test_replays_of_a_captured_step_match_the_step_run_call_by_call(scorer, d, bf16, loss, fused):
+@pytest.mark.parametrize("scorer,d,bf16,loss,B,N", [
+    ("complex", 256, True, "sampled_softmax", 512, 1024), ("distmult", 64, False, "logsigmoid", 512, 1024),   # small blocks: scores in memory
+    ("complex", 256, True, "sampled_softmax", 1024, 4400),   # the forward pass keeps its weights
+    ("distmult", 64, False, "logsigmoid", 2304, 3328)])      # planes
+def test_replays_of_a_captured_step_match_the_step_run_call_by_call(scorer, d, bf16, loss, B, N, fused):
     import paper_2211_12281_amd as kge
-    n_ent, n_rel, B, N, steps = 6000, 12, 512, 1024, 4
+    n_ent, n_rel, steps = 6000, 12, 4
     G = make_case(scorer, n_ent, n_rel, d, B, N, bf16, amp=0.3)
     h, r, t = (torch.from_numpy(G[k]).cuda() for k in ("h", "r", "t"))
     kw = dict(n_ent_for_c=n_ent) if loss == "sampled_softmax" else dict(gamma=6.0, adv_temp=1.0)

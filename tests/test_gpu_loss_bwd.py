@@ -61,12 +61,17 @@ def test_other_row_sizes(orc, scorer, dim, bf16):
     _compare(orc, scorer, "logsigmoid", G, bf16, 3000)
 
 
-@pytest.mark.parametrize("scorer,B,N", [("complex", 700, 3000), ("distmult", 2304, 4100), ("complex", 130, 70)])
+STORED_CASES = [("complex", 700, 3000), ("distmult", 2304, 4100), ("complex", 130, 70)]
+
+
+@pytest.mark.parametrize("scorer,B,N", STORED_CASES)
 def test_stored_weights_of_the_forward_pass_serve_the_pass_over_the_negatives(orc, scorer, B, N):
     """Sampled softmax, bilinear scorers, bf16 rows of 512 bytes: the forward kernel keeps its weights and the pass over the
     negatives contracts them with the scaled queries.  Several own tiles, forward splits and ragged tails of both passes,
     against the oracle; and against the kernel that recomputes the scores (the forward pass may be split differently there,
-    which moves its reference exponents and with them the bf16 rounding of the weights)."""
+    which moves its reference exponents and with them the bf16 rounding of the weights).  (Of these sizes the second alone keeps its weights
+    in the library's own dispatch, the others are small blocks with the scores in memory: test_gpu_small_block.py runs all three with the
+    block kernels as well.)"""
     import paper_2211_12281_amd as kge
     G = make_case(scorer, 9000, 9, 256, B, N, True, amp=0.3, zipf=True)
     _compare(orc, scorer, "sampled_softmax", G, True, 9000)
@@ -125,11 +130,14 @@ def test_repeated_calls_are_bitwise_identical(orc):
         assert bool((a[k] == b[k]).all()), k
 
 
-@pytest.mark.parametrize("scorer,loss", [("distmult", "sampled_softmax"), ("complex", "logsigmoid"),
-                                         ("transe", "logsigmoid")])
+WIDE_CASES = [("distmult", "sampled_softmax"), ("complex", "logsigmoid"), ("transe", "logsigmoid")]
+
+
+@pytest.mark.parametrize("scorer,loss", WIDE_CASES)
 def test_wide_score_range_raises_the_reference_repeatedly(orc, scorer, loss):
     """Scores spread over tens of nats and negatives ordered by ascending score of the first query:
-    the running reference exponent of the softmax weights is raised many times along the stream."""
+    the running reference exponent of the softmax weights is raised many times along the stream (in the block kernels:
+    test_gpu_small_block.py runs this with them; here a small block takes its maximum from the scores in memory)."""
     amp = 1.2 if scorer != "transe" else 2.5
     G = make_case(scorer, 3000, 7, 64, 130, 700, False, amp=amp)
     s0 = orc.score_batch(scorer, G["ent"], G["rel"], G["relw"], G["h"][:1], G["r"][:1], G["t"][:1], G["neg"])[1][0]
@@ -162,10 +170,13 @@ def test_l3_regulariser_edge_shapes(orc):
                  loss_scale=0.5)
 
 
-@pytest.mark.parametrize("scorer,loss", [("distmult", "sampled_softmax"), ("transe", "logsigmoid"), ("complex", "sampled_softmax")])
+WIDE_BF16_CASES = [("distmult", "sampled_softmax"), ("transe", "logsigmoid"), ("complex", "sampled_softmax")]
+
+
+@pytest.mark.parametrize("scorer,loss", WIDE_BF16_CASES)
 def test_wide_score_range_bf16_tables(orc, scorer, loss):
-    """The same stress of the running reference exponent on bf16 tables, whose row-owner pass hands the coefficients
-    and the rescaling factors from one wave to its partner."""
+    """The same stress of the running reference exponent on bf16 tables, whose row-owner pass (test_gpu_small_block.py runs
+    this with it) hands the coefficients and the rescaling factors from one wave to its partner."""
     amp = 1.2 if scorer != "transe" else 2.5
     G = make_case(scorer, 3000, 7, 64, 130, 700, True, amp=amp)
     s0 = orc.score_batch(scorer, G["ent"], G["rel"], G["relw"], G["h"][:1], G["r"][:1], G["t"][:1], G["neg"])[1][0]
@@ -226,14 +237,21 @@ def test_scores_that_outgrow_the_first_tile(orc, scorer):
 
 
 
-@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", [
-    ("complex", 256, True, "sampled_softmax", 300, 701),     # hot path: the gather of the negatives draws the ids
-    ("transe", 256, True, "logsigmoid", 130, 260),           # two-role kernels, same gather
-    ("distmult", 64, False, "sampled_softmax", 200, 333),    # fp32 tables: the draw is a launch of its own inside the call
-    ("transh", 128, False, "logsigmoid", 64, 97),
+# (small blocks take the gather that draws the ids whatever their kernels; test_gpu_small_block.py runs all of these with the block kernels)
+DRAWN_CASES = [
+    ("complex", 256, True, "sampled_softmax", 300, 701),     # block kernels: hot path, the gather of the negatives draws the ids
+    ("transe", 256, True, "logsigmoid", 130, 260),           # ... two-role kernels, same gather
+    ("distmult", 64, False, "sampled_softmax", 200, 333),    # ... planes, same gather
+    ("transh", 128, False, "logsigmoid", 64, 97),            # planes on either route
+    ("transh", 256, True, "logsigmoid", 130, 260),           # bf16 TransH: the draw is a launch of its own, then the transposing gather
+    ("complex", 400, True, "sampled_softmax", 70, 300),      # ... and so with the block kernels on rows of over 512 bytes
+    ("rotate", 256, False, "logsigmoid", 70, 300),
     ("transe", 256, True, "logsigmoid", 0, 50),              # no queries: zero rows and the ids
     ("complex", 256, True, "sampled_softmax", 40, 0),        # no negatives: nothing is drawn
-])
+]
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", DRAWN_CASES)
 def test_negatives_drawn_inside_the_call_equal_the_two_calls(scorer, dim, bf16, loss, B, N):
     """kge_loss_bwd_sampled: the ids of kge_sample_negatives bit for bit, and every output of kge_loss_bwd on them
     bit for bit (same kernels on the same ids); a sub-range of the entities, and the step read from a device counter."""
@@ -271,15 +289,20 @@ def test_negatives_drawn_inside_the_call_argument_checks():
             kge.loss_bwd(model, "sampled_softmax", h, r, t, neg, draw=draw, n_ent_for_c=500)
 
 
-@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", [
-    ("complex", 256, True, "sampled_softmax", 700, 3000),    # the sorts share the launch of the rows' finish
-    ("distmult", 256, True, "sampled_softmax", 4096, 16384), # the same at the size of a full step (288 + 256 workgroups)
+# (all but the second are small blocks in the library's own dispatch, where the sorts follow the call's work; test_gpu_small_block.py runs
+# them with the block kernels)
+PLANNED_CASES = [
+    ("complex", 256, True, "sampled_softmax", 700, 3000),    # block kernels: the sorts share the launch of the rows' finish
+    ("distmult", 256, True, "sampled_softmax", 4096, 16384), # the same at the size of a full step (256 + 64 workgroups of sorts, 4,096 rows)
     ("distmult", 256, True, "logsigmoid", 300, 900),         # every other configuration: the sorts follow the call's work
     ("complex", 64, False, "sampled_softmax", 200, 333),
     ("transh", 128, False, "logsigmoid", 64, 97),
     ("complex", 256, True, "sampled_softmax", 40, 0),        # no negatives
     ("distmult", 256, True, "sampled_softmax", 0, 50),       # no queries: the relations' plan is empty
-])
+]
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", PLANNED_CASES)
 def test_planned_call_equals_the_sampled_call_followed_by_the_plans(scorer, dim, bf16, loss, B, N):
     """kge_loss_bwd_sampled_planned against kge_loss_bwd_sampled + kge_sparse_adam_plan_tables: every output bit for bit,
     and the plans through the updates that read them (entity rows by [h | t | drawn negatives], relation rows by r)."""

@@ -23,14 +23,21 @@ def test_small_blocks_match_oracle(orc, scorer, dim, bf16, B, N, loss):
     base._compare(orc, scorer, loss, G, bf16, 3000, kw=dict(kw, reg_l3=1e-3 if B % 2 else 0.0))
 
 
-@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", [
-    ("transe", 256, True, "logsigmoid", 1024, 2048), ("transe", 256, True, "logsigmoid", 1024, 2049),
-    ("complex", 256, True, "sampled_softmax", 900, 4600), ("rotate", 128, False, "logsigmoid", 2600, 2700),
-    ("complex", 400, True, "sampled_softmax", 300, 12000)])
+# the largest padded blocks on the small side of every line of the rule (limits of 2, 4 and 7 million pairs by row width and shape)
+LARGEST_SMALL = [
+    ("transe", 256, True, "logsigmoid", 1024, 4096), ("complex", 256, True, "sampled_softmax", 900, 4000),     # many negatives: 4M pairs
+    ("transe", 240, True, "sampled_softmax", 2040, 1020), ("distmult", 256, True, "logsigmoid", 1500, 1200),   # otherwise 2M
+    ("rotate", 256, False, "logsigmoid", 2560, 2816), ("distmult", 128, False, "sampled_softmax", 3000, 2300), # other rows: 7M
+    ("complex", 400, True, "sampled_softmax", 700, 9000), ("transe", 512, True, "logsigmoid", 1400, 4600),
+    ("complex", 400, True, "logsigmoid", 256, 12000), ("transe", 64, False, "logsigmoid", 200, 16000)]         # very many negatives: 4M
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", LARGEST_SMALL)
 def test_both_sides_of_the_rule_agree(scorer, dim, bf16, loss, B, N):
-    """Blocks at the line between the two routes, each route against the other (block_passes takes the block kernels for all)."""
+    """Each route against the other (block_passes takes the block kernels for all); that the two are different kernels shows in the bits."""
+    import torch
     import paper_2211_12281_amd as kge
-    G = make_case(scorer, 9000, 9, dim, B, N, bf16, amp=0.3 if scorer == "complex" else 0.1, zipf=True)
+    G = make_case(scorer, 9000, 9, dim, B, N, bf16, amp=0.3 if scorer in ("distmult", "complex") else 0.1, zipf=True)
     model = gpu_model(scorer, G, bf16)
     args = (dev_idx(G["h"]), dev_idx(G["r"]), dev_idx(G["t"]), dev_idx(G["neg"]))
     kw = dict(n_ent_for_c=9000) if loss == "sampled_softmax" else dict(gamma=2.0, adv_temp=0.8)
@@ -40,11 +47,20 @@ def test_both_sides_of_the_rule_agree(scorer, dim, bf16, loss, B, N):
         want = kge.loss_bwd(model, loss, *args, **kw)
     finally:
         kge.debug_select("block_passes", False)
+    assert not torch.equal(got["g_ent"][2 * B:], want["g_ent"][2 * B:]) and not torch.equal(got["g_ent"][:B], want["g_ent"][:B])
     tol = RTOL_BF16 if bf16 else RTOL_F32
     assert abs(got["loss"].item() - want["loss"].item()) <= 1e-4 * abs(want["loss"].item())
     for sl in (slice(0, B), slice(B, 2 * B), slice(2 * B, 2 * B + N)):
         assert norm_err(got["g_ent"][sl].cpu().numpy(), want["g_ent"][sl].cpu().numpy()) <= tol
     assert norm_err(got["g_rel"].cpu().numpy(), want["g_rel"].cpu().numpy()) <= tol
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", [("complex", 256, True, "sampled_softmax", 900, 4600), ("rotate", 128, False, "logsigmoid", 2600, 2700),
+                                                      ("complex", 400, True, "sampled_softmax", 300, 12000)])
+def test_blocks_over_the_line_match_oracle(orc, scorer, dim, bf16, loss, B, N):
+    """The smallest blocks that the library's own dispatch gives to the block kernels."""
+    G = make_case(scorer, 9000, 9, dim, B, N, bf16, amp=0.3 if scorer == "complex" else 0.1, zipf=True)
+    base._compare(orc, scorer, loss, G, bf16, 9000, kw=dict(n_ent_for_c=9000) if loss == "sampled_softmax" else dict(gamma=2.0, adv_temp=0.8))
 
 
 @pytest.mark.parametrize("scorer,dim,B,N,amp", [("distmult", 256, 300, 900, 0.5), ("distmult", 400, 130, 2500, 0.9), ("transe", 256, 200, 1024, 0.1)])
@@ -78,8 +94,10 @@ def test_query_gradients_hold_more_than_one_bf16_of_a_coefficient(orc, scorer, d
 def block_passes():
     import paper_2211_12281_amd as kge
     kge.debug_select("block_passes", True)
-    yield
-    kge.debug_select("block_passes", False)
+    try:
+        yield
+    finally:
+        kge.debug_select("block_passes", False)
 
 
 @pytest.mark.parametrize("scorer", base.SCORERS)
@@ -95,16 +113,44 @@ def test_block_kernels_other_row_sizes(orc, block_passes, scorer, dim, bf16):
     base.test_other_row_sizes(orc, scorer, dim, bf16)
 
 
+@pytest.mark.parametrize("scorer", base.SCORERS)
+@pytest.mark.parametrize("bf16", [False, True])
+def test_block_kernels_regulariser(orc, block_passes, scorer, bf16):
+    base.test_l3_regulariser_matches_oracle(orc, scorer, bf16)
+
+
 @pytest.mark.parametrize("scorer", ["transe", "complex"])
 def test_block_kernels_edge_shapes(orc, block_passes, scorer):
     base.test_edge_shapes(orc, scorer)
 
 
-@pytest.mark.parametrize("scorer", ["distmult", "complex"])
-def test_block_kernels_scores_that_outgrow_the_first_tile(orc, block_passes, scorer):
-    for name in dir(base):
-        if "outgrow" in name and name.startswith("test_"):
-            getattr(base, name)(orc, scorer)
+@pytest.mark.parametrize("scorer,loss", base.WIDE_CASES)
+def test_block_kernels_wide_score_range(orc, block_passes, scorer, loss):
+    base.test_wide_score_range_raises_the_reference_repeatedly(orc, scorer, loss)
+
+
+@pytest.mark.parametrize("scorer,loss", base.WIDE_BF16_CASES)
+def test_block_kernels_wide_score_range_bf16(orc, block_passes, scorer, loss):
+    base.test_wide_score_range_bf16_tables(orc, scorer, loss)
+
+
+def test_block_kernels_repeated_calls(orc, block_passes):
+    base.test_repeated_calls_are_bitwise_identical(orc)
+
+
+@pytest.mark.parametrize("scorer,B,N", base.STORED_CASES)
+def test_block_kernels_stored_weights(orc, block_passes, scorer, B, N):
+    base.test_stored_weights_of_the_forward_pass_serve_the_pass_over_the_negatives(orc, scorer, B, N)
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", base.DRAWN_CASES)
+def test_block_kernels_drawn_negatives(block_passes, scorer, dim, bf16, loss, B, N):
+    base.test_negatives_drawn_inside_the_call_equal_the_two_calls(scorer, dim, bf16, loss, B, N)
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,loss,B,N", base.PLANNED_CASES)
+def test_block_kernels_planned_call(block_passes, scorer, dim, bf16, loss, B, N):
+    base.test_planned_call_equals_the_sampled_call_followed_by_the_plans(scorer, dim, bf16, loss, B, N)
 
 
 @pytest.mark.parametrize("scorer,dim,B,N", [("transh", 128, 129, 257), ("transh", 8, 31, 33), ("transe", 40, 1, 4000), ("rotate", 128, 300, 1),
