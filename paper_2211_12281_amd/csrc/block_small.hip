@@ -272,7 +272,7 @@ struct SmallRowsArgs {
     float *lossb, *gpos; uint32_t *C; int bf16, dist; float4 *sumq; int q_splits;
 };
 __global__ __launch_bounds__(256) void small_rows_kernel(const SmallRowsArgs a) {
-    __shared__ float red[4][4], Kb;
+    __shared__ float red[4][4], fb;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N, loss = a.loss;
     const int npad = (N + 31) / 32 * 32;
     auto put = [&](int n, float c) -> float {                   // returns what the contraction over the negatives sees of it
@@ -299,17 +299,23 @@ __global__ __launch_bounds__(256) void small_rows_kernel(const SmallRowsArgs a) 
     const float fp = a.pos[b];
     float m = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < R; ++j) m = fmaxf(m, tid + 256 * j < N ? v[j] * xscale : -INFINITY);
-    for (int n = tid + 256 * R; n < N; n += 256) m = fmaxf(m, row[n] * xscale);
+    for (int j = 0; j < R; ++j) m = fmaxf(m, v[j]);
+    for (int n = tid + 256 * R; n < N; n += 256) m = fmaxf(m, row[n]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     if (lane == 0) red[0][wave] = m;
     __syncthreads();
-    m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+    const float s_max = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+    m = s_max > -INFINITY ? s_max * xscale : -INFINITY;
     const float m_neg = m > -INFINITY ? -m : 0.f;               // (a row of nothing but -inf: every weight 0)
+    // m is rounded, s xscale below is not: the largest score's own weight would be off by more than a factor of two beyond 2^24, and
+    // nothing or infinite beyond 2^31; there its remainder is taken from every exponent (not without C: who makes the coefficients
+    // elsewhere, from K, has the same rounding in K)
+    const float rest = fmaf(s_max, xscale, m_neg), rem = a.C && fabsf(rest) > 1.f && fabsf(rest) < INFINITY ? rest : 0.f;
+    auto weight = [&](float s) { return kge_exp2(fmaf(s, xscale, m_neg) - rem); };       // relative to the largest: at most about 1
     float l = 0.f, ac = 0.f;
     auto add = [&](float s) {
-        const float e = kge_exp2(fmaf(s, xscale, m_neg));
+        const float e = weight(s);
         l += e;
         if (loss == KGE_LOGSIGMOID) {
             const float y = a.gamma + s, t = kge_exp2(-fabsf(y) * KGE_LOG2E);
@@ -328,14 +334,14 @@ __global__ __launch_bounds__(256) void small_rows_kernel(const SmallRowsArgs a) 
         ac = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
         const KgeRowFinish o = kge_rowfinish_merged(m, l, ac, N, loss, a.gamma, a.c_corr, a.scale, fp);
         a.lossb[b] = o.L; a.gpos[b] = o.gp; a.rowinfo[b].K = o.K;
-        Kb = o.K;
+        fb = l > 0.f ? a.scale * o.share / l : 0.f;
     }
     if (!a.C) return;
     __syncthreads();
-    const float K = Kb;
+    const float f = fb;                                         // dL / d(score) of a weight of 1 (log-sigmoid: times sigma(gamma + s))
     float csum = 0.f;
     auto coef = [&](int n, float s) {
-        float w = kge_exp2(fmaf(s, xscale, K));
+        float w = weight(s) * f;
         if (loss == KGE_LOGSIGMOID) {
             const float y = a.gamma + s;
             const float t = kge_exp2(-fabsf(y) * KGE_LOG2E), rcp = __builtin_amdgcn_rcpf(1.f + t);

@@ -9,23 +9,25 @@
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ float kge_softplus_f(float y) { return fmaxf(y, 0.f) + log1pf(expf(-fabsf(y))); }
 
-struct KgeRowFinish { float L, gp, K; };
+struct KgeRowFinish { float L, gp, K, share; };     // share: of the partition sum that the negatives hold (log-sigmoid: 1, no negatives: 0)
 // from the statistics of the whole row: m the maximum of x log2(e) (x = a s or s), l the sum of exp(x - max), ac the sum of
 // exp(x - max) softplus(gamma + s)
 __device__ __forceinline__ KgeRowFinish kge_rowfinish_merged(float m, float l, float ac, int N, int loss, float gamma, float c_corr,
                                                              float scale, float fp) {
     const float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
     KgeRowFinish o;
+    o.share = 0.f;
     if (loss == KGE_LOGSIGMOID) {
         o.L = kge_softplus_f(-(gamma + fp));
         const float e = expf(-fabsf(gamma + fp));           // sigma(-(gamma+fp)), stable
         o.gp = -((gamma + fp) >= 0.f ? e / (1.f + e) : 1.f / (1.f + e)) * scale;
-        if (N > 0 && l > 0.f) { o.L += ac / l; o.K = -m - log2f(l) + log2f(scale); } else o.K = -INFINITY;
+        if (N > 0 && l > 0.f) { o.L += ac / l; o.K = -m - log2f(l) + log2f(scale); o.share = 1.f; } else o.K = -INFINITY;
     } else {
         if (N > 0 && l > 0.f) {
             const float A = c_corr + logf(l) + m * LN2;     // log of the negatives' share of the partition sum
             const float M = fmaxf(A, fp);
-            const float lse = M + logf(expf(A - M) + expf(fp - M));
+            const float ea = expf(A - M), ep = expf(fp - M), lse = M + logf(ea + ep);
+            o.share = ea / (ea + ep);
             o.L = lse - fp;
             o.gp = (expf(fp - lse) - 1.f) * scale;
             o.K = (c_corr - lse + logf(scale)) * LOG2E;

@@ -90,6 +90,22 @@ def test_query_gradients_hold_more_than_one_bf16_of_a_coefficient(orc, scorer, d
     assert excess.max() <= 0, float(excess.max() / np.abs(want).max())
 
 
+@pytest.mark.parametrize("scorer,dim,bf16", [("distmult", 64, False), ("complex", 256, True), ("distmult", 256, False), ("transe", 96, False)])
+@pytest.mark.parametrize("loss", ["logsigmoid", "sampled_softmax"])
+def test_scores_too_large_for_an_exact_exponent(orc, scorer, dim, bf16, loss):
+    """Scores of 1e10 to 1e15, where one rounding of the row's maximum is worth hundreds of units of the exponent: losses and gradients
+    stay finite, and the loss is the oracle's."""
+    import torch
+    import paper_2211_12281_amd as kge
+    G = make_case(scorer, 500, 5, dim, 70, 130, bf16, amp=0.5)
+    G["ent"] *= np.float32(2.0 ** (40 if scorer == "transe" else 22))
+    kw = dict(n_ent_for_c=500) if loss == "sampled_softmax" else dict(gamma=1.0, adv_temp=1.0)
+    out = kge.loss_bwd(gpu_model(scorer, G, bf16), loss, *(dev_idx(G[k]) for k in ("h", "r", "t", "neg")), **kw)
+    ref = orc.loss_bwd(scorer, loss, G["ent"], G["rel"], None, G["h"], G["r"], G["t"], G["neg"], **kw)
+    assert all(bool(torch.isfinite(v).all()) for v in out.values() if v is not None and v.is_floating_point())
+    assert abs(out["loss"].item() - ref["loss"]) <= (RTOL_BF16 if bf16 else RTOL_F32) * abs(ref["loss"])
+
+
 @pytest.fixture
 def block_passes():
     import paper_2211_12281_amd as kge
