@@ -937,7 +937,7 @@ int kge_run_chain_tfinish(const KgeModelDev &m, const int32_t *h, const int32_t 
         return kge_launch_status();
     }
     // Kernels for the columns that a row has: with arrays for 512 columns the TransH rule took 171 registers, two waves per SIMD, and with
-    // it the gradient rows of the negatives in the same launch (same box, arrays for 512 columns / these: TransH fp32 1,024 x 1,024 x 128, whole
+    // it the gradient rows of the negatives in the same launch (arrays for 512 columns / these: TransH fp32 1,024 x 1,024 x 128, whole
     // call 80 / 64 us; 8,192 x 4,096 step 470 / 453; RotatE fp32 4,096 x 4,096 x 256 382 / 368).
 #define KGE_CT_LAUNCH(BF, SC, W4, NJ) hipLaunchKernelGGL((kge_chain_tfinish_kernel<BF, SC, false, W4, NJ>), dim3(1 + cb + tb), dim3(256), 0, st, cb, a, f, lossb, scale, loss_out)
 #define KGE_CT_NJ(BF, SC, W4) do { if (m.dim <= 128) KGE_CT_LAUNCH(BF, SC, W4, 2); else if (m.dim <= 256) KGE_CT_LAUNCH(BF, SC, W4, 4); else KGE_CT_LAUNCH(BF, SC, W4, KGE_MAXJ); } while (0)
