@@ -17,7 +17,8 @@
 // Arithmetic: bf16 operands with fp32 accumulation, or three bf16 pieces per fp32 value.  On bf16 tables the coefficients are
 // finished when they are made, where the block kernels round the weight relative to a row reference (the dominating pairs are 1 and
 // round to themselves) and apply the normaliser in fp32; so dQ takes every coefficient as TWO bf16 pieces, 17 significand bits, and its
-// error stays below theirs.  dT takes the first piece alone, as their pass over the negatives does.
+// error stays below theirs.  dT takes the first piece alone, as their pass over the negatives does; the sum of a negative's
+// coefficients (distance scorers) both, so that the rounding stays on the queries (rounded sums: dT's error 6-22 % larger).
 #include "block_kernel.hpp"
 #include "prep_kernels.h"
 #include "row_finish.hpp"
@@ -173,7 +174,8 @@ __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile
         } else fc.v = kge_split3(make_uint4(r.c[0], r.c[1], r.c[2], r.c[3]), make_uint4(r.c[4], r.c[5], r.c[6], r.c[7]));
         if constexpr (!OWN_Q && KIND == KGE_KIND_DIST) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) csum += __uint_as_float(BF16 ? r.c[j] << 16 : r.c[j]);
+            for (int j = 0; j < 8; ++j)                         // (both pieces: dT = sum c q - (sum c) t, and t is not part of the rounding)
+                csum += BF16 ? __uint_as_float(r.c[j] << 16) + __uint_as_float(r.c[j] & 0xffff0000u) : __uint_as_float(r.c[j]);
         }
 #pragma unroll
         for (int h = 0; h < NB; ++h) {

@@ -67,7 +67,7 @@ def test_blocks_over_the_line_match_oracle(orc, scorer, dim, bf16, loss, B, N):
 def test_query_gradients_hold_more_than_one_bf16_of_a_coefficient(orc, scorer, dim, B, N, amp):
     """bf16 tables, with relations that leave the heads as they are (no rounding of the query): the heads' gradient rows are then
     sum_n c_n t_n (distances: c_n / distance (t_n - q)) with exact operands, and c_n in two bf16 pieces is within 2^-17 of itself -
-    peaked scores, whose dominating coefficient one bf16 would move by up to 2^-9."""
+    peaked scores, whose dominating coefficient one bf16 would move by up to 2^-8."""
     import paper_2211_12281_amd as kge
     G = make_case(scorer, 3000, 5, dim, B, N, True, amp=amp)
     G["rel"][:] = 1.0 if scorer == "distmult" else 0.0
@@ -88,6 +88,38 @@ def test_query_gradients_hold_more_than_one_bf16_of_a_coefficient(orc, scorer, d
     want = ref["g_ent"][:B]
     excess = np.abs(out["g_ent"][:B].cpu().numpy().astype(np.float64) - want) - (2.0 ** -17 * terms + RTOL_F32 * np.abs(want).max())
     assert excess.max() <= 0, float(excess.max() / np.abs(want).max())
+
+
+@pytest.mark.parametrize("dim,B,N", [(256, 5, 300), (400, 3, 1100)])
+@pytest.mark.parametrize("loss", ["logsigmoid", "sampled_softmax"])
+def test_negative_gradients_of_distances_take_unrounded_sums(orc, dim, B, N, loss):
+    """bf16 TransE, negatives far larger than the queries: a negative's gradient sum_b c_b q_b - (sum_b c_b) t has the rounding of its
+    coefficients (one bf16, eight significand bits: up to 2^-8) on the queries alone; rounded coefficients in the sum would put it on
+    the larger t."""
+    import paper_2211_12281_amd as kge
+    G = make_case("transe", 3000, 5, dim, B, N, True, amp=1.0)
+    heads = np.unique(np.concatenate([G["h"], G["t"]]))
+    G["ent"][heads] *= np.float32(2.0 ** -6)
+    G["neg"] = np.where(np.isin(G["neg"], heads), (heads.max() + 1) % 3000, G["neg"]).astype(np.int32)
+    G["neg"] = G["neg"][~np.isin(G["neg"], heads)]
+    G["rel"][:] = 0.0
+    kw = dict(n_ent_for_c=3000) if loss == "sampled_softmax" else dict(gamma=12.0, adv_temp=0.3)
+    out = kge.loss_bwd(gpu_model("transe", G, True), loss, *(dev_idx(G[k]) for k in ("h", "r", "t", "neg")), loss_scale=1.0, **kw)
+    ref = orc.loss_bwd("transe", loss, G["ent"], G["rel"], None, G["h"], G["r"], G["t"], G["neg"], loss_scale=1.0, **kw)
+    pos, S = orc.score_batch("transe", G["ent"], G["rel"], None, G["h"], G["r"], G["t"], G["neg"])
+    if loss == "sampled_softmax":
+        z = np.concatenate([pos[:, None], S + np.log(2999 / len(G["neg"]))], axis=1)
+        z = np.exp(z - z.max(axis=1, keepdims=True))
+        c = z[:, 1:] / z.sum(axis=1, keepdims=True)
+    else:
+        w = np.exp(0.3 * (S - S.max(axis=1, keepdims=True)))
+        c = w / w.sum(axis=1, keepdims=True) / (1.0 + np.exp(-(12.0 + S)))
+    c = c / -S
+    q, T = np.abs(G["ent"][G["h"]].astype(np.float64)), np.abs(G["ent"][G["neg"]].astype(np.float64))
+    want = ref["g_ent"][2 * B:]
+    bound = 2.0 ** -8 * (c.T @ q) + (2.0 ** -17 * c.sum(axis=0)[:, None]) * T + RTOL_F32 * np.abs(want)
+    excess = np.abs(out["g_ent"][2 * B:].cpu().numpy().astype(np.float64) - want) / bound
+    assert excess.max() <= 1.0, float(excess.max())
 
 
 @pytest.mark.parametrize("scorer,dim,bf16", [("distmult", 64, False), ("complex", 256, True), ("distmult", 256, False), ("transe", 96, False)])
