@@ -76,3 +76,47 @@ def test_table_and_selection_edges(orc, M, K, K_out, pool, p):
         lists[M - 1, 2, 5:] = lists[M - 1, 2, 4]
         lists[M - 1, 0, 7:60:3] = -1
     _check(orc, lists, p, K_out)
+
+
+def _agreeing(g, M, Q, K, spread):
+    """Lists of models that rank one pool alike up to noise, as trained models do."""
+    out = np.empty((M, Q, K), dtype=np.int32)
+    for q in range(Q):
+        ids = g.choice(5_000_000, size=4 * K, replace=False)
+        base = -np.log(np.arange(1, 4 * K + 1))
+        for m in range(M):
+            out[m, q] = ids[np.argsort(-(base + spread * g.standard_normal(4 * K)))[:K]]
+    return out
+
+
+@pytest.mark.parametrize("M,K,K_out,spread,p,Q", [
+    (16, 100, 10, 0.7, -1.0, 1281),      # one wave per query from 1,281 queries on; every query is proved
+    (16, 100, 10, 0.7, 1.0, 1281),
+    (16, 100, 10, 30.0, 1.0, 1281),      # lists that share little: the bound holds for none, all queries go to the other kernel
+    (16, 100, 10, 3.0, -0.5, 1283),      # ... for some
+    (64, 100, 20, 3.0, -1.0, 257),       # more than the small table's 128 entities in the first ranks: the walk ends early
+    (5, 100, 26, 0.7, 0.3, 2049),        # the middle table, a model count that fills no word of ranks
+    (128, 64, 36, 0.7, -1.0, 258),       # the most models
+    (9, 100, 80, 0.7, -1.0, 1793),       # the widest table
+    (63, 128, 200, 0.7, -1.0, 257),      # the longest whole lists of the widest table, two waves per workgroup and one
+    (64, 128, 200, 0.7, 1.0, 257),
+    (20, 129, 200, 0.7, 1.0, 769),       # the first without a table
+    (2, 255, 200, 0.7, 1.0, 2049),       # the longest list whose ranks fit a byte: two models of it fit the widest table
+    (1, 256, 200, 0.7, 1.0, 2049),
+    (12, 10, 100, 0.7, -1.0, 13),        # short lists taken whole; fewer entities than winners
+    (4, 64, 50, 30.0, 1.0, 13),          # 256 entries: every entity fits, nothing to prove
+    (43, 3, 40, 0.7, -64.0, 13),         # sums that a float can't tell apart
+    (1, 200, 10, 0.7, 16.0, 2050)])
+def test_wave_kernel_and_the_queries_it_leaves(orc, M, K, K_out, spread, p, Q):
+    g = np.random.default_rng(M * 1000 + K + K_out)
+    lists = _agreeing(g, M, 13, K, spread)
+    if K >= 64:                                                        # repeats: neighbours, in one piece of 64 entries, far apart; short lists
+        lists[0, 0, 1] = lists[0, 0, 0]
+        lists[M - 1, 1, 5:30] = lists[M - 1, 1, 4]
+        lists[M // 2, 2, K - 1] = lists[M // 2, 2, 0]
+        lists[0, 3, 2:] = -1
+        lists[:, 4, 3:] = -7
+        lists[:, 5] = lists[0, 5]
+        lists[:, 6, 20:40] = lists[:, 6, :20]
+    lists[:, 7] = -1
+    _check(orc, np.ascontiguousarray(lists[:, np.arange(Q) % 13]), p, K_out)
