@@ -51,35 +51,82 @@ template <bool BF16> __device__ __forceinline__ kge_f32x16 small_mma(kge_f32x16 
 }
 
 // ---- scores: workgroup = 64 queries x 64 negatives, wave = 32 x 32 ----
-template <bool BF16, int KIND>
-__global__ __launch_bounds__(256) void small_score_kernel(const SmallArgs a) {
-    constexpr int ES = BF16 ? 2 : 4, U = BF16 ? 16 : 8;         // matrix steps (16 columns) requested together
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, g = lane >> 5;
-    const int b0 = blockIdx.y * 64 + (wave >> 1) * 32, n0 = blockIdx.x * 64 + (wave & 1) * 32;
-    if (b0 >= a.B || n0 >= a.N) return;
-    const char *pq = (const char *)a.Q + ((size_t)(b0 + lr) * a.dp + 8 * g) * ES;
-    const char *pt = (const char *)a.T + ((size_t)(n0 + lr) * a.dp + 8 * g) * ES;
+// The workgroup's 128 rows come into the LDS in NCH pieces of 256 bytes a row, all of them requested at once by asynchronous copies
+// (four rows of a piece per instruction); the matrix steps of a piece run while the later ones are under way.  Operands taken straight
+// from memory, 32 rows x 32 bytes per load instruction and every row by two waves, were bound by the lines that a load touches:
+// SCORE_FIGURES.
+// Piece: [64 queries, 64 negatives][256 bytes], 16-byte chunk c of row r at position c ^ kge_pl_swz(r).
+constexpr int SMALL_PIECE = 128 * 256;
+// fp32: two groups of four waves share a tile's steps (the three pieces of every value cost more than the matrix instructions), the
+// second hands its sums over through the LDS.
+constexpr int small_score_groups(bool bf16) { return bf16 ? 1 : 2; }
+template <bool BF16, int KIND, int NCH>
+__global__ __launch_bounds__(256 * small_score_groups(BF16)) void small_score_kernel(const SmallArgs a) {
+    constexpr int ES = BF16 ? 2 : 4, STEP = 16 * ES, SPP = 256 / STEP;     // bytes of a matrix step of sixteen columns, steps per piece
+    constexpr int G = small_score_groups(BF16), IPW = 32 / (4 * G);        // copies per wave and piece
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const int lane = threadIdx.x & 63, wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3, grp = wave8 >> 2;
+    const int lr = lane & 31, g = lane >> 5;
+    const int bw = blockIdx.y * 64, nw = blockIdx.x * 64;
+    const int b0 = bw + (wave >> 1) * 32, n0 = nw + (wave & 1) * 32;
+    // norms of the wave's rows: 32 of the queries, 32 of the negatives
+    const uint32_t side = NCH * SMALL_PIECE + wave * 256;
+    if constexpr (KIND == KGE_KIND_DIST)
+        kge_async_copy4(g == 0 ? (const void *)&a.rowinfo[b0 + lr].qn : (const void *)(a.tn + n0 + lr), lds0 + side);
+    const int steps = (a.dim + 15) / 16;                        // (dp is a multiple of 256 (bf16) or 128 columns, zero past d)
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int j = 0; j < IPW; ++j) {
+            const int i = j * 4 * G + wave8;                    // rows 4 i .. + 3; i % 4 = wave
+            const int chunk = (lane & 15) ^ ((lane >> 4) << 2) ^ wave;
+            const char *src = (i < 16 ? (const char *)a.Q + (size_t)(bw + 4 * i) * a.dp * ES : (const char *)a.T + (size_t)(nw + 4 * i - 64) * a.dp * ES) + c * 256;
+            // (columns that no step reads stay where they are; every row has some that one does)
+            if (c * 256 + chunk * 16 < steps * STEP)
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds0 + c * SMALL_PIECE + i * 1024),
+                             "v"((lane >> 4) * a.dp * ES + chunk * 16), "s"(src) : "memory");
+        }
     kge_f32x16 acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-    const int steps = (a.dim + 15) / 16;                        // (rounded up to U: dp is a multiple of 256 (bf16) or 128 columns, zero past d)
-    for (int s = 0; s < steps; s += U) {
-        uint4 q[U][ES / 2], t[U][ES / 2];
+    const char *pq = lds + ((wave >> 1) * 32 + lr) * 256, *pt = lds + (64 + (wave & 1) * 32 + lr) * 256;
+    const int swz = kge_pl_swz(lr);
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+    for (int c = 0; c < NCH; ++c) {
+        // (piece c of this wave's copies is here when only those of the later pieces are in flight)
+        if (c == NCH - 1) kge_wait_vmcnt<0>();
+        else if (c == NCH - 2) kge_wait_vmcnt<IPW>();
+        else if (c == NCH - 3) kge_wait_vmcnt<2 * IPW>();
+        else kge_wait_vmcnt<3 * IPW>();
+        __syncthreads();
 #pragma unroll
-            for (int e = 0; e < ES / 2; ++e) {
-                q[u][e] = *(const uint4 *)(pq + (s + u) * 16 * ES + e * 16);
-                t[u][e] = *(const uint4 *)(pt + (s + u) * 16 * ES + e * 16);
-            }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int v = 0; v < SPP / G; ++v) {
+            const int u = v * G + grp;
+            if (c * SPP + u >= steps) break;
             Frag<BF16> fq, ft;
-            if constexpr (BF16) { fq.v = q[u][0]; ft.v = t[u][0]; }
-            else { fq.v = kge_split3(q[u][0], q[u][1]); ft.v = kge_split3(t[u][0], t[u][1]); }
+            auto at = [&](const char *p, int e) { return *(const uint4 *)(p + c * SMALL_PIECE + ((u * ES + g * (ES / 2) + e) ^ swz) * 16); };
+            if constexpr (BF16) { fq.v = at(pq, 0); ft.v = at(pt, 0); }
+            else { fq.v = kge_split3(at(pq, 0), at(pq, 1)); ft.v = kge_split3(at(pt, 0), at(pt, 1)); }
             acc = small_mma<BF16>(acc, fq, ft);
         }
     }
+    if constexpr (G == 2) {
+        __syncthreads();                                        // (the pieces are done with)
+        float4 *half = (float4 *)lds + wave * 256 + lane;
+        if (grp == 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) half[i * 64] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+        }
+        __syncthreads();
+        if (grp == 1) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 h = half[i * 64];
+            acc[4 * i] += h.x; acc[4 * i + 1] += h.y; acc[4 * i + 2] += h.z; acc[4 * i + 3] += h.w;
+        }
+    }
+    if (b0 >= a.B || n0 >= a.N) return;
     // lane = negative n0 + lr; register i = query b0 + 8 (i / 4) + 4 g + i % 4
     const int n = n0 + lr;
     float sv[16];
@@ -88,12 +135,13 @@ __global__ __launch_bounds__(256) void small_score_kernel(const SmallArgs a) {
         for (int i = 0; i < 16; ++i) sv[i] = acc[i];
     } else {
         // |q|^2 + |t|^2 - 2 q.t; entries where it cancels (below 1e-3 of the norms) by direct differences
-        const float tn = a.tn[n];
+        const float *norms = (const float *)(lds + side);
+        const float tn = norms[32 + lr];
         float d2[16], thr[16];
         bool cancel = false;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const float qn = a.rowinfo[b0 + 8 * (i >> 2) + 4 * g + (i & 3)].qn;
+            const float qn = norms[8 * (i >> 2) + 4 * g + (i & 3)];
             d2[i] = fmaf(-2.f, acc[i], qn + tn);
             thr[i] = 1e-3f * (qn + tn);
             cancel = cancel || d2[i] < thr[i];
@@ -387,11 +435,24 @@ int kge_run_small_score(bool bf16, int kind, const void *Q, const void *T, const
     SmallArgs a{};
     a.Q = Q; a.T = T; a.rowinfo = rowinfo; a.tn = tn; a.S = S; a.ldS = ldS; a.B = B; a.N = N; a.Bp = Bp; a.Np = Np; a.dp = dp; a.dim = dim;
     const dim3 grid((N + 63) / 64, (B + 63) / 64);
-#define SMALL_SCORE(BF, KD) hipLaunchKernelGGL((small_score_kernel<BF, KD>), grid, dim3(256), 0, st, a)
-    if (bf16) { if (kind == KGE_KIND_DIST) SMALL_SCORE(true, KGE_KIND_DIST); else SMALL_SCORE(true, KGE_KIND_MULT); }
-    else      { if (kind == KGE_KIND_DIST) SMALL_SCORE(false, KGE_KIND_DIST); else SMALL_SCORE(false, KGE_KIND_MULT); }
+    const int pieces = (dim * (bf16 ? 2 : 4) + 255) / 256;
+    if (pieces > 4 || dp * (bf16 ? 2 : 4) < pieces * 256) return KGE_E_INVALID_ARG;
+#define SMALL_SCORE3(BF, KD, NCH)                                                                                           \
+    {                                                                                                                       \
+        static KgeLdsLimit limit;                                                                                           \
+        constexpr int bytes = NCH * SMALL_PIECE + 4 * 256;                                                                  \
+        if (limit.set((const void *)small_score_kernel<BF, KD, NCH>, bytes) != KGE_OK) return KGE_E_HIP;                    \
+        hipLaunchKernelGGL((small_score_kernel<BF, KD, NCH>), grid, dim3(256 * small_score_groups(BF)), bytes, st, a);                               \
+        return kge_launch_status();                                                                                         \
+    }
+#define SMALL_SCORE(BF, KD)                                                                                                 \
+    switch (pieces) {                                                                                                       \
+    case 1: SMALL_SCORE3(BF, KD, 1) case 2: SMALL_SCORE3(BF, KD, 2) case 3: SMALL_SCORE3(BF, KD, 3) default: SMALL_SCORE3(BF, KD, 4)  \
+    }
+    if (bf16) { if (kind == KGE_KIND_DIST) SMALL_SCORE(true, KGE_KIND_DIST) else SMALL_SCORE(true, KGE_KIND_MULT) }
+    else      { if (kind == KGE_KIND_DIST) SMALL_SCORE(false, KGE_KIND_DIST) else SMALL_SCORE(false, KGE_KIND_MULT) }
 #undef SMALL_SCORE
-    return kge_launch_status();
+#undef SMALL_SCORE3
 }
 
 // splits of the gradients' contraction index (str streamed rows): a wave of a workgroup's eight takes sixteen matrix steps at most
