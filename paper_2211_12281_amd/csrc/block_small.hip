@@ -11,8 +11,7 @@
 //               the gradients, the exponentials bound that launch (26 us instead of 19 for the RotatE case below)
 //   gradients   one launch for both operands: dQ = C T and dT = C^t Q; a workgroup makes 32 rows x 64 or 128 columns, its eight waves
 //               share out the contraction index and add up through the LDS, so that there are no partials in memory
-// (kge_loss_bwd, block kernels / here: RotatE fp32, B 448, N 1,088, d 256: 108 / 53 us; ComplEx bf16, B 640, N 1,536, d 400: 112 / 46 us;
-// the launches of the first: gather 7.6, scores 13.5, rows 5.2, gradients 19, chain rule 10 us.)
+// (kge_loss_bwd, block kernels / here: RotatE fp32, B 448, N 1,088, d 256: 108 / 46 us; ComplEx bf16, B 640, N 1,536, d 400: 112 / 40 us.)
 // What bounds each launch is its latency: start-up, two or three dependent loads and the matrix instructions of one wave.
 // Arithmetic: bf16 operands with fp32 accumulation, or three bf16 pieces per fp32 value.  On bf16 tables the coefficients are
 // finished when they are made, where the block kernels round the weight relative to a row reference (the dominating pairs are 1 and
@@ -25,7 +24,7 @@
 
 namespace {
 
-constexpr int SMALL_AHEAD = 2;         // matrix steps of the gradients in flight (3 and 4: the same time, 1-4 % slower on long contractions)
+constexpr int SMALL_AHEAD = 2;         // matrix steps of the gradients in flight (3: the same time, 1-4 % slower for rows of 1,024 bytes)
 
 struct SmallArgs {
     const void *Q, *T;                 // [Bp][dp] queries, [Np][dp] negatives (rows past B, N and columns past d are zero)
@@ -54,7 +53,8 @@ template <bool BF16> __device__ __forceinline__ kge_f32x16 small_mma(kge_f32x16 
 // The workgroup's 128 rows come into the LDS in NCH pieces of 256 bytes a row, all of them requested at once by asynchronous copies
 // (four rows of a piece per instruction); the matrix steps of a piece run while the later ones are under way.  Operands taken straight
 // from memory, 32 rows x 32 bytes per load instruction and every row by two waves, were bound by the lines that a load touches:
-// SCORE_FIGURES.
+// ComplEx bf16 640 x 1,536 x 400 12.7 -> 7.4 us, TransE bf16 512 x 1,024 x 256 8.2 -> 5.6, RotatE fp32 448 x 1,088 x 256 12.8 -> 10.4 (12.2
+// with one group of four waves).
 // Piece: [64 queries, 64 negatives][256 bytes], 16-byte chunk c of row r at position c ^ kge_pl_swz(r).
 constexpr int SMALL_PIECE = 128 * 256;
 // fp32: two groups of four waves share a tile's steps (the three pieces of every value cost more than the matrix instructions), the
@@ -170,19 +170,31 @@ __global__ __launch_bounds__(256 * small_score_groups(BF16)) void small_score_ke
     }
 }
 
+__device__ __forceinline__ uint32_t small_low_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ uint32_t small_high_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+// (p and bytes are the same in every lane)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t small_buffer(const void *p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00027000);
+}
+
 // ---- gradients: workgroup = 32 own rows x CT columns, eight waves share the split's part of the contraction index ----
 // A lane's columns are CT / 32 neighbours (one load per streamed row), column h of every lane is block h of the matrix product.
 template <bool BF16, int KIND, bool OWN_Q, int CT>
 __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile, int d_tile, int split, float *lds) {
     constexpr int NB = CT / 32;                                 // columns per lane, column blocks
     constexpr int ES = BF16 ? 2 : 4, XW = NB * ES / 4;          // 32-bit words of a lane's columns
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, g = lane >> 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 31, g = lane >> 5;
     const int o = own_tile * 32 + lr;                           // own row of the lane's coefficients
     const int str_n = OWN_Q ? a.N : a.B;
-    const int dcol = d_tile * CT + NB * lr;
-    const char *X = (const char *)(OWN_Q ? a.T : a.Q) + (size_t)dcol * ES;
-    const size_t xrow = (size_t)a.dp * ES;
-    const uint32_t *Cp = a.C + (OWN_Q ? (size_t)o * a.ldS : (size_t)o);
+    const int xrow = a.dp * ES;
+    // (buffer loads: a scalar offset, streamed row 16 s + j of the step, and one of the lane that never changes; no vector instruction)
+    const char *X = (const char *)(OWN_Q ? a.T : a.Q) + (size_t)d_tile * (CT * ES);
+    const uint32_t x_lane = (uint32_t)(8 * g * xrow + NB * ES * lr);
+    const int ldc = (int)a.ldS * 4;
+    const char *Cq = (const char *)a.C + (OWN_Q ? (size_t)own_tile * 32 * ldc : (size_t)own_tile * 128);
+    const uint32_t c_lane = OWN_Q ? (uint32_t)(lr * ldc + 32 * g) : (uint32_t)(8 * g * ldc + 4 * lr);
+    const auto xbuf = small_buffer(X, (OWN_Q ? a.Np : a.Bp) * xrow - d_tile * (CT * ES));
+    const auto cbuf = small_buffer(Cq, OWN_Q ? 32 * ldc : a.Bp * ldc - own_tile * 128);
     kge_f32x16 acc[NB];
 #pragma unroll
     for (int h = 0; h < NB; ++h) for (int i = 0; i < 16; ++i) acc[h][i] = 0.f;
@@ -193,30 +205,36 @@ __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile
     // raw operands of a step: the lane's eight streamed rows (rows and columns behind the block: zero coefficients, zero rows)
     struct Raw { uint32_t c[8], x[8][XW]; };
     auto load = [&](int s, Raw &r) {
-        const int k0 = s * 16 + 8 * g;
         if constexpr (OWN_Q) {                                  // (rows of C start 16-byte aligned)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                const uint4 v = *(const uint4 *)(Cp + k0 + 4 * e);
+                const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(cbuf, c_lane + 16 * e, s * 64, 0));
                 r.c[4 * e] = v.x; r.c[4 * e + 1] = v.y; r.c[4 * e + 2] = v.z; r.c[4 * e + 3] = v.w;
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) r.c[j] = Cp[(size_t)(k0 + j) * a.ldS];
+            for (int j = 0; j < 8; ++j) r.c[j] = __builtin_amdgcn_raw_buffer_load_b32(cbuf, c_lane, (s * 16 + j) * ldc, 0);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const char *p = X + (size_t)(k0 + j) * xrow;
-            if constexpr (XW == 1) r.x[j][0] = *(const uint32_t *)p;
-            else if constexpr (XW == 2) { const uint2 v = *(const uint2 *)p; r.x[j][0] = v.x; r.x[j][1] = v.y; }
-            else { const uint4 v = *(const uint4 *)p; r.x[j][0] = v.x; r.x[j][1] = v.y; r.x[j][2] = v.z; r.x[j][3] = v.w; }
+            const int row = (s * 16 + j) * xrow;
+            if constexpr (XW == 1) r.x[j][0] = __builtin_amdgcn_raw_buffer_load_b32(xbuf, x_lane, row, 0);
+            else if constexpr (XW == 2) { const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(xbuf, x_lane, row, 0)); r.x[j][0] = v.x; r.x[j][1] = v.y; }
+            else { const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xbuf, x_lane, row, 0)); r.x[j][0] = v.x; r.x[j][1] = v.y; r.x[j][2] = v.z; r.x[j][3] = v.w; }
         }
     };
-    auto step = [&](const Raw &r) {
+    auto step = [&](Raw &r) {
         Frag<BF16> fc, fc2;                                     // fc2: the second pieces (dQ on bf16 tables)
+        // (pinned here as they came: otherwise their packing moves to the request, and the wait for memory with it)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            asm volatile("" : "+v"(r.c[j]));
+#pragma unroll
+            for (int w = 0; w < XW; ++w) asm volatile("" : "+v"(r.x[j][w]));
+        }
         if constexpr (BF16) {
-            auto first = [&](int j) { return (r.c[j] & 0xffffu) | (r.c[j + 1] << 16); };
-            auto second = [&](int j) { return (r.c[j] >> 16) | (r.c[j + 1] & 0xffff0000u); };
+            auto first = [&](int j) { return small_low_halves(r.c[j], r.c[j + 1]); };
+            auto second = [&](int j) { return small_high_halves(r.c[j], r.c[j + 1]); };
             fc.v = make_uint4(first(0), first(2), first(4), first(6));
             if constexpr (OWN_Q) fc2.v = make_uint4(second(0), second(2), second(4), second(6));
         } else fc.v = kge_split3(make_uint4(r.c[0], r.c[1], r.c[2], r.c[3]), make_uint4(r.c[4], r.c[5], r.c[6], r.c[7]));
@@ -233,7 +251,7 @@ __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const uint32_t x0 = r.x[2 * j][h >> 1], x1 = r.x[2 * j + 1][h >> 1];
-                    w[j] = h & 1 ? (x0 >> 16) | (x1 & 0xffff0000u) : (x0 & 0xffffu) | (x1 << 16);
+                    w[j] = h & 1 ? small_high_halves(x0, x1) : small_low_halves(x0, x1);
                 }
                 f.v = make_uint4(w[0], w[1], w[2], w[3]);
             } else
@@ -242,20 +260,25 @@ __device__ __forceinline__ void small_grad_body(const SmallArgs &a, int own_tile
             acc[h] = small_mma<BF16>(acc[h], fc, f);
         }
     };
-    if (s_lo < s_hi) {                                          // (the next AH - 1 steps are requested before this one is used)
+    // (the next AH - 1 steps are requested before this one is used; the scheduler is held to that order: left alone it moved every
+    // request behind the step in front of it, and a wave waited for memory in every step)
+    if (s_lo < s_hi) {
         constexpr int AH = SMALL_AHEAD;
         Raw r[AH];
 #pragma unroll
         for (int u = 0; u < AH - 1; ++u) load(min(s_lo + u, s_hi - 1), r[u]);
-        for (int s = s_lo; s < s_hi; s += AH) {
+        int s = s_lo;
+        for (; s + AH <= s_hi; s += AH) {
 #pragma unroll
             for (int u = 0; u < AH; ++u) {
-                if (s + u < s_hi) {
-                    load(min(s + u + AH - 1, s_hi - 1), r[(u + AH - 1) % AH]);
-                    step(r[u]);
-                }
+                load(min(s + u + AH - 1, s_hi - 1), r[(u + AH - 1) % AH]);
+                __builtin_amdgcn_sched_barrier(0);
+                step(r[u]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+#pragma unroll
+        for (int u = 0; u < AH - 1; ++u) if (s + u < s_hi) step(r[u]);
     }
     // Register i of acc[h]: own row 8 (i / 4) + 4 g + i % 4, column NB lr + h.  The upper four waves hand theirs to the lower four,
     // those add up in wave order.
@@ -458,6 +481,16 @@ int kge_run_small_score(bool bf16, int kind, const void *Q, const void *T, const
 // splits of the gradients' contraction index (str streamed rows): a wave of a workgroup's eight takes sixteen matrix steps at most
 int kge_small_splits(int str) { return (str + 2047) / 2048; }
 
+// columns of a workgroup of the gradients: 128 read the coefficients half as often as 64, if they fill the chip and few of them lie
+// behind the row.  Calls, 128 / 64 columns, us: TransE bf16 512 x 1,024 x 256 (96 workgroups of 128 columns) 32.7 / 30.7, RotatE fp32
+// 448 x 1,088 x 256 (96) 45.2 / 41.1, ComplEx bf16 640 x 1,536 x 400 (272) 44.7 / 43.0, 512 x 4,096 x 256 (288) 51.9 / 48.4;  TransE bf16
+// 1,024 x 3,900 x 256 (308) 57.7 / 60.0, ComplEx 1,000 x 2,000 x 400 (380) 54.6 / 56.6, 1,500 x 2,500 x 512 (504) 85.4 / 89.6;  rows that
+// 128 columns pad by a fifth or a third: DistMult 2,048 x 2,048 x 320 73.1 / 69.6, fp32 2,500 x 2,500 x 192 132.8 / 112.4
+static int small_columns(int B, int N, int dim) {
+    const int wide = (dim + 127) / 128, narrow = (dim + 63) / 64, tiles = (B + 31) / 32 + (N + 31) / 32;
+    return tiles * wide <= 300 || 12 * wide > 7 * narrow ? 64 : 128;
+}
+
 int kge_run_small_grad(bool bf16, int kind, const void *Q, const void *T, const void *C, int64_t ldS, int B, int N, int Bp, int Np, int dp,
                        int dim, int q_splits, int t_splits, float *accq, float *acct, float4 *sumt, hipStream_t st) {
     if (dp % 128 || Bp % 32 || Np % 32 || ldS % 8 || B < 1 || N < 1 || q_splits != kge_small_splits(N) || t_splits != kge_small_splits(B))
@@ -466,7 +499,7 @@ int kge_run_small_grad(bool bf16, int kind, const void *Q, const void *T, const 
     SmallArgs a{};
     a.Q = Q; a.T = T; a.C = (const uint32_t *)C; a.ldS = ldS; a.B = B; a.N = N; a.Bp = Bp; a.Np = Np; a.dp = dp; a.dim = dim;
     a.accq = accq; a.acct = acct; a.sumt = sumt;
-    const int ct = dim > 64 ? 128 : 64;
+    const int ct = small_columns(B, N, dim);
     a.d_tiles = (dim + ct - 1) / ct;
     a.q_splits = q_splits; a.t_splits = t_splits;
     a.q_steps = ((N + 15) / 16 + q_splits - 1) / q_splits; a.t_steps = ((B + 15) / 16 + t_splits - 1) / t_splits;
