@@ -20,7 +20,7 @@
 // coefficients (distance scorers) both, so that the rounding stays on the queries (rounded sums: dT's error 6-22 % larger).
 #include "block_kernel.hpp"
 #include "prep_kernels.h"
-#include "row_finish.hpp"
+#include "small_rows.hpp"
 
 namespace {
 
@@ -338,116 +338,17 @@ __global__ __launch_bounds__(512) void small_grad_kernel(const SmallArgs a) {
     else small_grad_body<BF16, KIND, false, CT>(a, own, d_tile, split, lds);
 }
 
-// ---- rows: loss statistics of a row of S and their finish, one workgroup per query (rows past B get what kge_rowfinish_kernel gives
-// them); with C the row's coefficients, fp32 or two bf16 pieces (C may be S itself: a thread overwrites what it has read) ----
-struct SmallRowsArgs {
-    const float *S; int64_t ldS; int B, N, Bp; int loss; float gamma, adv_temp, c_corr, scale; const float *pos; KgeRowInfo *rowinfo;
-    float *lossb, *gpos; uint32_t *C; int bf16, dist; float4 *sumq; int q_splits;
-};
-__global__ __launch_bounds__(256) void small_rows_kernel(const SmallRowsArgs a) {
-    __shared__ float red[4][4], fb;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, N = a.N, loss = a.loss;
-    const int npad = (N + 31) / 32 * 32;
-    auto put = [&](int n, float c) -> float {                   // returns what the contraction over the negatives sees of it
-        uint32_t w = __float_as_uint(c);
-        if (a.bf16) {
-            const __bf16 x0 = (__bf16)c, x1 = (__bf16)(c - (float)x0);
-            w = (uint32_t)__builtin_bit_cast(uint16_t, x0) | (uint32_t)__builtin_bit_cast(uint16_t, x1) << 16;
-            c = (float)x0 + (float)x1;
-        }
-        a.C[(size_t)b * a.ldS + n] = w;
-        return c;
-    };
-    if (b >= a.B) {
-        if (tid == 0) { a.lossb[b] = 0.f; a.gpos[b] = 0.f; a.rowinfo[b].K = -INFINITY; }
-        if (a.C && b < (a.B + 31) / 32 * 32) for (int n = tid; n < npad; n += 256) put(n, 0.f);
-        return;
-    }
-    const float xscale = (loss == KGE_LOGSIGMOID ? a.adv_temp : 1.f) * KGE_LOG2E;
-    const float *row = a.S + (size_t)b * a.ldS;
-    constexpr int R = 8;                                        // scores that a thread keeps (2,048 negatives)
-    float v[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) { const int n = tid + 256 * j; v[j] = n < N ? row[n] : -INFINITY; }
-    const float fp = a.pos[b];
-    float m = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < R; ++j) m = fmaxf(m, v[j]);
-    for (int n = tid + 256 * R; n < N; n += 256) m = fmaxf(m, row[n]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (lane == 0) red[0][wave] = m;
-    __syncthreads();
-    const float s_max = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
-    m = s_max > -INFINITY ? s_max * xscale : -INFINITY;
-    const float m_neg = m > -INFINITY ? -m : 0.f;               // (a row of nothing but -inf: every weight 0)
-    // m is rounded, s xscale below is not: the largest score's own weight would be off by more than a factor of two beyond 2^24, and
-    // nothing or infinite beyond 2^31; there its remainder is taken from every exponent (not without C: who makes the coefficients
-    // elsewhere, from K, has the same rounding in K)
-    const float rest = fmaf(s_max, xscale, m_neg), rem = a.C && fabsf(rest) > 1.f && fabsf(rest) < INFINITY ? rest : 0.f;
-    auto weight = [&](float s) { return kge_exp2(fmaf(s, xscale, m_neg) - rem); };       // relative to the largest: at most about 1
-    float l = 0.f, ac = 0.f;
-    auto add = [&](float s) {
-        const float e = weight(s);
-        l += e;
-        if (loss == KGE_LOGSIGMOID) {
-            const float y = a.gamma + s, t = kge_exp2(-fabsf(y) * KGE_LOG2E);
-            if (e > 0.f) ac = fmaf(e, fmaxf(y, 0.f) + KGE_LN2 * kge_log2(1.f + t), ac);
-        }
-    };
-#pragma unroll
-    for (int j = 0; j < R; ++j) if (tid + 256 * j < N) add(v[j]);
-    for (int n = tid + 256 * R; n < N; n += 256) add(row[n]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { l += __shfl_xor(l, o); ac += __shfl_xor(ac, o); }
-    if (lane == 0) { red[1][wave] = l; red[2][wave] = ac; }
-    __syncthreads();
-    if (tid == 0) {
-        l = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-        ac = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
-        const KgeRowFinish o = kge_rowfinish_merged(m, l, ac, N, loss, a.gamma, a.c_corr, a.scale, fp);
-        a.lossb[b] = o.L; a.gpos[b] = o.gp; a.rowinfo[b].K = o.K;
-        fb = l > 0.f ? a.scale * o.share / l : 0.f;
-    }
-    if (!a.C) return;
-    __syncthreads();
-    const float f = fb;                                         // dL / d(score) of a weight of 1 (log-sigmoid: times sigma(gamma + s))
-    float csum = 0.f;
-    auto coef = [&](int n, float s) {
-        float w = weight(s) * f;
-        if (loss == KGE_LOGSIGMOID) {
-            const float y = a.gamma + s;
-            const float t = kge_exp2(-fabsf(y) * KGE_LOG2E), rcp = __builtin_amdgcn_rcpf(1.f + t);
-            w *= y >= 0.f ? rcp : t * rcp;
-        }
-        if (a.dist) w = s < 0.f ? w * __builtin_amdgcn_rcpf(-s) : 0.f;
-        csum += put(n, w);
-    };
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const int n = tid + 256 * j;
-        if (n < N) coef(n, v[j]); else if (n < npad) put(n, 0.f);
-    }
-    for (int n = tid + 256 * R; n < npad; n += 256) { if (n < N) coef(n, row[n]); else put(n, 0.f); }
-    if (a.dist) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) csum += __shfl_xor(csum, o);
-        if (lane == 0) red[3][wave] = csum;
-        __syncthreads();
-        for (int s = tid; s < a.q_splits; s += 256)             // (the whole sum with the first split's partial rows)
-            a.sumq[(size_t)s * a.Bp + b] = make_float4(s == 0 ? (red[3][0] + red[3][1]) + (red[3][2] + red[3][3]) : 0.f, 0.f, 0.f, 0.f);
-    }
+// ---- rows: one workgroup per query (small_rows.hpp) ----
+__global__ __launch_bounds__(256) void small_rows_kernel(const KgeSmallRowsArgs a) {
+    __shared__ KgeSmallRowsShared sh;
+    kge_small_rows_body((int)blockIdx.x, (int)threadIdx.x, sh, a);
 }
 
 }  // namespace
 
-int kge_run_small_rows(const float *S, int64_t ldS, int B, int N, int Bp, int loss, float gamma, float adv_temp, float c_corr, float scale,
-                       const float *pos, KgeRowInfo *rowinfo, float *lossb, float *gpos, hipStream_t st, void *C, bool bf16, int kind,
-                       float4 *sumq, int q_splits) {
-    if (Bp == 0) return KGE_OK;
-    const SmallRowsArgs a{S, ldS, B, N, Bp, loss, gamma, adv_temp, c_corr, scale, pos, rowinfo, lossb, gpos, (uint32_t *)C, bf16 ? 1 : 0,
-                          kind == KGE_KIND_DIST ? 1 : 0, sumq, q_splits};
-    hipLaunchKernelGGL(small_rows_kernel, dim3(Bp), dim3(256), 0, st, a);
+int kge_run_small_rows(const KgeSmallRowsArgs &a, hipStream_t st) {
+    if (a.Bp == 0) return KGE_OK;
+    hipLaunchKernelGGL(small_rows_kernel, dim3(a.Bp), dim3(256), 0, st, a);
     return kge_launch_status();
 }
 

@@ -12,7 +12,8 @@ int kge_run_sparse_adam_plan(int64_t n_rows, const int32_t *idx, int64_t M, void
 int kge_run_sparse_adam_apply(float *param, void *shadow, float *m, float *v, int64_t n_rows, int dim, int64_t ld,
                               const float *grads, int64_t M, const kge_adam_cfg_t &cfg, void *ws, hipStream_t st);
 int kge_run_sparse_adam_apply_tables(const kge_adam_table_t *tb, int n, const kge_adam_cfg_t &cfg, hipStream_t st);
-int kge_run_sparse_adam_plan_tables(const kge_adam_plan_t *pl, int n, hipStream_t st, const KgeRowFinishQArgs *rf = nullptr);
+int kge_run_sparse_adam_plan_tables(const kge_adam_plan_t *pl, int n, hipStream_t st, const KgeRowFinishQArgs *rf = nullptr,
+                                    const KgeSmallRowsArgs *sr = nullptr);
 int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, int64_t Q, int64_t lo, int64_t hi,
                  int K, int32_t *out_idx, float *out_score, const int32_t *true_t, int64_t *out_rank, void *ws,
                  size_t ws_bytes, hipStream_t st);
@@ -557,11 +558,13 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     // (the plans of the sparse update that the caller asked for: their sorts need the ids alone and share the launch of the
     // rows' finish where there is one of that kind; otherwise they follow at the end)
     bool planned = false;
-    if (have_block && (g.small || g.l1))                    // one row pass gives the loss statistics and their finish
-        rc = kge_run_small_rows(b.S, g.Np, g.B, g.N, g.Bp, cfg->loss, cfg->gamma, cfg->adv_temp, c_corr, scale, b.pos, b.rowinfo, b.lossb,
-                                b.gpos, st, g.transh ? nullptr : b.S, g.small && g.bf16, g.small ? g.kind : KGE_KIND_MULT,
-                                b.sumq, g.nsplit_q);
-    else if (keep_weights && plans) {
+    if (have_block && (g.small || g.l1)) {                  // one row pass gives the loss statistics and their finish
+        const KgeSmallRowsArgs sr{b.S, g.Np, g.B, g.N, g.Bp, cfg->loss, cfg->gamma, cfg->adv_temp, c_corr, scale, b.pos, b.rowinfo,
+                                  b.lossb, b.gpos, g.transh ? nullptr : (uint32_t *)b.S, g.small && g.bf16, g.small && g.kind == KGE_KIND_DIST,
+                                  b.sumq, g.nsplit_q};
+        rc = plans ? kge_run_sparse_adam_plan_tables(plans, n_plans, st, nullptr, &sr) : kge_run_small_rows(sr, st);
+        planned = plans != nullptr;
+    } else if (keep_weights && plans) {
         const KgeRowFinishQArgs rf{b.stat_part, g.nsplit_q, g.Bp, g.B, g.N, cfg->loss, cfg->gamma, c_corr, scale, b.pos, b.rowinfo,
                                    b.lossb, b.gpos, (const uint16_t *)b.Q, (uint16_t *)b.Qs};
         rc = kge_run_sparse_adam_plan_tables(plans, n_plans, st, &rf);

@@ -123,6 +123,14 @@ struct KgeRowFinishQArgs {
     KgeRowInfo *rowinfo; float *lossb, *gpos; const uint16_t *Q; uint16_t *Qs;
 };
 
+// Row pass over a score block in memory (small_rows.hpp).  C null: statistics alone; bf16: coefficients as two bf16 pieces; dist: over the
+// distance, their sums to sumq [q_splits][Bp]
+struct KgeSmallRowsArgs {
+    const float *S; int64_t ldS; int B, N, Bp; int loss; float gamma, adv_temp, c_corr, scale; const float *pos; KgeRowInfo *rowinfo;
+    float *lossb, *gpos; uint32_t *C; int bf16, dist; float4 *sumq; int q_splits;
+};
+
+
 bool kge_fwd_pp_applies(bool bf16, int rb, bool transh, int dsplit);
 bool kge_gradt_pp_applies(bool bf16, int rb, bool transh, int dsplit);
 // the kernel of block_sym.hip serves both passes of the same configurations; it walks the stream in tiles of 64 rows

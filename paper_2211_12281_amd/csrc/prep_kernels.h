@@ -90,8 +90,6 @@ int kge_run_l1h_grad(bool bf16, bool own_is_query, const float *Q, const float *
 int kge_small_splits(int str);
 int kge_run_small_score(bool bf16, int kind, const void *Q, const void *T, const KgeRowInfo *rowinfo, const float *tn, int B, int N, int Bp,
                         int Np, int dp, int dim, float *S, int64_t ldS, hipStream_t st);
-int kge_run_small_rows(const float *S, int64_t ldS, int B, int N, int Bp, int loss, float gamma, float adv_temp, float c_corr, float scale,
-                       const float *pos, KgeRowInfo *rowinfo, float *lossb, float *gpos, hipStream_t st, void *C = nullptr,
-                       bool bf16 = false, int kind = 0, float4 *sumq = nullptr, int q_splits = 0);
+int kge_run_small_rows(const KgeSmallRowsArgs &a, hipStream_t st);
 int kge_run_small_grad(bool bf16, int kind, const void *Q, const void *T, const void *C, int64_t ldS, int B, int N, int Bp, int Np, int dp,
                        int dim, int q_splits, int t_splits, float *accq, float *acct, float4 *sumt, hipStream_t st);

@@ -4,7 +4,9 @@
 //   3. one Adam step on each distinct row, fp32 master weights + moments, optional bf16 shadow
 // Only rows that occur in idx are read or written (arXiv 2211.12281, Section 1: sparse access).
 #include "kge_internal.h"
+#include "prep_kernels.h"
 #include "row_finish.hpp"
+#include "small_rows.hpp"
 #include <math.h>
 #include <mutex>
 
@@ -574,6 +576,17 @@ void sort_small_rowfinish_kernel(const SmallSorts T, const int sort_blocks, cons
     else kge_rowfinish_qscale_body((int)blockIdx.x - sort_blocks, q);
 }
 
+// The same with the row pass over a score block in memory (small blocks, 1-norm): four rows per workgroup.
+__global__ __attribute__((amdgpu_flat_work_group_size(SMALL_NT, SMALL_NT), amdgpu_waves_per_eu(8, 8)))
+void sort_small_rows_kernel(const SmallSorts T, const int sort_blocks, const KgeSmallRowsArgs a) {
+    __shared__ KgeSmallRowsShared sh[SMALL_NT / 256];
+    if ((int)blockIdx.x < sort_blocks) sort_small_body(T, (int)blockIdx.x);
+    else {
+        const int q = (int)threadIdx.x >> 8;
+        kge_small_rows_body(((int)blockIdx.x - sort_blocks) * (SMALL_NT / 256) + q, (int)threadIdx.x & 255, sh[q], a);
+    }
+}
+
 // Runs of equal rows ("segments") in the sorted order are reduced in two ways:
 //  - a segment that lies inside one aligned chunk of SEG_CHUNK positions is summed and updated by the
 //    wave of its first position (kernel A): full parallelism over the many short segments;
@@ -817,8 +830,9 @@ static void sort_result(int64_t M, int64_t key_range, void *ws, const uint32_t *
 }
 
 // Several tables: those of up to SMALL_MAX ids share one launch (256 or 32 workgroups each), longer ones take the radix passes.
-// rf: the finish of the rows' losses joins the launch of the small sorts (or gets a launch of the same kernel to itself).
-int kge_run_sparse_adam_plan_tables(const kge_adam_plan_t *pl, int n, hipStream_t st, const KgeRowFinishQArgs *rf) {
+// rf: the finish of the rows' losses joins the launch of the small sorts (or gets a launch of the same kernel to itself); sr: the row
+// pass over a score block does (or gets its own).
+int kge_run_sparse_adam_plan_tables(const kge_adam_plan_t *pl, int n, hipStream_t st, const KgeRowFinishQArgs *rf, const KgeSmallRowsArgs *sr) {
     KgeProfScope prof(KGE_PROF_SORT, st);
     SmallSorts T = {};
     int small = 0, nwg = 0;
@@ -843,8 +857,14 @@ int kge_run_sparse_adam_plan_tables(const kge_adam_plan_t *pl, int n, hipStream_
         for (int k = 0; k < small; ++k) ms[k] = T.t[k].M;
         small_parts(ms, small, lb);
         for (int k = 0; k < small; ++k) { T.t[k].lb = lb[k]; nwg += 1 << lb[k]; }
-        if (!rf) hipLaunchKernelGGL(sort_small_kernel, dim3(nwg), dim3(SMALL_NT), 0, st, T);
+        if (!rf && !sr) hipLaunchKernelGGL(sort_small_kernel, dim3(nwg), dim3(SMALL_NT), 0, st, T);
     }
+    if (sr && small > 0) {
+        const int rows_wg = SMALL_NT / 256;
+        hipLaunchKernelGGL(sort_small_rows_kernel, dim3(nwg + (sr->Bp + rows_wg - 1) / rows_wg), dim3(SMALL_NT), 0, st, T, nwg, *sr);
+        return kge_launch_status();
+    }
+    if (sr) return kge_run_small_rows(*sr, st);
     if (rf && rf->Bp > 0) {
         const int rows_wg = SMALL_NT / 64;
         hipLaunchKernelGGL(sort_small_rowfinish_kernel, dim3(nwg + (rf->Bp + rows_wg - 1) / rows_wg), dim3(SMALL_NT), 0, st, T, nwg, *rf);

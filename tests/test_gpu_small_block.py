@@ -2,6 +2,7 @@
 end; and the block kernels, which larger blocks use, on the cases of test_gpu_loss_bwd.py that are too small to reach them."""
 import numpy as np
 import pytest
+import torch
 
 import test_gpu_loss_bwd as base
 from helpers import RTOL_BF16, RTOL_F32, dev_idx, gpu_model, make_case, norm_err
@@ -224,3 +225,37 @@ def test_columns_per_lane_of_the_row_kernels(orc, scorer, bf16, dim, N):
     dim = dim if bf16 or dim <= 256 else 240               # (fp32 rows end at 256 columns)
     G = make_case(scorer, 3000, 9, dim, 37, N, bf16, amp=0.3 if scorer in ("distmult", "complex") else 0.1, zipf=True)
     base._compare(orc, scorer, "logsigmoid", G, bf16, 3000, kw=dict(gamma=1.0, adv_temp=0.7, reg_l3=1e-3))
+
+
+@pytest.mark.parametrize("scorer,dim,bf16,p_norm,B,N,n_ent", [
+    ("transe", 64, True, 2, 1, 1, 50), ("distmult", 64, False, 2, 257, 2051, 4000),        # rows beyond the last group of four, beyond the eight scores a thread keeps
+    ("rotate", 128, True, 1, 130, 300, 900), ("transh", 64, False, 1, 67, 95, 300),        # 1-norm; without coefficients
+    ("transe", 32, True, 1, 70, 33_000, 60_000)])                                          # entity ids for the radix passes: the rows have their own launch
+def test_row_pass_beside_the_sorts(scorer, dim, bf16, p_norm, B, N, n_ent):
+    """kge_loss_bwd_sampled_planned on score blocks in memory against the call and its plans: bit for bit, plans as updates."""
+    import kge_synth as ks
+    import paper_2211_12281_amd as kge
+    g = torch.Generator(device="cuda").manual_seed(B + N)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    rows = lambda n, d: (torch.randn((n, d), generator=g, device="cuda") * 0.3).to(dt)
+    k_rel = dim // 2 if scorer == "rotate" else dim
+    model = kge.Model(scorer, rows(n_ent, dim), rows(9, k_rel), rows(9, dim) if scorer == "transh" else None, p_norm=p_norm)
+    draw_ids = lambda n, size: torch.randint(0, n, (size,), generator=g, device="cuda", dtype=torch.int32)
+    h, r, t = draw_ids(n_ent, B), draw_ids(9, B), draw_ids(n_ent, B)
+    res = []
+    for planned in (False, True):
+        ids = torch.cat([h, t, torch.full((N,), -1, dtype=torch.int32, device="cuda")])
+        ws = (kge.Workspace(), kge.Workspace())
+        plans = [(n_ent, dim, ids, ws[0]), (9, k_rel, r, ws[1])]
+        kw = dict(gamma=6.0, adv_temp=1.0, n_ent_for_c=n_ent, draw=(ks.BASE_SEED, 3, ks.TAG_NEG, 0, n_ent))
+        out = kge.loss_bwd(model, "logsigmoid", h, r, t, ids[2 * B:], plans=plans if planned else None, **kw)
+        if not planned:
+            kge.sparse_adam_plan_tables(plans)
+        st = [torch.zeros((n, d), device="cuda") for n, d in ((n_ent, dim), (9, k_rel)) for _ in range(3)]
+        kge.sparse_adam_apply_tables([(st[0], None, st[1], st[2], out["g_ent"], ws[0]), (st[3], None, st[4], st[5], out["g_rel"], ws[1])],
+                                     1e-2, step=2)
+        torch.cuda.synchronize()
+        res.append([x for x in out.values() if x is not None] + [ids] + st)
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+    assert bool((res[0][-1] != 0).any())
