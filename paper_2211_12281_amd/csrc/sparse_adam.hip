@@ -740,6 +740,103 @@ __global__ void adam_boundary_tables_kernel(const AdamTables T, AdamConst c) {
     }
 }
 
+// Short tables: everything in ONE launch.  Per chunk and 64 columns one workgroup takes the boundary-crossing segment that starts there, if
+// one does: sixteen lanes per piece, 32 pieces at a time, added through the LDS in the order of adam_boundary_body, so the same bits.
+// The second launch costs 3-4 us of the GPU's time and as much of the host's; a segment of M rows takes M / 1,024 rounds here, which is why
+// M is limited (with tables of 1,000 rows beside it, two launches / one, us: 2,048 Zipf ids of 256 columns 15.9 / 13.3 - the host's
+// time -, 2,048 equal ids 16.2 / 13.3, 512 columns 17.6 / 13.5;  3,000 equal ids 16.2 / 18.2, 4,096 16.1 / 22.9, 8,192 Zipf ids 15.9 / 16.8;
+// sixteen pieces at a time, their row numbers fetched one by one: 2,048 equal ids 26, a wave per piece in workgroups of 1,024: 24).
+constexpr int64_t ADAM_ONE_M = 2048;
+constexpr int ADAM_ONE_COLS = 64, ADAM_ONE_NT = 512, ADAM_ONE_GROUPS = ADAM_ONE_NT / 16;
+__device__ __forceinline__ void adam_segment_body(int64_t k, int slice, const AdamTable &t, AdamConst c, float (*piece)[ADAM_ONE_COLS]) {
+    static_assert(SEG_CHUNK == 32, "");
+    const int lane = threadIdx.x & 63, l16 = lane & 15, grp = threadIdx.x >> 4;        // groups of sixteen lanes
+    const uint32_t *sk = t.sk;
+    const int64_t c0 = k * SEG_CHUNK, c1 = c0 + SEG_CHUNK;
+    if (c1 >= t.M) return;                                  // nothing continues past the last chunk
+    const uint32_t key = sk[c1 - 1];
+    if (sk[c1] != key) return;                              // no segment crosses this chunk's end
+    const uint64_t m = __ballot(lane < SEG_CHUNK && sk[c0 + (lane < SEG_CHUNK ? lane : 0)] == key);
+    const uint32_t others = ~(uint32_t)m;
+    const int start = others ? 32 - __builtin_clz(others) : 0;
+    if (start == 0 && c0 > 0 && sk[c0 - 1] == key) return;  // the segment started in an earlier chunk
+    int pieces = 1;                                         // this chunk's and those of the chunks that start inside the segment
+    for (;;) {
+        const int64_t pos = c0 + (int64_t)(pieces + lane) * SEG_CHUNK;
+        const uint64_t cont = __ballot(pos < t.M && sk[pos] == key);
+        const int run = cont == ~0ull ? 64 : __builtin_ctzll(~cont);
+        pieces += run;
+        if (run < 64) break;
+    }
+    const int col = slice * ADAM_ONE_COLS + 4 * l16;
+    const float *grads = t.grads + (col < t.dim ? col : 0);
+    float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int p0 = 0; p0 < pieces; p0 += ADAM_ONE_GROUPS) {
+        const int p = p0 + grp;
+        const int64_t at = c0 + (int64_t)(p < pieces ? p : 0) * SEG_CHUNK;
+        // the piece: the chunk's positions from `start` on, or its leading ones
+        const uint64_t b0 = __ballot(at + l16 < t.M && sk[at + l16 < t.M ? at + l16 : c0] == key);
+        const uint64_t b1 = __ballot(at + 16 + l16 < t.M && sk[at + 16 + l16 < t.M ? at + 16 + l16 : c0] == key);
+        const uint32_t in = (uint32_t)(b0 >> (lane & 48)) & 0xffffu | (uint32_t)(b1 >> (lane & 48)) << 16;
+        const int lo = p == 0 ? start : 0, hi = p >= pieces ? 0 : p == 0 || in == ~0u ? 32 : __builtin_ctz(~in);
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t row[32];                                   // (rows that are not the segment's: any that exists)
+#pragma unroll
+        for (int j = 0; j < 32; ++j) row[j] = t.sp[at + j < t.M ? at + j : c0];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float4 v[16];
+            if (!__any(hi > 16 * h)) break;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = *(const float4 *)(grads + (int64_t)row[16 * h + u] * t.dim);
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int j = 16 * h + u;
+                if (j >= lo && j < hi) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
+            }
+        }
+        *(float4 *)(piece[grp] + 4 * l16) = s;
+        __syncthreads();
+        if (grp == 0) {
+#pragma unroll
+            for (int w = 0; w < ADAM_ONE_GROUPS; ++w) {
+                const float4 v = *(const float4 *)(piece[w] + 4 * l16);
+                if (p0 + w == 0) g = v;
+                else if (p0 + w < pieces) { g.x += v.x; g.y += v.y; g.z += v.z; g.w += v.w; }
+            }
+        }
+        __syncthreads();
+    }
+    if (grp != 0 || col >= t.dim) return;
+    adam_resolve(c);
+    adam_apply(key, col, g, t.ld, t.param, t.shadow, t.mom, t.var, c);
+}
+
+// (piece_blocks: chunks x slices of the columns)
+__global__ __launch_bounds__(ADAM_ONE_NT) void adam_one_tables_kernel(const AdamTables T, AdamConst c) {
+    __shared__ __attribute__((aligned(16))) float piece[ADAM_ONE_GROUPS][ADAM_ONE_COLS];
+    int b = (int)blockIdx.x;
+#pragma unroll
+    for (int k = 0; k < ADAM_MAX_TABLES; ++k) {
+        const AdamTable &t = T.t[k];
+        if (b < t.piece_blocks) {
+            const int slices = (t.dim + ADAM_ONE_COLS - 1) / ADAM_ONE_COLS;
+            adam_segment_body(b / slices, b % slices, t, c, piece);
+            return;
+        }
+        b -= t.piece_blocks;
+    }
+#pragma unroll
+    for (int k = 0; k < ADAM_MAX_TABLES; ++k) {
+        const AdamTable &t = T.t[k];
+        if (b < t.interior_blocks) {
+            adam_interior_body(b, t.sk, t.sp, t.M, t.grads, t.dim, t.ld, t.param, t.shadow, t.mom, t.var, c);
+            return;
+        }
+        b -= t.interior_blocks;
+    }
+}
+
 __global__ void adam_boundary_kernel(const uint32_t *sk, int64_t M, int dim, int64_t ld, const float *part,
                                      float *param, uint16_t *shadow, float *mom, float *var, AdamConst c) {
     adam_boundary_body(blockIdx.x, sk, M, dim, ld, part, param, shadow, mom, var, c);
@@ -892,6 +989,7 @@ static AdamConst adam_const(const kge_adam_cfg_t &cfg) {
 int kge_run_sparse_adam_apply_tables(const kge_adam_table_t *tb, int n, const kge_adam_cfg_t &cfg, hipStream_t st) {
     AdamTables T = {};
     int pieces = 0, interior = 0;
+    bool one = true;
     for (int k = 0; k < n; ++k) {
         AdamTable &t = T.t[k];
         void *ws = tb[k].ws;
@@ -902,9 +1000,24 @@ int kge_run_sparse_adam_apply_tables(const kge_adam_table_t *tb, int n, const kg
         const int64_t nchunk = (tb[k].M + SEG_CHUNK - 1) / SEG_CHUNK;
         t.M = tb[k].M; t.grads = tb[k].grads; t.dim = tb[k].dim; t.ld = tb[k].ld; t.param = tb[k].param_f32;
         t.shadow = (uint16_t *)tb[k].param_bf16; t.mom = tb[k].m; t.var = tb[k].v; t.part = s.part;
+        one = one && t.M <= ADAM_ONE_M;
         t.piece_blocks = nchunk > 1 ? (int)((nchunk + 3) / 4) : 0;
         t.interior_blocks = (int)((tb[k].M + 3) / 4);
         pieces += t.piece_blocks; interior += t.interior_blocks;
+    }
+    if (one) {
+        pieces = interior = 0;
+        for (int k = 0; k < n; ++k) {
+            AdamTable &t = T.t[k];
+            t.interior_blocks = (int)((t.M + ADAM_ONE_NT / 64 - 1) / (ADAM_ONE_NT / 64));
+            interior += t.interior_blocks;
+            const int nchunk = (int)((t.M + SEG_CHUNK - 1) / SEG_CHUNK);
+            t.piece_blocks = nchunk > 1 ? (nchunk - 1) * ((t.dim + ADAM_ONE_COLS - 1) / ADAM_ONE_COLS) : 0;   // (nothing starts in the last chunk)
+            pieces += t.piece_blocks;
+        }
+        KgeProfScope prof(KGE_PROF_ADAM, st);
+        hipLaunchKernelGGL(adam_one_tables_kernel, dim3(pieces + interior), dim3(ADAM_ONE_NT), 0, st, T, adam_const(cfg));
+        return kge_launch_status();
     }
     const AdamConst c = adam_const(cfg);
     KgeProfScope prof(KGE_PROF_ADAM, st);

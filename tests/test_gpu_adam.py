@@ -313,6 +313,36 @@ def test_several_tables_in_one_call_give_the_bits_of_one_call_per_table():
 
 
 @pytest.mark.parametrize("shapes", [
+    [(50000, 256, 4096, "zipf"), (12, 128, 1100, "zipf"), (7, 64, 33, "same")],   # the longest short table; runs of dozens of rows
+    [(3, 512, 4096, "same"), (5000, 4, 32, "zipf")],                              # one run over every chunk; no chunk boundary
+    [(40, 500, 2049, "runs"), (9, 8, 31, "same"), (300, 260, 65, "runs"), (2, 64, 64, "same")],   # runs that start and end at boundaries
+    [(50000, 64, 4097, "zipf"), (100, 64, 300, "zipf")],                          # one id too many: two launches
+    [(5000, 516, 300, "zipf")]])                                                  # a row too wide
+def test_short_tables_in_one_launch_give_the_bits_of_two(shapes):
+    """kge_sparse_adam_apply_tables on short tables (one launch) against kge_sparse_adam_apply table by table (two)."""
+    import paper_2211_12281_amd as kge
+    dev = lambda a: torch.from_numpy(a.copy()).cuda()
+    tables, refs = [], []
+    for k, (n_rows, d, M, how) in enumerate(shapes):
+        theta, m, v = _state(n_rows, d, 60 + k, True)
+        g = np.random.default_rng(160 + k)
+        idx = {"zipf": lambda: ks.ZipfIds(n_rows, 1.1).draw(g, M), "same": lambda: np.full(M, 1, np.int32),
+               "runs": lambda: (np.arange(M) // 32 % n_rows).astype(np.int32)}[how]()
+        grads, idx, sh = dev((g.normal(size=(M, d)) * 1e-2).astype(F)), dev(idx), torch.zeros((n_rows, d), dtype=torch.bfloat16, device="cuda")
+        ws = kge.Workspace()
+        kge.sparse_adam_plan(n_rows, d, idx, ws)
+        ref = [dev(theta), sh.clone(), dev(m), dev(v)]
+        kge.sparse_adam_apply(*ref, grads, ws, 2e-3, step=7)
+        refs.append(ref)
+        tables.append((dev(theta), sh, dev(m), dev(v), grads, ws))
+    kge.sparse_adam_apply_tables(tables, 2e-3, step=7)
+    torch.cuda.synchronize()
+    for ref, got in zip(refs, tables):
+        for a, c in zip(ref, got):
+            assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a, c.view(torch.int16) if c.dtype == torch.bfloat16 else c)
+
+
+@pytest.mark.parametrize("shapes", [
     [(10_000_000, 64, 24576, "zipf"), (1000, 64, 9000, "same"), (200, 64, 4096, "zipf"), (77, 64, 0, "zipf")],
     [(10_000_000, 64, 24576, "zipf"), (1000, 64, 4096, "zipf")],          # entities and relations of a training step
     [(200, 64, 4096, "zipf"), (10_000_000, 64, 24576, "zipf"), (1000, 64, 100, "zipf"), (5000, 64, 8193, "zipf")],
