@@ -151,13 +151,16 @@ def _check(code: int, what: str):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()             # (an int: every argument it is passed for is declared c_void_p)
 
 
 def _stream(stream=None):
     """The HIP stream of a call: torch's current one, or the given torch.cuda.Stream (saves the lookup and the
     stream context around the call)."""
-    return C.c_void_p((stream if stream is not None else torch.cuda.current_stream()).cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    # (torch.cuda.current_stream().cuda_stream without the Stream object: 0.3 us instead of 2.7)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _i32(t):
@@ -362,28 +365,30 @@ def sparse_adam_plan_tables(plans, stream=None):
 
 
 def _plan_array(plans):
-    arr = (KgeAdamPlanT * len(plans))()
-    for a, (n_rows, dim, idx, ws) in zip(arr, plans):
+    rows = []
+    for n_rows, dim, idx, ws in plans:
         M = idx.numel()
         buf = ws.get(workspace_bytes(OP_SPARSE_ADAM, None, M, dim))
-        a.n_rows, a.dim, a.idx, a.M, a.ws, a.ws_bytes = n_rows, dim, _ptr(_i32(idx)), M, _ptr(buf), buf.numel()
-    return arr
+        rows.append((n_rows, dim, _i32(idx).data_ptr(), M, buf.data_ptr(), buf.numel()))
+    return (KgeAdamPlanT * len(rows))(*rows)
 
 
 def sparse_adam_apply_tables(tables, lr: float, beta1: float = 0.9, beta2: float = 0.999, eps: float = 1e-8, step: int = 1,
                              stream=None, step_counter=None):
     """kge_sparse_adam_apply_tables: tables = [(param, shadow, m, v, grads, ws), ...], each planned into its own ws."""
-    arr = (KgeAdamTableT * len(tables))()
-    for a, (param, shadow, m, v, grads, ws) in zip(arr, tables):
+    rows = []
+    for param, shadow, m, v, grads, ws in tables:
         assert param.dtype == torch.float32 and m.dtype == torch.float32 and v.dtype == torch.float32
         assert grads.dtype == torch.float32 and grads.is_contiguous() and param.stride(1) == 1
-        assert m.stride() == param.stride() and v.stride() == param.stride()
+        strides = param.stride()
+        assert m.stride() == strides and v.stride() == strides
         if shadow is not None:
-            assert shadow.dtype == torch.bfloat16 and shadow.stride() == param.stride()
-        M, d = grads.shape[0], param.shape[1]
+            assert shadow.dtype == torch.bfloat16 and shadow.stride() == strides
+        (n_rows, d), M = param.shape, grads.shape[0]
         buf = ws.get(workspace_bytes(OP_SPARSE_ADAM, None, M, d))
-        a.param_f32, a.param_bf16, a.m, a.v = _ptr(param), _ptr(shadow), _ptr(m), _ptr(v)
-        a.n_rows, a.dim, a.ld, a.grads, a.M, a.ws, a.ws_bytes = param.shape[0], d, param.stride(0), _ptr(grads), M, _ptr(buf), buf.numel()
+        rows.append((param.data_ptr(), _ptr(shadow), m.data_ptr(), v.data_ptr(), n_rows, d, strides[0], grads.data_ptr(), M,
+                     buf.data_ptr(), buf.numel()))
+    arr = (KgeAdamTableT * len(rows))(*rows)
     cfg = KgeAdamCfgT(lr, beta1, beta2, eps, step, _counter(step_counter))
     _check(load().kge_sparse_adam_apply_tables(arr, len(tables), C.byref(cfg), _stream(stream)), "kge_sparse_adam_apply_tables")
 

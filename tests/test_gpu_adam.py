@@ -313,11 +313,11 @@ def test_several_tables_in_one_call_give_the_bits_of_one_call_per_table():
 
 
 @pytest.mark.parametrize("shapes", [
-    [(50000, 256, 4096, "zipf"), (12, 128, 1100, "zipf"), (7, 64, 33, "same")],   # the longest short table; runs of dozens of rows
-    [(3, 512, 4096, "same"), (5000, 4, 32, "zipf")],                              # one run over every chunk; no chunk boundary
-    [(40, 500, 2049, "runs"), (9, 8, 31, "same"), (300, 260, 65, "runs"), (2, 64, 64, "same")],   # runs that start and end at boundaries
-    [(50000, 64, 4097, "zipf"), (100, 64, 300, "zipf")],                          # one id too many: two launches
-    [(5000, 516, 300, "zipf")]])                                                  # a row too wide
+    [(50000, 256, 2048, "zipf"), (12, 128, 1100, "zipf"), (7, 64, 33, "same")],   # the longest short table; runs of dozens of rows
+    [(3, 512, 2048, "same"), (5000, 4, 32, "zipf")],                              # one run over every chunk; no chunk boundary
+    [(40, 500, 2017, "runs"), (9, 8, 31, "same"), (300, 260, 65, "runs"), (2, 64, 64, "same")],   # runs that start and end at boundaries
+    [(50000, 64, 2049, "zipf"), (100, 64, 300, "zipf")],                          # one id too many: two launches
+    [(5000, 516, 300, "zipf")]])                                                  # columns past eight slices
 def test_short_tables_in_one_launch_give_the_bits_of_two(shapes):
     """kge_sparse_adam_apply_tables on short tables (one launch) against kge_sparse_adam_apply table by table (two)."""
     import paper_2211_12281_amd as kge
