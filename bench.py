@@ -340,7 +340,8 @@ class TrainWorkload:
         # accumulate |.| for the scores, select by the sign and accumulate for a gradient pass
         # TransH: x = q' - t + A w^ costs two, and the kernels carry A (one, scores), P (one, scores), the gradient of
         # w^ (two, pass over the queries) or the hyperplane term of dt (one, pass over the negatives) besides
-        per = 2.0
+        # (TransE, RotatE: both gradient passes are one launch, in the slot block_fwd)
+        per = 4.0 if slot == "block_fwd" else 2.0
         if self.scorer == "transh":
             per = {"block_score": 5.0, "block_fwd": 5.0, "block_gradt": 4.0}.get(slot, 5.0)
         return per * self.B * self.N * self.d

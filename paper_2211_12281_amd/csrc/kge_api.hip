@@ -587,8 +587,8 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
                                    cfg->loss, cfg->gamma, cfg->adv_temp, g.nsplit_t, b.acct, nullptr, st, g.pn)) != KGE_OK) return rc;
     } else if (have_block && g.l1) {
         // gradient rows of the queries and of the shared negatives from the pairs' weights, which the row pass left in S
-        if ((rc = kge_run_l1_grad(g.bf16, true, b.Q32, b.T, b.S, g.Np, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, g.nsplit_q, b.accq, st)) != KGE_OK) return rc;
-        if ((rc = kge_run_l1_grad(g.bf16, false, b.T, b.Q32, b.S, g.Np, g.B, g.N, g.Np, g.Bp, g.dp, model->dim, g.nsplit_t, b.acct, st)) != KGE_OK) return rc;
+        if ((rc = kge_run_l1_grad(g.bf16, b.Q32, b.T, b.S, g.Np, g.B, g.N, g.Bp, g.Np, g.dp, model->dim, g.nsplit_q, g.nsplit_t, b.accq,
+                                  b.acct, st)) != KGE_OK) return rc;
     } else if (have_block) {
         // pass 2 (column owner): gradient of the shared negatives from the finished row constants
         KgeBlockArgs c = a;

@@ -8,8 +8,8 @@
 // with w(b, n) = dL/dS[b, n] from S and the finished row constants; sign(0) = 0 (sub-gradient at the kink).
 // The queries are read from an unrounded fp32 copy also when the tables are bf16 (a sign flips when rounding moves a
 // difference across zero; the table rows themselves are exact).  The block kernels stage fp32 tiles in the LDS (row pitch 68 floats: the
-// 16 lanes that read 16 different rows at one column offset hit 16 different 16-byte bank groups): the scores 64 x 64 or 32 x 64 with a
-// 4 x 4 or 2 x 4 register tile per thread, the gradients 32 streamed rows x 64 columns against an 8 x 4 register tile; they are bound by the vector pipe in large blocks and by the latency of a chunk (loads, barrier) in small ones, so the loads of
+// 16 lanes that read 16 different rows at one column offset hit 16 different 16-byte bank groups): the scores 64 x 64, 32 x 64 or 32 x 48
+// with a 4 x 4, 2 x 4 or 2 x 3 register tile per thread, the gradients 32 streamed rows x 64 columns against an 8 x 4 register tile; they are bound by the vector pipe in large blocks and by the latency of a chunk (loads, barrier) in small ones, so the loads of
 // the next chunk are issued before the present one is used (gradient passes 44 -> 24 us each at 512 x 1,280 x 384).
 #include "row_ops.hpp"
 
@@ -26,12 +26,12 @@ typedef float l1_f32x4 __attribute__((ext_vector_type(4)));
 // the loads of the next tile are issued before this one is used
 template <int R> struct L1TileR { uint32_t w[R / 16][4]; };      // R rows
 using L1Tile = L1TileR<L1_TILE>;
-template <bool BF16, int R>
-__device__ __forceinline__ void l1_fetch(const void *src, int64_t ld, int r0, int c0, L1TileR<R> &t) {
+template <bool BF16, int R>                                       // (rows: of the array; a tile may reach past them)
+__device__ __forceinline__ void l1_fetch(const void *src, int64_t ld, int r0, int c0, L1TileR<R> &t, int rows = 0x7fffffff) {
 #pragma unroll
     for (int k = 0; k < R / 16; ++k) {
         const int e = threadIdx.x + 256 * k, row = e >> 4, cq = e & 15;
-        const int64_t off = (int64_t)(r0 + row) * ld + c0 + 4 * cq;
+        const int64_t off = (int64_t)min(r0 + row, rows - 1) * ld + c0 + 4 * cq;
         if constexpr (BF16) {
             const uint2 raw = *(const uint2 *)((const __bf16 *)src + off);
             t.w[k][0] = raw.x; t.w[k][1] = raw.y;
@@ -61,20 +61,20 @@ __device__ __forceinline__ void l1_stage(const void *src, int64_t ld, int r0, in
     l1_put<BF16>(t, tile);
 }
 
-// S[b, n] = -sum_j |q_bj - t_nj|; workgroup = 16 QR queries x 64 negatives, thread = queries QR ty + i, negatives tx + 16 k
-template <bool BF16, int QR>
-__global__ __launch_bounds__(256) void l1_score_kernel(const float *Q, const void *T, int B, int N, int dp, int cols, float *S, int64_t ldS) {
-    __shared__ __attribute__((aligned(16))) float qs[16 * QR * L1_PITCH], ts[L1_TILE * L1_PITCH];
+// S[b, n] = -sum_j |q_bj - t_nj|; workgroup = 16 QR queries x 16 KN negatives, thread = queries QR ty + i, negatives tx + 16 k
+template <bool BF16, int QR, int KN>
+__global__ __launch_bounds__(256) void l1_score_kernel(const float *Q, const void *T, int B, int N, int Np, int dp, int cols, float *S, int64_t ldS) {
+    __shared__ __attribute__((aligned(16))) float qs[16 * QR * L1_PITCH], ts[16 * KN * L1_PITCH];
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int n0 = blockIdx.x * L1_TILE, b0 = blockIdx.y * 16 * QR;
-    float acc[QR][4];
+    const int n0 = blockIdx.x * 16 * KN, b0 = blockIdx.y * 16 * QR;
+    float acc[QR][KN];
 #pragma unroll
     for (int i = 0; i < QR; ++i)
-        for (int k = 0; k < 4; ++k) acc[i][k] = 0.f;
+        for (int k = 0; k < KN; ++k) acc[i][k] = 0.f;
     L1TileR<16 * QR> tq;
-    L1Tile tt;
+    L1TileR<16 * KN> tt;
     l1_fetch<false>(Q, dp, b0, 0, tq);
-    l1_fetch<BF16>(T, dp, n0, 0, tt);
+    l1_fetch<BF16>(T, dp, n0, 0, tt, Np);
     for (int j0 = 0; j0 < cols; j0 += L1_TILE) {
         __syncthreads();
         l1_put<false>(tq, qs);
@@ -82,19 +82,19 @@ __global__ __launch_bounds__(256) void l1_score_kernel(const float *Q, const voi
         __syncthreads();
         if (j0 + L1_TILE < cols) {
             l1_fetch<false>(Q, dp, b0, j0 + L1_TILE, tq);
-            l1_fetch<BF16>(T, dp, n0, j0 + L1_TILE, tt);
+            l1_fetch<BF16>(T, dp, n0, j0 + L1_TILE, tt, Np);
         }
 #pragma unroll 4
         for (int jq = 0; jq < 16; ++jq) {
-            l1_f32x4 q4[QR], t4[4];
+            l1_f32x4 q4[QR], t4[KN];
 #pragma unroll
             for (int i = 0; i < QR; ++i) q4[i] = *(const l1_f32x4 *)(qs + (QR * ty + i) * L1_PITCH + 4 * jq);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) t4[i] = *(const l1_f32x4 *)(ts + (tx + 16 * i) * L1_PITCH + 4 * jq);
+            for (int i = 0; i < KN; ++i) t4[i] = *(const l1_f32x4 *)(ts + (tx + 16 * i) * L1_PITCH + 4 * jq);
 #pragma unroll
             for (int i = 0; i < QR; ++i)
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
+                for (int k = 0; k < KN; ++k)
 #pragma unroll
                     for (int c = 0; c < 4; ++c) acc[i][k] += fabsf(q4[i][c] - t4[k][c]);
         }
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void l1_score_kernel(const float *Q, const voi
     for (int i = 0; i < QR; ++i) {
         const int b = b0 + QR * ty + i;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < KN; ++k) {
             const int n = n0 + tx + 16 * k;
             if (b < B && n < N) S[(int64_t)b * ldS + n] = -acc[i][k];
         }
@@ -128,13 +128,17 @@ __device__ __forceinline__ float l1_sigmoid(float y) {
 constexpr int L1_GO = 128, L1_GD = 64, L1_GS = 32;   // own rows, dimensions, streamed rows per chunk of a gradient workgroup
 constexpr int L1_WP = 132;                            // floats per LDS row of the weights (16 lanes x 16 bytes stay conflict-free)
 
+struct L1GradPart { const void *own, *str; float *acc_part; int own_pad, own_tiles, col_tiles, chunks, cps; };
+
 template <bool BF16, bool OWN_Q>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void l1_grad_kernel(
-        const void *own, const void *str, const float *W, int64_t ldW, int B, int N, int own_pad, int dp, int chunks, int cps, float *acc_part) {
-    __shared__ __attribute__((aligned(16))) float ss[L1_GS * L1_PITCH], ws[L1_GS * L1_WP];
+__device__ __forceinline__ void l1_grad_body(const L1GradPart &p, int blk, const float *W, int64_t ldW, int B, int N, int dp, float *ss, float *ws) {
+    const void *own = p.own, *str = p.str;
+    const int own_pad = p.own_pad, chunks = p.chunks, cps = p.cps;
+    float *acc_part = p.acc_part;
     constexpr bool SBF = BF16 && OWN_Q, OBF = BF16 && !OWN_Q;   // table type of the streamed / own operand
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int o0 = blockIdx.x * L1_GO, j0 = blockIdx.y * L1_GD, split = blockIdx.z;
+    const int rest = blk / p.own_tiles, split = rest / p.col_tiles;
+    const int o0 = (blk - rest * p.own_tiles) * L1_GO, j0 = (rest - split * p.col_tiles) * L1_GD;
     float ov[8][4], acc[8][4];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -210,6 +214,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     for (int i = 0; i < 8; ++i)
         *(l1_f32x4 *)(acc_part + ((int64_t)split * own_pad + o0 + 4 * ty + (i & 3) + 64 * (i >> 2)) * dp + j0 + 4 * tx) =
             l1_f32x4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+}
+
+// Both passes in ONE launch, the queries' workgroups first: they need nothing of one another, and each alone leaves a last round of
+// workgroups that covers a part of the chip (512 x 1,280 x 384: 24.7 + 23.6 -> 44 us;  whole calls, us: TransE bf16 4,000 x 300 x 64 76 -> 60,
+// fp32 512 x 1,280 x 128 57 -> 48, bf16 4,096 x 4,096 x 256 726 -> 686).
+template <bool BF16>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void l1_grad_kernel(
+        const L1GradPart q, const L1GradPart t, const int q_blocks, const float *W, int64_t ldW, int B, int N, int dp) {
+    __shared__ __attribute__((aligned(16))) float ss[L1_GS * L1_PITCH], ws[L1_GS * L1_WP];
+    if ((int)blockIdx.x < q_blocks) l1_grad_body<BF16, true>(q, (int)blockIdx.x, W, ldW, B, N, dp, ss, ws);
+    else l1_grad_body<BF16, false>(t, (int)blockIdx.x - q_blocks, W, ldW, B, N, dp, ss, ws);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -417,14 +432,18 @@ int kge_run_l1_score(bool bf16, const float *Q, const void *T, int B, int N, int
     if (Bp / L1_TILE > 65535) return KGE_E_UNSUPPORTED;   // grid limit of the second dimension
     KgeProfScope prof(KGE_PROF_BLOCK_SCORE, st);
     // (rows past B and N and columns past the dimension are padding: no workgroup takes a tile of them alone)
-    const int cols = (dim + L1_TILE - 1) / L1_TILE * L1_TILE, nt = (N + L1_TILE - 1) / L1_TILE;
+    const int cols = (dim + L1_TILE - 1) / L1_TILE * L1_TILE;
+    auto tiles = [&](int qr, int kn) { return (int64_t)((N + 16 * kn - 1) / (16 * kn)) * ((B + 16 * qr - 1) / (16 * qr)); };
     // 64 x 64 tiles feed eight operations from every LDS read; 32 queries per tile where the others would not fill the chip twice
-    // (512 x 1,280 x 384: 22 us against 31)
-    const bool half = (int64_t)nt * ((B + 63) / 64) < 512;
-    const dim3 grid(nt, half ? (B + 31) / 32 : (B + 63) / 64);
-#define L1_SCORE(BF, QR) hipLaunchKernelGGL((l1_score_kernel<BF, QR>), grid, dim3(256), 0, st, Q, T, B, N, dp, cols, S, ldS)
-    if (bf16) { if (half) L1_SCORE(true, 2); else L1_SCORE(true, 4); }
-    else      { if (half) L1_SCORE(false, 2); else L1_SCORE(false, 4); }
+    // (512 x 1,280 x 384: 22 us against 31), and there 48 negatives or 64, whichever leaves the fullest compute unit less to do
+    // (512 x 1,280 x 384: 432 workgroups of 48, 18.7 us; 320 of 64, 21.5)
+    const bool half = tiles(4, 4) < 512;
+    auto load = [&](int kn) { return (tiles(2, kn) + 255) / 256 * kn; };
+    const int kn = !half || load(4) <= load(3) ? 4 : 3;
+    const dim3 grid((N + 16 * kn - 1) / (16 * kn), half ? (B + 31) / 32 : (B + 63) / 64);
+#define L1_SCORE(BF, QR, KN) hipLaunchKernelGGL((l1_score_kernel<BF, QR, KN>), grid, dim3(256), 0, st, Q, T, B, N, Np, dp, cols, S, ldS)
+    if (bf16) { if (!half) L1_SCORE(true, 4, 4); else if (kn == 4) L1_SCORE(true, 2, 4); else L1_SCORE(true, 2, 3); }
+    else      { if (!half) L1_SCORE(false, 4, 4); else if (kn == 4) L1_SCORE(false, 2, 4); else L1_SCORE(false, 2, 3); }
 #undef L1_SCORE
     return kge_launch_status();
 }
@@ -444,19 +463,22 @@ size_t kge_l1_most_part(int own_pad, int str_pad, int dp, bool transh) {
     return go * (split < whole ? split : whole);
 }
 
-int kge_run_l1_grad(bool bf16, bool own_is_query, const void *own, const void *str, const float *W, int64_t ldW, int B, int N, int own_pad,
-                    int str_pad, int dp, int dim, int nsplit, float *acc_part, hipStream_t st) {
-    if (own_pad % L1_GO || str_pad % L1_GS || dp % L1_GD) return KGE_E_INVALID_ARG;
-    if (nsplit <= 0 || nsplit != kge_l1_nsplit(own_pad, str_pad, dp, false)) return KGE_E_INVALID_ARG;
-    KgeProfScope prof(own_is_query ? KGE_PROF_BLOCK_FWD : KGE_PROF_BLOCK_GRADT, st);
-    // (the split count is that of the padded block, its work that of the rows and columns there are; a split past them writes zeros)
-    const int own_n = own_is_query ? B : N, str_n = own_is_query ? N : B;
-    const int chunks = (str_n + L1_GS - 1) / L1_GS, cps = (chunks + nsplit - 1) / nsplit;
-    const dim3 grid((own_n + L1_GO - 1) / L1_GO, (dim + L1_GD - 1) / L1_GD, nsplit);
-#define L1_GRAD(BF, OQ) hipLaunchKernelGGL((l1_grad_kernel<BF, OQ>), grid, dim3(256), 0, st, own, str, W, ldW, B, N, own_pad, dp, chunks, cps, acc_part)
-    if (bf16) { if (own_is_query) L1_GRAD(true, true); else L1_GRAD(true, false); }
-    else      { if (own_is_query) L1_GRAD(false, true); else L1_GRAD(false, false); }
-#undef L1_GRAD
+int kge_run_l1_grad(bool bf16, const float *Q, const void *T, const float *W, int64_t ldW, int B, int N, int Bp, int Np, int dp, int dim,
+                    int nsplit_q, int nsplit_t, float *accq, float *acct, hipStream_t st) {
+    if (Bp % L1_GO || Np % L1_GO || Bp % L1_GS || Np % L1_GS || dp % L1_GD) return KGE_E_INVALID_ARG;
+    if (nsplit_q <= 0 || nsplit_t <= 0 || nsplit_q != kge_l1_nsplit(Bp, Np, dp, false) || nsplit_t != kge_l1_nsplit(Np, Bp, dp, false))
+        return KGE_E_INVALID_ARG;
+    KgeProfScope prof(KGE_PROF_BLOCK_FWD, st);
+    // (the split counts are those of the padded block, their work that of the rows and columns there are; a split past them writes zeros)
+    auto part = [&](const void *own, const void *str, float *acc, int own_pad, int own_n, int str_n, int nsplit) {
+        const int chunks = (str_n + L1_GS - 1) / L1_GS;
+        return L1GradPart{own, str, acc, own_pad, (own_n + L1_GO - 1) / L1_GO, (dim + L1_GD - 1) / L1_GD, chunks, (chunks + nsplit - 1) / nsplit};
+    };
+    const L1GradPart q = part(Q, T, accq, Bp, B, N, nsplit_q), t = part(T, Q, acct, Np, N, B, nsplit_t);
+    const int64_t qb = (int64_t)q.own_tiles * q.col_tiles * nsplit_q, tb = (int64_t)t.own_tiles * t.col_tiles * nsplit_t;
+    if (qb + tb > 0x7fffffff) return KGE_E_UNSUPPORTED;
+    if (bf16) hipLaunchKernelGGL(l1_grad_kernel<true>, dim3((unsigned)(qb + tb)), dim3(256), 0, st, q, t, (int)qb, W, ldW, B, N, dp);
+    else      hipLaunchKernelGGL(l1_grad_kernel<false>, dim3((unsigned)(qb + tb)), dim3(256), 0, st, q, t, (int)qb, W, ldW, B, N, dp);
     return kge_launch_status();
 }
 

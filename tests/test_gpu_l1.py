@@ -116,6 +116,8 @@ def test_other_row_sizes_and_shapes(orc, dim, bf16):
 @pytest.mark.parametrize("dim,bf16,B,N", [
     (72, False, 1440, 1473), (64, True, 1408, 1472),     # score tiles of 64 queries (the sizes above take tiles of 32) and the last of the others
     (136, False, 257, 1300),                             # columns past the row in its last tile; rows past the block in its last tiles
+    (48, True, 33, 256), (64, False, 97, 511),           # tiles of 48 negatives whose last reaches past the padded rows
+    (64, False, 480, 1024),                              # 330 workgroups of 48 negatives against 240 of 64: the tile of 64 has less to do
     (32, True, 1024, 40), (32, True, 1025, 40)])         # four waves per row in the chain rule, and one
 def test_tiles_and_their_edges(orc, dim, bf16, B, N):
     G = _grid_case("transe", 3000, 9, dim, B, N, False)
