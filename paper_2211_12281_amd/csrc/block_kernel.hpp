@@ -69,12 +69,11 @@ __device__ __forceinline__ uint32_t kge_pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
-// fp32 operands on the bf16 matrix pipe.  The fp32 MFMA of gfx950 runs at 1/16 of the bf16 rate, so the fp32 passes
-// whose registers allow it (KgeBlockCfg::X3) split every operand value into THREE bf16 pieces, x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0),
-// x2 = bf16(x - x0 - x1) (round to nearest; 8 significand bits each, |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|; the bf16
-// exponent range is that of fp32, so no scaling is needed), and accumulate the six products of total order <= 2 in
-// fp32: a.b = a0 b0 + a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0 + O(2^-26 |a| |b|).  Six 32x32x16 bf16 MFMAs (192 cycles)
-// replace the eight 32x32x2 fp32 ones (512 cycles) of sixteen k-steps.
+// fp32 operands on the bf16 matrix pipe, for the small blocks (block_small.hip), whose operands come straight from fp32 rows and
+// coefficients: the fp32 MFMA of gfx950 runs at 1/16 of the bf16 rate, so every operand value is split into THREE bf16 pieces,
+// x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1) (round to nearest; 8 significand bits each,
+// |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|; the bf16 exponent range is that of fp32, so nothing is scaled), and the six products of total
+// order <= 2 are accumulated in fp32: a.b = a0 b0 + a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0 + O(2^-26 |a| |b|).
 // Eight values of a lane (two 16-byte fragments: slot j of lane half g of both operands is one contraction index,
 // whatever its number) become three bf16 fragments.
 struct KgeP3 { uint4 p[3]; };
@@ -108,6 +107,27 @@ __device__ __forceinline__ kge_f32x16 kge_mma3(kge_f32x16 acc, const KgeP3 &A, c
     acc = mm(acc, A.p[1], B.p[0]);
     acc = mm(acc, A.p[0], B.p[0]);
     return acc;
+}
+
+// Two fp16 pieces of a value scaled by a power of two (kge_plane_scale: rows; coefficients below): x = x0 + x1 to 2^-23 of the largest
+// value that shares the scale, three products per pair, a0 b0 + a0 b1 + a1 b0 (a1 b1 <= 2^-24 |a| |b| is left out).
+struct KgeP2 { uint4 p[2]; };
+typedef _Float16 kge_f16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ KgeP2 kge_split2(const float (&x)[8]) {
+    kge_f16x8 h, l;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { h[i] = (_Float16)x[i]; l[i] = (_Float16)(x[i] - (float)h[i]); }
+    KgeP2 r;
+    r.p[0] = __builtin_bit_cast(uint4, h); r.p[1] = __builtin_bit_cast(uint4, l);
+    return r;
+}
+__device__ __forceinline__ kge_f32x16 kge_mma2(kge_f32x16 acc, const KgeP2 &A, const KgeP2 &B) {
+    auto mm = [](kge_f32x16 c, uint4 x, uint4 y) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(kge_f16x8, x), __builtin_bit_cast(kge_f16x8, y), c, 0, 0, 0);
+    };
+    acc = mm(acc, A.p[0], B.p[1]);
+    acc = mm(acc, A.p[1], B.p[0]);
+    return mm(acc, A.p[0], B.p[0]);
 }
 
 // Asynchronous global -> LDS copies: lane l of a wave-wide instruction writes its 16 (4) bytes to LDS
@@ -153,27 +173,6 @@ __device__ __noinline__ float kge_direct_d2(const void *qv, const void *tv, cons
     return kge_direct_d2_inline<BF16, TRANSH>(qv, tv, wv, dp);
 }
 
-// the same for operands that are bf16 planes of rows of dp elements (their three pieces add up to the fp32 value), plane strides in bytes
-template <bool TRANSH>
-__device__ __forceinline__ float kge_direct_d2_planes(const char *qv, int64_t qplane, const char *tv, int64_t tplane, const char *wv, int64_t wplane, int dp) {
-    auto val = [](const char *r, int64_t plane, int j) {
-        const __bf16 *x = (const __bf16 *)r;
-        return ((float)x[j] + (float)x[j + plane / 2]) + (float)x[j + plane];
-    };
-    float A = 0.f;
-    if constexpr (TRANSH)
-#pragma unroll 1
-        for (int j = 0; j < dp; ++j) A += val(wv, wplane, j) * val(tv, tplane, j);
-    float acc = 0.f;
-#pragma unroll 1
-    for (int j = 0; j < dp; ++j) {
-        float x = val(qv, qplane, j) - val(tv, tplane, j);
-        if constexpr (TRANSH) x += A * val(wv, wplane, j);
-        acc += x * x;
-    }
-    return acc;
-}
-
 template <bool BF16, int RB, int MODE, bool TRANSH, int KIND, int DSPLIT>
 struct KgeBlockCfg {
     static constexpr bool OWN_ROW = MODE == KGE_MODE_FWD;
@@ -185,11 +184,13 @@ struct KgeBlockCfg {
     static constexpr int ST = KGE_STREAM_TILE;
     static constexpr int NB = DP / 32;                     // 32-column output blocks of phase 2
     static constexpr int NBH = NB / DSPLIT;                // ... handled by one z-slice
-    // PL: the operands come as bf16 planes; a tile is three planes of [ST rows][2 DP bytes], chunk c of row r at c ^ kge_pl_swz(r), and the
+    // PL: the operands come as two fp16 planes; a tile is two planes of [ST rows][2 DP bytes], chunk c of row r at c ^ kge_pl_swz(r), and the
     // transposed fragments of phase 2 are LDS transpose reads of it (ds_read_b64_tr_b16)
     static constexpr bool PL = kge_block_planes(BF16, RB, MODE);
     static constexpr int PLANE = ST * DP * 2;
-    static constexpr int X_BYTES = PL ? 3 * PLANE : ST * RB;    // else [ST rows][RB bytes], chunk c of row r at c ^ (r & 7)
+    // groups of fragments requested together: what the registers hold without scratch
+    static constexpr int PL_CHUNK = TRANSH ? 4 : RB == 512 && OWN_ROW && KIND == KGE_KIND_DIST ? 1 : 2;
+    static constexpr int X_BYTES = PL ? 2 * PLANE : ST * RB;    // else [ST rows][RB bytes], chunk c of row r at c ^ (r & 7)
     static constexpr int XT_ROWB = ST * ES;                // one transposed row: ST stream entries (64 or 128 bytes)
     static constexpr int XT_BYTES = DP * XT_ROWB;
     static constexpr bool HAS_X2 = TRANSH && !OWN_ROW;     // second streamed operand (normals)
@@ -199,15 +200,9 @@ struct KgeBlockCfg {
     static constexpr int SIDE_SLOT = OWN_ROW ? 4 * 256 : 4 * 1024;   // per-wave copies of the tile's side info
     // Workgroups per compute unit (= waves per SIMD): two where a workgroup's registers fit in 256, so that
     // the MFMA, LDS and vector phases of one workgroup run under those of the other.
-    // fp32 training passes that contract bf16 pieces (kge_split3 / kge_mma3): the own operand's pieces take 1.5 times the
-    // registers of its fp32 fragments, which the pass over the queries has only for rows of up to 512 bytes (measured, rows
-    // of 1,024 bytes: pass over the negatives 550 -> 461 us, pass over the queries 589 -> 727 us with 170-320 bytes of
-    // scratch).  The score block of this kernel stays on the fp32 instructions: kge_score on fp32 tables runs
-    // block_f32h2_score.hip, and this one is what that is compared with.
-    static constexpr bool X3 = PL || (!BF16 && MODE == KGE_MODE_GRADT);
     static constexpr int OCC = kge_block_occ(BF16, RB, TRANSH, MODE);
-    // TransH queries as planes: q and w^ together would take 192 registers, and the compiler then reloads a third of them from scratch in
-    // every tile, so the wave's 32 rows of w^ stay in the LDS, laid out like a tile (8,192 x 4,096 x 128: 289 -> 208 us)
+    // TransH queries as planes: q and w^ together would take 128 registers, and the compiler then reloads fifty of them from scratch in
+    // every tile, so the wave's 32 rows of w^ stay in the LDS, laid out like a tile
     static constexpr bool WL = PL && TRANSH && OWN_ROW;
     static constexpr int WL_BYTES = WL ? 4 * X_BYTES : 0;
     static constexpr int LDS_MAX = 160 * 1024 / OCC - WL_BYTES;
@@ -221,12 +216,12 @@ struct KgeBlockCfg {
     static_assert(NSTAGE >= 2, "two stages must fit");
     static_assert(X_BYTES % 4096 == 0 && XT_BYTES % 4096 == 0, "tile copies must divide over four waves");
     static_assert((NSTAGE - 2) * LPW < 64, "vmcnt range");
-    static_assert(!TRANSH || BF16 || PL || MODE == KGE_MODE_SCORE, "TransH trains on bf16 rows, on planes, or on the vector pipe");
+    static_assert(BF16 || PL || MODE == KGE_MODE_SCORE, "fp32 rows are trained on planes (TransH of more than 512 bytes: on the vector pipe)");
     static_assert(OW == 1 || !TRANSH, "two own fragments per wave leave no registers for the TransH operands");
     static_assert(KS % 8 == 0, "phase 1 works in groups of four fragments, split in two halves");
 };
 
-// Position of the 16-byte chunks of a plane row of 256 bytes: sixteen consecutive rows at one chunk index (phase 1) fall into sixteen
+// Position of the 16-byte chunks of a plane row of 256 or 512 bytes: sixteen consecutive rows at one chunk index (phase 1) fall into sixteen
 // different bank groups, and so do four consecutive rows at four neighbouring chunks (the transpose reads of phase 2).
 __device__ __forceinline__ constexpr int kge_pl_swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 typedef short kge_i16x4 __attribute__((ext_vector_type(4)));
@@ -265,9 +260,11 @@ void kge_block_kernel(const KgeBlockArgs a) {
     const int64_t own_plane = (int64_t)a.own_pad * C::DP * 2, str_plane = (int64_t)a.str_tiles * C::ST * C::DP * 2;   // PL: bytes per plane
     uint4 own[OW][PL ? 1 : C::KS];
     uint4 ownw[(TRANSH && OWN_ROW && !PL) ? C::KS : 1];
-    // the own operand as bf16 pieces, sixteen contraction indices per entry
-    constexpr bool X3 = C::X3, WL = C::WL;
-    KgeP3 ownp[X3 ? OW : 1][X3 ? C::KS / 2 : 1];
+    // the own operand as fp16 pieces, sixteen contraction indices per entry
+    constexpr bool WL = C::WL;
+    static_assert(!PL || OW == 1, "");
+    KgeP2 own2p[PL ? C::KS / 2 : 1];
+    float o_inv = 1.f;                                    // PL: 1 / scale of the own row
     float o_qn[OW], o_c[OW], o_wn[OW], o_tn[OW];          // own-side scalars
 #pragma unroll
     for (int h = 0; h < OW; ++h) {
@@ -275,9 +272,10 @@ void kge_block_kernel(const KgeBlockArgs a) {
         if constexpr (PL) {
             const char *p = (const char *)a.own + (size_t)oidx * (C::DP * 2) + g * 16;
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl)
+            for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
-                for (int k2 = 0; k2 < C::KS / 2; ++k2) ownp[h][k2].p[pl] = *(const uint4 *)(p + pl * own_plane + k2 * 32);
+                for (int k2 = 0; k2 < C::KS / 2; ++k2) own2p[k2].p[pl] = *(const uint4 *)(p + pl * own_plane + k2 * 32);
+            o_inv = a.own_inv[oidx];
         } else {
             const char *p = (const char *)a.own + (size_t)oidx * RB + g * 16;
 #pragma unroll
@@ -317,9 +315,13 @@ void kge_block_kernel(const KgeBlockArgs a) {
     // ---- asynchronous staging of one stream tile --------------------------------------------------
     // X tile: instruction jj of this wave covers LDS bytes [(wave*X_IPW + jj) KB, +1 KB) of the tile; the
     // lane's 16 bytes are position (byte % RB)/16 of row byte/RB and must hold source chunk pos ^ (row & 7).
-    // (PL: copy c = wave X_IPW + jj fills rows 4 (c % 8) .. + 3 of plane c / 8; the lane's offset differs by (c % 4) in the swizzle only)
+    // (PL: copy c = wave X_IPW + jj fills the RPC rows from RPC (c % CPP) on of plane c / CPP; the lane's offset differs in the swizzle only)
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const int pl_off = (lane >> 4) * (C::DP * 2) + (((lane & 15) ^ ((lane >> 4) << 2)) * 16);
+    constexpr int RPC = PL ? 1024 / (C::DP * 2) : 1, CPP = PL ? C::PLANE / 1024 : 1;
+    static_assert(!PL || RPC == 4 || RPC == 2, "");
+    const int pl_row = RPC == 4 ? lane >> 4 : lane >> 5;
+    const int pl_off = pl_row * (C::DP * 2) + (((lane & (64 / RPC - 1)) ^ (pl_row << 2)) * 16);
+    auto pl_swz = [](int c) { return (RPC == 4 ? c & 3 : (c & 1) << 3 | ((c >> 1) & 3)) << 4; };       // rest of kge_pl_swz of the copy's rows
     int x_off[PL ? 1 : C::X_IPW];                          // source byte offset inside the tile
 #pragma unroll
     for (int jj = 0; jj < (PL ? 0 : C::X_IPW); ++jj) {
@@ -347,9 +349,9 @@ void kge_block_kernel(const KgeBlockArgs a) {
         const int64_t woff = (int64_t)(own_base + wave_u * 32) * (C::DP * 2);
 #pragma unroll
         for (int c = 0; c < C::X_BYTES / 1024; ++c) {
-            const char *src = (const char *)a.own2 + (c >> 3) * own_plane + woff + (c & 7) * 1024;
+            const char *src = (const char *)a.own2 + (c / CPP) * own_plane + woff + (c % CPP) * 1024;
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(wl0 + c * 1024)),
-                         "v"(pl_off ^ ((c & 3) << 4)), "s"(src) : "memory");
+                         "v"(pl_off ^ pl_swz(c)), "s"(src) : "memory");
         }
     }
     auto issue = [&](int tile, int slot) {
@@ -362,9 +364,9 @@ void kge_block_kernel(const KgeBlockArgs a) {
 #pragma unroll
                 for (int jj = 0; jj < C::X_IPW; ++jj) {
                     const int c = wave_u * C::X_IPW + jj;
-                    const char *src = (const char *)(op ? a.str2 : a.str) + (c >> 3) * str_plane + toff + (c & 7) * 1024;
+                    const char *src = (const char *)(op ? a.str2 : a.str) + (c / CPP) * str_plane + toff + (c % CPP) * 1024;
                     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(sbase + op * C::X_BYTES + c * 1024)),
-                                 "v"(pl_off ^ ((c & 3) << 4)), "s"(src) : "memory");
+                                 "v"(pl_off ^ pl_swz(c)), "s"(src) : "memory");
                 }
         } else {
             const char *src = (const char *)a.str + (size_t)tile * C::ST * RB;
@@ -392,8 +394,12 @@ void kge_block_kernel(const KgeBlockArgs a) {
         }
         // side info of the tile's 32 stream rows, one private copy per wave
         const uint32_t sside = lds0 + C::NSTAGE * C::STAGE_BYTES + (slot % C::SIDE_SLOTS) * C::SIDE_SLOT;
-        if constexpr (OWN_ROW) kge_async_copy4(a.tn + tile * C::ST + lr, __builtin_amdgcn_readfirstlane(sside + wave * 256));
-        else kge_async_copy16(a.rowinfo + tile * C::ST + lr, __builtin_amdgcn_readfirstlane(sside + wave * 1024));
+        // (PL: the second half of the copy are the rows' 1 / scale)
+        if constexpr (OWN_ROW)
+            kge_async_copy4((PL && g ? a.str_inv : a.tn) + tile * C::ST + lr, __builtin_amdgcn_readfirstlane(sside + wave * 256));
+        else
+            kge_async_copy16(PL && g ? (const void *)(a.str_inv + tile * C::ST + 4 * (lr & 7)) : (const void *)(a.rowinfo + tile * C::ST + lr),
+                             __builtin_amdgcn_readfirstlane(sside + wave * 1024));
     };
     // fragment addresses inside a stage: chunk (2 ks + g) of row lr sits at position chunk ^ (lr & 7)
     int frag_off[4];
@@ -402,11 +408,11 @@ void kge_block_kernel(const KgeBlockArgs a) {
     // PL: chunk (2 k2 + g) of row lr of a plane; and the transpose reads: source lane i of a group of sixteen points at row
     // 16 j2 + 8 hh + 4 g + i / 4, columns 32 blk + 16 q16 + 4 (i % 4) .. + 3, and lane l receives column 32 blk + l % 32 of the rows
     // 16 j2 + 8 hh + 4 g .. + 3 - the streamed rows of its coefficients 8 j2 + 4 hh .. + 3
-    int pl_frag[PL ? 8 : 1], pl_tr[2][PL ? C::NB : 1];
+    int pl_frag[PL ? C::KS / 2 : 1], pl_tr[2][PL ? C::NB : 1];
     if constexpr (PL) {
         const int i16 = lane & 15, q16 = (lane >> 4) & 1;
 #pragma unroll
-        for (int k2 = 0; k2 < 8; ++k2) pl_frag[k2] = lr * (C::DP * 2) + ((2 * k2 + g) ^ kge_pl_swz(lr)) * 16;
+        for (int k2 = 0; k2 < C::KS / 2; ++k2) pl_frag[k2] = lr * (C::DP * 2) + ((2 * k2 + g) ^ kge_pl_swz(lr)) * 16;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
@@ -427,10 +433,11 @@ void kge_block_kernel(const KgeBlockArgs a) {
 #pragma unroll
             for (int k2 = 0; k2 < C::KS / 2; ++k2)
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
-                    uint4 &v = ownp[h][k2].p[pl];
+                for (int pl = 0; pl < 2; ++pl) {
+                    uint4 &v = own2p[k2].p[pl];
                     asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
                 }
+            asm volatile("" : "+v"(o_inv));
         } else {
 #pragma unroll
             for (int ks = 0; ks < C::KS; ++ks) {
@@ -440,14 +447,6 @@ void kge_block_kernel(const KgeBlockArgs a) {
             }
         }
         asm volatile("" : "+v"(o_qn[h]), "+v"(o_c[h]), "+v"(o_wn[h]), "+v"(o_tn[h]));
-    }
-
-    // (fp32 rows over 512 bytes: split here; the fp32 fragments are not used again)
-    if constexpr (X3 && !PL) {
-#pragma unroll
-        for (int h = 0; h < OW; ++h)
-#pragma unroll
-            for (int k2 = 0; k2 < C::KS / 2; ++k2) ownp[h][k2] = kge_split3(own[h][2 * k2], own[h][2 * k2 + 1]);
     }
 
     // ---- state of the tile in work (set by the loops below, used by the pieces) -------------------
@@ -466,21 +465,22 @@ void kge_block_kernel(const KgeBlockArgs a) {
     };
     kge_f32x16 acc[OW], accw;                              // phase-1 accumulators: [stream, own]
     uint4 bf[OW][2], bf2[2];                               // bf16 B-operands of phase 2
-    float coefs[(BF16 || X3) ? 1 : 16];                    // fp32 B-operands of phase 2 (OW == 1) ...
-    KgeP3 coefp[2], coefp2[2];                             // ... or their bf16 pieces
+    KgeP2 coef2p[2], coefw2p[2];                           // PL: the fp16 pieces of coefficients times c_scale
+    // PL: the power of two that the own row's coefficients, and with them its accumulated gradient, are multiplied by; 0: none yet
+    float c_scale = 0.f;
 
     // ---- phase 1: acc[h][stream, own] = X_tile . own^t; a fragment read from the LDS feeds all own fragments
     constexpr bool HASW = TRANSH && !OWN_ROW;
     constexpr int G1 = HASW ? 2 : 4, NG1 = C::KS / G1;      // fragments per group, groups
     uint4 av[PL ? 1 : C::KS], aw[HASW && !PL ? C::KS : 1];
-    KgeP3 xp[PL ? C::KS / 2 : 1], xwp[HASW && PL ? C::KS / 2 : 1], owp[WL ? C::KS / 2 : 1];
+    KgeP2 xp[PL ? C::KS / 2 : 1], xwp[HASW && PL ? C::KS / 2 : 1], owp[WL ? C::KS / 2 : 1];
     auto ld1 = [&](const char *stage, int grp) {
         if constexpr (PL) {
 #pragma unroll
             for (int k = 0; k < G1 / 2; ++k) {
                 const int k2 = grp * (G1 / 2) + k;
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
+                for (int pl = 0; pl < 2; ++pl) {
                     xp[k2].p[pl] = *(const uint4 *)(stage + pl_frag[k2] + pl * C::PLANE);
                     if constexpr (WL) owp[k2].p[pl] = *(const uint4 *)(own_w + pl_frag[k2] + pl * C::PLANE);
                     if constexpr (HASW) xwp[k2].p[pl] = *(const uint4 *)(stage + C::X_BYTES + pl_frag[k2] + pl * C::PLANE);
@@ -504,22 +504,17 @@ void kge_block_kernel(const KgeBlockArgs a) {
 #pragma unroll
         for (int k = 0; k < G1; ++k) {
             const int ks = grp * G1 + k;
-            if constexpr (!X3) {
+            if constexpr (PL) {
+                if ((k & 1) == 0) {
+                    acc[0] = kge_mma2(acc[0], xp[ks >> 1], own2p[ks >> 1]);
+                    if constexpr (WL) accw = kge_mma2(accw, xp[ks >> 1], owp[ks >> 1]);
+                    if constexpr (HASW) accw = kge_mma2(accw, xwp[ks >> 1], own2p[ks >> 1]);
+                }
+            } else {
 #pragma unroll
                 for (int h = 0; h < OW; ++h) acc[h] = kge_mma16<BF16>(acc[h], av[ks], own[h][ks]);
                 if constexpr (TRANSH && OWN_ROW) accw = kge_mma16<BF16>(accw, av[ks], ownw[ks]);
                 if constexpr (HASW) accw = kge_mma16<BF16>(accw, aw[ks], own[0][ks]);
-            } else if constexpr (PL) {
-                if ((k & 1) == 0) {
-#pragma unroll
-                    for (int h = 0; h < OW; ++h) acc[h] = kge_mma3(acc[h], xp[ks >> 1], ownp[h][ks >> 1]);
-                    if constexpr (WL) accw = kge_mma3(accw, xp[ks >> 1], owp[ks >> 1]);
-                    if constexpr (HASW) accw = kge_mma3(accw, xwp[ks >> 1], ownp[0][ks >> 1]);
-                }
-            } else if ((k & 1) == 0) {                      // bf16 pieces: two k-steps at a time (G1 is even)
-                const KgeP3 x = kge_split3(av[ks], av[ks + 1]);
-#pragma unroll
-                for (int h = 0; h < OW; ++h) acc[h] = kge_mma3(acc[h], x, ownp[h][ks >> 1]);
             }
         }
     };
@@ -528,12 +523,12 @@ void kge_block_kernel(const KgeBlockArgs a) {
     constexpr int NG2 = PHASE2 ? C::NBH / G2 : 0;
     constexpr int F2 = BF16 ? 2 : 4;                       // 16-byte fragments per block
     uint4 av2[PHASE2 && !PL ? C::NBH : 1][F2], aw2[(PHASE2 && HASW && !PL) ? C::NBH : 1][F2];
-    KgeP3 tp[PL ? C::NBH : 1][2], twp[PL && HASW ? C::NBH : 1][2];
+    KgeP2 tp[PL ? C::NBH : 1][2], twp[PL && HASW ? C::NBH : 1][2];
     auto ld2 = [&](const char *stage, int grp) {
         if constexpr (PL) {
-            auto frag = [&](const char *s, int blk, int j2, KgeP3 &x) {
+            auto frag = [&](const char *s, int blk, int j2, KgeP2 &x) {
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
+                for (int pl = 0; pl < 2; ++pl) {
                     const char *q = s + pl * C::PLANE + j2 * (16 * C::DP * 2);
                     const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((kge_i16x4 __attribute__((address_space(3))) *)(q + pl_tr[0][dblk0 + blk])));
                     const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((kge_i16x4 __attribute__((address_space(3))) *)(q + pl_tr[1][dblk0 + blk])));
@@ -583,35 +578,31 @@ void kge_block_kernel(const KgeBlockArgs a) {
                     if constexpr (TRANSH && OWN_ROW) acc2b[blk] = kge_mma16<true>(acc2b[blk], av2[blk][s2], bf2[s2]);
                     if constexpr (HASW) acc2[0][blk] = kge_mma16<true>(acc2[0][blk], aw2[blk][s2], bf2[s2]);
                 }
-            } else if constexpr (!X3) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const kge_f32x4 fa = __builtin_bit_cast(kge_f32x4, av2[blk][j]);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc2[0][blk] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[r], coefs[4 * j + r], acc2[0][blk], 0, 0, 0);
-                }
-            } else if constexpr (PL) {
-#pragma unroll
-                for (int j2 = 0; j2 < 2; ++j2) {
-                    acc2[0][blk] = kge_mma3(acc2[0][blk], tp[blk][j2], coefp[j2]);
-                    if constexpr (TRANSH && OWN_ROW) acc2b[blk] = kge_mma3(acc2b[blk], tp[blk][j2], coefp2[j2]);
-                    if constexpr (HASW) acc2[0][blk] = kge_mma3(acc2[0][blk], twp[blk][j2], coefp2[j2]);
-                }
             } else {
 #pragma unroll
-                for (int j2 = 0; j2 < 2; ++j2) {            // stream entries 16 j2 .. + 15: fragments 2 j2 and 2 j2 + 1
-                    const KgeP3 x = kge_split3(av2[blk][2 * j2], av2[blk][2 * j2 + 1]);
-                    acc2[0][blk] = kge_mma3(acc2[0][blk], x, coefp[j2]);
+                for (int j2 = 0; j2 < 2; ++j2) {
+                    acc2[0][blk] = kge_mma2(acc2[0][blk], tp[blk][j2], coef2p[j2]);
+                    if constexpr (TRANSH && OWN_ROW) acc2b[blk] = kge_mma2(acc2b[blk], tp[blk][j2], coefw2p[j2]);
+                    if constexpr (HASW) acc2[0][blk] = kge_mma2(acc2[0][blk], twp[blk][j2], coefw2p[j2]);
                 }
             }
         }
     };
     // ---- epilogue: scores / loss weights / gradient coefficients of the tile, element by element ----
+    auto str_inv_of = [&](int sl) { return *(const float *)(side + (OWN_ROW ? 128 : 512) + sl * 4); };     // PL: 1 / scale of a streamed row
     // scores of own fragment h against the tile (SCORE mode stores them), 1/distance, w.t
     auto scores = [&](int h, float (&sv)[16], float (&dv)[16], float (&Av)[16]) {
         const int oidx = oidx0 + 32 * h;
 #pragma unroll
         for (int i = 0; i < 16; ++i) { dv[i] = 0.f; Av[i] = 0.f; }
+        if constexpr (PL) {                                // (exact: powers of two)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float s_inv = str_inv_of(8 * (i >> 2) + 4 * g + (i & 3));
+                acc[0][i] *= o_inv * s_inv;
+                if constexpr (TRANSH) accw[i] *= (OWN_ROW ? s_inv : o_inv) * (1.f / KGE_PLANE_UNIT_SCALE);
+            }
+        }
         if constexpr (KIND == KGE_KIND_MULT) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) sv[i] = acc[h][i];
@@ -636,13 +627,10 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 auto again = [&](int i) {
                     const int sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
                     const int b = OWN_ROW ? oidx : sidx, n = OWN_ROW ? sidx : oidx;
-                    constexpr int ROWB = PL ? C::DP * 2 : RB;
-                    const char *qb = (const char *)(OWN_ROW ? a.own : a.str) + (size_t)b * ROWB;
-                    const char *tb = (const char *)(OWN_ROW ? a.str : a.own) + (size_t)n * ROWB;
-                    const char *wb = TRANSH ? (const char *)(OWN_ROW ? a.own2 : a.str2) + (size_t)b * ROWB : nullptr;
-                    const int64_t qp = OWN_ROW ? own_plane : str_plane, tp = OWN_ROW ? str_plane : own_plane;
-                    if constexpr (PL) return kge_direct_d2_planes<TRANSH>(qb, qp, tb, tp, wb, qp, C::DP);
-                    else if constexpr (BF16) return kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
+                    const char *own = (const char *)(PL ? a.own32 : a.own), *str = (const char *)(PL ? a.str32 : a.str);
+                    const char *qb = (OWN_ROW ? own : str) + (size_t)b * RB, *tb = (OWN_ROW ? str : own) + (size_t)n * RB;
+                    const char *wb = !TRANSH ? nullptr : PL ? (const char *)a.w32 + (size_t)b * RB : (const char *)(OWN_ROW ? a.own2 : a.str2) + (size_t)b * RB;
+                    if constexpr (BF16) return kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
                     else return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
                 };
                 if constexpr (BF16) {
@@ -653,7 +641,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                     }
                 } else {
                     // fp32: a loop over the lane's entries, in line - a call costs its caller-saved registers all through the kernel, where
-                    // the bf16 pieces leave none (bf16 tables have them, and lose 0.5-1.5 % by this form)
+                    // the pieces leave none (bf16 tables have them, and lose 0.5-1.5 % by this form)
                     uint32_t todo = 0;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) todo |= d2[i] < thr[i] ? 1u << i : 0u;
@@ -762,15 +750,42 @@ void kge_block_kernel(const KgeBlockArgs a) {
                                              kge_pack_bf16x2(coef2[8 * s2 + 4], coef2[8 * s2 + 5]),
                                              kge_pack_bf16x2(coef2[8 * s2 + 6], coef2[8 * s2 + 7]));
                 }
-            } else if constexpr (!X3) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) coefs[i] = coef[i];
             } else {
-                auto four = [](const float *c) { return make_uint4(__float_as_uint(c[0]), __float_as_uint(c[1]), __float_as_uint(c[2]), __float_as_uint(c[3])); };
+                // coefficients of the scaled rows; their own scale keeps the own row's largest below 2^14.  It is lowered in a rarely taken
+                // branch when a tile has larger ones (and what the row has accumulated with it), set by the first tile that has any:
+                // to 2^6, so that what is 2^-30 of it is still more than the second piece's last bit.
+                float cm = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float s_inv = str_inv_of(8 * (i >> 2) + 4 * g + (i & 3));
+                    coef[i] *= s_inv;
+                    cm = fmaxf(cm, fabsf(coef[i]));
+                    if constexpr (TRANSH) { coef2[i] *= OWN_ROW ? s_inv : 1.f / KGE_PLANE_UNIT_SCALE; cm = fmaxf(cm, fabsf(coef2[i])); }
+                }
+                cm = fmaxf(cm, __shfl_xor(cm, 32));        // (lanes l and l ^ 32 feed the same row)
+                const bool trip = cm * c_scale > 16384.f || (c_scale == 0.f && cm > 0.f);
+                if (__any(trip)) {
+                    const int e = 133 + 127 - (int)((__float_as_uint(cm) >> 23) & 255u);
+                    const float s_new = trip ? __uint_as_float((uint32_t)(e < 1 ? 1 : e > 254 ? 254 : e) << 23) : c_scale;
+                    const float r = !trip ? 1.f : c_scale > 0.f ? s_new / c_scale : 0.f;
+                    c_scale = s_new;
+#pragma unroll
+                    for (int b = 0; b < C::NBH; ++b) {
+                        for (int i = 0; i < 16; ++i) acc2[0][b][i] *= r;
+                        asm volatile("" ::: "memory");
+                        if constexpr (TRANSH && OWN_ROW) { for (int i = 0; i < 16; ++i) acc2b[b][i] *= r; asm volatile("" ::: "memory"); }
+                    }
+                }
+                auto pieces = [&](const float *c) {
+                    float x[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) x[i] = c[i] * c_scale;
+                    return kge_split2(x);
+                };
 #pragma unroll
                 for (int j2 = 0; j2 < 2; ++j2) {
-                    coefp[j2] = kge_split3(four(coef + 8 * j2), four(coef + 8 * j2 + 4));
-                    if constexpr (TRANSH) coefp2[j2] = kge_split3(four(coef2 + 8 * j2), four(coef2 + 8 * j2 + 4));
+                    coef2p[j2] = pieces(coef + 8 * j2);
+                    if constexpr (TRANSH) coefw2p[j2] = pieces(coef2 + 8 * j2);
                 }
             }
         }
@@ -821,7 +836,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
         // allow it).  Deeper software pipelining of the reads, enforced with scheduling barriers, was
         // measured and did not pay: inside a chunk the order is left to the compiler.
         zero1();
-        constexpr int CH1 = OW > 1 ? 1 : (NG1 > 4 ? 4 : NG1);   // groups per chunk: at most 64 (16) registers in flight
+        constexpr int CH1 = OW > 1 ? 1 : PL ? C::PL_CHUNK : (NG1 > 4 ? 4 : NG1);   // groups per chunk: at most 64 (16) registers in flight
 #pragma unroll
         for (int c0 = 0; c0 < NG1; c0 += CH1) {
 #pragma unroll
@@ -831,7 +846,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
         }
         epilogue();
         if constexpr (PHASE2) {
-            constexpr int CH2 = OW > 1 ? 1 : NG2;
+            constexpr int CH2 = OW > 1 ? 1 : PL ? C::PL_CHUNK : NG2;
 #pragma unroll
             for (int c0 = 0; c0 < NG2; c0 += CH2) {
 #pragma unroll
@@ -856,6 +871,15 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 a.sum_part[(size_t)split * a.own_pad + oidx] = make_float4(sum1[h], sum2[h], sum3[h], 0.f);
                 if constexpr (MODE == KGE_MODE_FWD)
                     a.stat_part[(size_t)split * a.own_pad + oidx] = make_float4(st_m[h], st_l[h], st_acc[h], 0.f);
+            }
+            if constexpr (PL) {
+                const float inv = c_scale > 0.f ? 1.f / c_scale : 1.f;
+#pragma unroll
+                for (int blk = 0; blk < C::NBH; ++blk)
+                    for (int i = 0; i < 16; ++i) {
+                        acc2[h][blk][i] *= inv;
+                        if constexpr (TRANSH && OWN_ROW) acc2b[blk][i] *= inv;
+                    }
             }
 #pragma unroll
             for (int blk = 0; blk < C::NBH; ++blk) {

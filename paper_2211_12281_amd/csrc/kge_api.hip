@@ -179,15 +179,14 @@ struct Carver {
 
 struct Buffers {
     void *Q, *W, *Q2, *T, *Qt, *Wt, *Tt;
-    void *Q3, *W3, *T3;                // three bf16 pieces of Q, of TransH's unit normals and of T, [3][rows][dp] (Geometry::planes)
     KgeRowInfo *rowinfo; float *tn, *pos, *lossb, *gpos;
     float4 *stat_part; float *accq, *accq2; float4 *sumq; float *acct; float4 *sumt;
     float *regv;                       // L3 norms of the gathered slots: [Bp heads][Bp tails][Np negatives]
     float *S, *Q32;                    // small blocks and 1-norm scorers: the score block [Bp][Np], later the pairs' coefficients in
                                        // its place; the queries unrounded [Bp][dp]
     float *W32, *A, *P;                // ... TransH: the unit normals unrounded, w^ . t and sign(x) . w^ per pair [Bp][Np]
-    void *Qp2, *Tp2;                   // score-only calls on fp32 tables: two fp16 planes of the scaled Q (TransH: and of W) and T
-    float *t_inv;                      // ... 1 / scale of the rows of T
+    void *Qp2, *Tp2;                   // score-only calls on fp32 tables, Geometry::planes: two fp16 planes of the scaled Q (TransH: and of W) and T
+    float *t_inv, *q_inv;              // ... 1 / scale of the rows of T (and of Q)
     void *pstore, *Qs;                 // sampled softmax on the kernels of block_sym.hip / block_gradp.hip: the weights of the
                                        // forward pass [Bp x Np bf16, in records], the queries scaled per forward split [nsplit_q][Bp][dp]
     float *nbias;                      // training calls: 0 for each of the N negatives, -inf for the padding rows behind them
@@ -196,21 +195,19 @@ struct Buffers {
 size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
     Carver c(ws);
     const size_t es = g.es, rowsB = (size_t)g.Bp * g.dp, rowsN = (size_t)g.Np * g.dp;
-    b.Q = g.planes ? nullptr : c.take<char>(rowsB * es);
-    b.W = g.transh && !g.planes ? c.take<char>(rowsB * es) : nullptr;
-    b.T = g.planes ? nullptr : c.take<char>(rowsN * es);
-    b.Q3 = g.planes ? c.take<char>(rowsB * 6) : nullptr;
-    b.W3 = g.transh && g.planes ? c.take<char>(rowsB * 6) : nullptr;
-    b.T3 = g.planes ? c.take<char>(rowsN * 6) : nullptr;
+    b.Q = c.take<char>(rowsB * es);
+    b.W = g.transh ? c.take<char>(rowsB * es) : nullptr;
+    b.T = c.take<char>(rowsN * es);
     b.rowinfo = c.take<KgeRowInfo>(g.Bp);
     b.tn = c.take<float>(g.Np);
     b.pos = c.take<float>(g.Bp);
     b.Q32 = g.l1 ? c.take<float>(rowsB) : nullptr;
     b.W32 = g.l1 && g.transh ? c.take<float>(rowsB) : nullptr;
     b.A = b.P = nullptr;
-    b.Qp2 = b.Tp2 = nullptr; b.t_inv = nullptr;
-    if (!bwd && score_h2_applies(g)) {
+    b.Qp2 = b.Tp2 = nullptr; b.t_inv = b.q_inv = nullptr;
+    if (bwd ? g.planes : score_h2_applies(g)) {
         b.Qp2 = c.take<char>((g.transh ? 4 : 2) * rowsB * 2); b.Tp2 = c.take<char>(2 * rowsN * 2); b.t_inv = c.take<float>(g.Np);
+        if (bwd) b.q_inv = c.take<float>(g.Bp);
     }
     b.Q2 = nullptr; b.Qt = b.Wt = b.Tt = nullptr; b.lossb = b.gpos = nullptr; b.stat_part = nullptr;
     b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.nbias = nullptr;
@@ -526,7 +523,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     if (plain_gather) {
         KgeProfScope prof(KGE_PROF_GATHER, st);
         rc = kge_run_qbuild_tgather(md, h, r, t, g.B, g.Bp, g.dp, b.Q, b.W, b.Q2, b.Q32, b.W32, b.rowinfo, b.pos,
-                                    neg, g.N, g.Np, b.T, b.tn, st, nullptr, nullptr, nullptr, nullptr, b.nbias, gen, b.Q3, b.W3, b.T3);
+                                    neg, g.N, g.Np, b.T, b.tn, st, nullptr, b.Qp2, b.Tp2, b.t_inv, b.nbias, gen, b.q_inv);
     }
     else rc = kge_run_qbuild(md, h, r, t, g.B, g.Bp, g.dp, b.Q, b.W, b.Q2, b.Q32, b.W32, b.rowinfo, b.pos, nullptr, st);
     if (rc != KGE_OK) return rc;
@@ -547,7 +544,12 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
             (rc = kge_run_transpose(g.transh ? b.Q2 : b.Q, b.Qt, g.Bp, g.dp, g.bf16, st)) != KGE_OK) return rc;
         if (g.transh && !g.planes && (rc = kge_run_transpose(b.W, b.Wt, g.Bp, g.dp, g.bf16, st)) != KGE_OK) return rc;
         // pass 1 (row owner): loss statistics of every row and the unnormalised gradient of the queries
-        a.own = g.planes ? b.Q3 : b.Q; a.own2 = g.planes ? b.W3 : b.W; a.str = g.planes ? b.T3 : b.T; a.strT = b.Tt; a.strT_ld = g.Np; a.rowinfo = b.rowinfo; a.tn = b.tn;
+        a.own = b.Q; a.own2 = b.W; a.str = b.T;
+        if (g.planes) {
+            a.own = b.Qp2; a.own2 = g.transh ? (const char *)b.Qp2 + (size_t)4 * g.Bp * g.dp : nullptr; a.str = b.Tp2;
+            a.own_inv = b.q_inv; a.str_inv = b.t_inv; a.own32 = (const float *)b.Q; a.str32 = (const float *)b.T; a.w32 = (const float *)b.W;
+        }
+        a.strT = b.Tt; a.strT_ld = g.Np; a.rowinfo = b.rowinfo; a.tn = b.tn;
         a.B = g.B; a.N = g.N; a.dp = g.dp; a.str_tiles = g.str_tiles_n; a.tiles_per_split = g.tps_q;
         a.kind = g.kind; a.loss = cfg->loss; a.gamma = cfg->gamma; a.adv_temp = cfg->adv_temp; a.c_corr = c_corr;
         a.stat_part = b.stat_part; a.acc_part = b.accq; a.acc_part2 = b.accq2; a.sum_part = b.sumq; a.own_pad = g.Bp;
@@ -592,7 +594,8 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     } else if (have_block) {
         // pass 2 (column owner): gradient of the shared negatives from the finished row constants
         KgeBlockArgs c = a;
-        c.own = a.str; c.own2 = nullptr; c.str = a.own; c.str2 = a.own2; c.strT = b.Qt; c.strT2 = b.Wt; c.strT_ld = g.Bp;
+        c.own = a.str; c.own2 = nullptr; c.str = a.own; c.str2 = a.own2; c.own_inv = a.str_inv; c.str_inv = a.own_inv; c.own32 = a.str32;
+        c.str32 = a.own32; c.strT = b.Qt; c.strT2 = b.Wt; c.strT_ld = g.Bp;
         c.str_tiles = g.str_tiles_b; c.tiles_per_split = g.tps_t;
         c.acc_part = b.acct; c.acc_part2 = nullptr; c.sum_part = b.sumt; c.stat_part = nullptr; c.own_pad = g.Np;
         if (keep_weights) c.str2 = b.Qs; else c.pstore = nullptr;    // (str2: the scaled queries; the recomputing kernel behind streams the plain ones)

@@ -46,6 +46,8 @@ static inline int64_t kge_round_up(int64_t x, int64_t m) { return (x + m - 1) / 
 constexpr int KGE_STREAM_TILE = 32;   // rows streamed through LDS per iteration
 constexpr int KGE_PAD = 256;          // B and N are padded to this in the workspace copies
 
+constexpr float KGE_PLANE_UNIT_SCALE = 1024.f;      // scale of the planes of TransH's unit normals (all rows)
+
 enum { KGE_MODE_SCORE = 0, KGE_MODE_FWD = 1, KGE_MODE_GRADT = 2 };
 enum { KGE_KIND_MULT = 0, KGE_KIND_DIST = 1 };
 
@@ -63,16 +65,20 @@ constexpr int kge_block_ow(bool bf16, int rb, bool transh, int mode, int kind) {
 // Workgroups of a block-kernel pass that share a compute unit: the SCORE pass keeps no gradient
 // accumulators and fits two, where two ring stages of its tiles fit in half of the LDS.
 constexpr int kge_block_occ(bool bf16, int rb, bool transh, int mode) {
-    (void)bf16;
+    if (!bf16 && rb == 512 && !transh && mode != KGE_MODE_SCORE) return 2;
     return (mode == KGE_MODE_SCORE && !transh && KGE_STREAM_TILE * rb <= 32 * 1024) ? 2 : 1;
 }
 
-// fp32 training passes on rows of up to 512 bytes read their operands as three bf16 planes [3][rows][dp] (x = x0 + x1 + x2, see
-// kge_split3), which the gather writes instead of the fp32 rows and their transposed copies.  With fp32 operands every wave split every
-// streamed value twice, once for each phase, on the vector pipe that the loss weights need (TransH 8,192 x 4,096 x 128: 329 + 262 us for the
-// two passes, 15 for the transposes and gathers saved; now 208 + 199.  TransE: whole call 326 -> 238 us; DistMult 4,096 x 4,096 x 96:
-// 166 -> 123).  Rows of 1,024 bytes stay: their planes leave no registers in the pass over the queries.
-constexpr bool kge_block_planes(bool bf16, int rb, int mode) { return !bf16 && rb == 512 && mode != KGE_MODE_SCORE; }
+// The fp32 training passes read their operands as two fp16 planes [2][rows][dp] of rows scaled by a power of two of their own (kge_split2),
+// which the gather writes beside the fp32 rows; there are no transposed copies.  The fp32 matrix instruction runs at 1/16 of the 16-bit
+// rate; three products of pieces replace sixteen.  Calls in us, before / here.  Rows of 512 bytes (before: three bf16 pieces, six products):
+// TransH 8,192 x 4,096 x 128 392 / 322 (passes 211 + 201 -> 170 + 164: the epilogue and the contractions of a tile one after the other in one
+// wave per SIMD), TransE 234 / 188, ComplEx 8,000 x 3,000 x 128 230 / 154, DistMult 4,096 x 4,096 x 96 111 / 92.  Rows of 1,024 bytes (fp32
+// instructions over the queries, bf16 pieces made in registers over the negatives): TransE 4,096 x 4,096 x 256 366 / 242, DistMult 2,048 x
+// 8,192 x 200 302 / 151, RotatE 8,192 x 2,000 x 256 353 / 220, ComplEx 4,096 x 4,096 x 256 330 / 191.
+// Errors against 64 bits over 120 drawn calls on rows of up to 512 bytes: 0.97-1.00 times those of before (geometric mean of every gradient),
+// half on rows of 1,024 bytes.
+constexpr bool kge_block_planes(bool bf16, int rb, int mode) { (void)rb; return !bf16 && mode != KGE_MODE_SCORE; }
 
 // Per-row side information of the queries: squared norm of q, c = w.q (TransH), the per-row
 // constant K of the gradient coefficient exp2(x * log2e + K) (log2 domain), squared norm of the
@@ -82,7 +88,9 @@ struct __attribute__((aligned(16))) KgeRowInfo { float qn, c, K, wn; };
 // Arguments of one block-kernel launch.  "own" is the operand a workgroup keeps in registers
 // (queries when OWN_ROW, negatives otherwise); "str" is the operand streamed through LDS.
 struct KgeBlockArgs {
-    // (kge_block_planes: own, own2, str, str2 are bf16 planes [3][own_pad or 32 str_tiles][dp] and there are no transposed copies)
+    // (kge_block_planes: own, own2, str, str2 are fp16 planes [2][own_pad or 32 str_tiles][dp] of rows scaled by 1 / own_inv, 1 / str_inv -
+    // the normals by KGE_PLANE_UNIT_SCALE -, own32, str32 and w32 the fp32 rows; there are no transposed copies)
+    const float *own_inv, *str_inv, *own32, *str32, *w32;
     const void *own, *own2;        // [own_pad][dp]; own2: TransH normals when OWN_ROW
     const void *str, *str2;        // [str_pad][dp]; str2: TransH normals when !OWN_ROW
     const void *strT, *strT2;      // [dp][strT_ld] transposed stream operand(s), GRAD only

@@ -20,7 +20,6 @@ int kge_run_qbuild(const KgeModelDev &m, const int32_t *h, const int32_t *r, con
                    float *pos_out, hipStream_t st, void *planes = nullptr);
 // planes (fp32 tables only, optional): also the two fp16 pieces of every element of the rows scaled by a power of two,
 // [2][rows][dp], and 1 / scale of every row in inv_scale
-constexpr float KGE_PLANE_UNIT_SCALE = 1024.f;      // scale of the planes of TransH's unit normals (all rows)
 int kge_run_tgather(const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T, float *tn,
                     hipStream_t st, void *planes = nullptr, float *inv_scale = nullptr);
 // The draw of kge_run_negatives for a gather that makes it itself: id n of (seed, step [+ *step_counter], tag) in
@@ -33,8 +32,7 @@ int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t
                            void *q_planes = nullptr, void *t_planes = nullptr, float *t_inv_scale = nullptr,
                            float *bias = nullptr,             // bias [Np]: 0 for the N negatives, -inf behind them
                            const KgeNegGen *gen = nullptr,    // gen->out set: neg is ignored, the ids are drawn and written there
-                           // fp32 tables: the rows of Q, of TransH's unit normals and of T as three bf16 pieces [3][rows][dp]; Q and T may be null
-                           void *q3 = nullptr, void *w3 = nullptr, void *t3 = nullptr);
+                           float *q_inv_scale = nullptr);     // q_planes: 1 / scale of the queries' rows (also in rowinfo.K until that is set)
 // gather of the negatives and their transposed copy Tt [dp][Np] in one launch
 int kge_run_tgather_t(const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T, void *Tt, float *tn,
                       hipStream_t st);

@@ -70,11 +70,10 @@ struct KgeQbuildArgs {
     float *pos_ws, *pos_out;
     _Float16 *planes;                  // optional: the two fp16 pieces of the scaled q, [2][Bp][dp], with W two more for the
                                        // unit normal (scaled by KGE_PLANE_UNIT_SCALE); then rowinfo.K = 1 / scale of the row
-    uint16_t *q3, *w3;                 // optional: the three bf16 pieces of q and of the unit normal, [3][Bp][dp] each (Q may be null then)
+    float *inv_scale;                  // optional: 1 / scale of the rows [Bp]
 };
 struct KgeTgatherArgs {
     const int32_t *neg; int N, Np; void *T; float *tn; _Float16 *planes; float *inv_scale; float *bias;
-    uint16_t *t3;                      // optional: the three bf16 pieces of the rows, [3][Np][dp] (T may be null then)
     KgeNegGen gen;                     // gen.out set: the ids are drawn here (and written to gen.out) instead of read from neg
 };
 
@@ -86,23 +85,13 @@ __device__ __forceinline__ float kge_plane_scale(float amax, float &inv) {
     if (!(amax > 0.f)) { inv = 1.f; return 1.f; }
     int e;
     (void)frexpf(amax, &e);                                 // amax = f 2^e, f in [0.5, 1)
-    e = e < -100 ? -100 : (e > 100 ? 100 : e);
+    e = e < -115 ? -115 : (e > 128 ? 128 : e);              // (the scale and its reciprocal are normal numbers)
     inv = ldexpf(1.f, e - 11);
     return ldexpf(1.f, 11 - e);
 }
 __device__ __forceinline__ void kge_store_planes(_Float16 *planes, int64_t n, int64_t i, float xs) {
     const _Float16 x1 = (_Float16)xs;
     planes[i] = x1; planes[n + i] = (_Float16)(xs - (float)x1);
-}
-
-// x as three bf16 pieces (round to nearest at each step), piece p of element i at planes[p n + i]
-__device__ __forceinline__ void kge_store_pieces(uint16_t *planes, int64_t n, int64_t i, float x) {
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        const __bf16 b = (__bf16)x;
-        planes[p * n + i] = __builtin_bit_cast(uint16_t, b);
-        x -= (float)b;
-    }
 }
 
 // NJ: columns per lane (dp <= 64 NJ)
@@ -119,8 +108,6 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
     if (b >= B) {
         for (int j = lane; j < dp; j += 64) {
             if (Q) El<BF16>::st(Q, (int64_t)b * dp + j, 0.f);
-            if (!BF16 && a.q3) kge_store_pieces(a.q3, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
-            if (!BF16 && a.w3) kge_store_pieces(a.w3, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
             if (W) El<BF16>::st(W, (int64_t)b * dp + j, 0.f);
             if (Q2) El<BF16>::st(Q2, (int64_t)b * dp + j, 0.f);
             if (Q32) Q32[(int64_t)b * dp + j] = 0.f;
@@ -128,14 +115,16 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
             if (a.planes) kge_store_planes(a.planes, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
             if (a.planes && W) kge_store_planes(a.planes + 2 * (int64_t)Bp * dp, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
         }
-        if (lane == 0) { rowinfo[b] = KgeRowInfo{0.f, 0.f, a.planes ? 1.f : 0.f, 0.f}; if (pos_ws) pos_ws[b] = 0.f; }
+        if (lane == 0) { rowinfo[b] = KgeRowInfo{0.f, 0.f, a.planes ? 1.f : 0.f, 0.f}; if (pos_ws) pos_ws[b] = 0.f; if (a.inv_scale) a.inv_scale[b] = 1.f; }
         return;
     }
     KgeRowCtx<BF16, NJ> cx;
     kge_build_query<BF16, SC, NJ>(m, h[b], r[b], lane, cx);
     const int d = m.dim;
     const int64_t toff = (int64_t)t[b] * m.ent_ld;
-    float qn = 0.f, cq = 0.f, wn = 0.f, s_pos = 0.f, wt = 0.f;
+    using Norm = typename El<BF16>::Norm;
+    Norm qn = 0, cq = 0, wn = 0;
+    float s_pos = 0.f, wt = 0.f;
     float tv[NJ];
     float q_scale = 1.f, q_inv = 0.f;
     if (a.planes) {
@@ -150,12 +139,10 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
         const float tj = El<BF16>::ld(m.ent, toff + (j < d ? j : 0));
         tv[k] = j < d ? tj : 0.f;
         const float qr = El<BF16>::rnd(cx.q[k]), wr = El<BF16>::rnd(cx.w[k]);
-        qn += qr * qr; cq += wr * qr; wn += wr * wr;          // norms of what the matrix cores will see
+        qn += (Norm)qr * qr; cq += (Norm)wr * qr; wn += (Norm)wr * wr;        // norms of what the matrix cores will see
         wt += cx.w[k] * tv[k];
         if (j < dp) {
             if (Q) El<BF16>::st(Q, (int64_t)b * dp + j, cx.q[k]);
-            if (!BF16 && a.q3) kge_store_pieces(a.q3, (int64_t)Bp * dp, (int64_t)b * dp + j, cx.q[k]);
-            if (!BF16 && a.w3) kge_store_pieces(a.w3, (int64_t)Bp * dp, (int64_t)b * dp + j, cx.w[k]);
             if (W) El<BF16>::st(W, (int64_t)b * dp + j, cx.w[k]);
             if (Q32) Q32[(int64_t)b * dp + j] = cx.q[k];      // unrounded copies for the 1-norm kernels
             if (W32) W32[(int64_t)b * dp + j] = cx.w[k];
@@ -170,7 +157,7 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
 #pragma unroll
         for (int k = 0; k < NJ; ++k) {
             const int j = lane + 64 * k;
-            if (j < dp) El<BF16>::st(Q2, (int64_t)b * dp + j, El<BF16>::rnd(cx.q[k]) - cq * El<BF16>::rnd(cx.w[k]));
+            if (j < dp) El<BF16>::st(Q2, (int64_t)b * dp + j, El<BF16>::rnd(cx.q[k]) - (float)cq * El<BF16>::rnd(cx.w[k]));
         }
     }
     // positive score by the direct formula (Table 2), fp32
@@ -186,7 +173,8 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
     s_pos = kge_wave_sum(s_pos);
     if (!(SC == KGE_DISTMULT || SC == KGE_COMPLEX)) s_pos = m.p1 ? -s_pos : -sqrtf(s_pos);
     if (lane == 0) {
-        rowinfo[b] = KgeRowInfo{qn, cq, q_inv, SC == KGE_TRANSH ? wn : 1.f};     // (K: set by the row finish when training)
+        rowinfo[b] = KgeRowInfo{(float)qn, (float)cq, q_inv, SC == KGE_TRANSH ? (float)wn : 1.f};     // (K: set by the row finish when training)
+        if (a.inv_scale) a.inv_scale[b] = q_inv;
         if (pos_ws) pos_ws[b] = s_pos;
         if (pos_out) pos_out[b] = s_pos;
     }
@@ -210,7 +198,7 @@ __host__ __device__ inline int kge_tgather_rows_per_wave(int dp, int es) { retur
 template <bool BF16>
 __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T,
                                                  float *tn, _Float16 *planes = nullptr, float *inv_scale = nullptr,
-                                                 const KgeNegGen *gen = nullptr, uint16_t *t3 = nullptr) {
+                                                 const KgeNegGen *gen = nullptr) {
     const int lane = threadIdx.x & 63;
     const bool draw = gen && gen->out;
     uint32_t step = 0;
@@ -254,33 +242,21 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
             const bool live = n < Np && lg < lpr;
             if (live && T) *(uint4 *)((char *)T + ((int64_t)n * dp) * ES + lg * 16) = v[u];
             const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-            float s = 0.f, amax = 0.f;
+            typename El<BF16>::Norm s = 0;
+            float amax = 0.f;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 if constexpr (BF16) {
                     const float a0 = __uint_as_float(w[k] << 16), a1 = __uint_as_float(w[k] & 0xffff0000u);
                     s += a0 * a0; s += a1 * a1;
-                } else { const float a0 = __uint_as_float(w[k]); s += a0 * a0; amax = fmaxf(amax, fabsf(a0)); }
+                } else { const float a0 = __uint_as_float(w[k]); s += (double)a0 * a0; amax = fmaxf(amax, fabsf(a0)); }
             }
             // sum (and largest magnitude) over the lanes of the row's group (fixed order)
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1)
                 if (o < gl) { s += __shfl_xor(s, o); amax = fmaxf(amax, __shfl_xor(amax, o)); }
-            if (lg == 0 && n < Np) tn[n] = s;
+            if (lg == 0 && n < Np) tn[n] = (float)s;
             if constexpr (!BF16) {
-                if (t3 && live) {                       // the lane's four elements: one 8-byte store per plane
-                    float x[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) x[k] = __uint_as_float(w[k]);
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) {
-                        typedef __bf16 b4 __attribute__((ext_vector_type(4)));
-                        b4 o;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) { o[k] = (__bf16)x[k]; x[k] -= (float)o[k]; }
-                        *(b4 *)(t3 + ((int64_t)p * Np + n) * dp + lg * 4) = o;
-                    }
-                }
                 if (planes) {
                     float inv;
                     const float sc = kge_plane_scale(amax, inv);
@@ -310,15 +286,15 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
             if (draw && lane == 0) gen->out[n] = id;
             off = (int64_t)id * m.ent_ld;
         }
-        float s = 0.f, amax = 0.f;
+        typename El<BF16>::Norm s = 0;
+        float amax = 0.f;
         for (int j = lane; j < dp; j += 64) {
             float v = (n < N && j < m.dim) ? El<BF16>::ld(m.ent, off + j) : 0.f;
             if (T) El<BF16>::st(T, (int64_t)n * dp + j, v);
-            if (!BF16 && t3) kge_store_pieces(t3, (int64_t)Np * dp, (int64_t)n * dp + j, v);
-            s += v * v; amax = fmaxf(amax, fabsf(v));
+            s += (typename El<BF16>::Norm)v * v; amax = fmaxf(amax, fabsf(v));
         }
         s = kge_wave_sum(s);
-        if (lane == 0) tn[n] = s;
+        if (lane == 0) tn[n] = (float)s;
         if (!BF16 && planes) {                              // (second walk over the row, now that its scale is known)
             float inv;
             const float sc = kge_plane_scale(kge_wave_max(amax), inv);
@@ -344,7 +320,7 @@ __global__ void kge_qbuild_tgather_kernel(int q_blocks, KgeQbuildArgs a, KgeTgat
     if (g.bias)                                                         // 0 for the negatives, -inf for the padding rows behind them
         for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < g.Np; n += gridDim.x * blockDim.x) g.bias[n] = n < g.N ? 0.f : -INFINITY;
     if ((int)blockIdx.x < q_blocks) kge_qbuild_body<BF16, SC, NJ>(blockIdx.x, a);
-    else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen, g.t3);
+    else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen);
 }
 
 // gather of the shared negatives AND their transposed copy in one launch: a workgroup takes 32 negatives, every
@@ -804,7 +780,7 @@ int kge_run_qbuild(const KgeModelDev &m, const int32_t *h, const int32_t *r, con
                    float *pos_out, hipStream_t st, void *planes) {
     const int grid = (Bp + 3) / 4;
     if (grid == 0) return KGE_OK;
-    const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)planes, nullptr, nullptr};
+    const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)planes, nullptr};
 #define KGE_QBUILD(BF, SC) hipLaunchKernelGGL((kge_qbuild_kernel<BF, SC>), dim3(grid), dim3(256), 0, st, a)
     if (m.bf16) { KGE_SC_SWITCH(true, KGE_QBUILD) } else { KGE_SC_SWITCH(false, KGE_QBUILD) }
 #undef KGE_QBUILD
@@ -815,13 +791,13 @@ int kge_run_qbuild(const KgeModelDev &m, const int32_t *h, const int32_t *r, con
 int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t *r, const int32_t *t, int B, int Bp,
                            int dp, void *Q, void *W, void *Q2, float *Q32, float *W32, KgeRowInfo *rowinfo, float *pos_ws,
                            const int32_t *neg, int N, int Np, void *T, float *tn, hipStream_t st, float *pos_out,
-                           void *q_planes, void *t_planes, float *t_inv_scale, float *bias, const KgeNegGen *gen, void *q3, void *w3, void *t3) {
+                           void *q_planes, void *t_planes, float *t_inv_scale, float *bias, const KgeNegGen *gen, float *q_inv_scale) {
     const int rows_wg = 4 * kge_tgather_rows_per_wave(dp, m.bf16 ? 2 : 4);
     const int qb = (Bp + 3) / 4, tb = (Np + rows_wg - 1) / rows_wg;
     if (qb == 0 || tb == 0 || ((q_planes || t_planes) && m.bf16) || (t_planes && !t_inv_scale)) return KGE_E_INVALID_ARG;
     const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)q_planes,
-                          (uint16_t *)q3, (uint16_t *)w3};
-    const KgeTgatherArgs g{neg, N, Np, T, tn, (_Float16 *)t_planes, t_inv_scale, bias, (uint16_t *)t3, gen ? *gen : KgeNegGen{}};
+                          q_inv_scale};
+    const KgeTgatherArgs g{neg, N, Np, T, tn, (_Float16 *)t_planes, t_inv_scale, bias, gen ? *gen : KgeNegGen{}};
     // (kernels for the columns of a padded row: the query is built without branches, lanes past the row read its first column again;
     // one kernel for 512 columns: TransH 8,192 x 4,096 step 454 instead of 453 us, ComplEx 4,096 x 16,384 196 / 195)
 #define KGE_QT_NJ(BF, SC, NJ) hipLaunchKernelGGL((kge_qbuild_tgather_kernel<BF, SC, NJ>), dim3(qb + tb), dim3(256), 0, st, qb, a, g)

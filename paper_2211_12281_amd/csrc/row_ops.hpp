@@ -7,18 +7,28 @@
 template <bool BF16> struct El;
 template <> struct El<true> {
     using T = __bf16;
+    using Norm = float;
     static __device__ __forceinline__ float ld(const void *p, int64_t i) { return (float)((const __bf16 *)p)[i]; }
     static __device__ __forceinline__ void st(void *p, int64_t i, float v) { ((__bf16 *)p)[i] = (__bf16)v; }
     static __device__ __forceinline__ float rnd(float v) { return (float)(__bf16)v; }
 };
 template <> struct El<false> {
     using T = float;
+    // sums of squares and products that the expanded distance |q|^2 + |t|^2 - 2 q.t starts from: their rounding is not divided by anything
+    // (with fp32 sums the drawn calls' gradient errors were 0.2-3 % larger)
+    using Norm = double;
     static __device__ __forceinline__ float ld(const void *p, int64_t i) { return ((const float *)p)[i]; }
     static __device__ __forceinline__ void st(void *p, int64_t i, float v) { ((float *)p)[i] = v; }
     static __device__ __forceinline__ float rnd(float v) { return v; }
 };
 
 __device__ __forceinline__ float kge_wave_sum(float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+__device__ __forceinline__ double kge_wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;

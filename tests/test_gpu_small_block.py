@@ -203,10 +203,11 @@ def test_block_kernels_planned_call(block_passes, scorer, dim, bf16, loss, B, N)
 
 
 @pytest.mark.parametrize("scorer,dim,B,N", [("transh", 128, 129, 257), ("transh", 8, 31, 33), ("transe", 40, 1, 4000), ("rotate", 128, 300, 1),
-                                            ("complex", 64, 130, 95), ("distmult", 120, 127, 161)])
+                                            ("complex", 64, 130, 95), ("distmult", 120, 127, 161),
+                                            ("transe", 256, 129, 257), ("rotate", 136, 31, 33), ("complex", 200, 1, 4000)])
 @pytest.mark.parametrize("loss", ["logsigmoid", "sampled_softmax"])
 def test_block_kernels_on_planes(orc, block_passes, scorer, dim, B, N, loss):
-    """fp32 rows of up to 512 bytes, which the block kernels read as bf16 pieces: padding columns, a row more or less than a tile; the
+    """fp32 rows, which the block kernels read as fp16 pieces: padding columns, a row more or less than a tile; the
     heads among the negatives and short relations, so that distances of the norm expansion cancel and are taken again from the rows."""
     G = make_case(scorer, 3000, 9, dim, B, N, False, amp=0.3 if scorer in ("distmult", "complex") else 0.1, zipf=True)
     if scorer in ("transe", "transh"):
@@ -259,3 +260,24 @@ def test_row_pass_beside_the_sorts(scorer, dim, bf16, p_norm, B, N, n_ent):
     for a, b in zip(*res):
         assert torch.equal(a, b)
     assert bool((res[0][-1] != 0).any())
+
+
+@pytest.mark.parametrize("scorer,dim,loss,order", [
+    ("transe", 128, "logsigmoid", -1), ("transe", 256, "sampled_softmax", -1), ("rotate", 256, "logsigmoid", 1), ("rotate", 64, "sampled_softmax", -1),
+    ("transh", 128, "logsigmoid", -1), ("transh", 64, "sampled_softmax", 1), ("distmult", 256, "logsigmoid", 1), ("complex", 128, "sampled_softmax", -1),
+    ("distmult", 200, "sampled_softmax", 1)])
+def test_block_kernels_on_planes_with_rows_of_all_sizes(orc, block_passes, scorer, dim, loss, order):
+    """Every row of the planes has a scale of its own, and so have the coefficients of an own row: negatives between 2^-40 and 4 times
+    the usual size, the largest first (the coefficients of a distance scorer, weight over distance times row scale, then grow 2^42-fold along
+    the pass: what is accumulated is rescaled again and again) or last (the first tile sets a scale that later ones don't reach); heads
+    and tails likewise, so that the pass over the negatives meets the same."""
+    G = make_case(scorer, 6000, 9, dim, 300, 700, False, amp=0.3 if scorer in ("distmult", "complex") else 0.1)
+    used = np.unique(np.concatenate([G["h"], G["t"], G["neg"]]))
+    size = np.float32(2.0) ** np.linspace(-40, 2, len(used)).round().astype(np.float32)
+    G["ent"][used] *= size[:, None]
+    of = dict(zip(used.tolist(), size.tolist()))
+    G["neg"] = np.array(sorted(G["neg"].tolist(), key=lambda i: order * of[i]), dtype=np.int32)
+    at = np.array(sorted(range(len(G["h"])), key=lambda b: order * of[int(G["h"][b])]))
+    for k in ("h", "r", "t"):
+        G[k] = np.ascontiguousarray(G[k][at])
+    base._compare(orc, scorer, loss, G, False, 6000)
