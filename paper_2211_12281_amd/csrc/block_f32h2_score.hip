@@ -47,14 +47,9 @@ template <bool NT> __device__ __forceinline__ void h2_store(const ScoreH2Args &a
     else a.S_out[i] = v;
 }
 
-// workgroups that stream the same queries share a die (workgroup ids go round the 8 dies: with 8 or more splits a die
-// takes the splits congruent to it; with fewer, a split takes 8 / splits dies and the own tiles are dealt over them)
 __device__ __forceinline__ bool h2_place(const ScoreH2Args &a, int &own_tile, int &t0, int &t1) {
-    const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
     int split;
-    if (a.xcd_per == 1) { own_tile = kk % a.own_tiles; split = xcd + 8 * (kk / a.own_tiles); }
-    else { split = xcd / a.xcd_per; own_tile = kk * a.xcd_per + xcd % a.xcd_per; }
-    if (own_tile >= a.own_tiles || split >= a.nsplit) return false;
+    if (!kge_place(a.own_tiles, a.nsplit, a.xcd_per, own_tile, split)) return false;
     t0 = split * a.tiles_per_split;
     t1 = min(a.str_tiles, t0 + a.tiles_per_split);
     return t0 < t1;
@@ -330,14 +325,7 @@ template <typename K>
 int launch_h2(K kern, int lds_bytes, KgeLdsLimit &lds_limit, const ScoreH2Args &a, hipStream_t st) {
     if (lds_limit.set((const void *)kern, lds_bytes) != KGE_OK) return KGE_E_HIP;
     ScoreH2Args b = a;
-    int groups;
-    if (a.nsplit >= 8) { b.xcd_per = 1; groups = a.own_tiles * ((a.nsplit + 7) / 8); }
-    else {
-        int s2 = 1;
-        while (s2 < a.nsplit) s2 <<= 1;
-        b.xcd_per = 8 / s2;
-        groups = (a.own_tiles + b.xcd_per - 1) / b.xcd_per;
-    }
+    const int groups = kge_place_plan(a.own_tiles, a.nsplit, 128, (int64_t)H2_ST * a.str_tiles, 1, &b.xcd_per);
     hipLaunchKernelGGL(kern, dim3(8 * groups), dim3(256), lds_bytes, st, b);
     return kge_launch_status();
 }

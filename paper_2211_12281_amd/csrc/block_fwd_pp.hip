@@ -75,12 +75,8 @@ void kge_pp_kernel(const KgeBlockArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, g = lane >> 5;
     const bool role_b = wave >= 4;
     const int pair = wave & 3;
-    // placement as in the one-role kernel: workgroups that stream the same negatives share a die
-    const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
     int own_tile, split;
-    if (a.xcd_per == 1) { own_tile = kk % a.own_tiles; split = xcd + 8 * (kk / a.own_tiles); }
-    else { split = xcd / a.xcd_per; own_tile = kk * a.xcd_per + xcd % a.xcd_per; }
-    if (own_tile >= a.own_tiles || split >= a.nsplit) return;
+    if (!kge_place(a.own_tiles, a.nsplit, a.xcd_per, own_tile, split)) return;
     const int oidx = own_tile * 128 + pair * 32 + lr;       // the pair's own row of this lane
     const int str_limit = FWD ? a.N : a.B;                  // valid stream rows
     const int t0 = split * a.tiles_per_split;
@@ -399,14 +395,7 @@ int pp_launch(const KgeBlockArgs &a, int own_tiles, int nsplit, hipStream_t st) 
     if ((int64_t)own_tiles * 128 != a.own_pad || a.dp != PP_DP) return KGE_E_INVALID_ARG;
     KgeBlockArgs b = a;
     b.own_tiles = own_tiles; b.nsplit = nsplit;
-    int groups;
-    if (nsplit >= 8) { b.xcd_per = 1; groups = own_tiles * ((nsplit + 7) / 8); }
-    else {
-        int s2 = 1;
-        while (s2 < nsplit) s2 <<= 1;
-        b.xcd_per = 8 / s2;
-        groups = (own_tiles + b.xcd_per - 1) / b.xcd_per;
-    }
+    const int groups = kge_place_plan(own_tiles, nsplit, 128, (int64_t)PP_ST * a.str_tiles, 1, &b.xcd_per);
     hipLaunchKernelGGL(kern, dim3(8 * groups), dim3(512), LDS, st, b);
     return kge_launch_status();
 }

@@ -11,7 +11,7 @@
 // ring of 2-4 stages in tiles of 32 rows.  The ring is filled by asynchronous global->LDS copies
 // (no registers, several tiles in flight); rows are stored unpadded with their 16-byte chunks
 // XOR-swizzled so that the fragment reads of 8 consecutive rows hit 8 different bank groups.
-// Workgroups that stream the same rows are placed on the same XCD (shared L2).  Per tile and wave:
+// Workgroups that read the same rows share a die and its L2 (kge_place_plan).  Per tile and wave:
 //   phase 1   acc[32 stream x 32 own] = X_tile . own^t          (contraction over d)
 //   epilogue  score / loss weights / gradient coefficients, element by element
 //   phase 2   out^t[d x 32 own] += Xt_tile[d x 32 stream] . coef[stream x own]
@@ -239,21 +239,14 @@ void kge_block_kernel(const KgeBlockArgs a) {
     char *side_ring = lds + C::NSTAGE * C::STAGE_BYTES;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, g = lane >> 5;
-    // Workgroups go to the 8 XCDs round-robin: the workgroups that stream the same rows (same split)
-    // get ids with the same residue mod 8 and share that XCD's L2.
-    // With fewer than 8 splits, each split's own-tiles are dealt to 8 / nsplit XCDs.
-    const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
     int own_tile, split;
-    if (a.xcd_per == 1) { own_tile = kk % a.own_tiles; split = xcd + 8 * (kk / a.own_tiles); }
-    else { split = xcd / a.xcd_per; own_tile = kk * a.xcd_per + xcd % a.xcd_per; }
-    if (own_tile >= a.own_tiles) return;
+    if (!kge_place(a.own_tiles, a.nsplit, a.xcd_per, own_tile, split)) return;
     const int own_base = own_tile * C::OWN_TILE;
     const int dblk0 = blockIdx.y * C::NBH;
     const int oidx0 = own_base + wave * 32 * OW + lr;     // own row of fragment h: oidx0 + 32 h
     const int t0 = split * a.tiles_per_split;
     const int t1 = min(a.str_tiles, t0 + a.tiles_per_split);
     const int str_limit = OWN_ROW ? a.N : a.B;            // valid stream rows
-    if (split >= a.nsplit) return;
 
     // ---- own operand fragments: 16 bytes per lane per 32-byte k-step --------------------------
     constexpr bool PL = C::PL;
@@ -905,15 +898,9 @@ int kge_block_launch(const KgeBlockArgs &a, int own_tiles, int nsplit, hipStream
     if ((int64_t)own_tiles * C::OWN_TILE != a.own_pad) return KGE_E_INVALID_ARG;   // the caller's geometry must match
     KgeBlockArgs b = a;
     b.own_tiles = own_tiles; b.nsplit = nsplit;
-    int groups;                                            // workgroups per XCD
-    if (nsplit >= 8) { b.xcd_per = 1; groups = own_tiles * ((nsplit + 7) / 8); }
-    else {
-        int s2 = 1;
-        while (s2 < nsplit) s2 <<= 1;
-        b.xcd_per = 8 / s2;
-        groups = (own_tiles + b.xcd_per - 1) / b.xcd_per;
-    }
-    dim3 grid(8 * groups, MODE != KGE_MODE_SCORE ? DSPLIT : 1);
+    constexpr int GRID_Y = MODE != KGE_MODE_SCORE ? DSPLIT : 1;
+    const int groups = kge_place_plan(own_tiles, nsplit, C::OWN_TILE, (int64_t)C::ST * a.str_tiles, GRID_Y, &b.xcd_per);
+    dim3 grid(8 * groups, GRID_Y);
     hipLaunchKernelGGL(kern, grid, dim3(256), C::LDS_BYTES, st, b);
     return kge_launch_status();
 }

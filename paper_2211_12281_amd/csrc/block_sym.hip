@@ -85,12 +85,8 @@ void kge_sym_kernel(const KgeBlockArgs a) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, g = lane >> 5;
     const int oh = wave >> 1, sh = wave & 1, partner = wave ^ 1;
-    // placement: workgroups that stream the same rows share a die
-    const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
     int own_tile, split;
-    if (a.xcd_per == 1) { own_tile = kk % a.own_tiles; split = xcd + 8 * (kk / a.own_tiles); }
-    else { split = xcd / a.xcd_per; own_tile = kk * a.xcd_per + xcd % a.xcd_per; }
-    if (own_tile >= a.own_tiles || split >= a.nsplit) return;
+    if (!kge_place(a.own_tiles, a.nsplit, a.xcd_per, own_tile, split)) return;
     const int obase = own_tile * 128 + oh * 64 + lr;        // own row of block ob: obase + 32 ob
     const int str_limit = FWD ? a.N : a.B;                  // valid stream rows
     // tiles of 64 rows; only tiles that hold a valid row are visited
@@ -526,14 +522,7 @@ int sym_launch(const KgeBlockArgs &a, int own_tiles, int nsplit, hipStream_t st)
     if (MODE == KGE_MODE_FWD && !a.str_bias) return KGE_E_INVALID_ARG;
     KgeBlockArgs b = a;
     b.own_tiles = own_tiles; b.nsplit = nsplit;
-    int groups;
-    if (nsplit >= 8) { b.xcd_per = 1; groups = own_tiles * ((nsplit + 7) / 8); }
-    else {
-        int s2 = 1;
-        while (s2 < nsplit) s2 <<= 1;
-        b.xcd_per = 8 / s2;
-        groups = (own_tiles + b.xcd_per - 1) / b.xcd_per;
-    }
+    const int groups = kge_place_plan(own_tiles, nsplit, 128, (int64_t)32 * a.str_tiles, 1, &b.xcd_per);
     hipLaunchKernelGGL(kern, dim3(8 * groups), dim3(256), LDS, st, b);
     return kge_launch_status();
 }

@@ -87,6 +87,39 @@ struct __attribute__((aligned(16))) KgeRowInfo { float qn, c, K, wn; };
 
 // Arguments of one block-kernel launch.  "own" is the operand a workgroup keeps in registers
 // (queries when OWN_ROW, negatives otherwise); "str" is the operand streamed through LDS.
+// Placement of the workgroups (own tile, split) of the block kernels on the 8 dies, to which workgroup ids go in turn: a
+// die takes the splits congruent to xcd / per modulo 8 / per and the own tiles congruent to xcd % per modulo per (per 1,
+// 2, 4 or 8), so its L2 fills with 1 / per of the own rows and per / 8 of the streamed ones.
+__device__ __forceinline__ bool kge_place(int own_tiles, int nsplit, int per, int &own_tile, int &split) {
+    const int lp = __builtin_ctz(per), xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
+    const int own_per = (own_tiles + per - 1) >> lp, turn = kk / own_per;
+    own_tile = ((kk - turn * own_per) << lp) + (xcd & (per - 1));
+    split = (xcd >> lp) + (turn << (3 - lp));
+    return own_tile < own_tiles && split < nsplit;
+}
+// Returns the workgroups per die (the grid is 8 times that, in x; y of them per id).  First the fewest workgroups on the
+// fullest die, counted in turns of its 32 compute units; then the fewest rows into a die, the own ones weighed three times:
+// a workgroup waits for its own rows before its first tile, while the streamed ones arrive under the products of the tile
+// before.  Measured for per = 1 / 2 / 4 / 8, us of the whole call: fp32 scores DistMult 2,048 x 8,192 x 256 45.4 / 45.3 /
+// 43.7 / 42.2, ComplEx 512 x 4,096 x 128 16.1 / 15.3 / 15.0 / 14.3, bf16 2,048 x 8,192 x 256 31.9 / 31.2 / 30.5 / 29.1;
+// loss + gradients ComplEx 4,096 x 4,096 x 400 bf16 234.8 / 229.0 / 226.0 / 228.4 and RotatE x 256 fp32 243.3 / 241.8 /
+// 241.8 / 244.0 (there the streamed operand is as large as a die's L2, 4 MB).  Weights 2 and 3 take the best or next to it in
+// all of these; 1 gives DistMult fp32 1,024 x 8,192 x 128 86.8 for 86.0, 4 gives the d 400 block 229.0 for 226.8.
+inline int kge_place_plan(int own_tiles, int nsplit, int own_rows, int64_t str_rows, int y, int32_t *per) {
+    if (nsplit < 1) nsplit = 1;                            // nothing to stream: the workgroups find no split and end
+    int64_t best_load = 0, best_rows = 0;
+    int groups = 0;
+    for (int p = 8; p >= 1; p >>= 1) {
+        const int d = 8 / p;
+        const int64_t own_die = (own_tiles + p - 1) / p, split_die = (nsplit + d - 1) / d;
+        const int64_t load = (own_die * split_die * y + 31) / 32;
+        const int64_t rows = 3 * own_die * own_rows + str_rows * split_die / nsplit;
+        if (groups && (load > best_load || (load == best_load && rows >= best_rows))) continue;
+        best_load = load; best_rows = rows; groups = (int)(own_die * split_die); *per = p;
+    }
+    return groups;
+}
+
 struct KgeBlockArgs {
     // (kge_block_planes: own, own2, str, str2 are fp16 planes [2][own_pad or 32 str_tiles][dp] of rows scaled by 1 / own_inv, 1 / str_inv -
     // the normals by KGE_PLANE_UNIT_SCALE -, own32, str32 and w32 the fp32 rows; there are no transposed copies)
@@ -111,7 +144,7 @@ struct KgeBlockArgs {
     float4 *sum_part;              // FWD / GRADT: [nsplit][own_pad] {s1, s2, s3, 0}
     int32_t own_pad;
     int32_t own_tiles, nsplit;     // launch geometry (the grid is one-dimensional in (split, own tile))
-    int32_t xcd_per;               // XCDs that share one split (1 when there are 8 or more splits)
+    int32_t xcd_per;               // dies that share one split (kge_place_plan)
     const float *str_bias;         // FWD, kernel of block_sym.hip: [Np] 0 for a negative, -inf for a padding row (added to its scores)
     // the coefficients of the forward pass, kept for the pass over the negatives (block_sym.hip writes, block_gradp.hip reads):
     // one 4 KB record per (own tile of 128 queries, split, round of 64 negatives, wave), in the writer's register layout

@@ -52,6 +52,16 @@ def test_fp32_tables_on_the_bf16_pipe(orc, scorer, dim):
     assert norm_err(neg, neg2) <= RTOL_F32 and np.array_equal(pos, pos2)
 
 
+# row tiles and splits that are dealt over the 8 dies in each of the four ways (1, 2, 4 or 8 dies share a split), with
+# numbers of either that 8 does not divide
+@pytest.mark.parametrize("scorer,dim,bf16", [("distmult", 128, False), ("transe", 64, True)])
+@pytest.mark.parametrize("B,N", [(4096, 128), (4096, 384), (3000, 700), (1000, 1100), (1100, 2200), (40, 2000)])
+def test_every_workgroup_has_its_place(orc, scorer, dim, bf16, B, N):
+    G = make_case(scorer, 4000, 12, dim, B, N, bf16)
+    pos, neg, rp, rn = _run(orc, scorer, G, bf16)
+    assert norm_err(neg, rn) <= (RTOL_BF16 if bf16 else RTOL_F32)
+
+
 @pytest.mark.parametrize("scorer", ["transe", "transh", "distmult", "rotate"])
 @pytest.mark.parametrize("scale", [1e-4, 3e3, None])
 def test_fp32_score_block_does_not_depend_on_the_scale_of_the_tables(orc, scorer, scale):
