@@ -83,6 +83,14 @@ def test_query_counts_around_the_scan_variants(orc, scorer, bf16, dim, Q):
     _check(orc, scorer, G, bf16, 1, n, 20, ks.uniform_ids(ks.rng(4, ks.TAG_HELDOUT), 0, n, Q))
 
 
+# few queries: the candidates in 1, 2 and 3 chunks that grow up to 10 times (4,096 rows, 10 and 100 times that, and a tile more)
+@pytest.mark.parametrize("n", [4096, 4097, 40960, 40961, 409601])
+@pytest.mark.parametrize("K", [5, 100])
+def test_few_queries_with_fast_growing_chunks(orc, n, K):
+    G = make_case("transe", n, 5, 16, 3, 0, False)
+    _check(orc, "transe", G, False, 0, n, K, ks.uniform_ids(ks.rng(6, ks.TAG_HELDOUT), 0, n, 3))
+
+
 def test_long_lists_of_appends(orc):
     """Scores that rise with the id: every candidate of a chunk beats the threshold, so a query's list outgrows the LDS while
     no append area overflows; with K = 256 and repeated rows, whose values tie at the cut."""
