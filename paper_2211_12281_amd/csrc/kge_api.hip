@@ -87,12 +87,11 @@ int validate_model(const kge_model_t *m) {
 
 // Whether both passes of a training call run with the scores in memory (block_small.hip), by the padded size of the block.
 // Measured on both sides of the lines (whole kge_loss_bwd, block kernels / in memory, us):
-//   bf16 rows of 512 bytes (their block kernels are the best there are)  2,048 x 1,024: TransE 58 / 52, ComplEx softmax 50 / 51;
-//     4,096 x 1,024: 63 / 76, 57 / 73;  1,024 x 4,096: 68 / 70, 73 / 67 (a long row of S is cheap, many rows are not);
-//     2,048 x 4,096: 81 / 107, 68 / 103
-//   other rows  RotatE fp32 d 256: 512 x 1,024 88 / 48, 2,048 x 3,584 268 / 155, 2,048 x 4,096 225 / 171;  ComplEx bf16 d 400: 75 / 43,
-//     201 / 153, 168 / 166;  DistMult fp32 d 128 (its block kernels read planes): 48 / 38, 99 / 94, 85 / 102, 512 x 8,192 74 / 86;
-//     512 x 16,384: RotatE d 128 105 / 158, ComplEx d 400 176 / 237
+//   bf16 rows of 512 bytes (their block kernels are the best there are)  2,048 x 1,024: TransE 57 / 48, ComplEx softmax 50 / 47;
+//     1,024 x 4,096: 66 / 60, 72 / 59 (a long row of S is cheap, many rows are not)
+//   other rows  RotatE fp32 d 256: 512 x 1,024 71 / 40, 2,048 x 1,024 90 / 70, 1,024 x 4,096 109 / 99, 2,048 x 3,584 189 / 150, 512 x 8,192
+//     120 / 112;  ComplEx bf16 d 400: 75 / 37, 119 / 62, 130 / 84, 176 / 128, 140 / 100;  DistMult fp32 d 128: 45 / 32, 68 / 48, 71 / 67,
+//     81 / 86, 89 / 72
 // The scores of the largest block that qualifies take less memory than the split partials of the block kernels.
 struct SmallLimits { int64_t always, most; };           // pairs up to which every block is small, above which none is
 SmallLimits small_limits(const Geometry &g) {

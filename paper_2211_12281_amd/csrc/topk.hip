@@ -1160,7 +1160,7 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     // of their split: up to 128 in a row fit.
     constexpr int FIRST_TILES = 2;
     static_assert(FIRST_TILES * TK_ST / 2 <= TK_HALF, "the first chunk overflows no area");
-    // With many areas to a query (few queries) the chunks grow faster, up to 10 times what has been seen: a compaction is 16 us
+    // With many areas to a query (few queries) the chunks grow faster, up to 10 times what has been seen: a compaction is 16 to 20 us
     // of latency and a launch of the scan about 5, while the entries that come with the older threshold are few beside the
     // candidates.  Not beyond a mean of TK_HALF / 16 entries per area (more of them would fill up with clustered rows: the query
     // is then ranked exhaustively), which leaves calls of many queries at 4, nor beyond what the compaction's list holds; then
