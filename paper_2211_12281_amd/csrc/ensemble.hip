@@ -334,7 +334,7 @@ __global__ __launch_bounds__(256) void ens_top_kernel(const int32_t *lists, int 
         at_piece[i] = am << 8 | rank;
         t[i] = row[rank];
         const bool wrap = ac == 0;
-        ac = wrap ? ch - 1 : ac - 1;
+        ac = wrap && am < g ? 0 : wrap ? ch - 1 : ac - 1;       // (behind the last piece, the first ranks of list 0, that one again)
         if (wrap) {                                             // (a short first piece reaches back; past it the pieces stay there)
             row = am >= g ? row - down : row - am * QK;
             am = max(am - g, 0);

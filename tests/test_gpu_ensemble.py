@@ -120,3 +120,18 @@ def test_wave_kernel_and_the_queries_it_leaves(orc, M, K, K_out, spread, p, Q):
         lists[:, 6, 20:40] = lists[:, 6, :20]
     lists[:, 7] = -1
     _check(orc, np.ascontiguousarray(lists[:, np.arange(Q) % 13]), p, K_out)
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 6, 7, 16])
+@pytest.mark.parametrize("K", [100, 129, 150, 192, 193, 255])
+def test_wave_kernel_counts_an_entity_at_its_first_position(orc, M, K):
+    """A list that repeats one of its first entities in its 2nd, 3rd or 4th 64 ranks, in queries that repeat nothing else: list 0, which
+    is walked last, and list M - 1; lists of two, three and four pieces of 64 ranks, whose number leaves every remainder modulo 4."""
+    g = np.random.default_rng(100 * M + K)
+    lists = _agreeing(g, M, 13, K, 0.7)
+    at = [64, 65, 99, K - 1, K - 2, min(130, K - 1), min(191, K - 1), K // 2]
+    for q, k in enumerate(at):
+        lists[0, q, k] = lists[0, q, q % 3]
+    for q, k in enumerate(at[2:6]):
+        lists[M - 1, 8 + q, k] = lists[M - 1, 8 + q, 0]
+    _check(orc, np.ascontiguousarray(lists[:, np.arange(2060) % 13]), -1.0, 10)
