@@ -302,11 +302,11 @@ __global__ __launch_bounds__(256) void ens_top_kernel(const int32_t *lists, int 
 #pragma unroll
     for (int i = 0; i < T::BUCKETS / 64; ++i) ((int4 *)tab)[i * 64 + lane] = make_int4(-2, -2, -2, -2);
     {
-        int all = C * (sizeof(Idx) == 1 ? 0x01010101 : 0x00010001);
+        const int all = (int)((uint32_t)C * (sizeof(Idx) == 1 ? 0x01010101u : 0x00010001u));
 #pragma unroll
         for (int i = 0; i < T::BUCKETS * (int)sizeof(Idx) / 64; ++i) ((int *)num)[i * 64 + lane] = all;
     }
-    const int none = K * 0x01010101;
+    const int none = (int)((uint32_t)K * 0x01010101u);
     for (int i = lane; i < (C + 4) / 4 * words; i += 64) ((int4 *)rk)[i] = make_int4(none, none, none, none);
     __syncthreads();
     const int64_t q = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
