@@ -329,19 +329,22 @@ __global__ __launch_bounds__(256) void ens_top_kernel(const int32_t *lists, int 
     int am = M - g, ac = ch - 1;                                // next piece to request: (first) list, 64 ranks
     const int32_t *row = at_lane + am * QK;
     const int64_t down = g * QK;
-    auto request = [&](int i) {
+    auto request = [&](int i, bool again) {
         const int rank = min(ac * 64, max(K - 64, 0));
         at_piece[i] = am << 8 | rank;
         t[i] = row[rank];
+        if (again) return;
         const bool wrap = ac == 0;
-        ac = wrap && am < g ? 0 : wrap ? ch - 1 : ac - 1;       // (behind the last piece, the first ranks of list 0, that one again)
+        ac = wrap ? ch - 1 : ac - 1;
         if (wrap) {                                             // (a short first piece reaches back; past it the pieces stay there)
             row = am >= g ? row - down : row - am * QK;
             am = max(am - g, 0);
         }
     };
+    // (the walk has to end with the last piece, the first ranks of list 0: what is missing to whole rings, the first piece makes up for)
+    const int extra = -pieces & (RING - 1);
 #pragma unroll
-    for (int i = 0; i < RING; ++i) request(i);
+    for (int i = 0; i < RING; ++i) request(i, i < extra);
 
     // ---- 1. candidates: the entities of the first ranks, rank by rank ----
     // (64 / M ranks at a time, or 64 models of one; every lane has an entry here too, ranks past R do no harm)
@@ -403,7 +406,6 @@ __global__ __launch_bounds__(256) void ens_top_kernel(const int32_t *lists, int 
         for (int done = 0; done < pieces; done += RING) {
 #pragma unroll
             for (int h = 0; h < RING; h += U) {
-                if (h > 0 && done + h >= pieces) break;
                 int x[U], k[U], at[U], b[U], s[U];
                 int4 v[U];
 #pragma unroll
@@ -414,7 +416,7 @@ __global__ __launch_bounds__(256) void ens_top_kernel(const int32_t *lists, int 
                     k[i] = (at_piece[h + i] & 255) + sk; at[i] = (at_piece[h + i] >> 8) + sub;
                 }
 #pragma unroll
-                for (int i = 0; i < U; ++i) request(h + i);
+                for (int i = 0; i < U; ++i) request(h + i, false);
                 int full = 0;                                   // (not found in a full bucket: the entity may lie in the next)
 #pragma unroll
                 for (int i = 0; i < U; ++i) {
