@@ -298,6 +298,7 @@ __global__ __launch_bounds__(256) void ens_top_kernel(const int32_t *lists, int 
     uint32_t *rk = (uint32_t *)(own + T::TABLE);                // [C + 4][words] ranks, a byte per model, K: absent
     uint8_t *rkb = (uint8_t *)rk;
     const int words = T::words(M), pitch = words * 4;
+    const bool dense = tm.absent != 0.0;                        // absent models contribute (p > 0)
     for (int i = tid; i <= K; i += blockDim.x) terms[i] = i == K ? tm.absent : tm.rank[i];
 #pragma unroll
     for (int i = 0; i < T::BUCKETS / 64; ++i) ((int4 *)tab)[i * 64 + lane] = make_int4(-2, -2, -2, -2);
@@ -348,11 +349,12 @@ __global__ __launch_bounds__(256) void ens_top_kernel(const int32_t *lists, int 
 
     // ---- 1. candidates: the entities of the first ranks, rank by rank ----
     // (64 / M ranks at a time, or 64 models of one; every lane has an entry here too, ranks past R do no harm)
-    int n = 0, r = R;
+    int n = 0, r = R, walked;
     {
         constexpr int DEEP = 4;
         const int per = M < 64 ? min(64 / M, K) : 1, mch = (M + 63) / 64;
         const int ik = M < 64 && lane < per * M ? lane / M : 0, im = M >= 64 ? lane : lane < per * M ? lane - ik * M : 0;
+        walked = min((R + per - 1) / per * per, K);
         const int32_t *mine = base + im * QK + ik;
         int k0 = 0, mc = 0;                                     // next to request: (first) rank, 64 models
         int in[DEEP], low[DEEP];
@@ -387,14 +389,15 @@ __global__ __launch_bounds__(256) void ens_top_kernel(const int32_t *lists, int 
                     num[at] = (Idx)(c < C ? c : C);
                 }
                 n += __popcll(fresh);
-                if (n > C) { n = C; r = at_rank; more = false; break; }         // (this rank is not whole)
+                if (n > C) { n = C; r = walked = at_rank; more = false; break; }         // (this rank is not whole)
             }
         }
     }
-    // (models that do not agree fill the table before two thirds of the R ranks, and the proof fails as a rule: 16 lists of 100 drawn at
-    // random from pools of 260, ten winners of 8,192 queries: 157 us with the rest of this kernel, 134 without, 100 with ens_kernel alone;
-    // 64 lists, 4,096 queries 786 / 639 / 623)
-    if (r < K && (n < K_out || 3 * r < 2 * R)) {
+    // Models that do not agree: the proof fails as a rule where the table is full before five sixths of the R ranks, and for p > 0 where
+    // the walked ranks name the same entities too seldom (less than 1.4 (1 - 1 / M) repeats per winner and further model; agreeing models:
+    // 1.5 to 2.4).  Those queries leave here (8 lists of 50 at random from pools of 125, p = 1, 8,192 queries: 103 us without the second
+    // test, 88 with it, 47 with ens_kernel alone; 16 of 100 from pools of 250, p = -1: 138 with a line at two thirds of R, 117).
+    if (r < K && (n < K_out || 6 * r < 5 * R || (dense && 5 * M * (M * walked - n) < 7 * (M - 1) * (M - 1) * K_out))) {
         if (lane == 0) out_idx[q * K_out] = ENS_FLAG;
         return;
     }
@@ -586,10 +589,14 @@ int kge_run_ensemble(const int32_t *lists, int M, int64_t Q, int K, double p, in
     // (models that agree roughly: ten winners of 10^2 queries needed the first 9 to 14 ranks for p < 0, 12 to 20 for p = 1)
     const int want = p > 0.0 ? (K_out * 5 + 1) / 2 : (K_out * 3 + 1) / 2, R = want < K ? want : K;
     const int per_cu = ENS_CU_LDS / (lds + 4096) < 1 ? 1 : ENS_CU_LDS / (lds + 4096) > 8 ? 8 : ENS_CU_LDS / (lds + 4096);
-    // A wave per query costs a second, nearly empty launch (4.6 us, 3 us of the caller's time) and has the longer chain for one
-    // query (64 lists of 100: 42 us against 37): queries that ens_kernel holds all at once stay there (16 lists of 100: 1,024
-    // queries 15.5 against 18.1 us, 2,048 27.6 against 19.6; 64 lists: 256 36.9 / 42, 512 75 / 42), but for short lists taken
-    // whole (32 lists of 10: 14.9 / 14.3 us for 128 queries, 25.3 / 17.2 for 2,048; 100 winners of 16 lists of 50: 40.1 / 36.6)
+    // A wave per query costs a second, nearly empty launch (4.6 us, 3 us of the caller's time), has the longer chain for one query (64 lists
+    // of 100: 42 us against 37), and what it can't prove is done twice.  So the line lies where agreeing models gain: queries that ens_kernel
+    // holds all at once stay there, but for short lists taken whole (32 lists of 10: 14.9 / 14.3 us for 128 queries, 25.3 / 17.2 for
+    // 2,048; 100 winners of 16 lists of 50: 40.1 / 36.6).  ens_kernel / here, us, ten winners, p = -1 and 1, agreeing models:  16 lists of
+    // 100: 2,500 queries 33 / 27, 75 / 31, 8,192 queries 99 / 40, 209 / 47;  8 of 50: 2,500 queries 16 / 16, 20 / 19, 8,192 queries 39 / 24, 47 / 28.
+    // Models that do not agree LOSE by it - nothing known before the launch tells them apart -: lists drawn at random from pools 2.5 times as
+    // long, 8,192 queries: 16 of 100 100 / 117, 187 / 209;  8 of 50 40 / 26, 47 / 88;  16 of 200 302 / 320, 565 / 585;  64 of 100, 4,096
+    // queries 622 / 638, 1,249 / 1,266.
     const int cpl = (R == K && K <= 64) || Q > 256 * per_cu ? ens_candidates(M, K, R) : 0;
     if (cpl == 0) {
         hipLaunchKernelGGL(ens_kernel, dim3((unsigned)Q), dim3(256), lds, st, lists, M, Q, K, slots, shift, tm, K_out, out_idx, out_score);
@@ -607,7 +614,7 @@ int kge_run_ensemble(const int32_t *lists, int M, int64_t Q, int K, double p, in
 #undef ENS_TOP
     if (kge_launch_status() != KGE_OK) return KGE_E_HIP;
     if (R == K && M * K <= 64 * cpl) return KGE_OK;             // (every list whole and every entity in the table: nothing is ever flagged)
-    const int64_t most = 256 * per_cu;
+    const int64_t most = 256 * (per_cu < 6 ? per_cu : 6);         // (its registers allow six)
     hipLaunchKernelGGL(ens_flagged_kernel, dim3((unsigned)(Q < most ? Q : most)), dim3(256), lds, st, lists, M, Q, K, slots, shift, tm, K_out,
                        out_idx, out_score);
     return kge_launch_status();

@@ -134,4 +134,4 @@ def test_wave_kernel_counts_an_entity_at_its_first_position(orc, M, K):
         lists[0, q, k] = lists[0, q, q % 3]
     for q, k in enumerate(at[2:6]):
         lists[M - 1, 8 + q, k] = lists[M - 1, 8 + q, 0]
-    _check(orc, np.ascontiguousarray(lists[:, np.arange(2060) % 13]), -1.0, 10)
+    _check(orc, np.ascontiguousarray(lists[:, np.arange(2060) % 13]), -1.0, 10)     # (one wave per query from 2,049 queries on, or fewer)
