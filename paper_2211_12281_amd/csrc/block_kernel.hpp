@@ -189,7 +189,7 @@ struct KgeBlockCfg {
     static constexpr bool PL = kge_block_planes(BF16, RB, MODE);
     static constexpr int PLANE = ST * DP * 2;
     // groups of fragments requested together: what the registers hold without scratch
-    static constexpr int PL_CHUNK = TRANSH ? 4 : RB == 512 && OWN_ROW && KIND == KGE_KIND_DIST ? 1 : 2;
+    static constexpr int PL_CHUNK = TRANSH ? 4 : OWN_ROW && KIND == KGE_KIND_DIST ? 1 : 2;
     static constexpr int X_BYTES = PL ? 2 * PLANE : ST * RB;    // else [ST rows][RB bytes], chunk c of row r at c ^ (r & 7)
     static constexpr int XT_ROWB = ST * ES;                // one transposed row: ST stream entries (64 or 128 bytes)
     static constexpr int XT_BYTES = DP * XT_ROWB;
@@ -255,7 +255,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
     uint4 ownw[(TRANSH && OWN_ROW && !PL) ? C::KS : 1];
     // the own operand as fp16 pieces, sixteen contraction indices per entry
     constexpr bool WL = C::WL;
-    static_assert(!PL || OW == 1, "");
+    static_assert(!PL || (OW == 1 && DSPLIT == 1), "");
     KgeP2 own2p[PL ? C::KS / 2 : 1];
     float o_inv = 1.f;                                    // PL: 1 / scale of the own row
     float o_qn[OW], o_c[OW], o_wn[OW], o_tn[OW];          // own-side scalars
@@ -401,15 +401,16 @@ void kge_block_kernel(const KgeBlockArgs a) {
     // PL: chunk (2 k2 + g) of row lr of a plane; and the transpose reads: source lane i of a group of sixteen points at row
     // 16 j2 + 8 hh + 4 g + i / 4, columns 32 blk + 16 q16 + 4 (i % 4) .. + 3, and lane l receives column 32 blk + l % 32 of the rows
     // 16 j2 + 8 hh + 4 g .. + 3 - the streamed rows of its coefficients 8 j2 + 4 hh .. + 3
-    int pl_frag[PL ? C::KS / 2 : 1], pl_tr[2][PL ? C::NB : 1];
+    // (rows of 512 bytes in a plane: the swizzle leaves the upper bit of the chunk alone, so the second half of the row is 256 bytes on)
+    int pl_frag[8], pl_tr[2][4];
     if constexpr (PL) {
         const int i16 = lane & 15, q16 = (lane >> 4) & 1;
 #pragma unroll
-        for (int k2 = 0; k2 < C::KS / 2; ++k2) pl_frag[k2] = lr * (C::DP * 2) + ((2 * k2 + g) ^ kge_pl_swz(lr)) * 16;
+        for (int k2 = 0; k2 < 8; ++k2) pl_frag[k2] = lr * (C::DP * 2) + ((2 * k2 + g) ^ kge_pl_swz(lr)) * 16;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-            for (int b = 0; b < C::NB; ++b) {
+            for (int b = 0; b < 4; ++b) {
                 const int row = 8 * hh + 4 * g + (i16 >> 2);
                 pl_tr[hh][b] = row * (C::DP * 2) + ((4 * b + 2 * q16 + ((i16 & 3) >> 1)) ^ kge_pl_swz(row)) * 16 + (i16 & 1) * 8;
             }
@@ -474,9 +475,9 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 const int k2 = grp * (G1 / 2) + k;
 #pragma unroll
                 for (int pl = 0; pl < 2; ++pl) {
-                    xp[k2].p[pl] = *(const uint4 *)(stage + pl_frag[k2] + pl * C::PLANE);
-                    if constexpr (WL) owp[k2].p[pl] = *(const uint4 *)(own_w + pl_frag[k2] + pl * C::PLANE);
-                    if constexpr (HASW) xwp[k2].p[pl] = *(const uint4 *)(stage + C::X_BYTES + pl_frag[k2] + pl * C::PLANE);
+                    xp[k2].p[pl] = *(const uint4 *)(stage + pl_frag[k2 & 7] + (k2 >> 3) * 256 + pl * C::PLANE);
+                    if constexpr (WL) owp[k2].p[pl] = *(const uint4 *)(own_w + pl_frag[k2 & 7] + (k2 >> 3) * 256 + pl * C::PLANE);
+                    if constexpr (HASW) xwp[k2].p[pl] = *(const uint4 *)(stage + C::X_BYTES + pl_frag[k2 & 7] + (k2 >> 3) * 256 + pl * C::PLANE);
                 }
             }
             return;
@@ -522,9 +523,9 @@ void kge_block_kernel(const KgeBlockArgs a) {
             auto frag = [&](const char *s, int blk, int j2, KgeP2 &x) {
 #pragma unroll
                 for (int pl = 0; pl < 2; ++pl) {
-                    const char *q = s + pl * C::PLANE + j2 * (16 * C::DP * 2);
-                    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((kge_i16x4 __attribute__((address_space(3))) *)(q + pl_tr[0][dblk0 + blk])));
-                    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((kge_i16x4 __attribute__((address_space(3))) *)(q + pl_tr[1][dblk0 + blk])));
+                    const char *q = s + pl * C::PLANE + j2 * (16 * C::DP * 2) + (blk >> 2) * 256;
+                    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((kge_i16x4 __attribute__((address_space(3))) *)(q + pl_tr[0][blk & 3])));
+                    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((kge_i16x4 __attribute__((address_space(3))) *)(q + pl_tr[1][blk & 3])));
                     x.p[pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
                 }
             };
