@@ -109,7 +109,7 @@ __device__ __forceinline__ kge_f32x16 kge_mma3(kge_f32x16 acc, const KgeP3 &A, c
     return acc;
 }
 
-// Two fp16 pieces of a value scaled by a power of two (kge_plane_scale: rows; coefficients below): x = x0 + x1 to 2^-23 of the largest
+// Two fp16 pieces of a value scaled by a power of two (kge_plane_exp: rows; coefficients below): x = x0 + x1 to 2^-23 of the largest
 // value that shares the scale, three products per pair, a0 b0 + a0 b1 + a1 b0 (a1 b1 <= 2^-24 |a| |b| is left out).
 struct KgeP2 { uint4 p[2]; };
 typedef _Float16 kge_f16x8 __attribute__((ext_vector_type(8)));
@@ -257,7 +257,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
     constexpr bool WL = C::WL;
     static_assert(!PL || (OW == 1 && DSPLIT == 1), "");
     KgeP2 own2p[PL ? C::KS / 2 : 1];
-    float o_inv = 1.f;                                    // PL: 1 / scale of the own row
+    int o_exp = 0;                                        // PL: exponent of 1 / scale of the own row
     float o_qn[OW], o_c[OW], o_wn[OW], o_tn[OW];          // own-side scalars
 #pragma unroll
     for (int h = 0; h < OW; ++h) {
@@ -268,7 +268,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
             for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
                 for (int k2 = 0; k2 < C::KS / 2; ++k2) own2p[k2].p[pl] = *(const uint4 *)(p + pl * own_plane + k2 * 32);
-            o_inv = a.own_inv[oidx];
+            o_exp = a.own_exp[oidx];
         } else {
             const char *p = (const char *)a.own + (size_t)oidx * RB + g * 16;
 #pragma unroll
@@ -387,11 +387,11 @@ void kge_block_kernel(const KgeBlockArgs a) {
         }
         // side info of the tile's 32 stream rows, one private copy per wave
         const uint32_t sside = lds0 + C::NSTAGE * C::STAGE_BYTES + (slot % C::SIDE_SLOTS) * C::SIDE_SLOT;
-        // (PL: the second half of the copy are the rows' 1 / scale)
+        // (PL: the second half of the copy are the rows' exponents)
         if constexpr (OWN_ROW)
-            kge_async_copy4((PL && g ? a.str_inv : a.tn) + tile * C::ST + lr, __builtin_amdgcn_readfirstlane(sside + wave * 256));
+            kge_async_copy4(PL && g ? (const void *)(a.str_exp + tile * C::ST + lr) : (const void *)(a.tn + tile * C::ST + lr), __builtin_amdgcn_readfirstlane(sside + wave * 256));
         else
-            kge_async_copy16(PL && g ? (const void *)(a.str_inv + tile * C::ST + 4 * (lr & 7)) : (const void *)(a.rowinfo + tile * C::ST + lr),
+            kge_async_copy16(PL && g ? (const void *)(a.str_exp + tile * C::ST + 4 * (lr & 7)) : (const void *)(a.rowinfo + tile * C::ST + lr),
                              __builtin_amdgcn_readfirstlane(sside + wave * 1024));
     };
     // fragment addresses inside a stage: chunk (2 ks + g) of row lr sits at position chunk ^ (lr & 7)
@@ -431,7 +431,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                     uint4 &v = own2p[k2].p[pl];
                     asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
                 }
-            asm volatile("" : "+v"(o_inv));
+            asm volatile("" : "+v"(o_exp));
         } else {
 #pragma unroll
             for (int ks = 0; ks < C::KS; ++ks) {
@@ -583,7 +583,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
         }
     };
     // ---- epilogue: scores / loss weights / gradient coefficients of the tile, element by element ----
-    auto str_inv_of = [&](int sl) { return *(const float *)(side + (OWN_ROW ? 128 : 512) + sl * 4); };     // PL: 1 / scale of a streamed row
+    auto str_exp_of = [&](int sl) { return *(const int *)(side + (OWN_ROW ? 128 : 512) + sl * 4); };       // PL: exponent of 1 / scale of a streamed row
     // scores of own fragment h against the tile (SCORE mode stores them), 1/distance, w.t
     auto scores = [&](int h, float (&sv)[16], float (&dv)[16], float (&Av)[16]) {
         const int oidx = oidx0 + 32 * h;
@@ -592,9 +592,9 @@ void kge_block_kernel(const KgeBlockArgs a) {
         if constexpr (PL) {                                // (exact: powers of two)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const float s_inv = str_inv_of(8 * (i >> 2) + 4 * g + (i & 3));
-                acc[0][i] *= o_inv * s_inv;
-                if constexpr (TRANSH) accw[i] *= (OWN_ROW ? s_inv : o_inv) * (1.f / KGE_PLANE_UNIT_SCALE);
+                const int s_exp = str_exp_of(8 * (i >> 2) + 4 * g + (i & 3));
+                acc[0][i] = ldexpf(acc[0][i], o_exp + s_exp);
+                if constexpr (TRANSH) accw[i] = ldexpf(accw[i], (OWN_ROW ? s_exp : o_exp) + KGE_PLANE_UNIT_EXP);
             }
         }
         if constexpr (KIND == KGE_KIND_MULT) {
@@ -751,10 +751,10 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 float cm = 0.f;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const float s_inv = str_inv_of(8 * (i >> 2) + 4 * g + (i & 3));
-                    coef[i] *= s_inv;
+                    const int s_exp = str_exp_of(8 * (i >> 2) + 4 * g + (i & 3));
+                    coef[i] = ldexpf(coef[i], s_exp);
                     cm = fmaxf(cm, fabsf(coef[i]));
-                    if constexpr (TRANSH) { coef2[i] *= OWN_ROW ? s_inv : 1.f / KGE_PLANE_UNIT_SCALE; cm = fmaxf(cm, fabsf(coef2[i])); }
+                    if constexpr (TRANSH) { coef2[i] = ldexpf(coef2[i], OWN_ROW ? s_exp : KGE_PLANE_UNIT_EXP); cm = fmaxf(cm, fabsf(coef2[i])); }
                 }
                 cm = fmaxf(cm, __shfl_xor(cm, 32));        // (lanes l and l ^ 32 feed the same row)
                 const bool trip = cm * c_scale > 16384.f || (c_scale == 0.f && cm > 0.f);

@@ -185,7 +185,8 @@ struct Buffers {
                                        // its place; the queries unrounded [Bp][dp]
     float *W32, *A, *P;                // ... TransH: the unit normals unrounded, w^ . t and sign(x) . w^ per pair [Bp][Np]
     void *Qp2, *Tp2;                   // score-only calls on fp32 tables, Geometry::planes: two fp16 planes of the scaled Q (TransH: and of W) and T
-    float *t_inv, *q_inv;              // ... 1 / scale of the rows of T (and of Q)
+    float *t_inv;                      // ... score-only calls: 1 / scale of the rows of T
+    int32_t *q_exp, *t_exp;            // ... training calls: exponents of 1 / scale of the rows of Q and T
     void *pstore, *Qs;                 // sampled softmax on the kernels of block_sym.hip / block_gradp.hip: the weights of the
                                        // forward pass [Bp x Np bf16, in records], the queries scaled per forward split [nsplit_q][Bp][dp]
     float *nbias;                      // training calls: 0 for each of the N negatives, -inf for the padding rows behind them
@@ -203,10 +204,11 @@ size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
     b.Q32 = g.l1 ? c.take<float>(rowsB) : nullptr;
     b.W32 = g.l1 && g.transh ? c.take<float>(rowsB) : nullptr;
     b.A = b.P = nullptr;
-    b.Qp2 = b.Tp2 = nullptr; b.t_inv = b.q_inv = nullptr;
+    b.Qp2 = b.Tp2 = nullptr; b.t_inv = nullptr; b.q_exp = b.t_exp = nullptr;
     if (bwd ? g.planes : score_h2_applies(g)) {
-        b.Qp2 = c.take<char>((g.transh ? 4 : 2) * rowsB * 2); b.Tp2 = c.take<char>(2 * rowsN * 2); b.t_inv = c.take<float>(g.Np);
-        if (bwd) b.q_inv = c.take<float>(g.Bp);
+        b.Qp2 = c.take<char>((g.transh ? 4 : 2) * rowsB * 2); b.Tp2 = c.take<char>(2 * rowsN * 2);
+        if (bwd) { b.t_exp = c.take<int32_t>(g.Np); b.q_exp = c.take<int32_t>(g.Bp); }
+        else b.t_inv = c.take<float>(g.Np);
     }
     b.Q2 = nullptr; b.Qt = b.Wt = b.Tt = nullptr; b.lossb = b.gpos = nullptr; b.stat_part = nullptr;
     b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.nbias = nullptr;
@@ -522,7 +524,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     if (plain_gather) {
         KgeProfScope prof(KGE_PROF_GATHER, st);
         rc = kge_run_qbuild_tgather(md, h, r, t, g.B, g.Bp, g.dp, b.Q, b.W, b.Q2, b.Q32, b.W32, b.rowinfo, b.pos,
-                                    neg, g.N, g.Np, b.T, b.tn, st, nullptr, b.Qp2, b.Tp2, b.t_inv, b.nbias, gen, b.q_inv);
+                                    neg, g.N, g.Np, b.T, b.tn, st, nullptr, b.Qp2, b.Tp2, nullptr, b.nbias, gen, b.q_exp, b.t_exp);
     }
     else rc = kge_run_qbuild(md, h, r, t, g.B, g.Bp, g.dp, b.Q, b.W, b.Q2, b.Q32, b.W32, b.rowinfo, b.pos, nullptr, st);
     if (rc != KGE_OK) return rc;
@@ -546,7 +548,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
         a.own = b.Q; a.own2 = b.W; a.str = b.T;
         if (g.planes) {
             a.own = b.Qp2; a.own2 = g.transh ? (const char *)b.Qp2 + (size_t)4 * g.Bp * g.dp : nullptr; a.str = b.Tp2;
-            a.own_inv = b.q_inv; a.str_inv = b.t_inv; a.own32 = (const float *)b.Q; a.str32 = (const float *)b.T; a.w32 = (const float *)b.W;
+            a.own_exp = b.q_exp; a.str_exp = b.t_exp; a.own32 = (const float *)b.Q; a.str32 = (const float *)b.T; a.w32 = (const float *)b.W;
         }
         a.strT = b.Tt; a.strT_ld = g.Np; a.rowinfo = b.rowinfo; a.tn = b.tn;
         a.B = g.B; a.N = g.N; a.dp = g.dp; a.str_tiles = g.str_tiles_n; a.tiles_per_split = g.tps_q;
@@ -593,7 +595,7 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
     } else if (have_block) {
         // pass 2 (column owner): gradient of the shared negatives from the finished row constants
         KgeBlockArgs c = a;
-        c.own = a.str; c.own2 = nullptr; c.str = a.own; c.str2 = a.own2; c.own_inv = a.str_inv; c.str_inv = a.own_inv; c.own32 = a.str32;
+        c.own = a.str; c.own2 = nullptr; c.str = a.own; c.str2 = a.own2; c.own_exp = a.str_exp; c.str_exp = a.own_exp; c.own32 = a.str32;
         c.str32 = a.own32; c.strT = b.Qt; c.strT2 = b.Wt; c.strT_ld = g.Bp;
         c.str_tiles = g.str_tiles_b; c.tiles_per_split = g.tps_t;
         c.acc_part = b.acct; c.acc_part2 = nullptr; c.sum_part = b.sumt; c.stat_part = nullptr; c.own_pad = g.Np;

@@ -46,7 +46,9 @@ static inline int64_t kge_round_up(int64_t x, int64_t m) { return (x + m - 1) / 
 constexpr int KGE_STREAM_TILE = 32;   // rows streamed through LDS per iteration
 constexpr int KGE_PAD = 256;          // B and N are padded to this in the workspace copies
 
-constexpr float KGE_PLANE_UNIT_SCALE = 1024.f;      // scale of the planes of TransH's unit normals (all rows)
+constexpr float KGE_PLANE_UNIT_SCALE = 1024.f;      // scale of the planes of TransH's unit normals (all rows), score-only calls
+// training calls: rows are scaled to a largest element in [2^(KGE_PLANE_TOP - 1), 2^KGE_PLANE_TOP), unit normals by 2^-KGE_PLANE_UNIT_EXP
+constexpr int KGE_PLANE_TOP = 11, KGE_PLANE_UNIT_EXP = -10;
 
 enum { KGE_MODE_SCORE = 0, KGE_MODE_FWD = 1, KGE_MODE_GRADT = 2 };
 enum { KGE_KIND_MULT = 0, KGE_KIND_DIST = 1 };
@@ -121,9 +123,10 @@ inline int kge_place_plan(int own_tiles, int nsplit, int own_rows, int64_t str_r
 }
 
 struct KgeBlockArgs {
-    // (kge_block_planes: own, own2, str, str2 are fp16 planes [2][own_pad or 32 str_tiles][dp] of rows scaled by 1 / own_inv, 1 / str_inv -
-    // the normals by KGE_PLANE_UNIT_SCALE -, own32, str32 and w32 the fp32 rows; there are no transposed copies)
-    const float *own_inv, *str_inv, *own32, *str32, *w32;
+    // (kge_block_planes: own, own2, str, str2 are fp16 planes [2][own_pad or 32 str_tiles][dp] of rows times 2^-own_exp, 2^-str_exp -
+    // the normals times 2^-KGE_PLANE_UNIT_EXP -, own32, str32 and w32 the fp32 rows; there are no transposed copies)
+    const int32_t *own_exp, *str_exp;
+    const float *own32, *str32, *w32;
     const void *own, *own2;        // [own_pad][dp]; own2: TransH normals when OWN_ROW
     const void *str, *str2;        // [str_pad][dp]; str2: TransH normals when !OWN_ROW
     const void *strT, *strT2;      // [dp][strT_ld] transposed stream operand(s), GRAD only

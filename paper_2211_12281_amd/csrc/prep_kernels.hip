@@ -70,10 +70,10 @@ struct KgeQbuildArgs {
     float *pos_ws, *pos_out;
     _Float16 *planes;                  // optional: the two fp16 pieces of the scaled q, [2][Bp][dp], with W two more for the
                                        // unit normal (scaled by KGE_PLANE_UNIT_SCALE); then rowinfo.K = 1 / scale of the row
-    float *inv_scale;                  // optional: 1 / scale of the rows [Bp]
+    int32_t *exps;                     // with planes, training: the exponents of the rows' 1 / scale [Bp] (kge_plane_exp; unit normals: KGE_PLANE_UNIT_EXP)
 };
 struct KgeTgatherArgs {
-    const int32_t *neg; int N, Np; void *T; float *tn; _Float16 *planes; float *inv_scale; float *bias;
+    const int32_t *neg; int N, Np; void *T; float *tn; _Float16 *planes; float *inv_scale; int32_t *exps; float *bias;
     KgeNegGen gen;                     // gen.out set: the ids are drawn here (and written to gen.out) instead of read from neg
 };
 
@@ -88,6 +88,20 @@ __device__ __forceinline__ float kge_plane_scale(float amax, float &inv) {
     e = e < -115 ? -115 : (e > 128 ? 128 : e);              // (the scale and its reciprocal are normal numbers)
     inv = ldexpf(1.f, e - 11);
     return ldexpf(1.f, 11 - e);
+}
+// The training passes: the row is 2^e times its planes, e an integer, so every fp32 row has one (a product of two rows' scales is no
+// fp32 number where both are tiny or one is huge).  A row that holds an infinity: its finite elements count for nothing beside it, and
+// +-2^15 times 2^235 is an infinity in every product with a value of 2^-122 or more (inf - fp16(inf) would make the whole row NaN).
+__device__ __forceinline__ int kge_plane_exp(float amax) {
+    if (!(amax > 0.f)) return 0;
+    if (amax == INFINITY) return 235;
+    int e;
+    (void)frexpf(amax, &e);
+    return e - KGE_PLANE_TOP;
+}
+__device__ __forceinline__ float kge_plane_scaled(float x, int e) {
+    x = ldexpf(x, -e);
+    return fabsf(x) == INFINITY ? copysignf(32768.f, x) : x;
 }
 __device__ __forceinline__ void kge_store_planes(_Float16 *planes, int64_t n, int64_t i, float xs) {
     const _Float16 x1 = (_Float16)xs;
@@ -115,7 +129,7 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
             if (a.planes) kge_store_planes(a.planes, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
             if (a.planes && W) kge_store_planes(a.planes + 2 * (int64_t)Bp * dp, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
         }
-        if (lane == 0) { rowinfo[b] = KgeRowInfo{0.f, 0.f, a.planes ? 1.f : 0.f, 0.f}; if (pos_ws) pos_ws[b] = 0.f; if (a.inv_scale) a.inv_scale[b] = 1.f; }
+        if (lane == 0) { rowinfo[b] = KgeRowInfo{0.f, 0.f, a.planes ? 1.f : 0.f, 0.f}; if (pos_ws) pos_ws[b] = 0.f; if (a.exps) a.exps[b] = 0; }
         return;
     }
     KgeRowCtx<BF16, NJ> cx;
@@ -127,12 +141,15 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
     float s_pos = 0.f, wt = 0.f;
     float tv[NJ];
     float q_scale = 1.f, q_inv = 0.f;
+    int q_exp = 0;
     if (a.planes) {
         float amax = 0.f;
 #pragma unroll
         for (int k = 0; k < NJ; ++k) amax = fmaxf(amax, fabsf(cx.q[k]));
-        q_scale = kge_plane_scale(kge_wave_max(amax), q_inv);
+        amax = kge_wave_max(amax);
+        if (a.exps) q_exp = kge_plane_exp(amax); else q_scale = kge_plane_scale(amax, q_inv);
     }
+    const float w_scale = a.exps ? ldexpf(1.f, -KGE_PLANE_UNIT_EXP) : KGE_PLANE_UNIT_SCALE;
 #pragma unroll
     for (int k = 0; k < NJ; ++k) {
         const int j = lane + 64 * k;
@@ -146,9 +163,9 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
             if (W) El<BF16>::st(W, (int64_t)b * dp + j, cx.w[k]);
             if (Q32) Q32[(int64_t)b * dp + j] = cx.q[k];      // unrounded copies for the 1-norm kernels
             if (W32) W32[(int64_t)b * dp + j] = cx.w[k];
-            if (a.planes) kge_store_planes(a.planes, (int64_t)Bp * dp, (int64_t)b * dp + j, q_scale * cx.q[k]);
+            if (a.planes) kge_store_planes(a.planes, (int64_t)Bp * dp, (int64_t)b * dp + j, a.exps ? kge_plane_scaled(cx.q[k], q_exp) : q_scale * cx.q[k]);
             if (a.planes && W)
-                kge_store_planes(a.planes + 2 * (int64_t)Bp * dp, (int64_t)Bp * dp, (int64_t)b * dp + j, KGE_PLANE_UNIT_SCALE * cx.w[k]);
+                kge_store_planes(a.planes + 2 * (int64_t)Bp * dp, (int64_t)Bp * dp, (int64_t)b * dp + j, w_scale * cx.w[k]);
         }
     }
     qn = kge_wave_sum(qn);
@@ -174,7 +191,7 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
     if (!(SC == KGE_DISTMULT || SC == KGE_COMPLEX)) s_pos = m.p1 ? -s_pos : -sqrtf(s_pos);
     if (lane == 0) {
         rowinfo[b] = KgeRowInfo{(float)qn, (float)cq, q_inv, SC == KGE_TRANSH ? (float)wn : 1.f};     // (K: set by the row finish when training)
-        if (a.inv_scale) a.inv_scale[b] = q_inv;
+        if (a.exps) a.exps[b] = q_exp;
         if (pos_ws) pos_ws[b] = s_pos;
         if (pos_out) pos_out[b] = s_pos;
     }
@@ -198,7 +215,7 @@ __host__ __device__ inline int kge_tgather_rows_per_wave(int dp, int es) { retur
 template <bool BF16>
 __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T,
                                                  float *tn, _Float16 *planes = nullptr, float *inv_scale = nullptr,
-                                                 const KgeNegGen *gen = nullptr) {
+                                                 const KgeNegGen *gen = nullptr, int32_t *exps = nullptr) {
     const int lane = threadIdx.x & 63;
     const bool draw = gen && gen->out;
     uint32_t step = 0;
@@ -258,20 +275,21 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
             if (lg == 0 && n < Np) tn[n] = (float)s;
             if constexpr (!BF16) {
                 if (planes) {
-                    float inv;
-                    const float sc = kge_plane_scale(amax, inv);
+                    float inv = 0.f;
+                    const int e = exps ? kge_plane_exp(amax) : 0;
+                    const float sc = exps ? 0.f : kge_plane_scale(amax, inv);
                     if (live) {                         // the lane's four elements: one 8-byte store per plane
                         typedef _Float16 h4 __attribute__((ext_vector_type(4)));
                         h4 p1, p2;
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
-                            const float xs = sc * __uint_as_float(w[k]);
+                            const float x = __uint_as_float(w[k]), xs = exps ? kge_plane_scaled(x, e) : sc * x;
                             p1[k] = (_Float16)xs; p2[k] = (_Float16)(xs - (float)p1[k]);
                         }
                         _Float16 *dst = planes + (int64_t)n * dp + lg * 4;
                         *(h4 *)dst = p1; *(h4 *)(dst + (int64_t)Np * dp) = p2;
                     }
-                    if (lg == 0 && n < Np) inv_scale[n] = inv;
+                    if (lg == 0 && n < Np) { if (exps) exps[n] = e; else inv_scale[n] = inv; }
                 }
             }
         }
@@ -296,13 +314,15 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
         s = kge_wave_sum(s);
         if (lane == 0) tn[n] = (float)s;
         if (!BF16 && planes) {                              // (second walk over the row, now that its scale is known)
-            float inv;
-            const float sc = kge_plane_scale(kge_wave_max(amax), inv);
+            float inv = 0.f;
+            amax = kge_wave_max(amax);
+            const int e = exps ? kge_plane_exp(amax) : 0;
+            const float sc = exps ? 0.f : kge_plane_scale(amax, inv);
             for (int j = lane; j < dp; j += 64) {
                 const float v = (n < N && j < m.dim) ? El<BF16>::ld(m.ent, off + j) : 0.f;
-                kge_store_planes(planes, (int64_t)Np * dp, (int64_t)n * dp + j, sc * v);
+                kge_store_planes(planes, (int64_t)Np * dp, (int64_t)n * dp + j, exps ? kge_plane_scaled(v, e) : sc * v);
             }
-            if (lane == 0) inv_scale[n] = inv;
+            if (lane == 0) { if (exps) exps[n] = e; else inv_scale[n] = inv; }
         }
     }
 }
@@ -320,7 +340,7 @@ __global__ void kge_qbuild_tgather_kernel(int q_blocks, KgeQbuildArgs a, KgeTgat
     if (g.bias)                                                         // 0 for the negatives, -inf for the padding rows behind them
         for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < g.Np; n += gridDim.x * blockDim.x) g.bias[n] = n < g.N ? 0.f : -INFINITY;
     if ((int)blockIdx.x < q_blocks) kge_qbuild_body<BF16, SC, NJ>(blockIdx.x, a);
-    else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen);
+    else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen, g.exps);
 }
 
 // gather of the shared negatives AND their transposed copy in one launch: a workgroup takes 32 negatives, every
@@ -791,13 +811,13 @@ int kge_run_qbuild(const KgeModelDev &m, const int32_t *h, const int32_t *r, con
 int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t *r, const int32_t *t, int B, int Bp,
                            int dp, void *Q, void *W, void *Q2, float *Q32, float *W32, KgeRowInfo *rowinfo, float *pos_ws,
                            const int32_t *neg, int N, int Np, void *T, float *tn, hipStream_t st, float *pos_out,
-                           void *q_planes, void *t_planes, float *t_inv_scale, float *bias, const KgeNegGen *gen, float *q_inv_scale) {
+                           void *q_planes, void *t_planes, float *t_inv_scale, float *bias, const KgeNegGen *gen, int32_t *q_exp, int32_t *t_exp) {
     const int rows_wg = 4 * kge_tgather_rows_per_wave(dp, m.bf16 ? 2 : 4);
     const int qb = (Bp + 3) / 4, tb = (Np + rows_wg - 1) / rows_wg;
-    if (qb == 0 || tb == 0 || ((q_planes || t_planes) && m.bf16) || (t_planes && !t_inv_scale)) return KGE_E_INVALID_ARG;
+    if (qb == 0 || tb == 0 || ((q_planes || t_planes) && m.bf16) || (t_planes && !t_inv_scale && !t_exp)) return KGE_E_INVALID_ARG;
     const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)q_planes,
-                          q_inv_scale};
-    const KgeTgatherArgs g{neg, N, Np, T, tn, (_Float16 *)t_planes, t_inv_scale, bias, gen ? *gen : KgeNegGen{}};
+                          q_exp};
+    const KgeTgatherArgs g{neg, N, Np, T, tn, (_Float16 *)t_planes, t_inv_scale, t_exp, bias, gen ? *gen : KgeNegGen{}};
     // (kernels for the columns of a padded row: the query is built without branches, lanes past the row read its first column again;
     // one kernel for 512 columns: TransH 8,192 x 4,096 step 454 instead of 453 us, ComplEx 4,096 x 16,384 196 / 195)
 #define KGE_QT_NJ(BF, SC, NJ) hipLaunchKernelGGL((kge_qbuild_tgather_kernel<BF, SC, NJ>), dim3(qb + tb), dim3(256), 0, st, qb, a, g)

@@ -281,3 +281,38 @@ def test_block_kernels_on_planes_with_rows_of_all_sizes(orc, block_passes, score
     for k in ("h", "r", "t"):
         G[k] = np.ascontiguousarray(G[k][at])
     base._compare(orc, scorer, loss, G, False, 6000)
+
+
+@pytest.mark.parametrize("scorer,dim", [("transe", 128), ("rotate", 64), ("rotate", 256)])
+def test_block_kernels_on_planes_of_tiny_rows(orc, block_passes, scorer, dim):
+    """Rows whose largest element lies below 2^-64: the product of two rows' scales is no fp32 number, their dot product and their
+    squared norms (2^-124) are."""
+    G = make_case(scorer, 3000, 9, dim, 130, 300, False, amp=0.5)
+    G["neg"] = np.setdiff1d(np.arange(3000, dtype=np.int32), np.concatenate([G["h"], G["t"]]))[:300].copy()    # (squares of r alone are 0)
+    G["ent"] *= np.float32(2.0 ** -64.6 / np.abs(G["ent"]).max())
+    if scorer == "transe":
+        G["rel"] *= np.float32(2.0 ** -76)
+    base._compare(orc, scorer, "logsigmoid", G, False, 3000, kw=dict(gamma=1.0, adv_temp=1.0))
+
+
+@pytest.mark.parametrize("scorer", ["distmult", "complex"])
+@pytest.mark.parametrize("loss", ["logsigmoid", "sampled_softmax"])
+@pytest.mark.parametrize("dim", [128, 256])
+def test_block_kernels_on_planes_keep_a_loss_beside_a_score_of_minus_infinity(orc, block_passes, scorer, loss, dim):
+    """A negative with an infinite element, whose score is -inf for every query, weighs nothing: the loss and all gradients are those
+    of a negative with -1e30 in its place."""
+    import paper_2211_12281_amd as kge
+    G = make_case(scorer, 3000, 9, dim, 140, 300, False, amp=0.3)
+    G["neg"] = np.setdiff1d(np.arange(3000, dtype=np.int32), np.concatenate([G["h"], G["t"]]))[:300].copy()
+    G["ent"][G["h"], 3] = 0.25                              # (q_3 > 0 for both scorers)
+    G["rel"][:, 3] = 0.25
+    if scorer == "complex":
+        G["ent"][G["h"], dim // 2 + 3] = 0.0
+    G["ent"][G["neg"][77], 3] = -1e30
+    kw = dict(n_ent_for_c=3000) if loss == "sampled_softmax" else dict(gamma=0.0, adv_temp=1.0)
+    ref = orc.loss_bwd(scorer, loss, G["ent"], G["rel"], G["relw"], G["h"], G["r"], G["t"], G["neg"], **kw)
+    G["ent"][G["neg"][77], 3] = -np.inf
+    out = kge.loss_bwd(gpu_model(scorer, G, False), loss, dev_idx(G["h"]), dev_idx(G["r"]), dev_idx(G["t"]), dev_idx(G["neg"]), **kw)
+    assert abs(out["loss"].item() - ref["loss"]) <= RTOL_F32 * abs(ref["loss"])
+    for k in ("g_ent", "g_rel"):
+        assert norm_err(out[k].cpu().numpy(), ref[k]) <= RTOL_F32
