@@ -316,3 +316,23 @@ def test_block_kernels_on_planes_keep_a_loss_beside_a_score_of_minus_infinity(or
     assert abs(out["loss"].item() - ref["loss"]) <= RTOL_F32 * abs(ref["loss"])
     for k in ("g_ent", "g_rel"):
         assert norm_err(out[k].cpu().numpy(), ref[k]) <= RTOL_F32
+
+
+@pytest.mark.parametrize("scorer,dim,loss", [("distmult", 128, "logsigmoid"), ("distmult", 256, "sampled_softmax"), ("complex", 64, "sampled_softmax"),
+                                             ("complex", 256, "logsigmoid"), ("transe", 128, "logsigmoid")])
+def test_block_kernels_on_planes_with_columns_of_all_sizes(orc, block_passes, scorer, dim, loss):
+    """Columns between 2^0 and 2^-20 of the rows' largest elements, each compared by itself.  An element keeps 2^-24 of itself or 2^-40 of
+    the largest: 2^-20 = 1e-6 for the smallest column.  A column's sum over 300 or 700 pairs of either sign is down to a fortieth of its
+    terms' size (the same calls leave up to 4.1e-5 where every element keeps 24 bits): 1e-4."""
+    import paper_2211_12281_amd as kge
+    G = make_case(scorer, 6000, 9, dim, 300, 700, False, amp=0.3 if scorer in ("distmult", "complex") else 0.1)
+    half = dim // 2 if scorer == "complex" else dim
+    size = np.float32(2.0) ** -np.round(np.arange(half) * 20 / (half - 1)).astype(np.float32)
+    G["ent"] *= np.concatenate([size] * (dim // half))
+    kw = base._kw(scorer, loss, 6000)
+    ref = orc.loss_bwd(scorer, loss, G["ent"], G["rel"], G["relw"], G["h"], G["r"], G["t"], G["neg"], **kw)
+    out = kge.loss_bwd(gpu_model(scorer, G, False), loss, dev_idx(G["h"]), dev_idx(G["r"]), dev_idx(G["t"]), dev_idx(G["neg"]), **kw)
+    got, want = out["g_ent"].cpu().numpy().astype(np.float64), ref["g_ent"]
+    for sl in (slice(0, 300), slice(600, 1300)):
+        err = np.linalg.norm(got[sl] - want[sl], axis=0) / np.linalg.norm(want[sl], axis=0)
+        assert err.max() <= 1e-4, (sl, int(err.argmax()), float(err.max()))
