@@ -803,13 +803,24 @@ void kge_block_kernel(const KgeBlockArgs a) {
                     const float r = trip ? (have ? kge_exp2(-tm) : 0.f) : 1.f;   // nothing accumulated yet without one
                     st_m[h] = m_new;
                     st_l[h] *= r; st_acc[h] *= r; sum1[h] *= r; sum2[h] *= r; sum3[h] *= r;
+                    float ra = r;
+                    if constexpr (PL) {
+                        // coefficients relative to the new reference are 2^-tm as large: their scale rises by as much (or the later ones, which
+                        // now count, would be left with the last bits of a scale that was set for the earlier ones) and what is
+                        // accumulated stays about as it is
+                        if (trip && c_scale > 0.f) {
+                            const float s_new = fminf(c_scale * kge_exp2(floorf(tm)), 0x1p126f);
+                            ra = ldexpf(r, (int)(__float_as_uint(s_new) >> 23) - (int)(__float_as_uint(c_scale) >> 23));
+                            c_scale = s_new;
+                        }
+                    }
 #pragma unroll
                     for (int b = 0; b < C::NBH; ++b) {
                         // one block at a time: the accumulators live in AGPRs and pass through VGPRs here; the
                         // empty statements keep this rarely executed code from being turned into selects
-                        for (int i = 0; i < 16; ++i) acc2[h][b][i] *= r;
+                        for (int i = 0; i < 16; ++i) acc2[h][b][i] *= ra;
                         asm volatile("" ::: "memory");
-                        if constexpr (TRANSH) { for (int i = 0; i < 16; ++i) acc2b[b][i] *= r; asm volatile("" ::: "memory"); }
+                        if constexpr (TRANSH) { for (int i = 0; i < 16; ++i) acc2b[b][i] *= ra; asm volatile("" ::: "memory"); }
                     }
 #pragma unroll
                     for (int i = 0; i < 16; ++i) x2[i] += shift;       // masked entries stay at -inf
