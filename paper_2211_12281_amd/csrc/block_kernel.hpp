@@ -603,9 +603,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
         } else {
             // squared distance by the norm expansion |q|^2 + |t|^2 - 2 q.t (TransH: plus the terms of the
             // projection); entries where it cancels (below 1e-3 of the norms) are redone by direct
-            // differences in a rarely taken branch.  Planes, whose products are good to 2^-22 instead of 2^-24 of the norms: below 4e-3
-            // (negatives at 0.05 of its length from the query, worst error of their gradients: 8.5e-6 with a line of 1e-3, 6e-7 with 4e-3;
-            // no time on tables that are not crowded)
+            // differences in a rarely taken branch
             float d2[16], thr[16];
             bool cancel = false;
 #pragma unroll
@@ -616,7 +614,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 else { float4 ri = *(const float4 *)(side + sl * 16); qn = ri.x; cc = ri.y; wn = ri.w; tnv = o_tn[h]; }
                 d2[i] = fmaf(-2.f, acc[h][i], qn + tnv);
                 if constexpr (TRANSH) { const float A = accw[i]; Av[i] = A; d2[i] += A * (2.f * cc - A * (2.f - wn)); }
-                thr[i] = (PL ? 4e-3f : 1e-3f) * (qn + tnv);
+                thr[i] = 1e-3f * (qn + tnv);
                 cancel = cancel || d2[i] < thr[i];
             }
             if (__any(cancel)) {
