@@ -603,7 +603,10 @@ void kge_block_kernel(const KgeBlockArgs a) {
         } else {
             // squared distance by the norm expansion |q|^2 + |t|^2 - 2 q.t (TransH: plus the terms of the
             // projection); entries where it cancels (below 1e-3 of the norms) are redone by direct
-            // differences in a rarely taken branch
+            // differences in a rarely taken branch.  (The line with planes: above it their errors are 0.6 to 0.9 times those of 24-bit operands
+            // with norms summed in 32 bits, negatives at 0.05 and 0.1 of its length from a query; four products are no better.  A line of 4e-3
+            // gives a tenth of the error at 0.05, but tables with a common part ten to thirty times their spread take 15 to 100 times as
+            // long: TransE 8,192 x 4,096 x 128 at 0.05 7.0 ms instead of 0.2)
             float d2[16], thr[16];
             bool cancel = false;
 #pragma unroll
