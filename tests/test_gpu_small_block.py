@@ -359,3 +359,30 @@ def test_block_kernels_on_planes_when_later_small_rows_outweigh_large_ones(orc, 
     assert abs(out["loss"].item() - ref["loss"]) <= RTOL_F32 * abs(ref["loss"])
     got, want = out["g_ent"].cpu().numpy()[:B, :half], ref["g_ent"][:B, :half]
     assert norm_err(got, want) <= 2 * RTOL_F32
+
+
+@pytest.mark.parametrize("scorer,dim,B,N,size", [("complex", 8, 2600, 2700, 42469632), ("transh", 48, 1500, 2700, 59421952),
+                                                 ("distmult", 128, 2600, 2700, 42469632), ("transe", 64, 4096, 4096, 45869312)])
+def test_block_kernels_on_planes_in_a_smaller_workspace(orc, scorer, dim, B, N, size):
+    """Two workgroups share a compute unit, so these calls would like up to twice the split partials that one needs; in a workspace sized for
+    those they run with fewer splits, in one of a third with fewer still, and one without room for a split each is refused."""
+    import paper_2211_12281_amd as kge
+    class Fixed:
+        def __init__(self, n): self.buf = torch.empty(n, dtype=torch.uint8, device="cuda")
+        def get(self, n): return self.buf
+    G = make_case(scorer, 9000, 9, dim, B, N, False, amp=0.3 if scorer in ("distmult", "complex") else 0.1, zipf=True)
+    model, kw = gpu_model(scorer, G, False), dict(gamma=1.0, adv_temp=0.8)
+    args = (dev_idx(G["h"]), dev_idx(G["r"]), dev_idx(G["t"]), dev_idx(G["neg"]))
+    run = lambda ws: {k: v.clone() for k, v in kge.loss_bwd(model, "logsigmoid", *args, ws=ws, **kw).items() if v is not None}
+    want = run(kge.Workspace())
+    for n in (size, size // 3):
+        buf = Fixed(n + (1 << 20))
+        buf.buf[n:] = 77
+        buf.buf, guard = buf.buf[:n], buf.buf[n:]
+        got = run(buf)
+        assert bool((guard == 77).all())
+        assert abs(got["loss"].item() - want["loss"].item()) <= 1e-6 * abs(want["loss"].item())
+        for k in ("g_ent", "g_rel"):
+            assert norm_err(got[k].cpu().numpy(), want[k].cpu().numpy()) <= RTOL_F32
+    with pytest.raises(RuntimeError):
+        run(Fixed(1 << 20))
