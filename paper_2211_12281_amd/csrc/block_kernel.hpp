@@ -191,7 +191,7 @@ struct KgeBlockCfg {
     // groups of fragments requested together: what the registers hold without scratch
     static constexpr int PL_CHUNK = TRANSH ? 4 : OWN_ROW && KIND == KGE_KIND_DIST ? 1 : 2;
     static constexpr int X_BYTES = PL ? 2 * PLANE : ST * RB;    // else [ST rows][RB bytes], chunk c of row r at c ^ (r & 7)
-    static constexpr int XT_ROWB = ST * ES;                // one transposed row: ST stream entries (64 or 128 bytes)
+    static constexpr int XT_ROWB = ST * ES;                // one transposed row: ST stream entries (bf16: 64 bytes)
     static constexpr int XT_BYTES = DP * XT_ROWB;
     static constexpr bool HAS_X2 = TRANSH && !OWN_ROW;     // second streamed operand (normals)
     static constexpr bool HAS_XT = MODE != KGE_MODE_SCORE && !PL;
@@ -322,17 +322,14 @@ void kge_block_kernel(const KgeBlockArgs a) {
         const int r = byte / RB, pos = (byte % RB) / 16;
         x_off[jj] = r * RB + ((pos ^ (r & 7)) * 16);
     }
-    // Xt tile: rows of XT_ROWB bytes (dcol-major).  bf16: 64-byte rows, two rows per 128-byte line, chunk
-    // slot ((row&1)*4 + c) ^ ((row>>1)&7) within the line; fp32: 128-byte rows, chunk c at c ^ (row & 7).
+    // Xt tile: rows of 64 bytes (dcol-major), two rows per 128-byte line, chunk slot ((row&1)*4 + c) ^ ((row>>1)&7) within the line.
     int64_t xt_off[C::HAS_XT ? C::XT_IPW : 1];             // source byte offset relative to the tile's first column
     if constexpr (C::HAS_XT) {
 #pragma unroll
         for (int jj = 0; jj < C::XT_IPW; ++jj) {
             const int byte = (wave * C::XT_IPW + jj) * 1024 + lane * 16;
             const int line = byte >> 7, slot = (byte >> 4) & 7;
-            int row, c;
-            if constexpr (BF16) { const int sslot = slot ^ (line & 7); row = 2 * line + (sslot >> 2); c = sslot & 3; }
-            else { row = line; c = slot ^ (row & 7); }
+            const int sslot = slot ^ (line & 7), row = 2 * line + (sslot >> 2), c = sslot & 3;
             xt_off[jj] = (int64_t)row * a.strT_ld * C::ES + c * 16;
         }
     }
@@ -515,8 +512,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
     // ---- phase 2: out^t[d, own] += Xt_tile[d, stream] . coef[stream, own] ---------------------------
     constexpr int G2 = BF16 ? (HASW ? 1 : 2) : 1;          // blocks per group
     constexpr int NG2 = PHASE2 ? C::NBH / G2 : 0;
-    constexpr int F2 = BF16 ? 2 : 4;                       // 16-byte fragments per block
-    uint4 av2[PHASE2 && !PL ? C::NBH : 1][F2], aw2[(PHASE2 && HASW && !PL) ? C::NBH : 1][F2];
+    uint4 av2[PHASE2 && !PL ? C::NBH : 1][2], aw2[(PHASE2 && HASW && !PL) ? C::NBH : 1][2];   // (bf16: two 16-byte fragments per block)
     KgeP2 tp[PL ? C::NBH : 1][2], twp[PL && HASW ? C::NBH : 1][2];
     auto ld2 = [&](const char *stage, int grp) {
         if constexpr (PL) {
@@ -544,17 +540,12 @@ void kge_block_kernel(const KgeBlockArgs a) {
             const int blk = grp * G2 + bb;
             const int row = (dblk0 + blk) * 32 + lr;
 #pragma unroll
-            for (int f = 0; f < F2; ++f) {
-                const char *p;
-                if constexpr (BF16) {
-                    // The transposed operand keeps, inside every group of 16 stream entries, the 8 entries of
-                    // one lane half contiguous (the producer swaps bits 2 and 3 of the column), so the
-                    // A-fragment of (block, f) is ONE 16-byte chunk: chunk 2 f + g of row dcol, at its slot.
-                    const int sslot = (((row & 1) << 2) | (2 * f + g)) ^ ((row >> 1) & 7);
-                    p = xt + (row >> 1) * 128 + sslot * 16;
-                } else {
-                    p = xt + row * 128 + ((2 * f + g) ^ (row & 7)) * 16;
-                }
+            for (int f = 0; f < 2; ++f) {
+                // The transposed operand keeps, inside every group of 16 stream entries, the 8 entries of
+                // one lane half contiguous (the producer swaps bits 2 and 3 of the column), so the
+                // A-fragment of (block, f) is ONE 16-byte chunk: chunk 2 f + g of row dcol, at its slot.
+                const int sslot = (((row & 1) << 2) | (2 * f + g)) ^ ((row >> 1) & 7);
+                const char *p = xt + (row >> 1) * 128 + sslot * 16;
                 av2[blk][f] = *(const uint4 *)p;
                 if constexpr (HASW) aw2[blk][f] = *(const uint4 *)(p + C::XT_BYTES);
             }

@@ -52,7 +52,7 @@ struct Geometry {
                                         // 1-norm, and in training calls TransH rows over 512 bytes (2-norm; the matrix-core
                                         // kernels have no registers for two operands of that width)
     int pn;                             // ... the norm they compute
-    bool planes;                        // training call on the fp32 block kernels that read bf16 planes (kge_block_planes)
+    bool planes;                        // training call on the fp32 block kernels that read fp16 planes (kge_block_planes)
     bool small;                         // training call: both passes with the scores in memory (block_small.hip)
     int es, rb, dp, kind;
     int B, N, Bp, Np;
@@ -213,14 +213,15 @@ size_t carve(const Geometry &g, bool bwd, void *ws, Buffers &b) {
     b.Q2 = nullptr; b.Qt = b.Wt = b.Tt = nullptr; b.lossb = b.gpos = nullptr; b.stat_part = nullptr;
     b.accq = b.accq2 = b.acct = nullptr; b.sumq = b.sumt = nullptr; b.regv = nullptr; b.S = nullptr; b.nbias = nullptr;
     if (bwd) {
-        b.Q2 = g.transh && !g.l1 && !g.planes ? c.take<char>(rowsB * es) : nullptr;
+        // (the bf16 block kernels' transposed copies; fp32 rows have planes)
+        const bool copies = g.bf16 && !g.l1 && !g.small;
+        b.Q2 = g.transh && copies ? c.take<char>(rowsB * es) : nullptr;
         if (g.small) b.S = c.take<float>(g.pairs);
-        else if (g.planes) {}
-        else if (!g.l1) {
+        else if (copies) {
             b.Qt = c.take<char>(rowsB * es);
             b.Wt = g.transh ? c.take<char>(rowsB * es) : nullptr;
             b.Tt = c.take<char>(rowsN * es);
-        } else {
+        } else if (g.l1) {
             b.S = c.take<float>(g.pairs);
             if (g.transh) { b.A = c.take<float>(g.pairs); b.P = c.take<float>(g.pairs); }
         }
@@ -559,8 +560,8 @@ static int loss_bwd_impl(const kge_model_t *model, const kge_loss_cfg_t *cfg, co
         if (!plain_gather && (rc = kge_run_tgather_t(md, neg, g.N, g.Np, g.dp, b.T, b.Tt, b.tn, st)) != KGE_OK) return rc;
         // (nor does the two-role kernel of the pass over the negatives need transposed queries)
         if (!g.planes && !kge_gradt_pp_applies(g.bf16, g.rb, g.transh, g.dsplit_t) &&
-            (rc = kge_run_transpose(g.transh ? b.Q2 : b.Q, b.Qt, g.Bp, g.dp, g.bf16, st)) != KGE_OK) return rc;
-        if (g.transh && !g.planes && (rc = kge_run_transpose(b.W, b.Wt, g.Bp, g.dp, g.bf16, st)) != KGE_OK) return rc;
+            (rc = kge_run_transpose(g.transh ? b.Q2 : b.Q, b.Qt, g.Bp, g.dp, st)) != KGE_OK) return rc;
+        if (g.transh && !g.planes && (rc = kge_run_transpose(b.W, b.Wt, g.Bp, g.dp, st)) != KGE_OK) return rc;
         // pass 1 (row owner): loss statistics of every row and the unnormalised gradient of the queries
         a.own = b.Q; a.own2 = b.W; a.str = b.T;
         if (g.planes) {

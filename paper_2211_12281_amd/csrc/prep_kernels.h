@@ -34,10 +34,10 @@ int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t
                            const KgeNegGen *gen = nullptr,    // gen->out set: neg is ignored, the ids are drawn and written there
                            // training: exponents of the planes' scales (kge_plane_exp) in place of rowinfo.K and t_inv_scale
                            int32_t *q_exp = nullptr, int32_t *t_exp = nullptr);
-// gather of the negatives and their transposed copy Tt [dp][Np] in one launch
+// gather of the negatives and their transposed copy Tt [dp][Np] in one launch (bf16 tables)
 int kge_run_tgather_t(const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T, void *Tt, float *tn,
                       hipStream_t st);
-int kge_run_transpose(const void *src, void *dst, int R, int C, bool bf16, hipStream_t st);
+int kge_run_transpose(const void *src, void *dst, int R, int C, hipStream_t st);     // elements of 2 bytes
 // bf16 rows of 256 elements: the finish plus the query rows scaled for every forward split, Qs [nsplit][Bp][256] (block_gradp.hip)
 int kge_run_rowfinish_qscale(const float4 *stat_part, int nsplit, int Bp, int B, int N, int loss, float gamma, float c_corr,
                               float scale, const float *pos, KgeRowInfo *rowinfo, float *lossb, float *gpos, const void *Q,

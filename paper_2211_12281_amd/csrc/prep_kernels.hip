@@ -343,15 +343,15 @@ __global__ void kge_qbuild_tgather_kernel(int q_blocks, KgeQbuildArgs a, KgeTgat
     else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen, g.exps);
 }
 
-// gather of the shared negatives AND their transposed copy in one launch: a workgroup takes 32 negatives, every
+// gather of the shared negatives AND their transposed copy in one launch (bf16 tables): a workgroup takes 32 negatives, every
 // wave 8 of them (all of a lane's loads are issued before the first is used), the rows pass through the LDS
-// and leave again as the 32-entry segments of the dp rows of Tt (bf16: with the column permutation of
-// kge_transpose_kernel).  NJ = dp / 64.
-template <bool BF16, int NJ>
+// and leave again as the 32-entry segments of the dp rows of Tt, with the column permutation of
+// kge_transpose_kernel.  NJ = dp / 64.
+template <int NJ>
 __global__ __launch_bounds__(256) void kge_tgather_t_kernel(KgeModelDev m, const int32_t *neg, int N, int Np, void *T, void *Tt,
                                                             float *tn) {
-    using E = typename El<BF16>::T;
-    constexpr int DP = 64 * NJ, PITCH = DP + (BF16 ? 2 : 1);           // odd stride in 4-byte words
+    using E = __bf16;
+    constexpr int DP = 64 * NJ, PITCH = DP + 2;                         // odd stride in 4-byte words
     extern __shared__ __attribute__((aligned(16))) char tg_lds[];
     E *tile = (E *)tg_lds;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(256) void kge_tgather_t_kernel(KgeModelDev m, const
 #pragma unroll
         for (int k = 0; k < NJ; ++k) {
             const int j = lane + 64 * k;
-            const float x = El<BF16>::ld(m.ent, off + (j < m.dim ? j : 0));
+            const float x = El<true>::ld(m.ent, off + (j < m.dim ? j : 0));
             v[rr][k] = (n < N && j < m.dim) ? x : 0.f;
         }
     }
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(256) void kge_tgather_t_kernel(KgeModelDev m, const
 #pragma unroll
         for (int k = 0; k < NJ; ++k) {
             const int j = lane + 64 * k;
-            El<BF16>::st(T, (int64_t)n * DP + j, v[rr][k]);
+            El<true>::st(T, (int64_t)n * DP + j, v[rr][k]);
             tile[row * PITCH + j] = (E)v[rr][k];
             s += v[rr][k] * v[rr][k];
         }
@@ -384,24 +384,23 @@ __global__ __launch_bounds__(256) void kge_tgather_t_kernel(KgeModelDev m, const
     }
     __syncthreads();
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int px = BF16 ? ((tx & ~12) | ((tx & 4) << 1) | ((tx & 8) >> 1)) : tx;
+    const int px = (tx & ~12) | ((tx & 4) << 1) | ((tx & 8) >> 1);
     for (int c = ty; c < DP; c += 8) ((E *)Tt)[(int64_t)c * Np + n0 + px] = tile[tx * PITCH + c];
 }
 
 // ---------------------------------------------------------------------------------------------
-// transpose: src [R][C] -> dst [C][R]   (R, C multiples of 32; elements of 2 or 4 bytes).
-// PERM: inside every group of 16 source rows, bits 2 and 3 of the row number are swapped in the
+// transpose: src [R][C] -> dst [C][R]   (R, C multiples of 32; elements of 2 bytes).
+// Inside every group of 16 source rows, bits 2 and 3 of the row number are swapped in the
 // destination column, which makes the 8 entries that one lane half of the block kernel contracts in
-// its second phase contiguous (one 16-byte fragment for 2-byte elements).
+// its second phase contiguous (one 16-byte fragment).
 // ---------------------------------------------------------------------------------------------
-template <typename T, bool PERM>
-__global__ void kge_transpose_kernel(const T *src, T *dst, int R, int C) {
-    __shared__ T tile[32][33];
+__global__ void kge_transpose_kernel(const uint16_t *src, uint16_t *dst, int R, int C) {
+    __shared__ uint16_t tile[32][33];
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;      // 256 threads: 32 x 8
     const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
     for (int i = ty; i < 32; i += 8) tile[i][tx] = src[(int64_t)(r0 + i) * C + c0 + tx];
     __syncthreads();
-    const int px = PERM ? ((tx & ~12) | ((tx & 4) << 1) | ((tx & 8) >> 1)) : tx;
+    const int px = (tx & ~12) | ((tx & 4) << 1) | ((tx & 8) >> 1);
     for (int i = ty; i < 32; i += 8) dst[(int64_t)(c0 + i) * R + r0 + px] = tile[tx][i];
 }
 
@@ -842,21 +841,18 @@ int kge_run_tgather(const KgeModelDev &m, const int32_t *neg, int N, int Np, int
 int kge_run_tgather_t(const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T, void *Tt, float *tn,
                       hipStream_t st) {
     if (Np == 0) return KGE_OK;
-    if (Np % 32 || (dp != 128 && dp != 256 && dp != 512)) return KGE_E_INVALID_ARG;
+    if (!m.bf16 || Np % 32 || (dp != 256 && dp != 512)) return KGE_E_INVALID_ARG;
     const int grid = Np / 32;
-#define KGE_TG(BF, NJ) hipLaunchKernelGGL((kge_tgather_t_kernel<BF, NJ>), dim3(grid), dim3(256), 32 * (64 * NJ + (BF ? 2 : 1)) * (BF ? 2 : 4), st, \
-                                          m, neg, N, Np, T, Tt, tn)
-    if (m.bf16) { if (dp == 128) KGE_TG(true, 2); else if (dp == 256) KGE_TG(true, 4); else KGE_TG(true, 8); }
-    else        { if (dp == 128) KGE_TG(false, 2); else if (dp == 256) KGE_TG(false, 4); else return KGE_E_INVALID_ARG; }   // fp32 rows: 512 or 1,024 bytes
+#define KGE_TG(NJ) hipLaunchKernelGGL((kge_tgather_t_kernel<NJ>), dim3(grid), dim3(256), 32 * (64 * NJ + 2) * 2, st, m, neg, N, Np, T, Tt, tn)
+    if (dp == 256) KGE_TG(4); else KGE_TG(8);               // rows of 512 or 1,024 bytes
 #undef KGE_TG
     return kge_launch_status();
 }
 
-int kge_run_transpose(const void *src, void *dst, int R, int C, bool bf16, hipStream_t st) {
+int kge_run_transpose(const void *src, void *dst, int R, int C, hipStream_t st) {
     if (R == 0 || C == 0) return KGE_OK;
     dim3 grid(C / 32, R / 32);
-    if (bf16) hipLaunchKernelGGL((kge_transpose_kernel<uint16_t, true>), grid, dim3(256), 0, st, (const uint16_t *)src, (uint16_t *)dst, R, C);
-    else      hipLaunchKernelGGL((kge_transpose_kernel<uint32_t, false>), grid, dim3(256), 0, st, (const uint32_t *)src, (uint32_t *)dst, R, C);
+    hipLaunchKernelGGL(kge_transpose_kernel, grid, dim3(256), 0, st, (const uint16_t *)src, (uint16_t *)dst, R, C);
     return kge_launch_status();
 }
 
