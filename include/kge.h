@@ -156,12 +156,19 @@ int kge_score(const kge_model_t *model, const int32_t *h, const int32_t *r, cons
  * workspace (B*N floats, three of them) and both passes run on the vector pipe in fp32, about ten times slower than the
  * matrix-core route of the narrower rows.
  * Arithmetic of the two contractions per pass (scores; gradient rows): bf16 tables -> bf16 matrix cores with fp32
- * accumulation.  fp32 tables -> every operand value as three bf16 pieces x0 + x1 + x2 (round to nearest at each step:
- * 24 significand bits, the exponent range of fp32, nothing scaled) and the six piece products of total order <= 2 on
- * the bf16 matrix cores with fp32 accumulation (what is dropped is below 2^-26 |a| |b| per product); the pass over the
- * queries with rows of 1,024 bytes uses the fp32 matrix instructions, unless the scores are in memory.  Where they are, the
- * coefficients dL/dS of bf16 tables enter the queries' gradients as two bf16 pieces and the negatives' as one; elsewhere
- * the queries' are one piece of the weight relative to a reference of its row, times the row's factor in fp32.
+ * accumulation.  Where the scores are in memory, the coefficients dL/dS of bf16 tables enter the queries' gradients as two bf16
+ * pieces and the negatives' as one; elsewhere the queries' are one piece of the weight relative to a reference of its row, times the
+ * row's factor in fp32.
+ * fp32 tables, scores in memory -> every operand value as three bf16 pieces x0 + x1 + x2 (round to nearest at each step: 24
+ * significand bits, the exponent range of fp32, nothing scaled) and the six piece products of total order <= 2 on the bf16 matrix cores
+ * with fp32 accumulation (what is dropped is below 2^-26 |a| |b| per product).
+ * fp32 tables, larger blocks -> every operand row times a power of two of its own (largest element in [2^14, 2^15); any fp32 row has one), every
+ * value as two fp16 pieces x0 + x1, and the three products a0 b0 + a0 b1 + a1 b0 on the 16-bit matrix cores with fp32 accumulation.
+ * A value is good to 2^-24 of itself down to 2^-16 of its row's largest element, and to 2^-40 of that element below: a gradient column
+ * that is 2^-20 of the others in every row is good to about 1e-6, one of 2^-24 to 1e-4.  a1 b1, dropped, is below 2^-24 |a| |b|.  The pairs'
+ * coefficients likewise, times a power of two per row of the gradient that follows the largest.  A row with an infinite element counts
+ * by that element alone; a score of -inf has no weight.  Distances come from |q|^2 + |t|^2 - 2 q.t, and below 1e-3 of |q|^2 + |t|^2 from the
+ * fp32 rows themselves.
  */
 int kge_loss_bwd(const kge_model_t *model, const kge_loss_cfg_t *cfg, const int32_t *h,
                  const int32_t *r, const int32_t *t, int64_t B, const int32_t *neg, int64_t N,
@@ -456,7 +463,10 @@ size_t kge_workspace_bytes(int op, const kge_model_t *model, int64_t B, int64_t 
  * count, and forgets them.
  * Host-side state shared by all callers of the process; not thread-safe; off by default.
  */
-enum { KGE_PROF_BLOCK_SCORE = 0, KGE_PROF_BLOCK_FWD = 1, KGE_PROF_BLOCK_GRADT = 2, KGE_PROF_ADAM = 3,
+enum { KGE_PROF_BLOCK_SCORE = 0,
+       KGE_PROF_BLOCK_FWD = 1,    /* 1-norm of TransE and RotatE: both gradient passes, which are one launch ... */
+       KGE_PROF_BLOCK_GRADT = 2,  /* ... and this slot stays empty */
+       KGE_PROF_ADAM = 3,
        KGE_PROF_SORT = 4, KGE_PROF_TOPK_SCAN = 5, KGE_PROF_ENC_FWD = 6, KGE_PROF_ENC_BWD = 7,
        KGE_PROF_GATHER = 8,   /* kge_loss_bwd: query build + gather of the negatives' rows (one launch) */
        KGE_PROF_FINISH = 9,   /* kge_loss_bwd: chain rule of the queries + finish of the negatives' gradient rows (one launch) */

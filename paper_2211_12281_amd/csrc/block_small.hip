@@ -8,10 +8,10 @@
 //   scores      S[b, n], one 32 x 32 tile per wave, operands straight from memory (both are contiguous along d)
 //   rows        one workgroup per query: loss, gradient of the positive score and the coefficients C[b, n] = dL/dS[b, n] (distance
 //               scorers: over the distance) from its row of S; once per pair - made from S and a row constant by every workgroup of
-//               the gradients, the exponentials bound that launch (26 us instead of 19 for the RotatE case below)
+//               the gradients, the exponentials bound that launch (a third more time for the RotatE case below)
 //   gradients   one launch for both operands: dQ = C T and dT = C^t Q; a workgroup makes 32 rows x 64 or 128 columns, its eight waves
 //               share out the contraction index and add up through the LDS, so that there are no partials in memory
-// (kge_loss_bwd, block kernels / here: RotatE fp32, B 448, N 1,088, d 256: 108 / 46 us; ComplEx bf16, B 640, N 1,536, d 400: 112 / 40 us.)
+// (kge_loss_bwd, block kernels / here: RotatE fp32, B 448, N 1,088, d 256: 108 / 44 us; ComplEx bf16, B 640, N 1,536, d 400: 112 / 39 us.)
 // What bounds each launch is its latency: start-up, two or three dependent loads and the matrix instructions of one wave.
 // Arithmetic: bf16 operands with fp32 accumulation, or three bf16 pieces per fp32 value.  On bf16 tables the coefficients are
 // finished when they are made, where the block kernels round the weight relative to a row reference (the dominating pairs are 1 and

@@ -67,7 +67,8 @@ constexpr int kge_block_ow(bool bf16, int rb, bool transh, int mode, int kind) {
 }
 
 // Workgroups of a block-kernel pass that share a compute unit: the SCORE pass keeps no gradient
-// accumulators and fits two, where two ring stages of its tiles fit in half of the LDS.
+// accumulators and fits two, where two ring stages of its tiles fit in half of the LDS; so do the training passes on planes
+// of 256 bytes a row with one operand.
 constexpr int kge_block_occ(bool bf16, int rb, bool transh, int mode) {
     if (!bf16 && rb == 512 && !transh && mode != KGE_MODE_SCORE) return 2;
     return (mode == KGE_MODE_SCORE && !transh && KGE_STREAM_TILE * rb <= 32 * 1024) ? 2 : 1;
@@ -77,11 +78,13 @@ constexpr int kge_block_occ(bool bf16, int rb, bool transh, int mode) {
 // which the gather writes beside the fp32 rows; there are no transposed copies.  The fp32 matrix instruction runs at 1/16 of the 16-bit
 // rate; three products of pieces replace sixteen.  Calls in us, before / here.  Rows of 512 bytes (before: three bf16 pieces, six products):
 // TransH 8,192 x 4,096 x 128 392 / 322 (passes 211 + 201 -> 170 + 164: the epilogue and the contractions of a tile one after the other in one
-// wave per SIMD), TransE 234 / 188, ComplEx 8,000 x 3,000 x 128 230 / 154, DistMult 4,096 x 4,096 x 96 111 / 92.  Rows of 1,024 bytes (fp32
-// instructions over the queries, bf16 pieces made in registers over the negatives): TransE 4,096 x 4,096 x 256 366 / 242, DistMult 2,048 x
-// 8,192 x 200 302 / 151, RotatE 8,192 x 2,000 x 256 353 / 220, ComplEx 4,096 x 4,096 x 256 330 / 191.
+// wave per SIMD), TransE 234 / 183, ComplEx 8,000 x 3,000 x 128 230 / 154, DistMult 4,096 x 4,096 x 96 111 / 92.  Rows of 1,024 bytes (fp32
+// instructions over the queries, bf16 pieces made in registers over the negatives): TransE 4,096 x 4,096 x 256 366 / 216, DistMult 2,048 x
+// 8,192 x 200 302 / 152, RotatE 8,192 x 2,000 x 256 353 / 230.
 // Errors against 64 bits over 120 drawn calls on rows of up to 512 bytes: 0.97-1.00 times those of before (geometric mean of every gradient),
-// half on rows of 1,024 bytes.
+// half on rows of 1,024 bytes.  Beyond those ranges: rows at 0.05 and 0.1 of its length from a query 0.6-0.9 times, at 1e-5 (where the
+// gradient is the difference of two rows' sums: 1e-2 of it either way) 1.05-1.2 times; a column that is 2^-20 of the others the same, one of
+// 2^-24 1.2e-4 instead of 1.1e-5.
 constexpr bool kge_block_planes(bool bf16, int rb, int mode) { (void)rb; return !bf16 && mode != KGE_MODE_SCORE; }
 
 // Per-row side information of the queries: squared norm of q, c = w.q (TransH), the per-row
@@ -89,8 +92,6 @@ constexpr bool kge_block_planes(bool bf16, int rb, int mode) { (void)rb; return 
 // (rounded) TransH normal.
 struct __attribute__((aligned(16))) KgeRowInfo { float qn, c, K, wn; };
 
-// Arguments of one block-kernel launch.  "own" is the operand a workgroup keeps in registers
-// (queries when OWN_ROW, negatives otherwise); "str" is the operand streamed through LDS.
 // Placement of the workgroups (own tile, split) of the block kernels on the 8 dies, to which workgroup ids go in turn: a
 // die takes the splits congruent to xcd / per modulo 8 / per and the own tiles congruent to xcd % per modulo per (per 1,
 // 2, 4 or 8), so its L2 fills with 1 / per of the own rows and per / 8 of the streamed ones.
@@ -124,6 +125,8 @@ inline int kge_place_plan(int own_tiles, int nsplit, int own_rows, int64_t str_r
     return groups;
 }
 
+// Arguments of one block-kernel launch.  "own" is the operand a workgroup keeps in registers
+// (queries when OWN_ROW, negatives otherwise); "str" is the operand streamed through LDS.
 struct KgeBlockArgs {
     // (kge_block_planes: own, own2, str, str2 are fp16 planes [2][own_pad or 32 str_tiles][dp] of rows times 2^-own_exp, 2^-str_exp -
     // the normals times 2^-KGE_PLANE_UNIT_EXP -, own32, str32 and w32 the fp32 rows; there are no transposed copies)

@@ -1155,8 +1155,8 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     const int64_t total_tiles = p.npad / TK_ST;
     // Growing chunks: thresholds are refreshed between chunks.  The first chunk appends everything: it holds at most 128
     // tiles and two per split, so that an area (one lane half: TK_ST / 2 candidates of a tile) takes 32 entries and a query
-    // 4,096; afterwards a chunk is 3x what has been seen or more, so a query with a well-mixed candidate order appends about 3 KP
-    // entries per chunk or more, spread over nsplit x 2 private areas.  Neighbouring rows that all beat the threshold fill the areas
+    // 4,096; afterwards a chunk is 2.2x to 9x what has been seen, so a query with a well-mixed candidate order appends about as many
+    // times KP entries per chunk, spread over nsplit x 2 private areas.  Neighbouring rows that all beat the threshold fill the areas
     // of their split: up to 128 in a row fit.
     constexpr int FIRST_TILES = 2;
     static_assert(FIRST_TILES * TK_ST / 2 <= TK_HALF, "the first chunk overflows no area");
