@@ -1155,26 +1155,16 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     const int64_t total_tiles = p.npad / TK_ST;
     // Growing chunks: thresholds are refreshed between chunks.  The first chunk appends everything: it holds at most 128
     // tiles and two per split, so that an area (one lane half: TK_ST / 2 candidates of a tile) takes 32 entries and a query
-    // 4,096; afterwards a chunk is 2.2x to 9x what has been seen, so a query with a well-mixed candidate order appends about as many
-    // times KP entries per chunk, spread over nsplit x 2 private areas.  Neighbouring rows that all beat the threshold fill the areas
-    // of their split: up to 128 in a row fit.
+    // 4,096; afterwards a chunk is 3x what has been seen, so a query with a well-mixed candidate order appends about 3 KP
+    // entries per chunk, spread over nsplit x 2 private areas.  Neighbouring rows that all beat the threshold fill the areas
+    // of their split: up to 128 in a row fit.  (Growing up to 10 times where a query has many areas saves two compactions and launches -
+    // 128 queries x 5.7M 867 -> 822 us, 16 x 300,000 271 -> 212 -, but tables whose neighbouring rows are alike then overflow an area, and the
+    // query is ranked exhaustively: clusters of 50 rows, 512 queries x 1M, 0.75 -> 149 ms.)
     constexpr int FIRST_TILES = 2;
     static_assert(FIRST_TILES * TK_ST / 2 <= TK_HALF, "the first chunk overflows no area");
-    // With many areas to a query (few queries) the chunks grow faster, up to 10 times what has been seen: a compaction is 16 to 20 us
-    // of latency and a launch of the scan about 5, while the entries that come with the older threshold are few beside the
-    // candidates.  Not beyond a mean of TK_HALF / 16 entries per area (more of them would fill up with clustered rows: the query
-    // is then ranked exhaustively), which leaves calls of many queries at 4, nor beyond what the compaction's list holds; then
-    // evened out over the chunks that takes.  Measured for 4 / 6 / 8 / 10 times, us: TransE bf16 d 256, 128 queries x 5.7M, K 100
-    // 867 / 838 / 822 / 822; 16 x 300,000, K 10 271 / 235 / 235 / 212; DistMult fp32 128 x 1M, K 100 829 / 833 / 807 / 807; TransH
-    // bf16 128 x 1M, K 256 465 / 463 / 439 / 439; 2,048 x 1M (stays at 4) 2,402 / 2,402 / 2,397 / 2,400.
-    const int64_t first = p.nseg * FIRST_TILES < 128 ? p.nseg * FIRST_TILES : 128;
-    double growth = 4.0;
-    const double most = fmin(10.0, fmin(1.0 + 2.0 * p.nseg * (TK_HALF / 16) / p.KP, 0.9 * TK_LISTCAP / p.KP));
-    const double span = (double)total_tiles / (double)first;
-    if (most > growth && span > 1.0) growth = pow(span, 1.0 / ceil(log(span) / log(most)));
     int64_t seen = 0;
     while (seen < total_tiles) {
-        int64_t tiles = seen == 0 ? first : (int64_t)ceil((growth - 1) * (double)seen);
+        int64_t tiles = seen == 0 ? (p.nseg * FIRST_TILES < 128 ? p.nseg * FIRST_TILES : 128) : 3 * seen;
         if (tiles > total_tiles - seen) tiles = total_tiles - seen;
         TopkArgs c = base;
         c.tile_lo = seen; c.tile_hi = seen + tiles; c.own_tiles = own_tiles;

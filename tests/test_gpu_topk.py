@@ -1,6 +1,7 @@
 """kge_topk and kge_partition_triples against the oracle: indices bit-exact, scores within tolerance."""
 import numpy as np
 import pytest
+import torch
 
 import kge_synth as ks
 from helpers import RTOL_BF16, RTOL_F32, dev_idx, gpu_model, make_case, norm_err, rank_band_eps, small_graph, to_dev
@@ -83,12 +84,44 @@ def test_query_counts_around_the_scan_variants(orc, scorer, bf16, dim, Q):
     _check(orc, scorer, G, bf16, 1, n, 20, ks.uniform_ids(ks.rng(4, ks.TAG_HELDOUT), 0, n, Q))
 
 
-# few queries: the candidates in 1, 2 and 3 chunks that grow up to 10 times (4,096 rows, 10 and 100 times that, and a tile more)
+# few queries: the candidates in one chunk, in two and more (4,096 rows, 10 and 100 times that, and a tile more)
 @pytest.mark.parametrize("n", [4096, 4097, 40960, 40961, 409601])
 @pytest.mark.parametrize("K", [5, 100])
 def test_few_queries_with_fast_growing_chunks(orc, n, K):
     G = make_case("transe", n, 5, 16, 3, 0, False)
     _check(orc, "transe", G, False, 0, n, K, ks.uniform_ids(ks.rng(6, ks.TAG_HELDOUT), 0, n, 3))
+
+
+def test_clusters_of_neighbouring_rows_overflow_no_append_area():
+    """A table whose rows come in clusters of 50 that are alike, as one sorted by community has them: the winners of a query are neighbours
+    and land in few append areas.  A query whose area overflows is ranked exhaustively, which takes a hundred times as long as the scan, so
+    the call's time beside that of the same rows in any order shows whether one did."""
+    import paper_2211_12281_amd as kge
+    n, d, Q, K = 1_000_000, 256, 512, 100
+    g = torch.Generator(device="cuda").manual_seed(5)
+    cen = torch.randn((n // 50, d), generator=g, device="cuda") * 0.06
+    ent = torch.empty((n, d), dtype=torch.bfloat16, device="cuda")
+    for i in range(0, n, 1 << 18):
+        j = min(n, i + (1 << 18))
+        ent[i:j] = (cen[torch.arange(i, j, device="cuda") // 50] + torch.randn((j - i, d), generator=g, device="cuda") * 0.02).bfloat16()
+    rel = (torch.randn((9, d), generator=g, device="cuda") * 0.01).bfloat16()
+    h = torch.randint(0, n, (Q,), generator=g, device="cuda", dtype=torch.int32)
+    r = torch.randint(0, 9, (Q,), generator=g, device="cuda", dtype=torch.int32)
+    order = torch.randperm(n, generator=g, device="cuda")
+    at = torch.empty_like(order)
+    at[order] = torch.arange(n, device="cuda")
+    ms = []
+    for model, heads in ((kge.Model("transe", ent, rel), h), (kge.Model("transe", ent[order].contiguous(), rel), at[h.long()].int())):
+        for _ in range(2):
+            kge.topk(model, heads, r, 0, n, K)
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        for _ in range(3):
+            kge.topk(model, heads, r, 0, n, K)
+        e[1].record()
+        torch.cuda.synchronize()
+        ms.append(e[0].elapsed_time(e[1]) / 3)
+    assert ms[0] <= 10 * ms[1], ms
 
 
 def test_long_lists_of_appends(orc):
