@@ -92,7 +92,7 @@ constexpr bool kge_block_planes(bool bf16, int rb, int mode) { (void)rb; return 
 // (rounded) TransH normal.
 struct __attribute__((aligned(16))) KgeRowInfo { float qn, c, K, wn; };
 
-// Placement of the workgroups (own tile, split) of the block kernels on the 8 dies, to which workgroup ids go in turn: a
+// Placement of the workgroups (own tile, split) of the block kernels but block_gradp.hip on the 8 dies, to which workgroup ids go in turn: a
 // die takes the splits congruent to xcd / per modulo 8 / per and the own tiles congruent to xcd % per modulo per (per 1,
 // 2, 4 or 8), so its L2 fills with 1 / per of the own rows and per / 8 of the streamed ones.
 __device__ __forceinline__ bool kge_place(int own_tiles, int nsplit, int per, int &own_tile, int &split) {
