@@ -109,7 +109,7 @@ __device__ __forceinline__ kge_f32x16 kge_mma3(kge_f32x16 acc, const KgeP3 &A, c
     return acc;
 }
 
-// Two fp16 pieces of a value scaled by a power of two (kge_plane_exp: rows; coefficients below): x = x0 + x1 to 2^-24 of x or to
+// Two fp16 pieces of a value scaled by a power of two (KgePlaneScale: rows; coefficients below): x = x0 + x1 to 2^-24 of x or to
 // 2^-25 over the scale, whichever is larger, three products per pair, a0 b0 + a0 b1 + a1 b0 (a1 b1 <= 2^-24 |a| |b| is left out).
 struct KgeP2 { uint4 p[2]; };
 typedef _Float16 kge_f16x8 __attribute__((ext_vector_type(8)));

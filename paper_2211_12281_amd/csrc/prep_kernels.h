@@ -32,7 +32,7 @@ int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t
                            void *q_planes = nullptr, void *t_planes = nullptr, float *t_inv_scale = nullptr,
                            float *bias = nullptr,             // bias [Np]: 0 for the N negatives, -inf behind them
                            const KgeNegGen *gen = nullptr,    // gen->out set: neg is ignored, the ids are drawn and written there
-                           // training: exponents of the planes' scales (kge_plane_exp) in place of rowinfo.K and t_inv_scale
+                           // training: exponents of the planes' scales (KgePlaneScale) in place of rowinfo.K and t_inv_scale
                            int32_t *q_exp = nullptr, int32_t *t_exp = nullptr);
 // gather of the negatives and their transposed copy Tt [dp][Np] in one launch (bf16 tables)
 int kge_run_tgather_t(const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T, void *Tt, float *tn,

@@ -70,46 +70,47 @@ struct KgeQbuildArgs {
     float *pos_ws, *pos_out;
     _Float16 *planes;                  // optional: the two fp16 pieces of the scaled q, [2][Bp][dp], with W two more for the
                                        // unit normal (scaled by KGE_PLANE_UNIT_SCALE); then rowinfo.K = 1 / scale of the row
-    int32_t *exps;                     // with planes, training: the exponents of the rows' 1 / scale [Bp] (kge_plane_exp; unit normals: KGE_PLANE_UNIT_EXP)
+    int32_t *exps;                     // with planes, training: the exponents of the rows' 1 / scale [Bp] (KgePlaneScale; unit normals: KGE_PLANE_UNIT_EXP)
 };
 struct KgeTgatherArgs {
     const int32_t *neg; int N, Np; void *T; float *tn; _Float16 *planes; float *inv_scale; int32_t *exps; float *bias;
     KgeNegGen gen;                     // gen.out set: the ids are drawn here (and written to gen.out) instead of read from neg
 };
 
-// fp32 rows as TWO fp16 planes for the matrix cores: the row is scaled by a power of two s that brings its largest
-// magnitude into [2^10, 2^11) (well inside the fp16 range, with the second piece of every element that matters still
-// normal), then s x = x1 + x2 with x1 = fp16(s x), x2 = fp16(s x - x1): 22 significand bits, residual < 2^-22 s |x|.
-// Plane p of element i at planes[p n + i]; the contraction is multiplied by the two rows' 1 / s afterwards (exact).
-__device__ __forceinline__ float kge_plane_scale(float amax, float &inv) {
-    if (!(amax > 0.f)) { inv = 1.f; return 1.f; }
-    int e;
-    (void)frexpf(amax, &e);                                 // amax = f 2^e, f in [0.5, 1)
-    e = e < -115 ? -115 : (e > 128 ? 128 : e);              // (the scale and its reciprocal are normal numbers)
-    inv = ldexpf(1.f, e - 11);
-    return ldexpf(1.f, 11 - e);
-}
-// The training passes: the row is 2^e times its planes, e an integer, so every fp32 row has one (a product of two rows' scales is no
-// fp32 number where both are tiny or one is huge).  A row that holds an infinity: its finite elements count for nothing beside it, and
-// +-2^15 times 2^235 is an infinity in every product with a value of 2^-122 or more (inf - fp16(inf) would make the whole row NaN).
-__device__ __forceinline__ int kge_plane_exp(float amax) {
-    if (!(amax > 0.f)) return 0;
-    if (amax == INFINITY) return 235;
-    int e;
-    (void)frexpf(amax, &e);
-    return e - KGE_PLANE_TOP;
-}
-__device__ __forceinline__ float kge_plane_scaled(float x, int e) {
-    x = ldexpf(x, -e);
-    return fabsf(x) == INFINITY ? copysignf(32768.f, x) : x;
-}
+// fp32 rows as TWO fp16 planes for the matrix cores: the row is 2^e times its planes, which are x1 = fp16(2^-e x) and x2 = fp16(2^-e x - x1),
+// plane p of element i at planes[p n + i].
+// Score-only calls: e brings the row's largest magnitude into [2^10, 2^11) and the contraction is multiplied by the two rows' 2^e (exact).
+// Training calls: into [2^(KGE_PLANE_TOP - 1), 2^KGE_PLANE_TOP), and the kernels take the exponents, so every fp32 row has one (a product
+// of two rows' scales is no fp32 number where both are tiny or one is huge).  A row that holds an infinity: its finite elements count for
+// nothing beside it, and +-2^15 times 2^235 is an infinity in every product with a value of 2^-122 or more (inf - fp16(inf) would make the
+// whole row NaN).  (A template argument of the kernels: chosen at run time it cost the score-only calls 0.4-0.9 us of 42.)
+constexpr int KGE_PLANE_INF_EXP = 235;
+template <bool TRAIN> struct KgePlaneScale {
+    int e = 0;
+    float s = 1.f;                                          // score-only calls: 2^-e
+    __device__ __forceinline__ explicit KgePlaneScale(float amax) {
+        if (!(amax > 0.f)) return;
+        (void)frexpf(amax, &e);                             // amax = f 2^e, f in [0.5, 1)
+        if constexpr (TRAIN) e = amax == INFINITY ? KGE_PLANE_INF_EXP : e - KGE_PLANE_TOP;
+        else {
+            e = (e < -115 ? -115 : e > 128 ? 128 : e) - 11; // (2^e and 2^-e are normal numbers)
+            s = ldexpf(1.f, -e);
+        }
+    }
+    __device__ __forceinline__ float operator()(float x) const {
+        if constexpr (!TRAIN) return s * x;
+        x = ldexpf(x, -e);
+        if (e == KGE_PLANE_INF_EXP && fabsf(x) == INFINITY) x = copysignf(32768.f, x);
+        return x;
+    }
+};
 __device__ __forceinline__ void kge_store_planes(_Float16 *planes, int64_t n, int64_t i, float xs) {
     const _Float16 x1 = (_Float16)xs;
     planes[i] = x1; planes[n + i] = (_Float16)(xs - (float)x1);
 }
 
 // NJ: columns per lane (dp <= 64 NJ)
-template <bool BF16, int SC, int NJ = KGE_MAXJ>
+template <bool BF16, int SC, int NJ = KGE_MAXJ, bool TRAIN = false>
 __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a) {
     const KgeModelDev &m = a.m;
     const int32_t *h = a.h, *r = a.r, *t = a.t;
@@ -126,10 +127,10 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
             if (Q2) El<BF16>::st(Q2, (int64_t)b * dp + j, 0.f);
             if (Q32) Q32[(int64_t)b * dp + j] = 0.f;
             if (W32) W32[(int64_t)b * dp + j] = 0.f;
-            if (a.planes) kge_store_planes(a.planes, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
-            if (a.planes && W) kge_store_planes(a.planes + 2 * (int64_t)Bp * dp, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
+            if (!BF16 && a.planes) kge_store_planes(a.planes, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
+            if (!BF16 && a.planes && W) kge_store_planes(a.planes + 2 * (int64_t)Bp * dp, (int64_t)Bp * dp, (int64_t)b * dp + j, 0.f);
         }
-        if (lane == 0) { rowinfo[b] = KgeRowInfo{0.f, 0.f, a.planes ? 1.f : 0.f, 0.f}; if (pos_ws) pos_ws[b] = 0.f; if (a.exps) a.exps[b] = 0; }
+        if (lane == 0) { rowinfo[b] = KgeRowInfo{0.f, 0.f, !BF16 && a.planes ? 1.f : 0.f, 0.f}; if (pos_ws) pos_ws[b] = 0.f; if (TRAIN) a.exps[b] = 0; }
         return;
     }
     KgeRowCtx<BF16, NJ> cx;
@@ -140,16 +141,13 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
     Norm qn = 0, cq = 0, wn = 0;
     float s_pos = 0.f, wt = 0.f;
     float tv[NJ];
-    float q_scale = 1.f, q_inv = 0.f;
-    int q_exp = 0;
-    if (a.planes) {
-        float amax = 0.f;
+    float q_max = 0.f;
+    if (!BF16 && a.planes) {
 #pragma unroll
-        for (int k = 0; k < NJ; ++k) amax = fmaxf(amax, fabsf(cx.q[k]));
-        amax = kge_wave_max(amax);
-        if (a.exps) q_exp = kge_plane_exp(amax); else q_scale = kge_plane_scale(amax, q_inv);
+        for (int k = 0; k < NJ; ++k) q_max = fmaxf(q_max, fabsf(cx.q[k]));
+        q_max = kge_wave_max(q_max);
     }
-    const float w_scale = a.exps ? ldexpf(1.f, -KGE_PLANE_UNIT_EXP) : KGE_PLANE_UNIT_SCALE;
+    const KgePlaneScale<TRAIN> q_scale(q_max);
 #pragma unroll
     for (int k = 0; k < NJ; ++k) {
         const int j = lane + 64 * k;
@@ -163,9 +161,10 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
             if (W) El<BF16>::st(W, (int64_t)b * dp + j, cx.w[k]);
             if (Q32) Q32[(int64_t)b * dp + j] = cx.q[k];      // unrounded copies for the 1-norm kernels
             if (W32) W32[(int64_t)b * dp + j] = cx.w[k];
-            if (a.planes) kge_store_planes(a.planes, (int64_t)Bp * dp, (int64_t)b * dp + j, a.exps ? kge_plane_scaled(cx.q[k], q_exp) : q_scale * cx.q[k]);
-            if (a.planes && W)
-                kge_store_planes(a.planes + 2 * (int64_t)Bp * dp, (int64_t)Bp * dp, (int64_t)b * dp + j, w_scale * cx.w[k]);
+            if (!BF16 && a.planes) kge_store_planes(a.planes, (int64_t)Bp * dp, (int64_t)b * dp + j, q_scale(cx.q[k]));
+            if (!BF16 && a.planes && W)
+                kge_store_planes(a.planes + 2 * (int64_t)Bp * dp, (int64_t)Bp * dp, (int64_t)b * dp + j,
+                                 (TRAIN ? (float)(1 << -KGE_PLANE_UNIT_EXP) : KGE_PLANE_UNIT_SCALE) * cx.w[k]);
         }
     }
     qn = kge_wave_sum(qn);
@@ -190,8 +189,8 @@ __device__ __forceinline__ void kge_qbuild_body(int blk, const KgeQbuildArgs &a)
     s_pos = kge_wave_sum(s_pos);
     if (!(SC == KGE_DISTMULT || SC == KGE_COMPLEX)) s_pos = m.p1 ? -s_pos : -sqrtf(s_pos);
     if (lane == 0) {
-        rowinfo[b] = KgeRowInfo{(float)qn, (float)cq, q_inv, SC == KGE_TRANSH ? (float)wn : 1.f};     // (K: set by the row finish when training)
-        if (a.exps) a.exps[b] = q_exp;
+        rowinfo[b] = KgeRowInfo{(float)qn, (float)cq, !BF16 && !TRAIN && a.planes ? ldexpf(1.f, q_scale.e) : 0.f, SC == KGE_TRANSH ? (float)wn : 1.f};     // (K: set by the row finish when training)
+        if (TRAIN) a.exps[b] = q_scale.e;
         if (pos_ws) pos_ws[b] = s_pos;
         if (pos_out) pos_out[b] = s_pos;
     }
@@ -212,7 +211,7 @@ __host__ __device__ inline int kge_tgather_group_lanes(int dp, int es) {
 constexpr int KGE_TG_INFLIGHT = 4;                          // row loads in flight per lane
 __host__ __device__ inline int kge_tgather_rows_per_wave(int dp, int es) { return KGE_TG_INFLIGHT * (64 / kge_tgather_group_lanes(dp, es)); }
 
-template <bool BF16>
+template <bool BF16, bool TRAIN = false>
 __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, const int32_t *neg, int N, int Np, int dp, void *T,
                                                  float *tn, _Float16 *planes = nullptr, float *inv_scale = nullptr,
                                                  const KgeNegGen *gen = nullptr, int32_t *exps = nullptr) {
@@ -275,21 +274,19 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
             if (lg == 0 && n < Np) tn[n] = (float)s;
             if constexpr (!BF16) {
                 if (planes) {
-                    float inv = 0.f;
-                    const int e = exps ? kge_plane_exp(amax) : 0;
-                    const float sc = exps ? 0.f : kge_plane_scale(amax, inv);
+                    const KgePlaneScale<TRAIN> scale(amax);
                     if (live) {                         // the lane's four elements: one 8-byte store per plane
                         typedef _Float16 h4 __attribute__((ext_vector_type(4)));
                         h4 p1, p2;
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
-                            const float x = __uint_as_float(w[k]), xs = exps ? kge_plane_scaled(x, e) : sc * x;
+                            const float xs = scale(__uint_as_float(w[k]));
                             p1[k] = (_Float16)xs; p2[k] = (_Float16)(xs - (float)p1[k]);
                         }
                         _Float16 *dst = planes + (int64_t)n * dp + lg * 4;
                         *(h4 *)dst = p1; *(h4 *)(dst + (int64_t)Np * dp) = p2;
                     }
-                    if (lg == 0 && n < Np) { if (exps) exps[n] = e; else inv_scale[n] = inv; }
+                    if (lg == 0 && n < Np) { if constexpr (TRAIN) exps[n] = scale.e; else inv_scale[n] = ldexpf(1.f, scale.e); }
                 }
             }
         }
@@ -314,15 +311,12 @@ __device__ __forceinline__ void kge_tgather_body(int blk, const KgeModelDev &m, 
         s = kge_wave_sum(s);
         if (lane == 0) tn[n] = (float)s;
         if (!BF16 && planes) {                              // (second walk over the row, now that its scale is known)
-            float inv = 0.f;
-            amax = kge_wave_max(amax);
-            const int e = exps ? kge_plane_exp(amax) : 0;
-            const float sc = exps ? 0.f : kge_plane_scale(amax, inv);
+            const KgePlaneScale<TRAIN> scale(kge_wave_max(amax));
             for (int j = lane; j < dp; j += 64) {
                 const float v = (n < N && j < m.dim) ? El<BF16>::ld(m.ent, off + j) : 0.f;
-                kge_store_planes(planes, (int64_t)Np * dp, (int64_t)n * dp + j, exps ? kge_plane_scaled(v, e) : sc * v);
+                kge_store_planes(planes, (int64_t)Np * dp, (int64_t)n * dp + j, scale(v));
             }
-            if (lane == 0) { if (exps) exps[n] = e; else inv_scale[n] = inv; }
+            if (lane == 0) { if constexpr (TRAIN) exps[n] = scale.e; else inv_scale[n] = ldexpf(1.f, scale.e); }
         }
     }
 }
@@ -335,12 +329,12 @@ template <bool BF16, int SC>
 __global__ void kge_qbuild_kernel(KgeQbuildArgs a) { kge_qbuild_body<BF16, SC>(blockIdx.x, a); }
 // query build and gather of the negatives in ONE launch (the first q_blocks workgroups build queries): the two are
 // independent, and a launch of their own each would cost the second one's start-up on the critical path
-template <bool BF16, int SC, int NJ>
+template <bool BF16, int SC, int NJ, bool TRAIN>
 __global__ void kge_qbuild_tgather_kernel(int q_blocks, KgeQbuildArgs a, KgeTgatherArgs g) {
     if (g.bias)                                                         // 0 for the negatives, -inf for the padding rows behind them
         for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < g.Np; n += gridDim.x * blockDim.x) g.bias[n] = n < g.N ? 0.f : -INFINITY;
-    if ((int)blockIdx.x < q_blocks) kge_qbuild_body<BF16, SC, NJ>(blockIdx.x, a);
-    else kge_tgather_body<BF16>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen, g.exps);
+    if ((int)blockIdx.x < q_blocks) kge_qbuild_body<BF16, SC, NJ, TRAIN>(blockIdx.x, a);
+    else kge_tgather_body<BF16, TRAIN>(blockIdx.x - q_blocks, a.m, g.neg, g.N, g.Np, a.dp, g.T, g.tn, g.planes, g.inv_scale, &g.gen, g.exps);
 }
 
 // gather of the shared negatives AND their transposed copy in one launch (bf16 tables): a workgroup takes 32 negatives, every
@@ -813,13 +807,17 @@ int kge_run_qbuild_tgather(const KgeModelDev &m, const int32_t *h, const int32_t
                            void *q_planes, void *t_planes, float *t_inv_scale, float *bias, const KgeNegGen *gen, int32_t *q_exp, int32_t *t_exp) {
     const int rows_wg = 4 * kge_tgather_rows_per_wave(dp, m.bf16 ? 2 : 4);
     const int qb = (Bp + 3) / 4, tb = (Np + rows_wg - 1) / rows_wg;
-    if (qb == 0 || tb == 0 || ((q_planes || t_planes) && m.bf16) || (t_planes && !t_inv_scale && !t_exp)) return KGE_E_INVALID_ARG;
+    if (qb == 0 || tb == 0 || ((q_planes || t_planes) && m.bf16) || (t_planes && !t_inv_scale && !t_exp) || !t_exp != !q_exp || (t_exp && !(q_planes && t_planes))) return KGE_E_INVALID_ARG;
     const KgeQbuildArgs a{m, h, r, t, B, Bp, dp, Q, W, Q2, Q32, W32, rowinfo, pos_ws, pos_out, (_Float16 *)q_planes,
                           q_exp};
     const KgeTgatherArgs g{neg, N, Np, T, tn, (_Float16 *)t_planes, t_inv_scale, t_exp, bias, gen ? *gen : KgeNegGen{}};
     // (kernels for the columns of a padded row: the query is built without branches, lanes past the row read its first column again;
     // one kernel for 512 columns: TransH 8,192 x 4,096 step 454 instead of 453 us, ComplEx 4,096 x 16,384 196 / 195)
-#define KGE_QT_NJ(BF, SC, NJ) hipLaunchKernelGGL((kge_qbuild_tgather_kernel<BF, SC, NJ>), dim3(qb + tb), dim3(256), 0, st, qb, a, g)
+#define KGE_QT_NJ(BF, SC, NJ)                                                                                                          \
+    do {                                                                                                                               \
+        if (!BF && t_exp) hipLaunchKernelGGL((kge_qbuild_tgather_kernel<BF, SC, NJ, !BF>), dim3(qb + tb), dim3(256), 0, st, qb, a, g); \
+        else hipLaunchKernelGGL((kge_qbuild_tgather_kernel<BF, SC, NJ, false>), dim3(qb + tb), dim3(256), 0, st, qb, a, g);            \
+    } while (0)
 #define KGE_QT(BF, SC) do { if (dp <= 128) KGE_QT_NJ(BF, SC, 2); else if (dp <= 256) KGE_QT_NJ(BF, SC, 4); else KGE_QT_NJ(BF, SC, KGE_MAXJ); } while (0)
     if (m.bf16) { KGE_SC_SWITCH(true, KGE_QT) } else { KGE_SC_SWITCH(false, KGE_QT) }
 #undef KGE_QT
