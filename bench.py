@@ -640,8 +640,9 @@ def main():
                 # says that the path is not on the fp32 pipe); the 16-bit pipe does three times that work, against
                 # its own peak:
                 roof["issued_f16"] = {"achieved": 3 * ach, "peak": PEAK_BF16_TFLOPS, "frac": 3 * ach / PEAK_BF16_TFLOPS}
-            if dom in ("block_fwd", "block_gradt") and not wl.bf16:
-                # fp32 training passes: the same split of every operand, three fp16 matrix products per fp32 one
+            if dom in ("block_fwd", "block_gradt") and not wl.bf16 and wl.B * wl.N > 7 << 20:
+                # fp32 training passes: the same split of every operand, three fp16 matrix products per fp32 one (smaller blocks
+                # keep their scores in memory and contract three bf16 pieces)
                 roof["issued_f16"] = {"achieved": 3 * ach, "peak": PEAK_BF16_TFLOPS, "frac": 3 * ach / PEAK_BF16_TFLOPS}
         else:
             roof = {"kernel": dom, "bound": "hbm", "achieved": None, "peak": PEAK_HBM_GBS, "unit": "GB/s",
