@@ -166,7 +166,7 @@ int kge_score(const kge_model_t *model, const int32_t *h, const int32_t *r, cons
  * value as two fp16 pieces x0 + x1, and the three products a0 b0 + a0 b1 + a1 b0 on the 16-bit matrix cores with fp32 accumulation.
  * A value is good to 2^-24 of itself down to 2^-16 of its row's largest element, and to 2^-40 of that element below: a gradient column
  * that is 2^-20 of the others in every row is good to about 1e-6, one of 2^-24 to 1e-4.  a1 b1, dropped, is below 2^-24 |a| |b|.  The pairs'
- * coefficients likewise, times a power of two per row of the gradient that follows the largest.  A row with an infinite element counts
+ * coefficients likewise, times a scale per row of the gradient that follows the largest.  A row with an infinite element counts
  * by that element alone; a bilinear score of -inf has no weight.  Distances come from |q|^2 + |t|^2 - 2 q.t, and below 1e-3 of |q|^2 + |t|^2 from the
  * fp32 rows themselves.
  */
