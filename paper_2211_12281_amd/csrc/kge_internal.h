@@ -77,10 +77,10 @@ constexpr int kge_block_occ(bool bf16, int rb, bool transh, int mode) {
 // The fp32 training passes read their operands as two fp16 planes [2][rows][dp] of rows scaled by a power of two of their own (kge_split2),
 // which the gather writes beside the fp32 rows; there are no transposed copies.  The fp32 matrix instruction runs at 1/16 of the 16-bit
 // rate; three products of pieces replace sixteen.  Calls in us, before / here.  Rows of 512 bytes (before: three bf16 pieces, six products):
-// TransH 8,192 x 4,096 x 128 392 / 322 (passes 211 + 201 -> 170 + 164: the epilogue and the contractions of a tile one after the other in one
-// wave per SIMD), TransE 234 / 181, ComplEx 8,000 x 3,000 x 128 230 / 154, DistMult 4,096 x 4,096 x 96 111 / 92.  Rows of 1,024 bytes (fp32
-// instructions over the queries, bf16 pieces made in registers over the negatives): TransE 4,096 x 4,096 x 256 366 / 213, DistMult 2,048 x
-// 8,192 x 200 302 / 147, RotatE 8,192 x 2,000 x 256 353 / 228.
+// TransH 8,192 x 4,096 x 128 388 / 310 (passes 211 + 201 -> 148 + 147: the epilogue and the contractions of a tile one after the other in one
+// wave per SIMD), TransE 234 / 178, ComplEx 8,000 x 3,000 x 128 229 / 154, DistMult 4,096 x 4,096 x 96 110 / 93.  Rows of 1,024 bytes (fp32
+// instructions over the queries, bf16 pieces made in registers over the negatives): TransE 4,096 x 4,096 x 256 366 / 214, DistMult 2,048 x
+// 8,192 x 200 302 / 145, RotatE 8,192 x 2,000 x 256 384 / 228.
 // Errors against 64 bits over 120 drawn calls on rows of up to 512 bytes: 0.97-1.00 times those of before (geometric mean of every gradient),
 // half on rows of 1,024 bytes.  Beyond those ranges: rows at 0.05 and 0.1 of its length from a query 0.6-0.9 times, at 1e-5 (where the
 // gradient is the difference of two rows' sums: 1e-2 of it either way) 1.05-1.2 times; a column that is 2^-20 of the others the same, one of
