@@ -338,18 +338,19 @@ def test_block_kernels_on_planes_with_columns_of_all_sizes(orc, block_passes, sc
         assert err.max() <= 1e-4, (sl, int(err.argmax()), float(err.max()))
 
 
+@pytest.mark.parametrize("top", [30.0, 39.0, 45.0, 120.0])
 @pytest.mark.parametrize("loss,dim", [("sampled_softmax", 64), ("logsigmoid", 128), ("sampled_softmax", 256)])
-def test_block_kernels_on_planes_when_later_small_rows_outweigh_large_ones(orc, block_passes, loss, dim):
-    """Of every four tiles of negatives the first holds rows of 2^30 with scores of about -30, the others rows of 1 with scores of about
-    30: the reference rises by 2^90 after the first tile, and the scale of the coefficients, set for 2^30 times theirs, with it.  The
-    large elements lie where the queries are zero; the other columns are compared."""
+def test_block_kernels_on_planes_when_later_small_rows_outweigh_large_ones(orc, block_passes, loss, dim, top):
+    """Of every four tiles of negatives the first holds rows of 2^30 with scores of about -top, the others rows of 1 with scores of about
+    top: the reference rises by 2^90 (top 30) after the first tile, and the scale of the coefficients, set for 2^30 times theirs, with
+    it, or ends where it would pass 2^126 (some rows at 39, all above).  The large elements lie where the queries are zero; the other columns are compared."""
     import paper_2211_12281_amd as kge
     B, N, half = 4096, 1600, dim // 2
     g = np.random.default_rng(dim)
     ent = np.zeros((B + N + 10, dim), dtype=np.float32)
     ent[:B, :half] = g.uniform(0.5, 1.5, (B, half))
     sign = np.where(np.arange(N) % 128 < 32, -1.0, 1.0)[:, None]
-    ent[B:B + N, :half] = sign * 30.0 / half * g.uniform(0.9, 1.1, (N, half))
+    ent[B:B + N, :half] = sign * top / half * g.uniform(0.9, 1.1, (N, half))
     ent[B:B + N, half:] = np.where(sign < 0, 2.0 ** 30, 1.0) * g.uniform(-1, 1, (N, half))
     G = dict(ent=ent, rel=np.ones((3, dim), dtype=np.float32), relw=None, h=np.arange(B, dtype=np.int32), r=(np.arange(B) % 3).astype(np.int32),
              t=np.full(B, B + N, dtype=np.int32), neg=np.arange(B, B + N, dtype=np.int32))
