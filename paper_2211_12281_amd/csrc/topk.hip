@@ -72,7 +72,12 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // 16-byte chunks XOR-swizzled by a bit permutation of (row mod 16) (tk_swz): the MFMA A-fragment reads of 16
 // consecutive rows at one chunk index then fall into 16 different bank groups (an XOR with row mod 8 reaches half the
 // LDS's rate: half of the LDS's active cycles were bank conflicts).  The MFMAs of tile t+1 are issued before the epilogue of tile t, so the
-// matrix pipe works while the vector ALU filters.
+// matrix pipe works while the vector ALU filters.  What bounds it is what the two waves of a SIMD issue beside their MFMAs, and then
+// the power that MFMAs on toggling operands draw (8,192 queries over 4M rows without hits: 1,390-1,420 TFLOP/s; 1,500 without the
+// copies, 1,540 with neither copies nor epilogue).  So a tile costs the epilogue one maximum per accumulator: the held-out tail's
+// count and the appends are behind one test of it, no accumulator is copied (two rounds per turn of the loop), no register is
+// spilled (a reload waits for the copies in flight), and the copies of rows that do not fill RB bytes are as cheap as the others' (a
+// lane mask each).  8,192 queries x 10M, d 256: 39.3 -> 35.8 ms; 539 x 4.7M, d 112 (padded): 3.55 -> 1.87 ms.
 //
 // FN: the squared norms of the candidates (distance scorers: part of the value; all: their maximum, which the safety check
 // needs) come from the tiles in the LDS instead of a pass of their own over the table.  Every workgroup of a distance scan
@@ -91,7 +96,7 @@ void topk_scan_kernel(const TopkArgs a) {
     constexpr int LPW = IPW + (SIDE ? 1 : 0);
     constexpr int NSTAGE = RB == 512 ? 4 : 3;
     constexpr int SIDE_SLOTS = NSTAGE + 1;
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+    extern __shared__ __attribute__((aligned(256))) char lds[];
     char *side_base = lds + NSTAGE * TILE_BYTES;        // [SIDE_SLOTS][4 waves][64 floats]
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
 
@@ -114,7 +119,7 @@ void topk_scan_kernel(const TopkArgs a) {
     }
 
     uint4 own[OB][KS];
-    float thr[NQ], vt[NQ];
+    float thr[NQ], vt[NQ], low[NQ];
     int qid[NQ], myc[NQ];
     uint32_t above[NQ];
 #pragma unroll
@@ -126,6 +131,7 @@ void topk_scan_kernel(const TopkArgs a) {
         for (int ks = 0; ks < KS; ++ks) own[ob][ks] = *(const uint4 *)(p + ks * 32);
         thr[ob] = a.thr[qid[ob]];
         vt[ob] = a.vt[qid[ob]];
+        low[ob] = fminf(thr[ob], vt[ob]);               // (vt is +inf where there is no held-out tail)
         above[ob] = 0;
     }
     float cq = 0.f;
@@ -139,33 +145,48 @@ void topk_scan_kernel(const TopkArgs a) {
     // ---- loader geometry of this lane: instruction jj covers LDS bytes [(wave*IPW+jj) KB, +1 KB) ----
     // A copy takes a wave-uniform base (the tile's first row, scalar registers) and ONE 32-bit offset per lane that does not
     // change from tile to tile (row in the tile x stride + source chunk), and its LDS address is scalar arithmetic on the
-    // wave's number: no vector instruction per copy in the loop.  Rows shorter than RB (padding columns, which read the 16
-    // zero bytes) and the table's last, ragged tile take per-lane 64-bit addresses, computed where they are needed.
+    // wave's number: no vector instruction per copy in the loop.  The table's last, ragged tile (and rows too far apart for the
+    // offset) take per-lane 64-bit addresses, computed where they are needed; their padding columns read the 16 zero bytes.
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    auto ld_row_of = [&](int jj) { return ((wave_u * IPW + jj) * 1024 + lane * 16) / RB; };
-    auto ld_col_of = [&](int jj) {
-        const int byte = (wave_u * IPW + jj) * 1024 + lane * 16, r = byte / RB, pos = (byte % RB) / 16;
+    auto ld_row_of = [&](int jj, int ln) { return ((wave_u * IPW + jj) * 1024 + ln * 16) / RB; };
+    auto ld_col_of = [&](int jj, int ln) {
+        const int byte = (wave_u * IPW + jj) * 1024 + ln * 16, r = byte / RB, pos = (byte % RB) / 16;
         return (pos ^ tk_swz(r)) * 16;                  // source chunk that belongs at this LDS position
     };
     uint32_t ld_off[IPW];
 #pragma unroll
-    for (int jj = 0; jj < IPW; ++jj) ld_off[jj] = (uint32_t)(ld_row_of(jj) * a.ent_stride + ld_col_of(jj));
-    const bool unpadded = a.valid_bytes == RB && a.ent_stride < (1ll << 26);     // (uniform; 32 rows x stride fits the offset)
+    for (int jj = 0; jj < IPW; ++jj) ld_off[jj] = (uint32_t)(ld_row_of(jj, lane) * a.ent_stride + ld_col_of(jj, lane));
+    // (a lane number that the compiler cannot see through: what rare paths derive from it is computed there instead of in
+    // front of the loop, where it would hold - and spill - registers; a reload waits for the asynchronous copies in flight)
+    auto here = [&] { int ln = lane; asm volatile("" : "+v"(ln)); return ln; };
+    // Rows shorter than RB: the lanes of the padding columns take no part in the copies (they may lie behind the table's end), and
+    // what they would write is zeroed once, here.
+    uint64_t ld_live[IPW];
+#pragma unroll
+    for (int jj = 0; jj < IPW; ++jj) ld_live[jj] = __ballot(ld_col_of(jj, lane) < a.valid_bytes);
+    if (a.valid_bytes != RB) {
+        for (int i = tid * 16; i < NSTAGE * TILE_BYTES; i += 256 * 16) *(uint4 *)(lds + i) = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+    }
+    const bool offsets32 = a.ent_stride < (1ll << 26);  // (uniform; 32 rows x stride fits the offset)
     auto issue = [&](int64_t tile, int slot) {
         tile = tile < t1 ? tile : t1 - 1;               // past the end: a harmless repeat keeps vmcnt uniform
         const int stage = slot % NSTAGE;
         const uint32_t lbase = lds0 + stage * TILE_BYTES + wave_u * (IPW * 1024);
-        if (unpadded && tile * TK_ST + TK_ST <= a.ncand) {
+        if (offsets32 && tile * TK_ST + TK_ST <= a.ncand) {
             const char *tb = a.ent + tile * TK_ST * a.ent_stride;
 #pragma unroll
             for (int jj = 0; jj < IPW; ++jj)
-                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lbase + jj * 1024), "v"(ld_off[jj]), "s"(tb) : "memory");
+                // (the whole wave is here: all lanes are live again behind the copy)
+                asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
+                             ::"s"(lbase + jj * 1024), "v"(ld_off[jj]), "s"(tb), "s"(ld_live[jj]) : "memory");
         } else {
+            const int ln = here();
 #pragma unroll
             for (int jj = 0; jj < IPW; ++jj) {
-                int64_t cand = tile * TK_ST + ld_row_of(jj);
+                int64_t cand = tile * TK_ST + ld_row_of(jj, ln);
                 cand = cand < a.ncand ? cand : a.ncand - 1; // rows past the end are masked in the epilogue
-                const int col = ld_col_of(jj);
+                const int col = ld_col_of(jj, ln);
                 const char *gp = col < a.valid_bytes ? a.ent + cand * a.ent_stride + col : (const char *)a.zeros;
                 async_copy16(gp, lbase + jj * 1024);
             }
@@ -173,19 +194,22 @@ void topk_scan_kernel(const TopkArgs a) {
         if constexpr (SIDE) async_copy4(a.tn + tile * TK_ST + lr, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
     };
     // ---- A-fragment addresses: chunk (2 ks + g) of row lr sits at position chunk ^ tk_swz(lr) ----------
-    int frag_off[8];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) frag_off[b] = lr * RB + 16 * ((2 * b + g) ^ tk_swz(lr));
+    // (stages and rows are whole multiples of 256 bytes, so chunk 2 b + g of a row is chunk g's address with b's bits flipped: one
+    // register instead of eight)
+    const uint32_t frag0 = lds0 + lr * RB + 16 * (g ^ tk_swz(lr));
     auto mma_tile = [&](int slot, kge_f32x16 (&acc)[OB]) {
-        const char *base = lds + (slot % NSTAGE) * TILE_BYTES;
+        const uint32_t frag = frag0 + (slot % NSTAGE) * TILE_BYTES;
+        auto fragment = [&](int ks) {
+            return *(const __attribute__((address_space(3))) kge_u32x4 *)(uintptr_t)((frag ^ (32 * (ks & 7))) + 256 * (ks >> 3));
+        };
         // Rows of 512 bytes: the fragment of step ks + AH is requested before the MFMAs of step ks are issued, and the
         // scheduler is held to that order (left to itself the compiler reads each fragment right before its two MFMAs and
         // waits for it).  The kernels of 1,024-byte rows have no registers for fragments in flight: held to this order they
         // spill operands inside the loop, so they keep the compiler's.
         constexpr int AH = RB == 512 ? (TH ? 2 : 3) : 0;
-        uint4 av[AH > 0 ? AH + 1 : KS];
+        kge_u32x4 av[AH > 0 ? AH + 1 : KS];
 #pragma unroll
-        for (int ks = 0; ks < (AH > 0 ? AH : KS); ++ks) av[ks] = *(const uint4 *)(base + frag_off[ks & 7] + 256 * (ks >> 3));
+        for (int ks = 0; ks < (AH > 0 ? AH : KS); ++ks) av[ks] = fragment(ks);
         if constexpr (SIDE) {
             // TransE: the accumulators start at -|t|^2 of their candidate row and the queries are stored
             // doubled, so the contraction itself yields 2 q.t - |t|^2
@@ -208,12 +232,12 @@ void topk_scan_kernel(const TopkArgs a) {
         for (int ks = 0; ks < KS; ++ks) {
             if constexpr (AH == 0) {
 #pragma unroll
-                for (int ob = 0; ob < OB; ++ob) acc[ob] = kge_mma16<BF16>(acc[ob], av[ks], own[ob][ks]);
+                for (int ob = 0; ob < OB; ++ob) acc[ob] = kge_mma16<BF16>(acc[ob], __builtin_bit_cast(uint4, av[ks]), own[ob][ks]);
             } else {
-                if (ks + AH < KS) av[(ks + AH) % (AH + 1)] = *(const uint4 *)(base + frag_off[(ks + AH) & 7] + 256 * ((ks + AH) >> 3));
+                if (ks + AH < KS) av[(ks + AH) % (AH + 1)] = fragment(ks + AH);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int ob = 0; ob < OB; ++ob) acc[ob] = kge_mma16<BF16>(acc[ob], av[ks % (AH + 1)], own[ob][ks]);
+                for (int ob = 0; ob < OB; ++ob) acc[ob] = kge_mma16<BF16>(acc[ob], __builtin_bit_cast(uint4, av[ks % (AH + 1)]), own[ob][ks]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -224,8 +248,9 @@ void topk_scan_kernel(const TopkArgs a) {
     float *nrm = (float *)side_base;                    // [2][32] minus the squared norms (even and odd slots)
     float nmax = 0.f;
     auto norm_tile = [&](int slot) {
-        const int row = wave * 8 + (lane >> 3);
-        const char *base = lds + (slot % NSTAGE) * TILE_BYTES + row * RB + (lane & 7) * 16;
+        const int ln = KIND == KGE_KIND_MULT ? here() : lane;    // (bilinear: one tile in own_tiles)
+        const int row = wave * 8 + (ln >> 3);
+        const char *base = lds + (slot % NSTAGE) * TILE_BYTES + row * RB + (ln & 7) * 16;
         constexpr int NP = RB / 128;
         float sq = 0.f;
 #pragma unroll
@@ -242,7 +267,7 @@ void topk_scan_kernel(const TopkArgs a) {
         sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0xB1, 0xf, 0xf, true));    // lane ^ 1
         sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0x4E, 0xf, 0xf, true));    // lane ^ 2
         sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0x141, 0xf, 0xf, true));   // 7 - lane: the other four
-        if constexpr (KIND == KGE_KIND_DIST) if ((lane & 7) == 0) nrm[(slot & 1) * 32 + row] = -sq;
+        if constexpr (KIND == KGE_KIND_DIST) if ((ln & 7) == 0) nrm[(slot & 1) * 32 + row] = -sq;
         nmax = fmaxf(nmax, sq);
     };
     int turn = FN && KIND == KGE_KIND_MULT ? (int)(t0 % a.own_tiles) : 0;    // bilinear: the query tile whose turn a candidate tile is
@@ -261,22 +286,18 @@ void topk_scan_kernel(const TopkArgs a) {
     wait_vmcnt<(NSTAGE - 2) * LPW>();
     __syncthreads();
     issue(t0 + NSTAGE - 1, NSTAGE - 1);
-    kge_f32x16 acc[OB];
-    norms_of(0);
-    mma_tile(0, acc);
-
-    for (int64_t tile = t0; tile < t1; ++tile) {
+    // One round: start the MFMAs of the next tile, then the epilogue of this one, whose accumulators the other name holds (two
+    // rounds per turn of the loop, so that no accumulator is copied).
+    auto round = [&](int64_t tile, kge_f32x16 (&acc)[OB], kge_f32x16 (&accn)[OB]) {
         const int slot = (int)(tile - t0);
         // ---- tile + 1: wait for its data, refill the stage that tile `tile` just vacated, start its MFMAs
-        kge_f32x16 accn[OB];
         wait_vmcnt<(NSTAGE - 2) * LPW>();
         __syncthreads();
         issue(tile + NSTAGE, slot + NSTAGE);
         if constexpr (FN) { if (tile + 1 < t1) norms_of(slot + 1); }
         mma_tile(slot + 1, accn);                       // (the last iteration recomputes a stale stage: unused)
-        // ---- epilogue of tile `tile`: cheap wave-level test first, the append path only on a hit ----
+        // ---- epilogue of tile `tile`: cheap wave-level test first, counting and appending only on a hit ----
         const bool tile_full = tile * TK_ST + TK_ST <= a.ncand;
-        float vv[NQ][16];                               // the values are the accumulators themselves
         if constexpr (FN && KIND == KGE_KIND_DIST) {    // (this tile's norms were written before the barrier above)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -286,50 +307,62 @@ void topk_scan_kernel(const TopkArgs a) {
                     for (int u = 0; u < 4; ++u) acc[ob][4 * j + u] += tn4[u];
             }
         }
+        if constexpr (TH) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if constexpr (TH) { const float x = acc[1][i] - cq; vv[0][i] = fmaf(x, x, acc[0][i]); }
-            else {
-#pragma unroll
-                for (int ob = 0; ob < OB; ++ob) vv[ob][i] = acc[ob][i];
-            }
+            for (int i = 0; i < 16; ++i) { const float x = acc[1][i] - cq; acc[0][i] = fmaf(x, x, acc[0][i]); }
         }
         if (!tile_full) {
+            const int gg = here() >> 5;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const bool out = tile * TK_ST + 8 * (i >> 2) + 4 * g + (i & 3) >= a.ncand;
+                const bool out = tile * TK_ST + 8 * (i >> 2) + 4 * gg + (i & 3) >= a.ncand;
 #pragma unroll
-                for (int ob = 0; ob < NQ; ++ob) vv[ob][i] = out ? -INFINITY : vv[ob][i];
+                for (int ob = 0; ob < NQ; ++ob) acc[ob][i] = out ? -INFINITY : acc[ob][i];
             }
         }
 #pragma unroll
         for (int ob = 0; ob < NQ; ++ob) {
-            if (a.true_t) {
-                // v > vt exactly when vt - v is negative: the sign bits are shifted into one word (one subtraction and
-                // one funnel shift per entry, no compare results through scalar registers) and counted at the end
-                uint32_t signs = 0;
+            const kge_f32x16 &v = acc[ob];              // the values are the accumulators themselves
+            float mx = v[0];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) signs = __builtin_amdgcn_alignbit(signs, __float_as_uint(vt[ob] - vv[ob][i]), 31);
-                above[ob] += (uint32_t)__builtin_popcount(signs);
-            }
-            float mx = vv[ob][0];
+            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, v[i]);
+            if (__any(mx > low[ob])) {
+                if (a.true_t && __any(mx > vt[ob])) {
+                    // v > vt exactly when vt - v is negative: the sign bits are shifted into one word (one subtraction and
+                    // one funnel shift per entry, no compare results through scalar registers) and counted at the end
+                    uint32_t signs = 0;
 #pragma unroll
-            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, vv[ob][i]);
-            if (__any(mx > thr[ob])) {
+                    for (int i = 0; i < 16; ++i) signs = __builtin_amdgcn_alignbit(signs, __float_as_uint(vt[ob] - v[i]), 31);
+                    above[ob] += (uint32_t)__builtin_popcount(signs);
+                }
+                // A hit is nearly always the only one of its lane, and then it is the maximum: its place comes from a mask of the
+                // comparisons, without sixteen branches that each wait for a compare result.
+                uint32_t hits = 0;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    if (vv[ob][i] > thr[ob]) {
-                        const int64_t cand = tile * TK_ST + 8 * (i >> 2) + 4 * g + (i & 3);
-                        // (the area's address is formed here, on the rarely taken path, instead of living in registers)
-                        if (myc[ob] < TK_HALF)
-                            a.seg[(((size_t)qid[ob] * a.nseg + split) * 2 + g) * TK_HALF + myc[ob]] = make_uint2(__float_as_uint(vv[ob][i]), (uint32_t)cand);
-                        ++myc[ob];                      // counts past the area mark the overflow for the compaction
-                    }
+                for (int i = 0; i < 16; ++i) hits |= v[i] > thr[ob] ? 1u << i : 0u;
+                // (an entry's area is addressed here, on the rarely taken path, instead of living in registers)
+                const int ln = here(), gg = ln >> 5, qq = own_base + (wave_u * NQ + ob) * 32 + (ln & 31);
+                auto append = [&](int i, float x) {
+                    const int64_t cand = tile * TK_ST + 8 * (i >> 2) + 4 * gg + (i & 3);
+                    if (myc[ob] < TK_HALF)
+                        a.seg[(((size_t)qq * a.nseg + split) * 2 + gg) * TK_HALF + myc[ob]] = make_uint2(__float_as_uint(x), (uint32_t)cand);
+                    ++myc[ob];                          // counts past the area mark the overflow for the compaction
+                };
+                if (!__any((hits & (hits - 1)) != 0)) {
+                    if (hits) append(__builtin_ctz(hits), mx);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) if (hits >> i & 1) append(i, v[i]);
                 }
             }
         }
-#pragma unroll
-        for (int ob = 0; ob < OB; ++ob) acc[ob] = accn[ob];
+    };
+    kge_f32x16 acc_a[OB], acc_b[OB];
+    norms_of(0);
+    mma_tile(0, acc_a);
+    for (int64_t tile = t0; tile < t1; tile += 2) {
+        round(tile, acc_a, acc_b);
+        if (tile + 1 < t1) round(tile + 1, acc_b, acc_a);
     }
     wait_vmcnt<0>();                                    // no copy may still be in flight when the LDS is released
 #pragma unroll
