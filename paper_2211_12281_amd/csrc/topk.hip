@@ -7,11 +7,10 @@
 //                query's current threshold is appended to the query's candidate buffer (rare after warm-up);
 //                the table is walked in growing chunks, thresholds are refreshed between chunks
 //   3. compact   per query: keep the KP best buffered entries (KP > K), new threshold = the KP-th value
-//   4. rescore   survivors get the ranking key in fp64 with a sequential fused-multiply-add loop
-//   5. final     sort by (key, index), check with a rigorous rounding bound that no discarded candidate
-//                could belong to the top-K, write the list and the rank of the held-out tail
-//   6. fallback  queries that fail the check (or overflowed their buffer) are re-ranked by an exhaustive
-//                fp64 scan
+//   4. finish    survivors get the ranking key in fp64 with a sequential fused-multiply-add loop; sort by (key, index),
+//                check with a rigorous rounding bound that no discarded candidate could belong to the top-K, write
+//                the list and the rank of the held-out tail; queries that fail the check (or overflowed their
+//                buffer) are re-ranked by an exhaustive fp64 scan
 #include "row_ops.hpp"
 #include "block_kernel.hpp"
 #include <math.h>
@@ -42,8 +41,11 @@ struct TopkArgs {
     uint32_t *rankcnt;                  // [Qp] candidates whose value beats the held-out tail's
     int32_t nq;                         // number of real queries (rows past it are padding)
     int64_t tile_lo, tile_hi;
-    int32_t tiles_per_wg;
+    int32_t nsplit;                     // tile tile_lo + i belongs to split i mod nsplit
     int32_t own_tiles;
+    int64_t samp_row, samp_step;        // kernels with SAMPLE: row r of tile i is candidate r samp_row + i samp_step
+    int32_t flush;                      // ... tiles behind one group of maxima
+    int32_t fold;                       // ... one maximum per lane and group instead of four
     const void *zeros;                  // 16 zero bytes (source of the padding columns)
 };
 
@@ -56,6 +58,10 @@ __device__ __forceinline__ void async_copy16(const void *g, uint32_t lds_addr) {
 }
 __device__ __forceinline__ void async_copy4(const void *g, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(g) : "memory");
+}
+// (v > 0: bit order = value order; an old value that is read only costs an update more)
+__device__ __forceinline__ void topk_raise(uint32_t *tmax, float v) {
+    if (v > 0.f && __float_as_uint(v) > __hip_atomic_load(tmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(tmax, __float_as_uint(v));
 }
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
@@ -83,7 +89,14 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // needs) come from the tiles in the LDS instead of a pass of their own over the table.  Every workgroup of a distance scan
 // makes the norms of every tile (a wave those of eight rows), which pays while few query tiles share a candidate tile;
 // the bilinear scan needs only the maximum and gives each candidate tile to one of the query tiles.
-template <bool BF16, int RB, int KIND, int OB, bool TH = false, bool FN = false>
+//
+// A split's tiles are dealt round-robin, so that neighbouring rows that all beat the threshold - a table sorted by type or
+// community - are spread over the append areas of many splits.
+//
+// SAMPLE: no appends; the tiles' rows are drawn from the whole table at even distances (row r of tile i is candidate
+// r samp_row + i samp_step) and every lane leaves the maxima of its rows by groups.  The KP-th largest group maximum is a value
+// that at least KP candidates reach: the threshold that the scan proper starts with, whatever the order of the rows.
+template <bool BF16, int RB, int KIND, int OB, bool TH = false, bool FN = false, bool SAMPLE = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void topk_scan_kernel(const TopkArgs a) {
     static_assert(!TH || (OB == 2 && KIND == KGE_KIND_DIST), "TransH: one block of queries, one of normals");
@@ -107,11 +120,12 @@ void topk_scan_kernel(const TopkArgs a) {
     const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
     const int own_tile = kk % a.own_tiles, split = xcd + 8 * (kk / a.own_tiles);
     const int own_base = own_tile * (128 * NQ);
-    const int64_t t0 = a.tile_lo + (int64_t)split * a.tiles_per_wg;
-    const int64_t t1 = t0 + a.tiles_per_wg < a.tile_hi ? t0 + a.tiles_per_wg : a.tile_hi;
+    const int64_t ntiles = a.tile_hi - a.tile_lo;
+    const int nt = split < a.nsplit ? (int)((ntiles - split + a.nsplit - 1) / a.nsplit) : 0;     // tiles of this split
+    auto tile_of = [&](int k) { return a.tile_lo + split + (int64_t)k * a.nsplit; };
     // Every (query, split, lane half) owns a private append area, so appending needs no atomics: the
     // count lives in a register and is stored once at the end.  Two lanes (g = 0, 1) serve one query.
-    if (t0 >= t1) {
+    if (nt <= 0) {
         if (split < a.nseg)
             for (int ob = 0; ob < NQ; ++ob)
                 a.segcnt[((size_t)(own_base + (wave * NQ + ob) * 32 + lr) * a.nseg + split) * 2 + g] = 0;
@@ -129,8 +143,8 @@ void topk_scan_kernel(const TopkArgs a) {
         const char *p = (const char *)a.Qmat + (size_t)qid[ob] * RB + g * 16;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) own[ob][ks] = *(const uint4 *)(p + ks * 32);
-        thr[ob] = a.thr[qid[ob]];
-        vt[ob] = a.vt[qid[ob]];
+        thr[ob] = SAMPLE ? 0.f : a.thr[qid[ob]];
+        vt[ob] = SAMPLE ? 0.f : a.vt[qid[ob]];
         low[ob] = fminf(thr[ob], vt[ob]);               // (vt is +inf where there is no held-out tail)
         above[ob] = 0;
     }
@@ -169,11 +183,24 @@ void topk_scan_kernel(const TopkArgs a) {
         __syncthreads();
     }
     const bool offsets32 = a.ent_stride < (1ll << 26);  // (uniform; 32 rows x stride fits the offset)
-    auto issue = [&](int64_t tile, int slot) {
-        tile = tile < t1 ? tile : t1 - 1;               // past the end: a harmless repeat keeps vmcnt uniform
+    const char *ld_ptr[SAMPLE ? IPW : 1];               // rows from all over the table: a pointer per copy
+    if constexpr (SAMPLE) {
+#pragma unroll
+        for (int jj = 0; jj < IPW; ++jj) ld_ptr[jj] = a.ent + (int64_t)ld_row_of(jj, lane) * a.samp_row * a.ent_stride + ld_col_of(jj, lane);
+    }
+    auto issue = [&](int k, int slot) {
+        k = k < nt ? k : nt - 1;                        // past the end: a harmless repeat keeps vmcnt uniform
+        const int64_t tile = tile_of(k);
         const int stage = slot % NSTAGE;
         const uint32_t lbase = lds0 + stage * TILE_BYTES + wave_u * (IPW * 1024);
-        if (offsets32 && tile * TK_ST + TK_ST <= a.ncand) {
+        const float *side = a.tn + (SAMPLE ? lr * a.samp_row + tile * a.samp_step : tile * TK_ST + lr);
+        if constexpr (SAMPLE) {
+            const int64_t at = tile * a.samp_step * a.ent_stride;
+#pragma unroll
+            for (int jj = 0; jj < IPW; ++jj)
+                asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b64 exec, -1"
+                             ::"s"(lbase + jj * 1024), "v"(ld_ptr[jj] + at), "s"(ld_live[jj]) : "memory");
+        } else if (offsets32 && tile * TK_ST + TK_ST <= a.ncand) {
             const char *tb = a.ent + tile * TK_ST * a.ent_stride;
 #pragma unroll
             for (int jj = 0; jj < IPW; ++jj)
@@ -191,7 +218,7 @@ void topk_scan_kernel(const TopkArgs a) {
                 async_copy16(gp, lbase + jj * 1024);
             }
         }
-        if constexpr (SIDE) async_copy4(a.tn + tile * TK_ST + lr, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
+        if constexpr (SIDE) async_copy4(side, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
     };
     // ---- A-fragment addresses: chunk (2 ks + g) of row lr sits at position chunk ^ tk_swz(lr) ----------
     // (stages and rows are whole multiples of 256 bytes, so chunk 2 b + g of a row is chunk g's address with b's bits flipped: one
@@ -270,11 +297,11 @@ void topk_scan_kernel(const TopkArgs a) {
         if constexpr (KIND == KGE_KIND_DIST) if ((ln & 7) == 0) nrm[(slot & 1) * 32 + row] = -sq;
         nmax = fmaxf(nmax, sq);
     };
-    int turn = FN && KIND == KGE_KIND_MULT ? (int)(t0 % a.own_tiles) : 0;    // bilinear: the query tile whose turn a candidate tile is
+    int turn = 0;                                       // bilinear: the query tile whose turn a candidate tile is
     auto norms_of = [&](int slot) {
         if constexpr (FN) {
             if constexpr (KIND == KGE_KIND_DIST) norm_tile(slot);
-            else {
+            else if constexpr (!SAMPLE) {
                 if (turn == own_tile) norm_tile(slot);
                 turn = turn + 1 == a.own_tiles ? 0 : turn + 1;
             }
@@ -282,19 +309,22 @@ void topk_scan_kernel(const TopkArgs a) {
     };
 
 #pragma unroll
-    for (int s2 = 0; s2 < NSTAGE - 1; ++s2) issue(t0 + s2, s2);
+    for (int s2 = 0; s2 < NSTAGE - 1; ++s2) issue(s2, s2);
     wait_vmcnt<(NSTAGE - 2) * LPW>();
     __syncthreads();
-    issue(t0 + NSTAGE - 1, NSTAGE - 1);
+    issue(NSTAGE - 1, NSTAGE - 1);
+    float best[SAMPLE ? NQ : 1][4];                     // running maxima of the rows 8 j + 4 g .. + 3 of the tiles of a group
+    int until = a.flush;
+    if constexpr (SAMPLE) for (int ob = 0; ob < NQ; ++ob) for (int j = 0; j < 4; ++j) best[ob][j] = -INFINITY;
     // One round: start the MFMAs of the next tile, then the epilogue of this one, whose accumulators the other name holds (two
     // rounds per turn of the loop, so that no accumulator is copied).
-    auto round = [&](int64_t tile, kge_f32x16 (&acc)[OB], kge_f32x16 (&accn)[OB]) {
-        const int slot = (int)(tile - t0);
+    auto round = [&](int slot, kge_f32x16 (&acc)[OB], kge_f32x16 (&accn)[OB]) {
+        const int64_t tile = tile_of(slot);
         // ---- tile + 1: wait for its data, refill the stage that tile `tile` just vacated, start its MFMAs
         wait_vmcnt<(NSTAGE - 2) * LPW>();
         __syncthreads();
-        issue(tile + NSTAGE, slot + NSTAGE);
-        if constexpr (FN) { if (tile + 1 < t1) norms_of(slot + 1); }
+        issue(slot + NSTAGE, slot + NSTAGE);
+        if constexpr (FN) { if (slot + 1 < nt) norms_of(slot + 1); }
         mma_tile(slot + 1, accn);                       // (the last iteration recomputes a stale stage: unused)
         // ---- epilogue of tile `tile`: cheap wave-level test first, counting and appending only on a hit ----
         const bool tile_full = tile * TK_ST + TK_ST <= a.ncand;
@@ -310,6 +340,29 @@ void topk_scan_kernel(const TopkArgs a) {
         if constexpr (TH) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) { const float x = acc[1][i] - cq; acc[0][i] = fmaf(x, x, acc[0][i]); }
+        }
+        if constexpr (SAMPLE) {
+#pragma unroll
+            for (int ob = 0; ob < NQ; ++ob)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    best[ob][j] = fmaxf(fmaxf(fmaxf(best[ob][j], acc[ob][4 * j]), fmaxf(acc[ob][4 * j + 1], acc[ob][4 * j + 2])), acc[ob][4 * j + 3]);
+            if (--until == 0 || slot + 1 == nt) {
+                until = a.flush;
+#pragma unroll
+                for (int ob = 0; ob < NQ; ++ob) {
+                    const size_t area = ((size_t)qid[ob] * a.nseg + split) * 2 + g;
+                    auto put = [&](float x) {           // (the plan keeps a split's groups within an area)
+                        if (myc[ob] >= TK_HALF) return;
+                        a.seg[area * TK_HALF + myc[ob]] = make_uint2(__float_as_uint(x), (uint32_t)((split * 2 + g) * TK_HALF + myc[ob]));
+                        ++myc[ob];
+                    };
+                    if (a.fold) put(fmaxf(fmaxf(best[ob][0], best[ob][1]), fmaxf(best[ob][2], best[ob][3])));
+                    else for (int j = 0; j < 4; ++j) put(best[ob][j]);
+                    for (int j = 0; j < 4; ++j) best[ob][j] = -INFINITY;
+                }
+            }
+            return;
         }
         if (!tile_full) {
             const int gg = here() >> 5;
@@ -360,20 +413,26 @@ void topk_scan_kernel(const TopkArgs a) {
     kge_f32x16 acc_a[OB], acc_b[OB];
     norms_of(0);
     mma_tile(0, acc_a);
-    for (int64_t tile = t0; tile < t1; tile += 2) {
-        round(tile, acc_a, acc_b);
-        if (tile + 1 < t1) round(tile + 1, acc_b, acc_a);
+    for (int k = 0; k < nt; k += 2) {
+        round(k, acc_a, acc_b);
+        if (k + 1 < nt) round(k + 1, acc_b, acc_a);
     }
     wait_vmcnt<0>();                                    // no copy may still be in flight when the LDS is released
 #pragma unroll
     for (int ob = 0; ob < NQ; ++ob) a.segcnt[((size_t)qid[ob] * a.nseg + split) * 2 + g] = myc[ob];
+    if constexpr (SAMPLE) return;
     if (a.true_t) {
 #pragma unroll
         for (int ob = 0; ob < NQ; ++ob) if (above[ob] && qid[ob] < a.nq) atomicAdd(a.rankcnt + qid[ob], above[ob]);
     }
     if constexpr (FN) {
+        // One update per workgroup, and only where the maximum grows: updates of one address follow each other at 11 ns.
         nmax = kge_wave_max(nmax);
-        if (lane == 0 && nmax > 0.f) atomicMax(a.tmax, __float_as_uint(nmax));   // (positive: bit order = value order)
+        __syncthreads();                                // (the ring is no longer read)
+        float *wmax = (float *)lds;
+        if (lane == 0) wmax[wave] = nmax;
+        __syncthreads();
+        if (tid == 0) topk_raise(a.tmax, fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3])));
     }
 }
 
@@ -408,36 +467,39 @@ __device__ void bitonic_asc_pair(double *key, int *idx, int P) {
         }
 }
 
-// Per query: merge the kept list with the fresh append areas, keep the KP best (in no particular order), refresh the threshold.
-// The KP-th key is found by refining a range: a histogram of the keys in it over at most 1,024 bins, the bin that holds the
-// KP-th, again with that bin - two or three rounds as a rule, seven at most, since the keys (value, index) differ - where a
-// sort of the list takes 55 to 91 steps with a barrier each.  All of it is latency, so a compute unit wants many workgroups:
-// the list lives in the LDS up to TK_LISTCAP entries (32 KB; what the first chunk can append to a query, and more than a later
-// one appends as a rule); the appends of a longer one are read again from the areas in every round.
-constexpr int TK_LISTCAP = 4096;
+// Per query: merge the kept list with the fresh append areas, keep the KP best (in no particular order), refresh the threshold;
+// without a list to keep (the maxima of a sample), the threshold alone.
+// All of it is latency: a thread holds up to TK_MINE entries in registers (4,096 per query; the rest of a longer list is read again
+// in every round), all loads of a list are in flight together, and the KP-th key is found by refining a range - a histogram of the
+// keys in it over 1,024 bins, the bin that holds the KP-th, again with that bin - until the bin holds no more than a wave, which
+// ranks it.  One round as a rule, six at most, since the keys (value, index) differ.
+constexpr int TK_MINE = 16;
 constexpr int TK_MAXAREAS = 1024;       // 2 nseg at most
 constexpr int TK_BINS = 1024;
 __global__ __launch_bounds__(256) void topk_compact_kernel(uint2 *keep, int32_t *keepcnt, const uint2 *seg, const int32_t *segcnt,
                                                            int nseg, int nsplit, int KP, float *thr, int32_t *flag, int Q) {
-    __shared__ uint64_t s[TK_LISTCAP];
+    __shared__ uint16_t place[TK_MINE * 256];               // the area (place in abase) of entry i
     __shared__ int hist[TK_BINS];
-    __shared__ int abase[TK_MAXAREAS + 1];                  // start of every area's entries behind the kept list
-    __shared__ int wsum[4], total_s, over, found, out_n;
-    __shared__ uint64_t wlo[4], whi[4], next_lo, next_hi;
+    __shared__ int abase[TK_MAXAREAS + 1];                  // start of every area's entries behind the kept list; area t + 256 j at 4 t + j
+    __shared__ uint64_t few[64];
+    __shared__ uint64_t found_lo, found_hi, cut_s;
+    __shared__ uint32_t wlo[4], whi[4];
+    __shared__ int wsum[4], total_s, over, few_n, found_need, found_count, out_n;
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (q >= Q) return;
-    const int kept = keepcnt[q];
+    const int kept = keep ? keepcnt[q] : 0;
     const int nareas = nsplit * 2;                          // <= 2 * nseg <= TK_MAXAREAS
-    if (tid == 0) { over = 0; out_n = 0; }
+    auto area_of = [](int p) { return (p >> 2) + 256 * (p & 3); };
+    if (tid == 0) { over = 0; out_n = 0; few_n = 0; }
     __syncthreads();
-    // counts (clamped to the area size), then their exclusive prefix sums behind the kept list: thread t takes four areas
-    // in a row, a shuffle scan inside every wave, the waves' sums through the LDS
+    // counts (clamped to the area size) and their exclusive prefix sums behind the kept list: thread t takes the areas t + 256 j, a
+    // shuffle scan inside every wave, the waves' sums through the LDS
     {
-        const int a0 = 4 * tid;
         int c[4], incl = 0;
 #pragma unroll
+        for (int j = 0; j < 4; ++j) c[j] = tid + 256 * j < nareas ? segcnt[(size_t)q * nseg * 2 + tid + 256 * j] : 0;
+#pragma unroll
         for (int j = 0; j < 4; ++j) {
-            c[j] = a0 + j < nareas ? segcnt[(size_t)q * nseg * 2 + a0 + j] : 0;
             if (c[j] > TK_HALF) { over = 1; c[j] = TK_HALF; }
             incl += c[j];
         }
@@ -450,82 +512,68 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(uint2 *keep, int32_t 
         for (int w = 0; w < wave; ++w) start += wsum[w];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if (a0 + j <= nareas) abase[a0 + j] = start;
+            abase[4 * tid + j] = start;
+            for (int e = 0; e < c[j]; ++e) if (start + e < TK_MINE * 256) place[start + e] = (uint16_t)(4 * tid + j);
             start += c[j];
         }
-        if (tid == 255) { if (nareas == TK_MAXAREAS) abase[nareas] = start; total_s = start; }
+        if (tid == 255) { abase[TK_MAXAREAS] = start; total_s = start; }
     }
     __syncthreads();
     if (over && tid == 0) flag[q] = 1;                      // entries were dropped: exhaustive re-rank later
     const int total = total_s;
-    const bool in_lds = total <= TK_LISTCAP;                // (the same for every thread)
-    // entry i >= kept: its area by bisection (four searches, then four loads in flight per thread)
-    auto load4 = [&](int i0, uint64_t (&k)[4]) {
-        int lo[4];
+    const uint2 *areas = seg + (size_t)q * nseg * 2 * TK_HALF;
+    uint64_t mine[TK_MINE];                                 // entries tid + 256 j
+    {
+        uint2 e[TK_MINE];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) lo[u] = 0;
-        for (int step = 512; step > 0; step >>= 1) {
-            if (step >= nareas) continue;
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (lo[u] + step < nareas && abase[lo[u] + step] <= i0 + u * 256) lo[u] += step;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = i0 + u * 256;
-            uint2 e = make_uint2(0u, 0u);
-            if (i < total) e = seg[((size_t)q * nseg * 2 + lo[u]) * TK_HALF + (i - abase[lo[u]])];
-            k[u] = pack_value(e.x, e.y);
-        }
-    };
-    for (int i = tid; i < kept; i += 256) { const uint2 e = keep[(size_t)q * KP + i]; s[i] = pack_value(e.x, e.y); }
-    if (in_lds)
-        for (int i0 = kept + tid; i0 < total; i0 += 1024) {
-            uint64_t k[4];
-            load4(i0, k);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) if (i0 + u * 256 < total) s[i0 + u * 256] = k[u];
-        }
-    __syncthreads();
-    auto walk = [&](auto &&f) {                             // f(key) for every entry of the list
-        const int n = in_lds ? total : kept;
-        for (int i = tid; i < n; i += 256) f(s[i]);
-        if (!in_lds)
-            for (int i0 = kept + tid; i0 < total; i0 += 1024) {
-                uint64_t k[4];
-                load4(i0, k);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) if (i0 + u * 256 < total) f(k[u]);
+        for (int j = 0; j < TK_MINE; ++j) {
+            e[j] = make_uint2(0u, 0u);
+            if (j * 256 < total) {                          // (uniform)
+                const int i = tid + j * 256;
+                if (i < kept) e[j] = keep[(size_t)q * KP + i];
+                else if (i < total) { const int p = place[i]; e[j] = areas[area_of(p) * TK_HALF + (i - abase[p])]; }
             }
+        }
+#pragma unroll
+        for (int j = 0; j < TK_MINE; ++j) mine[j] = pack_value(e[j].x, e[j].y);
+    }
+    auto walk = [&](auto &&f) {                             // f(key) for every entry of the list
+#pragma unroll
+        for (int j = 0; j < TK_MINE; ++j) if (j * 256 < total && tid + j * 256 < total) f(mine[j]);
+        for (int i = TK_MINE * 256 + tid; i < total; i += 256) {
+            int p = 0;
+            for (int step = TK_MAXAREAS / 2; step > 0; step >>= 1) if (abase[p + step] <= i) p += step;
+            const uint2 e = areas[area_of(p) * TK_HALF + (i - abase[p])];
+            f(pack_value(e.x, e.y));
+        }
     };
     uint64_t cut = 0;                                       // keys >= cut stay
-    if (total > KP) {
-        uint64_t mn = ~0ull, mx = 0ull;
-        walk([&](uint64_t k) { mn = k < mn ? k : mn; mx = k > mx ? k : mx; });
+    if (total >= KP) {
+        uint32_t mn = ~0u, mx = 0u;
+        walk([&](uint64_t k) { const uint32_t v = (uint32_t)(k >> 32); mn = v < mn ? v : mn; mx = v > mx ? v : mx; });
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
-            const uint64_t x = __shfl_xor((unsigned long long)mn, o), y = __shfl_xor((unsigned long long)mx, o);
+            const uint32_t x = __shfl_xor(mn, o), y = __shfl_xor(mx, o);
             mn = x < mn ? x : mn; mx = y > mx ? y : mx;
         }
         if (lane == 0) { wlo[wave] = mn; whi[wave] = mx; }
-        __syncthreads();
-        uint64_t lo = wlo[0], hi = whi[0];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) { lo = wlo[w] < lo ? wlo[w] : lo; hi = whi[w] > hi ? whi[w] : hi; }
-        int need = KP;                                      // taken from the top of [lo, hi]
-        for (;;) {
+        for (int j = 0; j < TK_BINS / 256; ++j) hist[j * 256 + tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < 4; ++w) { mn = wlo[w] < mn ? wlo[w] : mn; mx = whi[w] > mx ? whi[w] : mx; }
+        uint64_t lo = (uint64_t)mn << 32, hi = (uint64_t)mx << 32 | 0xFFFFFFFFu;
+        int need = KP, count = total;                       // taken from the top of [lo, hi]; entries in it
+        while (count > 64 && hi > lo) {
             const uint64_t width = hi - lo;
             const int bits = width ? 64 - __clzll((long long)width) : 0, shift = bits > 10 ? bits - 10 : 0;
-#pragma unroll
-            for (int j = 0; j < TK_BINS / 256; ++j) hist[j * 256 + tid] = 0;
-            __syncthreads();
             walk([&](uint64_t k) { if (k >= lo && k <= hi) atomicAdd(&hist[(int)((k - lo) >> shift)], 1); });
             __syncthreads();
             // thread t holds four bins from the top; its first bin counts behind those of the threads before it
             const int b0 = TK_BINS - 1 - 4 * tid;
             int c[4], incl = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { c[j] = hist[b0 - j]; incl += c[j]; }
+            for (int j = 0; j < 4; ++j) { c[j] = hist[b0 - j]; incl += c[j]; hist[b0 - j] = 0; }
             const int own = incl;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o); if (lane >= o) incl += v; }
@@ -536,40 +584,33 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(uint2 *keep, int32_t 
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (before < need && before + c[j] >= need) {      // (exactly one bin of all)
-                    next_lo = lo + ((uint64_t)(b0 - j) << shift);
-                    next_hi = next_lo + ((1ull << shift) - 1);
-                    found = need - before;                         // taken from this bin
-                    if (c[j] == need - before || shift == 0) found = 0;    // all of it
+                    found_lo = lo + ((uint64_t)(b0 - j) << shift);
+                    found_hi = found_lo + ((1ull << shift) - 1);
+                    found_need = need - before;                    // taken from this bin
+                    found_count = c[j];
                 }
                 before += c[j];
             }
             __syncthreads();
-            lo = next_lo; hi = next_hi < hi ? next_hi : hi;
-            need = found;
-            if (need == 0) break;
+            lo = found_lo; hi = found_hi < hi ? found_hi : hi;
+            need = found_need; count = found_count;
         }
-        cut = lo;
-    }
-    // (the walk reads the kept list from the LDS, so its global copy may be rewritten)
-    uint64_t mn = ~0ull;
-    walk([&](uint64_t k) {
-        if (k >= cut) {
-            keep[(size_t)q * KP + atomicAdd(&out_n, 1)] = unpack_value(k);
-            mn = k < mn ? k : mn;
-        }
-    });
-    if (total >= KP) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) { const uint64_t x = __shfl_xor((unsigned long long)mn, o); mn = x < mn ? x : mn; }
+        // (at most 64 entries left in [lo, hi]: a wave ranks them)
+        walk([&](uint64_t k) { if (k >= lo && k <= hi) { const int i = atomicAdd(&few_n, 1); if (i < 64) few[i] = k; } });
         __syncthreads();
-        if (lane == 0) wlo[wave] = mn;
-        __syncthreads();
-        if (tid == 0) {
-#pragma unroll
-            for (int w = 1; w < 4; ++w) mn = wlo[w] < mn ? wlo[w] : mn;
-            thr[q] = __uint_as_float(unpack_value(mn).x);
+        if (wave == 0) {
+            const uint64_t k = lane < count ? few[lane] : 0ull;
+            int larger = 0;
+            for (int i = 0; i < count; ++i) larger += few[i] > k;
+            if (lane < count && larger == need - 1) cut_s = k;
         }
+        __syncthreads();
+        cut = cut_s;
+        if (tid == 0) thr[q] = __uint_as_float(unpack_value(cut).x);
     }
+    if (!keep) return;
+    __syncthreads();                                        // (every entry of the kept list is in a register: its copy may be rewritten)
+    walk([&](uint64_t k) { if (k >= cut) keep[(size_t)q * KP + atomicAdd(&out_n, 1)] = unpack_value(k); });
     if (tid == 0) keepcnt[q] = total < KP ? total : KP;
 }
 
@@ -614,149 +655,218 @@ __device__ __forceinline__ double key_step(int scorer, double acc, double q0, do
     }
 }
 
-// key of one tail row against the exact query qv[0 .. d)
-template <bool BF16>
-__device__ double canonical_key(int scorer, int d, const double *qv, const void *ent, int64_t toff) {
-    double acc = 0.0;
-    if (topk_cplx(scorer)) {
-        const int c = d >> 1;
-        for (int j = 0; j < c; ++j)
-            acc = key_step(scorer, acc, qv[j], (double)El<BF16>::ld(ent, toff + j), qv[j + c], (double)El<BF16>::ld(ent, toff + j + c));
-    } else {
-        for (int j = 0; j < d; ++j) acc = key_step(scorer, acc, qv[j], (double)El<BF16>::ld(ent, toff + j), 0.0, 0.0);
+// One walk over `steps` key steps of a row (whole 16-byte pieces: rows are, and so are their halves): the scorer is decided once
+// per walk, since a branch per step costs as much as the step.  re(p) and im(p) are the pieces of the row behind step p 16 / ES
+// (complex scorers: its real and imaginary parts), qv, qi and wv the query's components of these steps.  TransH walks twice: A = u . t,
+// then the squared distance.
+template <bool BF16, class Re, class Im>
+__device__ __forceinline__ void key_walk(int scorer, bool second, int steps, const double *qv, const double *qi, const double *wv, Re &&re, Im &&im,
+                                         double &A, double &acc) {
+    constexpr int PER = BF16 ? 8 : 4;                   // columns of a piece
+    auto elem = [](const kge_u32x4 &x, int e) -> double {
+        if constexpr (BF16) return (double)__uint_as_float((e & 1) ? (x[e >> 1] & 0xffff0000u) : (x[e >> 1] << 16));
+        else return (double)__uint_as_float(x[e]);
+    };
+    auto real = [&](auto &&step) {
+        for (int p = 0; p * PER < steps; ++p) {
+            const kge_u32x4 x = re(p);
+#pragma unroll
+            for (int e = 0; e < PER; ++e) step(qv[p * PER + e], elem(x, e), p * PER + e);
+        }
+    };
+    auto complex_ = [&](auto &&step) {
+        for (int p = 0; p * PER < steps; ++p) {
+            const kge_u32x4 x = re(p), y = im(p);
+#pragma unroll
+            for (int e = 0; e < PER; ++e) step(qv[p * PER + e], elem(x, e), qi[p * PER + e], elem(y, e));
+        }
+    };
+    switch (scorer) {
+    case KGE_DISTMULT: real([&](double a, double t, int) { acc = key_step(KGE_DISTMULT, acc, a, t, 0.0, 0.0); }); break;
+    case KGE_TRANSE: real([&](double a, double t, int) { acc = key_step(KGE_TRANSE, acc, a, t, 0.0, 0.0); }); break;
+    case KGE_COMPLEX: complex_([&](double a, double t, double a2, double t2) { acc = key_step(KGE_COMPLEX, acc, a, t, a2, t2); }); break;
+    case KGE_ROTATE: complex_([&](double a, double t, double a2, double t2) { acc = key_step(KGE_ROTATE, acc, a, t, a2, t2); }); break;
+    default:
+        if (!second) real([&](double, double t, int j) { A = fma(wv[j], t, A); });
+        else real([&](double a, double t, int j) { const double z = fma(A, wv[j], __dsub_rn(a, t)); acc = fma(z, z, acc); });
     }
+}
+
+// key of one tail row against the exact query qv[0 .. d) (TransH: q', and the unit normal wv[0 .. d))
+template <bool BF16>
+__device__ double canonical_key(int scorer, int d, const double *qv, const double *wv, const void *ent, int64_t toff) {
+    constexpr int ES = BF16 ? 2 : 4;
+    const kge_u32x4 *row = (const kge_u32x4 *)((const char *)ent + toff * ES);
+    const int half = d >> 1, imag = half * ES / 16;
+    double A = 0.0, acc = 0.0;
+    auto re = [&](int p) { return row[p]; };
+    auto im = [&](int p) { return row[imag + p]; };
+    key_walk<BF16>(scorer, false, topk_cplx(scorer) ? half : d, qv, qv + half, wv, re, im, A, acc);
+    if (scorer == KGE_TRANSH) key_walk<BF16>(scorer, true, d, qv, qv + half, wv, re, im, A, acc);
     return topk_mult(scorer) ? -acc : acc;
 }
 
-// TransH key of one tail row against q' = qv[0 .. d) and the unit normal wv[0 .. d)
-template <bool BF16>
-__device__ double canonical_key_th(int d, const double *qv, const double *wv, const void *ent, int64_t toff) {
-    double A = 0.0, acc = 0.0;
-    for (int j = 0; j < d; ++j) A = fma(wv[j], (double)El<BF16>::ld(ent, toff + j), A);
-    for (int j = 0; j < d; ++j) {
-        const double x = fma(A, wv[j], __dsub_rn(qv[j], (double)El<BF16>::ld(ent, toff + j)));
-        acc = fma(x, x, acc);
-    }
-    return acc;
-}
-
-// One wave re-scores 64 survivors of one query, lane = survivor, so that the 64 sequential fp64 chains run in
-// lockstep.  The candidate rows arrive through the LDS in chunks of 64 columns (complex scorers: 32 real parts
-// followed by the 32 imaginary parts of the same coordinates): coalesced row reads on the way in, conflict-free
-// column reads (row stride odd in dwords) on the way out; the exact query components of a chunk are computed once
-// per wave.  The key is the one of canonical_key, step by step.
-template <bool BF16>
-__global__ __launch_bounds__(256) void topk_rescore_kernel(KgeModelDev m, const int32_t *h, const int32_t *r, int Q,
-                                                           int64_t cand_lo, const int32_t *cnt, const uint2 *buf, int KP,
-                                                           double *keyd, const double *qx) {
-    constexpr int DW = BF16 ? 32 : 64;                  // dwords per row chunk of 64 columns
-    constexpr int E = BF16 ? 2 : 1;                     // columns per dword
-    __shared__ uint32_t rows[4][64 * (DW + 1)];
-    __shared__ double qd[4][64], wd[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int groups = KP / 64;
-    const int64_t task = (int64_t)blockIdx.x * 4 + wave;
-    const int q = (int)(task / groups), s0 = (int)(task % groups) * 64;
-    if (q >= Q) return;
-    const int n = cnt[q];
-    if (s0 >= n) return;
-    const bool valid = s0 + lane < n;
-    const int64_t cand = cand_lo + buf[(size_t)q * KP + (valid ? s0 + lane : s0)].y;
-    const int d = m.dim, half = d >> 1;
-    const bool cplx = topk_cplx(m.scorer), th = m.scorer == KGE_TRANSH;
-    const double *qxq = th ? qx + (size_t)q * 2 * d : nullptr;     // TransH: q' then the unit normal, fp64
-    const int span = cplx ? 32 : 64, total = cplx ? half : d;      // key steps per chunk, in all
-    const int64_t hoff = (int64_t)h[q] * m.ent_ld, roff = (int64_t)r[q] * m.rel_ld;
-    uint32_t *mine = rows[wave];
-    auto elem = [&](const uint32_t *row, int e) -> double {        // staged element e of a row
-        if constexpr (BF16) return (double)__uint_as_float((e & 1) ? (row[e >> 1] & 0xffff0000u) : (row[e >> 1] << 16));
-        else return (double)__uint_as_float(row[e]);
-    };
-    double acc = 0.0, A = 0.0;
-    // (TransH walks the row twice: first A = u . t, then the squared distance)
-    for (int pass = th ? 0 : 1; pass < 2; ++pass)
-    for (int c0 = 0; c0 < total; c0 += span) {
-        const int steps = total - c0 < span ? total - c0 : span;
-        // staged element e <-> table column: real scorers c0 + e; complex: c0 + e (e < 32), d/2 + c0 + e - 32 (else)
-        auto column = [&](int e) { return cplx ? (e < 32 ? c0 + e : half + c0 + e - 32) : c0 + e; };
-        auto live = [&](int e) { return (cplx ? (e & 31) : e) < steps; };
-        if (live(lane)) {
-            if (th) { qd[wave][lane] = qxq[c0 + lane]; wd[wave][lane] = qxq[d + c0 + lane]; }
-            else qd[wave][lane] = query_f64<BF16>(m, hoff, roff, column(lane));
-        }
-        constexpr int RPI = 64 / DW;                    // rows per wave-wide load
-        const int sub = lane / DW, dw = lane % DW;
-        // (sixteen loads in flight: one after the other, each waits out the memory's latency)
-        for (int r0 = 0; r0 < 64; r0 += 16 * RPI) {
-            uint32_t v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int64_t c = __shfl(cand, r0 + u * RPI + sub);
-                v[u] = 0u;
-                if (live(dw * E)) v[u] = *(const uint32_t *)((const char *)m.ent + (c * m.ent_ld + column(dw * E)) * (BF16 ? 2 : 4));
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) mine[(r0 + u * RPI + sub) * (DW + 1) + dw] = v[u];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const uint32_t *row = mine + lane * (DW + 1);
-        if (th) {
-            if (pass == 0) for (int j = 0; j < steps; ++j) A = fma(wd[wave][j], elem(row, j), A);
-            else for (int j = 0; j < steps; ++j) {
-                const double x = fma(A, wd[wave][j], __dsub_rn(qd[wave][j], elem(row, j)));
-                acc = fma(x, x, acc);
-            }
-        } else if (cplx) {
-            for (int j = 0; j < steps; ++j) acc = key_step(m.scorer, acc, qd[wave][j], elem(row, j), qd[wave][32 + j], elem(row, 32 + j));
-        } else {
-            for (int j = 0; j < steps; ++j) acc = key_step(m.scorer, acc, qd[wave][j], elem(row, j), 0.0, 0.0);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    if (valid) keyd[(size_t)q * KP + s0 + lane] = topk_mult(m.scorer) ? -acc : acc;
-}
+template <bool BF16> constexpr int TK_ROW_STRIDE = 64 * (BF16 ? 2 : 4) + 16;
+constexpr int TK_FINISH_LDS = 4096 + 1024 * 12 + 4 * 64 * TK_ROW_STRIDE<false>;    // the most that a call takes (K <= 256, rows <= 1,024 bytes)
 
 struct QInfo { double qn; float eps_a, eps_b; float eps_w, c; };   // |q~|^2 (fp64), rounding-bound coefficients; TransH: |dw|, c
 
-// final ordering, safety check, outputs
+// Exhaustive fp64 re-rank of one query by its workgroup (lds: TK_EXACT_BYTES; qv, wv: its exact components).
+constexpr int TK_CAPX = 2048;
+constexpr int TK_EXACT_BYTES = TK_CAPX * 12;
 template <bool BF16>
-__global__ void topk_final_kernel(KgeModelDev m, const int32_t *h, const int32_t *r, int Q, int64_t cand_lo,
-                                  int64_t ncand, const int32_t *cnt, const uint2 *buf, int KP, int KPP,
-                                  const double *keyd, const float *thr, const QInfo *qinfo, const float *tmax2,
-                                  int K, int32_t *out_idx, float *out_score, const int32_t *true_t,
-                                  const uint32_t *rankcnt, int64_t *out_rank, int32_t *flag) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+__device__ __forceinline__ void topk_exact(const KgeModelDev &m, int64_t cand_lo, int64_t ncand, int K, int32_t *out_idx, float *out_score,
+                                           const int32_t *true_t, int tt, int64_t *out_rank, int q, const double *qv, const double *wv, char *lds) {
     double *key = (double *)lds;
-    int *idx = (int *)(lds + (size_t)KPP * 8);
-    const int q = blockIdx.x;
-    if (q >= Q) return;
-    const int n = cnt[q];
-    for (int i = threadIdx.x; i < KPP; i += blockDim.x) {
-        key[i] = i < n ? keyd[(size_t)q * KP + i] : INFINITY;
-        idx[i] = i < n ? (int)buf[(size_t)q * KP + i].y : 0x7FFFFFFF;
-    }
+    int *idx = (int *)(lds + TK_CAPX * 8);
+    __shared__ int count;
+    __shared__ double tau;
+    __shared__ unsigned long long above;
+    auto key_of = [&](int64_t toff) { return canonical_key<BF16>(m.scorer, m.dim, qv, wv, m.ent, toff); };
+    if (threadIdx.x == 0) { count = 0; tau = INFINITY; above = 0ull; }
+    for (int i = threadIdx.x; i < TK_CAPX; i += blockDim.x) { key[i] = INFINITY; idx[i] = 0x7FFFFFFF; }
     __syncthreads();
-    bitonic_asc_pair(key, idx, KPP);
+    double tkey = 0.0;
+    if (true_t) { tkey = key_of((int64_t)tt * m.ent_ld); }
+    unsigned long long mine = 0;
+    for (int64_t c0 = 0; c0 < ncand; c0 += blockDim.x) {
+        const int64_t c = c0 + threadIdx.x;
+        if (c < ncand) {
+            const double kc = key_of((cand_lo + c) * m.ent_ld);
+            if (true_t && (kc < tkey || (kc == tkey && cand_lo + c < tt))) ++mine;
+            if (kc <= tau) { const int s = atomicAdd(&count, 1); key[s] = kc; idx[s] = (int)c; }   // s < TK_CAPX by the compaction below
+        }
+        __syncthreads();
+        // every thread reads the counter between two barriers, so that no wave can start the next round's appends before
+        // a slower one has taken the same decision
+        const bool compact = count > TK_CAPX - (int)blockDim.x;   // next round could overflow: compact to the K best
+        __syncthreads();
+        if (compact) {
+            bitonic_asc_pair(key, idx, TK_CAPX);
+            if (threadIdx.x == 0) { count = K; tau = key[K - 1]; }
+            __syncthreads();
+            for (int i = K + threadIdx.x; i < TK_CAPX; i += blockDim.x) { key[i] = INFINITY; idx[i] = 0x7FFFFFFF; }
+            __syncthreads();
+        }
+    }
+    bitonic_asc_pair(key, idx, TK_CAPX);
     const bool dm = topk_mult(m.scorer);
     for (int i = threadIdx.x; i < K; i += blockDim.x) {
-        const bool ok = i < n;
+        const bool ok = idx[i] != 0x7FFFFFFF;
         out_idx[(size_t)q * K + i] = ok ? (int32_t)(cand_lo + idx[i]) : -1;
         out_score[(size_t)q * K + i] = ok ? (dm ? (float)(-key[i]) : (float)(-sqrt(key[i]))) : -INFINITY;
     }
-    if (threadIdx.x == 0) {
-        // Everything that was discarded has a matrix-core value <= theta (the KP-th best value).  Its
+    if (true_t) {
+        atomicAdd(&above, mine);
+        __syncthreads();
+        if (threadIdx.x == 0) out_rank[q] = 1 + (int64_t)above;
+    }
+}
+
+// Re-scoring, final ordering, safety check and outputs: one query per workgroup.
+//
+// A wave re-scores 64 survivors at a time, lane = survivor, so that the 64 sequential fp64 chains run in lockstep.  The candidate
+// rows arrive through the LDS in chunks of 64 columns (complex scorers: 32 real parts followed by the 32 imaginary parts of the same
+// coordinates), 16 bytes per lane and load; the loads of the next chunk are in flight while a chunk is walked.  Rows are 16 bytes
+// longer in the LDS than in memory: sixteen lanes' 16-byte pieces fall into different banks.  The key is the one of
+// canonical_key, step by step, against the exact query, whose components are made once per workgroup.
+template <bool BF16>
+__global__ __launch_bounds__(256) void topk_finish_kernel(KgeModelDev m, const int32_t *h, const int32_t *r, int Q, int64_t cand_lo,
+                                  int64_t ncand, const int32_t *cnt, const uint2 *buf, int KP, int KPP,
+                                  const float *thr, const QInfo *qinfo, const float *tmax2,
+                                  int K, int32_t *out_idx, float *out_score, const int32_t *true_t,
+                                  const uint32_t *rankcnt, int64_t *out_rank, const int32_t *flag, const double *qx) {
+    constexpr int ES = BF16 ? 2 : 4;
+    constexpr int PIECES = 64 * ES / 16;                // 16-byte pieces of a row's chunk
+    constexpr int PER = 16 / ES;                        // columns of a piece
+    constexpr int RPL = 64 / PIECES;                    // rows per wave-wide load
+    constexpr int NL = 64 / RPL;                        // loads per chunk
+    constexpr int STRIDE = TK_ROW_STRIDE<BF16>;         // bytes between rows in the LDS
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ int pos_s, flag_s;
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (q >= Q) return;
+    const int d = m.dim, half = d >> 1;
+    const bool cplx = topk_cplx(m.scorer), th = m.scorer == KGE_TRANSH, dm = topk_mult(m.scorer);
+    double *qv = (double *)lds, *wv = qv + d;                       // exact query; TransH: unit normal
+    double *key = qv + (th ? 2 * d : d);
+    int *idx = (int *)(key + KPP);
+    char *rows = (char *)(idx + KPP);                   // [waves with survivors][64][STRIDE]
+    const int n = cnt[q];
+    const float theta = thr[q], tm2 = *tmax2;
+    const QInfo qi = qinfo[q];
+    const int64_t hoff = (int64_t)h[q] * m.ent_ld, roff = (int64_t)r[q] * m.rel_ld;
+    const int tt = true_t ? true_t[q] : -1;
+    if (tid == 0) { pos_s = -1; flag_s = flag[q]; }
+    const int span = cplx ? 32 : 64, total = cplx ? half : d;       // key steps per chunk, in all
+    const int nchunk = (total + span - 1) / span, walks = th ? 2 * nchunk : nchunk;    // (TransH: A = u . t first, then the distance)
+    const int piece = lane % PIECES, lrow = lane / PIECES;
+    char *mine = rows + wave * 64 * STRIDE;
+    uint32_t own, cand[NL];
+    kge_u32x4 v[NL];
+    auto load = [&](int w) {
+        const int at = (w < nchunk ? w : w - nchunk) * span + (cplx ? piece % (PIECES / 2) : piece) * PER;
+        const int col = at + (cplx && piece >= PIECES / 2 ? half : 0);
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            v[u] = kge_u32x4{0u, 0u, 0u, 0u};
+            if (at < total) v[u] = *(const kge_u32x4 *)((const char *)m.ent + ((cand_lo + cand[u]) * m.ent_ld + col) * ES);
+        }
+    };
+    auto begin = [&](int s0) {
+        own = buf[(size_t)q * KP + (s0 + lane < n ? s0 + lane : s0)].y;
+#pragma unroll
+        for (int u = 0; u < NL; ++u) cand[u] = __shfl(own, u * RPL + lrow);
+        load(0);
+    };
+    if (wave * 64 < n) begin(wave * 64);
+    for (int j = tid; j < d; j += 256) {                // (while the first rows are on their way)
+        if (th) { qv[j] = qx[(size_t)q * 2 * d + j]; wv[j] = qx[(size_t)q * 2 * d + d + j]; }
+        else qv[j] = query_f64<BF16>(m, hoff, roff, j);
+    }
+    for (int i = n + tid; i < KPP; i += 256) { key[i] = INFINITY; idx[i] = 0x7FFFFFFF; }
+    __syncthreads();
+    auto wave_fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    for (int s0 = wave * 64; s0 < n; s0 += 256) {
+        if (s0 > wave * 64) begin(s0);
+        double acc = 0.0, A = 0.0;
+        for (int w = 0; w < walks; ++w) {
+#pragma unroll
+            for (int u = 0; u < NL; ++u) *(kge_u32x4 *)(mine + (u * RPL + lrow) * STRIDE + piece * 16) = v[u];
+            if (w + 1 < walks) load(w + 1);
+            wave_fence();
+            const int c0 = (w < nchunk ? w : w - nchunk) * span, steps = total - c0 < span ? total - c0 : span;
+            const kge_u32x4 *row = (const kge_u32x4 *)(mine + lane * STRIDE);
+            key_walk<BF16>(m.scorer, w >= nchunk, steps, qv + c0, qv + half + c0, wv + c0, [&](int p) { return row[p]; },
+                           [&](int p) { return row[PIECES / 2 + p]; }, A, acc);
+            wave_fence();
+        }
+        if (s0 + lane < n) { key[s0 + lane] = dm ? -acc : acc; idx[s0 + lane] = (int)own; }
+    }
+    __syncthreads();
+    bitonic_asc_pair(key, idx, KPP);
+    const int lim = K < n ? K : n;
+    for (int i = tid; i < K; i += 256) {
+        const bool ok = i < n;
+        out_idx[(size_t)q * K + i] = ok ? (int32_t)(cand_lo + idx[i]) : -1;
+        out_score[(size_t)q * K + i] = ok ? (dm ? (float)(-key[i]) : (float)(-sqrt(key[i]))) : -INFINITY;
+        if (ok && true_t && cand_lo + idx[i] == tt) pos_s = i;      // (at most one)
+    }
+    if (tid == 0) {
+        // Everything that was discarded has a matrix-core value <= theta (the KP-th best value, or the sample's).  Its
         // exact value is at most theta + eps; the list is safe if that stays strictly below the exact
         // value of the K-th entry.  eps bounds the rounding of the query to the table type and the
         // fp32 accumulation:  DistMult (|dq| + d 2^-23 |q~|) Tmax;  TransE 2|dq|(|q~|+Tmax) + |dq|^2 +
         // d 2^-22 (|q~|+Tmax)^2, with Tmax the largest candidate norm; ComplEx and RotatE are the same two forms on
         // their own query (h * r, h * e^{ir}), whose fp32 evaluation error is part of dq.
-        if (n >= KP && ncand > KP && K <= n) {
-            const QInfo qi = qinfo[q];
-            const double Tm = sqrt((double)*tmax2);
+        const bool cut = theta > -INFINITY && ncand > KP;
+        if (cut && K > n) flag_s = 1;                   // (the sample's threshold, and not enough above it)
+        else if (cut) {
+            const double Tm = sqrt((double)tm2);
             double eps, exactK;
             if (dm) { eps = ((double)qi.eps_a + (double)qi.eps_b) * Tm; exactK = -key[K - 1]; }
             else if (m.scorer == KGE_TRANSH) {
@@ -778,82 +888,19 @@ __global__ void topk_final_kernel(KgeModelDev m, const int32_t *h, const int32_t
                 exactK = -key[K - 1] + qi.qn;
             }
             eps = eps * 1.01 + 1e-30;
-            if (!((double)thr[q] + eps < exactK)) flag[q] = 1;
-        }
-        if (out_rank) {
-            const int tt = true_t[q];
-            int64_t rank = 1 + (int64_t)rankcnt[q];
-            bool in_range = tt >= cand_lo && tt < cand_lo + ncand;
-            int pos = -1;
-            const int lim = K < n ? K : n;
-            for (int i = 0; i < lim; ++i) if (cand_lo + idx[i] == tt) { pos = i; break; }
-            if (pos >= 0) rank = pos + 1;                    // exact: position in the fp64 ordering
-            else if (in_range && rank <= lim) rank = lim + 1; // it is not in the exact list, so it ranks below it
-            out_rank[q] = rank;
+            if (!((double)theta + eps < exactK)) flag_s = 1;
         }
     }
-}
-
-// exhaustive fp64 re-rank of one flagged query per workgroup
-template <bool BF16>
-__global__ void topk_exact_kernel(KgeModelDev m, const int32_t *h, const int32_t *r, int Q, int64_t cand_lo,
-                                  int64_t ncand, int K, int32_t *out_idx, float *out_score, const int32_t *true_t,
-                                  int64_t *out_rank, const int32_t *flag, const double *qx) {
-    constexpr int CAPX = 2048;
-    __shared__ double key[CAPX];
-    __shared__ int idx[CAPX];
-    __shared__ int count;
-    __shared__ double tau;
-    __shared__ unsigned long long above;
-    const int q = blockIdx.x;
-    if (q >= Q || !flag[q]) return;
-    const int64_t hoff = (int64_t)h[q] * m.ent_ld, roff = (int64_t)r[q] * m.rel_ld;
-    __shared__ double qv[TK_MAXD], wv[TK_MAXD];
-    const bool th = m.scorer == KGE_TRANSH;
-    for (int j = threadIdx.x; j < m.dim; j += blockDim.x) {
-        if (th) { qv[j] = qx[(size_t)q * 2 * m.dim + j]; wv[j] = qx[(size_t)q * 2 * m.dim + m.dim + j]; }
-        else qv[j] = query_f64<BF16>(m, hoff, roff, j);
-    }
-    auto key_of = [&](int64_t toff) {
-        return th ? canonical_key_th<BF16>(m.dim, qv, wv, m.ent, toff) : canonical_key<BF16>(m.scorer, m.dim, qv, m.ent, toff);
-    };
-    if (threadIdx.x == 0) { count = 0; tau = INFINITY; above = 0ull; }
-    for (int i = threadIdx.x; i < CAPX; i += blockDim.x) { key[i] = INFINITY; idx[i] = 0x7FFFFFFF; }
     __syncthreads();
-    double tkey = 0.0; int tt = -1;
-    if (true_t) { tt = true_t[q]; tkey = key_of((int64_t)tt * m.ent_ld); }
-    unsigned long long mine = 0;
-    for (int64_t c0 = 0; c0 < ncand; c0 += blockDim.x) {
-        const int64_t c = c0 + threadIdx.x;
-        if (c < ncand) {
-            const double kc = key_of((cand_lo + c) * m.ent_ld);
-            if (true_t && (kc < tkey || (kc == tkey && cand_lo + c < tt))) ++mine;
-            if (kc <= tau) { const int s = atomicAdd(&count, 1); key[s] = kc; idx[s] = (int)c; }   // s < CAPX by the compaction below
-        }
-        __syncthreads();
-        // every thread reads the counter between two barriers, so that no wave can start the next round's appends before
-        // a slower one has taken the same decision
-        const bool compact = count > CAPX - (int)blockDim.x;   // next round could overflow: compact to the K best
-        __syncthreads();
-        if (compact) {
-            bitonic_asc_pair(key, idx, CAPX);
-            if (threadIdx.x == 0) { count = K; tau = key[K - 1]; }
-            __syncthreads();
-            for (int i = K + threadIdx.x; i < CAPX; i += blockDim.x) { key[i] = INFINITY; idx[i] = 0x7FFFFFFF; }
-            __syncthreads();
-        }
+    if (flag_s) {                                       // (the same for every thread)
+        topk_exact<BF16>(m, cand_lo, ncand, K, out_idx, out_score, true_t, tt, out_rank, q, qv, wv, rows);
+        return;
     }
-    bitonic_asc_pair(key, idx, CAPX);
-    const bool dm = topk_mult(m.scorer);
-    for (int i = threadIdx.x; i < K; i += blockDim.x) {
-        const bool ok = idx[i] != 0x7FFFFFFF;
-        out_idx[(size_t)q * K + i] = ok ? (int32_t)(cand_lo + idx[i]) : -1;
-        out_score[(size_t)q * K + i] = ok ? (dm ? (float)(-key[i]) : (float)(-sqrt(key[i]))) : -INFINITY;
-    }
-    if (true_t) {
-        atomicAdd(&above, mine);
-        __syncthreads();
-        if (threadIdx.x == 0) out_rank[q] = 1 + (int64_t)above;
+    if (tid == 0 && out_rank) {
+        int64_t rank = 1 + (int64_t)rankcnt[q];
+        if (pos_s >= 0) rank = pos_s + 1;                // exact: position in the fp64 ordering
+        else if (tt >= cand_lo && tt < cand_lo + ncand && rank <= lim) rank = lim + 1;    // it is not in the exact list, so it ranks below it
+        out_rank[q] = rank;
     }
 }
 
@@ -989,57 +1036,48 @@ __global__ void topk_prep_th_kernel(KgeModelDev m, const int32_t *h, const int32
     }
 }
 
-// squared norms of the candidate rows (stored negated: the scan starts its accumulators from them) and their maximum, one
-// atomic per wave.  Fast path (rows of 16-byte
-// aligned power-of-two length): a lane reads 16 bytes, a wave 64 / LPR rows per step, four steps in flight.
+// squared norms of the candidate rows (stored negated: the scan starts its accumulators from them) and their maximum.  A lane
+// reads 16 bytes (rows are multiples of 16 bytes and aligned to them), a wave 64 / LPR rows per step, four steps in flight.
 template <bool BF16>
-__global__ void topk_tnorm_kernel(const char *ent, int64_t stride, int d, int64_t ncand, int64_t npad, float *tn,
+__global__ __launch_bounds__(256) void topk_tnorm_kernel(const char *ent, int64_t stride, int d, int64_t ncand, int64_t npad, float *tn,
                                   uint32_t *tmax_bits) {
+    __shared__ float wmax[4];
     const int lane = threadIdx.x & 63;
-    const int64_t wid = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
+    const int64_t wid = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t nw = (int64_t)gridDim.x * 4;
     float mx = 0.f;
-    const int rowb = d * (BF16 ? 2 : 4), lpr = rowb / 16;           // lanes per row
-    const bool fast = rowb % 16 == 0 && lpr <= 64 && (lpr & (lpr - 1)) == 0 && stride % 16 == 0 && ((uintptr_t)ent & 15) == 0;
-    if (fast) {
-        const int rpw = 64 / lpr, sub = lane / lpr, li = lane % lpr;    // rows per wave step
-        constexpr int U = 4;
-        for (int64_t c0 = wid * rpw * U; c0 < npad; c0 += nw * rpw * U) {
-            kge_u32x4 v[U];
+    const int chunks = d * (BF16 ? 2 : 4) / 16;                     // 16-byte chunks of a row
+    const int lpr = chunks <= 1 ? 1 : 1 << (32 - __clz(chunks - 1)); // lanes per row
+    const int rpw = 64 / lpr, sub = lane / lpr, li = lane % lpr;    // rows per wave step
+    constexpr int U = 4;
+    for (int64_t c0 = wid * rpw * U; c0 < npad; c0 += nw * rpw * U) {
+        kge_u32x4 v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t c = c0 + u * rpw + sub;
-                v[u] = kge_u32x4{0u, 0u, 0u, 0u};
-                if (c < ncand) v[u] = *(const kge_u32x4 *)(ent + c * stride + li * 16);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float s = 0.f;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if constexpr (BF16) {
-                        const float a0 = __uint_as_float(v[u][k] << 16), a1 = __uint_as_float(v[u][k] & 0xffff0000u);
-                        s += a0 * a0; s += a1 * a1;
-                    } else { const float a0 = __uint_as_float(v[u][k]); s += a0 * a0; }
-                }
-                for (int o = lpr >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
-                const int64_t c = c0 + u * rpw + sub;
-                if (li == 0 && c < npad) tn[c] = -s;
-                mx = fmaxf(mx, s);
-            }
+        for (int u = 0; u < U; ++u) {
+            const int64_t c = c0 + u * rpw + sub;
+            v[u] = kge_u32x4{0u, 0u, 0u, 0u};
+            if (c < ncand && li < chunks) v[u] = *(const kge_u32x4 *)(ent + c * stride + li * 16);
         }
-    } else {
-        for (int64_t c = wid; c < npad; c += nw) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             float s = 0.f;
-            if (c < ncand) for (int j = lane; j < d; j += 64) { const float v = El<BF16>::ld(ent + c * stride, j); s += v * v; }
-            s = kge_wave_sum(s);
-            if (lane == 0) tn[c] = -s;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if constexpr (BF16) {
+                    const float a0 = __uint_as_float(v[u][k] << 16), a1 = __uint_as_float(v[u][k] & 0xffff0000u);
+                    s += a0 * a0; s += a1 * a1;
+                } else { const float a0 = __uint_as_float(v[u][k]); s += a0 * a0; }
+            }
+            for (int o = lpr >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
+            const int64_t c = c0 + u * rpw + sub;
+            if (li == 0 && c < npad) tn[c] = -s;
             mx = fmaxf(mx, s);
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    if (lane == 0) atomicMax(tmax_bits, __float_as_uint(mx));    // mx >= 0: bit order = value order
+    mx = kge_wave_max(mx);
+    if (lane == 0) wmax[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) topk_raise(tmax_bits, fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3])));
 }
 
 __global__ void topk_fill_empty_kernel(int32_t *out_idx, float *out_score, int64_t n, int64_t *out_rank, int Q) {
@@ -1081,8 +1119,34 @@ TopkPlan make_plan(const kge_model_t &m, int64_t Q, int64_t ncand, int K) {
     return p;
 }
 
+// Size of the sample and growth of the chunks.  What is weighed (seconds, measured): scanning a row for all queries - 0.1 ns while
+// the table's bytes bound it, 0.37 ps per query and 512 bytes beyond; a stage - threshold, launches and their latencies, 26 us +
+// 5.4 ns per query; an append, 40 ps.  A sample of S rows costs S rows, a stage that multiplies what the threshold stands for by g
+// costs itself and KP (g - 1) appends per query, so with ln(n / S) / ln(g) stages the best g depends on stage / appends alone (2.6 for 8,192
+// queries, 12 for 128) and the best S is where a row more saves as much of a stage.  g keeps a query's expected appends within what
+// a workgroup of the compaction holds in registers and 24 per area (of 64: an overflow would rank the query exhaustively).
+struct TopkStages { int64_t sample; double growth; };
+TopkStages topk_stages(const TopkPlan &p, int64_t Q, int64_t total_tiles) {
+    const double width = (p.rb == 512 ? 1.0 : 2.0) * (p.th ? 2.0 : 1.0) * (p.bf16 ? 1.0 : 8.0);
+    const double row = fmax(0.1e-9 * p.rb / 512, 0.37e-12 * (double)Q * width), stage = 26e-6 + 5.4e-9 * (double)Q;
+    const double appends = 40e-12 * (double)Q * p.KP;
+    const double most = fmin(3500.0, 24.0 * 2.0 * p.nseg) / (1.15 * p.KP);
+    double g = fmin(2.1 + 0.5 * stage / appends, most);
+    if (g < 1.5) g = 1.5;
+    TopkStages s;
+    s.sample = (int64_t)((stage + appends * (g - 1.0)) / log(g) / (1.2 * row) / TK_ST);
+    if (s.sample > total_tiles / 2) s.sample = total_tiles / 2;
+    if (s.sample < 128) s.sample = 128 < total_tiles - 1 ? 128 : total_tiles - 1;      // (whole tiles of candidates)
+    const double all = (double)total_tiles / (double)s.sample;
+    double stages = ceil(log(all) / log(g) - 0.25);
+    if (stages < 1.0) stages = 1.0;
+    s.growth = pow(all, 1.0 / stages);
+    if (s.growth > most && most >= 1.5) s.growth = pow(all, 1.0 / (stages + 1.0));
+    return s;
+}
+
 struct TopkWs {
-    void *Qm; float *vt, *thr, *tn; QInfo *qinfo; int32_t *cnt, *flag; uint32_t *rankcnt, *tmax; uint2 *keep, *seg; int32_t *segcnt; double *keyd; uint32_t *zeros;
+    void *Qm; float *vt, *thr, *tn; QInfo *qinfo; int32_t *cnt, *flag; uint32_t *rankcnt, *tmax; uint2 *keep, *seg; int32_t *segcnt; uint32_t *zeros;
     void *Wm; float *cq; double *qx;                    // TransH only
 };
 
@@ -1101,7 +1165,6 @@ size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w, bool most = false) {
     if (most && p.Qp / p.own > 4 && areas < (size_t)p.own * 1024 * 2) areas = (size_t)p.own * 1024 * 2;
     w.seg = (uint2 *)take(areas * TK_HALF * 8);
     w.segcnt = (int32_t *)take(areas * 4);
-    w.keyd = (double *)take((size_t)p.Qp * p.KP * 8);
     w.Wm = nullptr; w.cq = nullptr; w.qx = nullptr;
     if (p.th) {
         w.Wm = take((size_t)p.Qp * p.rb); w.cq = (float *)take((size_t)p.Qp * 4);
@@ -1110,29 +1173,29 @@ size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w, bool most = false) {
     return off + 256;
 }
 
-template <bool BF16, int RB, int KIND, int OB, bool TH, bool FN>
-int launch_scan(const TopkArgs &a, int own_tiles, int nsplit, hipStream_t st) {
+template <bool BF16, int RB, int KIND, int OB, bool TH, bool FN, bool SAMPLE>
+int launch_scan(const TopkArgs &a, hipStream_t st) {
     constexpr int NSTAGE = RB == 512 ? 4 : 3;
     constexpr int LDS = NSTAGE * TK_ST * RB + (NSTAGE + 1) * 4 * 256;
     static KgeLdsLimit lds_limit;
-    if (lds_limit.set((const void *)topk_scan_kernel<BF16, RB, KIND, OB, TH, FN>, LDS) != KGE_OK) return KGE_E_HIP;
-    hipLaunchKernelGGL((topk_scan_kernel<BF16, RB, KIND, OB, TH, FN>), dim3(own_tiles * ((nsplit + 7) / 8 * 8)), dim3(256), LDS, st, a);
+    if (lds_limit.set((const void *)topk_scan_kernel<BF16, RB, KIND, OB, TH, FN, SAMPLE>, LDS) != KGE_OK) return KGE_E_HIP;
+    hipLaunchKernelGGL((topk_scan_kernel<BF16, RB, KIND, OB, TH, FN, SAMPLE>), dim3(a.own_tiles * ((a.nsplit + 7) / 8 * 8)), dim3(256), LDS, st, a);
     return kge_launch_status();
 }
 
-template <bool BF16>
-int scan(const TopkPlan &p, int kind, const TopkArgs &a, int own_tiles, int nsplit, hipStream_t st) {
-    if (p.th) return p.fn ? launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, true>(a, own_tiles, nsplit, st)
-                          : launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, false>(a, own_tiles, nsplit, st);
+template <bool BF16, bool SAMPLE>
+int scan(const TopkPlan &p, int kind, const TopkArgs &a, hipStream_t st) {
+    if (p.th) return p.fn ? launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, true, SAMPLE>(a, st)
+                          : launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, false, SAMPLE>(a, st);
     if (kind == KGE_KIND_MULT) {
-        if (p.rb == 1024) return launch_scan<BF16, 1024, KGE_KIND_MULT, 1, false, true>(a, own_tiles, nsplit, st);
-        return p.ob == 1 ? launch_scan<BF16, 512, KGE_KIND_MULT, 1, false, true>(a, own_tiles, nsplit, st)
-                         : launch_scan<BF16, 512, KGE_KIND_MULT, 2, false, true>(a, own_tiles, nsplit, st);
+        if (p.rb == 1024) return launch_scan<BF16, 1024, KGE_KIND_MULT, 1, false, true, SAMPLE>(a, st);
+        return p.ob == 1 ? launch_scan<BF16, 512, KGE_KIND_MULT, 1, false, true, SAMPLE>(a, st)
+                         : launch_scan<BF16, 512, KGE_KIND_MULT, 2, false, true, SAMPLE>(a, st);
     }
-    if (p.rb == 1024) return p.fn ? launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, true>(a, own_tiles, nsplit, st)
-                                  : launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, false>(a, own_tiles, nsplit, st);
-    if (p.ob == 1) return launch_scan<BF16, 512, KGE_KIND_DIST, 1, false, true>(a, own_tiles, nsplit, st);
-    return launch_scan<BF16, 512, KGE_KIND_DIST, 2, false, false>(a, own_tiles, nsplit, st);
+    if (p.rb == 1024) return p.fn ? launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, true, SAMPLE>(a, st)
+                                  : launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, false, SAMPLE>(a, st);
+    if (p.ob == 1) return launch_scan<BF16, 512, KGE_KIND_DIST, 1, false, true, SAMPLE>(a, st);
+    return launch_scan<BF16, 512, KGE_KIND_DIST, 2, false, false, SAMPLE>(a, st);
 }
 
 }  // namespace
@@ -1173,10 +1236,10 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     }
     if (p.bf16) {
         if (!p.th) hipLaunchKernelGGL(topk_prep_kernel<true>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt, w.tmax, w.zeros);
-        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel<true>, dim3((unsigned)(p.npad / 4 < 8192 ? (p.npad + 3) / 4 : 8192)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
+        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel<true>, dim3((unsigned)(p.npad / 32 < 2048 ? p.npad / 32 : 2048)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
     } else {
         if (!p.th) hipLaunchKernelGGL(topk_prep_kernel<false>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt, w.tmax, w.zeros);
-        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel<false>, dim3((unsigned)(p.npad / 4 < 8192 ? (p.npad + 3) / 4 : 8192)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
+        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel<false>, dim3((unsigned)(p.npad / 32 < 2048 ? p.npad / 32 : 2048)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
     }
     if (hipGetLastError() != hipSuccess) return KGE_E_HIP;
 
@@ -1186,46 +1249,58 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     base.seg = w.seg; base.segcnt = w.segcnt; base.nseg = p.nseg; base.rankcnt = w.rankcnt; base.nq = (int)Q; base.zeros = w.zeros;
     const int own_tiles = p.Qp / p.own;
     const int64_t total_tiles = p.npad / TK_ST;
-    // Growing chunks: thresholds are refreshed between chunks.  The first chunk appends everything: it holds at most 128
-    // tiles and two per split, so that an area (one lane half: TK_ST / 2 candidates of a tile) takes 32 entries and a query
-    // 4,096; afterwards a chunk is 3x what has been seen, so a query with a well-mixed candidate order appends about 3 KP
-    // entries per chunk, spread over nsplit x 2 private areas.  Neighbouring rows that all beat the threshold fill the areas
-    // of their split: up to 128 in a row fit.  (Growing up to 10 times where a query has many areas saves two compactions and launches -
-    // 128 queries x 5.7M 867 -> 822 us, 16 x 300,000 271 -> 212 -, but tables whose neighbouring rows are alike then overflow an area, and the
-    // query is ranked exhaustively: clusters of 50 rows, 512 queries x 1M, 0.75 -> 149 ms.)
+    // One chunk appends everything where it fits: at most 128 tiles and two per split, so that an area (one lane half: TK_ST / 2
+    // candidates of a tile) takes 32 entries and a query 4,096.  Longer tables are sampled first (SAMPLE in the kernel); the scan then
+    // goes by chunks between which the thresholds are refreshed: the first covers g times the rows of the sample, the next g times
+    // that.
     constexpr int FIRST_TILES = 2;
     static_assert(FIRST_TILES * TK_ST / 2 <= TK_HALF, "the first chunk overflows no area");
-    int64_t seen = 0;
-    while (seen < total_tiles) {
-        int64_t tiles = seen == 0 ? (p.nseg * FIRST_TILES < 128 ? p.nseg * FIRST_TILES : 128) : 3 * seen;
-        if (tiles > total_tiles - seen) tiles = total_tiles - seen;
+    auto compact = [&](uint2 *keep, int nsplit) {
+        const int areas_of = (nsplit + 7) / 8 * 8 < p.nseg ? (nsplit + 7) / 8 * 8 : p.nseg;
+        hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)Q), dim3(256), 0, st, keep, w.cnt, w.seg, w.segcnt, p.nseg, areas_of, p.KP,
+                           w.thr, w.flag, (int)Q);
+    };
+    double reach = (double)total_tiles, growth = 1.0;
+    if (total_tiles > (p.nseg * FIRST_TILES < 128 ? p.nseg * FIRST_TILES : 128)) {
+        const TopkStages s = topk_stages(p, Q, total_tiles);
+        growth = s.growth; reach = s.sample * s.growth;
         TopkArgs c = base;
-        c.tile_lo = seen; c.tile_hi = seen + tiles; c.own_tiles = own_tiles;
-        int want = p.nseg;                                    // one split per private area
-        if (want > tiles) want = (int)tiles;
-        c.tiles_per_wg = (int)((tiles + want - 1) / want);
-        const int nsplit = (int)((tiles + c.tiles_per_wg - 1) / c.tiles_per_wg);
+        c.tile_lo = 0; c.tile_hi = s.sample; c.own_tiles = own_tiles;
+        c.nsplit = s.sample < p.nseg ? (int)s.sample : p.nseg;
+        c.samp_row = ncand / TK_ST; c.samp_step = c.samp_row / s.sample;      // (sample <= ncand / TK_ST: the last row is 31 samp_row + ...)
+        // about 1,000 to 2,500 groups of a query in all, at most 64 of a split and lane half
+        c.fold = c.nsplit * 8 > 2500;
+        const int64_t per = (s.sample + c.nsplit - 1) / c.nsplit, each = c.fold ? 2 : 8;      // tiles of a split; groups of a split and flush
+        c.flush = (int)((per * c.nsplit * each + 2047) / 2048);
+        const int64_t least = (per * each / 2 + TK_HALF - 1) / TK_HALF;
+        if (c.flush < least) c.flush = (int)least;
+        const int rc = p.bf16 ? scan<true, true>(p, kind, c, st) : scan<false, true>(p, kind, c, st);
+        if (rc != KGE_OK) return rc;
+        compact(nullptr, c.nsplit);
+    }
+    for (int64_t seen = 0; seen < total_tiles; reach *= growth) {
+        int64_t upto = (int64_t)(reach * 1.01);               // (no chunk of a few tiles at the end)
+        if (upto > total_tiles || upto <= seen) upto = total_tiles;
+        TopkArgs c = base;
+        c.tile_lo = seen; c.tile_hi = upto; c.own_tiles = own_tiles;
+        c.nsplit = upto - seen < p.nseg ? (int)(upto - seen) : p.nseg;      // one split per private area
         int rc;
         {
             KgeProfScope prof(KGE_PROF_TOPK_SCAN, st);
-            rc = p.bf16 ? scan<true>(p, kind, c, own_tiles, nsplit, st) : scan<false>(p, kind, c, own_tiles, nsplit, st);
+            rc = p.bf16 ? scan<true, false>(p, kind, c, st) : scan<false, false>(p, kind, c, st);
         }
         if (rc != KGE_OK) return rc;
-        seen += tiles;
-        const int areas_of = (nsplit + 7) / 8 * 8 < p.nseg ? (nsplit + 7) / 8 * 8 : p.nseg;
-        hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)Q), dim3(256), 0, st, w.keep, w.cnt, w.seg, w.segcnt, p.nseg, areas_of, p.KP,
-                           w.thr, w.flag, (int)Q);
+        seen = upto;
+        compact(w.keep, c.nsplit);
     }
-    const int64_t nres = Q * p.KP;
-    const int final_lds = p.KPP * 12;
-    if (p.bf16) {
-        hipLaunchKernelGGL(topk_rescore_kernel<true>, dim3((unsigned)((nres / 64 + 3) / 4)), dim3(256), 0, st, md, h, r, (int)Q, lo, w.cnt, w.keep, p.KP, w.keyd, w.qx);
-        hipLaunchKernelGGL(topk_final_kernel<true>, dim3((unsigned)Q), dim3(256), final_lds, st, md, h, r, (int)Q, lo, ncand, w.cnt, w.keep, p.KP, p.KPP, w.keyd, w.thr, w.qinfo, (const float *)w.tmax, K, out_idx, out_score, true_t, w.rankcnt, out_rank, w.flag);
-        hipLaunchKernelGGL(topk_exact_kernel<true>, dim3((unsigned)Q), dim3(256), 0, st, md, h, r, (int)Q, lo, ncand, K, out_idx, out_score, true_t, out_rank, w.flag, w.qx);
-    } else {
-        hipLaunchKernelGGL(topk_rescore_kernel<false>, dim3((unsigned)((nres / 64 + 3) / 4)), dim3(256), 0, st, md, h, r, (int)Q, lo, w.cnt, w.keep, p.KP, w.keyd, w.qx);
-        hipLaunchKernelGGL(topk_final_kernel<false>, dim3((unsigned)Q), dim3(256), final_lds, st, md, h, r, (int)Q, lo, ncand, w.cnt, w.keep, p.KP, p.KPP, w.keyd, w.thr, w.qinfo, (const float *)w.tmax, K, out_idx, out_score, true_t, w.rankcnt, out_rank, w.flag);
-        hipLaunchKernelGGL(topk_exact_kernel<false>, dim3((unsigned)Q), dim3(256), 0, st, md, h, r, (int)Q, lo, ncand, K, out_idx, out_score, true_t, out_rank, w.flag, w.qx);
-    }
-    return kge_launch_status();
+    const int groups = p.KP / 64 < 4 ? p.KP / 64 : 4, row_bytes = groups * 64 * (p.bf16 ? TK_ROW_STRIDE<true> : TK_ROW_STRIDE<false>);
+    const int finish_lds = p.dim * (p.th ? 16 : 8) + p.KPP * 12 + (row_bytes > TK_EXACT_BYTES ? row_bytes : TK_EXACT_BYTES);
+    auto finish = [&](auto kernel, KgeLdsLimit &limit) {
+        if (limit.set((const void *)kernel, TK_FINISH_LDS) != KGE_OK) return (int)KGE_E_HIP;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)Q), dim3(256), finish_lds, st, md, h, r, (int)Q, lo, ncand, w.cnt, w.keep, p.KP, p.KPP, w.thr,
+                           w.qinfo, (const float *)w.tmax, K, out_idx, out_score, true_t, w.rankcnt, out_rank, w.flag, w.qx);
+        return kge_launch_status();
+    };
+    static KgeLdsLimit limit_bf16, limit_f32;
+    return p.bf16 ? finish(topk_finish_kernel<true>, limit_bf16) : finish(topk_finish_kernel<false>, limit_f32);
 }

@@ -203,6 +203,28 @@ def test_adversarial_candidate_order_still_exact(orc):
     _check(orc, "distmult", G, False, 0, 30000, 20, np.array([29990, 3, 15000, 29999], dtype=np.int32))
 
 
+@pytest.mark.parametrize("order", ["rising", "falling", "clusters", "equal"])
+@pytest.mark.parametrize("scorer,dim,bf16,Q,n,K", [
+    ("distmult", 32, True, 5, 4129, 256), ("transe", 24, False, 129, 8191, 100),      # a tile more than one chunk; the smallest sample
+    ("complex", 272, True, 130, 5001, 10), ("transh", 48, True, 300, 9999, 50),       # rows over 512 bytes; two contractions
+    ("rotate", 64, False, 520, 6000, 256), ("distmult", 16, True, 8200, 2100, 3)])    # two blocks of queries; 32 splits
+def test_sampled_threshold_on_sorted_tables(orc, scorer, dim, bf16, Q, n, K, order):
+    """The threshold that the scan starts with comes from a sample of rows at even distances: tables sorted by length, tables whose
+    neighbours are alike, and tables that are one row over and over (more equal values than a list holds, lowest index first)."""
+    G = make_case(scorer, n, 7, dim, Q, 0, bf16)
+    if order == "clusters":
+        G["ent"] = G["ent"][np.arange(n) // 300 * 300] + (0.05 * G["ent"]).astype(np.float32)
+    elif order == "equal":
+        G["ent"][100:] = G["ent"][100]
+    else:
+        s = np.linspace(0.3, 1.5, n).astype(np.float32)[:, None]
+        G["ent"] = G["ent"] * (s if order == "rising" else s[::-1])
+    if bf16:
+        G["ent"] = ks.round_to_bf16(np.ascontiguousarray(G["ent"]))
+    G["ent"] = np.ascontiguousarray(G["ent"], dtype=np.float32)
+    _check(orc, scorer, G, bf16, 0, n, K, ks.uniform_ids(ks.rng(9, ks.TAG_HELDOUT), 0, n, Q))
+
+
 @pytest.mark.parametrize("scorer", ["distmult", "transe", "transh"])
 @pytest.mark.parametrize("dim,bf16,Q", [(16, True, 70), (144, True, 130), (248, False, 600), (8, False, 520), (240, True, 1030), (304, True, 130)])
 def test_columns_behind_a_row_are_not_read(scorer, dim, bf16, Q):
