@@ -250,6 +250,9 @@ void kge_block_kernel(const KgeBlockArgs a) {
 
     // ---- own operand fragments: 16 bytes per lane per 32-byte k-step --------------------------
     constexpr bool PL = C::PL;
+    // One wave per SIMD on planes: the own operand and the gradient accumulators stay in the accumulator registers (matrix
+    // instructions read them there), which leaves the vector registers for fragments requested ahead of their use.
+    constexpr bool ALONE = PL && C::OCC == 1;
     const int64_t own_plane = (int64_t)a.own_pad * C::DP * 2, str_plane = (int64_t)a.str_tiles * C::ST * C::DP * 2;   // PL: bytes per plane
     uint4 own[OW][PL ? 1 : C::KS];
     uint4 ownw[(TRANSH && OWN_ROW && !PL) ? C::KS : 1];
@@ -426,7 +429,8 @@ void kge_block_kernel(const KgeBlockArgs a) {
 #pragma unroll
                 for (int pl = 0; pl < 2; ++pl) {
                     uint4 &v = own2p[k2].p[pl];
-                    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+                    if constexpr (ALONE) asm volatile("" : "+a"(v.x), "+a"(v.y), "+a"(v.z), "+a"(v.w));
+                    else asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
                 }
             asm volatile("" : "+v"(o_exp));
         } else {
@@ -679,6 +683,22 @@ void kge_block_kernel(const KgeBlockArgs a) {
         for (int i = 0; i < 16; ++i) tm = fmaxf(tm, x2[i]);
         return fmaxf(tm, __shfl_xor(tm, 32));
     };
+    // what an own row has accumulated times r.  (ALONE: in place.  As ordinary products the accumulators are vector registers here, and
+    // the compiler carries them to and from the accumulator registers in every tile: 250 of 1,280 vector instructions.  The matrix
+    // instructions that wrote them are those of the previous tile, a phase 1 ago.)
+    auto rescale = [&](kge_f32x16 &x, float r) {
+        if constexpr (ALONE) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                float v = x[i], tmp;
+                asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1" : "+a"(v), "=&v"(tmp) : "v"(r));
+                x[i] = v;
+            }
+        } else {
+            for (int i = 0; i < 16; ++i) x[i] *= r;
+            asm volatile("" ::: "memory");
+        }
+    };
     // the coefficients of phase 2 for own fragment h, packed as its B-operand
     auto weights = [&](int h, const float (&sv)[16], const float (&dv)[16], const float (&Av)[16], const float (&x2)[16]) {
         float coef[16], coef2[16];
@@ -760,9 +780,8 @@ void kge_block_kernel(const KgeBlockArgs a) {
                     c_scale = s_new;
 #pragma unroll
                     for (int b = 0; b < C::NBH; ++b) {
-                        for (int i = 0; i < 16; ++i) acc2[0][b][i] *= r;
-                        asm volatile("" ::: "memory");
-                        if constexpr (TRANSH && OWN_ROW) { for (int i = 0; i < 16; ++i) acc2b[b][i] *= r; asm volatile("" ::: "memory"); }
+                        rescale(acc2[0][b], r);
+                        if constexpr (TRANSH && OWN_ROW) rescale(acc2b[b], r);
                     }
                 }
                 auto pieces = [&](const float *c) {
@@ -835,6 +854,31 @@ void kge_block_kernel(const KgeBlockArgs a) {
         // measured and did not pay: inside a chunk the order is left to the compiler.
         zero1();
         constexpr int CH1 = OW > 1 ? 1 : PL ? C::PL_CHUNK : (NG1 > 4 ? 4 : NG1);   // groups per chunk: at most 64 (16) registers in flight
+        if constexpr (ALONE) {
+            constexpr int AH1 = NG1 < 2 ? NG1 : 2, AH2 = 2;
+#pragma unroll
+            for (int gq = 0; gq < AH1; ++gq) ld1(base, gq);
+#pragma unroll
+            for (int gq = 0; gq < NG1; ++gq) {
+                if (gq + AH1 < NG1) ld1(base, gq + AH1);
+                __builtin_amdgcn_sched_barrier(0);
+                mma1(gq);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int gq = 0; gq < AH2; ++gq) ld2(base, gq);
+            __builtin_amdgcn_sched_barrier(0);
+            epilogue();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int gq = 0; gq < NG2; ++gq) {
+                if (gq + AH2 < NG2) ld2(base, gq + AH2);
+                __builtin_amdgcn_sched_barrier(0);
+                mma2(gq);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            continue;
+        }
 #pragma unroll
         for (int c0 = 0; c0 < NG1; c0 += CH1) {
 #pragma unroll
