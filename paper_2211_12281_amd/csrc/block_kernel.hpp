@@ -416,8 +416,9 @@ void kge_block_kernel(const KgeBlockArgs a) {
             }
     }
 
+    constexpr int FILL = C::NSTAGE - (ALONE ? 2 : 1);      // tiles requested ahead of the loop
 #pragma unroll
-    for (int s2 = 0; s2 < C::NSTAGE - 1; ++s2) issue(t0 + s2, s2);
+    for (int s2 = 0; s2 < FILL; ++s2) issue(t0 + s2, s2);
     // Pin the own operand as loaded before the loop.  Otherwise the compiler defers its waits for these
     // ordinary loads to their first uses inside the hot loop, and such a wait (which counts every memory
     // operation in flight) would also drain the asynchronous copies of the coming tiles on every iteration.
@@ -461,6 +462,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
     kge_f32x16 acc[OW], accw;                              // phase-1 accumulators: [stream, own]
     uint4 bf[OW][2], bf2[2];                               // bf16 B-operands of phase 2
     KgeP2 coef2p[2], coefw2p[2];                           // PL: the fp16 pieces of coefficients times c_scale
+    float coef[16], coef2[16];                             // coefficients of phase 2 (coef2: TransH's normals)
     // PL: what the own row's coefficients, and with them its accumulated gradient, are multiplied by (a power of two until its reference is
     // raised); 0: none yet, what has accumulated counts for nothing
     float c_scale = 0.f;
@@ -578,44 +580,94 @@ void kge_block_kernel(const KgeBlockArgs a) {
             }
         }
     };
+    // orders a region of the scheduler: a matrix instruction, then a share of its vector instructions
+#define KGE_MIX(n, valu)                                                        \
+    _Pragma("unroll") for (int mix_i = 0; mix_i < (n); ++mix_i) {               \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                      \
+        __builtin_amdgcn_sched_group_barrier(0x002, (valu), 0);                 \
+    }
     // ---- epilogue: scores / loss weights / gradient coefficients of the tile, element by element ----
     auto str_exp_of = [&](int sl) { return *(const int *)(side + (OWN_ROW ? 128 : 512) + sl * 4); };       // PL: exponent of 1 / scale of a streamed row
-    // scores of own fragment h against the tile (SCORE mode stores them), 1/distance, w.t
-    auto scores = [&](int h, float (&sv)[16], float (&dv)[16], float (&Av)[16]) {
-        const int oidx = oidx0 + 32 * h;
+    // the first part of the scores of own fragment h against the tile: products (bilinear scorers) or squared distances by the norm
+    // expansion |q|^2 + |t|^2 - 2 q.t (TransH: plus the terms of the projection), w.t, and whether any of the lane's entries cancels
+    auto norms_of = [&](int h, int i, float &qn, float &cc, float &wn, float &tnv) {
+        const int sl = 8 * (i >> 2) + 4 * g + (i & 3);
+        if constexpr (OWN_ROW) { qn = o_qn[h]; cc = o_c[h]; wn = o_wn[h]; tnv = *(const float *)(side + sl * 4); }
+        else { float4 ri = *(const float4 *)(side + sl * 16); qn = ri.x; cc = ri.y; wn = ri.w; tnv = o_tn[h]; }
+    };
+    // (the streamed rows of the entries 4 j .. 4 j + 3 are neighbours: one read each of their norms and exponents, four of their row info)
+    struct Side4 { kge_f32x4 tn, ri[OWN_ROW ? 1 : 4]; kge_u32x4 e; };
+    auto side4 = [&](int j, Side4 &x) {
+        x.e = *(const kge_u32x4 *)(side + (OWN_ROW ? 128 : 512) + (8 * j + 4 * g) * 4);
+        if constexpr (KIND == KGE_KIND_DIST) {
+            if constexpr (OWN_ROW) x.tn = *(const kge_f32x4 *)(side + (8 * j + 4 * g) * 4);
+            else {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) { dv[i] = 0.f; Av[i] = 0.f; }
-        if constexpr (PL) {                                // (exact: powers of two)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int s_exp = str_exp_of(8 * (i >> 2) + 4 * g + (i & 3));
-                acc[0][i] = ldexpf(acc[0][i], o_exp + s_exp);
-                if constexpr (TRANSH) accw[i] = ldexpf(accw[i], (OWN_ROW ? s_exp : o_exp) + KGE_PLANE_UNIT_EXP);
+                for (int u = 0; u < 4; ++u) x.ri[u] = *(const kge_f32x4 *)(side + (8 * j + 4 * g + u) * 16);
             }
         }
-        if constexpr (KIND == KGE_KIND_MULT) {
+    };
+    int s_exps[16];                                        // ALONE: exponents of the streamed rows of the lane's entries
+    auto scores4 = [&](int h, int j, const Side4 &x, float (&d2)[16], float (&Av)[16], bool &cancel) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) sv[i] = acc[h][i];
-        } else {
-            // squared distance by the norm expansion |q|^2 + |t|^2 - 2 q.t (TransH: plus the terms of the
-            // projection); entries where it cancels (below 1e-3 of the norms) are redone by direct
-            // differences in a rarely taken branch.  (The line with planes: above it their errors are 0.6 to 0.9 times those of 24-bit operands
-            // with norms summed in 32 bits, negatives at 0.05 and 0.1 of its length from a query; four products are no better.  A line of 4e-3
-            // gives a tenth of the error at 0.05, but tables with a common part ten to thirty times their spread take 15 to 100 times as
-            // long: TransE 8,192 x 4,096 x 128 at 0.05 7.0 ms instead of 0.2)
-            float d2[16], thr[16];
-            bool cancel = false;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int sl = 8 * (i >> 2) + 4 * g + (i & 3);
-                float qn, cc, wn, tnv;
-                if constexpr (OWN_ROW) { qn = o_qn[h]; cc = o_c[h]; wn = o_wn[h]; tnv = *(const float *)(side + sl * 4); }
-                else { float4 ri = *(const float4 *)(side + sl * 16); qn = ri.x; cc = ri.y; wn = ri.w; tnv = o_tn[h]; }
+        for (int u = 0; u < 4; ++u) {
+            const int i = 4 * j + u;
+            s_exps[i] = (int)x.e[u];
+            acc[0][i] = ldexpf(acc[0][i], o_exp + s_exps[i]);           // (exact: powers of two)
+            if constexpr (TRANSH) accw[i] = ldexpf(accw[i], (OWN_ROW ? s_exps[i] : o_exp) + KGE_PLANE_UNIT_EXP);
+            Av[i] = 0.f;
+            if constexpr (KIND == KGE_KIND_MULT) d2[i] = acc[h][i];
+            else {
+                const float qn = OWN_ROW ? o_qn[h] : x.ri[OWN_ROW ? 0 : u][0], cc = OWN_ROW ? o_c[h] : x.ri[OWN_ROW ? 0 : u][1];
+                const float wn = OWN_ROW ? o_wn[h] : x.ri[OWN_ROW ? 0 : u][3], tnv = OWN_ROW ? x.tn[u] : o_tn[h];
                 d2[i] = fmaf(-2.f, acc[h][i], qn + tnv);
                 if constexpr (TRANSH) { const float A = accw[i]; Av[i] = A; d2[i] += A * (2.f * cc - A * (2.f - wn)); }
-                thr[i] = 1e-3f * (qn + tnv);
-                cancel = cancel || d2[i] < thr[i];
+                cancel = cancel || d2[i] < 1e-3f * (qn + tnv);
             }
+        }
+    };
+    auto scores1 = [&](int h, float (&d2)[16], float (&Av)[16], bool &cancel) {
+        cancel = false;
+        if constexpr (ALONE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { Side4 x; side4(j, x); scores4(h, j, x, d2, Av, cancel); }
+            return;
+        }
+        if constexpr (PL) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][i] = ldexpf(acc[0][i], o_exp + str_exp_of(8 * (i >> 2) + 4 * g + (i & 3)));
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            Av[i] = 0.f;
+            if constexpr (KIND == KGE_KIND_MULT) d2[i] = acc[h][i];
+            else {
+                float qn, cc, wn, tnv;
+                norms_of(h, i, qn, cc, wn, tnv);
+                d2[i] = fmaf(-2.f, acc[h][i], qn + tnv);
+                if constexpr (TRANSH) { const float A = accw[i]; Av[i] = A; d2[i] += A * (2.f * cc - A * (2.f - wn)); }
+                cancel = cancel || d2[i] < 1e-3f * (qn + tnv);
+            }
+        }
+    };
+    // the scores themselves (SCORE mode stores them) and 1/distance.  Distances whose expansion cancels (below 1e-3 of the norms) are
+    // redone by direct differences in a rarely taken branch.  (The line with planes: above it their errors are 0.6 to 0.9 times those of
+    // 24-bit operands with norms summed in 32 bits, negatives at 0.05 and 0.1 of its length from a query; four products are no
+    // better.  A line of 4e-3 gives a tenth of the error at 0.05, but tables with a common part ten to thirty times their spread take 15 to
+    // 100 times as long: TransE 8,192 x 4,096 x 128 at 0.05 7.0 ms instead of 0.2)
+    auto scores2 = [&](int h, float (&d2)[16], bool cancel, float (&sv)[16], float (&dv)[16]) {
+        const int oidx = oidx0 + 32 * h;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dv[i] = 0.f;
+        if constexpr (KIND == KGE_KIND_MULT) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sv[i] = d2[i];
+        } else {
+            auto line = [&](int i) {
+                float qn, cc, wn, tnv;
+                norms_of(h, i, qn, cc, wn, tnv);
+                return 1e-3f * (qn + tnv);
+            };
             if (__any(cancel)) {
                 auto again = [&](int i) {
                     const int sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
@@ -629,7 +681,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 if constexpr (BF16) {
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        if (d2[i] < thr[i]) d2[i] = again(i);
+                        if (d2[i] < line(i)) d2[i] = again(i);
                         asm volatile("" ::: "memory");      // keeps the branch from being turned into selects
                     }
                 } else {
@@ -637,7 +689,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                     // the pieces leave none (bf16 tables have them, and lose 0.5-1.5 % by this form)
                     uint32_t todo = 0;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) todo |= d2[i] < thr[i] ? 1u << i : 0u;
+                    for (int i = 0; i < 16; ++i) todo |= d2[i] < line(i) ? 1u << i : 0u;
                     while (todo) {
                         const int i = __builtin_ctz(todo);
                         todo &= todo - 1;
@@ -685,7 +737,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
     };
     // what an own row has accumulated times r.  (ALONE: in place.  As ordinary products the accumulators are vector registers here, and
     // the compiler carries them to and from the accumulator registers in every tile: 250 of 1,280 vector instructions.  The matrix
-    // instructions that wrote them are those of the previous tile, a phase 1 ago.)
+    // instructions that wrote them are those of the previous tile, most of an epilogue ago.)
     auto rescale = [&](kge_f32x16 &x, float r) {
         if constexpr (ALONE) {
 #pragma unroll
@@ -699,9 +751,23 @@ void kge_block_kernel(const KgeBlockArgs a) {
             asm volatile("" ::: "memory");
         }
     };
+    // PL: the coefficients of phase 2 as its B-operand
+    constexpr int NPC = TRANSH ? 4 : 2;
+    auto make_piece = [&](int p) {
+        const int j2 = TRANSH ? p >> 1 : p;
+        const float *c = (TRANSH && (p & 1) ? coef2 : coef) + 8 * j2;
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = c[i] * c_scale;
+        if (TRANSH && (p & 1)) coefw2p[j2] = kge_split2(x); else coef2p[j2] = kge_split2(x);
+    };
+    auto make_pieces = [&]() {
+#pragma unroll
+        for (int p = 0; p < NPC; ++p) make_piece(p);
+    };
+    float row_K[16], row_c[16];                            // ALONE, GRADT: constants of the streamed rows, requested ahead of their use
     // the coefficients of phase 2 for own fragment h, packed as its B-operand
     auto weights = [&](int h, const float (&sv)[16], const float (&dv)[16], const float (&Av)[16], const float (&x2)[16]) {
-        float coef[16], coef2[16];
         if constexpr (MODE == KGE_MODE_FWD) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -729,7 +795,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int sl = 8 * (i >> 2) + 4 * g + (i & 3);
-                const float K2 = *(const float *)(side + sl * 16 + 8);       // -inf for padded queries
+                const float K2 = ALONE ? row_K[i] : *(const float *)(side + sl * 16 + 8);       // -inf for padded queries
                 float u = kge_exp2(fmaf(sv[i], xscale, K2));
                 if constexpr (LOSS == KGE_LOGSIGMOID) {
                     const float y = a.gamma + sv[i];
@@ -741,7 +807,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 coef[i] = c1;
                 if constexpr (KIND == KGE_KIND_DIST) sum1[h] += c1;
                 // (planes: the streamed rows are q and w^ themselves, not q - c w^ and w^)
-                if constexpr (TRANSH && PL) coef2[i] = c1 * (Av[i] - *(const float *)(side + sl * 16 + 4));
+                if constexpr (TRANSH && PL) coef2[i] = c1 * (Av[i] - (ALONE ? row_c[i] : *(const float *)(side + sl * 16 + 4)));
                 else if constexpr (TRANSH) coef2[i] = c1 * Av[i];
             }
         }
@@ -766,7 +832,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 float cm = 0.f;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int s_exp = str_exp_of(8 * (i >> 2) + 4 * g + (i & 3));
+                    const int s_exp = ALONE ? s_exps[i] : str_exp_of(8 * (i >> 2) + 4 * g + (i & 3));
                     coef[i] = ldexpf(coef[i], s_exp);
                     cm = fmaxf(cm, fabsf(coef[i]));
                     if constexpr (TRANSH) { coef2[i] = ldexpf(coef2[i], OWN_ROW ? s_exp : KGE_PLANE_UNIT_EXP); cm = fmaxf(cm, fabsf(coef2[i])); }
@@ -784,64 +850,136 @@ void kge_block_kernel(const KgeBlockArgs a) {
                         if constexpr (TRANSH && OWN_ROW) rescale(acc2b[b], r);
                     }
                 }
-                auto pieces = [&](const float *c) {
-                    float x[8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) x[i] = c[i] * c_scale;
-                    return kge_split2(x);
-                };
-#pragma unroll
-                for (int j2 = 0; j2 < 2; ++j2) {
-                    coef2p[j2] = pieces(coef + 8 * j2);
-                    if constexpr (TRANSH) coefw2p[j2] = pieces(coef2 + 8 * j2);
-                }
+                if constexpr (!ALONE) make_pieces();
             }
         }
     };
     // The FWD pass keeps all weights relative to a per-row reference exponent st_m that is only
     // raised (and what the row has accumulated rescaled) when a tile's maximum exceeds it by more than
     // KGE_TAU: weights stay below 2^KGE_TAU, and the rescaling is a rarely taken branch of the loop.
+    auto epilogue2 = [&](int h, float (&d2)[16], const float (&Av)[16], bool cancel) {
+        float sv[16], dv[16], x2[16];
+        scores2(h, d2, cancel, sv, dv);
+        if constexpr (MODE == KGE_MODE_FWD) {
+            const float tm = exponents(h, sv, x2);
+            const bool have = st_m[h] > -INFINITY;
+            const bool trip = tm > (have ? KGE_TAU : -INFINITY);   // without a reference, any finite entry sets one
+            if (__any(trip)) {
+                // the rows that tripped take the tile's maximum as their reference
+                const float m_new = trip ? (have ? tm + st_m[h] : tm) : st_m[h];
+                const float shift = trip ? -tm : 0.f;              // exponents relative to the new reference
+                const float r = trip ? (have ? kge_exp2(-tm) : 0.f) : 1.f;   // nothing accumulated yet without one
+                st_m[h] = m_new;
+                st_l[h] *= r; st_acc[h] *= r; sum1[h] *= r; sum2[h] *= r; sum3[h] *= r;
+                if constexpr (PL) {
+                    // What has accumulated is worth 2^-tm of itself: the scale that it carries, which the coefficients of the new
+                    // reference take, rises by as much (left where it was set for earlier rows, later ones that now outweigh them would
+                    // have the last bits of it), until it ends at 2^126: then what there is counts for nothing and the next tile sets another.
+                    // (With the accumulators rescaled here instead: TransH step 8,192 x 4,096 379 us for 369, ComplEx 4,096 x 4,096 x 256 194 / 185.)
+                    const float s_new = c_scale * kge_exp2(tm);
+                    if (trip) c_scale = s_new < 0x1p126f ? s_new : 0.f;
+                } else {
+#pragma unroll
+                    for (int b = 0; b < C::NBH; ++b) {
+                        // one block at a time: the accumulators live in AGPRs and pass through VGPRs here; the
+                        // empty statements keep this rarely executed code from being turned into selects
+                        for (int i = 0; i < 16; ++i) acc2[h][b][i] *= r;
+                        asm volatile("" ::: "memory");
+                        if constexpr (TRANSH) { for (int i = 0; i < 16; ++i) acc2b[b][i] *= r; asm volatile("" ::: "memory"); }
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x2[i] += shift;       // masked entries stay at -inf
+            }
+        }
+        weights(h, sv, dv, Av, x2);
+    };
     auto epilogue = [&]() {
 #pragma unroll
         for (int h = 0; h < OW; ++h) {
-            float sv[16], dv[16], Av[16], x2[16];
-            scores(h, sv, dv, Av);
-            if constexpr (MODE == KGE_MODE_FWD) {
-                const float tm = exponents(h, sv, x2);
-                const bool have = st_m[h] > -INFINITY;
-                const bool trip = tm > (have ? KGE_TAU : -INFINITY);   // without a reference, any finite entry sets one
-                if (__any(trip)) {
-                    // the rows that tripped take the tile's maximum as their reference
-                    const float m_new = trip ? (have ? tm + st_m[h] : tm) : st_m[h];
-                    const float shift = trip ? -tm : 0.f;              // exponents relative to the new reference
-                    const float r = trip ? (have ? kge_exp2(-tm) : 0.f) : 1.f;   // nothing accumulated yet without one
-                    st_m[h] = m_new;
-                    st_l[h] *= r; st_acc[h] *= r; sum1[h] *= r; sum2[h] *= r; sum3[h] *= r;
-                    if constexpr (PL) {
-                        // What has accumulated is worth 2^-tm of itself: the scale that it carries, which the coefficients of the new
-                        // reference take, rises by as much (left where it was set for earlier rows, later ones that now outweigh them would
-                        // have the last bits of it), until it ends at 2^126: then what there is counts for nothing and the next tile sets another.
-                        // (With the accumulators rescaled here instead: TransH step 8,192 x 4,096 379 us for 369, ComplEx 4,096 x 4,096 x 256 194 / 185.)
-                        const float s_new = c_scale * kge_exp2(tm);
-                        if (trip) c_scale = s_new < 0x1p126f ? s_new : 0.f;
-                    } else {
-#pragma unroll
-                        for (int b = 0; b < C::NBH; ++b) {
-                            // one block at a time: the accumulators live in AGPRs and pass through VGPRs here; the
-                            // empty statements keep this rarely executed code from being turned into selects
-                            for (int i = 0; i < 16; ++i) acc2[h][b][i] *= r;
-                            asm volatile("" ::: "memory");
-                            if constexpr (TRANSH) { for (int i = 0; i < 16; ++i) acc2b[b][i] *= r; asm volatile("" ::: "memory"); }
-                        }
-                    }
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) x2[i] += shift;       // masked entries stay at -inf
-                }
-            }
-            weights(h, sv, dv, Av, x2);
+            float d2[16], Av[16];
+            bool cancel;
+            scores1(h, d2, Av, cancel);
+            epilogue2(h, d2, Av, cancel);
         }
     };
 
+    if constexpr (ALONE) {
+        // One wave per SIMD: what it issues beside the matrix instructions has to run under them.  A round takes tile t from its squared
+        // distances to its coefficients; then the first contraction of tile t + 1 runs with their split into pieces, and the
+        // second contraction of tile t with the first part of the epilogue of tile t + 1.  What bounds it is what a wave can issue: about 1,000
+        // vector instructions, 96 matrix instructions and 350 others per tile and wave, one in four to five cycles (vector pipe 49 %,
+        // matrix pipe 33 % busy).  us, the parts one after the other / here: TransH 8,192 x 4,096 x 128 step 367 / 338, TransE 4,096 x
+        // 4,096 x 256 169 / 162, ComplEx 171 / 165, DistMult 2,048 x 8,192 x 200 142 / 140.  (With the fragments' order left to the
+        // compiler, which reads them where they are used, 359, 170, 171; the first contraction of tile t + 1 under the distances and
+        // weights of tile t instead: 336, 162, 169, 141.)
+        static_assert(C::NSTAGE >= 4, "tiles t and t + 1 are read, one is in flight, one is being refilled");
+        static_assert(NG1 % NPC == 0 && NG2 % 4 == 0, "");
+        constexpr int AH1 = 2, AH2 = 2, P1_MFMAS = NG1 * G1 / 2 * (TRANSH ? 6 : 3), P2_MFMAS = NG2 * (TRANSH ? 12 : 6);
+        auto land = [&]() {                                // the next tile has landed: NSTAGE - 3 younger ones may be in flight
+            kge_wait_vmcnt<(C::NSTAGE - 3) * C::LPW>();
+            __syncthreads();
+        };
+        float d2[16], Av[16];
+        bool cancel;
+        land();
+        issue(t0 + C::NSTAGE - 2, C::NSTAGE - 2);
+        set_tile(t0);
+        zero1();
+#pragma unroll
+        for (int gq = 0; gq < NG1; ++gq) { ld1(base, gq); mma1(gq); }
+        scores1(0, d2, Av, cancel);
+        for (int t = t0;;) {
+            if constexpr (MODE == KGE_MODE_GRADT) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float *ri = (const float *)(side + (8 * (i >> 2) + 4 * g + (i & 3)) * 16);
+                    row_K[i] = ri[2];
+                    if constexpr (TRANSH) row_c[i] = ri[1];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            epilogue2(0, d2, Av, cancel);
+            __builtin_amdgcn_sched_barrier(0);
+            land();
+            issue(t + C::NSTAGE - 1, t - t0 + C::NSTAGE - 1);
+            const char *stage = base;
+            set_tile(t + 1);                               // (past the end: the last tile again, unused)
+#pragma unroll
+            for (int gq = 0; gq < AH1; ++gq) ld1(base, gq);
+            __builtin_amdgcn_sched_barrier(0);
+            zero1();
+            Side4 sd[2];
+            // (fragments are requested two groups ahead of their matrix instructions, the side information of four entries a group
+            // ahead and before them: reads complete in order)
+#pragma unroll
+            for (int gq = 0; gq < NG1; ++gq) {
+                if (gq + 1 == NG1) side4(0, sd[0]);
+                if (gq + AH1 < NG1) ld1(base, gq + AH1);
+                else if (gq + AH1 - NG1 < AH2) ld2(stage, gq + AH1 - NG1);
+                __builtin_amdgcn_sched_barrier(0);
+                mma1(gq);
+#pragma unroll
+                for (int p = 0; p < NPC; ++p) if (p * NG1 / NPC == gq) make_piece(p);
+                KGE_MIX(P1_MFMAS / NG1, 6)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            cancel = false;
+#pragma unroll
+            for (int gq = 0; gq < NG2; ++gq) {
+                constexpr int every = NG2 / 4;             // groups per four entries
+                const int j = gq / every;
+                if (gq % every == 0 && j < 3) side4(j + 1, sd[(j + 1) & 1]);
+                if (gq + AH2 < NG2) ld2(stage, gq + AH2);
+                __builtin_amdgcn_sched_barrier(0);
+                mma2(gq);
+                if (gq % every == every - 1) scores4(0, j, sd[j & 1], d2, Av, cancel);
+                KGE_MIX(P2_MFMAS / NG2, 6)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (++t >= t1) break;
+        }
+    } else
     for (int t = t0; t < t1; ++t) {
         // tile t has landed when at most NSTAGE-2 younger tiles are still in flight; after the
         // barrier every wave has finished tile t-1, whose stage receives tile t + NSTAGE - 1
@@ -854,31 +992,6 @@ void kge_block_kernel(const KgeBlockArgs a) {
         // measured and did not pay: inside a chunk the order is left to the compiler.
         zero1();
         constexpr int CH1 = OW > 1 ? 1 : PL ? C::PL_CHUNK : (NG1 > 4 ? 4 : NG1);   // groups per chunk: at most 64 (16) registers in flight
-        if constexpr (ALONE) {
-            constexpr int AH1 = NG1 < 2 ? NG1 : 2, AH2 = 2;
-#pragma unroll
-            for (int gq = 0; gq < AH1; ++gq) ld1(base, gq);
-#pragma unroll
-            for (int gq = 0; gq < NG1; ++gq) {
-                if (gq + AH1 < NG1) ld1(base, gq + AH1);
-                __builtin_amdgcn_sched_barrier(0);
-                mma1(gq);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int gq = 0; gq < AH2; ++gq) ld2(base, gq);
-            __builtin_amdgcn_sched_barrier(0);
-            epilogue();
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int gq = 0; gq < NG2; ++gq) {
-                if (gq + AH2 < NG2) ld2(base, gq + AH2);
-                __builtin_amdgcn_sched_barrier(0);
-                mma2(gq);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            continue;
-        }
 #pragma unroll
         for (int c0 = 0; c0 < NG1; c0 += CH1) {
 #pragma unroll
