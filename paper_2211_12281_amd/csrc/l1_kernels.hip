@@ -10,7 +10,8 @@
 // difference across zero; the table rows themselves are exact).  The block kernels stage fp32 tiles in the LDS (row pitch 68 floats: the
 // 16 lanes that read 16 different rows at one column offset hit 16 different 16-byte bank groups): the scores 64 x 64, 32 x 64 or 32 x 48
 // with a 4 x 4, 2 x 4 or 2 x 3 register tile per thread, the gradients 32 streamed rows x 64 columns against an 8 x 4 register tile; they are bound by the vector pipe in large blocks and by the latency of a chunk (loads, barrier) in small ones, so the loads of
-// the next chunk are issued before the present one is used (gradient passes 44 -> 24 us each at 512 x 1,280 x 384).
+// the next chunk are issued before the present one is used (gradient passes 44 -> 24 us each at 512 x 1,280 x 384).  Small blocks take both
+// gradients from one kernel (l1_grad_both_kernel).
 #include "row_ops.hpp"
 
 namespace {
@@ -225,6 +226,99 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     __shared__ __attribute__((aligned(16))) float ss[L1_GS * L1_PITCH], ws[L1_GS * L1_WP];
     if ((int)blockIdx.x < q_blocks) l1_grad_body<BF16, true>(q, (int)blockIdx.x, W, ldW, B, N, dp, ss, ws);
     else l1_grad_body<BF16, false>(t, (int)blockIdx.x - q_blocks, W, ldW, B, N, dp, ss, ws);
+}
+
+// Both gradients from ONE sign per (query, negative, dimension): subtraction, median and a multiply-add for either side, four vector
+// operations where the two passes above take six.  A lane is a dimension: a wave owns 16 negatives (16 values and 16 sums in registers)
+// and the queries stream by in chunks of 32, whose weights lie in the LDS (a row's 16 in four reads that all lanes share) and whose values
+// are requested eight queries ahead.  A query's sum over the wave's negatives goes to the LDS; at the end of the chunk the workgroup adds
+// its four waves up into its group's partial row - one block of 64 negatives of the group after the other, so that there are no more
+// partials than the passes above leave: [groups][Bp][dp] and, by splits of the queries, [splits][Np][dp].
+// Bound by that chunk (weights and values in, sums out, two barriers, about 2,000 vector instructions per wave), not by the pipe: a step
+// is faster where a workgroup has few of them (512 x 1,280 x 384 bf16: 43.7 -> 34 us).  32 negatives per wave halve the LDS sums per pair,
+// but leave two waves per SIMD (call 67 -> 71 us), and weights by scalar loads wait for the line of a query's row at every step (71).
+constexpr int L1_BQ = 32, L1_BW = 16, L1_BN = 4 * L1_BW;       // queries of a chunk, negatives of a wave and of a block
+struct L1BothArgs { const float *Q; const void *T; const float *W; int64_t ldW; int B, N, Bp, Np, dp, col_tiles, groups, bpg, chunks, cps; float *accq, *acct; };
+
+template <bool BF16>
+__global__ __launch_bounds__(256) void l1_grad_both_kernel(const L1BothArgs a) {
+    __shared__ __attribute__((aligned(16))) float red[4][L1_BQ][64], ws[L1_BQ][L1_BN];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = (int)blockIdx.x % a.col_tiles, rest = (int)blockIdx.x / a.col_tiles, group = rest % a.groups, split = rest / a.groups;
+    const int j = col * 64 + lane;
+    const int c_lo = split * a.cps, c_hi = min(a.chunks, c_lo + a.cps), blocks = (a.N + L1_BN - 1) / L1_BN, npad = (a.N + 31) / 32 * 32;
+    constexpr int WL = L1_BQ * L1_BW / 256;                     // 16-byte pieces of a chunk's weights per thread
+    for (int nb = group * a.bpg; nb < min(blocks, (group + 1) * a.bpg); ++nb) {
+        const int n0 = (nb * 4 + wave) * L1_BW;
+        const bool live = n0 < a.N;
+        l1_f32x4 wn[WL];
+        auto fetch_w = [&](int ch) {                         // (the weights end at the next multiple of 32 behind N)
+#pragma unroll
+            for (int k = 0; k < WL; ++k) {
+                const int e = tid + 256 * k, row = e / L1_BW, n = nb * L1_BN + e % L1_BW * 4;
+                wn[k] = n < npad ? *(const l1_f32x4 *)(a.W + (int64_t)(ch * L1_BQ + row) * a.ldW + n) : l1_f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        };
+        if (c_lo < c_hi) fetch_w(c_lo);
+        float ov[L1_BW], acc[L1_BW];
+#pragma unroll
+        for (int i = 0; i < L1_BW; ++i) {
+            const int64_t off = (int64_t)(n0 + i) * a.dp + j;
+            ov[i] = (BF16 ? (float)((const __bf16 *)a.T)[off] : ((const float *)a.T)[off]) * L1_BIG;
+            acc[i] = 0.f;
+        }
+        for (int ch = c_lo; ch < c_hi; ++ch) {
+            const int b0 = ch * L1_BQ;
+            const float *qp = a.Q + (int64_t)b0 * a.dp + j;
+#pragma unroll
+            for (int k = 0; k < WL; ++k) { const int e = tid + 256 * k; *(l1_f32x4 *)&ws[e / L1_BW][e % L1_BW * 4] = wn[k]; }
+            __syncthreads();
+            if (ch + 1 < c_hi) fetch_w(ch + 1);
+            if (live) {
+                float qn[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) qn[u] = qp[(int64_t)u * a.dp];
+#pragma unroll 1
+                for (int b8 = 0; b8 < L1_BQ; b8 += 8) {
+                    float qc[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) { qc[u] = qn[u] * L1_BIG; qn[u] = qp[(int64_t)min(b8 + 8 + u, L1_BQ - 1) * a.dp]; }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        float d[2] = {0.f, 0.f};
+#pragma unroll
+                        for (int i4 = 0; i4 < L1_BW / 4; ++i4) {
+                            const l1_f32x4 w4 = *(const l1_f32x4 *)&ws[b8 + u][wave * L1_BW + 4 * i4];
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                const int i = 4 * i4 + c;
+                                const float s = __builtin_amdgcn_fmed3f(qc[u] - ov[i], -1.f, 1.f);
+                                acc[i] = fmaf(w4[c], s, acc[i]);
+                                d[c & 1] = fmaf(-w4[c], s, d[c & 1]);
+                            }
+                        }
+                        red[wave][b8 + u][lane] = d[0] + d[1];
+                    }
+                }
+            } else {
+                for (int bb = 0; bb < L1_BQ; ++bb) red[wave][bb][lane] = 0.f;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < L1_BQ * 64 / 256; ++k) {
+                const int bb = k * 4 + (tid >> 6), b = b0 + bb;
+                const float v = (red[0][bb][lane] + red[1][bb][lane]) + (red[2][bb][lane] + red[3][bb][lane]);
+                if (b < a.B) {
+                    float *p = a.accq + ((int64_t)group * a.Bp + b) * a.dp + j;
+                    *p = nb == group * a.bpg ? v : *p + v;
+                }
+            }
+            // (the next chunk's weights are written before, its sums behind a barrier)
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < L1_BW; ++i) if (n0 + i < a.N) a.acct[((int64_t)split * a.Np + n0 + i) * a.dp + j] = acc[i];
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -464,11 +558,33 @@ size_t kge_l1_most_part(int own_pad, int str_pad, int dp, bool transh) {
 }
 
 int kge_run_l1_grad(bool bf16, const float *Q, const void *T, const float *W, int64_t ldW, int B, int N, int Bp, int Np, int dp, int dim,
-                    int nsplit_q, int nsplit_t, float *accq, float *acct, hipStream_t st) {
+                    int &nsplit_q, int &nsplit_t, float *accq, float *acct, hipStream_t st) {
     if (Bp % L1_GO || Np % L1_GO || Bp % L1_GS || Np % L1_GS || dp % L1_GD) return KGE_E_INVALID_ARG;
     if (nsplit_q <= 0 || nsplit_t <= 0 || nsplit_q != kge_l1_nsplit(Bp, Np, dp, false) || nsplit_t != kge_l1_nsplit(Np, Bp, dp, false))
         return KGE_E_INVALID_ARG;
     KgeProfScope prof(KGE_PROF_BLOCK_FWD, st);
+    {
+        L1BothArgs a{Q, T, W, ldW, B, N, Bp, Np, dp};
+        const int blocks = (N + L1_BN - 1) / L1_BN;
+        a.col_tiles = (dim + L1_GD - 1) / L1_GD; a.chunks = (B + L1_BQ - 1) / L1_BQ;
+        const int most_g = nsplit_q < blocks ? nsplit_q : blocks, most_s = nsplit_t < a.chunks ? nsplit_t : a.chunks;
+        a.bpg = (blocks + most_g - 1) / most_g; a.groups = (blocks + a.bpg - 1) / a.bpg;
+        a.cps = (a.chunks + most_s - 1) / most_s;
+        const int splits = (a.chunks + a.cps - 1) / a.cps;
+        // a workgroup walks bpg blocks of negatives and, for each, cps chunks of queries.  Whole calls against the two passes, us:
+        // 2 to 4 chunks 512 x 1,280 x 384 bf16 76 -> 67, 4,096 x 512 x 256 125 -> 110, 200 x 16,000 x 64 fp32 120 -> 103, 2,000 x 1,000 x 64
+        // 55 -> 56; 8 chunks 2,048 x 2,048 x 256 199 -> 185, 1,000 x 8,192 x 128 fp32 233 -> 211; 32 chunks 1,000 x 4,000 x 384 287 -> 398,
+        // 2,048 x 4,096 x 256 360 -> 422; 45 chunks 3,000 x 3,000 x 256 403 -> 552
+        if (a.bpg * a.cps <= 8) {
+            a.accq = accq; a.acct = acct;
+            nsplit_q = a.groups; nsplit_t = splits;
+            const int64_t wgs = (int64_t)a.col_tiles * a.groups * splits;
+            if (wgs > 0x7fffffff) return KGE_E_UNSUPPORTED;
+            if (bf16) hipLaunchKernelGGL(l1_grad_both_kernel<true>, dim3((unsigned)wgs), dim3(256), 0, st, a);
+            else      hipLaunchKernelGGL(l1_grad_both_kernel<false>, dim3((unsigned)wgs), dim3(256), 0, st, a);
+            return kge_launch_status();
+        }
+    }
     // (the split counts are those of the padded block, their work that of the rows and columns there are; a split past them writes zeros)
     auto part = [&](const void *own, const void *str, float *acc, int own_pad, int own_n, int str_n, int nsplit) {
         const int chunks = (str_n + L1_GS - 1) / L1_GS;

@@ -71,9 +71,10 @@ int kge_run_l1_score(bool bf16, const float *Q, const void *T, int B, int N, int
                      hipStream_t st);
 int kge_l1_nsplit(int own_pad, int str_pad, int dp, bool transh);
 size_t kge_l1_most_part(int own_pad, int str_pad, int dp, bool transh);   // rows of partials (own_pad nsplit) of any block that is no larger
-// W: the finished weights dL/dS of the pairs (kge_run_small_rows); columns past dim rounded up to 64 are not written
+// W: the finished weights dL/dS of the pairs (kge_run_small_rows); columns past dim rounded up to 64 are not written; the split counts
+// come back as those that were used, no larger
 int kge_run_l1_grad(bool bf16, const float *Q, const void *T, const float *W, int64_t ldW, int B, int N, int Bp, int Np, int dp, int dim,
-                    int nsplit_q, int nsplit_t, float *accq, float *acct, hipStream_t st);
+                    int &nsplit_q, int &nsplit_t, float *accq, float *acct, hipStream_t st);
 // TransH under the 1-norm: Q, W = unrounded queries q' and unit normals [Bp][dp]; A = w^ . t and P = sign(x) . w^ per
 // pair beside S (both nullptr: scores only); the pass over the queries also fills acc_part2 with the gradient of w^
 int kge_run_l1h_score(bool bf16, const float *Q, const float *W, const void *T, int B, int N, int Bp, int Np, int dp, float *S,

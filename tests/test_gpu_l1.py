@@ -125,6 +125,16 @@ def test_tiles_and_their_edges(orc, dim, bf16, B, N):
     _compare(orc, "transe", "logsigmoid", G, bf16, 3000, dict(gamma=0.35 * dim, adv_temp=0.2, loss_scale=0.37))
 
 
+@pytest.mark.parametrize("dim,bf16,B,N", [
+    (32, False, 31, 63), (72, False, 33, 65), (144, True, 64, 16), (64, True, 1, 17),      # edges of a chunk of queries and of a wave's negatives
+    (256, False, 321, 1025),                             # the last wave, the last block and the last chunk with one row each
+    (136, False, 2050, 700),                             # several chunks to a split, a last split with fewer
+    (272, True, 1024, 2048), (272, True, 1100, 2048)])   # two blocks of negatives to a group, four chunks to each; the two passes
+def test_both_gradients_from_one_sign(orc, dim, bf16, B, N):
+    G = _grid_case("transe", 3000, 9, dim, B, N, True)   # (with ties: sign(0) = 0 on either side)
+    _compare(orc, "transe", "sampled_softmax", G, bf16, 3000, dict(n_ent_for_c=3000))
+
+
 def test_regulariser_and_repeatability(orc):
     import paper_2211_12281_amd as kge
     G = _grid_case("transe", 2000, 5, 64, 96, 200, True)
