@@ -218,6 +218,20 @@ def test_block_kernels_on_planes(orc, block_passes, scorer, dim, B, N, loss):
     base._compare(orc, scorer, loss, G, False, 3000, kw=kw)
 
 
+@pytest.mark.parametrize("scorer,dim,loss,B,N", [
+    ("transh", 128, "logsigmoid", 1800, 1001), ("transh", 96, "sampled_softmax", 2040, 1300),          # splits of two tiles; three, the last with fewer
+    ("transe", 256, "sampled_softmax", 1025, 2300), ("rotate", 200, "logsigmoid", 1281, 1537),         # three and two tiles
+    ("complex", 136, "sampled_softmax", 600, 1500), ("distmult", 256, "logsigmoid", 2300, 1250)])      # two tiles and one; five and three
+def test_block_kernels_on_planes_few_tiles(orc, block_passes, scorer, dim, loss, B, N):
+    """Rows of 1,024 bytes and TransH, whose rounds work on two tiles at a time: splits that end after the first rounds, with rows that
+    grow by a factor of 64 along the stream, so that the scales of a split's first tiles are lowered by those behind them."""
+    G = make_case(scorer, 3000, 9, dim, B, N, False, amp=0.2 if scorer in ("distmult", "complex") else 0.1)
+    G["neg"] = np.sort(G["neg"])
+    G["ent"] *= (2.0 ** (np.arange(3000) / 500.0 - 5.0)).astype(np.float32)[:, None]
+    kw = dict(n_ent_for_c=3000) if loss == "sampled_softmax" else dict(gamma=1.0, adv_temp=0.7)
+    base._compare(orc, scorer, loss, G, False, 3000, kw=kw)
+
+
 @pytest.mark.parametrize("scorer,bf16", [("transh", False), ("rotate", True), ("complex", False), ("transe", True), ("distmult", False)])
 @pytest.mark.parametrize("dim", [64, 128, 144, 256, 272])
 @pytest.mark.parametrize("N", [50, 2100])
