@@ -216,21 +216,23 @@ __device__ __forceinline__ void adam_apply(uint32_t key, int col, float4 g, int6
 // ---------------------------------------------------------------------------------------------
 // Up to SMALL_MAX row ids in ONE launch (the ids of a training step: 2B + N of them).  Only the grouping of equal ids and
 // the position order inside a group matter to the update, so the order is (low bits of the id, its other bits, position): workgroup w owns
-// the ids whose low byte is w (low five or six bits, 32 or 64 workgroups, for a table of at most SMALL_FEW or SMALL_MID ids: lists of
-// 64 to 128 ids on average, so that an even spread never reaches the long-list path; with 32 workgroups for 8,192 ids half of the lists
-// did: 17.5 us against 8.0).  Two workgroups share
-// a compute unit (66 KB of LDS, 64 registers), so that the workgroups of a step's entity and relation table, 256 and 32
-// or 64, run in one turn (with the LDS of a whole compute unit each, those past the 256th waited for a second turn: 18-20 us
-// instead of 14-18).  It reads ALL ids (a few tens of KB, from L2), counts those of lower workgroups (its place in the
+// the ids whose low five, six, seven or eight bits are w (small_parts), lists of 48 to 128 ids on average, so that an even spread never
+// reaches the long-list path (with 32 workgroups for 8,192 ids half of the lists did: 17.5 us against 8.0).  At most two workgroups share
+// a compute unit (66 KB of LDS, 64 registers), so that all of a step's tables run in one turn (with the LDS of a whole compute unit each,
+// those past the 256th waited for a second turn: 18-20 us instead of 14-18).
+// A workgroup reads ALL ids (a few tens of KB, from L2), counts those of lower workgroups (its place in the
 // output) and collects its own in position order; then it orders its list by the remaining bits, stable: a list
 // of up to 256 entries by counting, for every entry, the entries that come before it (four threads per entry); a longer
 // one (one id repeated thousands of times) after its dominant id has been split off, or, if what remains is still longer,
 // by counting passes of four bits; the list lies in LDS, or in the second pair of output buffers when it is longer than
 // SMALL_CAP.  No workgroup waits for another; several tables go into one launch (workgroup ranges).
-// What bounds it is instruction issue of sixteen waves on a compute unit, not the reading: 20,480 ids cost 5.4 us to read and count, 5
-// to collect before the elements without own ids were passed over by a scalar mask, 5 more where a hot id made a list long (every wave
-// counted all 64 candidates; now each counts four).  Alone 15.6 -> 11.8 us (Zipf ids), 2,048 ids 9.7 -> 7.0, with two tables of 8,192
-// relation ids 21.0 -> 14.2.
+// What bounds it is instruction issue of sixteen waves on a compute unit, not the reading (20,480 ids: 5.4 us to read and count, where
+// that took eight vector and ten scalar instructions an id).  Hence: the id rotated by its selecting bits makes "own" and "lower" one
+// comparison each; the ballots of the count stay for the collection, which passes over elements without own ids; (other bits, place in
+// the list) in one word makes ranking one comparison per pair; of the candidates for a hot id each wave counts four.  In a graph of
+// launches, before / here: 24,576 ids 10.1 / 8.4 us, with Zipf ids and a relation table of 4,096 13.0 / 10.4; 8,192 8.2 / 6.5; 2,048 +
+// 512 7.4 / 5.8; 20,480 Zipf ids and two tables of 8,192 16.8 / 13.8; one id 24,576 times 25.4 / 26.2.  Steps, where a third of the launch
+// is cold memory, gain 0.5-1.5 %.
 // ---------------------------------------------------------------------------------------------
 constexpr int SMALL_MAX = 32768;
 constexpr int SMALL_CAP = 3072;                             // longest list that is ordered in LDS
@@ -240,14 +242,19 @@ constexpr int SMALL_DIRECT = 256;                           // longest list that
 constexpr int SMALL_PT = 256;                               // threads that take part in a counting pass (a rare path: its
                                                             // counters are kept small so that two workgroups share a compute unit)
 constexpr int SMALL_TABLES = 4;
-constexpr int SMALL_FEW = 2048, SMALL_MID = 8192;          // a table of at most so many ids is cut into 32, 64 parts, not 256
+constexpr int SMALL_FEW = 2048, SMALL_MID = 8192, SMALL_MANY = 12288;   // a table of at most so many ids is cut into 32, 64, 128 parts, not 256
 __host__ __device__ constexpr int small_cnt_at(int f) { return f + (f >> 4); }     // one pad word per 16: strided reads spread over banks
 
 struct SmallSort { const int32_t *idx; int M, bits, lb; uint32_t *ka, *kb, *pa, *pb; };   // bits: of the largest id; lb: of the id that select the workgroup
 // the low bits that select a table's workgroup (a function of the table alone: the order of the sorted ids, and with it
 // the association order of the sums, must not depend on what else is in the launch)
-static void small_parts(const int *ms, int n, int *lb) {
-    for (int k = 0; k < n; ++k) lb[k] = ms[k] <= SMALL_FEW ? 5 : ms[k] <= SMALL_MID ? 6 : 8;
+// Of 8,193 to 12,288 ids 128 parts are slower alone (12,288: 6.7 us against 6.5 with 256) and faster beside a relation table, as a step
+// plans them (TransE step 2,048 x 8,192 143.5 / 144.6, RotatE 4,096 x 4,096 147.2 / 147.4); of 20,480 slower in a step too, where all of
+// memory is cold and two workgroups per unit wait for it together (TransH 8,192 x 4,096 339.6 / 336.6).  At most 24 bits are left, for a
+// list's words.
+static int small_parts(int m, int bits) {
+    const int lb = m <= SMALL_FEW ? 5 : m <= SMALL_MID ? 6 : m <= SMALL_MANY ? 7 : 8;
+    return lb > bits - 24 ? lb : bits - 24;
 }
 struct SmallSorts { SmallSort t[SMALL_TABLES]; };
 
@@ -331,16 +338,14 @@ __device__ __forceinline__ bool small_pass_trivial(const uint32_t *sk, const uin
     return true;
 }
 
-// The place of entry e (its id: key) in a list of n <= SMALL_DIRECT: the entries with a smaller id, and those with the same id that
-// come before it.  The four threads of an entry (tid / 4) count sixteen entries a step between them and add up; all return the sum.
-__device__ __forceinline__ int small_rank(const uint32_t *list, uint32_t key, int e, int n) {
+// The place of an entry (its word: small_word) in a list of n <= SMALL_DIRECT words, no two of them alike: the words below it.  The four
+// threads of an entry (tid / 4) count sixteen words a step between them and add up; all return the sum.  Words from n up to the next
+// multiple of sixteen are 0xffffffff.
+__device__ __forceinline__ int small_rank(const uint32_t *list, uint32_t word, int n) {
     int rank = 0;
-    const int sub = 4 * (threadIdx.x & 3);
-    for (int j0 = 0; j0 < n; j0 += 16) {
-        const int j = j0 + sub;
-        const uint4 k4 = *(const uint4 *)&list[j];         // (j < SMALL_DIRECT: inside the list's array, entries from n on are not counted)
-        rank += (j < n && (k4.x < key || (k4.x == key && j < e))) + (j + 1 < n && (k4.y < key || (k4.y == key && j + 1 < e))) +
-                (j + 2 < n && (k4.z < key || (k4.z == key && j + 2 < e))) + (j + 3 < n && (k4.w < key || (k4.w == key && j + 3 < e)));
+    for (int j = 4 * (threadIdx.x & 3); j < n; j += 16) {
+        const uint4 k4 = *(const uint4 *)&list[j];
+        rank += (k4.x < word) + (k4.y < word) + (k4.z < word) + (k4.w < word);
     }
     rank += __shfl_xor(rank, 1);
     return rank + __shfl_xor(rank, 2);
@@ -369,7 +374,6 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
     const int M = S.M;
     const int lb = S.lb;                                   // bits of the id that select the workgroup
     const int passes = S.bits > lb ? (S.bits - lb + 3) / 4 : 0;
-    const uint32_t lmask = (1u << lb) - 1u;
     uint32_t *ka = S.ka, *kb = S.kb, *pa = S.pa, *pb = S.pb;
     const int w = wg - first;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -381,7 +385,7 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
 #pragma unroll
     for (int r = 0; r < SMALL_ROUNDS; ++r) {
         const int i = 4 * (r * SMALL_NT + tid);
-        id[r] = make_uint4(0u, 0u, 0u, 0u);
+        id[r] = make_uint4(~0u, ~0u, ~0u, ~0u);             // (no id: below no workgroup's and in none's range)
         if (r < rounds) {
             if (vec && i + 3 < M) id[r] = *(const uint4 *)(idx + i);
             else {
@@ -394,23 +398,20 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
     }
     const uint64_t below = (1ull << lane) - 1ull;
     uint32_t lower = 0;                                    // ids of lower workgroups seen by this thread
-    uint32_t any = 0;                                      // bit 4 r + j: the wave holds own ids in element j of round r (uniform)
-    static_assert(4 * SMALL_ROUNDS <= 32, "a bit per element");
+    // rotated by lb bits a workgroup's ids are one range (the last value of which is no id)
+    const uint32_t k_lo = (uint32_t)w << (32 - lb), k_span = (1u << (32 - lb)) - 1u;
+    uint64_t o[SMALL_ROUNDS][4];                           // the wave's own ids in element j of round r
 #pragma unroll
     for (int r = 0; r < SMALL_ROUNDS; ++r) {
         if (r < rounds) {
-            const int i = 4 * (r * SMALL_NT + tid);
             const uint32_t e[4] = { id[r].x, id[r].y, id[r].z, id[r].w };
-            uint32_t own = 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const bool in = i + j < M;
-                lower += in && (int)(e[j] & lmask) < w;
-                const uint64_t o = __ballot(in && (int)(e[j] & lmask) == w);
-                own += (uint32_t)__builtin_popcountll(o);
-                any |= (o != 0 ? 1u : 0u) << (4 * r + j);
+                const uint32_t k = __builtin_amdgcn_alignbit(e[j], e[j], lb);
+                lower += k < k_lo;
+                o[r][j] = __ballot(k - k_lo < k_span);
             }
-            if (lane == 0) s_rc[r * (SMALL_NT / 64) + wave] = own;
+            if (lane == 0) s_rc[r * (SMALL_NT / 64) + wave] = __builtin_popcountll(o[r][0]) + __builtin_popcountll(o[r][1]) + __builtin_popcountll(o[r][2]) + __builtin_popcountll(o[r][3]);
         }
     }
     __syncthreads();
@@ -436,16 +437,15 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
             const int i = 4 * (r * SMALL_NT + tid);
             const uint32_t e[4] = { id[r].x, id[r].y, id[r].z, id[r].w };
             // (a group of 256 ids holds one of the workgroup's on average: most of the elements, and a third of the groups, none)
-            if ((any >> (4 * r) & 15u) == 0) continue;
+            if ((o[r][0] | o[r][1] | o[r][2] | o[r][3]) == 0) continue;
             uint32_t at = s_rc[r * (SMALL_NT / 64) + wave];    // plus the own ids of lower lanes in this round
             bool mine[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 mine[j] = false;
-                if ((any >> (4 * r + j) & 1u) == 0) continue;
-                mine[j] = i + j < M && (int)(e[j] & lmask) == w;
-                const uint64_t o = __ballot(mine[j]);
-                at = __builtin_amdgcn_mbcnt_hi((uint32_t)(o >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)o, at));
+                if (o[r][j] == 0) continue;
+                mine[j] = o[r][j] >> lane & 1;
+                at = __builtin_amdgcn_mbcnt_hi((uint32_t)(o[r][j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)o[r][j], at));
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -454,13 +454,15 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
     }
     __syncthreads();
     if (passes == 0) return;
+    auto word = [&](uint32_t key, int e) { return (key >> lb) * SMALL_DIRECT + (uint32_t)e; };      // (lb: small_parts)
     if (n <= SMALL_DIRECT) {
         // the place of entry e: the entries with a smaller id, and those with the same id that come before it
+        if (tid < SMALL_DIRECT) s_key[1][tid] = tid < n ? word(s_key[0][tid], tid) : 0xffffffffu;
+        __syncthreads();
         const int e = tid >> 2;
         if (e < n) {
-            const uint32_t key = s_key[0][e];
-            const int rank = small_rank(s_key[0], key, e, n);
-            if ((tid & 3) == 0) { ka[base + rank] = key; pa[base + rank] = s_pos[0][e]; }
+            const int rank = small_rank(s_key[1], s_key[1][e], n);
+            if ((tid & 3) == 0) { ka[base + rank] = s_key[0][e]; pa[base + rank] = s_pos[0][e]; }
         }
     } else {
         // A long list is usually ONE id repeated (Zipf's hottest rows): the entries with that id keep their order as one
@@ -524,18 +526,19 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
                     const uint64_t mc = __ballot(is_cold);
                     const int mine_at = ci + __builtin_popcountll(mc & below);          // cold entries before this one
                     if (e < whi) {
-                        if (is_cold) { s_key[1][mine_at] = k[u]; s_pos[1][mine_at] = q[u]; }
+                        if (is_cold) { s_key[1][mine_at] = word(k[u], mine_at); s_pos[1][mine_at] = q[u]; }
                         else { const int at = base + n_less + e - mine_at; ka[at] = hot; pa[at] = q[u]; }
                     }
                     ci += __builtin_popcountll(mc);
                 }
             }
-            __syncthreads();
             const int nc = n_cold, n_hot = n - nc;
+            if (tid < 16 && nc + tid < SMALL_DIRECT) s_key[1][nc + tid] = 0xffffffffu;
+            __syncthreads();
             const int e = tid >> 2;
             if (e < nc) {
-                const uint32_t key = s_key[1][e];
-                const int to = base + small_rank(s_key[1], key, e, nc) + (key > hot ? n_hot : 0);
+                const uint32_t mine_w = s_key[1][e], key = mine_w / SMALL_DIRECT << lb | (uint32_t)w;
+                const int to = base + small_rank(s_key[1], mine_w, nc) + (key > hot ? n_hot : 0);
                 if ((tid & 3) == 0) { ka[to] = key; pa[to] = s_pos[1][e]; }
             }
             return;
@@ -884,10 +887,8 @@ int kge_sort_pairs(const int32_t *idx, const int32_t *h, const int32_t *t, int64
     while (bits < 32 && (1ll << bits) < key_range) ++bits;
     if (sort_is_small(idx != nullptr, M)) {
         SmallSorts T = {};
-        const int m1 = (int)M;
-        int lb1;
-        small_parts(&m1, 1, &lb1);
-        T.t[0] = SmallSort{idx, m1, bits, lb1, s.ka, s.kb, s.pa, s.pb};
+        const int lb1 = small_parts((int)M, bits);
+        T.t[0] = SmallSort{idx, (int)M, bits, lb1, s.ka, s.kb, s.pa, s.pb};
         hipLaunchKernelGGL(sort_small_kernel, dim3(1 << lb1), dim3(SMALL_NT), 0, st, T);
         *sk = s.ka; *sp = s.pa;
         return kge_launch_status();
@@ -942,7 +943,7 @@ int kge_run_sparse_adam_plan_tables(const kge_adam_plan_t *pl, int n, hipStream_
             sort_carve(pl[k].M, 0, ws, s);
             int bits = 1;
             while (bits < 32 && (1ll << bits) < pl[k].n_rows) ++bits;
-            T.t[small++] = SmallSort{pl[k].idx, (int)pl[k].M, bits, 0, s.ka, s.kb, s.pa, s.pb};
+            T.t[small++] = SmallSort{pl[k].idx, (int)pl[k].M, bits, small_parts((int)pl[k].M, bits), s.ka, s.kb, s.pa, s.pb};
         } else {
             const uint32_t *sk, *sp;
             const int rc = kge_sort_pairs(pl[k].idx, nullptr, nullptr, 1, 1, pl[k].M, pl[k].n_rows, ws, &sk, &sp, st, nullptr, 0);
@@ -950,10 +951,7 @@ int kge_run_sparse_adam_plan_tables(const kge_adam_plan_t *pl, int n, hipStream_
         }
     }
     if (small > 0) {
-        int ms[SMALL_TABLES], lb[SMALL_TABLES];
-        for (int k = 0; k < small; ++k) ms[k] = T.t[k].M;
-        small_parts(ms, small, lb);
-        for (int k = 0; k < small; ++k) { T.t[k].lb = lb[k]; nwg += 1 << lb[k]; }
+        for (int k = 0; k < small; ++k) nwg += 1 << T.t[k].lb;
         if (!rf && !sr) hipLaunchKernelGGL(sort_small_kernel, dim3(nwg), dim3(SMALL_NT), 0, st, T);
     }
     if (sr && small > 0) {

@@ -115,11 +115,11 @@ def test_long_runs_of_equal_ids(orc, runs):
     assert norm_err(gm[touched], rm[touched]) <= RTOL_F32 and norm_err(gv[touched], rv[touched]) <= RTOL_F32
 
 
-@pytest.mark.parametrize("bits,M", [(5, 2048), (6, 2049), (6, 8192), (8, 8193), (8, 32768)])
+@pytest.mark.parametrize("bits,M", [(5, 2048), (6, 2049), (6, 8192), (7, 8193), (8, 8193), (7, 12288), (8, 12289), (8, 32768)])
 @pytest.mark.parametrize("n_rows", [3000, 1 << 18])
 @pytest.mark.parametrize("own,hot", [(1, 0), (255, 0), (256, 0), (257, 0), (257, 1), (257, 2), (1023, 0), (1023, 766), (1023, 767), (1023, 1023)])
 def test_lists_at_the_edges_of_the_one_launch_sort(orc, bits, M, n_rows, own, hot):
-    """Tables on both sides of the lines between 32, 64 and 256 workgroups (the low bits that select one), with ONE workgroup's list at
+    """Tables on both sides of the lines between 32, 64, 128 and 256 workgroups (the low bits that select one), with ONE workgroup's list at
     the lengths where a list is ordered otherwise (256 entries), and long lists whose most frequent id leaves 256 others, one more, all or
     none; with more bits of the id left to order by, and a gradient of its own for every position, so that a position that goes with
     another id shows."""
@@ -141,6 +141,27 @@ def test_lists_at_the_edges_of_the_one_launch_sort(orc, bits, M, n_rows, own, ho
     assert np.array_equal(gth[~touched], theta[~touched])
     assert update_err_ok(gth[touched], theta[touched], rth[touched])
     assert norm_err(gm[touched], rm[touched]) <= RTOL_F32 and norm_err(gv[touched], rv[touched]) <= RTOL_F32
+
+
+@pytest.mark.parametrize("n_rows", [1 << 29, (1 << 29) + 1, (1 << 30) + 1, (1 << 31) - 1])
+@pytest.mark.parametrize("M", [1, 4095, 4096, 8192, 32767])
+def test_order_of_the_largest_ids(n_rows, M):
+    """Ids of up to 31 bits, whose words (other bits of the id, place in the list) just fit 32: the sorted pairs group equal ids, each
+    group in position order."""
+    import paper_2211_12281_amd as kge
+    g = np.random.default_rng(M)
+    pool = np.unique(np.concatenate([n_rows - 1 - g.integers(0, 1 << 13, M // 2 + 1), g.integers(0, n_rows, M // 2 + 1)]))
+    idx = g.choice(pool, M).astype(np.int32)
+    idx[: M // 8] = n_rows - 1
+    ws = kge.Workspace()
+    kge.sparse_adam_plan(n_rows, 8, torch.from_numpy(idx).cuda(), ws)
+    words = ws.get(0).cpu().numpy()
+    off = -ws.get(0).data_ptr() % 256
+    pad = (4 * M + 255) // 256 * 256
+    keys, pos = words[off:off + 4 * M].view(np.uint32), words[off + 2 * pad:off + 2 * pad + 4 * M].view(np.uint32)
+    assert np.array_equal(np.sort(pos), np.arange(M)) and np.array_equal(keys, idx[pos].astype(np.uint32))
+    new = np.concatenate([[True], keys[1:] != keys[:-1]])
+    assert new.sum() == len(np.unique(idx)) and np.all(new[1:] | (pos[1:] > pos[:-1]))
 
 
 @pytest.mark.parametrize("n_rows,runs", [(200, [(17, 6000), (5, 3000), (199, 3100)]), (32, [(31, 4000), (3, 9)]), (11, [(4, 9000), (0, 4)]),
