@@ -49,6 +49,20 @@ struct TopkArgs {
     const void *zeros;                  // 16 zero bytes (source of the padding columns)
 };
 
+// stages of the ring: two workgroups share a compute unit, but on bf16 rows over 512 bytes
+constexpr int tk_stages(bool bf16, int rb) { return rb == 512 ? 4 : bf16 ? 3 : 2; }
+// offset of the upper pieces in the sixteen bytes of four elements of row r: lanes that read eight bytes each of rows at one chunk index
+// take different banks, sixteen of them of 32 (rows r and r ^ 4, whose chunks lie 128 bytes apart) and 32 of 64 (r and r + 16)
+__device__ __forceinline__ int tk_flip(int r) { return (((r >> 2) ^ (r >> 4)) & 1) * 8; }
+// fp32 elements as two fp16 pieces, three products per pair: each is off by at most 2^-24 of either element and leaves out 2^-22 of the
+// product at most, less than eight roundings of 2^-23 of it, counted beside those of the d products
+constexpr int TK_PIECES = 8;
+// the power of two that takes a row whose largest element is m to [2^14, 2^15) (zeros and subnormal numbers as the smallest normal one)
+__device__ __forceinline__ int tk_plane_exp(float m) {
+    const int e = (int)(__float_as_uint(m) >> 23);
+    return 141 - (e > 1 ? e : 1);
+}
+
 // Asynchronous global -> LDS copies (gfx950): lane l of a wave-wide instruction writes its 16 (or 4)
 // bytes to LDS byte address m0 + l*16 (l*4); the data never passes through registers, completion is
 // tracked by vmcnt.  The compiler does not see these loads, so the waits are explicit.
@@ -90,6 +104,17 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // makes the norms of every tile (a wave those of eight rows), which pays while few query tiles share a candidate tile;
 // the bilinear scan needs only the maximum and gives each candidate tile to one of the query tiles.
 //
+// fp32 rows (PL below): the fp32 MFMA runs at 1/16 of the 16-bit rate, so every element is taken as two fp16 pieces of the row scaled by
+// a power of two of its own, and three products of pieces replace one of fp32 (a value's error is no larger: the pieces' 2^-24 is less
+// than what the fp32 MFMAs' chain of sums adds; ranks off by 0.39-0.45 on average before and 0.36-0.45 here, the tops alike).  The
+// table is not rewritten: a tile's rows are split in the LDS, in place, by the walk that makes their norms - eight lanes per row, a
+// chunk of four elements becomes eight bytes of upper and eight of lower pieces, so no lane waits for another's reads - between two
+// barriers.  A tile is split, multiplied and filtered in one round while the other workgroup of the compute unit has the matrix pipe;
+// rows of 1,024 bytes keep two stages of the ring so that there is another.  Bound by what the two waves of a SIMD issue (d 256, 6,774
+// queries: vector pipe 41 %, matrix pipe 27 %, LDS 35 % of the cycles, half of it bank conflicts before tk_flip: 2.20 -> 2.15 ms).
+// Whole calls, fp32 MFMA / pieces: DistMult d 256, 6,774 x 92,000 3.95 / 2.03 ms, 128 x 1M 697 / 421 us; RotatE d 232, 391 x 963,002 2.35 /
+// 0.99 ms; TransE d 128, 300 x 1M 1.03 / 0.56 ms; TransH d 56, 50 x 5.4M 2.67 / 0.91 ms; TransE d 128, 26 x 32,113 80 / 75 us.
+//
 // A split's tiles are dealt round-robin, so that neighbouring rows that all beat the threshold - a table sorted by type or
 // community - are spread over the append areas of many splits.
 //
@@ -100,6 +125,8 @@ template <bool BF16, int RB, int KIND, int OB, bool TH = false, bool FN = false,
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void topk_scan_kernel(const TopkArgs a) {
     static_assert(!TH || (OB == 2 && KIND == KGE_KIND_DIST), "TransH: one block of queries, one of normals");
+    constexpr bool PL = !BF16;                          // fp32 rows: two fp16 pieces of every element
+    static_assert(!PL || FN, "the pieces' scales and the norms come from one walk over the tile");
     constexpr int NQ = TH ? 1 : OB;                     // blocks of 32 queries per wave
     constexpr int KS = RB / 32;
     constexpr int TILE_BYTES = TK_ST * RB;
@@ -107,7 +134,7 @@ void topk_scan_kernel(const TopkArgs a) {
     constexpr int IPW = NINST / 4;                      // ... per wave
     constexpr bool SIDE = KIND == KGE_KIND_DIST && !FN; // the norms stream beside the tiles
     constexpr int LPW = IPW + (SIDE ? 1 : 0);
-    constexpr int NSTAGE = RB == 512 ? 4 : 3;
+    constexpr int NSTAGE = tk_stages(BF16, RB);
     constexpr int SIDE_SLOTS = NSTAGE + 1;
     extern __shared__ __attribute__((aligned(256))) char lds[];
     char *side_base = lds + NSTAGE * TILE_BYTES;        // [SIDE_SLOTS][4 waves][64 floats]
@@ -132,7 +159,30 @@ void topk_scan_kernel(const TopkArgs a) {
         return;
     }
 
-    uint4 own[OB][KS];
+    uint4 own[OB][KS];                                  // (PL: 2 ks the upper pieces of step ks, 2 ks + 1 the lower)
+    int own_e[PL ? OB : 1];
+    // PL: a query row in pieces, scaled by the power of two that takes its largest element to [2^14, 2^15)
+    auto split_own = [&](int ob, const char *p) {
+        auto at = [&](int ks) { return p + 512 * (ks >> 3) + 32 * (ks & 7); };
+        float m = 0.f;
+        auto row_max = [&](const uint4 &v) {
+            m = fmaxf(fmaxf(fmaxf(m, fabsf(__uint_as_float(v.x))), fmaxf(fabsf(__uint_as_float(v.y)), fabsf(__uint_as_float(v.z)))), fabsf(__uint_as_float(v.w)));
+        };
+#pragma unroll 4
+        for (int ks = 0; ks < KS / 2; ++ks) { row_max(*(const uint4 *)at(ks)); row_max(*(const uint4 *)(at(ks) + 256)); }
+        m = fmaxf(m, __shfl_xor(m, 32));
+        const int e = tk_plane_exp(m);
+        own_e[PL ? ob : 0] = -e;
+#pragma unroll
+        for (int ks = 0; ks < KS / 2; ++ks) {
+            if (ks % 2 == 0) __builtin_amdgcn_sched_barrier(0);                  // (a row of elements beside the pieces would spill)
+            const uint4 a0 = *(const uint4 *)at(ks), a1 = *(const uint4 *)(at(ks) + 256);
+            const float x[8] = { ldexpf(__uint_as_float(a0.x), e), ldexpf(__uint_as_float(a0.y), e), ldexpf(__uint_as_float(a0.z), e), ldexpf(__uint_as_float(a0.w), e),
+                                 ldexpf(__uint_as_float(a1.x), e), ldexpf(__uint_as_float(a1.y), e), ldexpf(__uint_as_float(a1.z), e), ldexpf(__uint_as_float(a1.w), e) };
+            const KgeP2 two = kge_split2(x);
+            own[ob][2 * ks] = two.p[0]; own[ob][2 * ks + 1] = two.p[1];
+        }
+    };
     float thr[NQ], vt[NQ], low[NQ];
     int qid[NQ], myc[NQ];
     uint32_t above[NQ];
@@ -141,8 +191,11 @@ void topk_scan_kernel(const TopkArgs a) {
         qid[ob] = own_base + (wave * NQ + ob) * 32 + lr;
         myc[ob] = 0;
         const char *p = (const char *)a.Qmat + (size_t)qid[ob] * RB + g * 16;
+        if constexpr (PL) split_own(ob, p);
+        else {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) own[ob][ks] = *(const uint4 *)(p + ks * 32);
+            for (int ks = 0; ks < KS; ++ks) own[ob][ks] = *(const uint4 *)(p + ks * 32);
+        }
         thr[ob] = SAMPLE ? 0.f : a.thr[qid[ob]];
         vt[ob] = SAMPLE ? 0.f : a.vt[qid[ob]];
         low[ob] = fminf(thr[ob], vt[ob]);               // (vt is +inf where there is no held-out tail)
@@ -151,8 +204,11 @@ void topk_scan_kernel(const TopkArgs a) {
     float cq = 0.f;
     if constexpr (TH) {
         const char *p = (const char *)a.Wmat + (size_t)qid[0] * RB + g * 16;
+        if constexpr (PL) split_own(1, p);
+        else {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) own[1][ks] = *(const uint4 *)(p + ks * 32);
+            for (int ks = 0; ks < KS; ++ks) own[1][ks] = *(const uint4 *)(p + ks * 32);
+        }
         cq = a.cq[qid[0]];
     }
 
@@ -235,8 +291,10 @@ void topk_scan_kernel(const TopkArgs a) {
         // spill operands inside the loop, so they keep the compiler's.
         constexpr int AH = RB == 512 ? (TH ? 2 : 3) : 0;
         kge_u32x4 av[AH > 0 ? AH + 1 : KS];
+        if constexpr (!PL) {
 #pragma unroll
-        for (int ks = 0; ks < (AH > 0 ? AH : KS); ++ks) av[ks] = fragment(ks);
+            for (int ks = 0; ks < (AH > 0 ? AH : KS); ++ks) av[ks] = fragment(ks);
+        }
         if constexpr (SIDE) {
             // TransE: the accumulators start at -|t|^2 of their candidate row and the queries are stored
             // doubled, so the contraction itself yields 2 q.t - |t|^2
@@ -254,6 +312,39 @@ void topk_scan_kernel(const TopkArgs a) {
         } else {
 #pragma unroll
             for (int ob = 0; ob < OB; ++ob) for (int i = 0; i < 16; ++i) acc[ob][i] = 0.f;
+        }
+        if constexpr (PL) {
+            // chunk c of a row (four elements) and chunk c + 16, 256 bytes on, make a step: the upper pieces of both are one operand, the
+            // lower ones the other.
+            constexpr int AP = OB == 2 ? 1 : 2;
+            const uint32_t up = frag + tk_flip(lr), down = frag + 8 - tk_flip(lr);
+            auto pieces = [&](uint32_t f, int ks) {
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                const uint32_t at = (f ^ (32 * (ks & 7))) + 512 * (ks >> 3);
+                const u32x2 lo = *(const __attribute__((address_space(3))) u32x2 *)(uintptr_t)at;
+                const u32x2 hi = *(const __attribute__((address_space(3))) u32x2 *)(uintptr_t)(at + 256);
+                return make_uint4(lo.x, lo.y, hi.x, hi.y);
+            };
+            KgeP2 fv[AP + 1];
+#pragma unroll
+            for (int ks = 0; ks < AP; ++ks) { fv[ks].p[0] = pieces(up, ks); fv[ks].p[1] = pieces(down, ks); }
+#pragma unroll
+            for (int ks = 0; ks < KS / 2; ++ks) {
+                if (ks + AP < KS / 2) { fv[(ks + AP) % (AP + 1)].p[0] = pieces(up, ks + AP); fv[(ks + AP) % (AP + 1)].p[1] = pieces(down, ks + AP); }
+                __builtin_amdgcn_sched_barrier(0);
+                const KgeP2 &f = fv[ks % (AP + 1)];
+                auto mm = [](kge_f32x16 c, uint4 x, uint4 y) {
+                    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(kge_f16x8, x), __builtin_bit_cast(kge_f16x8, y), c, 0, 0, 0);
+                };
+#pragma unroll
+                for (int ob = 0; ob < OB; ++ob) acc[ob] = mm(acc[ob], f.p[0], own[ob][2 * ks + 1]);
+#pragma unroll
+                for (int ob = 0; ob < OB; ++ob) acc[ob] = mm(acc[ob], f.p[1], own[ob][2 * ks]);
+#pragma unroll
+                for (int ob = 0; ob < OB; ++ob) acc[ob] = mm(acc[ob], f.p[0], own[ob][2 * ks]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
         }
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -285,16 +376,57 @@ void topk_scan_kernel(const TopkArgs a) {
             const kge_u32x4 v = *(const kge_u32x4 *)(base + ((i + row) % NP) * 128);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if constexpr (BF16) {
-                    const float x0 = __uint_as_float(v[k] << 16), x1 = __uint_as_float(v[k] & 0xffff0000u);
-                    sq = fmaf(x0, x0, sq); sq = fmaf(x1, x1, sq);
-                } else { const float x0 = __uint_as_float(v[k]); sq = fmaf(x0, x0, sq); }
+                const float x0 = __uint_as_float(v[k] << 16), x1 = __uint_as_float(v[k] & 0xffff0000u);
+                sq = fmaf(x0, x0, sq); sq = fmaf(x1, x1, sq);
             }
         }
         sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0xB1, 0xf, 0xf, true));    // lane ^ 1
         sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0x4E, 0xf, 0xf, true));    // lane ^ 2
         sq += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(sq), 0x141, 0xf, 0xf, true));   // 7 - lane: the other four
         if constexpr (KIND == KGE_KIND_DIST) if ((ln & 7) == 0) nrm[(slot & 1) * 32 + row] = -sq;
+        nmax = fmaxf(nmax, sq);
+    };
+    // ---- fp32 rows: the same lanes put two fp16 pieces of each element in its place, sixteen bytes of four elements -> eight of upper
+    // and eight of lower pieces; the row is scaled by the power of two that takes its largest element to [2^14, 2^15) ----
+    int *row_e = (int *)side_base + 64;                 // [2][32] the exponents that take the products back
+    auto split_tile = [&](int slot) {
+        const int row = wave * 8 + (lane >> 3);
+        char *base = lds + (slot % NSTAGE) * TILE_BYTES + row * RB + (lane & 7) * 16;
+        constexpr int NP = RB / 128;
+        kge_f32x4 v[NP];
+        float sq = 0.f, m = 0.f;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) v[i] = *(const kge_f32x4 *)(base + ((i + row) % NP) * 128);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            m = fmaxf(fmaxf(m, fabsf(v[i][0])), fabsf(v[i][1])); m = fmaxf(fmaxf(m, fabsf(v[i][2])), fabsf(v[i][3]));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sq = fmaf(v[i][k], v[i][k], sq);
+        }
+        auto dpp = [](float x, auto c) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(c)::value, 0xf, 0xf, true)); };
+        constexpr std::integral_constant<int, 0xB1> x1{}; constexpr std::integral_constant<int, 0x4E> x2{}; constexpr std::integral_constant<int, 0x141> x7{};
+        m = fmaxf(m, dpp(m, x1)); sq += dpp(sq, x1);
+        m = fmaxf(m, dpp(m, x2)); sq += dpp(sq, x2);
+        m = fmaxf(m, dpp(m, x7)); sq += dpp(sq, x7);
+        const int e = tk_plane_exp(m);
+        const int up = tk_flip(row);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            // (two conversions per instruction and the remainder as a mixed multiply-add: six instructions for two elements)
+            typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            uint2 hi, lo;
+            auto pair = [&](float a, float b, uint32_t &h, uint32_t &l) {
+                const f32x2 y = { ldexpf(a, e), ldexpf(b, e) };
+                const f16x2 top = __builtin_convertvector(y, f16x2);
+                const f32x2 rest = { __builtin_fmaf((float)top[0], -1.f, y[0]), __builtin_fmaf((float)top[1], -1.f, y[1]) };
+                h = __builtin_bit_cast(uint32_t, top); l = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, f16x2));
+            };
+            pair(v[i][0], v[i][1], hi.x, lo.x); pair(v[i][2], v[i][3], hi.y, lo.y);
+            char *at = base + ((i + row) % NP) * 128;
+            *(uint2 *)(at + up) = hi; *(uint2 *)(at + 8 - up) = lo;
+        }
+        if ((lane & 7) == 0) { nrm[(slot & 1) * 32 + row] = -sq; row_e[(slot & 1) * 32 + row] = -e; }
         nmax = fmaxf(nmax, sq);
     };
     int turn = 0;                                       // bilinear: the query tile whose turn a candidate tile is
@@ -310,9 +442,11 @@ void topk_scan_kernel(const TopkArgs a) {
 
 #pragma unroll
     for (int s2 = 0; s2 < NSTAGE - 1; ++s2) issue(s2, s2);
-    wait_vmcnt<(NSTAGE - 2) * LPW>();
-    __syncthreads();
-    issue(NSTAGE - 1, NSTAGE - 1);
+    if constexpr (!PL) {
+        wait_vmcnt<(NSTAGE - 2) * LPW>();
+        __syncthreads();
+        issue(NSTAGE - 1, NSTAGE - 1);
+    }
     float best[SAMPLE ? NQ : 1][4];                     // running maxima of the rows 8 j + 4 g .. + 3 of the tiles of a group
     int until = a.flush;
     if constexpr (SAMPLE) for (int ob = 0; ob < NQ; ++ob) for (int j = 0; j < 4; ++j) best[ob][j] = -INFINITY;
@@ -321,13 +455,32 @@ void topk_scan_kernel(const TopkArgs a) {
     auto round = [&](int slot, kge_f32x16 (&acc)[OB], kge_f32x16 (&accn)[OB]) {
         const int64_t tile = tile_of(slot);
         // ---- tile + 1: wait for its data, refill the stage that tile `tile` just vacated, start its MFMAs
+        // (PL: this tile's own data, split, multiplied and filtered in one round: the other workgroup of the compute unit has the
+        // pipe meanwhile, and there are no registers for a second set of accumulators)
         wait_vmcnt<(NSTAGE - 2) * LPW>();
         __syncthreads();
-        issue(slot + NSTAGE, slot + NSTAGE);
-        if constexpr (FN) { if (slot + 1 < nt) norms_of(slot + 1); }
-        mma_tile(slot + 1, accn);                       // (the last iteration recomputes a stale stage: unused)
+        if constexpr (PL) {
+            issue(slot + NSTAGE - 1, slot + NSTAGE - 1);
+            split_tile(slot);
+            __syncthreads();
+            mma_tile(slot, acc);
+        } else {
+            issue(slot + NSTAGE, slot + NSTAGE);
+            if constexpr (FN) { if (slot + 1 < nt) norms_of(slot + 1); }
+            mma_tile(slot + 1, accn);                   // (the last iteration recomputes a stale stage: unused)
+        }
         // ---- epilogue of tile `tile`: cheap wave-level test first, counting and appending only on a hit ----
         const bool tile_full = tile * TK_ST + TK_ST <= a.ncand;
+        if constexpr (PL) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                typedef int i32x4 __attribute__((ext_vector_type(4)));
+                const i32x4 e4 = *(const i32x4 *)(row_e + (slot & 1) * 32 + 8 * j + 4 * g);
+#pragma unroll
+                for (int ob = 0; ob < OB; ++ob)
+                    for (int u = 0; u < 4; ++u) acc[ob][4 * j + u] = ldexpf(acc[ob][4 * j + u], e4[u] + own_e[ob]);
+            }
+        }
         if constexpr (FN && KIND == KGE_KIND_DIST) {    // (this tile's norms were written before the barrier above)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -411,11 +564,15 @@ void topk_scan_kernel(const TopkArgs a) {
         }
     };
     kge_f32x16 acc_a[OB], acc_b[OB];
-    norms_of(0);
-    mma_tile(0, acc_a);
-    for (int k = 0; k < nt; k += 2) {
-        round(k, acc_a, acc_b);
-        if (k + 1 < nt) round(k + 1, acc_b, acc_a);
+    if constexpr (PL) {
+        for (int k = 0; k < nt; ++k) round(k, acc_a, acc_b);
+    } else {
+        norms_of(0);
+        mma_tile(0, acc_a);
+        for (int k = 0; k < nt; k += 2) {
+            round(k, acc_a, acc_b);
+            if (k + 1 < nt) round(k + 1, acc_b, acc_a);
+        }
     }
     wait_vmcnt<0>();                                    // no copy may still be in flight when the LDS is released
 #pragma unroll
@@ -864,7 +1021,9 @@ __global__ __launch_bounds__(256) void topk_finish_kernel(KgeModelDev m, const i
         // d 2^-22 (|q~|+Tmax)^2, with Tmax the largest candidate norm; ComplEx and RotatE are the same two forms on
         // their own query (h * r, h * e^{ir}), whose fp32 evaluation error is part of dq.
         const bool cut = theta > -INFINITY && ncand > KP;
-        if (cut && K > n) flag_s = 1;                   // (the sample's threshold, and not enough above it)
+        // (the pieces of an infinite element make every sum a NaN, which is in no list)
+        const bool no_sums = !BF16 && (qi.qn == INFINITY || (dm && tm2 == INFINITY));
+        if (no_sums || (cut && K > n)) flag_s = 1;                   // (the sample's threshold, and not enough above it)
         else if (cut) {
             const double Tm = sqrt((double)tm2);
             double eps, exactK;
@@ -876,7 +1035,7 @@ __global__ __launch_bounds__(256) void topk_finish_kernel(KgeModelDev m, const i
                 const double s = sqrt(qi.qn) + Tm, dq = qi.eps_a, dw = qi.eps_w, c = fabs((double)qi.c);
                 const double wn = 1.0 + dw;                                            // |w~| <= |u| + |dw|
                 const double dc = dq + 6e-8 * c;
-                const double dx = (dw + (double)m.dim * 1.1920929e-07 * wn) * Tm + dc;
+                const double dx = (dw + (double)(m.dim + (BF16 ? 0 : TK_PIECES)) * 1.1920929e-07 * wn) * Tm + dc;
                 const double xm = wn * Tm * 1.0001 + c;                                // |A~ - c| at most
                 eps = 2.0 * dq * s + dq * dq + (double)qi.eps_b * s * s               // q~ for q', fp32 sums
                       + dx * (2.0 * xm + dx) + 4.8e-7 * (xm * xm + s * s)              // x~^2 for x^2, its fp32 evaluation
@@ -953,8 +1112,9 @@ __global__ void topk_prep_kernel(KgeModelDev m, const int32_t *h, const int32_t 
         QInfo qi;
         qi.qn = qn;
         qi.eps_a = (float)(sqrt(dq2) * 1.0001);
-        qi.eps_b = mult ? (float)(d * 1.1920929e-07 * sqrt(qn) * 1.0001)                       // d 2^-23 |q~|
-                                            : (float)((d + 2) * 2.3841858e-07);                  // (d+2) 2^-22: d products and the -|t|^2 start value
+        const int pieces = BF16 ? 0 : TK_PIECES;
+        qi.eps_b = mult ? (float)((d + pieces) * 1.1920929e-07 * sqrt(qn) * 1.0001)            // d 2^-23 |q~|
+                                            : (float)((d + 2 + pieces) * 2.3841858e-07);         // (d+2) 2^-22: d products and the -|t|^2 start value
         qi.eps_w = 0.f; qi.c = 0.f;
         qinfo[q] = qi;
         vt[q] = true_t ? (mult ? vtl : 2.f * vtl - tnl) : INFINITY;
@@ -1026,7 +1186,7 @@ __global__ void topk_prep_th_kernel(KgeModelDev m, const int32_t *h, const int32
         QInfo qi;
         qi.qn = qn;
         qi.eps_a = (float)(sqrt(dq2) * 1.0001);
-        qi.eps_b = (float)((d + 2) * 2.3841858e-07);
+        qi.eps_b = (float)((d + 2 + (BF16 ? 0 : TK_PIECES)) * 2.3841858e-07);
         qi.eps_w = (float)(sqrt(dw2) * 1.0001);
         qi.c = c;
         qinfo[q] = qi;
@@ -1038,7 +1198,6 @@ __global__ void topk_prep_th_kernel(KgeModelDev m, const int32_t *h, const int32
 
 // squared norms of the candidate rows (stored negated: the scan starts its accumulators from them) and their maximum.  A lane
 // reads 16 bytes (rows are multiples of 16 bytes and aligned to them), a wave 64 / LPR rows per step, four steps in flight.
-template <bool BF16>
 __global__ __launch_bounds__(256) void topk_tnorm_kernel(const char *ent, int64_t stride, int d, int64_t ncand, int64_t npad, float *tn,
                                   uint32_t *tmax_bits) {
     __shared__ float wmax[4];
@@ -1046,7 +1205,7 @@ __global__ __launch_bounds__(256) void topk_tnorm_kernel(const char *ent, int64_
     const int64_t wid = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int64_t nw = (int64_t)gridDim.x * 4;
     float mx = 0.f;
-    const int chunks = d * (BF16 ? 2 : 4) / 16;                     // 16-byte chunks of a row
+    const int chunks = d * 2 / 16;                                  // 16-byte chunks of a row
     const int lpr = chunks <= 1 ? 1 : 1 << (32 - __clz(chunks - 1)); // lanes per row
     const int rpw = 64 / lpr, sub = lane / lpr, li = lane % lpr;    // rows per wave step
     constexpr int U = 4;
@@ -1063,10 +1222,8 @@ __global__ __launch_bounds__(256) void topk_tnorm_kernel(const char *ent, int64_
             float s = 0.f;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if constexpr (BF16) {
-                    const float a0 = __uint_as_float(v[u][k] << 16), a1 = __uint_as_float(v[u][k] & 0xffff0000u);
-                    s += a0 * a0; s += a1 * a1;
-                } else { const float a0 = __uint_as_float(v[u][k]); s += a0 * a0; }
+                const float a0 = __uint_as_float(v[u][k] << 16), a1 = __uint_as_float(v[u][k] & 0xffff0000u);
+                s += a0 * a0; s += a1 * a1;
             }
             for (int o = lpr >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
             const int64_t c = c0 + u * rpw + sub;
@@ -1114,20 +1271,21 @@ TopkPlan make_plan(const kge_model_t &m, int64_t Q, int64_t ncand, int K) {
     // again, so inside while there are few - up to 24 for TransH (1M rows, 8 / 16 tiles: 1.41 / 2.57 inside, 1.62 / 2.72 ms
     // outside), up to 4 for rows over 512 bytes (4 / 8 / 16 tiles: 1.55 / 2.62 / 4.94 against 1.87 / 2.52 / 4.43); with two
     // blocks of queries per wave never (the kernel spills 40 registers: 892 against 943 us for one tile, 1,477 against 1,244 for two).
-    p.fn = (m.scorer == KGE_DISTMULT || m.scorer == KGE_COMPLEX) || (p.th ? tiles <= 24 : p.rb == 1024 ? tiles <= 4 : p.ob == 1);
+    // fp32 rows: inside, by the walk that makes their pieces.
+    p.fn = !p.bf16 || (m.scorer == KGE_DISTMULT || m.scorer == KGE_COMPLEX) || (p.th ? tiles <= 24 : p.rb == 1024 ? tiles <= 4 : p.ob == 1);
     p.npad = kge_round_up(ncand > 0 ? ncand : 1, TK_ST);
     return p;
 }
 
 // Size of the sample and growth of the chunks.  What is weighed (seconds, measured): scanning a row for all queries - 0.1 ns while
-// the table's bytes bound it, 0.37 ps per query and 512 bytes beyond; a stage - threshold, launches and their latencies, 26 us +
+// the table's bytes bound it, 0.37 ps per query and 512 bytes beyond (fp32 rows 1.1 to 1.4: a factor of 3.5); a stage - threshold, launches and their latencies, 26 us +
 // 5.4 ns per query; an append, 40 ps.  A sample of S rows costs S rows, a stage that multiplies what the threshold stands for by g
 // costs itself and KP (g - 1) appends per query, so with ln(n / S) / ln(g) stages the best g depends on stage / appends alone (2.6 for 8,192
 // queries, 12 for 128) and the best S is where a row more saves as much of a stage.  g keeps a query's expected appends within what
 // a workgroup of the compaction holds in registers and 24 per area (of 64: an overflow would rank the query exhaustively).
 struct TopkStages { int64_t sample; double growth; };
 TopkStages topk_stages(const TopkPlan &p, int64_t Q, int64_t total_tiles) {
-    const double width = (p.rb == 512 ? 1.0 : 2.0) * (p.th ? 2.0 : 1.0) * (p.bf16 ? 1.0 : 8.0);
+    const double width = (p.rb == 512 ? 1.0 : 2.0) * (p.th ? 2.0 : 1.0) * (p.bf16 ? 1.0 : 3.5);
     const double row = fmax(0.1e-9 * p.rb / 512, 0.37e-12 * (double)Q * width), stage = 26e-6 + 5.4e-9 * (double)Q;
     const double appends = 40e-12 * (double)Q * p.KP;
     const double most = fmin(3500.0, 24.0 * 2.0 * p.nseg) / (1.15 * p.KP);
@@ -1175,7 +1333,7 @@ size_t topk_carve(const TopkPlan &p, void *ws, TopkWs &w, bool most = false) {
 
 template <bool BF16, int RB, int KIND, int OB, bool TH, bool FN, bool SAMPLE>
 int launch_scan(const TopkArgs &a, hipStream_t st) {
-    constexpr int NSTAGE = RB == 512 ? 4 : 3;
+    constexpr int NSTAGE = tk_stages(BF16, RB);
     constexpr int LDS = NSTAGE * TK_ST * RB + (NSTAGE + 1) * 4 * 256;
     static KgeLdsLimit lds_limit;
     if (lds_limit.set((const void *)topk_scan_kernel<BF16, RB, KIND, OB, TH, FN, SAMPLE>, LDS) != KGE_OK) return KGE_E_HIP;
@@ -1185,17 +1343,20 @@ int launch_scan(const TopkArgs &a, hipStream_t st) {
 
 template <bool BF16, bool SAMPLE>
 int scan(const TopkPlan &p, int kind, const TopkArgs &a, hipStream_t st) {
-    if (p.th) return p.fn ? launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, true, SAMPLE>(a, st)
-                          : launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, false, SAMPLE>(a, st);
     if (kind == KGE_KIND_MULT) {
         if (p.rb == 1024) return launch_scan<BF16, 1024, KGE_KIND_MULT, 1, false, true, SAMPLE>(a, st);
         return p.ob == 1 ? launch_scan<BF16, 512, KGE_KIND_MULT, 1, false, true, SAMPLE>(a, st)
                          : launch_scan<BF16, 512, KGE_KIND_MULT, 2, false, true, SAMPLE>(a, st);
     }
-    if (p.rb == 1024) return p.fn ? launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, true, SAMPLE>(a, st)
-                                  : launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, false, SAMPLE>(a, st);
-    if (p.ob == 1) return launch_scan<BF16, 512, KGE_KIND_DIST, 1, false, true, SAMPLE>(a, st);
-    return launch_scan<BF16, 512, KGE_KIND_DIST, 2, false, false, SAMPLE>(a, st);
+    if constexpr (BF16) if (!p.fn) {
+        if (p.th) return launch_scan<true, 512, KGE_KIND_DIST, 2, true, false, SAMPLE>(a, st);
+        if (p.rb == 1024) return launch_scan<true, 1024, KGE_KIND_DIST, 1, false, false, SAMPLE>(a, st);
+        return launch_scan<true, 512, KGE_KIND_DIST, 2, false, false, SAMPLE>(a, st);
+    }
+    if (p.th) return launch_scan<BF16, 512, KGE_KIND_DIST, 2, true, true, SAMPLE>(a, st);
+    if (p.rb == 1024) return launch_scan<BF16, 1024, KGE_KIND_DIST, 1, false, true, SAMPLE>(a, st);
+    if constexpr (!BF16) if (p.ob == 2) return launch_scan<false, 512, KGE_KIND_DIST, 2, false, true, SAMPLE>(a, st);
+    return launch_scan<BF16, 512, KGE_KIND_DIST, 1, false, true, SAMPLE>(a, st);
 }
 
 }  // namespace
@@ -1236,10 +1397,9 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
     }
     if (p.bf16) {
         if (!p.th) hipLaunchKernelGGL(topk_prep_kernel<true>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt, w.tmax, w.zeros);
-        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel<true>, dim3((unsigned)(p.npad / 32 < 2048 ? p.npad / 32 : 2048)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
+        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel, dim3((unsigned)(p.npad / 32 < 2048 ? p.npad / 32 : 2048)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
     } else {
         if (!p.th) hipLaunchKernelGGL(topk_prep_kernel<false>, dim3((p.Qp + 3) / 4), dim3(256), 0, st, md, h, r, true_t, (int)Q, p.Qp, p.dp, w.Qm, w.vt, w.qinfo, w.thr, w.cnt, w.flag, w.rankcnt, w.tmax, w.zeros);
-        if (!p.fn) hipLaunchKernelGGL(topk_tnorm_kernel<false>, dim3((unsigned)(p.npad / 32 < 2048 ? p.npad / 32 : 2048)), dim3(256), 0, st, cand0, stride, model.dim, ncand, p.npad, w.tn, w.tmax);
     }
     if (hipGetLastError() != hipSuccess) return KGE_E_HIP;
 

@@ -253,6 +253,53 @@ def test_columns_behind_a_row_are_not_read(scorer, dim, bf16, Q):
     assert bool(torch.isfinite(two[1]).all())
 
 
+@pytest.mark.parametrize("scorer,dim,Q,n", [
+    ("distmult", 256, 130, 9001), ("transe", 136, 40, 4127), ("complex", 128, 513, 8200), ("transh", 120, 100, 6000),
+    ("rotate", 8, 20, 4200), ("transe", 64, 600, 5000), ("distmult", 32, 7, 33)])
+def test_fp32_rows_of_all_sizes(orc, scorer, dim, Q, n):
+    """fp32 rows, which the scan takes as two fp16 pieces scaled by row: rows over a factor of 2^40 and elements over 2^12, rows of zeros, of
+    subnormal numbers and of one element alone."""
+    g = np.random.default_rng(dim + Q)
+    G = make_case(scorer, n, 20, dim, Q, 0, False)
+    e = G["ent"]
+    e *= (2.0 ** g.integers(-36, 5, n)).astype(np.float32)[:, None] * (2.0 ** g.integers(-12, 1, e.shape)).astype(np.float32)
+    at = g.permutation(n)
+    e[at[0]] = 0
+    e[at[1]] = (g.normal(size=dim) * 1e-40).astype(np.float32)
+    e[at[2]] = 0
+    e[at[2], dim // 2] = 3.0
+    G["h"][:3] = at[:3]
+    true_t = g.integers(0, n, Q).astype(np.int32)
+    true_t[:3] = at[2::-1]
+    _check(orc, scorer, G, False, 0, n, min(50, n), true_t)
+
+
+@pytest.mark.parametrize("scorer", ["distmult", "transe", "transh"])
+def test_fp32_rows_with_nan_and_infinity(scorer):
+    """A row with a NaN is nobody's candidate and changes no other's place; a row with an infinity sends the call to the exact ranking."""
+    import paper_2211_12281_amd as kge
+    dim, Q, n, K = 128, 70, 5000, 20
+    g = np.random.default_rng(3)
+    G = make_case(scorer, n, 20, dim, Q, 0, False)
+    bad = np.setdiff1d(g.permutation(n)[:300], G["h"])[:40]
+    rest = np.setdiff1d(np.arange(n), bad)
+    args = [dev_idx(G["h"]), dev_idx(G["r"]), 0, n, K]
+    G["ent"][bad] = -G["ent"][G["h"][0]] if scorer == "distmult" else 100.0      # far from every query
+    want = [x.cpu().numpy() for x in kge.topk(gpu_model(scorer, G, False), *args)[:2]]
+    G["ent"][bad, g.integers(0, dim, len(bad))] = np.nan
+    got = [x.cpu().numpy() for x in kge.topk(gpu_model(scorer, G, False), *args)[:2]]
+    clean = ~np.isin(want[0], bad).any(axis=1)
+    assert clean.sum() > Q // 2 and np.array_equal(got[0][clean], want[0][clean]) and np.array_equal(got[1][clean], want[1][clean])
+    G["ent"][bad] = 0.0
+    G["ent"][bad[0], 5] = np.inf
+    got = kge.topk(gpu_model(scorer, G, False), *args)[0].cpu().numpy()
+    if scorer != "distmult":                                                     # (infinitely far)
+        G["ent"][bad[0]] = 1e6
+        want = kge.topk(gpu_model(scorer, G, False), *args)[0].cpu().numpy()
+        assert np.array_equal(got, want)
+    assert np.isin(rest, got).any()
+
+
 def test_partition_bucketing(orc):
     import paper_2211_12281_amd as kge
     g = ks.rng(1, ks.TAG_TRIPLE_H)
