@@ -44,7 +44,7 @@ struct EncGemm {
     const char *A; int64_t lda_b; const int32_t *idx0, *idx1; int n_idx0, m_valid;
     const char *B; int64_t ldb_b; int n_valid;
     float *C; int64_t ldc;
-    int ksteps, tiles_m, tiles_n;
+    int ksteps, tiles_m, tiles_n;                            // (tiles: of the launched kernel's size)
 };
 // A launch runs two contractions (heads against M_H, tails and negatives against M_T) so that the chip is filled
 // once; work items enumerate (contraction, row tile, column tile), column tile fastest.
@@ -67,11 +67,12 @@ template <int N> __device__ __forceinline__ void enc_wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Workgroup = 128 x 128 outputs, wave = 64 x 64 (2 x 2 blocks of 32 x 32).  Both operands pass through the LDS
+// Workgroup = MT x NT outputs (128 x 128, or 64 on a side: enc_launch_pair), wave = a quarter of them (2 x 2 blocks of 32 x 32 at 128 x
+// 128).  Both operands pass through the LDS
 // in chunks of two k-steps (64 bytes of every row).  The chunks are copied global -> LDS asynchronously into a
 // ring of ENC_NSTAGE stages, so that the rows of ENC_NSTAGE - 1 chunks (random table rows in the forward pass:
 // pure latency) are in flight while one chunk is multiplied; no registers are tied up by the copies.  The ring
-// takes 64 KB and the kernel at most 128 registers per lane, so two workgroups share a compute unit: one's
+// takes 64 KB at 128 x 128 and the kernel at most 128 registers per lane, so two workgroups share a compute unit: one's
 // prologue, barriers and write-out overlap the other's products.  A 64-byte LDS row keeps its four 16-byte pieces
 // XOR-swizzled by (row / 2) % 4, so that the fragment reads of 8 consecutive rows fall into 8 different bank
 // groups; a copy instruction fills 16 rows, lane l fetching piece (l % 4) ^ ((l / 8) % 4) of row l / 4 into slot
@@ -80,9 +81,11 @@ template <int N> __device__ __forceinline__ void enc_wait_vmcnt() {
 // through registers with zeros selected for the missing pieces.
 // Workgroup ids are dealt round-robin to the 8 dies: id -> work item (id % 8) * ceil(total / 8) + id / 8, so that
 // the tiles that share operand rows run on the same die and meet in its L2.
-template <bool BF16>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void enc_gemm_nt_kernel(const EncGemmPair pr) {
+template <bool BF16, int MT, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT == 128 ? 2 : 3, MT == 128 ? 2 : 3))) void enc_gemm_nt_kernel(const EncGemmPair pr) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int NI = MT / 64, NJ = NT / 64, RPW = MT / 4, BPW = NT / 4;    // row and column blocks of a wave; rows that it copies
+    constexpr int A_BYTES = MT * ENC_ROW_BYTES, STAGE = A_BYTES + NT * ENC_ROW_BYTES, LPW = NI + NJ;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, g = lane >> 5;
     const int per = (pr.total + 7) >> 3;
@@ -91,59 +94,69 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bool second = w >= pr.wgs0;
     const EncGemm &q = pr.g[second ? 1 : 0];
     w -= second ? pr.wgs0 : 0;
-    const int m0 = w / q.tiles_n * ENC_TILE, n0 = w % q.tiles_n * ENC_TILE;
+    const int m0 = w / q.tiles_n * MT, n0 = w % q.tiles_n * NT;
     const int nfull = q.ksteps >> 1, rem = q.ksteps & 1;
-    // staging: copy j (j < 2) of wave v fills rows 32 v + 16 j .. + 15 of a tile; this lane's row and piece
+    // staging: copy j of wave v fills rows 16 NI v + 16 j .. + 15 of A's tile, 16 NJ v + 16 j .. + 15 of B's; this lane's row and piece
     const int srow = lane >> 2, piece = (lane & 3) ^ ((srow >> 1) & 3);
-    const char *ga[2], *gb[2];
+    const char *ga[NI], *gb[NJ];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int ra = m0 + 32 * wave + 16 * j + srow, rb = n0 + 32 * wave + 16 * j + srow;
+    for (int j = 0; j < NI; ++j) {
+        const int ra = m0 + RPW * wave + 16 * j + srow;
         int64_t src = 0;
         if (ra < q.m_valid) src = ra < q.n_idx0 ? (int64_t)q.idx0[ra] : (int64_t)q.idx1[ra - q.n_idx0];
         ga[j] = q.A + src * q.lda_b + piece * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int rb = n0 + BPW * wave + 16 * j + srow;
         gb[j] = q.B + (int64_t)(rb < q.n_valid ? rb : 0) * q.ldb_b + piece * 16;
     }
     // the row indices must have arrived before the loop: a compiler-inserted wait inside it would drain the ring
 #pragma unroll
-    for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(ga[j]), "+v"(gb[j]));
+    for (int j = 0; j < NI; ++j) asm volatile("" : "+v"(ga[j]));
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(gb[j]));
     auto issue = [&](int c) {                             // chunk min(c, nfull - 1) -> stage c % ENC_NSTAGE
         const int64_t off = (int64_t)min(c, nfull - 1) * ENC_ROW_BYTES;
-        const uint32_t sb = lds0 + (uint32_t)(c & (ENC_NSTAGE - 1)) * ENC_STAGE_BYTES + (uint32_t)wave * (32 * ENC_ROW_BYTES);
+        const uint32_t sb = lds0 + (uint32_t)(c & (ENC_NSTAGE - 1)) * STAGE;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) enc_async_copy16(ga[j] + off, __builtin_amdgcn_readfirstlane(sb + j * 1024));
+        for (int j = 0; j < NI; ++j) enc_async_copy16(ga[j] + off, __builtin_amdgcn_readfirstlane(sb + (uint32_t)wave * (RPW * ENC_ROW_BYTES) + j * 1024));
 #pragma unroll
-        for (int j = 0; j < 2; ++j) enc_async_copy16(gb[j] + off, __builtin_amdgcn_readfirstlane(sb + ENC_HALF_BYTES + j * 1024));
+        for (int j = 0; j < NJ; ++j) enc_async_copy16(gb[j] + off, __builtin_amdgcn_readfirstlane(sb + A_BYTES + (uint32_t)wave * (BPW * ENC_ROW_BYTES) + j * 1024));
     };
-    enc_f32x16 acc[2][2];
+    enc_f32x16 acc[NI][NJ];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < NI; ++i)
+        for (int j = 0; j < NJ; ++j)
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64;
+    const int wm = (wave & 1) * (32 * NI), wn = (wave >> 1) * (32 * NJ);
     auto compute = [&](int stage) {
-        const char *sa = lds + stage * ENC_STAGE_BYTES, *sb = sa + ENC_HALF_BYTES;
+        const char *sa = lds + stage * STAGE, *sb = sa + A_BYTES;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            enc_u32x4 fa[2], fb[2];
+            enc_u32x4 fa[NI], fb[NJ];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int rowa = wm + 32 * i + lr, rowb = wn + 32 * i + lr;
+            for (int i = 0; i < NI; ++i) {
+                const int rowa = wm + 32 * i + lr;
                 fa[i] = *(const enc_u32x4 *)(sa + rowa * ENC_ROW_BYTES + (((2 * ks + g) ^ ((rowa >> 1) & 3)) * 16));
+            }
+#pragma unroll
+            for (int i = 0; i < NJ; ++i) {
+                const int rowb = wn + 32 * i + lr;
                 fb[i] = *(const enc_u32x4 *)(sb + rowb * ENC_ROW_BYTES + (((2 * ks + g) ^ ((rowb >> 1) & 3)) * 16));
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = enc_mma16<BF16>(acc[i][j], fa[i], fb[j]);
+                for (int j = 0; j < NJ; ++j) acc[i][j] = enc_mma16<BF16>(acc[i][j], fa[i], fb[j]);
         }
     };
-    static_assert((ENC_NSTAGE & (ENC_NSTAGE - 1)) == 0 && (ENC_NSTAGE - 2) * ENC_LPW < 64, "ring size");
+    static_assert((ENC_NSTAGE & (ENC_NSTAGE - 1)) == 0 && (ENC_NSTAGE - 2) * LPW < 64, "ring size");
     if (nfull > 0) {
         for (int c = 0; c < ENC_NSTAGE - 1; ++c) issue(c);
         for (int c = 0; c < nfull; ++c) {
             // chunks up to c + ENC_NSTAGE - 2 are issued; all but the last ENC_NSTAGE - 2 of them must have landed
-            enc_wait_vmcnt<(ENC_NSTAGE - 2) * ENC_LPW>();
+            enc_wait_vmcnt<(ENC_NSTAGE - 2) * LPW>();
             __syncthreads();                                // chunk c is complete; everyone is done with chunk c - 1
             issue(c + ENC_NSTAGE - 1);                      // ... whose stage is refilled (past the end: a harmless repeat)
             compute(c & (ENC_NSTAGE - 1));
@@ -155,21 +168,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const enc_u32x4 zero = {0u, 0u, 0u, 0u};
         const bool in = (piece >> 1) < rem;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const enc_u32x4 xa = in ? *(const enc_u32x4 *)(ga[j] + (int64_t)nfull * ENC_ROW_BYTES) : zero;
-            const enc_u32x4 xb = in ? *(const enc_u32x4 *)(gb[j] + (int64_t)nfull * ENC_ROW_BYTES) : zero;
-            char *dst = lds + (32 * wave + 16 * j) * ENC_ROW_BYTES + lane * 16;
-            *(enc_u32x4 *)dst = xa;
-            *(enc_u32x4 *)(dst + ENC_HALF_BYTES) = xb;
-        }
+        for (int j = 0; j < NI; ++j)
+            *(enc_u32x4 *)(lds + (RPW * wave + 16 * j) * ENC_ROW_BYTES + lane * 16) = in ? *(const enc_u32x4 *)(ga[j] + (int64_t)nfull * ENC_ROW_BYTES) : zero;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            *(enc_u32x4 *)(lds + A_BYTES + (BPW * wave + 16 * j) * ENC_ROW_BYTES + lane * 16) = in ? *(const enc_u32x4 *)(gb[j] + (int64_t)nfull * ENC_ROW_BYTES) : zero;
         __syncthreads();
         compute(0);
     }
     // accumulator layout: lane holds column lr of the B side; register e holds A-side row 8 (e/4) + 4 g + e%4
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             const int col = n0 + wn + 32 * j + lr;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
@@ -526,25 +537,42 @@ EncGemm enc_gemm_desc(const void *A, int64_t lda_b, const int32_t *idx0, int n_i
     EncGemm q{};
     q.A = (const char *)A; q.lda_b = lda_b; q.idx0 = idx0; q.idx1 = idx1; q.n_idx0 = n_idx0; q.m_valid = m_valid;
     q.B = (const char *)Bm; q.ldb_b = ldb_b; q.n_valid = n_valid; q.C = C; q.ldc = ldc; q.ksteps = ksteps;
-    q.tiles_m = (m_valid + ENC_TILE - 1) / ENC_TILE; q.tiles_n = (n_valid + ENC_TILE - 1) / ENC_TILE;
     return q;
 }
 
+template <bool BF16, int MT, int NT>
+int enc_launch_nt(EncGemmPair pr, hipStream_t st) {
+    constexpr int LDS = ENC_NSTAGE * (MT + NT) * ENC_ROW_BYTES;
+    static KgeLdsLimit limit;                               // the ring of stages is larger than the default dynamic limit
+    if (limit.set((const void *)enc_gemm_nt_kernel<BF16, MT, NT>, LDS) != KGE_OK) return KGE_E_HIP;
+    for (EncGemm &g : pr.g) { g.tiles_m = (g.m_valid + MT - 1) / MT; g.tiles_n = (g.n_valid + NT - 1) / NT; }
+    pr.wgs0 = pr.g[0].tiles_m * pr.g[0].tiles_n;
+    pr.total = pr.wgs0 + pr.g[1].tiles_m * pr.g[1].tiles_n;
+    if (pr.total == 0) return KGE_OK;
+    hipLaunchKernelGGL((enc_gemm_nt_kernel<BF16, MT, NT>), dim3((pr.total + 7) / 8 * 8), dim3(256), LDS, st, pr);
+    return KGE_OK;
+}
+
+// Tiles of 128 x 128 share most of what they read, smaller ones fill the chip where those are few.
+// bf16 (bound by the rows' latency and bytes): 64 x 64 where the large tiles leave a quarter of the compute units without one.  Whole
+// encode + encode_bwd, us, large / small tiles: 128 tiles (2,048 + 2,048 + 4,096 slots, d 256) 49.8 / 45.6, 126 (d 384) 55.7 / 50.4, 16 (1,024
+// and 3,000, d 128) 44.6 / 37.7, 192 65.8 / 65.6, 240 62.6 / 64.9, 256 64.2 / 66.3, 384 (24,576 slots, d 256) 81.7 / 84.2.
+// fp32 (bound by the matrix pipe of the fullest compute unit): 64 x 128, or 64 x 64 where that leaves it less to do.  128 x 128 / 64 x
+// 128 / 64 x 64: 24,576 slots, d 256 238 / 217 / 217; 16,384 158 / 154 / 171; 8,192 120 / 93 / 93; 1,234, d 80 87 / 60 / 48.  From 512 large
+// tiles, two of them on every unit, those: 16,384, d 400 269 / 277; 40,960, d 256 (640 tiles) 392 / 396.
 int enc_launch_pair(bool bf16, const EncGemm &g0, const EncGemm &g1, hipStream_t st) {
-    // the ring of stages is larger than the default dynamic limit
-    static KgeLdsLimit lim_bf16, lim_f32;
-    if (lim_bf16.set((const void *)enc_gemm_nt_kernel<true>, ENC_LDS_BYTES) != KGE_OK ||
-        lim_f32.set((const void *)enc_gemm_nt_kernel<false>, ENC_LDS_BYTES) != KGE_OK)
-        return KGE_E_HIP;
     EncGemmPair pr{};
     pr.g[0] = g0; pr.g[1] = g1;
-    pr.wgs0 = g0.tiles_m * g0.tiles_n;
-    pr.total = pr.wgs0 + g1.tiles_m * g1.tiles_n;
-    if (pr.total == 0) return KGE_OK;
-    const int grid = (pr.total + 7) / 8 * 8;
-    if (bf16) hipLaunchKernelGGL(enc_gemm_nt_kernel<true>, dim3(grid), dim3(256), ENC_LDS_BYTES, st, pr);
-    else      hipLaunchKernelGGL(enc_gemm_nt_kernel<false>, dim3(grid), dim3(256), ENC_LDS_BYTES, st, pr);
-    return KGE_OK;
+    auto tiles = [&](int mt, int nt) {
+        int64_t n = 0;
+        for (const EncGemm &g : pr.g) n += (int64_t)((g.m_valid + mt - 1) / mt) * ((g.n_valid + nt - 1) / nt);
+        return n;
+    };
+    const int64_t large = tiles(128, 128);
+    if (bf16) return large <= 192 ? enc_launch_nt<true, 64, 64>(pr, st) : enc_launch_nt<true, 128, 128>(pr, st);
+    if (large >= 512) return enc_launch_nt<false, 128, 128>(pr, st);
+    auto rounds = [&](int mt, int nt) { return (tiles(mt, nt) + 255) / 256 * mt * nt; };
+    return rounds(64, 64) < rounds(64, 128) ? enc_launch_nt<false, 64, 64>(pr, st) : enc_launch_nt<false, 64, 128>(pr, st);
 }
 
 }  // namespace

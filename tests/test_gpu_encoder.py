@@ -46,6 +46,15 @@ def test_forward_matches_oracle(orc, bf16, d, fd, B, N):
     assert abs(reg.item() - om) <= tol * om
 
 
+@pytest.mark.parametrize("bf16,d,fd,B,N", [
+    (True, 400, 48, 1000, 4000), (True, 400, 48, 1000, 4300),       # 192 and 200 tiles of 128 x 128: the small ones, the large ones
+    (False, 256, 40, 700, 6000), (False, 256, 40, 700, 8000),       # two rounds of the small tile against one and two of the wider
+    (False, 400, 8, 100, 16200),                                    # 512 large tiles
+    (True, 80, 16, 65, 127), (False, 72, 8, 63, 2)])                # a row more and less than a tile; one k-step alone
+def test_tiles_of_the_projection(orc, bf16, d, fd, B, N):
+    test_forward_matches_oracle(orc, bf16, d, fd, B, N)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("d,fd,B,N,p", [(64, 96, 150, 333, 0.2), (256, 768, 300, 2100, 0.0), (128, 32, 1, 1, 0.5),
                                         (32, 768, 0, 77, 0.1), (64, 64, 40, 0, 0.1)])
