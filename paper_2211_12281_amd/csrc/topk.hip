@@ -541,6 +541,9 @@ void topk_scan_kernel(const TopkArgs a) {
                     for (int i = 0; i < 16; ++i) signs = __builtin_amdgcn_alignbit(signs, __float_as_uint(vt[ob] - v[i]), 31);
                     above[ob] += (uint32_t)__builtin_popcount(signs);
                 }
+                // (a held-out tail that ranks low brings nearly every tile here: the comparisons below cost two calls of 8,192 x 10M 81.0
+                // ms, behind this test 72.6; with tails that rank high 33.7 -> 33.9 a call)
+                if (!__any(mx > thr[ob])) continue;
                 // A hit is nearly always the only one of its lane, and then it is the maximum: its place comes from a mask of the
                 // comparisons, without sixteen branches that each wait for a compare result.
                 uint32_t hits = 0;
