@@ -462,7 +462,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
     kge_f32x16 acc[OW], accw;                              // phase-1 accumulators: [stream, own]
     uint4 bf[OW][2], bf2[2];                               // bf16 B-operands of phase 2
     KgeP2 coef2p[2], coefw2p[2];                           // PL: the fp16 pieces of coefficients times c_scale
-    float coef[16], coef2[16];                             // coefficients of phase 2 (coef2: TransH's normals)
+    float coef_a[16], coef2_a[16];                         // ALONE: coefficients of phase 2 (coef2: TransH's normals)
     // PL: what the own row's coefficients, and with them its accumulated gradient, are multiplied by (a power of two until its reference is
     // raised); 0: none yet, what has accumulated counts for nothing
     float c_scale = 0.f;
@@ -607,6 +607,87 @@ void kge_block_kernel(const KgeBlockArgs a) {
             }
         }
     };
+    // scores of own fragment h against the tile (SCORE mode stores them), 1/distance, w.t, in one piece: kernels of several waves per SIMD
+    // (in the parts below, with the line of the cancellation recomputed, bf16 TransH takes 593 us a step of 8,192 x 4,096 for 527)
+    auto scores = [&](int h, float (&sv)[16], float (&dv)[16], float (&Av)[16]) {
+        const int oidx = oidx0 + 32 * h;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { dv[i] = 0.f; Av[i] = 0.f; }
+        if constexpr (PL) {                                // (exact: powers of two)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int s_exp = str_exp_of(8 * (i >> 2) + 4 * g + (i & 3));
+                acc[0][i] = ldexpf(acc[0][i], o_exp + s_exp);
+                if constexpr (TRANSH) accw[i] = ldexpf(accw[i], (OWN_ROW ? s_exp : o_exp) + KGE_PLANE_UNIT_EXP);
+            }
+        }
+        if constexpr (KIND == KGE_KIND_MULT) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sv[i] = acc[h][i];
+        } else {
+            // (squared distances and their cancellation: scores2)
+            float d2[16], thr[16];
+            bool cancel = false;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int sl = 8 * (i >> 2) + 4 * g + (i & 3);
+                float qn, cc, wn, tnv;
+                if constexpr (OWN_ROW) { qn = o_qn[h]; cc = o_c[h]; wn = o_wn[h]; tnv = *(const float *)(side + sl * 4); }
+                else { float4 ri = *(const float4 *)(side + sl * 16); qn = ri.x; cc = ri.y; wn = ri.w; tnv = o_tn[h]; }
+                d2[i] = fmaf(-2.f, acc[h][i], qn + tnv);
+                if constexpr (TRANSH) { const float A = accw[i]; Av[i] = A; d2[i] += A * (2.f * cc - A * (2.f - wn)); }
+                thr[i] = 1e-3f * (qn + tnv);
+                cancel = cancel || d2[i] < thr[i];
+            }
+            if (__any(cancel)) {
+                auto again = [&](int i) {
+                    const int sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
+                    const int b = OWN_ROW ? oidx : sidx, n = OWN_ROW ? sidx : oidx;
+                    const char *own = (const char *)(PL ? a.own32 : a.own), *str = (const char *)(PL ? a.str32 : a.str);
+                    const char *qb = (OWN_ROW ? own : str) + (size_t)b * RB, *tb = (OWN_ROW ? str : own) + (size_t)n * RB;
+                    const char *wb = !TRANSH ? nullptr : PL ? (const char *)a.w32 + (size_t)b * RB : (const char *)(OWN_ROW ? a.own2 : a.str2) + (size_t)b * RB;
+                    if constexpr (BF16) return kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
+                    else return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
+                };
+                if constexpr (BF16) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        if (d2[i] < thr[i]) d2[i] = again(i);
+                        asm volatile("" ::: "memory");      // keeps the branch from being turned into selects
+                    }
+                } else {
+                    // fp32: a loop over the lane's entries, in line - a call costs its caller-saved registers all through the kernel, where
+                    // the pieces leave none (bf16 tables have them, and lose 0.5-1.5 % by this form)
+                    uint32_t todo = 0;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) todo |= d2[i] < thr[i] ? 1u << i : 0u;
+                    while (todo) {
+                        const int i = __builtin_ctz(todo);
+                        todo &= todo - 1;
+                        const float v = again(i);
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) d2[k] = k == i ? v : d2[k];
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float dd = fmaxf(d2[i], 0.f);
+                const float inv = dd > 0.f ? __builtin_amdgcn_rsqf(dd) : 0.f;
+                dv[i] = inv;
+                sv[i] = -dd * inv;                          // -sqrt(d2)
+            }
+        }
+        if constexpr (MODE == KGE_MODE_SCORE) {
+            if (oidx < a.N) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int b = sbase + 8 * (i >> 2) + (i & 3);
+                    if (b < a.B) a.S_out[(size_t)b * a.N + oidx] = sv[i];
+                }
+            }
+        }
+    };
     int s_exps[16];                                        // ALONE: exponents of the streamed rows of the lane's entries
     auto scores4 = [&](int h, int j, const Side4 &x, float (&d2)[16], float (&Av)[16], bool &cancel) {
 #pragma unroll
@@ -628,27 +709,8 @@ void kge_block_kernel(const KgeBlockArgs a) {
     };
     auto scores1 = [&](int h, float (&d2)[16], float (&Av)[16], bool &cancel) {
         cancel = false;
-        if constexpr (ALONE) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { Side4 x; side4(j, x); scores4(h, j, x, d2, Av, cancel); }
-            return;
-        }
-        if constexpr (PL) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[0][i] = ldexpf(acc[0][i], o_exp + str_exp_of(8 * (i >> 2) + 4 * g + (i & 3)));
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            Av[i] = 0.f;
-            if constexpr (KIND == KGE_KIND_MULT) d2[i] = acc[h][i];
-            else {
-                float qn, cc, wn, tnv;
-                norms_of(h, i, qn, cc, wn, tnv);
-                d2[i] = fmaf(-2.f, acc[h][i], qn + tnv);
-                if constexpr (TRANSH) { const float A = accw[i]; Av[i] = A; d2[i] += A * (2.f * cc - A * (2.f - wn)); }
-                cancel = cancel || d2[i] < 1e-3f * (qn + tnv);
-            }
-        }
+        for (int j = 0; j < 4; ++j) { Side4 x; side4(j, x); scores4(h, j, x, d2, Av, cancel); }
     };
     // the scores themselves (SCORE mode stores them) and 1/distance.  Distances whose expansion cancels (below 1e-3 of the norms) are
     // redone by direct differences in a rarely taken branch.  (The line with planes: above it their errors are 0.6 to 0.9 times those of
@@ -678,15 +740,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
                     if constexpr (BF16) return kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
                     else return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
                 };
-                if constexpr (BF16) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        if (d2[i] < line(i)) d2[i] = again(i);
-                        asm volatile("" ::: "memory");      // keeps the branch from being turned into selects
-                    }
-                } else {
-                    // fp32: a loop over the lane's entries, in line - a call costs its caller-saved registers all through the kernel, where
-                    // the pieces leave none (bf16 tables have them, and lose 0.5-1.5 % by this form)
+                {
                     uint32_t todo = 0;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) todo |= d2[i] < line(i) ? 1u << i : 0u;
@@ -755,19 +809,16 @@ void kge_block_kernel(const KgeBlockArgs a) {
     constexpr int NPC = TRANSH ? 4 : 2;
     auto make_piece = [&](int p) {
         const int j2 = TRANSH ? p >> 1 : p;
-        const float *c = (TRANSH && (p & 1) ? coef2 : coef) + 8 * j2;
+        const float *c = (TRANSH && (p & 1) ? coef2_a : coef_a) + 8 * j2;
         float x[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = c[i] * c_scale;
         if (TRANSH && (p & 1)) coefw2p[j2] = kge_split2(x); else coef2p[j2] = kge_split2(x);
     };
-    auto make_pieces = [&]() {
-#pragma unroll
-        for (int p = 0; p < NPC; ++p) make_piece(p);
-    };
     float row_K[16], row_c[16];                            // ALONE, GRADT: constants of the streamed rows, requested ahead of their use
     // the coefficients of phase 2 for own fragment h, packed as its B-operand
     auto weights = [&](int h, const float (&sv)[16], const float (&dv)[16], const float (&Av)[16], const float (&x2)[16]) {
+        float coef[16], coef2[16];
         if constexpr (MODE == KGE_MODE_FWD) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -850,16 +901,30 @@ void kge_block_kernel(const KgeBlockArgs a) {
                         if constexpr (TRANSH && OWN_ROW) rescale(acc2b[b], r);
                     }
                 }
-                if constexpr (!ALONE) make_pieces();
+                if constexpr (ALONE) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) { coef_a[i] = coef[i]; if constexpr (TRANSH) coef2_a[i] = coef2[i]; }
+                } else {
+                    auto pieces = [&](const float *c) {
+                        float x[8];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) x[i] = c[i] * c_scale;
+                        return kge_split2(x);
+                    };
+#pragma unroll
+                    for (int j2 = 0; j2 < 2; ++j2) {
+                        coef2p[j2] = pieces(coef + 8 * j2);
+                        if constexpr (TRANSH) coefw2p[j2] = pieces(coef2 + 8 * j2);
+                    }
+                }
             }
         }
     };
     // The FWD pass keeps all weights relative to a per-row reference exponent st_m that is only
     // raised (and what the row has accumulated rescaled) when a tile's maximum exceeds it by more than
     // KGE_TAU: weights stay below 2^KGE_TAU, and the rescaling is a rarely taken branch of the loop.
-    auto epilogue2 = [&](int h, float (&d2)[16], const float (&Av)[16], bool cancel) {
-        float sv[16], dv[16], x2[16];
-        scores2(h, d2, cancel, sv, dv);
+    auto of_scores = [&](int h, const float (&sv)[16], const float (&dv)[16], const float (&Av)[16]) {
+        float x2[16];
         if constexpr (MODE == KGE_MODE_FWD) {
             const float tm = exponents(h, sv, x2);
             const bool have = st_m[h] > -INFINITY;
@@ -894,13 +959,17 @@ void kge_block_kernel(const KgeBlockArgs a) {
         }
         weights(h, sv, dv, Av, x2);
     };
+    auto epilogue2 = [&](int h, float (&d2)[16], const float (&Av)[16], bool cancel) {
+        float sv[16], dv[16];
+        scores2(h, d2, cancel, sv, dv);
+        of_scores(h, sv, dv, Av);
+    };
     auto epilogue = [&]() {
 #pragma unroll
         for (int h = 0; h < OW; ++h) {
-            float d2[16], Av[16];
-            bool cancel;
-            scores1(h, d2, Av, cancel);
-            epilogue2(h, d2, Av, cancel);
+            float sv[16], dv[16], Av[16];
+            scores(h, sv, dv, Av);
+            of_scores(h, sv, dv, Av);
         }
     };
 
