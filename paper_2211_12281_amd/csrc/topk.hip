@@ -28,7 +28,6 @@ struct TopkArgs {
     int64_t ent_stride;                 // bytes between rows
     int32_t valid_bytes;                // d * sizeof(element)
     int64_t ncand;
-    int64_t cand_lo;                    // entity id of candidate 0
     const float *tn;                    // [ncand rounded up to a tile] MINUS the squared norms of the candidates, or nullptr:
                                         // the scan makes them itself (kernels with FN)
     uint32_t *tmax;                     // largest squared norm of a candidate (kernels with FN)
@@ -40,9 +39,11 @@ struct TopkArgs {
     int32_t nseg;
     uint32_t *rankcnt;                  // [Qp] candidates whose value beats the held-out tail's
     int32_t nq;                         // number of real queries (rows past it are padding)
-    int64_t tile_lo, tile_hi;
-    int32_t nsplit;                     // tile tile_lo + i belongs to split i mod nsplit
-    int32_t own_tiles;
+    int32_t tile_lo, tile_hi;           // positions in the walk (topk_stride) whose tiles are scanned
+    int32_t nsplit;                     // position tile_lo + i belongs to split i mod nsplit
+    int32_t walk;                       // positions in all, as many as tiles or a few more: position p is tile p stride mod walk
+    int32_t stride, start, step;        // start: tile of position tile_lo; step: nsplit stride mod walk
+    int32_t tiles, own_tiles;           // tiles of candidates, of queries
     int64_t samp_row, samp_step;        // kernels with SAMPLE: row r of tile i is candidate r samp_row + i samp_step
     int32_t flush;                      // ... tiles behind one group of maxima
     int32_t fold;                       // ... one maximum per lane and group instead of four
@@ -116,11 +117,15 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // 0.99 ms; TransE d 128, 300 x 1M 1.03 / 0.56 ms; TransH d 56, 50 x 5.4M 2.67 / 0.91 ms; TransE d 128, 26 x 32,113 80 / 75 us.
 //
 // A split's tiles are dealt round-robin, so that neighbouring rows that all beat the threshold - a table sorted by type or
-// community - are spread over the append areas of many splits.
+// community - are spread over the append areas of many splits.  Where these are few, the tiles are walked in strides of about 0.618 of
+// the table (topk_stride), so that any stretch of the walk - a chunk, and in it the tiles of a split - holds rows from all over
+// the table: one sorted by length or popularity, too, appends about as many rows per area as a shuffled one.  (In order of the ids the first chunk is the head of the table, and
+// where that is the better part its rows beat a threshold that stands for all of it: 8,192 queries over 1M rows, d 128, lengths falling
+// from 1.5 to 0.3 262 ms, here 4.4; 2M rows, d 256, as rank^-0.2 1,560 and 7.6; shuffled 4.35 and 8.26 / 4.27 and 8.22.)
 //
 // SAMPLE: no appends; the tiles' rows are drawn from the whole table at even distances (row r of tile i is candidate
 // r samp_row + i samp_step) and every lane leaves the maxima of its rows by groups.  The KP-th largest group maximum is a value
-// that at least KP candidates reach: the threshold that the scan proper starts with, whatever the order of the rows.
+// that at least KP candidates reach: the threshold that the scan proper starts with.
 template <bool BF16, int RB, int KIND, int OB, bool TH = false, bool FN = false, bool SAMPLE = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void topk_scan_kernel(const TopkArgs a) {
@@ -147,9 +152,9 @@ void topk_scan_kernel(const TopkArgs a) {
     const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
     const int own_tile = kk % a.own_tiles, split = xcd + 8 * (kk / a.own_tiles);
     const int own_base = own_tile * (128 * NQ);
-    const int64_t ntiles = a.tile_hi - a.tile_lo;
-    const int nt = split < a.nsplit ? (int)((ntiles - split + a.nsplit - 1) / a.nsplit) : 0;     // tiles of this split
-    auto tile_of = [&](int k) { return a.tile_lo + split + (int64_t)k * a.nsplit; };
+    const int npos = a.tile_hi - a.tile_lo;
+    int nt = 0;                                         // tiles of this split
+    if (split < a.nsplit) nt = (npos - split + a.nsplit - 1) / a.nsplit;
     // Every (query, split, lane half) owns a private append area, so appending needs no atomics: the
     // count lives in a register and is stored once at the end.  Two lanes (g = 0, 1) serve one query.
     if (nt <= 0) {
@@ -239,24 +244,32 @@ void topk_scan_kernel(const TopkArgs a) {
         __syncthreads();
     }
     const bool offsets32 = a.ent_stride < (1ll << 26);  // (uniform; 32 rows x stride fits the offset)
-    const char *ld_ptr[SAMPLE ? IPW : 1];               // rows from all over the table: a pointer per copy
+    // the tiles of the split's positions, one after the other (the copies run ahead of the epilogue); below 2^27, sums below 2^28
+    auto along = [&](int tile) { return tile < a.walk ? tile : tile - a.walk; };
+    int in_tile = 0, out_tile = 0;
+    if constexpr (!SAMPLE)
+        in_tile = out_tile = along(__builtin_amdgcn_readfirstlane((int)((uint64_t)split * (uint32_t)a.stride % (uint32_t)a.walk)) + a.start);
+    const char *ld_ptr[SAMPLE ? IPW : 1];               // SAMPLE: rows from all over the table, a pointer per copy
     if constexpr (SAMPLE) {
 #pragma unroll
         for (int jj = 0; jj < IPW; ++jj) ld_ptr[jj] = a.ent + (int64_t)ld_row_of(jj, lane) * a.samp_row * a.ent_stride + ld_col_of(jj, lane);
     }
     auto issue = [&](int k, int slot) {
-        k = k < nt ? k : nt - 1;                        // past the end: a harmless repeat keeps vmcnt uniform
-        const int64_t tile = tile_of(k);
+        const bool on = k > 0 && k < nt;                // past the end: a harmless repeat keeps vmcnt uniform
         const int stage = slot % NSTAGE;
         const uint32_t lbase = lds0 + stage * TILE_BYTES + wave_u * (IPW * 1024);
-        const float *side = a.tn + (SAMPLE ? lr * a.samp_row + tile * a.samp_step : tile * TK_ST + lr);
         if constexpr (SAMPLE) {
-            const int64_t at = tile * a.samp_step * a.ent_stride;
+            const int64_t i = split + (int64_t)(k < nt ? k : nt - 1) * a.nsplit, at = i * a.samp_step * a.ent_stride;
 #pragma unroll
             for (int jj = 0; jj < IPW; ++jj)
                 asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b64 exec, -1"
                              ::"s"(lbase + jj * 1024), "v"(ld_ptr[jj] + at), "s"(ld_live[jj]) : "memory");
-        } else if (offsets32 && tile * TK_ST + TK_ST <= a.ncand) {
+            if constexpr (SIDE) async_copy4(a.tn + lr * a.samp_row + i * a.samp_step, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
+            return;
+        }
+        if (on) in_tile = along(in_tile + a.step);               // (one behind the table repeats the last row, masked in the epilogue like those of the last tile)
+        const int64_t tile = in_tile;
+        if (offsets32 && tile * TK_ST + TK_ST <= a.ncand) {
             const char *tb = a.ent + tile * TK_ST * a.ent_stride;
 #pragma unroll
             for (int jj = 0; jj < IPW; ++jj)
@@ -274,7 +287,7 @@ void topk_scan_kernel(const TopkArgs a) {
                 async_copy16(gp, lbase + jj * 1024);
             }
         }
-        if constexpr (SIDE) async_copy4(side, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
+        if constexpr (SIDE) async_copy4(a.tn + (tile < a.tiles ? tile : a.tiles - 1) * TK_ST + lr, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
     };
     // ---- A-fragment addresses: chunk (2 ks + g) of row lr sits at position chunk ^ tk_swz(lr) ----------
     // (stages and rows are whole multiples of 256 bytes, so chunk 2 b + g of a row is chunk g's address with b's bits flipped: one
@@ -453,7 +466,7 @@ void topk_scan_kernel(const TopkArgs a) {
     // One round: start the MFMAs of the next tile, then the epilogue of this one, whose accumulators the other name holds (two
     // rounds per turn of the loop, so that no accumulator is copied).
     auto round = [&](int slot, kge_f32x16 (&acc)[OB], kge_f32x16 (&accn)[OB]) {
-        const int64_t tile = tile_of(slot);
+        const int64_t tile = out_tile;
         // ---- tile + 1: wait for its data, refill the stage that tile `tile` just vacated, start its MFMAs
         // (PL: this tile's own data, split, multiplied and filtered in one round: the other workgroup of the compute unit has the
         // pipe meanwhile, and there are no registers for a second set of accumulators)
@@ -568,13 +581,15 @@ void topk_scan_kernel(const TopkArgs a) {
     };
     kge_f32x16 acc_a[OB], acc_b[OB];
     if constexpr (PL) {
-        for (int k = 0; k < nt; ++k) round(k, acc_a, acc_b);
+        for (int k = 0; k < nt; ++k, out_tile = along(out_tile + a.step)) round(k, acc_a, acc_b);
     } else {
         norms_of(0);
         mma_tile(0, acc_a);
         for (int k = 0; k < nt; k += 2) {
             round(k, acc_a, acc_b);
+            out_tile = along(out_tile + a.step);
             if (k + 1 < nt) round(k + 1, acc_b, acc_a);
+            out_tile = along(out_tile + a.step);
         }
     }
     wait_vmcnt<0>();                                    // no copy may still be in flight when the LDS is released
@@ -1306,6 +1321,29 @@ TopkStages topk_stages(const TopkPlan &p, int64_t Q, int64_t total_tiles) {
     return s;
 }
 
+// A stride of the walk over n places that are visited at p stride mod n: coprime with n, about 0.618 n, so that the visits of any stretch
+// of the walk lie at most a few times their mean distance apart, and with partial quotients of stride / n as small as a few tries find
+// (a large one would bring every q-th visit, q small, back to the same neighbourhood).
+int32_t topk_stride(int64_t n) {
+    if (n < 3) return n == 2 ? 1 : 0;
+    int64_t best = 1, best_q = INT64_MAX;
+    int64_t s = (int64_t)((double)n * 0.6180339887498949);
+    for (int tries = 0; tries < 8; ++s) {
+        if (s >= n) break;
+        int64_t a = n, b = s, most = 0;
+        while (b) {                                           // Euclid; the first and the last quotients say nothing
+            const int64_t q = a / b, r = a - q * b;
+            if (r && q > most) most = q;
+            a = b; b = r;
+        }
+        if (a != 1) continue;
+        if (most < best_q) { best = s; best_q = most; }
+        if (best_q <= 8) break;
+        ++tries;
+    }
+    return (int32_t)best;
+}
+
 struct TopkWs {
     void *Qm; float *vt, *thr, *tn; QInfo *qinfo; int32_t *cnt, *flag; uint32_t *rankcnt, *tmax; uint2 *keep, *seg; int32_t *segcnt; uint32_t *zeros;
     void *Wm; float *cq; double *qx;                    // TransH only
@@ -1408,7 +1446,7 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
 
     TopkArgs base{};
     base.Qmat = w.Qm; base.Wmat = w.Wm; base.cq = w.cq; base.ent = cand0; base.ent_stride = stride; base.valid_bytes = model.dim * p.es;
-    base.ncand = ncand; base.cand_lo = lo; base.tn = w.tn; base.tmax = w.tmax; base.thr = w.thr; base.vt = w.vt; base.true_t = true_t;
+    base.ncand = ncand; base.tn = w.tn; base.tmax = w.tmax; base.thr = w.thr; base.vt = w.vt; base.true_t = true_t;
     base.seg = w.seg; base.segcnt = w.segcnt; base.nseg = p.nseg; base.rankcnt = w.rankcnt; base.nq = (int)Q; base.zeros = w.zeros;
     const int own_tiles = p.Qp / p.own;
     const int64_t total_tiles = p.npad / TK_ST;
@@ -1424,11 +1462,22 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
                            w.thr, w.flag, (int)Q);
     };
     double reach = (double)total_tiles, growth = 1.0;
+    int64_t walk = total_tiles, stride_t = 1;
+    int most_splits = p.nseg;                                 // one split per private area
     if (total_tiles > (p.nseg * FIRST_TILES < 128 ? p.nseg * FIRST_TILES : 128)) {
         const TopkStages s = topk_stages(p, Q, total_tiles);
         growth = s.growth; reach = s.sample * s.growth;
+        // In order of the ids where the areas have room for all rows of the table that beat the first threshold, about KP / sample of
+        // them, wherever they lie (from 512 queries down as a rule: pages are walked one after the other, 128 queries x 5.7M 660 us against
+        // 681 in strides); otherwise in strides, over a number of positions that has no small factor.  Neither is dealt to the splits in the
+        // period of a table that repeats every 2^k tiles: the splits are odd in number, or the strides turn over an odd one.
+        if ((double)p.KP * total_tiles <= 24.0 * 2.0 * p.nseg * s.sample) most_splits -= most_splits % 2 == 0;
+        else {
+            while (walk % 2 == 0 || walk % 3 == 0 || walk % 5 == 0 || walk % 7 == 0) ++walk;
+            stride_t = topk_stride(walk);
+        }
         TopkArgs c = base;
-        c.tile_lo = 0; c.tile_hi = s.sample; c.own_tiles = own_tiles;
+        c.tile_lo = 0; c.tile_hi = (int32_t)s.sample; c.own_tiles = own_tiles;
         c.nsplit = s.sample < p.nseg ? (int)s.sample : p.nseg;
         c.samp_row = ncand / TK_ST; c.samp_step = c.samp_row / s.sample;      // (sample <= ncand / TK_ST: the last row is 31 samp_row + ...)
         // about 1,000 to 2,500 groups of a query in all, at most 64 of a split and lane half
@@ -1441,12 +1490,14 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
         if (rc != KGE_OK) return rc;
         compact(nullptr, c.nsplit);
     }
-    for (int64_t seen = 0; seen < total_tiles; reach *= growth) {
+    for (int64_t seen = 0; seen < walk; reach *= growth) {
         int64_t upto = (int64_t)(reach * 1.01);               // (no chunk of a few tiles at the end)
-        if (upto > total_tiles || upto <= seen) upto = total_tiles;
+        if (upto >= total_tiles || upto <= seen) upto = walk;
         TopkArgs c = base;
-        c.tile_lo = seen; c.tile_hi = upto; c.own_tiles = own_tiles;
-        c.nsplit = upto - seen < p.nseg ? (int)(upto - seen) : p.nseg;      // one split per private area
+        c.tile_lo = (int32_t)seen; c.tile_hi = (int32_t)upto; c.own_tiles = own_tiles;
+        c.nsplit = upto - seen < most_splits ? (int)(upto - seen) : most_splits;
+        c.walk = (int32_t)walk; c.tiles = (int32_t)total_tiles; c.stride = (int32_t)stride_t;
+        c.start = (int32_t)(seen * stride_t % walk); c.step = (int32_t)(c.nsplit * stride_t % walk);
         int rc;
         {
             KgeProfScope prof(KGE_PROF_TOPK_SCAN, st);

@@ -180,6 +180,49 @@ def test_neighbouring_winners_fit_an_append_area(scorer, dim, bf16, Q):
     assert times[0] < 3 * times[1], times
 
 
+@pytest.mark.parametrize("order,scorer,dim,bf16,Q,n,K", [
+    (order, *case) for case in [("distmult", 32, True, 8192, 1_000_000, 100), ("complex", 64, False, 4000, 300_000, 30)]      # 32 splits, several chunks
+    for order in ("falling", "rising", "rank", "hot head", "hot tail", "groups")] + [
+    (order, "distmult", 32, True, 1000, 1 << 20, 100) for order in ("runs", "falling", "hot head")])                         # 128 splits
+def test_order_of_the_rows_costs_nothing(scorer, dim, bf16, Q, n, K, order):
+    """Tables whose rows are sorted by length, popularity or group, or that repeat every 2^k tiles: no append area of the scan
+    overflows (where one does, the query is ranked exhaustively, some tens of times longer) and the call takes the time of
+    the same rows in another order; and the same lists either way."""
+    import torch
+    import paper_2211_12281_amd as kge
+    g = torch.Generator(device="cuda").manual_seed(5)
+    i = torch.arange(n, device="cuda")
+    length = {"falling": lambda: torch.linspace(1.5, 0.3, n, device="cuda"), "rising": lambda: torch.linspace(0.3, 1.5, n, device="cuda"),
+              "rank": lambda: (i + 1.0) ** -0.2, "hot head": lambda: torch.where(i < n // 100, 5.0, 1.0),
+              "hot tail": lambda: torch.where(i >= n - n // 100, 5.0, 1.0),
+              "runs": lambda: torch.where(i % 16384 < 32, 5.0, 1.0),
+              "groups": lambda: torch.exp2(torch.randint(-3, 3, (n // 5000 + 1,), generator=g, device="cuda").float())[i // 5000]}[order]()
+    dt = torch.bfloat16 if bf16 else torch.float32
+    table = (torch.randn((n, dim), generator=g, device="cuda") * length[:, None]).to(dt)
+    r = torch.randn((3, dim), generator=g, device="cuda").to(dt)
+    h = torch.randint(0, n, (Q,), generator=g, device="cuda", dtype=torch.int32)
+    rr = torch.randint(0, 3, (Q,), generator=g, device="cuda", dtype=torch.int32)
+    perm = torch.randperm(n, generator=g, device="cuda")
+    back = torch.empty_like(perm)
+    back[perm] = i                                         # row i of the table is row back[i] of the shuffled one
+    res, times = [], []
+    for t, heads in ((table, h), (table[perm], back[h.long()].to(torch.int32))):
+        model = kge.Model(scorer, t, r)
+        best = 1e9
+        for _ in range(3):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            idx, sc, _ = kge.topk(model, heads, rr, 0, n, K)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+        res.append((idx if t is table else perm[idx.long()].to(torch.int32), sc))
+    assert torch.equal(res[0][1], res[1][1])               # (equal scores are ordered by the table's own ids)
+    assert (res[0][0] == res[1][0]).float().mean() > 0.99
+    assert times[0] < 2.5 * times[1], times
+
+
 def test_ties_sub_ranges_and_padding(orc):
     G = make_case("distmult", 3000, 5, 32, 10, 0, False)
     for dst, src in [(1500, 3), (77, 3), (2999, 120), (10, 120), (5, 6)]:
