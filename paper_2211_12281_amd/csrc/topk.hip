@@ -44,7 +44,8 @@ struct TopkArgs {
     int32_t walk;                       // positions in all, as many as tiles or a few more: position p is tile p stride mod walk
     int32_t stride, start, step;        // start: tile of position tile_lo; step: nsplit stride mod walk
     int32_t tiles, own_tiles;           // tiles of candidates, of queries
-    int64_t samp_row, samp_step;        // kernels with SAMPLE: row r of tile i is candidate r samp_row + i samp_step
+    int32_t per;                        // kernels with SAMPLE: split s takes the tiles per s .. per (s + 1) - 1 of tile_hi, and row r of
+                                        // tile i is candidate (r tile_hi + i) stride mod ncand
     int32_t flush;                      // ... tiles behind one group of maxima
     int32_t fold;                       // ... one maximum per lane and group instead of four
     const void *zeros;                  // 16 zero bytes (source of the padding columns)
@@ -123,9 +124,10 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // where that is the better part its rows beat a threshold that stands for all of it: 8,192 queries over 1M rows, d 128, lengths falling
 // from 1.5 to 0.3 262 ms, here 4.4; 2M rows, d 256, as rank^-0.2 1,560 and 7.6; shuffled 4.35 and 8.26 / 4.27 and 8.22.)
 //
-// SAMPLE: no appends; the tiles' rows are drawn from the whole table at even distances (row r of tile i is candidate
-// r samp_row + i samp_step) and every lane leaves the maxima of its rows by groups.  The KP-th largest group maximum is a value
-// that at least KP candidates reach: the threshold that the scan proper starts with.
+// SAMPLE: no appends; the tiles' rows are drawn from the whole table in the same manner, row by row, and every lane leaves the
+// maxima of its rows by groups.  The KP-th largest group maximum is a value that at least KP candidates reach: the threshold
+// that the scan proper starts with.  (Rows at even distances see one phase of a table that repeats with a period of the
+// distance, and give a sorted table's best rows to one lane half in eight.)
 template <bool BF16, int RB, int KIND, int OB, bool TH = false, bool FN = false, bool SAMPLE = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void topk_scan_kernel(const TopkArgs a) {
@@ -154,7 +156,7 @@ void topk_scan_kernel(const TopkArgs a) {
     const int own_base = own_tile * (128 * NQ);
     const int npos = a.tile_hi - a.tile_lo;
     int nt = 0;                                         // tiles of this split
-    if (split < a.nsplit) nt = (npos - split + a.nsplit - 1) / a.nsplit;
+    if (split < a.nsplit) nt = SAMPLE ? min(a.per, npos - split * a.per) : (npos - split + a.nsplit - 1) / a.nsplit;
     // Every (query, split, lane half) owns a private append area, so appending needs no atomics: the
     // count lives in a register and is stored once at the end.  Two lanes (g = 0, 1) serve one query.
     if (nt <= 0) {
@@ -249,22 +251,32 @@ void topk_scan_kernel(const TopkArgs a) {
     int in_tile = 0, out_tile = 0;
     if constexpr (!SAMPLE)
         in_tile = out_tile = along(__builtin_amdgcn_readfirstlane((int)((uint64_t)split * (uint32_t)a.stride % (uint32_t)a.walk)) + a.start);
-    const char *ld_ptr[SAMPLE ? IPW : 1];               // SAMPLE: rows from all over the table, a pointer per copy
+    // SAMPLE: rows from all over the table, a candidate per copy (and one whose norm goes with the tile); below 2^31
+    uint32_t samp[SAMPLE ? IPW : 1], samp_side = 0;
     if constexpr (SAMPLE) {
+        auto first = [&](int row) { return (uint32_t)(((uint64_t)row * (uint32_t)a.tile_hi + (uint32_t)(split * a.per)) * (uint32_t)a.stride % (uint64_t)a.ncand); };
 #pragma unroll
-        for (int jj = 0; jj < IPW; ++jj) ld_ptr[jj] = a.ent + (int64_t)ld_row_of(jj, lane) * a.samp_row * a.ent_stride + ld_col_of(jj, lane);
+        for (int jj = 0; jj < IPW; ++jj) samp[jj] = first(ld_row_of(jj, lane));
+        if constexpr (SIDE) samp_side = first(lr);
     }
     auto issue = [&](int k, int slot) {
         const bool on = k > 0 && k < nt;                // past the end: a harmless repeat keeps vmcnt uniform
         const int stage = slot % NSTAGE;
         const uint32_t lbase = lds0 + stage * TILE_BYTES + wave_u * (IPW * 1024);
         if constexpr (SAMPLE) {
-            const int64_t i = split + (int64_t)(k < nt ? k : nt - 1) * a.nsplit, at = i * a.samp_step * a.ent_stride;
+            if (on) {
+                auto next = [&](uint32_t c) { const uint32_t x = c + (uint32_t)a.stride; return x < (uint32_t)a.ncand ? x : x - (uint32_t)a.ncand; };
 #pragma unroll
-            for (int jj = 0; jj < IPW; ++jj)
+                for (int jj = 0; jj < IPW; ++jj) samp[jj] = next(samp[jj]);
+                if constexpr (SIDE) samp_side = next(samp_side);
+            }
+#pragma unroll
+            for (int jj = 0; jj < IPW; ++jj) {
+                const char *row = a.ent + (uint64_t)samp[jj] * (uint32_t)a.ent_stride + ld_col_of(jj, lane);
                 asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b64 exec, -1"
-                             ::"s"(lbase + jj * 1024), "v"(ld_ptr[jj] + at), "s"(ld_live[jj]) : "memory");
-            if constexpr (SIDE) async_copy4(a.tn + lr * a.samp_row + i * a.samp_step, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
+                             ::"s"(lbase + jj * 1024), "v"(row), "s"(ld_live[jj]) : "memory");
+            }
+            if constexpr (SIDE) async_copy4(a.tn + samp_side, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
             return;
         }
         if (on) in_tile = along(in_tile + a.step);               // (one behind the table repeats the last row, masked in the epilogue like those of the last tile)
@@ -1479,10 +1491,11 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
         TopkArgs c = base;
         c.tile_lo = 0; c.tile_hi = (int32_t)s.sample; c.own_tiles = own_tiles;
         c.nsplit = s.sample < p.nseg ? (int)s.sample : p.nseg;
-        c.samp_row = ncand / TK_ST; c.samp_step = c.samp_row / s.sample;      // (sample <= ncand / TK_ST: the last row is 31 samp_row + ...)
+        c.stride = topk_stride(ncand);                        // (TK_ST sample <= ncand: no candidate twice)
         // about 1,000 to 2,500 groups of a query in all, at most 64 of a split and lane half
         c.fold = c.nsplit * 8 > 2500;
-        const int64_t per = (s.sample + c.nsplit - 1) / c.nsplit, each = c.fold ? 2 : 8;      // tiles of a split; groups of a split and flush
+        c.per = (int)((s.sample + c.nsplit - 1) / c.nsplit);
+        const int64_t per = c.per, each = c.fold ? 2 : 8;      // tiles of a split; groups of a split and flush
         c.flush = (int)((per * c.nsplit * each + 2047) / 2048);
         const int64_t least = (per * each / 2 + TK_HALF - 1) / TK_HALF;
         if (c.flush < least) c.flush = (int)least;

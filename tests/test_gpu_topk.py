@@ -183,11 +183,13 @@ def test_neighbouring_winners_fit_an_append_area(scorer, dim, bf16, Q):
 @pytest.mark.parametrize("order,scorer,dim,bf16,Q,n,K", [
     (order, *case) for case in [("distmult", 32, True, 8192, 1_000_000, 100), ("complex", 64, False, 4000, 300_000, 30)]      # 32 splits, several chunks
     for order in ("falling", "rising", "rank", "hot head", "hot tail", "groups")] + [
-    (order, "distmult", 32, True, 1000, 1 << 20, 100) for order in ("runs", "falling", "hot head")])                         # 128 splits
+    (order, "distmult", 32, True, 1000, 1 << 20, 100) for order in ("runs", "falling", "hot head")] + [                       # 128 splits
+    (order, "distmult", 32, True, 8192, 1 << 20, 256) for order in ("every other", "every 1,024th", "sorted")])               # ... and the sample
 def test_order_of_the_rows_costs_nothing(scorer, dim, bf16, Q, n, K, order):
     """Tables whose rows are sorted by length, popularity or group, or that repeat every 2^k tiles: no append area of the scan
     overflows (where one does, the query is ranked exhaustively, some tens of times longer) and the call takes the time of
-    the same rows in another order; and the same lists either way."""
+    the same rows in another order; and the same lists either way.  Tables that repeat with a period and tables in the order of the
+    scores: every maximum of the sample that the first threshold comes from stands for rows of all phases and of the whole table."""
     import torch
     import paper_2211_12281_amd as kge
     g = torch.Generator(device="cuda").manual_seed(5)
@@ -195,11 +197,16 @@ def test_order_of_the_rows_costs_nothing(scorer, dim, bf16, Q, n, K, order):
     length = {"falling": lambda: torch.linspace(1.5, 0.3, n, device="cuda"), "rising": lambda: torch.linspace(0.3, 1.5, n, device="cuda"),
               "rank": lambda: (i + 1.0) ** -0.2, "hot head": lambda: torch.where(i < n // 100, 5.0, 1.0),
               "hot tail": lambda: torch.where(i >= n - n // 100, 5.0, 1.0),
+              "every other": lambda: torch.where(i % 2 == 1, 1.0, 0.2), "every 1,024th": lambda: torch.where(i % 1024 == 1023, 5.0, 1.0),
+              "sorted": lambda: torch.linspace(0.01, 1.0, n, device="cuda"),
               "runs": lambda: torch.where(i % 16384 < 32, 5.0, 1.0),
               "groups": lambda: torch.exp2(torch.randint(-3, 3, (n // 5000 + 1,), generator=g, device="cuda").float())[i // 5000]}[order]()
     dt = torch.bfloat16 if bf16 else torch.float32
-    table = (torch.randn((n, dim), generator=g, device="cuda") * length[:, None]).to(dt)
-    r = torch.randn((3, dim), generator=g, device="cuda").to(dt)
+    table = torch.randn((n, dim), generator=g, device="cuda")
+    r = torch.randn((3, dim), generator=g, device="cuda")
+    if order == "sorted":                                  # (all scores positive and nearly proportional to the row's length)
+        table, r = 1.0 + 0.1 * table, r.abs()
+    table, r = (table * length[:, None]).to(dt), r.to(dt)
     h = torch.randint(0, n, (Q,), generator=g, device="cuda", dtype=torch.int32)
     rr = torch.randint(0, 3, (Q,), generator=g, device="cuda", dtype=torch.int32)
     perm = torch.randperm(n, generator=g, device="cuda")
