@@ -13,6 +13,7 @@
 //                buffer) are re-ranked by an exhaustive fp64 scan
 #include "row_ops.hpp"
 #include "block_kernel.hpp"
+#include "topk_bound.hpp"
 #include <math.h>
 
 namespace {
@@ -56,9 +57,6 @@ constexpr int tk_stages(bool bf16, int rb) { return rb == 512 ? 4 : bf16 ? 3 : 2
 // offset of the upper pieces in the sixteen bytes of four elements of row r: lanes that read eight bytes each of rows at one chunk index
 // take different banks, sixteen of them of 32 (rows r and r ^ 4, whose chunks lie 128 bytes apart) and 32 of 64 (r and r + 16)
 __device__ __forceinline__ int tk_flip(int r) { return (((r >> 2) ^ (r >> 4)) & 1) * 8; }
-// fp32 elements as two fp16 pieces, three products per pair: each is off by at most 2^-24 of either element and leaves out 2^-22 of the
-// product at most, less than eight roundings of 2^-23 of it, counted beside those of the d products
-constexpr int TK_PIECES = 8;
 // the power of two that takes a row whose largest element is m to [2^14, 2^15) (zeros and subnormal numbers as the smallest normal one)
 __device__ __forceinline__ int tk_plane_exp(float m) {
     const int e = (int)(__float_as_uint(m) >> 23);
@@ -107,7 +105,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // the bilinear scan needs only the maximum and gives each candidate tile to one of the query tiles.
 //
 // fp32 rows (PL below): the fp32 MFMA runs at 1/16 of the 16-bit rate, so every element is taken as two fp16 pieces of the row scaled by
-// a power of two of its own, and three products of pieces replace one of fp32 (a value's error is no larger: the pieces' 2^-24 is less
+// a power of two of its own, and three products of pieces replace one of fp32 (a value's error is no larger: the pieces' 2^-23 is less
 // than what the fp32 MFMAs' chain of sums adds; ranks off by 0.39-0.45 on average before and 0.36-0.45 here, the tops alike).  The
 // table is not rewritten: a tile's rows are split in the LDS, in place, by the walk that makes their norms - eight lanes per row, a
 // chunk of four elements becomes eight bytes of upper and eight of lower pieces, so no lane waits for another's reads - between two
@@ -1047,8 +1045,8 @@ __global__ __launch_bounds__(256) void topk_finish_kernel(KgeModelDev m, const i
         // Everything that was discarded has a matrix-core value <= theta (the KP-th best value, or the sample's).  Its
         // exact value is at most theta + eps; the list is safe if that stays strictly below the exact
         // value of the K-th entry.  eps bounds the rounding of the query to the table type and the
-        // fp32 accumulation:  DistMult (|dq| + d 2^-23 |q~|) Tmax;  TransE 2|dq|(|q~|+Tmax) + |dq|^2 +
-        // d 2^-22 (|q~|+Tmax)^2, with Tmax the largest candidate norm; ComplEx and RotatE are the same two forms on
+        // fp32 accumulation (units as topk_bound.hpp counts them):  DistMult (|dq| + units 2^-23 |q~|) Tmax;  TransE 2|dq|(|q~|+Tmax) +
+        // |dq|^2 + units 2^-22 (|q~|+Tmax)^2, with Tmax the largest candidate norm; ComplEx and RotatE are the same two forms on
         // their own query (h * r, h * e^{ir}), whose fp32 evaluation error is part of dq.
         const bool cut = theta > -INFINITY && ncand > KP;
         // (the pieces of an infinite element make every sum a NaN, which is in no list)
@@ -1065,7 +1063,7 @@ __global__ __launch_bounds__(256) void topk_finish_kernel(KgeModelDev m, const i
                 const double s = sqrt(qi.qn) + Tm, dq = qi.eps_a, dw = qi.eps_w, c = fabs((double)qi.c);
                 const double wn = 1.0 + dw;                                            // |w~| <= |u| + |dw|
                 const double dc = dq + 6e-8 * c;
-                const double dx = (dw + (double)(m.dim + (BF16 ? 0 : TK_PIECES)) * 1.1920929e-07 * wn) * Tm + dc;
+                const double dx = (dw + (double)topk_product_units(m.dim, BF16) * 1.1920929e-07 * wn) * Tm + dc;
                 const double xm = wn * Tm * 1.0001 + c;                                // |A~ - c| at most
                 eps = 2.0 * dq * s + dq * dq + (double)qi.eps_b * s * s               // q~ for q', fp32 sums
                       + dx * (2.0 * xm + dx) + 4.8e-7 * (xm * xm + s * s)              // x~^2 for x^2, its fp32 evaluation
@@ -1142,9 +1140,8 @@ __global__ void topk_prep_kernel(KgeModelDev m, const int32_t *h, const int32_t 
         QInfo qi;
         qi.qn = qn;
         qi.eps_a = (float)(sqrt(dq2) * 1.0001);
-        const int pieces = BF16 ? 0 : TK_PIECES;
-        qi.eps_b = mult ? (float)((d + pieces) * 1.1920929e-07 * sqrt(qn) * 1.0001)            // d 2^-23 |q~|
-                                            : (float)((d + 2 + pieces) * 2.3841858e-07);         // (d+2) 2^-22: d products and the -|t|^2 start value
+        qi.eps_b = mult ? (float)(topk_product_units(d, BF16) * 1.1920929e-07 * sqrt(qn) * 1.0001)
+                                            : (float)(topk_distance_units(d, BF16) * 2.3841858e-07);
         qi.eps_w = 0.f; qi.c = 0.f;
         qinfo[q] = qi;
         vt[q] = true_t ? (mult ? vtl : 2.f * vtl - tnl) : INFINITY;
@@ -1216,7 +1213,7 @@ __global__ void topk_prep_th_kernel(KgeModelDev m, const int32_t *h, const int32
         QInfo qi;
         qi.qn = qn;
         qi.eps_a = (float)(sqrt(dq2) * 1.0001);
-        qi.eps_b = (float)((d + 2 + (BF16 ? 0 : TK_PIECES)) * 2.3841858e-07);
+        qi.eps_b = (float)(topk_distance_units(d, BF16) * 2.3841858e-07);
         qi.eps_w = (float)(sqrt(dw2) * 1.0001);
         qi.c = c;
         qinfo[q] = qi;
