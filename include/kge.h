@@ -306,6 +306,11 @@ size_t kge_sparse_adam_static_limit(void);
  * the candidates.  Exact whenever rank <= K (it is the list position); beyond K it is counted
  * with the matrix-core scores and may differ from the fp64 rank by the number of candidates whose
  * score lies within the rounding error of the true tail's score.
+ * Arithmetic of the pre-selection (and of ranks beyond K): bf16 tables -> bf16 matrix cores with fp32 accumulation,
+ * queries rounded to bf16.  fp32 tables -> two fp16 pieces of every element, its row scaled by a power of two (each is good to
+ * 2^-23 of the element, or to 2^-40 of the row's largest where it is below 2^-16 of that), three fp16 products per fp32 one, fp32
+ * accumulation; ranks beyond K lie as close to those in 64 bits as fp32 products put them (mean distance over the five
+ * scorers, 16 to 256 dimensions, 200,000 candidates: 0.28, with fp32 products 0.31).
  * Scorers: DistMult, ComplEx, TransE, RotatE and TransH with p_norm = 2 (p_norm = 1, and TransH rows longer than
  * 512 bytes: KGE_E_UNSUPPORTED).  The rows of the entity table must start 16-byte aligned (model->ent and
  * ent_ld * sizeof(element) multiples of 16; else KGE_E_UNSUPPORTED): the scan copies them straight from the table.
