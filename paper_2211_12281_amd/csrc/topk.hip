@@ -44,6 +44,7 @@ struct TopkArgs {
     int32_t nsplit;                     // position tile_lo + i belongs to split i mod nsplit
     int32_t walk;                       // positions in all, as many as tiles or a few more: position p is tile p stride mod walk
     int32_t stride, start, step;        // start: tile of position tile_lo; step: nsplit stride mod walk
+    double ratio;                       // stride / walk (kernels with SAMPLE: stride / ncand)
     int32_t tiles, own_tiles;           // tiles of candidates, of queries
     int32_t per;                        // kernels with SAMPLE: split s takes the tiles per s .. per (s + 1) - 1 of tile_hi, and row r of
                                         // tile i is candidate (r tile_hi + i) stride mod ncand
@@ -72,6 +73,12 @@ __device__ __forceinline__ void async_copy16(const void *g, uint32_t lds_addr) {
 }
 __device__ __forceinline__ void async_copy4(const void *g, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(g) : "memory");
+}
+// u stride mod n for u, stride < n < 2^31 (ratio: stride / n): the quotient from doubles, off by one at most, in place of a 64-bit division
+__device__ __forceinline__ uint32_t topk_place(uint32_t u, uint32_t stride, uint32_t n, double ratio) {
+    int64_t r = (int64_t)((uint64_t)u * stride) - (int64_t)((uint64_t)(uint32_t)((double)u * ratio) * n);
+    r += r < 0 ? (int64_t)n : 0;
+    return (uint32_t)(r >= (int64_t)n ? r - (int64_t)n : r);
 }
 // (v > 0: bit order = value order; an old value that is read only costs an update more)
 __device__ __forceinline__ void topk_raise(uint32_t *tmax, float v) {
@@ -250,11 +257,11 @@ void topk_scan_kernel(const TopkArgs a) {
     auto along = [&](int tile) { return tile < a.walk ? tile : tile - a.walk; };
     int in_tile = 0, out_tile = 0;
     if constexpr (!SAMPLE)
-        in_tile = out_tile = along(__builtin_amdgcn_readfirstlane((int)((uint64_t)split * (uint32_t)a.stride % (uint32_t)a.walk)) + a.start);
+        in_tile = out_tile = along(__builtin_amdgcn_readfirstlane((int)topk_place(split, a.stride, a.walk, a.ratio)) + a.start);
     // SAMPLE: rows from all over the table, a candidate per copy (and one whose norm goes with the tile); below 2^31
     uint32_t samp[SAMPLE ? IPW : 1], samp_side = 0;
     if constexpr (SAMPLE) {
-        auto first = [&](int row) { return (uint32_t)(((uint64_t)row * (uint32_t)a.tile_hi + (uint32_t)(split * a.per)) * (uint32_t)a.stride % (uint64_t)a.ncand); };
+        auto first = [&](int row) { return topk_place((uint32_t)(row * a.tile_hi + split * a.per), a.stride, (uint32_t)a.ncand, a.ratio); };
 #pragma unroll
         for (int jj = 0; jj < IPW; ++jj) samp[jj] = first(ld_row_of(jj, lane));
         if constexpr (SIDE) samp_side = first(lr);
@@ -1491,6 +1498,7 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
         c.tile_lo = 0; c.tile_hi = (int32_t)s.sample; c.own_tiles = own_tiles;
         c.nsplit = s.sample < p.nseg ? (int)s.sample : p.nseg;
         c.stride = topk_stride(ncand);                        // (TK_ST sample <= ncand: no candidate twice)
+        c.ratio = (double)c.stride / (double)ncand;
         // about 1,000 to 2,500 groups of a query in all, at most 64 of a split and lane half
         c.fold = c.nsplit * 8 > 2500;
         c.per = (int)((s.sample + c.nsplit - 1) / c.nsplit);
@@ -1508,7 +1516,7 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
         TopkArgs c = base;
         c.tile_lo = (int32_t)seen; c.tile_hi = (int32_t)upto; c.own_tiles = own_tiles;
         c.nsplit = upto - seen < most_splits ? (int)(upto - seen) : most_splits;
-        c.walk = (int32_t)walk; c.tiles = (int32_t)total_tiles; c.stride = (int32_t)stride_t;
+        c.walk = (int32_t)walk; c.tiles = (int32_t)total_tiles; c.stride = (int32_t)stride_t; c.ratio = (double)stride_t / (double)walk;
         c.start = (int32_t)(seen * stride_t % walk); c.step = (int32_t)(c.nsplit * stride_t % walk);
         int rc;
         {
