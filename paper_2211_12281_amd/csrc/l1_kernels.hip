@@ -571,14 +571,18 @@ int kge_run_l1_grad(bool bf16, const float *Q, const void *T, const float *W, in
         a.bpg = (blocks + most_g - 1) / most_g; a.groups = (blocks + a.bpg - 1) / a.bpg;
         a.cps = (a.chunks + most_s - 1) / most_s;
         const int splits = (a.chunks + a.cps - 1) / a.cps;
-        // a workgroup walks bpg blocks of negatives and, for each, cps chunks of queries.  Whole calls against the two passes, us:
-        // 2 to 4 chunks 512 x 1,280 x 384 bf16 76 -> 67, 4,096 x 512 x 256 125 -> 110, 200 x 16,000 x 64 fp32 120 -> 103, 2,000 x 1,000 x 64
-        // 55 -> 56; 8 chunks 2,048 x 2,048 x 256 199 -> 185, 1,000 x 8,192 x 128 fp32 233 -> 211; 32 chunks 1,000 x 4,000 x 384 287 -> 398,
-        // 2,048 x 4,096 x 256 360 -> 422; 45 chunks 3,000 x 3,000 x 256 403 -> 552
-        if (a.bpg * a.cps <= 8) {
+        // A workgroup walks bpg blocks of negatives and, for each, cps chunks of queries: rounds that are bound by their latency, so long
+        // walks pay only where the chip is full of them.  Whole calls against the two passes, us, by rounds (workgroups): up to 3, always
+        // (243 to 1,392: 61.2 -> 59.6 to 117 -> 93; 270 and 300: 62.2 -> 61.4, 63.3 -> 63.6); 4 (165) 61 -> 70, (252) 67 -> 78, (368) 93 -> 98,
+        // (462) 77.9 -> 76.1, (476) 78.3 -> 79.7, (576) 115 -> 110, (612) 127 -> 115, (1,029) 126 -> 107; 6 (192) 66 -> 90, (352) 78 -> 91, (492) 106 ->
+        // 108, (567) 118.4 -> 117.9, (630) 118 -> 122, (704) 127 -> 118, (1,044) 186 -> 168; 8 (248) 83 -> 116, (464) 132 -> 136, (540) 121 -> 124,
+        // (684) 156 -> 151, (686) 138 -> 146, (693) 165 -> 155, (800) 160 -> 152, (1,024) 199 -> 184; 32 1,000 x 4,000 x 384 287 -> 398, 2,048 x 4,096 x
+        // 256 360 -> 422; 45 3,000 x 3,000 x 256 403 -> 552
+        const int rounds = a.bpg * a.cps;
+        const int64_t wgs = (int64_t)a.col_tiles * a.groups * splits;
+        if (rounds <= 3 || (rounds <= 8 && wgs >= (rounds == 4 ? 512 : 690))) {
             a.accq = accq; a.acct = acct;
             nsplit_q = a.groups; nsplit_t = splits;
-            const int64_t wgs = (int64_t)a.col_tiles * a.groups * splits;
             if (wgs > 0x7fffffff) return KGE_E_UNSUPPORTED;
             if (bf16) hipLaunchKernelGGL(l1_grad_both_kernel<true>, dim3((unsigned)wgs), dim3(256), 0, st, a);
             else      hipLaunchKernelGGL(l1_grad_both_kernel<false>, dim3((unsigned)wgs), dim3(256), 0, st, a);

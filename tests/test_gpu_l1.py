@@ -129,10 +129,34 @@ def test_tiles_and_their_edges(orc, dim, bf16, B, N):
     (32, False, 31, 63), (72, False, 33, 65), (144, True, 64, 16), (64, True, 1, 17),      # edges of a chunk of queries and of a wave's negatives
     (256, False, 321, 1025),                             # the last wave, the last block and the last chunk with one row each
     (136, False, 2050, 700),                             # several chunks to a split, a last split with fewer
-    (272, True, 1024, 2048), (272, True, 1100, 2048)])   # two blocks of negatives to a group, four chunks to each; the two passes
+    (336, True, 1024, 2048), (272, True, 1100, 2048),    # two blocks of negatives to a group, four chunks to each; the two passes
+    (272, True, 1024, 2048),                             # too few workgroups for eight rounds
+    (192, False, 311, 5439), (64, True, 383, 5285)])     # four rounds with enough of them, and without
 def test_both_gradients_from_one_sign(orc, dim, bf16, B, N):
     G = _grid_case("transe", 3000, 9, dim, B, N, True)   # (with ties: sign(0) = 0 on either side)
     _compare(orc, "transe", "sampled_softmax", G, bf16, 3000, dict(n_ent_for_c=3000))
+
+
+def test_half_the_columns_take_less_time():
+    """2,048 x 2,048 at 64 columns is a quarter of the workgroups of 256: a walk of eight rounds in each would take nearly the time of 128."""
+    import torch
+    import paper_2211_12281_amd as kge
+    ms = []
+    for dim in (64, 128):
+        G = _grid_case("transe", 3000, 9, dim, 2048, 2048, False)
+        model = _model("transe", G, True)
+        args = [model, "logsigmoid", dev_idx(G["h"]), dev_idx(G["r"]), dev_idx(G["t"]), dev_idx(G["neg"])]
+        ws, best = kge.Workspace(), 1e9
+        for _ in range(6):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(10):
+                kge.loss_bwd(*args, gamma=0.35 * dim, adv_temp=0.5, ws=ws)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 10)
+        ms.append(best)
+    assert ms[0] < 0.8 * ms[1], ms
 
 
 def test_regulariser_and_repeatability(orc):
