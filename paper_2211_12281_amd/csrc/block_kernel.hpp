@@ -790,8 +790,13 @@ void kge_block_kernel(const KgeBlockArgs a) {
         return fmaxf(tm, __shfl_xor(tm, 32));
     };
     // what an own row has accumulated times r.  (ALONE: in place.  As ordinary products the accumulators are vector registers here, and
-    // the compiler carries them to and from the accumulator registers in every tile: 250 of 1,280 vector instructions.  The matrix
-    // instructions that wrote them are those of the previous tile, most of an epilogue ago.)
+    // the compiler carries them to and from the accumulator registers in every tile: 250 of 1,280 vector instructions.  It counts no
+    // wait states for what inline asm reads and writes: settle() stands before the first call and behind the last.)
+    // 20 wait states are due between a matrix instruction of sixteen passes and a read of what it wrote, two between a write and a
+    // matrix instruction that reads it; the branch that rescales holds no matrix instruction.  (The last ones are most of an epilogue ago.)
+    auto settle = [] {
+        if constexpr (ALONE) { asm volatile("s_nop 15\n\ts_nop 7" ::: "memory"); __builtin_amdgcn_sched_barrier(0); }
+    };
     auto rescale = [&](kge_f32x16 &x, float r) {
         if constexpr (ALONE) {
 #pragma unroll
@@ -895,11 +900,13 @@ void kge_block_kernel(const KgeBlockArgs a) {
                     const float s_new = trip ? __uint_as_float((uint32_t)(e < 1 ? 1 : e > 254 ? 254 : e) << 23) : c_scale;
                     const float r = !trip ? 1.f : c_scale > 0.f ? s_new / c_scale : 0.f;
                     c_scale = s_new;
+                    settle();
 #pragma unroll
                     for (int b = 0; b < C::NBH; ++b) {
                         rescale(acc2[0][b], r);
                         if constexpr (TRANSH && OWN_ROW) rescale(acc2b[b], r);
                     }
+                    settle();
                 }
                 if constexpr (ALONE) {
 #pragma unroll
