@@ -712,7 +712,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) { Side4 x; side4(j, x); scores4(h, j, x, d2, Av, cancel); }
     };
-    // the scores themselves (SCORE mode stores them) and 1/distance.  Distances whose expansion cancels (below 1e-3 of the norms) are
+    // ALONE: the scores themselves and 1/distance.  Distances whose expansion cancels (below 1e-3 of the norms) are
     // redone by direct differences in a rarely taken branch.  (The line with planes: above it their errors are 0.6 to 0.9 times those of
     // 24-bit operands with norms summed in 32 bits, negatives at 0.05 and 0.1 of its length from a query; four products are no
     // better.  A line of 4e-3 gives a tenth of the error at 0.05, but tables with a common part ten to thirty times their spread take 15 to
@@ -734,23 +734,20 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 auto again = [&](int i) {
                     const int sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
                     const int b = OWN_ROW ? oidx : sidx, n = OWN_ROW ? sidx : oidx;
-                    const char *own = (const char *)(PL ? a.own32 : a.own), *str = (const char *)(PL ? a.str32 : a.str);
+                    const char *own = (const char *)a.own32, *str = (const char *)a.str32;
                     const char *qb = (OWN_ROW ? own : str) + (size_t)b * RB, *tb = (OWN_ROW ? str : own) + (size_t)n * RB;
-                    const char *wb = !TRANSH ? nullptr : PL ? (const char *)a.w32 + (size_t)b * RB : (const char *)(OWN_ROW ? a.own2 : a.str2) + (size_t)b * RB;
-                    if constexpr (BF16) return kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
-                    else return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
+                    const char *wb = TRANSH ? (const char *)a.w32 + (size_t)b * RB : nullptr;
+                    return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
                 };
-                {
-                    uint32_t todo = 0;
+                uint32_t todo = 0;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) todo |= d2[i] < line(i) ? 1u << i : 0u;
-                    while (todo) {
-                        const int i = __builtin_ctz(todo);
-                        todo &= todo - 1;
-                        const float v = again(i);
+                for (int i = 0; i < 16; ++i) todo |= d2[i] < line(i) ? 1u << i : 0u;
+                while (todo) {
+                    const int i = __builtin_ctz(todo);
+                    todo &= todo - 1;
+                    const float v = again(i);
 #pragma unroll
-                        for (int k = 0; k < 16; ++k) d2[k] = k == i ? v : d2[k];
-                    }
+                    for (int k = 0; k < 16; ++k) d2[k] = k == i ? v : d2[k];
                 }
             }
 #pragma unroll
@@ -759,15 +756,6 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 const float inv = dd > 0.f ? __builtin_amdgcn_rsqf(dd) : 0.f;
                 dv[i] = inv;
                 sv[i] = -dd * inv;                          // -sqrt(d2)
-            }
-        }
-        if constexpr (MODE == KGE_MODE_SCORE) {
-            if (oidx < a.N) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int b = sbase + 8 * (i >> 2) + (i & 3);
-                    if (b < a.B) a.S_out[(size_t)b * a.N + oidx] = sv[i];
-                }
             }
         }
     };
