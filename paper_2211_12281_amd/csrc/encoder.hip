@@ -554,12 +554,13 @@ int enc_launch_nt(EncGemmPair pr, hipStream_t st) {
 }
 
 // Tiles of 128 x 128 share most of what they read, smaller ones fill the chip where those are few.
-// bf16 (bound by the rows' latency and bytes): 64 x 64 where the large tiles leave a quarter of the compute units without one.  Whole
-// encode + encode_bwd, us, large / small tiles: 128 tiles (2,048 + 2,048 + 4,096 slots, d 256) 49.8 / 45.6, 126 (d 384) 55.7 / 50.4, 16 (1,024
-// and 3,000, d 128) 44.6 / 37.7, 192 65.8 / 65.6, 240 62.6 / 64.9, 256 64.2 / 66.3, 384 (24,576 slots, d 256) 81.7 / 84.2.
+// Whole encode + encode_bwd, us, on new slots in every pass (on the same slots again and again, their rows in the caches, small tiles look
+// better than they are).  bf16 (bound by the rows' latency and bytes): 64 x 64 while two of them to a compute unit are about
+// all there are.  128 x 128 / 64 x 64, by the number of small tiles: 251 57.9 / 52.8, 470 62.1 / 59.8, 511 52.8 / 50.0, 532 55.9 / 54.4, 536 57.3 / 56.4,
+// 558 57.4 / 57.2 (d 128: 534 65.1 / 66.8), 568 58.0 / 58.6, 57.6 / 58.1, 596 58.4 / 59.3, 664 60.1 / 61.2, 760 61.6 / 63.0, 1,536 96.4 / 102.2.
 // fp32 (bound by the matrix pipe of the fullest compute unit): 64 x 128, or 64 x 64 where that leaves it less to do.  128 x 128 / 64 x
-// 128 / 64 x 64: 24,576 slots, d 256 238 / 217 / 217; 16,384 158 / 154 / 171; 8,192 120 / 93 / 93; 1,234, d 80 87 / 60 / 48.  From 512 large
-// tiles, two of them on every unit, those: 16,384, d 400 269 / 277; 40,960, d 256 (640 tiles) 392 / 396.
+// 128 / 64 x 64: 24,576 slots, d 256 255 / 235 / 237; 16,384 169 / 166 / 184; 8,192 125 / 101 / 99; 1,234, d 80 88 / 61 / 49.  From 512 large
+// tiles, two of them on every unit, those: 16,384, d 400 288 / 302 / 300; 40,960, d 256 (640 tiles) 395 / 397 / 394.
 int enc_launch_pair(bool bf16, const EncGemm &g0, const EncGemm &g1, hipStream_t st) {
     EncGemmPair pr{};
     pr.g[0] = g0; pr.g[1] = g1;
@@ -568,9 +569,8 @@ int enc_launch_pair(bool bf16, const EncGemm &g0, const EncGemm &g1, hipStream_t
         for (const EncGemm &g : pr.g) n += (int64_t)((g.m_valid + mt - 1) / mt) * ((g.n_valid + nt - 1) / nt);
         return n;
     };
-    const int64_t large = tiles(128, 128);
-    if (bf16) return large <= 192 ? enc_launch_nt<true, 64, 64>(pr, st) : enc_launch_nt<true, 128, 128>(pr, st);
-    if (large >= 512) return enc_launch_nt<false, 128, 128>(pr, st);
+    if (bf16) return tiles(64, 64) <= 560 ? enc_launch_nt<true, 64, 64>(pr, st) : enc_launch_nt<true, 128, 128>(pr, st);
+    if (tiles(128, 128) >= 512) return enc_launch_nt<false, 128, 128>(pr, st);
     auto rounds = [&](int mt, int nt) { return (tiles(mt, nt) + 255) / 256 * mt * nt; };
     return rounds(64, 64) < rounds(64, 128) ? enc_launch_nt<false, 64, 64>(pr, st) : enc_launch_nt<false, 64, 128>(pr, st);
 }

@@ -47,7 +47,8 @@ def test_forward_matches_oracle(orc, bf16, d, fd, B, N):
 
 
 @pytest.mark.parametrize("bf16,d,fd,B,N", [
-    (True, 400, 48, 1000, 4000), (True, 400, 48, 1000, 4300),       # 192 and 200 tiles of 128 x 128: the small ones, the large ones
+    (True, 400, 48, 800, 3300), (True, 400, 48, 800, 3450),         # 546 and 560 tiles of 64 x 64: the most that are taken
+    (True, 400, 48, 1000, 4000), (True, 400, 48, 1000, 4300),       # 665 and 693: those of 128 x 128
     (False, 256, 40, 700, 6000), (False, 256, 40, 700, 8000),       # two rounds of the small tile against one and two of the wider
     (False, 400, 8, 100, 16200),                                    # 512 large tiles
     (True, 80, 16, 65, 127), (False, 72, 8, 63, 2)])                # a row more and less than a tile; one k-step alone
