@@ -84,12 +84,35 @@ def test_query_counts_around_the_scan_variants(orc, scorer, bf16, dim, Q):
     _check(orc, scorer, G, bf16, 1, n, 20, ks.uniform_ids(ks.rng(4, ks.TAG_HELDOUT), 0, n, Q))
 
 
-# few queries: the candidates in one chunk, in two and more (4,096 rows, 10 and 100 times that, and a tile more)
+# few queries: all candidates appended in one chunk and a sampled threshold (4,096 rows and one more), and larger tables
 @pytest.mark.parametrize("n", [4096, 4097, 40960, 40961, 409601])
 @pytest.mark.parametrize("K", [5, 100])
 def test_few_queries_with_fast_growing_chunks(orc, n, K):
     G = make_case("transe", n, 5, 16, 3, 0, False)
     _check(orc, "transe", G, False, 0, n, K, ks.uniform_ids(ks.rng(6, ks.TAG_HELDOUT), 0, n, 3))
+
+
+@pytest.mark.parametrize("Q,dim,bf16,K,n", [
+    (3, 16, False, 5, 16416), (3, 16, False, 5, 16417),                # one tile behind a maximum of the sample, and two
+    (3, 16, False, 5, 20000), (3, 16, False, 5, 20001),                # four maxima per lane and group, and one
+    (3, 16, False, 5, 65568), (3, 16, False, 5, 65569), (3, 16, False, 5, 131393),       # ... behind one, two and three tiles
+    (3, 16, False, 100, 1_053_900), (3, 16, False, 100, 1_054_500),    # one chunk behind the sample, and two
+    (8200, 16, True, 5, 148_500), (8200, 16, True, 5, 148_800),        # the same with 32 splits
+    (8200, 16, True, 5, 436_000), (8200, 16, True, 5, 436_800),        # two and three
+    (8200, 16, True, 5, 463_200), (8200, 16, True, 5, 463_800),        # three in order of the ids, and in strides
+    (8200, 16, True, 256, 277_300), (8200, 16, True, 256, 277_900)])   # two, the same
+def test_edges_of_the_stages(orc, Q, dim, bf16, K, n):
+    """Sizes on both sides of the lines between the forms of a call; 24 of the queries against the oracle."""
+    import paper_2211_12281_amd as kge
+    G = make_case("distmult", n, 5, dim, Q, 0, bf16)
+    true_t = ks.uniform_ids(ks.rng(6, ks.TAG_HELDOUT), 0, n, Q)
+    idx, sc, rank = (v.cpu().numpy() for v in kge.topk(gpu_model("distmult", G, bf16), dev_idx(G["h"]), dev_idx(G["r"]), 0, n, K, dev_idx(true_t)))
+    some = np.unique(np.linspace(0, Q - 1, 24).astype(int))
+    ridx, rsc, rrank = orc.topk("distmult", G["ent"], G["rel"], None, G["h"][some], G["r"][some], 0, n, K, true_t[some])
+    assert np.array_equal(idx[some], ridx)
+    assert np.max(np.abs(sc[some] - rsc)) <= RTOL_F32 * np.max(np.abs(rsc))
+    inside = rrank <= K
+    assert np.array_equal(rank[some][inside], rrank[inside]) and np.all(rank[some][~inside] > K)
 
 
 def test_clusters_of_neighbouring_rows_overflow_no_append_area():
@@ -125,8 +148,9 @@ def test_clusters_of_neighbouring_rows_overflow_no_append_area():
 
 
 def test_long_lists_of_appends(orc):
-    """Scores that rise with the id: every candidate of a chunk beats the threshold, so a query's list outgrows the LDS while
-    no append area overflows; with K = 256 and repeated rows, whose values tie at the cut."""
+    """Scores that rise with the id, K = 256 and repeated rows, whose values tie at the cut; and a million scores that rise and that fall:
+    all that beat the first threshold, some 5,000 of a query, are in one chunk - more than the compaction holds in registers, while no
+    append area overflows."""
     G = make_case("distmult", 16384, 3, 32, 5, 0, False)
     G["rel"][:] = np.abs(G["rel"]) + 0.01
     G["ent"] = np.abs(G["ent"]) * np.linspace(0.1, 3.0, 16384).astype(np.float32)[:, None]
@@ -135,6 +159,13 @@ def test_long_lists_of_appends(orc):
     G["ent"][15000:16384] = G["ent"][15000]
     _check(orc, "distmult", G, False, 0, 16384, 256, np.array([15500, 3, 9100, 16383, 0], dtype=np.int32))
     _check(orc, "distmult", G, False, 0, 9300, 200, None)
+    n = 1_000_000
+    G = make_case("distmult", n, 3, 16, 5, 0, True)
+    G["rel"] = ks.round_to_bf16(np.abs(G["rel"]) + 0.01)
+    rising = (1 + 0.1 * np.random.default_rng(1).normal(size=(n, 16))) * np.linspace(0.1, 1.0, n)[:, None]
+    for ent in (rising, rising[::-1]):
+        G["ent"] = ks.round_to_bf16(np.ascontiguousarray(ent, dtype=np.float32))
+        _check(orc, "distmult", G, True, 0, n, 256, np.array([0, n - 1, n // 2, 77, n - 300], dtype=np.int32))
 
 
 @pytest.mark.parametrize("scorer,dim,bf16,Q", [("distmult", 64, True, 200), ("transh", 64, True, 100), ("complex", 400, True, 60),
@@ -148,7 +179,7 @@ def test_neighbouring_winners_fit_an_append_area(scorer, dim, bf16, Q):
     n, hot = 400_000, 100
     g = torch.Generator(device="cuda").manual_seed(3)
     table = torch.rand((n, dim), generator=g, device="cuda") * 0.1 + 0.01
-    at = 300_013                                           # (the chunks of the scan end at 4,096 x 4^k rows)
+    at = 300_013
     table[at:at + hot] = 0.25 + 0.01 * torch.rand((hot, dim), generator=g, device="cuda")
     r = torch.zeros((3, dim), device="cuda")
     if scorer in ("distmult", "complex"):
@@ -326,13 +357,13 @@ def test_fp32_rows_of_all_sizes(orc, scorer, dim, Q, n):
 
 @pytest.mark.parametrize("scorer", ["distmult", "transe", "transh"])
 def test_fp32_rows_with_nan_and_infinity(scorer):
-    """A row with a NaN is nobody's candidate and changes no other's place; a row with an infinity sends the call to the exact ranking."""
+    """A row with a NaN is nobody's candidate and changes no other's place; rows and queries with an infinity are ranked by the exact scores:
+    plus infinity first, no place for a NaN, equal scores in order of the ids."""
     import paper_2211_12281_amd as kge
     dim, Q, n, K = 128, 70, 5000, 20
     g = np.random.default_rng(3)
     G = make_case(scorer, n, 20, dim, Q, 0, False)
     bad = np.setdiff1d(g.permutation(n)[:300], G["h"])[:40]
-    rest = np.setdiff1d(np.arange(n), bad)
     args = [dev_idx(G["h"]), dev_idx(G["r"]), 0, n, K]
     G["ent"][bad] = -G["ent"][G["h"][0]] if scorer == "distmult" else 100.0      # far from every query
     want = [x.cpu().numpy() for x in kge.topk(gpu_model(scorer, G, False), *args)[:2]]
@@ -342,12 +373,29 @@ def test_fp32_rows_with_nan_and_infinity(scorer):
     assert clean.sum() > Q // 2 and np.array_equal(got[0][clean], want[0][clean]) and np.array_equal(got[1][clean], want[1][clean])
     G["ent"][bad] = 0.0
     G["ent"][bad[0], 5] = np.inf
-    got = kge.topk(gpu_model(scorer, G, False), *args)[0].cpu().numpy()
-    if scorer != "distmult":                                                     # (infinitely far)
-        G["ent"][bad[0]] = 1e6
-        want = kge.topk(gpu_model(scorer, G, False), *args)[0].cpu().numpy()
-        assert np.array_equal(got, want)
-    assert np.isin(rest, got).any()
+    G["ent"][bad[1], 7] = -np.inf
+    G["h"][3] = bad[0]                                                           # a query with an infinity
+    got = [x.cpu().numpy() for x in kge.topk(gpu_model(scorer, G, False), dev_idx(G["h"]), *args[1:])[:2]]
+    e, q = G["ent"].astype(np.float64), G["ent"][G["h"]].astype(np.float64) * G["rel"][G["r"]]
+    finite = np.isfinite(e).all(axis=1)
+    if scorer == "distmult":
+        with np.errstate(invalid="ignore"):
+            s = q @ np.where(finite[:, None], e, 0.0).T
+            s[:, bad[0]], s[:, bad[1]] = (q * e[bad[0]]).sum(axis=1), (q * e[bad[1]]).sum(axis=1)
+            s[3] = (q[3] * e).sum(axis=1)
+        assert np.isposinf(s[:, bad[:2]]).any() and np.isneginf(s[:, bad[:2]]).any() and np.isnan(s[3]).any()
+        for k in range(Q):
+            order = np.lexsort((np.arange(n), -s[k]))
+            order = order[~np.isnan(s[k][order])][:K]
+            assert np.array_equal(got[0][k], order), k
+            assert np.array_equal(np.isinf(got[1][k]), np.isinf(s[k][order]))
+    else:                                                                        # (infinitely far: from an infinite query everything is)
+        G["ent"] = np.where(finite[:, None], G["ent"], np.float32(1e6))
+        want = kge.topk(gpu_model(scorer, G, False), dev_idx(G["h"]), *args[1:])[0].cpu().numpy()
+        rest = np.arange(Q) != 3
+        assert np.array_equal(got[0][rest], want[rest])
+        if scorer == "transe":
+            assert np.array_equal(got[0][3], np.flatnonzero(finite)[:K]) and np.isneginf(got[1][3]).all()
 
 
 def test_partition_bucketing(orc):
