@@ -77,8 +77,7 @@ constexpr int kge_block_occ(bool bf16, int rb, bool transh, int mode) {
 // The fp32 training passes read their operands as two fp16 planes [2][rows][dp] of rows scaled by a power of two of their own (kge_split2),
 // which the gather writes beside the fp32 rows; there are no transposed copies.  The fp32 matrix instruction runs at 1/16 of the 16-bit
 // rate; three products of pieces replace sixteen.  Calls in us, before / here.  Rows of 512 bytes (before: three bf16 pieces, six products):
-// TransH 8,192 x 4,096 x 128 388 / 310 (passes 211 + 201 -> 148 + 147: the epilogue and the contractions of a tile one after the other in one
-// wave per SIMD), TransE 234 / 178, ComplEx 8,000 x 3,000 x 128 229 / 154, DistMult 4,096 x 4,096 x 96 110 / 93.  Rows of 1,024 bytes (fp32
+// TransH 8,192 x 4,096 x 128 388 / 310, TransE 234 / 178, ComplEx 8,000 x 3,000 x 128 229 / 154, DistMult 4,096 x 4,096 x 96 110 / 93.  Rows of 1,024 bytes (fp32
 // instructions over the queries, bf16 pieces made in registers over the negatives): TransE 4,096 x 4,096 x 256 366 / 214, DistMult 2,048 x
 // 8,192 x 200 302 / 145, RotatE 8,192 x 2,000 x 256 384 / 228.
 // Errors against 64 bits over 120 drawn calls on rows of up to 512 bytes: 0.97-1.00 times those of before (geometric mean of every gradient),

@@ -248,8 +248,9 @@ __host__ __device__ constexpr int small_cnt_at(int f) { return f + (f >> 4); }  
 struct SmallSort { const int32_t *idx; int M, bits, lb; uint32_t *ka, *kb, *pa, *pb; };   // bits: of the largest id; lb: of the id that select the workgroup
 // the low bits that select a table's workgroup (a function of the table alone: the order of the sorted ids, and with it
 // the association order of the sums, must not depend on what else is in the launch)
-// Of 8,193 to 12,288 ids 128 parts are slower alone (12,288: 6.7 us against 6.5 with 256) and faster beside a relation table, as a step
-// plans them (TransE step 2,048 x 8,192 143.5 / 144.6, RotatE 4,096 x 4,096 147.2 / 147.4); of 20,480 slower in a step too, where all of
+// Of 8,193 to 12,288 ids 128 parts are slower alone (12,288: 6.7 us against 6.5 with 256; 10,000: 6.5 / 6.4) and faster beside relation
+// tables, as a step plans them (12,288 and 2,048 8.2 / 8.6, and twice 2,048 8.2 / 9.8, and 4,096 8.7 / 9.3; TransE step 2,048 x 8,192 143.5 /
+// 144.6, RotatE 4,096 x 4,096 147.2 / 147.4); of 20,480 slower in a step too, where all of
 // memory is cold and two workgroups per unit wait for it together (TransH 8,192 x 4,096 339.6 / 336.6).  At most 24 bits are left, for a
 // list's words.
 static int small_parts(int m, int bits) {
@@ -338,7 +339,7 @@ __device__ __forceinline__ bool small_pass_trivial(const uint32_t *sk, const uin
     return true;
 }
 
-// The place of an entry (its word: small_word) in a list of n <= SMALL_DIRECT words, no two of them alike: the words below it.  The four
+// The place of an entry (its word: (other bits of the id, place in the list), sort_small_body) in a list of n <= SMALL_DIRECT words, no two of them alike: the words below it.  The four
 // threads of an entry (tid / 4) count sixteen words a step between them and add up; all return the sum.  Words from n up to the next
 // multiple of sixteen are 0xffffffff.
 __device__ __forceinline__ int small_rank(const uint32_t *list, uint32_t word, int n) {
@@ -357,8 +358,7 @@ __device__ __forceinline__ void sort_small_body(const SmallSorts &T, const int w
     __shared__ __attribute__((aligned(16))) uint32_t s_key[2][SMALL_CAP];
     __shared__ uint32_t s_pos[2][SMALL_CAP];
     __shared__ uint32_t s_wave[SMALL_NT / 64];
-    // workgroups 0 .. nb0 - 1 take the first table, the next nb1 the second, ...: a table of up to SMALL_FEW ids is cut into
-    // 32 parts (by the low five bits), one of up to SMALL_MID into 64, a longer one into 256
+    // workgroups 0 .. nb0 - 1 take the first table, the next nb1 the second, ...: as many as small_parts cut a table into
     int first = 0, ti = SMALL_TABLES - 1;
     bool found = false;
 #pragma unroll

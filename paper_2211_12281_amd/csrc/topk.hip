@@ -119,7 +119,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // table is not rewritten: a tile's rows are split in the LDS, in place, by the walk that makes their norms - eight lanes per row, a
 // chunk of four elements becomes eight bytes of upper and eight of lower pieces, so no lane waits for another's reads - between two
 // barriers.  A tile is split, multiplied and filtered in one round while the other workgroup of the compute unit has the matrix pipe;
-// rows of 1,024 bytes keep two stages of the ring so that there is another.  Bound by what the two waves of a SIMD issue (d 256, 6,774
+// rows of 1,024 bytes keep two stages of the ring so that there is another, where there are two query tiles or more (make_plan).  Bound by what the two waves of a SIMD issue (d 256, 6,774
 // queries: vector pipe 41 %, matrix pipe 27 %, LDS 35 % of the cycles, half of it bank conflicts before tk_flip: 2.20 -> 2.15 ms).
 // Whole calls, fp32 MFMA / pieces: DistMult d 256, 6,774 x 92,000 3.95 / 2.03 ms, 128 x 1M 697 / 421 us; RotatE d 232, 391 x 963,002 2.35 /
 // 0.99 ms; TransE d 128, 300 x 1M 1.03 / 0.56 ms; TransH d 56, 50 x 5.4M 2.67 / 0.91 ms; TransE d 128, 26 x 32,113 80 / 75 us.
@@ -1298,8 +1298,10 @@ TopkPlan make_plan(const kge_model_t &m, int64_t Q, int64_t ncand, int K) {
     p.KPP = 1; while (p.KPP < p.KP) p.KPP <<= 1;
     // Splits of the candidates, each with its append areas.  Two workgroups per compute unit, so that the copies of one run beside the
     // epilogue of the other: 512 splits for one query tile on rows of 512 bytes (TransH, 128 queries, 5M candidates: 979 us, 256 splits
-    // 1,253), 256 for two (TransE, 256 queries, 1M: 456; 512 splits 525) and on wider rows, whose ring of stages leaves one workgroup
-    // the LDS of a compute unit (d 512, 128 queries, 1M: 550 / 595); about four turns of the 256 compute units above.
+    // 1,253), 256 for two (TransE, 256 queries, 1M: 456; 512 splits 525) and on wider rows: bf16, whose ring of stages leaves one workgroup
+    // the LDS of a compute unit (d 512, 128 queries, 1M: 550 / 595), and fp32, where two would fit and 512 splits are faster on large tables
+    // and slower on small ones (d 256, 256 / 512 splits: 128 queries x 4M 1,420 / 1,189, 1M 439 / 404, 300,000 193 / 194, 64 x 60,000
+    // 111 / 119, 30 x 25,000 92 / 105), but whose areas would take twice the workspace; about four turns of the 256 compute units above.
     const int tiles = p.Qp > 0 ? p.Qp / p.own : 1;
     { int w = 1024 / tiles; p.nseg = w < 32 ? 32 : tiles == 1 && p.rb == 512 ? 512 : (w > 256 ? 256 : w); }
     // Norms inside the scan (FN) or in a pass of their own.  Bilinear: always inside (one query tile's turn per candidate tile:
