@@ -44,11 +44,11 @@ struct TopkArgs {
     int32_t nsplit;                     // position tile_lo + i belongs to split i mod nsplit
     int32_t walk;                       // positions in all, as many as tiles or a few more: position p is tile p stride mod walk
     int32_t stride, start, step;        // start: tile of position tile_lo; step: nsplit stride mod walk
-    double ratio;                       // stride / walk (kernels with SAMPLE: stride / ncand)
+    double ratio;                       // stride / walk
     int32_t tiles, own_tiles;           // tiles of candidates, of queries
-    int32_t per;                        // kernels with SAMPLE: split s takes the tiles per s .. per (s + 1) - 1 of tile_hi, and row r of
-                                        // tile i is candidate (r tile_hi + i) stride mod ncand
-    int32_t flush;                      // ... tiles behind one group of maxima
+    int32_t samp_part, samp_gap;        // kernels with SAMPLE: row r is of the candidates r samp_part + r (r + 1) / 2 samp_gap + 0 .. samp_part - 1,
+    int32_t samp_w, samp_rem;           // a tile of one of tile_hi pieces of samp_w of them (the first samp_rem pieces are one longer)
+    int32_t flush;                      // ... tiles behind one group of maxima, at most
     int32_t fold;                       // ... one maximum per lane and group instead of four
     const void *zeros;                  // 16 zero bytes (source of the padding columns)
 };
@@ -131,10 +131,14 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // where that is the better part its rows beat a threshold that stands for all of it: 8,192 queries over 1M rows, d 128, lengths falling
 // from 1.5 to 0.3 262 ms, here 4.4; 2M rows, d 256, as rank^-0.2 1,560 and 7.6; shuffled 4.35 and 8.26 / 4.27 and 8.22.)
 //
-// SAMPLE: no appends; the tiles' rows are drawn from the whole table in the same manner, row by row, and every lane leaves the
-// maxima of its rows by groups.  The KP-th largest group maximum is a value that at least KP candidates reach: the threshold
-// that the scan proper starts with.  (Rows at even distances see one phase of a table that repeats with a period of the
-// distance, and give a sorted table's best rows to one lane half in eight.)
+// SAMPLE: no appends; a tile has a row of each of 32 parts of the table (topk_sample_rows), and every lane leaves the maxima of its
+// rows by groups.  The KP-th largest group maximum is a value that at least KP candidates reach: the threshold that the scan proper
+// starts with.  Every group of maxima stands for all of the table - tiles from all over it, places drawn at random within theirs, four of
+// the eight groups of a split for every part - so that about as many rows beat the threshold whatever their order (0.9 to 1.7 times
+// KP / sample of them over sorted, periodic, clustered and shuffled tables of 20,000 to 5.7M rows, and 2.5 over 8,000 sorted ones).
+// (Rows at even distances see one phase of a table that repeats with a period of the distance, and give a sorted table's best rows to one
+// group in eight.  Rows in strides of 0.618 of the table do neither, but take eight vector instructions a copy where these take two: a sample of
+// 23 queries x 378,761, d 432 23.8 us, here 21.9; fp32, 6,759 x 85,599, d 144 190 and 173.)
 template <bool BF16, int RB, int KIND, int OB, bool TH = false, bool FN = false, bool SAMPLE = false>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void topk_scan_kernel(const TopkArgs a) {
@@ -163,7 +167,7 @@ void topk_scan_kernel(const TopkArgs a) {
     const int own_base = own_tile * (128 * NQ);
     const int npos = a.tile_hi - a.tile_lo;
     int nt = 0;                                         // tiles of this split
-    if (split < a.nsplit) nt = SAMPLE ? min(a.per, npos - split * a.per) : (npos - split + a.nsplit - 1) / a.nsplit;
+    if (split < a.nsplit) nt = (npos - split + a.nsplit - 1) / a.nsplit;
     // Every (query, split, lane half) owns a private append area, so appending needs no atomics: the
     // count lives in a register and is stored once at the end.  Two lanes (g = 0, 1) serve one query.
     if (nt <= 0) {
@@ -258,32 +262,32 @@ void topk_scan_kernel(const TopkArgs a) {
     int in_tile = 0, out_tile = 0;
     if constexpr (!SAMPLE)
         in_tile = out_tile = along(__builtin_amdgcn_readfirstlane((int)topk_place(split, a.stride, a.walk, a.ratio)) + a.start);
-    // SAMPLE: rows from all over the table, a candidate per copy (and one whose norm goes with the tile); below 2^31
-    uint32_t samp[SAMPLE ? IPW : 1], samp_side = 0;
+    // SAMPLE: the split's tiles are split + nsplit x, and of `groups` groups of maxima number v takes x = v, v + groups, ...: every group has
+    // tiles from all over, and the splits, in step, are at about one place of every part of the table
+    int in_x = 0, in_group = 0;
+    const int groups = SAMPLE ? (nt + a.flush - 1) / a.flush : 0;
+    auto part_of = [&](int row) { return row * a.samp_part + row * (row + 1) / 2 * a.samp_gap; };
+    const char *ld_ptr[SAMPLE ? IPW : 1];               // rows from all over the table: a pointer per copy
     if constexpr (SAMPLE) {
-        auto first = [&](int row) { return topk_place((uint32_t)(row * a.tile_hi + split * a.per), a.stride, (uint32_t)a.ncand, a.ratio); };
 #pragma unroll
-        for (int jj = 0; jj < IPW; ++jj) samp[jj] = first(ld_row_of(jj, lane));
-        if constexpr (SIDE) samp_side = first(lr);
+        for (int jj = 0; jj < IPW; ++jj) ld_ptr[jj] = a.ent + (int64_t)part_of(ld_row_of(jj, lane)) * a.ent_stride + ld_col_of(jj, lane);
     }
     auto issue = [&](int k, int slot) {
         const bool on = k > 0 && k < nt;                // past the end: a harmless repeat keeps vmcnt uniform
         const int stage = slot % NSTAGE;
         const uint32_t lbase = lds0 + stage * TILE_BYTES + wave_u * (IPW * 1024);
         if constexpr (SAMPLE) {
-            if (on) {
-                auto next = [&](uint32_t c) { const uint32_t x = c + (uint32_t)a.stride; return x < (uint32_t)a.ncand ? x : x - (uint32_t)a.ncand; };
+            if (on && (in_x += groups) >= nt) in_x = ++in_group;
+            const uint32_t piece = (uint32_t)(split + a.nsplit * in_x), rem = (uint32_t)a.samp_rem, longer = piece < rem;
+            uint32_t h = piece * 0x9E3779B1u;           // the place in the piece, as drawn at random: all phases of a period
+            h = (h ^ h >> 16) * 0x2C1B3C6Du;
+            const uint32_t place = piece * (uint32_t)a.samp_w + (longer ? piece : rem) + __umulhi(h, (uint32_t)a.samp_w + longer);
+            const int64_t at = place * a.ent_stride;
 #pragma unroll
-                for (int jj = 0; jj < IPW; ++jj) samp[jj] = next(samp[jj]);
-                if constexpr (SIDE) samp_side = next(samp_side);
-            }
-#pragma unroll
-            for (int jj = 0; jj < IPW; ++jj) {
-                const char *row = a.ent + (uint64_t)samp[jj] * (uint32_t)a.ent_stride + ld_col_of(jj, lane);
+            for (int jj = 0; jj < IPW; ++jj)
                 asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b64 exec, -1"
-                             ::"s"(lbase + jj * 1024), "v"(row), "s"(ld_live[jj]) : "memory");
-            }
-            if constexpr (SIDE) async_copy4(a.tn + samp_side, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
+                             ::"s"(lbase + jj * 1024), "v"(ld_ptr[jj] + at), "s"(ld_live[jj]) : "memory");
+            if constexpr (SIDE) async_copy4(a.tn + part_of(lr) + place, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
             return;
         }
         if (on) in_tile = along(in_tile + a.step);               // (one behind the table repeats the last row, masked in the epilogue like those of the last tile)
@@ -479,8 +483,8 @@ void topk_scan_kernel(const TopkArgs a) {
         __syncthreads();
         issue(NSTAGE - 1, NSTAGE - 1);
     }
-    float best[SAMPLE ? NQ : 1][4];                     // running maxima of the rows 8 j + 4 g .. + 3 of the tiles of a group
-    int until = a.flush;
+    float best[SAMPLE ? NQ : 1][4];                     // running maxima of a group: tile k leaves those of its rows 8 j + 4 g .. + 3 in number j + k
+    int out_x = 0, out_group = 0;                       // SAMPLE: as in_x, in_group
     if constexpr (SAMPLE) for (int ob = 0; ob < NQ; ++ob) for (int j = 0; j < 4; ++j) best[ob][j] = -INFINITY;
     // One round: start the MFMAs of the next tile, then the epilogue of this one, whose accumulators the other name holds (two
     // rounds per turn of the loop, so that no accumulator is copied).
@@ -528,12 +532,15 @@ void topk_scan_kernel(const TopkArgs a) {
         }
         if constexpr (SAMPLE) {
 #pragma unroll
-            for (int ob = 0; ob < NQ; ++ob)
+            for (int ob = 0; ob < NQ; ++ob) {
+                float m[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    best[ob][j] = fmaxf(fmaxf(fmaxf(best[ob][j], acc[ob][4 * j]), fmaxf(acc[ob][4 * j + 1], acc[ob][4 * j + 2])), acc[ob][4 * j + 3]);
-            if (--until == 0 || slot + 1 == nt) {
-                until = a.flush;
+                    m[j] = fmaxf(fmaxf(fmaxf(best[ob][(j + 3) & 3], acc[ob][4 * j]), fmaxf(acc[ob][4 * j + 1], acc[ob][4 * j + 2])), acc[ob][4 * j + 3]);
+                for (int j = 0; j < 4; ++j) best[ob][j] = m[j];
+            }
+            if ((out_x += groups) >= nt) {
+                out_x = ++out_group;
 #pragma unroll
                 for (int ob = 0; ob < NQ; ++ob) {
                     const size_t area = ((size_t)qid[ob] * a.nseg + split) * 2 + g;
@@ -1364,6 +1371,18 @@ int32_t topk_stride(int64_t n) {
     return (int32_t)best;
 }
 
+// The sample's candidates: its rows take one of 32 parts of the table each.  The parts lie apart by gaps that grow evenly, a 32nd of the table in
+// all, so that a period of the table is at another phase in every part.
+void topk_sample_rows(int64_t ncand, int64_t sample, TopkArgs &c) {
+    constexpr int64_t GAPS = TK_ST * (TK_ST - 1) / 2;
+    int64_t gap = ncand / (TK_ST * GAPS);
+    if (gap > 1 && gap % 2 == 0) --gap;
+    if ((ncand - GAPS * gap) / TK_ST < sample) gap = 0;       // (TK_ST sample <= ncand)
+    const int64_t part = (ncand - GAPS * gap) / TK_ST;
+    c.samp_gap = (int32_t)gap; c.samp_part = (int32_t)part;
+    c.samp_w = (int32_t)(part / sample); c.samp_rem = (int32_t)(part % sample);
+}
+
 struct TopkWs {
     void *Qm; float *vt, *thr, *tn; QInfo *qinfo; int32_t *cnt, *flag; uint32_t *rankcnt, *tmax; uint2 *keep, *seg; int32_t *segcnt; uint32_t *zeros;
     void *Wm; float *cq; double *qx;                    // TransH only
@@ -1499,12 +1518,10 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
         TopkArgs c = base;
         c.tile_lo = 0; c.tile_hi = (int32_t)s.sample; c.own_tiles = own_tiles;
         c.nsplit = s.sample < p.nseg ? (int)s.sample : p.nseg;
-        c.stride = topk_stride(ncand);                        // (TK_ST sample <= ncand: no candidate twice)
-        c.ratio = (double)c.stride / (double)ncand;
+        topk_sample_rows(ncand, s.sample, c);
         // about 1,000 to 2,500 groups of a query in all, at most 64 of a split and lane half
         c.fold = c.nsplit * 8 > 2500;
-        c.per = (int)((s.sample + c.nsplit - 1) / c.nsplit);
-        const int64_t per = c.per, each = c.fold ? 2 : 8;      // tiles of a split; groups of a split and flush
+        const int64_t per = (s.sample + c.nsplit - 1) / c.nsplit, each = c.fold ? 2 : 8;      // tiles of a split; groups of a split and flush
         c.flush = (int)((per * c.nsplit * each + 2047) / 2048);
         const int64_t least = (per * each / 2 + TK_HALF - 1) / TK_HALF;
         if (c.flush < least) c.flush = (int)least;

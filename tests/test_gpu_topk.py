@@ -215,7 +215,7 @@ def test_neighbouring_winners_fit_an_append_area(scorer, dim, bf16, Q):
     (order, *case) for case in [("distmult", 32, True, 8192, 1_000_000, 100), ("complex", 64, False, 4000, 300_000, 30)]      # 32 splits, several chunks
     for order in ("falling", "rising", "rank", "hot head", "hot tail", "groups")] + [
     (order, "distmult", 32, True, 1000, 1 << 20, 100) for order in ("runs", "falling", "hot head")] + [                       # 128 splits
-    (order, "distmult", 32, True, 8192, 1 << 20, 256) for order in ("every other", "every 1,024th", "sorted")])               # ... and the sample
+    (order, "distmult", 32, True, 8192, 1 << 20, 256) for order in ("every other", "every 1,024th", "parts", "sorted")])               # ... and the sample
 def test_order_of_the_rows_costs_nothing(scorer, dim, bf16, Q, n, K, order):
     """Tables whose rows are sorted by length, popularity or group, or that repeat every 2^k tiles: no append area of the scan
     overflows (where one does, the query is ranked exhaustively, some tens of times longer) and the call takes the time of
@@ -229,6 +229,7 @@ def test_order_of_the_rows_costs_nothing(scorer, dim, bf16, Q, n, K, order):
               "rank": lambda: (i + 1.0) ** -0.2, "hot head": lambda: torch.where(i < n // 100, 5.0, 1.0),
               "hot tail": lambda: torch.where(i >= n - n // 100, 5.0, 1.0),
               "every other": lambda: torch.where(i % 2 == 1, 1.0, 0.2), "every 1,024th": lambda: torch.where(i % 1024 == 1023, 5.0, 1.0),
+              "parts": lambda: torch.where(i % (n // 32) >= n // 32 - 200, 5.0, 1.0),
               "sorted": lambda: torch.linspace(0.01, 1.0, n, device="cuda"),
               "runs": lambda: torch.where(i % 16384 < 32, 5.0, 1.0),
               "groups": lambda: torch.exp2(torch.randint(-3, 3, (n // 5000 + 1,), generator=g, device="cuda").float())[i // 5000]}[order]()
