@@ -607,10 +607,42 @@ void kge_block_kernel(const KgeBlockArgs a) {
             }
         }
     };
+    // squared distance of an entry by direct differences, from the unscaled rows
+    auto again = [&](int h, int i) {
+        const int oidx = oidx0 + 32 * h, sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
+        const int b = OWN_ROW ? oidx : sidx, n = OWN_ROW ? sidx : oidx;
+        const char *own = (const char *)(PL ? a.own32 : a.own), *str = (const char *)(PL ? a.str32 : a.str);
+        const char *qb = (OWN_ROW ? own : str) + (size_t)b * RB, *tb = (OWN_ROW ? str : own) + (size_t)n * RB;
+        const char *wb = !TRANSH ? nullptr : PL ? (const char *)a.w32 + (size_t)b * RB : (const char *)(OWN_ROW ? a.own2 : a.str2) + (size_t)b * RB;
+        if constexpr (BF16) return kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
+        else return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
+    };
+    // fp32: the entries below their line by a loop over them, in line - a call costs its caller-saved registers all through the kernel, where
+    // the pieces leave none (bf16 tables have them, and lose 0.5-1.5 % by this form)
+    auto again_of = [&](int h, float (&d2)[16], auto &&line) {
+        uint32_t todo = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) todo |= d2[i] < line(i) ? 1u << i : 0u;
+        while (todo) {
+            const int i = __builtin_ctz(todo);
+            todo &= todo - 1;
+            const float v = again(h, i);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) d2[k] = k == i ? v : d2[k];
+        }
+    };
+    auto from_squares = [&](const float (&d2)[16], float (&sv)[16], float (&dv)[16]) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float dd = fmaxf(d2[i], 0.f);
+            const float inv = dd > 0.f ? __builtin_amdgcn_rsqf(dd) : 0.f;
+            dv[i] = inv;
+            sv[i] = -dd * inv;                              // -sqrt(d2)
+        }
+    };
     // scores of own fragment h against the tile (SCORE mode stores them), 1/distance, w.t, in one piece: kernels of several waves per SIMD
     // (in the parts below, with the line of the cancellation recomputed, bf16 TransH takes 593 us a step of 8,192 x 4,096 for 527)
     auto scores = [&](int h, float (&sv)[16], float (&dv)[16], float (&Av)[16]) {
-        const int oidx = oidx0 + 32 * h;
 #pragma unroll
         for (int i = 0; i < 16; ++i) { dv[i] = 0.f; Av[i] = 0.f; }
         if constexpr (PL) {                                // (exact: powers of two)
@@ -630,55 +662,26 @@ void kge_block_kernel(const KgeBlockArgs a) {
             bool cancel = false;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int sl = 8 * (i >> 2) + 4 * g + (i & 3);
                 float qn, cc, wn, tnv;
-                if constexpr (OWN_ROW) { qn = o_qn[h]; cc = o_c[h]; wn = o_wn[h]; tnv = *(const float *)(side + sl * 4); }
-                else { float4 ri = *(const float4 *)(side + sl * 16); qn = ri.x; cc = ri.y; wn = ri.w; tnv = o_tn[h]; }
+                norms_of(h, i, qn, cc, wn, tnv);
                 d2[i] = fmaf(-2.f, acc[h][i], qn + tnv);
                 if constexpr (TRANSH) { const float A = accw[i]; Av[i] = A; d2[i] += A * (2.f * cc - A * (2.f - wn)); }
                 thr[i] = 1e-3f * (qn + tnv);
                 cancel = cancel || d2[i] < thr[i];
             }
             if (__any(cancel)) {
-                auto again = [&](int i) {
-                    const int sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
-                    const int b = OWN_ROW ? oidx : sidx, n = OWN_ROW ? sidx : oidx;
-                    const char *own = (const char *)(PL ? a.own32 : a.own), *str = (const char *)(PL ? a.str32 : a.str);
-                    const char *qb = (OWN_ROW ? own : str) + (size_t)b * RB, *tb = (OWN_ROW ? str : own) + (size_t)n * RB;
-                    const char *wb = !TRANSH ? nullptr : PL ? (const char *)a.w32 + (size_t)b * RB : (const char *)(OWN_ROW ? a.own2 : a.str2) + (size_t)b * RB;
-                    if constexpr (BF16) return kge_direct_d2<BF16, TRANSH>(qb, tb, wb, C::DP);
-                    else return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
-                };
                 if constexpr (BF16) {
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        if (d2[i] < thr[i]) d2[i] = again(i);
+                        if (d2[i] < thr[i]) d2[i] = again(h, i);
                         asm volatile("" ::: "memory");      // keeps the branch from being turned into selects
                     }
-                } else {
-                    // fp32: a loop over the lane's entries, in line - a call costs its caller-saved registers all through the kernel, where
-                    // the pieces leave none (bf16 tables have them, and lose 0.5-1.5 % by this form)
-                    uint32_t todo = 0;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) todo |= d2[i] < thr[i] ? 1u << i : 0u;
-                    while (todo) {
-                        const int i = __builtin_ctz(todo);
-                        todo &= todo - 1;
-                        const float v = again(i);
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) d2[k] = k == i ? v : d2[k];
-                    }
-                }
+                } else again_of(h, d2, [&](int i) { return thr[i]; });
             }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float dd = fmaxf(d2[i], 0.f);
-                const float inv = dd > 0.f ? __builtin_amdgcn_rsqf(dd) : 0.f;
-                dv[i] = inv;
-                sv[i] = -dd * inv;                          // -sqrt(d2)
-            }
+            from_squares(d2, sv, dv);
         }
         if constexpr (MODE == KGE_MODE_SCORE) {
+            const int oidx = oidx0 + 32 * h;
             if (oidx < a.N) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
@@ -718,7 +721,6 @@ void kge_block_kernel(const KgeBlockArgs a) {
     // better.  A line of 4e-3 gives a tenth of the error at 0.05, but tables with a common part ten to thirty times their spread take 15 to
     // 100 times as long: TransE 8,192 x 4,096 x 128 at 0.05 7.0 ms instead of 0.2)
     auto scores2 = [&](int h, float (&d2)[16], bool cancel, float (&sv)[16], float (&dv)[16]) {
-        const int oidx = oidx0 + 32 * h;
 #pragma unroll
         for (int i = 0; i < 16; ++i) dv[i] = 0.f;
         if constexpr (KIND == KGE_KIND_MULT) {
@@ -730,33 +732,8 @@ void kge_block_kernel(const KgeBlockArgs a) {
                 norms_of(h, i, qn, cc, wn, tnv);
                 return 1e-3f * (qn + tnv);
             };
-            if (__any(cancel)) {
-                auto again = [&](int i) {
-                    const int sidx = tile * C::ST + 8 * (i >> 2) + 4 * g + (i & 3);
-                    const int b = OWN_ROW ? oidx : sidx, n = OWN_ROW ? sidx : oidx;
-                    const char *own = (const char *)a.own32, *str = (const char *)a.str32;
-                    const char *qb = (OWN_ROW ? own : str) + (size_t)b * RB, *tb = (OWN_ROW ? str : own) + (size_t)n * RB;
-                    const char *wb = TRANSH ? (const char *)a.w32 + (size_t)b * RB : nullptr;
-                    return kge_direct_d2_inline<BF16, TRANSH>(qb, tb, wb, C::DP);
-                };
-                uint32_t todo = 0;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) todo |= d2[i] < line(i) ? 1u << i : 0u;
-                while (todo) {
-                    const int i = __builtin_ctz(todo);
-                    todo &= todo - 1;
-                    const float v = again(i);
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) d2[k] = k == i ? v : d2[k];
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float dd = fmaxf(d2[i], 0.f);
-                const float inv = dd > 0.f ? __builtin_amdgcn_rsqf(dd) : 0.f;
-                dv[i] = inv;
-                sv[i] = -dd * inv;                          // -sqrt(d2)
-            }
+            if (__any(cancel)) again_of(h, d2, line);
+            from_squares(d2, sv, dv);
         }
     };
     // FWD: exponents of the softmax weights of own fragment h relative to its reference st_m (log2
@@ -972,7 +949,7 @@ void kge_block_kernel(const KgeBlockArgs a) {
         // One wave per SIMD: what it issues beside the matrix instructions has to run under them.  A round takes tile t from its squared
         // distances to its coefficients; then the first contraction of tile t + 1 runs with their split into pieces, and the
         // second contraction of tile t with the first part of the epilogue of tile t + 1.  What bounds it is what a wave can issue: about 1,000
-        // vector instructions, 96 matrix instructions and 350 others per tile and wave, one in four to five cycles (vector pipe 49 %,
+        // vector instructions, 96 matrix instructions and 350 others per tile and wave, one in four to five cycles (vector pipe 44 to 50 %,
         // matrix pipe 33 % busy).  us, the parts one after the other / here: TransH 8,192 x 4,096 x 128 step 367 / 338, TransE 4,096 x
         // 4,096 x 256 169 / 162, ComplEx 171 / 165, DistMult 2,048 x 8,192 x 200 142 / 140.  (With the fragments' order left to the
         // compiler, which reads them where they are used, 359, 170, 171; the first contraction of tile t + 1 under the distances and

@@ -120,7 +120,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // chunk of four elements becomes eight bytes of upper and eight of lower pieces, so no lane waits for another's reads - between two
 // barriers.  A tile is split, multiplied and filtered in one round while the other workgroup of the compute unit has the matrix pipe;
 // rows of 1,024 bytes keep two stages of the ring so that there is another, where there are two query tiles or more (make_plan).  Bound by what the two waves of a SIMD issue (d 256, 6,774
-// queries: vector pipe 41 %, matrix pipe 27 %, LDS 35 % of the cycles, half of it bank conflicts before tk_flip: 2.20 -> 2.15 ms).
+// queries: vector pipe 38 %, matrix pipe 29 %, LDS 33 % of the cycles, a seventh of that bank conflicts, half of it before tk_flip: 2.20 -> 2.15 ms).
 // Whole calls, fp32 MFMA / pieces: DistMult d 256, 6,774 x 92,000 3.95 / 2.03 ms, 128 x 1M 697 / 421 us; RotatE d 232, 391 x 963,002 2.35 /
 // 0.99 ms; TransE d 128, 300 x 1M 1.03 / 0.56 ms; TransH d 56, 50 x 5.4M 2.67 / 0.91 ms; TransE d 128, 26 x 32,113 80 / 75 us.
 //
