@@ -14,6 +14,7 @@
 #include "row_ops.hpp"
 #include "block_kernel.hpp"
 #include "topk_bound.hpp"
+#include "topk_sample.hpp"
 #include <math.h>
 
 namespace {
@@ -46,8 +47,7 @@ struct TopkArgs {
     int32_t stride, start, step;        // start: tile of position tile_lo; step: nsplit stride mod walk
     double ratio;                       // stride / walk
     int32_t tiles, own_tiles;           // tiles of candidates, of queries
-    int32_t samp_part, samp_gap;        // kernels with SAMPLE: row r is of the candidates r samp_part + r (r + 1) / 2 samp_gap + 0 .. samp_part - 1,
-    int32_t samp_w, samp_rem;           // a tile of one of tile_hi pieces of samp_w of them (the first samp_rem pieces are one longer)
+    TopkSample samp;                    // kernels with SAMPLE: the candidates of tile_hi tiles
     int32_t flush;                      // ... tiles behind one group of maxima, at most
     int32_t fold;                       // ... one maximum per lane and group instead of four
     const void *zeros;                  // 16 zero bytes (source of the padding columns)
@@ -131,9 +131,9 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // where that is the better part its rows beat a threshold that stands for all of it: 8,192 queries over 1M rows, d 128, lengths falling
 // from 1.5 to 0.3 262 ms, here 4.4; 2M rows, d 256, as rank^-0.2 1,560 and 7.6; shuffled 4.35 and 8.26 / 4.27 and 8.22.)
 //
-// SAMPLE: no appends; a tile has a row of each of 32 parts of the table (topk_sample_rows), and every lane leaves the maxima of its
+// SAMPLE: no appends; a tile has a row of each of 32 parts of the table (topk_sample.hpp), and every lane leaves the maxima of its
 // rows by groups.  The KP-th largest group maximum is a value that at least KP candidates reach: the threshold that the scan proper
-// starts with.  Every group of maxima stands for all of the table - tiles from all over it, places drawn at random within theirs, four of
+// starts with.  Every group of maxima stands for all of the table - tiles from all over it, at changing places within their pieces, four of
 // the eight groups of a split for every part - so that about as many rows beat the threshold whatever their order (0.9 to 1.7 times
 // KP / sample of them over sorted, periodic, clustered and shuffled tables of 20,000 to 5.7M rows, and 2.5 over 8,000 sorted ones).
 // (Rows at even distances see one phase of a table that repeats with a period of the distance, and give a sorted table's best rows to one
@@ -266,11 +266,10 @@ void topk_scan_kernel(const TopkArgs a) {
     // tiles from all over, and the splits, in step, are at about one place of every part of the table
     int in_x = 0, in_group = 0;
     const int groups = SAMPLE ? (nt + a.flush - 1) / a.flush : 0;
-    auto part_of = [&](int row) { return row * a.samp_part + row * (row + 1) / 2 * a.samp_gap; };
     const char *ld_ptr[SAMPLE ? IPW : 1];               // rows from all over the table: a pointer per copy
     if constexpr (SAMPLE) {
 #pragma unroll
-        for (int jj = 0; jj < IPW; ++jj) ld_ptr[jj] = a.ent + (int64_t)part_of(ld_row_of(jj, lane)) * a.ent_stride + ld_col_of(jj, lane);
+        for (int jj = 0; jj < IPW; ++jj) ld_ptr[jj] = a.ent + (int64_t)a.samp.first(ld_row_of(jj, lane)) * a.ent_stride + ld_col_of(jj, lane);
     }
     auto issue = [&](int k, int slot) {
         const bool on = k > 0 && k < nt;                // past the end: a harmless repeat keeps vmcnt uniform
@@ -278,16 +277,13 @@ void topk_scan_kernel(const TopkArgs a) {
         const uint32_t lbase = lds0 + stage * TILE_BYTES + wave_u * (IPW * 1024);
         if constexpr (SAMPLE) {
             if (on && (in_x += groups) >= nt) in_x = ++in_group;
-            const uint32_t piece = (uint32_t)(split + a.nsplit * in_x), rem = (uint32_t)a.samp_rem, longer = piece < rem;
-            uint32_t h = piece * 0x9E3779B1u;           // the place in the piece, as drawn at random: all phases of a period
-            h = (h ^ h >> 16) * 0x2C1B3C6Du;
-            const uint32_t place = piece * (uint32_t)a.samp_w + (longer ? piece : rem) + __umulhi(h, (uint32_t)a.samp_w + longer);
+            const uint32_t place = a.samp.place((uint32_t)(split + a.nsplit * in_x));
             const int64_t at = place * a.ent_stride;
 #pragma unroll
             for (int jj = 0; jj < IPW; ++jj)
                 asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b64 exec, -1"
                              ::"s"(lbase + jj * 1024), "v"(ld_ptr[jj] + at), "s"(ld_live[jj]) : "memory");
-            if constexpr (SIDE) async_copy4(a.tn + part_of(lr) + place, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
+            if constexpr (SIDE) async_copy4(a.tn + a.samp.first(lr) + place, lds0 + NSTAGE * TILE_BYTES + ((slot % SIDE_SLOTS) * 4 + wave_u) * 256);
             return;
         }
         if (on) in_tile = along(in_tile + a.step);               // (one behind the table repeats the last row, masked in the epilogue like those of the last tile)
@@ -1371,18 +1367,6 @@ int32_t topk_stride(int64_t n) {
     return (int32_t)best;
 }
 
-// The sample's candidates: its rows take one of 32 parts of the table each.  The parts lie apart by gaps that grow evenly, a 32nd of the table in
-// all, so that a period of the table is at another phase in every part.
-void topk_sample_rows(int64_t ncand, int64_t sample, TopkArgs &c) {
-    constexpr int64_t GAPS = TK_ST * (TK_ST - 1) / 2;
-    int64_t gap = ncand / (TK_ST * GAPS);
-    if (gap > 1 && gap % 2 == 0) --gap;
-    if ((ncand - GAPS * gap) / TK_ST < sample) gap = 0;       // (TK_ST sample <= ncand)
-    const int64_t part = (ncand - GAPS * gap) / TK_ST;
-    c.samp_gap = (int32_t)gap; c.samp_part = (int32_t)part;
-    c.samp_w = (int32_t)(part / sample); c.samp_rem = (int32_t)(part % sample);
-}
-
 struct TopkWs {
     void *Qm; float *vt, *thr, *tn; QInfo *qinfo; int32_t *cnt, *flag; uint32_t *rankcnt, *tmax; uint2 *keep, *seg; int32_t *segcnt; uint32_t *zeros;
     void *Wm; float *cq; double *qx;                    // TransH only
@@ -1518,7 +1502,7 @@ int kge_run_topk(const kge_model_t &model, const int32_t *h, const int32_t *r, i
         TopkArgs c = base;
         c.tile_lo = 0; c.tile_hi = (int32_t)s.sample; c.own_tiles = own_tiles;
         c.nsplit = s.sample < p.nseg ? (int)s.sample : p.nseg;
-        topk_sample_rows(ncand, s.sample, c);
+        c.samp = topk_sample(ncand, s.sample);                // (TK_ST sample <= ncand)
         // about 1,000 to 2,500 groups of a query in all, at most 64 of a split and lane half
         c.fold = c.nsplit * 8 > 2500;
         const int64_t per = (s.sample + c.nsplit - 1) / c.nsplit, each = c.fold ? 2 : 8;      // tiles of a split; groups of a split and flush
