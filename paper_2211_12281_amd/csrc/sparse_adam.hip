@@ -231,8 +231,9 @@ __device__ __forceinline__ void adam_apply(uint32_t key, int col, float4 g, int6
 // comparison each; the ballots of the count stay for the collection, which passes over elements without own ids; (other bits, place in
 // the list) in one word makes ranking one comparison per pair; of the candidates for a hot id each wave counts four.  In a graph of
 // launches, before / here: 24,576 ids 10.1 / 8.4 us, with Zipf ids and a relation table of 4,096 13.0 / 10.4; 8,192 8.2 / 6.5; 2,048 +
-// 512 7.4 / 5.8; 20,480 Zipf ids and two tables of 8,192 16.8 / 13.8; one id 24,576 times 25.4 / 26.2.  Steps, where a third of the launch
-// is cold memory, gain 0.5-1.5 %.
+// 512 7.4 / 5.8; 20,480 Zipf ids and two tables of 8,192 16.8 / 13.8; one id 24,576 times 25.4 / 26.2 (the lane's bit
+// of a kept ballot is a 64-bit shift an element; compared again instead 25.6, but 24,576 ids 8.1 -> 8.6; a loop of its own for such lists 21.3, but every
+// other sort 1.5 to 3.5 more, for the registers that it spills).  Steps, where a third of the launch is cold memory, gain 0.5-1.5 %.
 // ---------------------------------------------------------------------------------------------
 constexpr int SMALL_MAX = 32768;
 constexpr int SMALL_CAP = 3072;                             // longest list that is ordered in LDS
